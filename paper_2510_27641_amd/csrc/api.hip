@@ -521,6 +521,8 @@ specattn_status specattn_init(void)
     if (st != SPECATTN_OK) return st;
     const specattn_status sg = attn_generic_configure();
     if (sg != SPECATTN_OK) return sg;
+    const specattn_status sm = layer_map_configure();
+    if (sm != SPECATTN_OK) return sm;
     return attn_mfma_configure();
 }
 

@@ -2,9 +2,9 @@
 //
 // 1. Similarity: S[i][j] = -(1/rows) * sum_r D_KL(A^v_j[r] || A^d_i[r]) over aligned attention rows of the two
 //    models (Eq. 4, averaged over the rows a representative data set yields).  fp32 probabilities in, fp64
-//    logarithms and sums; every (i, j) pair is cut into chunks, one workgroup per (chunk, pair) adds its
-//    terms in a fixed order, and a second small kernel adds the chunks in order - no atomics, so the result
-//    does not depend on scheduling.  ALU-bound (two fp64 logarithms per term), and small: this runs once.
+//    logarithms, products and sums.  Written as  sum p_j log p_j - sum p_j log q_i  the second sum is a contraction
+//    [draft layers x entries] . [entries x verifier layers], so every logarithm is taken once per layer instead of
+//    once per layer pair, and the products run on the fp64 matrix cores (v_mfma_f64_16x16x4).
 // 2. Alignment: the non-decreasing map f (verifier layer -> draft layer) that maximises sum_j S[f(j)][j],
 //    by the recurrence of Algorithm 3 (its "above" transition contains the other two):
 //    best[i][j] = S[i][j] + max_{k <= i} best[k][j-1], first maximum at ties.  One workgroup, thread i holds
@@ -12,112 +12,310 @@
 #include "common.h"
 
 #include <cmath>
+#include <mutex>
 
 namespace specattn {
 namespace {
 
-constexpr int KL_THREADS = 256;
-constexpr int MAP_THREADS = 1024;      // most draft layers the alignment kernel takes
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));   // layers start at any multiple of four bytes
 
-__global__ __launch_bounds__(KL_THREADS) void layer_kl_kernel(const float *__restrict__ ad, const float *__restrict__ av,
-                                                              int n, int64_t per_layer, int64_t chunk_len, int chunks,
-                                                              double *__restrict__ partial)
+constexpr int KL_WAVES = 8;
+constexpr int KL_THREADS = KL_WAVES * 64;
+constexpr int KL_WAVE_K = 64;                        // entries of a layer one wave takes per iteration
+constexpr int KL_ITER_K = KL_WAVES * KL_WAVE_K;
+constexpr int KL_TI = 32, KL_TJ = 32;                // draft and verifier layers per workgroup
+constexpr int KL_ROW = KL_WAVE_K + 2;                // doubles per staged row: rows start four banks apart
+constexpr int KL_WAVE_LDS = KL_TI * KL_ROW;          // doubles
+constexpr int KL_LDS_BYTES = (KL_WAVES * KL_WAVE_LDS + 2 * 128) * (int)sizeof(double);
+constexpr int MAP_THREADS = 1024;      // most draft layers the alignment kernel takes
+constexpr int MAP_LDS_BACK = 24576;    // back pointers kept in LDS (16 bits each); larger tables use the workspace
+
+// What stands for log(q) where there is none: a draft entry of 0 makes the divergence infinite as soon as a verifier
+// entry above 0 meets it (p >= 2^-149 leaves at least 1e155 in the sum, far beyond any finite divergence) and must not
+// disturb the sum otherwise (0 * -infinity would); negative and NaN entries likewise end as NaN.
+constexpr double LOG_OF_ZERO = -1e200, LOG_OF_INVALID = 1e290, DIVERGENCE_LIMIT = 1e100;
+
+// Natural logarithm in fp64 of a positive fp32 value, table-driven (P. T. P. Tang, "Table-driven implementation of the
+// logarithm function in IEEE floating-point arithmetic", 1990): x = 2^e z with z in [0.6875, 1.375), table entry i
+// holds 1/c and log c of the interval of z, log x = e log 2 + log c + log1p(z/c - 1) with a series of degree 8
+// (|z/c - 1| <= 2^-7: remainder below 2^-59 of it).  The intervals next to 1 have c = 1, so that values near 1 keep
+// their relative accuracy.  About 25 instructions, against more than 100 of the general fp64 logarithm.
+constexpr uint32_t LOG_OFF = 0x3fe60000u;            // upper half of 0.6875
+__device__ __forceinline__ double log_positive(float x, const f64x2 *tab)
 {
-    __shared__ double red[KL_THREADS / 64];
-    const int pair = blockIdx.y, i = pair / n, j = pair - i * n;
-    const int64_t begin = (int64_t)blockIdx.x * chunk_len;
-    const int64_t end = (begin + chunk_len) < per_layer ? (begin + chunk_len) : per_layer;
-    const float *pd = ad + (int64_t)i * per_layer, *pv = av + (int64_t)j * per_layer;
-    double acc = 0.0;
-    for (int64_t k = begin + threadIdx.x; k < end; k += KL_THREADS) {
-        const float p = pv[k], q = pd[k];
-        // 0 * log(0 / q) = 0; a draft entry of 0 under verifier mass gives +infinity through log(0)
-        if (p > 0.0f) acc += (double)p * (log((double)p) - log((double)q));
-    }
-    // fixed-order reduction: lanes of a wave by xor butterflies, then the waves in order
+    const double d = (double)x;
+    const uint32_t hi = (uint32_t)__double2hiint(d);
+    const uint32_t tmp = hi - LOG_OFF;
+    const double e = (double)((int32_t)tmp >> 20);
+    const double z = __hiloint2double((int)(hi - (tmp & 0xfff00000u)), __double2loint(d));
+    const f64x2 t = tab[(tmp >> 13) & 127u];
+    const double r = fma(z, t[0], -1.0);
+    double p = fma(r, -1.0 / 8, 1.0 / 7);
+    p = fma(p, r, -1.0 / 6);
+    p = fma(p, r, 1.0 / 5);
+    p = fma(p, r, -1.0 / 4);
+    p = fma(p, r, 1.0 / 3);
+    p = fma(p, r, -0.5);
+    p = fma(p * r, r, r);
+    return fma(e, 0.69314718055994530942, t[1]) + p;
+}
+__device__ __forceinline__ double log_draft(float q, const f64x2 *tab)
+{
+    const double l = log_positive(q, tab);
+    return q > 0.0f && q < INFINITY ? l : (q == 0.0f ? LOG_OF_ZERO : LOG_OF_INVALID);
+}
+
+// Entries k .. k+3 of a layer, zero at and beyond `end`.
+__device__ __forceinline__ f32x4u load4(const float *layer, int64_t k, int64_t end, bool live)
+{
+    f32x4u v = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (!live) return v;
+    if (k + 3 < end) return *reinterpret_cast<const f32x4u *>(layer + k);
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, 64);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+    for (int c = 0; c < 4; ++c)
+        if (k + c < end) v[c] = layer[k + c];
+    return v;
+}
+
+// Orders a wave's LDS accesses before those after it (the LDS unit serves a wave's accesses in order).
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Workgroup (chunk, draft group, verifier group): partial sums of 32 x 32 layer pairs over `iters` runs of 512 entries.
+// Every wave works on 64 entries of its own and meets the others only at the end: it takes the logarithms of its
+// draft entries into its part of LDS ([layer][entry], fp64), then goes through its verifier entries, 16 layers x 16
+// entries at a time, straight from memory: lane l holds entries 4 * (l / 16) .. + 3 of layer l % 16, which is
+// a B operand of four matrix instructions; their logarithms are the A operand of a third product whose diagonal is
+// sum p log p - taken in the same order as the other sums, so that a layer compared with itself gives exactly zero.
+// Bound by the logarithms (25 instructions each, m + n of them per entry) behind one unhidden trip to memory: 22 x 32
+// layers, 64 rows x 2048 positions (28 MB, 92 M terms) in 21 us; two general logarithms per term, one workgroup per
+// layer pair and chunk, took 329 us.
+__global__ __launch_bounds__(KL_THREADS) void layer_kl_kernel(const float *__restrict__ ad, const float *__restrict__ av, int m,
+                                                              int n, int64_t per_layer, int iters, double *__restrict__ partial)
+{
+    extern __shared__ __align__(16) double kl_lds[];
+    f64x2 *tab = reinterpret_cast<f64x2 *>(kl_lds + KL_WAVES * KL_WAVE_LDS);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int l16 = lane & 15, g = lane >> 4;
+    const int i0 = blockIdx.y * KL_TI, j0 = blockIdx.z * KL_TJ;
+    double *lq = kl_lds + wave * KL_WAVE_LDS;
+    if (tid < 128) {
+        const double lo = __hiloint2double((int)(LOG_OFF + ((uint32_t)tid << 13)), 0);
+        const double up = __hiloint2double((int)(LOG_OFF + ((uint32_t)(tid + 1) << 13)), 0);
+        const double inv = (lo == 1.0 || up == 1.0) ? 1.0 : 2.0 / (lo + up);
+        tab[tid] = (f64x2){inv, -log(inv)};
+    }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        double s = 0.0;
-        for (int w = 0; w < KL_THREADS / 64; ++w) s += red[w];
-        partial[(int64_t)pair * chunks + blockIdx.x] = s;
+    f64x4 acc[2][3];                                  // [verifier tile][draft tile 0, 1, the verifier's own logarithms]
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int t = 0; t < 3; ++t) acc[a][t] = (f64x4){0.0, 0.0, 0.0, 0.0};
+    for (int it = 0; it < iters; ++it) {
+        const int64_t k0 = ((int64_t)blockIdx.x * iters + it) * KL_ITER_K + wave * KL_WAVE_K;
+        if (k0 >= per_layer) break;                   // (uniform over the wave)
+        f32x4u q[8], p[2][4];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const int i = i0 + 4 * t + g;
+            q[t] = load4(ad + (int64_t)i * per_layer, k0 + 4 * l16, per_layer, i < m);
+        }
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const int j = j0 + 16 * a + l16;
+                p[a][s] = load4(av + (int64_t)j * per_layer, k0 + 16 * s + 4 * g, per_layer, j < n);
+            }
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            f64x2 *dst = reinterpret_cast<f64x2 *>(lq + (4 * t + g) * KL_ROW + 4 * l16);
+            dst[0] = (f64x2){log_draft(q[t][0], tab), log_draft(q[t][1], tab)};
+            dst[1] = (f64x2){log_draft(q[t][2], tab), log_draft(q[t][3], tab)};
+        }
+        wave_sync();
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            f64x2 a0[2], a1[2];
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                a0[c] = *reinterpret_cast<const f64x2 *>(lq + l16 * KL_ROW + 16 * s + 4 * g + 2 * c);
+                a1[c] = *reinterpret_cast<const f64x2 *>(lq + (16 + l16) * KL_ROW + 16 * s + 4 * g + 2 * c);
+            }
+#pragma unroll
+            for (int a = 0; a < 2; ++a) {
+                if (j0 + 16 * a >= n) continue;       // (uniform)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    // 0 * log(0 / q) = 0: entries that are not above 0 add nothing
+                    const bool some = p[a][s][c] > 0.0f;
+                    const double x = some ? (double)p[a][s][c] : 0.0;
+                    const double lp = some ? (p[a][s][c] < INFINITY ? log_positive(p[a][s][c], tab) : INFINITY) : 0.0;
+                    acc[a][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0[c >> 1][c & 1], x, acc[a][0], 0, 0, 0);
+                    acc[a][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1[c >> 1][c & 1], x, acc[a][1], 0, 0, 0);
+                    acc[a][2] = __builtin_amdgcn_mfma_f64_16x16x4f64(lp, x, acc[a][2], 0, 0, 0);
+                }
+            }
+        }
+        wave_sync();
+    }
+    // the waves' sums, in wave order.  Element (row 4 v + g, column l16) of a tile sits in register v of lane (g, l16).
+    __syncthreads();
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int t = 0; t < 3; ++t)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) lq[((a * 3 + t) * 16 + 4 * v + g) * 16 + l16] = acc[a][t][v];
+    __syncthreads();
+    for (int e = tid; e < KL_TI * KL_TJ; e += KL_THREADS) {
+        const int i = e >> 5, j = e & 31;
+        if (i0 + i >= m || j0 + j >= n) continue;
+        const int a = j >> 4, jj = j & 15;
+        double own = 0.0, cross = 0.0;
+#pragma unroll
+        for (int w = 0; w < KL_WAVES; ++w) {
+            const double *src = kl_lds + w * KL_WAVE_LDS;
+            own += src[((a * 3 + 2) * 16 + jj) * 16 + jj];
+            cross += src[((a * 3 + (i >> 4)) * 16 + (i & 15)) * 16 + jj];
+        }
+        partial[((int64_t)blockIdx.x * m + i0 + i) * n + j0 + j] = own - cross;
     }
 }
 
-__global__ void layer_kl_finish_kernel(const double *__restrict__ partial, int pairs, int chunks, double rows,
-                                       double *__restrict__ S)
+// Eight pairs per workgroup: 64 threads per pair add its chunks in a fixed order.
+__global__ __launch_bounds__(512) void layer_kl_finish_kernel(const double *__restrict__ partial, int pairs, int chunks, double rows,
+                                                              double *__restrict__ S)
 {
-    const int pair = blockIdx.x * blockDim.x + threadIdx.x;
-    if (pair >= pairs) return;
+    __shared__ double red[64][8];
+    const int pp = threadIdx.x & 7, cl = threadIdx.x >> 3;
+    const int pair = blockIdx.x * 8 + pp;
     double s = 0.0;
-    for (int c = 0; c < chunks; ++c) s += partial[(int64_t)pair * chunks + c];
-    S[pair] = -s / rows;
+    if (pair < pairs)
+        for (int c = cl; c < chunks; c += 64) s += partial[(int64_t)c * pairs + pair];
+    red[cl][pp] = s;
+    __syncthreads();
+#pragma unroll
+    for (int half = 32; half >= 1; half >>= 1) {
+        if (cl < half) red[cl][pp] += red[cl + half][pp];
+        __syncthreads();
+    }
+    if (cl == 0 && pair < pairs) {
+        s = red[0][pp];
+        S[pair] = s > DIVERGENCE_LIMIT ? -INFINITY : (s < -DIVERGENCE_LIMIT ? __longlong_as_double(0x7ff8000000000000ll) : -s / rows);
+    }
 }
 
 struct Best { double val; int idx; };
 
+// (value, index) of the lanes before, or of the lane itself where it is larger: the candidates with lower indices win
+// ties.  Lanes that a step has no source for keep what they have.
+template <int CTRL, int ROW_MASK> __device__ __forceinline__ void scan_step(Best &b)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(b.val), CTRL, ROW_MASK, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp((int)0xfff00000, __double2hiint(b.val), CTRL, ROW_MASK, 0xf, false);
+    const int ix = __builtin_amdgcn_update_dpp(0x7fffffff, b.idx, CTRL, ROW_MASK, 0xf, false);
+    const double left = __hiloint2double(hi, lo);
+    if (ix != 0x7fffffff && !(b.val > left)) { b.val = left; b.idx = ix; }
+}
+
+// One thread per draft layer.  A column is a prefix maximum inside every wave on the vector ALU and, with more than 64
+// draft layers, one over the wave totals through LDS (double-buffered: one barrier per column).  The columns of S are
+// fetched eight at a time, a block ahead; back pointers stay in LDS as long as they fit.  Bound by the serial chain of n
+// columns and n back pointers: 22 x 32 layers 12 us (67 us with ten LDS steps and a barrier each per column, 1024
+// threads whatever m).
 __global__ __launch_bounds__(MAP_THREADS) void layer_map_kernel(const double *__restrict__ S, int m, int n,
                                                                 int32_t *__restrict__ back, int32_t *__restrict__ f,
                                                                 double *__restrict__ total)
 {
-    __shared__ double sval[2][MAP_THREADS];
-    __shared__ int sidx[2][MAP_THREADS];
-    const int i = threadIdx.x;
-    // prefix maximum over the threads with the first index at ties: Hillis-Steele over (value, index) pairs;
-    // returns with the result of thread t in sval[b][t], sidx[b][t] and the buffer number b
-    auto prefix_max = [&](double v) -> int {
-        int b = 0;
-        sval[0][i] = v;
-        sidx[0][i] = i;
-        __syncthreads();
-        for (int off = 1; off < MAP_THREADS; off <<= 1) {
-            double mv = sval[b][i];
-            int mi = sidx[b][i];
-            if (i >= off) {
-                const double lv = sval[b][i - off];          // the candidates with lower indices win ties
-                if (!(mv > lv)) { mv = lv; mi = sidx[b][i - off]; }
-            }
-            sval[b ^ 1][i] = mv;
-            sidx[b ^ 1][i] = mi;
-            b ^= 1;
+    __shared__ double wval[2][MAP_THREADS / 64];
+    __shared__ int widx[2][MAP_THREADS / 64];
+    __shared__ uint16_t back_lds[MAP_LDS_BACK];
+    const int i = threadIdx.x, lane = i & 63, wave = i >> 6, waves = blockDim.x >> 6;
+    const bool in_lds = (int64_t)m * n <= MAP_LDS_BACK;
+    int turn = 0;
+    // prefix maximum over the threads with the first index at ties; with more than one wave a barrier
+    auto prefix_max = [&](double v) -> Best {
+        Best b = {v, i};
+        scan_step<0x111, 0xf>(b);     // row_shr:1
+        scan_step<0x112, 0xf>(b);     // row_shr:2
+        scan_step<0x114, 0xf>(b);     // row_shr:4
+        scan_step<0x118, 0xf>(b);     // row_shr:8
+        scan_step<0x142, 0xa>(b);     // row_bcast:15 into rows 1 and 3
+        scan_step<0x143, 0xc>(b);     // row_bcast:31 into rows 2 and 3
+        if (waves > 1) {
+            if (lane == 63) { wval[turn][wave] = b.val; widx[turn][wave] = b.idx; }
             __syncthreads();
+            for (int w = wave - 1; w >= 0; --w)
+                if (!(b.val > wval[turn][w])) { b.val = wval[turn][w]; b.idx = widx[turn][w]; }
+            turn ^= 1;
         }
         return b;
     };
-    double best = i < m ? S[(int64_t)i * n] : -INFINITY;       // column 0; threads past m never win a maximum
-    for (int j = 1; j < n; ++j) {
-        const int b = prefix_max(best);
-        if (i < m) {
-            const int k = sidx[b][i];
-            back[(int64_t)i * n + j] = k;
-            best = S[(int64_t)i * n + j] + sval[b][i];
+    constexpr int AHEAD = 8;
+    const double *row = S + (int64_t)(i < m ? i : m - 1) * n;
+    double cur[AHEAD], nxt[AHEAD];
+#pragma unroll
+    for (int c = 0; c < AHEAD; ++c) cur[c] = row[c < n ? c : n - 1];
+    double best = -INFINITY;                                   // threads past m never win a maximum
+    for (int j0 = 0; j0 < n; j0 += AHEAD) {
+#pragma unroll
+        for (int c = 0; c < AHEAD; ++c) nxt[c] = row[j0 + AHEAD + c < n ? j0 + AHEAD + c : n - 1];
+#pragma unroll
+        for (int c = 0; c < AHEAD; ++c) {
+            const int j = j0 + c;
+            if (j >= n) break;                                 // (uniform)
+            if (j == 0) {
+                if (i < m) best = cur[c];
+                continue;
+            }
+            const Best b = prefix_max(best);
+            if (i < m) {
+                if (in_lds) back_lds[i * n + j] = (uint16_t)b.idx;
+                else back[(int64_t)i * n + j] = b.idx;
+                best = cur[c] + b.val;
+            }
         }
-        __syncthreads();                                       // everyone has read the scan result
+#pragma unroll
+        for (int c = 0; c < AHEAD; ++c) cur[c] = nxt[c];
     }
-    const int b = prefix_max(best);
+    const Best last = prefix_max(best);
+    __shared__ int start;
+    if (i == (int)blockDim.x - 1) {
+        start = last.idx < m ? last.idx : 0;                   // first maximum of the last column (all entries -infinity or NaN: layer 0)
+        *total = last.val;
+    }
+    __syncthreads();                                           // also orders the back pointers
     if (i == 0) {
-        int at = sidx[b][MAP_THREADS - 1];                     // first maximum of the last column
-        at = at < m ? at : 0;                                  // all entries -infinity or NaN: layer 0
-        *total = sval[b][MAP_THREADS - 1];
+        int at = start;
         f[n - 1] = at;
-        __threadfence_block();
         for (int j = n - 1; j > 0; --j) {
-            at = __hip_atomic_load(&back[(int64_t)at * n + j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            at = in_lds ? back_lds[at * n + j] : __hip_atomic_load(&back[(int64_t)at * n + j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             f[j - 1] = at;
         }
     }
 }
 
-int kl_chunks(int pairs, int64_t per_layer)
+// Runs of 512 entries per workgroup, and workgroups along the entries: one workgroup per CU (its LDS allows no second) as
+// soon as there are that many runs.
+struct KlPlan { int iters, chunks, gi, gj; };
+KlPlan kl_plan(int m, int n, int64_t per_layer)
 {
-    // enough workgroups to fill the chip, chunks of at least 4096 terms
-    int64_t want = (4 * (int64_t)cu_count() + pairs - 1) / pairs;
-    const int64_t most = (per_layer + 4095) / 4096;
-    if (want > most) want = most;
-    if (want > 1024) want = 1024;
-    return want < 1 ? 1 : (int)want;
+    KlPlan p;
+    p.gi = (m + KL_TI - 1) / KL_TI;
+    p.gj = (n + KL_TJ - 1) / KL_TJ;
+    const int64_t runs = (per_layer + KL_ITER_K - 1) / KL_ITER_K;
+    int64_t want = cu_count() / ((int64_t)p.gi * p.gj);
+    want = want < 1 ? 1 : want;
+    p.iters = (int)((runs + want - 1) / want);
+    p.chunks = (int)((runs + p.iters - 1) / p.iters);
+    return p;
 }
 
 bool bad_dims(int m, int n, int rows, int L)
@@ -126,6 +324,30 @@ bool bad_dims(int m, int n, int rows, int L)
 }
 
 }  // namespace
+
+// The similarity kernel's LDS size, set once per device.
+specattn_status layer_map_configure()
+{
+    constexpr int MAX_DEVICES = 64;
+    static std::mutex mu;
+    static bool done[MAX_DEVICES] = {false};
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEVICES) {
+        (void)hipGetLastError();
+        set_error("no current device");
+        return SPECATTN_EHIP;
+    }
+    std::lock_guard<std::mutex> lock(mu);
+    if (done[dev]) return SPECATTN_OK;
+    if (hipFuncSetAttribute(reinterpret_cast<const void *>(&layer_kl_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, KL_LDS_BYTES) != hipSuccess) {
+        (void)hipGetLastError();
+        set_error("cannot reserve %d bytes of LDS", KL_LDS_BYTES);
+        return SPECATTN_EHIP;
+    }
+    done[dev] = true;
+    return SPECATTN_OK;
+}
+
 }  // namespace specattn
 
 using namespace specattn;
@@ -135,7 +357,7 @@ extern "C" {
 size_t specattn_layer_similarity_workspace_size(int32_t m, int32_t n, int32_t rows, int32_t L)
 {
     if (bad_dims(m, n, rows, L)) return 0;
-    const size_t bytes = (size_t)m * n * kl_chunks(m * n, (int64_t)rows * L) * sizeof(double);
+    const size_t bytes = (size_t)m * n * kl_plan(m, n, (int64_t)rows * L).chunks * sizeof(double);
     return (bytes + 255) & ~(size_t)255;
 }
 
@@ -153,15 +375,16 @@ specattn_status specattn_layer_similarity(const float *attn_draft, const float *
     if (workspace_bytes < need) { set_error("workspace has %zu bytes, %zu needed", workspace_bytes, need); return SPECATTN_EWORKSPACE; }
     const int pairs = m * n;
     const int64_t per_layer = (int64_t)rows * L;
-    const int chunks = kl_chunks(pairs, per_layer);
-    const int64_t chunk_len = (per_layer + chunks - 1) / chunks;
+    const KlPlan plan = kl_plan(m, n, per_layer);
+    specattn_status st = layer_map_configure();
+    if (st != SPECATTN_OK) return st;
     hipStream_t hs = static_cast<hipStream_t>(stream);
     double *partial = static_cast<double *>(workspace);
-    hipLaunchKernelGGL(layer_kl_kernel, dim3(chunks, pairs), dim3(KL_THREADS), 0, hs, attn_draft, attn_verifier, n, per_layer,
-                       chunk_len, chunks, partial);
-    specattn_status st = check_launch("layer_kl_kernel");
+    hipLaunchKernelGGL(layer_kl_kernel, dim3(plan.chunks, plan.gi, plan.gj), dim3(KL_THREADS), KL_LDS_BYTES, hs, attn_draft, attn_verifier,
+                       m, n, per_layer, plan.iters, partial);
+    st = check_launch("layer_kl_kernel");
     if (st != SPECATTN_OK) return st;
-    hipLaunchKernelGGL(layer_kl_finish_kernel, dim3((pairs + 255) / 256), dim3(256), 0, hs, partial, pairs, chunks, (double)rows, S);
+    hipLaunchKernelGGL(layer_kl_finish_kernel, dim3((pairs + 7) / 8), dim3(512), 0, hs, partial, pairs, plan.chunks, (double)rows, S);
     return check_launch("layer_kl_finish_kernel");
 }
 
@@ -182,7 +405,7 @@ specattn_status specattn_layer_map(const double *S, int32_t m, int32_t n, int32_
     if (!workspace) { set_error("workspace is NULL, %zu bytes needed", need); return SPECATTN_EWORKSPACE; }
     if (reinterpret_cast<uintptr_t>(workspace) % 256) { set_error("workspace must be 256-byte aligned"); return SPECATTN_EWORKSPACE; }
     if (workspace_bytes < need) { set_error("workspace has %zu bytes, %zu needed", workspace_bytes, need); return SPECATTN_EWORKSPACE; }
-    hipLaunchKernelGGL(layer_map_kernel, dim3(1), dim3(MAP_THREADS), 0, static_cast<hipStream_t>(stream), S, m, n,
+    hipLaunchKernelGGL(layer_map_kernel, dim3(1), dim3((m + 63) / 64 * 64), 0, static_cast<hipStream_t>(stream), S, m, n,
                        static_cast<int32_t *>(workspace), f, total);
     return check_launch("layer_map_kernel");
 }

@@ -63,6 +63,31 @@ def test_similarity_zeros_and_minus_infinity():
     assert rng is not None
 
 
+@pytest.mark.parametrize("m,n,rows,L", [(16, 16, 1, 63), (17, 15, 1, 64), (33, 31, 1, 65), (32, 33, 1, 511), (31, 65, 3, 171),
+                                        (1, 32, 1, 4611), (3, 2, 1, 131072 * 2 + 512 * 3 + 1)])
+def test_similarity_tile_edges(m, n, rows, L):
+    """Layers around the 16- and 32-wide tiles, entries around a wave's 64 and a workgroup's 512, several runs per
+    workgroup (more than 512 entries per CU); values over the whole fp32 range, subnormals and ones among them."""
+    rng = np.random.default_rng(m * 100 + n)
+    ad = np.exp(rng.uniform(-100, 0, size=(m, rows, L))).astype(np.float32)
+    av = np.exp(rng.uniform(-100, 0, size=(n, rows, L))).astype(np.float32)
+    ad[:, 0, ::7] = 1.0
+    av[:, 0, 1::5] = np.float32(1.0) - np.float32(2.0 ** -24)
+    av[:, 0, ::11] = 0.0
+    ad[:, :, -1] = np.float32(1e-40)
+    close(gpu_similarity(ad, av), oracle.layer_similarity_fast(ad, av))
+
+
+@pytest.mark.parametrize("m,n", [(63, 20), (65, 33), (128, 200), (129, 7), (1000, 30), (2, 12289), (22, 8), (22, 9)])
+def test_alignment_scan_edges(m, n):
+    """Draft layers around one wave and several, columns around a block of eight, back pointers in LDS and in memory."""
+    rng = np.random.default_rng(m * 7 + n)
+    S = np.round(rng.normal(size=(m, n)) * 3) / 2
+    f_ref, v_ref = oracle.layer_map(S)
+    f, v = gpu_map(S)
+    assert v == v_ref and np.array_equal(f, f_ref)
+
+
 def test_layers_compared_with_themselves():
     ad, _ = W.layer_attention_maps(seed=9, m=5, n=5, rows=4, L=128)
     S = gpu_similarity(ad, ad)
