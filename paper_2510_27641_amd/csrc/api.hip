@@ -96,7 +96,7 @@ specattn_status check_attn(const specattn_attn_args *a, bool fused)
         // more than 64 query rows per kv head only fit the matrix-core route (the portable kernel's tables hold 64)
         AttnLaunch probe{};
         probe.dtype = (int)a->dtype; probe.d = a->d; probe.T = a->T; probe.H_kv = a->H_kv;
-        if ((a->H_q / a->H_kv) * a->T > 64 && !attn_mfma_supported(probe)) { set_error("G*T exceeds 64 query rows per kv head (only bf16 / fp16 with d = 128 and H_kv <= %d take more)", ATTN_MFMA_MAX_ROWS); return SPECATTN_ESHAPE; }
+        if ((a->H_q / a->H_kv) * a->T > 64 && !attn_mfma_supported(probe)) { set_error("G*T exceeds 64 query rows per kv head (only bf16 / fp16 with H_kv <= %d take more)", ATTN_MFMA_MAX_ROWS); return SPECATTN_ESHAPE; }
     }
     if (!fused && !dense && a->idx_capacity < 1) { set_error("idx_capacity must be at least 1"); return SPECATTN_ESHAPE; }
     if (!fused && !dense && a->idx_stride_row < a->idx_capacity) { set_error("idx_stride_row is smaller than idx_capacity"); return SPECATTN_ESHAPE; }
@@ -137,7 +137,7 @@ bool fused_on_chip(const specattn_select_args *s, const specattn_attn_args *a)
 {
     AttnLaunch probe{};
     probe.dtype = (int)a->dtype; probe.d = a->d; probe.T = a->T; probe.H_kv = a->H_kv;
-    return attn_mfma_supported(probe) && s->chunk_size <= 1;
+    return attn_mfma_supported(probe) && a->d == 128 && s->chunk_size <= 1;
 }
 size_t a256(size_t x) { return (x + 255) & ~(size_t)255; }
 

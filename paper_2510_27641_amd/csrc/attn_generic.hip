@@ -281,11 +281,9 @@ static size_t workspace_bytes(int rows, int G, int T, int d, int idx_capacity, b
     const size_t qt = (size_t)G * T;
     size_t bytes = (size_t)rows * ns * qt * (size_t)(d + 2) * sizeof(float);
     bytes = (bytes + 255) & ~(size_t)255;
-    if (d == 128) {                                  // the matrix-core variant may take this shape (larger groups of
-        const size_t other = least ? attn_mfma_workspace_min_bytes(rows, G, T)   // query heads run as several launches over it)
-                                   : attn_mfma_workspace_bytes(rows, G, T);
-        if (other > bytes) bytes = other;
-    }
+    // the matrix-core variant may take this shape (the size does not depend on the element type)
+    const size_t other = least ? attn_mfma_workspace_min_bytes(rows, G, T, d) : attn_mfma_workspace_bytes(rows, G, T, d);
+    if (other > bytes) bytes = other;
     return bytes;
 }
 size_t attn_workspace_bytes(int rows, int G, int T, int d, int idx_capacity) { return workspace_bytes(rows, G, T, d, idx_capacity, false); }

@@ -245,7 +245,7 @@ specattn_status launch_check_lists(const AttnLaunch &a, int64_t pool_slots, int3
 specattn_status launch_csr(const int32_t *indices, int64_t idx_stride, const int32_t *counts, int rows, int capacity,
                            int64_t *indptr, int32_t *packed, hipStream_t stream);
 
-// matrix-core variant (bf16 / fp16, d = 128)
+// matrix-core variant (bf16 / fp16, d = 128 or 64)
 constexpr int ATTN_MFMA_WAVES = 8;        // waves per workgroup (one workgroup per CU: two workgroups of four waves
                                           // do not share a CU's memory pipeline evenly - the one dispatched later
                                           // issues its gathers only when the earlier one's waves are waiting)
@@ -255,8 +255,12 @@ bool attn_mfma_supported(const AttnLaunch &a);
 specattn_status attn_mfma_configure();    // one-time kernel attributes on the current device
 specattn_status attn_generic_configure(); // the same for the fp32-ALU variants
 specattn_status layer_map_configure();    // and for the layer similarity
-size_t attn_mfma_workspace_bytes(int rows, int G, int T);       // what lets every launch take as many rows as it can
-size_t attn_mfma_workspace_min_bytes(int rows, int G, int T);   // the least a call runs with
+size_t attn_mfma_workspace_bytes(int rows, int G, int T, int d);       // what lets every launch take as many rows as it can
+size_t attn_mfma_workspace_min_bytes(int rows, int G, int T, int d);   // the least a call runs with
+// kernel variants by query tiles (1 .. 4), layout and element type; null where none is built
+const void *attn_mfma_list_128(int nqt, int layout, bool f16);
+const void *attn_mfma_mask_128(int nqt, int layout, bool f16);
+const void *attn_mfma_list_64(int nqt, int layout, bool f16);
 specattn_status launch_attn_mfma(const AttnLaunch &a, hipStream_t stream);
 
 }  // namespace specattn

@@ -1,0 +1,96 @@
+"""One to four tiles of 16 query rows per kv head in one launch, and 64-wide heads, on the matrix-core kernel, at the
+sizes where tiles begin and end.
+
+Bounds: 128-wide heads as everywhere (2e-3; the bf16 weights carry 16 bits).  64-wide heads hand their weights over
+with 22 bits (fp16) or 24 (bf16), so what is left is the fp32 accumulation over at most a few thousand terms, the bound
+of the fp32 route (1e-5)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from helpers import TOL, dev, gpu_attention, kv_tensors, oracle_attention, row_rel_err
+from paper_2510_27641_amd import binding as sa
+from paper_2510_27641_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def lists(mask):
+    B, H, n = mask.shape
+    idx = np.zeros((B * H, n), dtype=np.int32)
+    cnt = np.zeros(B * H, dtype=np.int32)
+    for r, m in enumerate(mask.reshape(B * H, n)):
+        at = np.flatnonzero(m)
+        idx[r, :at.size], cnt[r] = at, at.size
+    return dev(idx), dev(cnt)
+
+
+def tol(w):
+    return TOL["f32"] if w.d == 64 else TOL[w.dtype]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G,T", [(1, 1), (2, 8), (17, 1), (4, 8), (11, 3), (8, 6), (7, 7), (8, 8), (13, 5), (16, 8)])
+def test_query_rows_around_the_tiles(d, G, T, dtype):
+    # 1, 16, 17, 32, 33, 48, 49 and 64 query rows in one launch; 65 and 128 in two shares of heads
+    w = W.llama8b_layer(seed=G * T, B=2, n=900, H_q=2 * G, H_kv=2, T=T, d=d, dtype=dtype)
+    mask = oracle.topp_select(w.probs.reshape(-1, w.n), w.top_p).mask().reshape(w.B, w.H_kv, w.n)
+    q, k, v = kv_tensors(w)
+    idx, cnt = lists(mask)
+    out, lse = gpu_attention(q, k, v, idx, cnt)
+    ref, ref_lse = oracle_attention(w, mask)
+    assert row_rel_err(out, ref) <= tol(w)
+    assert np.abs(lse - ref_lse).max() <= 1e-3
+
+
+@pytest.mark.parametrize("G", [4, 8])
+@pytest.mark.parametrize("count", [0, 1, 63, 64, 65, 127, 128, 129, 8 * 64 - 1, 8 * 64 + 1, 2000])
+def test_counts_around_the_tiles_of_64_wide_heads(count, G):
+    w = W.llama8b_layer(seed=3, B=1, n=2048, H_q=3 * G, H_kv=3, T=5, d=64)
+    rng = np.random.default_rng(count)
+    mask = np.zeros((1, 3, w.n), dtype=np.uint8)
+    for h in range(3):
+        mask[0, h, rng.choice(w.n, size=max(0, count - h), replace=False)] = 1
+    q, k, v = kv_tensors(w)
+    idx, cnt = lists(mask)
+    out, lse = gpu_attention(q, k, v, idx, cnt)
+    ref, ref_lse = oracle_attention(w, mask)
+    assert row_rel_err(out, ref) <= tol(w)
+    if count == 0:
+        assert (out == 0).all() and np.isneginf(lse).all()
+
+
+@pytest.mark.parametrize("mode", ["table", "physical"])
+@pytest.mark.parametrize("d,H_q", [(64, 16), (64, 24), (128, 24), (128, 32)])
+def test_paged_layouts(mode, d, H_q):
+    w = W.ragged_paged(seed=5, B=4, len_lo=50, len_hi=3000, H_q=H_q, H_kv=2, T=4, d=d)
+    ref = oracle.topp_select(w.probs.reshape(-1, w.n), w.top_p, np.repeat(w.seq_lens, w.H_kv))
+    mask = ref.mask().reshape(w.B, w.H_kv, w.n)
+    idx, cnt = lists(mask)
+    if mode == "physical":
+        i = idx.cpu().numpy()
+        for r in range(i.shape[0]):
+            c = int(ref.counts[r])
+            i[r, :c] = w.page_table[r // w.H_kv, i[r, :c] // W.PAGE_SIZE] * W.PAGE_SIZE + i[r, :c] % W.PAGE_SIZE
+        idx = dev(i)
+    q, k, v = kv_tensors(w)
+    out, _ = gpu_attention(q, k, v, idx, cnt, page_table=dev(w.page_table) if mode == "table" else None,
+                           page_size=W.PAGE_SIZE, physical=mode == "physical", n_max=w.n)
+    want, _ = oracle_attention(w, mask)
+    assert row_rel_err(out, want) <= tol(w)
+
+
+@pytest.mark.parametrize("shape", [dict(B=40, n=250, H_q=64, H_kv=8, T=8), dict(B=1, n=60, H_q=7 * 512, H_kv=512, T=7)])
+def test_small_workspace(shape):
+    """The built-in 16 MiB do not hold partials of 64 query rows for all rows of these calls: the first goes out in
+    batches of fewer rows, the second (one sequence of 512 rows) in shares of at most 32 query rows."""
+    w = W.llama8b_layer(seed=8, **shape)
+    mask = oracle.topp_select(w.probs.reshape(-1, w.n), w.top_p).mask().reshape(w.B, w.H_kv, w.n)
+    q, k, v = kv_tensors(w)
+    idx, cnt = lists(mask)
+    out = torch.full(q.shape, float("nan"), dtype=torch.float32, device="cuda")
+    sa.specattn_sparse_decode_attn_static(sa.attn_args(q, k, v, out=out, indices=idx, counts=cnt))
+    torch.cuda.synchronize()
+    assert row_rel_err(out.cpu().numpy(), oracle_attention(w, mask)[0]) <= TOL["bf16"]
