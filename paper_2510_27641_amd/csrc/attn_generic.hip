@@ -1,36 +1,59 @@
-// Sparse decode attention over a selected index list (Section 3.1.2, Eq. 2-3; Section 3.5):
-// portable fp32-ALU variant for any supported shape and dtype (fp32 or bf16 inputs), plus the
-// split merge used by every variant.
+// Sparse decode attention over a selected index list (Section 3.1.2, Eq. 2-3; Section 3.5): the variant that
+// computes both contractions in fp32, for every element type - fp32 inputs, and what the 16-bit matrix-core kernel
+// does not take (more than 512 kv heads, workspaces too small for its partials).
 //
-// Work split: one workgroup per (row, split); a split is a contiguous slice of the row's index
-// list.  Each workgroup streams its slice in tiles of 32 positions through LDS, keeps the
-// running softmax state (max m, sum l, un-normalised output o) for all G*T query rows of the
-// kv head, and writes one partial (m, l, o).  merge_kernel combines the partials of a row:
-//   O = sum_s exp(m_s - m) o_s / sum_s exp(m_s - m) l_s,  lse = m + log(sum_s exp(m_s - m) l_s).
+// Work split: one workgroup of eight waves per (row, split); a split is a contiguous run of the row's kept positions
+// and tile k of 16 positions goes to wave k mod 8.  Each wave keeps the running softmax state (max m, sum l,
+// un-normalised output o) of all G*T query rows of the kv head; the eight states are combined in LDS in wave order.
+// A row with one split is finished there; otherwise the split leaves one partial (m, l, o) and merge_kernel combines
+//   O = sum_s 2^(m_s - m) o_s / sum_s 2^(m_s - m) l_s,  lse = ln 2 * (m + log2(sum_s 2^(m_s - m) l_s)).
+//
+// Both products run on the fp32 matrix cores (v_mfma_f32_16x16x4: full fp32 operands and sums, the rate of the vector
+// ALU but one operand fetch per 16 products), with no layout change anywhere between memory and the cores:
+//   S^T = K Q^T   : lane (p = lane % 16, g = lane / 16) loads elements 16j + 4g .. + 3 of key p with one 16-byte load
+//                   (64 contiguous bytes of each of 16 rows per instruction); k-step (j, i) contracts the elements
+//                   16j + 4g + i, an order of the head dimension that the Q fragments share.
+//   O^T += V^T P^T: lane (m = lane % 16, g) loads elements 4m .. 4m + 3 of value row 4g + c - four whole rows per
+//                   instruction - and component i is row m of the output tile of dv = 4m + i.  The weights of positions
+//                   4g + c are what the score product left in this very lane.
+// What bounds it: small calls, latency (list word -> K and V rows -> eight states); large ones, HBM or, from two
+// query tiles on, the fp32 matrix rate.  The kernel before it fed the vector ALU from LDS, four barriers per 32 positions:
+// selection and attention of 8 rows of 1024 positions (d = 64, 5 tokens) 26.9 us then, 13.9 us now; 32 rows of 424 (d =
+// 128, 28 query rows) 67 and 22 us; 8 rows of 5039 (d = 64) 54 and 22 us; error against 64 bits 2.4e-7 .. 4.5e-7 then,
+// 1.7e-7 .. 2.7e-7 now.
 #include "common.h"
-
-#include <hip/hip_bf16.h>
 
 #include <mutex>
 
 namespace specattn {
 namespace {
 
-constexpr int GEN_THREADS = 256;
-constexpr int GEN_TILE = 32;
-constexpr int MAX_QT = 64;            // G*T query rows per kv head handled by the generic kernel
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
+constexpr int GEN_WAVES = 8;
+constexpr int GEN_THREADS = GEN_WAVES * 64;
+constexpr int GEN_TILE = 16;          // positions
+constexpr int MAX_QT = 64;            // G*T query rows per kv head handled here
+constexpr float RESCALE_SLACK = 8.0f; // log2 units the running max may exceed the reference by
+
+// four consecutive elements as fp32
 template <typename T> struct Elem;
 template <> struct Elem<float> {
-    static __device__ __forceinline__ float ld(const void *p, int64_t i) { return static_cast<const float *>(p)[i]; }
+    static __device__ __forceinline__ f32x4 ld4(const void *p, int64_t i) { return *reinterpret_cast<const f32x4 *>(static_cast<const float *>(p) + i); }
 };
 template <> struct Elem<_Float16> {
-    static __device__ __forceinline__ float ld(const void *p, int64_t i) { return (float) static_cast<const _Float16 *>(p)[i]; }
-};
-template <> struct Elem<__hip_bfloat16> {
-    static __device__ __forceinline__ float ld(const void *p, int64_t i)
+    static __device__ __forceinline__ f32x4 ld4(const void *p, int64_t i)
     {
-        return __uint_as_float((uint32_t) static_cast<const uint16_t *>(p)[i] << 16);
+        typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+        return __builtin_convertvector(*reinterpret_cast<const f16x4 *>(static_cast<const _Float16 *>(p) + i), f32x4);
+    }
+};
+template <> struct Elem<uint16_t> {   // bf16
+    static __device__ __forceinline__ f32x4 ld4(const void *p, int64_t i)
+    {
+        const uint2 u = *reinterpret_cast<const uint2 *>(static_cast<const uint16_t *>(p) + i);
+        return (f32x4){__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16),
+                       __uint_as_float(u.y & 0xffff0000u)};
     }
 };
 
@@ -63,169 +86,307 @@ __device__ __forceinline__ KvMap make_map(const AttnLaunch &a, int b, int h)
     return m;
 }
 
-template <typename T, int D>
-__global__ __launch_bounds__(GEN_THREADS) void attn_generic_kernel(AttnLaunch a, int n_splits, float *part_o,
-                                                                  float *part_ml)
+// LDS, in floats: the Q tile and a state of every wave for one query tile, rows padded by one 16-byte chunk so that
+// 16 rows at one column fall on different banks; (m, l) of every wave and query row; scores of the new tokens.
+template <int D> struct Lds {
+    static constexpr int ROW = D + 4;
+    static constexpr int q_floats(int nqt) { return nqt * 16 * ROW; }
+    static constexpr int O_FLOATS = GEN_WAVES * 16 * ROW;
+    static constexpr int ML_FLOATS = GEN_WAVES * MAX_QT * 2;
+    static constexpr int TAIL_FLOATS = MAX_QT * SPECATTN_MAX_T;
+    static constexpr size_t bytes(int nqt) { return sizeof(float) * (size_t)(q_floats(nqt) + O_FLOATS + ML_FLOATS + TAIL_FLOATS); }
+};
+
+template <typename T, int D, int NQT>
+__global__ __launch_bounds__(GEN_THREADS, 1) void attn_f32_kernel(AttnLaunch a, int n_splits, float *part_o, float *part_ml)
 {
-    extern __shared__ float smem[];
-    const int QT = (a.H_q / a.H_kv) * a.T;
-    float *Qs = smem;                       // [QT][D]
-    float *Ks = Qs + MAX_QT * D;            // [TILE][D+1]
-    float *Vs = Ks + GEN_TILE * (D + 1);    // [TILE][D]
-    float *Ss = Vs + GEN_TILE * D;          // [QT][TILE+1]
-    float *alpha = Ss + MAX_QT * (GEN_TILE + 1);   // [QT]
-    float *m_run = alpha + MAX_QT;          // [QT]
-    float *l_run = m_run + MAX_QT;          // [QT]
+    extern __shared__ __attribute__((aligned(16))) float smem[];
+    typedef Lds<D> L;
+    constexpr int KJ = D / 16;            // 16-byte loads per key and lane
+    constexpr int DH = D / 64;            // value loads per row and lane
+    float *Qs = smem;
+    float *Os = Qs + L::q_floats(NQT);
+    float *ml = Os + L::O_FLOATS;         // [wave][query row][2]
+    float *tail = ml + L::ML_FLOATS;      // [query row][new token]
 
     const int r = blockIdx.x / n_splits, s = blockIdx.x - r * n_splits;
     const int b = r / a.H_kv, h = r - b * a.H_kv;
-    const int G = a.H_q / a.H_kv;
-    const int tid = threadIdx.x;
+    const int G = a.H_q / a.H_kv, QT = G * a.T;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, g = lane >> 4;
+    const float scale2 = a.sm_scale * 1.4426950408889634f;            // scores in log2 units
     const int count = attn_row_count(a, r);
     const int tiles = (count + GEN_TILE - 1) / GEN_TILE;
-    const int tiles_per_split = (tiles + n_splits - 1) / n_splits;
-    const int j_begin = s * tiles_per_split * GEN_TILE;
-    int j_end = j_begin + tiles_per_split * GEN_TILE;
-    j_end = j_end > count ? count : j_end;
+    const int per = (tiles + n_splits - 1) / n_splits;
+    const int t_end = (s + 1) * per < tiles ? (s + 1) * per : tiles;
     const int32_t *idx = a.dense ? nullptr : a.indices + (int64_t)r * a.idx_stride;
     const KvMap map = make_map(a, b, h);
-    const float scale = a.sm_scale;
 
-    for (int e = tid; e < QT * D; e += GEN_THREADS) {
-        const int qi = e / D, dd = e - qi * D;
-        const int g = qi / a.T, t = qi - g * a.T;
-        const int64_t qo = (int64_t)b * a.q_stride_b + (int64_t)(h * G + g) * a.q_stride_h + (int64_t)t * a.q_stride_t + dd;
-        Qs[e] = Elem<T>::ld(a.q, qo);
-    }
-    if (tid < QT) { m_run[tid] = -INFINITY; l_run[tid] = 0.0f; }
-    constexpr int OPT = (MAX_QT * D) / GEN_THREADS;      // outputs owned per thread (upper bound)
-    float acc[OPT];
+    // Element offset of the position whose key this lane helps to load; ranks past the end repeat the last one.
+    auto tile_off = [&](int t) -> int64_t {
+        const int jj = t * GEN_TILE + l16;
+        return map.off(attn_list_pos(a, idx, jj < count ? jj : count - 1));
+    };
+    f32x4 kf[KJ], vf[4][DH];
+    auto load_k = [&](int64_t off) {
 #pragma unroll
-    for (int k = 0; k < OPT; ++k) acc[k] = 0.0f;
+        for (int j = 0; j < KJ; ++j) kf[j] = Elem<T>::ld4(a.k, off + 16 * j + 4 * g);
+    };
+    auto load_v = [&](int64_t off) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int64_t row = __shfl(off, 4 * g + c, 64);
+#pragma unroll
+            for (int u = 0; u < DH; ++u) vf[c][u] = Elem<T>::ld4(a.v, row + 64 * u + 4 * l16);
+        }
+    };
+    int t = s * per + wave;
+    int64_t off_next = 0;
+    if (t < t_end) {                      // the first tile's rows are on their way before anything else is set up
+        const int64_t off = tile_off(t);
+        load_k(off);
+        load_v(off);
+        if (t + GEN_WAVES < t_end) off_next = tile_off(t + GEN_WAVES);
+    }
+    for (int e = tid; e < NQT * 16 * (D / 4); e += GEN_THREADS) {
+        const int qi = e / (D / 4), ch = e - qi * (D / 4);
+        f32x4 x = (f32x4){0.f, 0.f, 0.f, 0.f};
+        if (qi < QT) {
+            const int gh = qi / a.T, tt = qi - gh * a.T;
+            x = Elem<T>::ld4(a.q, (int64_t)b * a.q_stride_b + (int64_t)(h * G + gh) * a.q_stride_h + (int64_t)tt * a.q_stride_t + 4 * ch);
+        }
+        *reinterpret_cast<f32x4 *>(Qs + qi * L::ROW + 4 * ch) = x;
+    }
     __syncthreads();
 
-    for (int j0 = j_begin; j0 < j_end; j0 += GEN_TILE) {
-        const int np = (j_end - j0) < GEN_TILE ? (j_end - j0) : GEN_TILE;
-        for (int e = tid; e < GEN_TILE * D; e += GEN_THREADS) {
-            const int p = e / D, dd = e - p * D;
-            float kv = 0.0f, vv = 0.0f;
-            if (p < np) {
-                const int64_t o = map.off(attn_list_pos(a, idx, j0 + p)) + dd;
-                kv = Elem<T>::ld(a.k, o);
-                vv = Elem<T>::ld(a.v, o);
-            }
-            Ks[p * (D + 1) + dd] = kv;
-            Vs[p * D + dd] = vv;
-        }
-        __syncthreads();
-        for (int e = tid; e < QT * GEN_TILE; e += GEN_THREADS) {
-            const int qi = e / GEN_TILE, p = e - qi * GEN_TILE;
-            float dot = 0.0f;
-#pragma unroll 8
-            for (int dd = 0; dd < D; ++dd) dot = fmaf(Qs[qi * D + dd], Ks[p * (D + 1) + dd], dot);
-            Ss[qi * (GEN_TILE + 1) + p] = p < np ? dot * scale : -INFINITY;
-        }
-        __syncthreads();
-        if (tid < QT) {
-            float mx = m_run[tid];
-            for (int p = 0; p < np; ++p) mx = fmaxf(mx, Ss[tid * (GEN_TILE + 1) + p]);
-            const float al = (m_run[tid] == -INFINITY) ? 0.0f : __expf(m_run[tid] - mx);
-            float sum = 0.0f;
-            for (int p = 0; p < GEN_TILE; ++p) {
-                const float w = p < np ? __expf(Ss[tid * (GEN_TILE + 1) + p] - mx) : 0.0f;
-                Ss[tid * (GEN_TILE + 1) + p] = w;
-                sum += w;
-            }
-            alpha[tid] = al;
-            l_run[tid] = l_run[tid] * al + sum;
-            m_run[tid] = mx;
-        }
-        __syncthreads();
+    f32x4 o[NQT][DH][4];                  // [query tile][64 u +][i]: dv = 64 u + 16 g + 4 x + i in component x
+    float m_ref[NQT], l_sum[NQT];
 #pragma unroll
-        for (int k = 0; k < OPT; ++k) {
-            const int e = tid + k * GEN_THREADS;
-            if (e < QT * D) {
-                const int qi = e / D, dd = e - qi * D;
-                float o = acc[k] * alpha[qi];
-                for (int p = 0; p < GEN_TILE; ++p) o = fmaf(Ss[qi * (GEN_TILE + 1) + p], Vs[p * D + dd], o);
-                acc[k] = o;
+    for (int qt = 0; qt < NQT; ++qt) {
+        m_ref[qt] = -INFINITY;
+        l_sum[qt] = 0.0f;
+#pragma unroll
+        for (int u = 0; u < DH; ++u)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o[qt][u][i] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    }
+    int q_at = l16 * L::ROW + 4 * g;
+    // Scores of the 16 positions in kf against query tile qt: lane (q = l16, g) gets positions 4 g + i.  (Two chains:
+    // half the depth of dependent products, and of rounded sums.)
+    auto scores = [&](int qt) -> f32x4 {
+        f32x4 acc[2] = {(f32x4){0.f, 0.f, 0.f, 0.f}, (f32x4){0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+        for (int j = 0; j < KJ; ++j) {
+            const f32x4 qf = *reinterpret_cast<const f32x4 *>(Qs + q_at + qt * 16 * L::ROW + 16 * j);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[i & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[j][i], qf[i], acc[i & 1], 0, 0, 0);
+        }
+        return acc[0] + acc[1];
+    };
+    for (; t < t_end; t += GEN_WAVES) {
+        asm volatile("" : "+v"(q_at));    // (Q is read from LDS again for every tile: held, it would spill)
+        const bool has_next = t + GEN_WAVES < t_end;
+        const int remaining = count - t * GEN_TILE;
+        f32x4 p[NQT];
+#pragma unroll
+        for (int qt = 0; qt < NQT; ++qt) p[qt] = scores(qt);
+        const int64_t off = off_next;
+        if (has_next) {                   // (uniform) the key registers are free again
+            load_k(off);
+            if (t + 2 * GEN_WAVES < t_end) off_next = tile_off(t + 2 * GEN_WAVES);
+        }
+#pragma unroll
+        for (int qt = 0; qt < NQT; ++qt) {
+            f32x4 x = p[qt];
+            if (remaining < GEN_TILE) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (4 * g + i >= remaining) x[i] = -INFINITY;
+            }
+            const float mloc = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])) * scale2;
+            if (__any(mloc > m_ref[qt] + RESCALE_SLACK)) {             // first tile, then rare
+                float mx = fmaxf(mloc, __shfl_xor(mloc, 16, 64));
+                mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+                const float mnew = fmaxf(m_ref[qt], mx);
+                const float alpha = (m_ref[qt] == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(m_ref[qt] - mnew);
+                l_sum[qt] *= alpha;
+#pragma unroll
+                for (int u = 0; u < DH; ++u)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) o[qt][u][i] *= alpha;
+                m_ref[qt] = mnew;
+            }
+            const float mr = (m_ref[qt] == -INFINITY) ? 0.0f : m_ref[qt];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                p[qt][i] = __builtin_amdgcn_exp2f(fmaf(x[i], scale2, -mr));
+                l_sum[qt] += p[qt][i];
             }
         }
-        __syncthreads();
+        if (remaining < GEN_TILE) {       // a weight of zero must not meet an infinite value
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int u = 0; u < DH; ++u)
+                    if (4 * g + c >= remaining) vf[c][u] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int u = 0; u < DH; ++u)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int qt = 0; qt < NQT; ++qt)
+                        o[qt][u][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[c][u][i], p[qt][c], o[qt][u][i], 0, 0, 0);
+        if (has_next) load_v(off);
     }
 
-    float *po = part_o + ((int64_t)r * n_splits + s) * QT * D;
-    float *pml = part_ml + ((int64_t)r * n_splits + s) * QT * 2;
+    // ---- scores of the new tokens behind the cache (first split): wave qt takes query tile qt ----------------
+    const bool with_tail = a.k_new != nullptr && s == 0;               // uniform
+    const int64_t noff = ((int64_t)b * a.H_kv + h) * a.T * D;
+    if (with_tail && wave < NQT) {
+        const int row = l16 < a.T ? l16 : a.T - 1;
 #pragma unroll
-    for (int k = 0; k < OPT; ++k) {
-        const int e = tid + k * GEN_THREADS;
-        if (e < QT * D) po[e] = acc[k];
+        for (int j = 0; j < KJ; ++j) kf[j] = Elem<T>::ld4(a.k_new, noff + (int64_t)row * D + 16 * j + 4 * g);
+        const f32x4 x = scores(wave);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (4 * g + i < a.T) tail[(wave * 16 + l16) * SPECATTN_MAX_T + 4 * g + i] = x[i] * scale2;
     }
-    if (tid < QT) { pml[2 * tid] = m_run[tid]; pml[2 * tid + 1] = l_run[tid]; }
+
+    // ---- combine the eight states, one query tile per round ---------------------------------------------------
+#pragma unroll
+    for (int qt = 0; qt < NQT; ++qt) {
+        float l = l_sum[qt];
+        l += __shfl_xor(l, 16, 64);
+        l += __shfl_xor(l, 32, 64);
+        if (g == 0) {
+            ml[(wave * MAX_QT + qt * 16 + l16) * 2] = m_ref[qt];
+            ml[(wave * MAX_QT + qt * 16 + l16) * 2 + 1] = l;
+        }
+        if (qt) __syncthreads();          // the round before has been read out
+#pragma unroll
+        for (int u = 0; u < DH; ++u)
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+                *reinterpret_cast<f32x4 *>(Os + (wave * 16 + l16) * L::ROW + 64 * u + 16 * g + 4 * x) =
+                    (f32x4){o[qt][u][0][x], o[qt][u][1][x], o[qt][u][2][x], o[qt][u][3][x]};
+        __syncthreads();
+        const int ql = tid / (D / 4), dv = 4 * (tid & (D / 4 - 1)), q = qt * 16 + ql;
+        if (ql < 16 && q < QT) {
+            const int gh = q / a.T, tt = q - gh * a.T;
+            float m = -INFINITY;
+#pragma unroll
+            for (int w = 0; w < GEN_WAVES; ++w) m = fmaxf(m, ml[(w * MAX_QT + q) * 2]);
+            if (with_tail)
+                for (int p = 0; p <= tt; ++p) m = fmaxf(m, tail[q * SPECATTN_MAX_T + p]);
+            f32x4 acc = (f32x4){0.f, 0.f, 0.f, 0.f};
+            float lt = 0.0f;
+#pragma unroll
+            for (int w = 0; w < GEN_WAVES; ++w) {
+                const float mw = ml[(w * MAX_QT + q) * 2];
+                const float f = (mw == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(mw - m);
+                lt += f * ml[(w * MAX_QT + q) * 2 + 1];
+                acc += f * *reinterpret_cast<const f32x4 *>(Os + (w * 16 + ql) * L::ROW + dv);
+            }
+            if (with_tail)
+                for (int p = 0; p <= tt; ++p) {
+                    const float f = __builtin_amdgcn_exp2f(tail[q * SPECATTN_MAX_T + p] - m);
+                    lt += f;
+                    acc += f * Elem<T>::ld4(a.v_new, noff + (int64_t)p * D + dv);
+                }
+            if (n_splits == 1) {
+                const int64_t orow = ((int64_t)b * a.H_q + (h * G + gh)) * a.T + tt;
+                const f32x4 res = lt > 0.0f ? acc / lt : (f32x4){0.f, 0.f, 0.f, 0.f};
+                *reinterpret_cast<f32x4 *>(a.out + orow * D + dv) = res;
+                if (a.out_lowp) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) st_lowp(a.out_lowp, orow * D + dv + i, res[i], a.dtype);
+                }
+                if (a.lse && dv == 0) a.lse[orow] = lt > 0.0f ? (m + log2f(lt)) * 0.6931471805599453f : -INFINITY;
+            } else {
+                const int64_t slot = ((int64_t)r * n_splits + s) * QT + q;
+                *reinterpret_cast<f32x4 *>(part_o + slot * D + dv) = acc;
+                if (dv == 0) { part_ml[2 * slot] = m; part_ml[2 * slot + 1] = lt; }
+            }
+        }
+    }
 }
 
-// One workgroup per (row, query row): combine the partials of all splits, then the new tokens
-// behind the cache (query t sees new tokens 0..t), if the caller gave any.
+// One workgroup per (row, query row): combine the partials of all splits in split order, eight per round trip.
 __global__ void merge_kernel(AttnLaunch a, int n_splits, const float *part_o, const float *part_ml)
 {
-    __shared__ float red[2 * SPECATTN_MAX_T];
     const int G = a.H_q / a.H_kv;
     const int QT = G * a.T;
     const int r = blockIdx.x / QT, qi = blockIdx.x - r * QT;
     const int b = r / a.H_kv, h = r - b * a.H_kv;
-    const int g = qi / a.T, t = qi - g * a.T;
-    const int D = a.d;
-    float dots[SPECATTN_MAX_T];
-    const int n_tail = a.k_new ? t + 1 : 0;
-    if (n_tail) tail_dots(a, b, h * G + g, t, red, dots);
-    float m = -INFINITY;
-    for (int s = 0; s < n_splits; ++s) m = fmaxf(m, part_ml[(((int64_t)r * n_splits + s) * QT + qi) * 2]);
+    const int D = a.d, dv = threadIdx.x;
+    float m = -INFINITY, l = 0.0f, o = 0.0f;
+    for (int s0 = 0; s0 < n_splits; s0 += 8) {
+        float ms[8], ls[8], os[8], mx = m;
 #pragma unroll
-    for (int p = 0; p < SPECATTN_MAX_T; ++p)
-        if (p < n_tail) m = fmaxf(m, dots[p] * a.sm_scale);
-    float l = 0.0f;
-    for (int s = 0; s < n_splits; ++s) {
-        const float *p = part_ml + (((int64_t)r * n_splits + s) * QT + qi) * 2;
-        if (p[0] != -INFINITY) l += __expf(p[0] - m) * p[1];
-    }
-    float wt[SPECATTN_MAX_T];
-#pragma unroll
-    for (int p = 0; p < SPECATTN_MAX_T; ++p) {
-        wt[p] = p < n_tail ? __expf(dots[p] * a.sm_scale - m) : 0.0f;
-        l += wt[p];
-    }
-    const int64_t orow = ((int64_t)b * a.H_q + (h * G + g)) * a.T + t;
-    const int64_t noff = ((int64_t)b * a.H_kv + h) * a.T * D;
-    for (int dd = threadIdx.x; dd < D; dd += blockDim.x) {
-        float o = 0.0f;
-        for (int s = 0; s < n_splits; ++s) {
-            const float ms = part_ml[(((int64_t)r * n_splits + s) * QT + qi) * 2];
-            if (ms != -INFINITY) o += __expf(ms - m) * part_o[(((int64_t)r * n_splits + s) * QT + qi) * D + dd];
+        for (int k = 0; k < 8; ++k) {
+            const bool ok = s0 + k < n_splits;
+            const int64_t slot = ((int64_t)r * n_splits + (ok ? s0 + k : 0)) * QT + qi;
+            ms[k] = ok ? part_ml[2 * slot] : -INFINITY;
+            ls[k] = ok ? part_ml[2 * slot + 1] : 0.0f;
+            os[k] = ok ? part_o[slot * D + dv] : 0.0f;
         }
 #pragma unroll
-        for (int p = 0; p < SPECATTN_MAX_T; ++p)
-            if (p < n_tail) o += wt[p] * ld_elem(a.v_new, noff + (int64_t)p * D + dd, a.dtype);
-        const float res = l > 0.0f ? o / l : 0.0f;
-        a.out[orow * D + dd] = res;
-        if (a.out_lowp) st_lowp(a.out_lowp, orow * D + dd, res, a.dtype);
+        for (int k = 0; k < 8; ++k) mx = fmaxf(mx, ms[k]);
+        const float fa = (m == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(m - mx);
+        l *= fa;
+        o *= fa;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const float f = (ms[k] == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(ms[k] - mx);
+            l += f * ls[k];
+            o += f * os[k];
+        }
+        m = mx;
     }
-    if (a.lse && threadIdx.x == 0) a.lse[orow] = l > 0.0f ? m + __logf(l) : -INFINITY;
+    const int g = qi / a.T, t = qi - g * a.T;
+    const int64_t orow = ((int64_t)b * a.H_q + (h * G + g)) * a.T + t;
+    const float res = l > 0.0f ? o / l : 0.0f;
+    a.out[orow * D + dv] = res;
+    if (a.out_lowp) st_lowp(a.out_lowp, orow * D + dv, res, a.dtype);
+    if (a.lse && dv == 0) a.lse[orow] = l > 0.0f ? (m + log2f(l)) * 0.6931471805599453f : -INFINITY;
 }
 
-constexpr size_t generic_lds_bytes(int d)
+template <typename T, int D> const void *variant(int nqt)
 {
-    return sizeof(float) * (size_t)(MAX_QT * d + GEN_TILE * (d + 1) + GEN_TILE * d + MAX_QT * (GEN_TILE + 1) + 3 * MAX_QT);
+    switch (nqt) {
+    case 1: return reinterpret_cast<const void *>(&attn_f32_kernel<T, D, 1>);
+    case 2: return reinterpret_cast<const void *>(&attn_f32_kernel<T, D, 2>);
+    case 3: return reinterpret_cast<const void *>(&attn_f32_kernel<T, D, 3>);
+    case 4: return reinterpret_cast<const void *>(&attn_f32_kernel<T, D, 4>);
+    }
+    return nullptr;
 }
-
-template <typename T, int D>
-specattn_status run_generic(const AttnLaunch &a, int rows, int n_splits, float *part_o, float *part_ml,
-                            hipStream_t stream)
+const void *variant(int dtype, int d, int nqt)
 {
-    const specattn_status st = attn_generic_configure();
-    if (st != SPECATTN_OK) return st;
-    hipLaunchKernelGGL((attn_generic_kernel<T, D>), dim3(rows * n_splits), dim3(GEN_THREADS), generic_lds_bytes(D), stream, a,
-                       n_splits, part_o, part_ml);
-    return check_launch("attn_generic_kernel");
+    if (d != 64 && d != 128) return nullptr;
+    if (dtype == SPECATTN_F32) return d == 64 ? variant<float, 64>(nqt) : variant<float, 128>(nqt);
+    if (dtype == SPECATTN_BF16) return d == 64 ? variant<uint16_t, 64>(nqt) : variant<uint16_t, 128>(nqt);
+    if (dtype == SPECATTN_F16) return d == 64 ? variant<_Float16, 64>(nqt) : variant<_Float16, 128>(nqt);
+    return nullptr;
+}
+size_t lds_bytes(int d, int nqt) { return d == 64 ? Lds<64>::bytes(nqt) : Lds<128>::bytes(nqt); }
+static_assert(Lds<128>::bytes(4) <= 160 * 1024, "the tables must fit");
+
+// Splits of a row in this kernel, never more than attn_num_splits (which sizes the workspace).  A row whose list is
+// short is finished by one workgroup: the second launch costs more (4.5 us) than the rounds saved, a round of eight
+// tiles being about a microsecond of latency per query tile and 64 elements of head dimension.  The line, both sides
+// measured: 12 rows of 1214 (d = 64) 16.4 us with one split and 18.5 us with several, 32 rows of 1948 (d = 64) 17.0
+// and 18.7 us, but 32 rows of 1617 (d = 128, two query tiles) 31 and 22 us.  Otherwise two workgroups per CU, which evens
+// out rows of different counts.
+int splits(int rows, int capacity, int nqt, int d)
+{
+    if ((int64_t)capacity * nqt * (d / 64) <= 2048) return 1;
+    const int most = attn_num_splits(rows, capacity), want = (2 * cu_count() + rows - 1) / rows;
+    return want < most ? want : most;
 }
 
 }  // namespace
@@ -245,18 +406,11 @@ specattn_status attn_generic_configure()
     }
     std::lock_guard<std::mutex> lock(mu);
     if (done[dev]) return SPECATTN_OK;
-    const struct { const void *fn; size_t lds; } variants[] = {
-        {reinterpret_cast<const void *>(&attn_generic_kernel<float, 64>), generic_lds_bytes(64)},
-        {reinterpret_cast<const void *>(&attn_generic_kernel<float, 128>), generic_lds_bytes(128)},
-        {reinterpret_cast<const void *>(&attn_generic_kernel<__hip_bfloat16, 64>), generic_lds_bytes(64)},
-        {reinterpret_cast<const void *>(&attn_generic_kernel<__hip_bfloat16, 128>), generic_lds_bytes(128)},
-        {reinterpret_cast<const void *>(&attn_generic_kernel<_Float16, 64>), generic_lds_bytes(64)},
-        {reinterpret_cast<const void *>(&attn_generic_kernel<_Float16, 128>), generic_lds_bytes(128)},
-    };
-    for (const auto &v : variants) {
-        if (hipFuncSetAttribute(v.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)v.lds) != hipSuccess) {
+    for (int k = 0; k < 3 * 2 * 4; ++k) {
+        const int dtype = k % 3, d = k / 3 % 2 ? 128 : 64, nqt = k / 6 + 1;
+        if (hipFuncSetAttribute(variant(dtype, d, nqt), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes(d, nqt)) != hipSuccess) {
             (void)hipGetLastError();
-            set_error("cannot reserve %zu bytes of LDS", v.lds);
+            set_error("cannot reserve %zu bytes of LDS", lds_bytes(d, nqt));
             return SPECATTN_EHIP;
         }
     }
@@ -294,20 +448,23 @@ specattn_status launch_attn(const AttnLaunch &a, hipStream_t stream)
     if (attn_mfma_supported(a)) return launch_attn_mfma(a, stream);
     const int rows = a.B * a.H_kv;
     const int G = a.H_q / a.H_kv;
-    const int QT = G * a.T;
-    const int ns = attn_num_splits(rows, a.idx_capacity << a.chunk_shift);
+    const int QT = G * a.T, nqt = (QT + 15) / 16;
+    int ns = splits(rows, a.idx_capacity << a.chunk_shift, nqt, a.d);
+    const void *fn = variant(a.dtype, a.d, nqt);
+    if (!fn) { set_error("no attention kernel for dtype %d, d %d", a.dtype, a.d); return SPECATTN_EUNSUPPORTED; }
+    specattn_status st = attn_generic_configure();
+    if (st != SPECATTN_OK) return st;
     float *part_o = static_cast<float *>(a.workspace);
     float *part_ml = part_o + (size_t)rows * ns * QT * a.d;
-    specattn_status st;
-    if (a.dtype == SPECATTN_F32 && a.d == 64) st = run_generic<float, 64>(a, rows, ns, part_o, part_ml, stream);
-    else if (a.dtype == SPECATTN_F32 && a.d == 128) st = run_generic<float, 128>(a, rows, ns, part_o, part_ml, stream);
-    else if (a.dtype == SPECATTN_BF16 && a.d == 64) st = run_generic<__hip_bfloat16, 64>(a, rows, ns, part_o, part_ml, stream);
-    else if (a.dtype == SPECATTN_BF16 && a.d == 128) st = run_generic<__hip_bfloat16, 128>(a, rows, ns, part_o, part_ml, stream);
-    else if (a.dtype == SPECATTN_F16 && a.d == 64) st = run_generic<_Float16, 64>(a, rows, ns, part_o, part_ml, stream);
-    else if (a.dtype == SPECATTN_F16 && a.d == 128) st = run_generic<_Float16, 128>(a, rows, ns, part_o, part_ml, stream);
-    else { set_error("no attention kernel for dtype %d, d %d", a.dtype, a.d); return SPECATTN_EUNSUPPORTED; }
-    if (st != SPECATTN_OK) return st;
-    hipLaunchKernelGGL(merge_kernel, dim3(rows * QT), dim3(a.d < 64 ? 64 : a.d), 0, stream, a, ns, part_o, part_ml);
+    void *kargs[] = {const_cast<AttnLaunch *>(&a), &ns, &part_o, &part_ml};
+    if (hipLaunchKernel(fn, dim3(rows * ns), dim3(GEN_THREADS), kargs, lds_bytes(a.d, nqt), stream) != hipSuccess) {
+        set_error("attn_f32_kernel: launch failed");
+        (void)hipGetLastError();
+        return SPECATTN_EHIP;
+    }
+    st = check_launch("attn_f32_kernel");
+    if (st != SPECATTN_OK || ns == 1) return st;
+    hipLaunchKernelGGL(merge_kernel, dim3(rows * QT), dim3(a.d), 0, stream, a, ns, part_o, part_ml);
     return check_launch("merge_kernel");
 }
 
