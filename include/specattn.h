@@ -125,9 +125,9 @@ typedef struct specattn_select_args {
  * (tiles are assigned to waves and workgroups by the counts alone), so repeated
  * calls on the same inputs give bit-identical out and lse.
  *
- * Shapes: bf16 and fp16 run on the matrix cores for any G = H_q / H_kv (up to 64 query rows
- * G*T per pass; larger groups are taken in equal shares of heads, each streaming the kept K/V
- * again).  fp32 runs on a portable kernel limited to G*T <= 64.
+ * Shapes: bf16 and fp16 with d = 128 take any G = H_q / H_kv (up to 64 query rows G*T per pass;
+ * larger groups are taken in equal shares of heads, each streaming the kept K/V again).  fp32, and
+ * d = 64, are limited to G*T <= 64.
  *
  * Dense layers (Section 4 keeps the first layers of the verifier dense): with
  * indices == NULL and counts == NULL every position below seq_lens[b] (n_max

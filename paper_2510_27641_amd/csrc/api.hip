@@ -93,10 +93,11 @@ specattn_status check_attn(const specattn_attn_args *a, bool fused)
     if (a->T > SPECATTN_MAX_T) { set_error("T exceeds %d", SPECATTN_MAX_T); return SPECATTN_ESHAPE; }
     if (a->d != 64 && a->d != 128) { set_error("d must be 64 or 128"); return SPECATTN_ESHAPE; }
     {
-        // more than 64 query rows per kv head only fit the matrix-core route (the portable kernel's tables hold 64)
+        // more than 64 query rows per kv head only fit the 16-bit route at d = 128 (the fp32 kernel's tables hold 64,
+        // and d = 64 has to be able to run there when its workspace is small)
         AttnLaunch probe{};
         probe.dtype = (int)a->dtype; probe.d = a->d; probe.T = a->T; probe.H_kv = a->H_kv;
-        if ((a->H_q / a->H_kv) * a->T > 64 && !attn_mfma_supported(probe)) { set_error("G*T exceeds 64 query rows per kv head (only bf16 / fp16 with H_kv <= %d take more)", ATTN_MFMA_MAX_ROWS); return SPECATTN_ESHAPE; }
+        if ((a->H_q / a->H_kv) * a->T > 64 && !(attn_mfma_supported(probe) && a->d == 128)) { set_error("G*T exceeds 64 query rows per kv head (only bf16 / fp16 with d = 128 and H_kv <= %d take more)", ATTN_MFMA_MAX_ROWS); return SPECATTN_ESHAPE; }
     }
     if (!fused && !dense && a->idx_capacity < 1) { set_error("idx_capacity must be at least 1"); return SPECATTN_ESHAPE; }
     if (!fused && !dense && a->idx_stride_row < a->idx_capacity) { set_error("idx_stride_row is smaller than idx_capacity"); return SPECATTN_ESHAPE; }
@@ -208,6 +209,8 @@ using namespace specattn;
 
 extern "C" {
 
+static size_t workspace_bytes(const specattn_select_args *sel, const specattn_attn_args *attn, bool full);
+
 specattn_status specattn_topp_select(const specattn_select_args *sel, void *workspace, size_t workspace_bytes,
                                      void *stream)
 {
@@ -314,7 +317,7 @@ specattn_status specattn_sparse_decode_attn(const specattn_attn_args *attn, void
     clear_error();
     specattn_status st = check_attn(attn, false);
     if (st != SPECATTN_OK) return st;
-    st = check_workspace(attn->workspace, attn->workspace_bytes, specattn_workspace_size(nullptr, attn));
+    st = check_workspace(attn->workspace, attn->workspace_bytes, workspace_bytes(nullptr, attn, false));
     if (st != SPECATTN_OK) return st;
     return launch_attn(make_attn(attn), static_cast<hipStream_t>(stream));
 }
@@ -358,9 +361,11 @@ specattn_status specattn_fused(const specattn_select_args *sel, const specattn_a
         set_error("the fused call has no index list: indices_are_physical does not apply (pass the page table)");
         return SPECATTN_EUNSUPPORTED;
     }
-    st = check_workspace(attn->workspace, attn->workspace_bytes, specattn_workspace_size(sel, attn));
+    st = check_workspace(attn->workspace, attn->workspace_bytes, workspace_bytes(sel, attn, false));
     if (st != SPECATTN_OK) return st;
     const int rows = sel->B * sel->H_kv;
+    const bool full = attn->workspace_bytes >= workspace_bytes(sel, attn, true);
+    const size_t attn_bytes = (full ? attn_workspace_bytes : attn_workspace_accepted_bytes)(rows, attn->H_q / attn->H_kv, attn->T, attn->d, attn->n_max);
     if (!fused_on_chip(sel, attn)) {
         // selection into the workspace, then attention over that list
         if (sel->reuse_selection || sel->block_counts || sel->kept_mask) {
@@ -370,7 +375,6 @@ specattn_status specattn_fused(const specattn_select_args *sel, const specattn_a
         const int chunk = sel->chunk_size > 1 ? sel->chunk_size : 1;
         const int cap = (sel->n_max + chunk - 1) / chunk;
         char *ws = static_cast<char *>(attn->workspace);
-        const size_t attn_bytes = attn_workspace_bytes(rows, attn->H_q / attn->H_kv, attn->T, attn->d, attn->n_max);
         specattn_select_args s2 = *sel;
         s2.indices = reinterpret_cast<int32_t *>(ws + attn_bytes);
         s2.idx_stride_row = cap;
@@ -394,8 +398,8 @@ specattn_status specattn_fused(const specattn_select_args *sel, const specattn_a
     AttnLaunch al = make_attn(attn);
     const int blocks = (sel->n_max + SEL_BLOCK - 1) / SEL_BLOCK;
     // workspace: [attention partials][block counts: rows * blocks ints][kept mask: rows * blocks * 32 words]
-    char *extra = static_cast<char *>(attn->workspace) +
-                  attn_workspace_bytes(rows, attn->H_q / attn->H_kv, attn->T, attn->d, attn->n_max);
+    al.workspace_bytes = attn_bytes;
+    char *extra = static_cast<char *>(attn->workspace) + attn_bytes;
     int32_t *bc = sel->block_counts ? sel->block_counts : reinterpret_cast<int32_t *>(extra);
     extra += ((size_t)rows * blocks * sizeof(int32_t) + 255) & ~(size_t)255;
     uint32_t *mask = sel->kept_mask ? sel->kept_mask : reinterpret_cast<uint32_t *>(extra);
@@ -422,7 +426,9 @@ specattn_status specattn_fused(const specattn_select_args *sel, const specattn_a
     return launch_attn_mfma(al, s);
 }
 
-size_t specattn_workspace_size(const specattn_select_args *sel, const specattn_attn_args *attn)
+// What a call asks for (full), or the least it is accepted with: an attention call with less room than it asks for takes
+// fewer query rows per launch, or the kernel with the smaller partials.
+static size_t workspace_bytes(const specattn_select_args *sel, const specattn_attn_args *attn, bool full)
 {
     if (!sel && !attn) return 0;
     if (sel && !attn) {                               // token selection keeps its state on chip;
@@ -445,7 +451,7 @@ size_t specattn_workspace_size(const specattn_select_args *sel, const specattn_a
     const bool dense = !attn->indices && !attn->counts;
     const int cap = (sel || dense) ? attn->n_max : attn->idx_capacity * (attn->chunk_size > 1 ? attn->chunk_size : 1);
     if (cap <= 0) return 0;
-    size_t bytes = attn_workspace_bytes(rows, attn->H_q / attn->H_kv, attn->T, attn->d, cap);
+    size_t bytes = (full ? attn_workspace_bytes : attn_workspace_accepted_bytes)(rows, attn->H_q / attn->H_kv, attn->T, attn->d, cap);
     if (sel && !fused_on_chip(sel, attn)) {           // fused by way of a list in the workspace
         if (sel->n_max <= 0) return 0;
         const int chunk = sel->chunk_size > 1 ? sel->chunk_size : 1;
@@ -461,6 +467,11 @@ size_t specattn_workspace_size(const specattn_select_args *sel, const specattn_a
         bytes += ((size_t)rows * blocks * (SEL_BLOCK / 32) * sizeof(uint32_t) + 255) & ~(size_t)255;
     }
     return bytes;
+}
+
+size_t specattn_workspace_size(const specattn_select_args *sel, const specattn_attn_args *attn)
+{
+    return workspace_bytes(sel, attn, true);
 }
 
 // Device address of this GPU's copy of `scratch`, looked up once per device (any thread may call).

@@ -23,6 +23,7 @@
 // 1.7e-7 .. 2.7e-7 now.
 #include "common.h"
 
+#include <algorithm>
 #include <mutex>
 
 namespace specattn {
@@ -429,25 +430,34 @@ int attn_num_splits(int rows, int idx_capacity)
     return s;
 }
 
-static size_t workspace_bytes(int rows, int G, int T, int d, int idx_capacity, bool least)
+static size_t generic_bytes(int rows, int G, int T, int d, int idx_capacity)
 {
     const size_t ns = (size_t)attn_num_splits(rows, idx_capacity);
-    const size_t qt = (size_t)G * T;
-    size_t bytes = (size_t)rows * ns * qt * (size_t)(d + 2) * sizeof(float);
-    bytes = (bytes + 255) & ~(size_t)255;
-    // the matrix-core variant may take this shape (the size does not depend on the element type)
-    const size_t other = least ? attn_mfma_workspace_min_bytes(rows, G, T, d) : attn_mfma_workspace_bytes(rows, G, T, d);
-    if (other > bytes) bytes = other;
-    return bytes;
+    const size_t bytes = (size_t)rows * ns * (size_t)G * T * (size_t)(d + 2) * sizeof(float);
+    return (bytes + 255) & ~(size_t)255;
 }
-size_t attn_workspace_bytes(int rows, int G, int T, int d, int idx_capacity) { return workspace_bytes(rows, G, T, d, idx_capacity, false); }
-size_t attn_workspace_min_bytes(int rows, int G, int T, int d, int idx_capacity) { return workspace_bytes(rows, G, T, d, idx_capacity, true); }
+// the 16-bit variant may take any shape (the size does not depend on the element type)
+size_t attn_workspace_bytes(int rows, int G, int T, int d, int idx_capacity)
+{
+    return std::max(generic_bytes(rows, G, T, d, idx_capacity), attn_mfma_workspace_bytes(rows, G, T, d));
+}
+size_t attn_workspace_min_bytes(int rows, int G, int T, int d, int idx_capacity)
+{
+    return std::max(generic_bytes(rows, G, T, d, idx_capacity), attn_mfma_workspace_min_bytes(rows, G, T, d));
+}
+size_t attn_workspace_accepted_bytes(int rows, int G, int T, int d, int idx_capacity)
+{
+    const size_t bytes = generic_bytes(rows, G, T, d, idx_capacity);
+    return d == 64 ? bytes : std::max(bytes, attn_mfma_workspace_narrow_bytes(rows, G, T, d));
+}
 
 specattn_status launch_attn(const AttnLaunch &a, hipStream_t stream)
 {
-    if (attn_mfma_supported(a)) return launch_attn_mfma(a, stream);
     const int rows = a.B * a.H_kv;
     const int G = a.H_q / a.H_kv;
+    // (at d = 64 a call is accepted with a workspace that holds this kernel's partials only)
+    if (attn_mfma_supported(a) && (a.d == 128 || a.workspace_bytes >= attn_mfma_workspace_min_bytes(rows, G, a.T, a.d)))
+        return launch_attn_mfma(a, stream);
     const int QT = G * a.T, nqt = (QT + 15) / 16;
     int ns = splits(rows, a.idx_capacity << a.chunk_shift, nqt, a.d);
     const void *fn = variant(a.dtype, a.d, nqt);

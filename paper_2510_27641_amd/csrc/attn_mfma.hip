@@ -138,6 +138,10 @@ size_t attn_mfma_workspace_bytes(int rows, int G, int T, int d)
     const size_t wide = workspace_for(rows < most ? rows : most, nqt, d), least = attn_mfma_workspace_min_bytes(rows, G, T, d);
     return wide > least ? wide : least;
 }
+size_t attn_mfma_workspace_narrow_bytes(int rows, int G, int T, int d)
+{
+    return workspace_for(rows < MAX_ROWS_LIST ? rows : MAX_ROWS_LIST, query_tiles(G, T, NARROW), d);
+}
 size_t attn_mfma_workspace_min_bytes(int rows, int G, int T, int d)
 {
     return workspace_for(rows < MAX_ROWS ? rows : MAX_ROWS, query_tiles(G, T, NARROW), d);

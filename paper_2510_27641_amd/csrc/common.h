@@ -235,7 +235,8 @@ __device__ __forceinline__ void tail_dots(const AttnLaunch &a, int b, int hq, in
 // number of splits per row the attention launch will use for this shape
 int attn_num_splits(int rows, int idx_capacity);
 size_t attn_workspace_bytes(int rows, int G, int T, int d, int idx_capacity);
-size_t attn_workspace_min_bytes(int rows, int G, int T, int d, int idx_capacity);   // the least the call runs with
+size_t attn_workspace_min_bytes(int rows, int G, int T, int d, int idx_capacity);   // what the built-in scratch has to hold
+size_t attn_workspace_accepted_bytes(int rows, int G, int T, int d, int idx_capacity);   // the least a call is accepted with
 specattn_status launch_attn(const AttnLaunch &a, hipStream_t stream);
 
 // counts the index-list violations of an attention call into *n_bad (device memory)
@@ -256,6 +257,7 @@ specattn_status attn_mfma_configure();    // one-time kernel attributes on the c
 specattn_status attn_generic_configure(); // the same for the fp32-ALU variants
 specattn_status layer_map_configure();    // and for the layer similarity
 size_t attn_mfma_workspace_bytes(int rows, int G, int T, int d);       // what lets every launch take as many rows as it can
+size_t attn_mfma_workspace_narrow_bytes(int rows, int G, int T, int d);   // the same with two query tiles per launch
 size_t attn_mfma_workspace_min_bytes(int rows, int G, int T, int d);   // the least a call runs with
 // kernel variants by query tiles (1 .. 4), layout and element type; null where none is built
 const void *attn_mfma_list_128(int nqt, int layout, bool f16);

@@ -305,17 +305,27 @@ __global__ __launch_bounds__(MAP_THREADS) void layer_map_kernel(const double *__
 // Runs of 512 entries per workgroup, and workgroups along the entries: one workgroup per CU (its LDS allows no second) as
 // soon as there are that many runs.
 struct KlPlan { int iters, chunks, gi, gj; };
-KlPlan kl_plan(int m, int n, int64_t per_layer)
+KlPlan kl_plan(int m, int n, int64_t per_layer, int64_t most_chunks)
 {
     KlPlan p;
     p.gi = (m + KL_TI - 1) / KL_TI;
     p.gj = (n + KL_TJ - 1) / KL_TJ;
     const int64_t runs = (per_layer + KL_ITER_K - 1) / KL_ITER_K;
     int64_t want = cu_count() / ((int64_t)p.gi * p.gj);
+    want = want > most_chunks ? most_chunks : want;
     want = want < 1 ? 1 : want;
     p.iters = (int)((runs + want - 1) / want);
     p.chunks = (int)((runs + p.iters - 1) / p.iters);
     return p;
+}
+
+// Chunks a call is accepted with at least: what fills the chip with one workgroup per layer pair and chunk of 4096 terms
+// or more.  (A workspace between that and the full size takes fewer, longer chunks.)
+int64_t kl_least_chunks(int m, int n, int64_t per_layer)
+{
+    const int64_t pairs = (int64_t)m * n, want = (4 * (int64_t)cu_count() + pairs - 1) / pairs, most = (per_layer + 4095) / 4096;
+    const int64_t least = want < most ? want : most;
+    return least < 1 ? 1 : (least > 1024 ? 1024 : least);
 }
 
 bool bad_dims(int m, int n, int rows, int L)
@@ -357,7 +367,7 @@ extern "C" {
 size_t specattn_layer_similarity_workspace_size(int32_t m, int32_t n, int32_t rows, int32_t L)
 {
     if (bad_dims(m, n, rows, L)) return 0;
-    const size_t bytes = (size_t)m * n * kl_plan(m, n, (int64_t)rows * L).chunks * sizeof(double);
+    const size_t bytes = (size_t)m * n * kl_plan(m, n, (int64_t)rows * L, INT64_MAX).chunks * sizeof(double);
     return (bytes + 255) & ~(size_t)255;
 }
 
@@ -369,13 +379,15 @@ specattn_status specattn_layer_similarity(const float *attn_draft, const float *
     if (!attn_draft || !attn_verifier || !S) { set_error("attn_draft, attn_verifier and S must not be NULL"); return SPECATTN_EINVAL; }
     if (m <= 0 || n <= 0 || rows <= 0 || L <= 0) { set_error("m, n, rows and L must be positive"); return SPECATTN_EINVAL; }
     if (bad_dims(m, n, rows, L)) { set_error("at most 65535 layer pairs and 2^40 entries per layer"); return SPECATTN_ESHAPE; }
-    const size_t need = specattn_layer_similarity_workspace_size(m, n, rows, L);
+    const int pairs = m * n;
+    const int64_t per_layer = (int64_t)rows * L, least = kl_least_chunks(m, n, per_layer);
+    size_t need = specattn_layer_similarity_workspace_size(m, n, rows, L);
+    const size_t least_bytes = ((size_t)pairs * least * sizeof(double) + 255) & ~(size_t)255;
+    need = need < least_bytes ? need : least_bytes;
     if (!workspace) { set_error("workspace is NULL, %zu bytes needed", need); return SPECATTN_EWORKSPACE; }
     if (reinterpret_cast<uintptr_t>(workspace) % 256) { set_error("workspace must be 256-byte aligned"); return SPECATTN_EWORKSPACE; }
     if (workspace_bytes < need) { set_error("workspace has %zu bytes, %zu needed", workspace_bytes, need); return SPECATTN_EWORKSPACE; }
-    const int pairs = m * n;
-    const int64_t per_layer = (int64_t)rows * L;
-    const KlPlan plan = kl_plan(m, n, per_layer);
+    const KlPlan plan = kl_plan(m, n, per_layer, (int64_t)(workspace_bytes / ((size_t)pairs * sizeof(double))));
     specattn_status st = layer_map_configure();
     if (st != SPECATTN_OK) return st;
     hipStream_t hs = static_cast<hipStream_t>(stream);

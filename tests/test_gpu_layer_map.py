@@ -148,3 +148,15 @@ def test_whole_mapping_on_synthetic_models():
     # the value reached by the GPU's map, evaluated on the oracle's matrix, is the oracle's optimum
     assert abs(sum(S_ref[got[j], j] for j in range(32)) - v_ref) <= 1e-9 * abs(v_ref)
     print("f =", got.tolist())
+
+
+def test_similarity_in_a_small_workspace():
+    """Room for two chunks per layer pair (4 x 256 workgroups over 704 pairs): accepted, in longer chunks; less is not."""
+    ad, av = W.layer_attention_maps(seed=12, m=22, n=32, rows=8, L=2048)
+    S = torch.full((22, 32), float("nan"), dtype=torch.float64, device="cuda")
+    ws = sa.alloc_workspace(22 * 32 * 2 * 8)
+    sa.specattn_layer_similarity(dev(ad), dev(av), S, ws)
+    torch.cuda.synchronize()
+    close(S.cpu().numpy(), oracle.layer_similarity_fast(ad, av))
+    with pytest.raises(RuntimeError, match="needed"):
+        sa.specattn_layer_similarity(dev(ad), dev(av), S, ws[:22 * 32 * 8])

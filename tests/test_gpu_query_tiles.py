@@ -34,7 +34,13 @@ def tol(w):
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("G,T", [(1, 1), (2, 8), (17, 1), (4, 8), (11, 3), (8, 6), (7, 7), (8, 8), (13, 5), (16, 8)])
 def test_query_rows_around_the_tiles(d, G, T, dtype):
-    # 1, 16, 17, 32, 33, 48, 49 and 64 query rows in one launch; 65 and 128 in two shares of heads
+    # 1, 16, 17, 32, 33, 48, 49 and 64 query rows in one launch; 65 and 128 in two shares of heads (d = 128 only)
+    if d == 64 and G * T > 64:
+        z = torch.zeros((1, 2 * G, T, d), dtype=torch.bfloat16, device="cuda")
+        a = sa.attn_args(z, z[:, :2], z[:, :2], out=z.float(), indices=None, counts=None)
+        with pytest.raises(RuntimeError, match="query rows"):
+            sa.specattn_sparse_decode_attn(a)
+        return
     w = W.llama8b_layer(seed=G * T, B=2, n=900, H_q=2 * G, H_kv=2, T=T, d=d, dtype=dtype)
     mask = oracle.topp_select(w.probs.reshape(-1, w.n), w.top_p).mask().reshape(w.B, w.H_kv, w.n)
     q, k, v = kv_tensors(w)
@@ -94,3 +100,43 @@ def test_small_workspace(shape):
     sa.specattn_sparse_decode_attn_static(sa.attn_args(q, k, v, out=out, indices=idx, counts=cnt))
     torch.cuda.synchronize()
     assert row_rel_err(out.cpu().numpy(), oracle_attention(w, mask)[0]) <= TOL["bf16"]
+
+
+def generic_bytes(w, capacity):
+    rows, splits = w.B * w.H_kv, max(1, min(-(-1024 // (w.B * w.H_kv)), -(-capacity // 256), 64))
+    return -(-rows * splits * (w.H_q // w.H_kv) * w.T * (w.d + 2) * 4 // 256) * 256
+
+
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("shape", [dict(d=64, B=1, n=1000, H_q=8, H_kv=8, T=1), dict(d=64, B=2, n=3000, H_q=16, H_kv=2, T=6),
+                                   dict(d=128, B=2, n=3000, H_q=16, H_kv=2, T=6)])
+def test_workspaces_for_two_query_tiles_are_accepted(shape, fused):
+    """64-wide heads run with room for the partials of the fp32 kernel, 128-wide ones with room for two query tiles
+    (256 workgroups plus one slot per row, and the cost prefix)."""
+    w = W.llama8b_layer(seed=4, **shape)
+    mask = oracle.topp_select(w.probs.reshape(-1, w.n), w.top_p).mask().reshape(w.B, w.H_kv, w.n)
+    q, k, v = kv_tensors(w)
+    rows = w.B * w.H_kv
+    need = generic_bytes(w, w.n)
+    if w.d == 128:
+        G, heads = w.H_q // w.H_kv, 32 // w.T
+        per = -(-G // -(-G // heads))                          # heads per launch of at most 32 query rows
+        need = max(need, 256 + (256 + rows) * -(-per * w.T // 16) * 16 * (w.d + 2) * 4)
+    probs = dev(w.probs)
+    counts = torch.zeros(rows, dtype=torch.int32, device="cuda")
+    out = torch.full(q.shape, float("nan"), dtype=torch.float32, device="cuda")
+    if fused:
+        sel = sa.select_args(probs, w.top_p, indices=None, counts=counts)
+        att = sa.attn_args(q, k, v, out=out)
+        need += sa.specattn_workspace_size(sel, att) - sa.specattn_workspace_size(None, att)
+    else:
+        idx, cnt = lists(mask)
+        att = sa.attn_args(q, k, v, out=out, indices=idx, counts=cnt)
+    ws = sa.alloc_workspace(need)
+    att.workspace, att.workspace_bytes = ws.data_ptr(), need
+    sa.specattn_fused(sel, att) if fused else sa.specattn_sparse_decode_attn(att)
+    torch.cuda.synchronize()
+    assert row_rel_err(out.cpu().numpy(), oracle_attention(w, mask)[0]) <= tol(w)
+    att.workspace_bytes = need - 256
+    with pytest.raises(RuntimeError, match="needed"):
+        sa.specattn_fused(sel, att) if fused else sa.specattn_sparse_decode_attn(att)
