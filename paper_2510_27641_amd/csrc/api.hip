@@ -241,7 +241,7 @@ specattn_status specattn_topp_select(const specattn_select_args *sel, void *work
         return launch_threshold_union(sel->probs, sel->probs_stride_b, sel->probs_stride_h, sel->B, sel->H_kv, 1, sel->n_max,
                                       sel->seq_lens, tau, valid, mflags, ws + 3 * a256, sel->indices, sel->idx_stride_row,
                                       sel->idx_capacity, sel->counts, sel->row_flags, sel->page_table, sel->page_size,
-                                      sel->max_pages_per_seq, sel->emit_physical, hs);
+                                      sel->max_pages_per_seq, sel->emit_physical, nullptr, hs);
     }
     if (sel->bisect_iters > 0) {                    // Algorithm 2 as the paper runs it, then the mask and compaction passes
         // workspace: [tau][valid][flags][block counts][ballots], the layout of the union with one member per row
@@ -256,7 +256,7 @@ specattn_status specattn_topp_select(const specattn_select_args *sel, void *work
         return launch_threshold_union(sel->probs, sel->probs_stride_b, sel->probs_stride_h, sel->B, sel->H_kv, 1, sel->n_max,
                                       sel->seq_lens, tau, valid, mflags, ws + 3 * a256, sel->indices, sel->idx_stride_row,
                                       sel->idx_capacity, sel->counts, sel->row_flags, sel->page_table, sel->page_size,
-                                      sel->max_pages_per_seq, sel->emit_physical, hs);
+                                      sel->max_pages_per_seq, sel->emit_physical, nullptr, hs);
     }
     if (sel->chunk_size > 1) {                      // reduce to chunk masses, then select over those
         const int cs = log2i(sel->chunk_size);
@@ -298,7 +298,8 @@ static specattn_status check_union(const specattn_union_args *u)
 size_t specattn_union_workspace_size(const specattn_union_args *u)
 {
     if (!u || u->B <= 0 || u->H_draft <= 0 || u->S <= 0 || u->H_kv <= 0 || u->n_max <= 0 || u->H_draft % u->H_kv) return 0;
-    return union_workspace_bytes(u->B, u->H_kv, (u->H_draft / u->H_kv) * u->S, u->n_max);
+    const int M = (u->H_draft / u->H_kv) * u->S;
+    return union_workspace_bytes(u->B, u->H_kv, M, u->n_max) + union_masks_bytes(u->B, u->H_kv, M, u->n_max);
 }
 
 specattn_status specattn_topp_select_union(const specattn_union_args *u, void *workspace, size_t workspace_bytes,
@@ -307,9 +308,10 @@ specattn_status specattn_topp_select_union(const specattn_union_args *u, void *w
     clear_error();
     specattn_status st = check_union(u);
     if (st != SPECATTN_OK) return st;
-    st = check_workspace(workspace, workspace_bytes, specattn_union_workspace_size(u));
+    // (accepted without room for the members' kept bits: the rows are then read a second time)
+    st = check_workspace(workspace, workspace_bytes, union_workspace_bytes(u->B, u->H_kv, (u->H_draft / u->H_kv) * u->S, u->n_max));
     if (st != SPECATTN_OK) return st;
-    return launch_union(u, workspace, static_cast<hipStream_t>(stream));
+    return launch_union(u, workspace, workspace_bytes, static_cast<hipStream_t>(stream));
 }
 
 specattn_status specattn_sparse_decode_attn(const specattn_attn_args *attn, void *stream)

@@ -120,3 +120,35 @@ def test_union_feeds_sparse_attention():
     torch.cuda.synchronize()
     o_ref, _ = oracle_attention(w, ref.mask().reshape(2, 8, 6000))
     assert row_rel_err(out.cpu().numpy(), o_ref) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("n,S,H_d,capacity", [(1, 2, 2, 1), (127, 3, 2, 127), (4095, 2, 4, 4095), (4096, 17, 2, 900), (65535, 2, 2, 65535),
+                                              (65537, 2, 2, 65537), (66000, 3, 4, 20000)])
+def test_both_routes_give_the_same_lists(n, S, H_d, capacity):
+    """From the members' kept bits (segments of 4096 positions, more from 16 of them on) and, in a workspace without room
+    for the bits, from the rows: the same bytes, paged and not."""
+    rng = np.random.default_rng(n)
+    lens = np.array([n, max(1, n // 3)], dtype=np.int32)
+    probs = dev(W.draft_step_probs(rng, 2, H_d, S, n, lens=lens))
+    sl = dev(lens)
+    pages = -(-n // W.PAGE_SIZE)
+    table = dev(rng.permutation(2 * pages).astype(np.int32).reshape(2, pages))
+    for physical in (False, True):
+        got = []
+        for room in (True, False):
+            idx = torch.full((4, capacity), -7, dtype=torch.int32, device="cuda")
+            counts = torch.full((4,), -7, dtype=torch.int32, device="cuda")
+            flags = torch.full((4,), -7, dtype=torch.int32, device="cuda")
+            a = sa.union_args(probs, 0.9, 2, indices=idx, counts=counts, row_flags=flags, seq_lens=sl,
+                              page_table=table if physical else None, page_size=W.PAGE_SIZE if physical else 0, emit_physical=physical)
+            masks = -(-4 * (H_d // 2) * S * -(-n // 1024) * 128 // 256) * 256
+            need = sa.specattn_union_workspace_size(a)
+            ws = sa.alloc_workspace(need if room else need - masks)
+            ws.fill_(0xA5)
+            sa.specattn_topp_select_union(a, ws)
+            torch.cuda.synchronize()
+            got.append((idx.cpu().numpy(), counts.cpu().numpy(), flags.cpu().numpy()))
+        assert all(np.array_equal(x, y) for x, y in zip(*got))
+        assert (got[0][1] > 0).all()
+        with pytest.raises(RuntimeError, match="needed"):
+            sa.specattn_topp_select_union(a, ws[:ws.numel() - 256])
