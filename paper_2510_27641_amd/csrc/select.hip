@@ -24,6 +24,8 @@ constexpr int CNT_SHIFT = 44;                 // counter = count << 44 | sum of 
 constexpr unsigned long long CNT_ONE = 1ull << CNT_SHIFT;
 constexpr unsigned long long SIG_MASK = CNT_ONE - 1;
 
+typedef uint32_t u32x4a __attribute__((ext_vector_type(4), aligned(4)));   // 16-byte load from any float's address
+
 struct LocSlot {                 // a candidate outcome of one locate step
     unsigned long long packed;
     double m_above;
@@ -245,7 +247,6 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
     len = (len + (1 << a.chunk_shift) - 1) >> a.chunk_shift;     // rows of chunk masses: length in chunks
     len = len > a.n_max ? a.n_max : len;
     const float *row = a.probs + (int64_t)b * a.stride_b + (int64_t)h * a.stride_h;
-    const bool aligned = (reinterpret_cast<uintptr_t>(row) & 15) == 0;
     const int n_items = (len + ITEM - 1) / ITEM;
 
     // -0.0 is zero; negative, infinite and NaN entries make the row invalid.  Branch-free: the largest bit pattern
@@ -258,25 +259,23 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
         return x < 0x7f7fffffu ? x : 0x7f7fffffu;
     };
     auto clean4 = [&](uint4 u) -> uint4 { return make_uint4(clean(u.x), clean(u.y), clean(u.z), clean(u.w)); };
-    // Slow form of an item's load (rows that are not 16-byte aligned or hold fewer than four entries).
+    // Slow form of an item's load (rows of fewer than four entries).
     auto load_item = [&](int i) -> uint4 {
         const int p = (i * THREADS + tid) * 4;
         uint4 u = make_uint4(0, 0, 0, 0);
-        if (p + 3 < len && aligned) {
-            u = *reinterpret_cast<const uint4 *>(row + p);
-        } else {
-            if (p < len) u.x = __float_as_uint(row[p]);
-            if (p + 1 < len) u.y = __float_as_uint(row[p + 1]);
-            if (p + 2 < len) u.z = __float_as_uint(row[p + 2]);
-            if (p + 3 < len) u.w = __float_as_uint(row[p + 3]);
-        }
+        if (p < len) u.x = __float_as_uint(row[p]);
+        if (p + 1 < len) u.y = __float_as_uint(row[p + 1]);
+        if (p + 2 < len) u.z = __float_as_uint(row[p + 2]);
+        if (p + 3 < len) u.w = __float_as_uint(row[p + 3]);
         return clean4(u);
     };
     // Fast form: every thread issues plain 16-byte loads with nothing between them that waits for data, so
-    // all of a thread's loads are in flight together.  An item that reaches past the row's end loads the
+    // all of a thread's loads are in flight together.  They need no more than the 4-byte alignment of a float: the rows
+    // of an odd length start anywhere (entry by entry, as such rows used to be read, 64 rows of 13001 took 16.6 us, and
+    // 14.5 us now).  An item that reaches past the row's end loads the
     // row's last whole vector instead (in bounds) and is masked afterwards; the at most three entries behind
     // the last whole vector are fetched once, by the thread that owns them.
-    const bool vec_ok = aligned && len >= 4;                   // uniform
+    const bool vec_ok = len >= 4;                              // uniform
     const int last4 = (len - 4) & ~3;                          // start of the row's last whole vector
     const int tail_p = (len & 3) ? (len & ~3) : -1;            // start of the partial vector, if any
     uint4 tailv = make_uint4(0, 0, 0, 0);
@@ -288,8 +287,7 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
     auto raw_load = [&](int i) -> uint4 {
         const int p = (i * THREADS + tid) * 4;
         // streaming load: a row is read once and should not displace anything in the caches
-        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-        const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(row + (p < last4 ? p : last4)));
+        const u32x4a v = __builtin_nontemporal_load(reinterpret_cast<const u32x4a *>(row + (p < last4 ? p : last4)));
         return make_uint4(v.x, v.y, v.z, v.w);
     };
     auto finish_item = [&](int i, uint4 u) -> uint4 {
@@ -706,14 +704,14 @@ __global__ __launch_bounds__(MW_THREADS) void mw_pass_kernel(MwLaunch w)
     for (int k = tid; k < NB; k += MW_THREADS) sh.hist[k] = 0ull;
     __syncthreads();
     const float *row = a.probs + (int64_t)b * a.stride_b + (int64_t)h * a.stride_h;
-    const bool aligned = (reinterpret_cast<uintptr_t>(row) & 15) == 0;
     bool bad = false;
     int p_end = (sl + 1) * w.slice_len;
     p_end = p_end > len ? len : p_end;
     for (int p = sl * w.slice_len + tid * 4; p < p_end; p += MW_THREADS * 4) {
         uint4 u = make_uint4(0, 0, 0, 0);
-        if (p + 3 < len && aligned) {
-            u = *reinterpret_cast<const uint4 *>(row + p);
+        if (p + 3 < len) {
+            const u32x4a v = *reinterpret_cast<const u32x4a *>(row + p);
+            u = make_uint4(v.x, v.y, v.z, v.w);
         } else {
             if (p < len) u.x = __float_as_uint(row[p]);
             if (p + 1 < len) u.y = __float_as_uint(row[p + 1]);
@@ -804,9 +802,10 @@ __global__ __launch_bounds__(256) void chunk_mass_kernel(const float *__restrict
         if (u > 0x80000000u || (u & 0x7fffffffu) >= 0x7f800000u) bad = true;     // negative, infinite or NaN
         sum += (double)x;
     };
-    if (p1 == p0 + chunk && chunk >= 4 && (reinterpret_cast<uintptr_t>(row + p0) & 15) == 0) {
+    if (p1 == p0 + chunk && chunk >= 4) {
+        typedef float f32x4a __attribute__((ext_vector_type(4), aligned(4)));
         for (int p = p0; p < p1; p += 4) {
-            const float4 v = *reinterpret_cast<const float4 *>(row + p);
+            const f32x4a v = *reinterpret_cast<const f32x4a *>(row + p);
             add(v.x); add(v.y); add(v.z); add(v.w);
         }
     } else {
@@ -880,17 +879,28 @@ specattn_status launch_select_multi_wg(const SelectLaunch &a, void *scratch, flo
 
 specattn_status launch_select(const SelectLaunch &a, hipStream_t stream)
 {
-    const int n = a.n_max;
-    // Many rows: small workgroups, several per CU, so that one row's load overlaps another row's
-    // passes.  Few rows: as many threads per row as its length allows, for latency.
-    const bool many = a.B * a.H_kv >= 2 * cu_count();
-    // block counts are per 1024 positions, so every variant has THREADS*4 a multiple of 1024
+    const int n = a.n_max, rows = a.B * a.H_kv, cus = cu_count();
+    // Workgroups of 256 / 512 / 1024 threads run four (at up to 8 vectors a thread) / three to two / one to a CU.  Few rows:
+    // as many threads as shorten a row's passes (512; 1024 from 8193 entries on, while every row has a CU of its own).
+    // Many rows: the shape that fits most rows on the chip at once, so that one row's load overlaps another row's passes.
+    // Block counts are per 1024 positions, so every variant has THREADS*4 a multiple of 1024.
+    // Measured, us (256 CUs; shape: time):
+    //   2044 x 64 rows      512x1 8.1, 256x2 8.9;        2044 x 1024   512x1 16.1, 256x2 13.2
+    //   4096 x 128          512x2 9.2, 256x4 10.9;       4096 x 1024   512x2 18.9, 256x4 17.2
+    //   8192 x 512          512x4 14.9, 256x8 16.8;      6001 x 1024   512x4 22.1, 256x8 21.3 (one round of four to a CU);
+    //   8192 x 1536         512x4 32.0, 256x8 35.5
+    //   16384 x 256         1024x4 15.5, 512x8 16.0;     13001 x 384   1024x4 25.3, 512x8 19.0, 256x16 23.6
+    //   13001 x 2048        512x8 62.6, 256x16 58.1;     16384 x 2048  512x8 69.5, 256x16 72.6 (no vector of 512x8 idle)
+    //   32768 x 256         1024x8 25.2, 512x16 29.7;    32768 x 512   1024x8 49.1, 512x16 39.9
     if (n <= 1024) return launch_one<256, 1, true>(a, stream);
-    if (n <= 2048) return launch_one<256, 2, true>(a, stream);
-    if (n <= 4096) return launch_one<256, 4, true>(a, stream);
-    if (n <= 8192) return many ? launch_one<256, 8, true>(a, stream) : launch_one<512, 4, true>(a, stream);
-    if (n <= 16384) return many ? launch_one<256, 16, true>(a, stream) : launch_one<1024, 4, true>(a, stream);
-    if (n <= 32768) return many ? launch_one<512, 16, true>(a, stream) : launch_one<1024, 8, true>(a, stream);
+    if (n <= 2048) return rows <= 2 * cus ? launch_one<512, 1, true>(a, stream) : launch_one<256, 2, true>(a, stream);
+    if (n <= 4096) return rows <= 2 * cus ? launch_one<512, 2, true>(a, stream) : launch_one<256, 4, true>(a, stream);
+    if (n <= 8192) return rows > 3 * cus && rows <= 4 * cus ? launch_one<256, 8, true>(a, stream) : launch_one<512, 4, true>(a, stream);
+    if (n <= 16384) {
+        if (rows <= cus) return launch_one<1024, 4, true>(a, stream);
+        return rows <= 2 * cus || n > 15360 ? launch_one<512, 8, true>(a, stream) : launch_one<256, 16, true>(a, stream);
+    }
+    if (n <= 32768) return rows > cus ? launch_one<512, 16, true>(a, stream) : launch_one<1024, 8, true>(a, stream);
     if (n <= 65536) return launch_one<1024, 16, true>(a, stream);
     return launch_one<1024, 1, false>(a, stream);
 }

@@ -22,6 +22,8 @@ constexpr int U_ITERS = 4;                                  // float4 loads per 
 constexpr int U_BLOCK = U_THREADS * 4 * U_ITERS;            // 4096 positions per workgroup
 constexpr int U_WORDS = U_ITERS * U_WAVES * 4;              // ballots per block: [iter][wave][component]
 
+typedef float f32x4a __attribute__((ext_vector_type(4), aligned(4)));   // 16-byte load from any float's address
+
 struct UnionLaunch {
     const float *probs;
     int64_t stride_b, stride_m;     // elements between sequences / between consecutive member rows
@@ -59,13 +61,12 @@ __global__ __launch_bounds__(U_THREADS) void union_mask_kernel(UnionLaunch a)
         if (a.mcounts[m0 + m] <= 0) continue;                 // invalid member rows keep nothing (uniform)
         const int t = __float_as_int(a.tau[m0 + m]);         // > 0 for every valid row: zeros are never kept
         const float *row = rows + (int64_t)m * a.stride_m;
-        const bool aligned = (reinterpret_cast<uintptr_t>(row) & 15) == 0;
 #pragma unroll
         for (int it = 0; it < U_ITERS; ++it) {
             const int p = blk * U_BLOCK + it * U_THREADS * 4 + tid * 4;
-            float4 v = make_float4(-1.f, -1.f, -1.f, -1.f);   // positions past the row's end: below any threshold
-            if (p + 3 < len && aligned) {
-                v = *reinterpret_cast<const float4 *>(row + p);
+            f32x4a v = {-1.f, -1.f, -1.f, -1.f};              // positions past the row's end: below any threshold
+            if (p + 3 < len) {
+                v = *reinterpret_cast<const f32x4a *>(row + p);
             } else {
                 if (p < len) v.x = row[p];
                 if (p + 1 < len) v.y = row[p + 1];

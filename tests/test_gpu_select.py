@@ -244,3 +244,29 @@ def test_split_path_paged_physical_output():
     to_phys = lambda r, pos: w.page_table[r // H, pos // W.PAGE_SIZE] * W.PAGE_SIZE + pos % W.PAGE_SIZE
     flagged, mism = compare_select(got, ref, to_physical=to_phys)
     assert mism == 0
+
+
+@pytest.mark.parametrize("rows,n", [(8, 2047), (520, 2048), (8, 4093), (520, 4095), (9, 8191), (800, 6001), (8, 16383), (300, 16381),
+                                    (520, 13001), (520, 15361), (300, 20001), (8, 32767), (5, 40001)])
+def test_thread_shapes_and_rows_at_any_address(rows, n):
+    """Every shape of workgroup that the row count and the row length lead to, on rows that start at any multiple of four
+    bytes (odd lengths): lists, thresholds, bits and block counts."""
+    rng = np.random.default_rng(n)
+    probs = W.draft_probs(rng, rows, n).reshape(1, rows, n)
+    probs[0, 1, n - 1] = 0.5                                   # the entry behind the last whole vector
+    probs[0, 2, 3] = -0.0
+    got = gpu_select(probs, 0.93, split=False)
+    ref = oracle.topp_select(probs.reshape(-1, n), 0.93)
+    assert compare_select(got, ref)[1] == 0
+    p = dev(probs)
+    blocks = -(-n // 1024)
+    counts = torch.zeros(rows, dtype=torch.int32, device="cuda")
+    bc = torch.full((rows, blocks), -1, dtype=torch.int32, device="cuda")
+    bits = torch.full((rows, blocks * 32), -1, dtype=torch.int32, device="cuda")
+    sa.specattn_topp_select(sa.select_args(p, 0.93, indices=None, counts=counts, block_counts=bc, kept_mask=bits))
+    torch.cuda.synchronize()
+    kept = np.unpackbits(bits.cpu().numpy().view(np.uint8), axis=1, bitorder="little")
+    assert np.array_equal(kept.sum(1), got["counts"]) and not kept[:, n:].any()
+    assert np.array_equal(kept.reshape(rows, blocks, 1024).sum(2), bc.cpu().numpy())
+    for r in (0, 1, 2, rows - 1):
+        assert np.array_equal(np.flatnonzero(kept[r]), got["indices"][r, :got["counts"][r]])
