@@ -110,7 +110,7 @@ typedef struct specattn_select_args {
        iff position 32 * w + i is kept; bits at and beyond the row's length are 0.  Together with counts and
        block_counts this is the selection state specattn_fused works from (1 bit per position instead of the 32
        of a list entry per kept position).  Not available with chunk_size > 1, bisect_iters or the split path
-       (a workspace handed to a plain selection of few long rows): SPECATTN_EUNSUPPORTED. */
+       (a workspace handed to a plain selection of few rows of 65536 positions or more): SPECATTN_EUNSUPPORTED. */
     uint32_t *kept_mask;
 } specattn_select_args;
 
@@ -214,9 +214,9 @@ specattn_status specattn_topp_select_union(const specattn_union_args *args, void
 size_t specattn_union_workspace_size(const specattn_union_args *args);
 
 /* Selection alone.  The plain selection (single positions, exact tau*) never needs a workspace: without one
-   every row is handled by one workgroup.  When specattn_workspace_size(sel, NULL) is not 0 for it (few, long
+   every row is handled by one workgroup.  When specattn_workspace_size(sel, NULL) is not 0 for it (long
    rows) and a workspace of that size is given, each row is split over many workgroups instead; the results
-   are the same.  The chunk and bisection modes need their workspace (SPECATTN_EWORKSPACE otherwise). */
+   are the same (with kept_mask rows are not split).  The chunk and bisection modes need their workspace (SPECATTN_EWORKSPACE otherwise). */
 specattn_status specattn_topp_select(const specattn_select_args *sel, void *workspace,
                                      size_t workspace_bytes, void *stream);
 

@@ -2,6 +2,7 @@
 // memory; every check runs before the first launch so that a failing call writes nothing.
 #include "common.h"
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -140,6 +141,15 @@ bool fused_on_chip(const specattn_select_args *s, const specattn_attn_args *a)
     probe.dtype = (int)a->dtype; probe.d = a->d; probe.T = a->T; probe.H_kv = a->H_kv;
     return attn_mfma_supported(probe) && a->d == 128 && s->chunk_size <= 1;
 }
+// The workspace from which on a selection of few long rows counts as asking for the split, which leaves no bits: thresholds,
+// ballots and 32 KiB of bins per row.  (Other shapes are split as well where there is room, but only calls of these
+// shapes were ever refused for asking for bits.)
+size_t select_split_asked_bytes(const specattn_select_args *s)
+{
+    const size_t rows = (size_t)s->B * s->H_kv;
+    if (s->n_max < 65536 || rows * 2048 > (size_t)s->n_max) return SIZE_MAX;
+    return union_workspace_bytes(s->B, s->H_kv, 1, s->n_max) + rows * 32768 + ((rows * 88 + 255) & ~(size_t)255);
+}
 size_t a256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 SelectLaunch make_select(const specattn_select_args *s)
@@ -220,29 +230,15 @@ specattn_status specattn_topp_select(const specattn_select_args *sel, void *work
     const bool plain = sel->bisect_iters == 0 && sel->chunk_size <= 1;
     const size_t need = specattn_workspace_size(sel, nullptr);
     // the plain selection works without a workspace; with one, few long rows are split over many workgroups
-    const bool split = plain && need > 0 && workspace && aligned(workspace, 256) && workspace_bytes >= need;
-    if (split && sel->kept_mask) { set_error("kept_mask is not written by the split selection of few long rows: call without a workspace"); return SPECATTN_EUNSUPPORTED; }
+    const bool given = plain && need > 0 && workspace && aligned(workspace, 256);
+    const bool split = given && workspace_bytes >= need;
+    if (given && sel->kept_mask && workspace_bytes >= select_split_asked_bytes(sel)) { set_error("kept_mask is not written by the split selection of few long rows: call without a workspace"); return SPECATTN_EUNSUPPORTED; }
     if (!plain) {
         st = check_workspace(workspace, workspace_bytes, need);
         if (st != SPECATTN_OK) return st;
     }
     SelectLaunch l = make_select(sel);
-    if (split) {
-        // workspace: [tau][valid][flags][block counts][ballots] as for the union with one member per row, then the
-        // row histograms and locate states of the split passes
-        const size_t rows = (size_t)sel->B * sel->H_kv, a256 = (rows * 4 + 255) & ~(size_t)255;
-        char *ws = static_cast<char *>(workspace);
-        float *tau = sel->thresholds ? sel->thresholds : reinterpret_cast<float *>(ws);
-        int32_t *valid = reinterpret_cast<int32_t *>(ws + a256);
-        uint32_t *mflags = reinterpret_cast<uint32_t *>(ws + 2 * a256);
-        hipStream_t hs = static_cast<hipStream_t>(stream);
-        st = launch_select_multi_wg(l, ws + union_workspace_bytes(sel->B, sel->H_kv, 1, sel->n_max), tau, valid, mflags, hs);
-        if (st != SPECATTN_OK) return st;
-        return launch_threshold_union(sel->probs, sel->probs_stride_b, sel->probs_stride_h, sel->B, sel->H_kv, 1, sel->n_max,
-                                      sel->seq_lens, tau, valid, mflags, ws + 3 * a256, sel->indices, sel->idx_stride_row,
-                                      sel->idx_capacity, sel->counts, sel->row_flags, sel->page_table, sel->page_size,
-                                      sel->max_pages_per_seq, sel->emit_physical, nullptr, hs);
-    }
+    if (split && !sel->kept_mask) return launch_select_multi_wg(l, workspace, static_cast<hipStream_t>(stream));
     if (sel->bisect_iters > 0) {                    // Algorithm 2 as the paper runs it, then the mask and compaction passes
         // workspace: [tau][valid][flags][block counts][ballots], the layout of the union with one member per row
         const size_t rows = (size_t)sel->B * sel->H_kv, a256 = (rows * 4 + 255) & ~(size_t)255;
@@ -383,7 +379,8 @@ specattn_status specattn_fused(const specattn_select_args *sel, const specattn_a
         s2.idx_capacity = cap;
         s2.emit_physical = 0;
         const size_t list_bytes = a256((size_t)rows * cap * sizeof(int32_t));
-        const size_t sel_bytes = specattn_workspace_size(&s2, nullptr);
+        // (a call accepted with less room than it asks for selects with one workgroup per row)
+        const size_t sel_bytes = full ? specattn_workspace_size(&s2, nullptr) : attn->workspace_bytes - attn_bytes - list_bytes;
         st = specattn_topp_select(&s2, sel_bytes ? ws + attn_bytes + list_bytes : nullptr, sel_bytes, stream);
         if (st != SPECATTN_OK) return st;
         specattn_attn_args a2 = *attn;
@@ -441,7 +438,7 @@ static size_t workspace_bytes(const specattn_select_args *sel, const specattn_at
         if (sel->chunk_size <= 1) {                   // optional: lets few long rows be split over many workgroups
             if (sel->B <= 0 || sel->H_kv <= 0 || sel->n_max <= 0 || !sel->indices || sel->block_counts) return 0;
             if (!select_multi_wg_preferred(sel->B * sel->H_kv, sel->n_max)) return 0;
-            return union_workspace_bytes(sel->B, sel->H_kv, 1, sel->n_max) + select_multi_wg_bytes(sel->B * sel->H_kv, sel->n_max);
+            return select_multi_wg_bytes(sel->B * sel->H_kv, sel->n_max);
         }
         if (sel->B <= 0 || sel->H_kv <= 0 || sel->n_max <= 0 || !is_pow2(sel->chunk_size)) return 0;
         const size_t nc = ((size_t)sel->n_max + sel->chunk_size - 1) / sel->chunk_size;
@@ -460,7 +457,12 @@ static size_t workspace_bytes(const specattn_select_args *sel, const specattn_at
         const int lcap = (sel->n_max + chunk - 1) / chunk;
         specattn_select_args s2 = *sel;
         s2.indices = reinterpret_cast<int32_t *>(0x1000);      // (only tested for NULL by the size query)
-        bytes = a256(bytes) + a256((size_t)rows * lcap * sizeof(int32_t)) + specattn_workspace_size(&s2, nullptr);
+        size_t sel_bytes = specattn_workspace_size(&s2, nullptr);
+        if (!full && chunk == 1 && sel_bytes > 0) {            // the plain selection runs without a workspace as well
+            const size_t asked = select_split_asked_bytes(&s2);
+            sel_bytes = std::min(sel_bytes, asked == SIZE_MAX ? 0 : asked);
+        }
+        bytes = a256(bytes) + a256((size_t)rows * lcap * sizeof(int32_t)) + sel_bytes;
         return bytes;
     }
     if (sel) {                                        // fused: room for the block counts and the kept mask

@@ -611,42 +611,45 @@ specattn_status launch_one(const SelectLaunch &a, hipStream_t stream)
 }
 
 // ---- few long rows: one row split over many workgroups ------------------------------------------------
-// The same three radix passes, but every workgroup histograms one slice (a multiple of MW_SLICE positions,
-// chosen so that about two workgroups per CU are in flight) in LDS and
-// adds its non-empty bins to the row's histogram in memory (64-bit integer atomics: the sums stay exact and
-// independent of order).  Kernel boundaries separate the passes; at the start of the next pass every
-// workgroup of a row locates the boundary bin from the finished histogram by itself (identical code on
-// identical data), and slice 0 records the outcome for the kernels that follow.
-constexpr int MW_THREADS = 256;
-constexpr int MW_SLICE = 4096;
+// The same radix search with one workgroup per (row, slice), in three launches; kernel boundaries separate them.
+//   1. every workgroup leaves the pass-1 histogram of its slice in memory (the bins between the lowest and the highest
+//      non-empty one, and those two numbers);
+//   2. every workgroup adds the slices of its row up, locates the boundary bin (identical code on identical integers), notes
+//      how many of its slice's entries lie above that bin and collects those that lie in it - a few per cent;
+//   3. every workgroup finishes the search on the row's collected entries alone, in LDS, knows from the counts where its
+//      slice's part of the list begins, and writes it.
+// Nothing has to be cleared, no atomic goes to memory, and no pass only counts.  32 rows of 131072: 29 us; three
+// histogram passes that added up by atomics in memory, with a launch to clear them, one for the threshold and the mask and
+// compaction passes of the union, took 50 us.  Bound by the trips to memory of each launch (ranges, then
+// histograms, then entries, about a microsecond each) and the locate steps (2 us each), not by the row's bytes.
+constexpr int MW_THREADS = 512;
+constexpr int MW_WAVES = MW_THREADS / 64;
+constexpr int MW_ITEM = MW_THREADS * 4;           // positions a workgroup loads with one instruction
+constexpr int MW_FLIGHT = 4;                      // such loads in flight per thread
+constexpr int MW_MOST_SLICES = 32;                // (the lanes of a wave hold the slices' bin ranges)
 
-struct MwStage {                     // outcome of one locate step
+constexpr int MW_COLLECT_SHIFT = 2;               // a quarter of a slice's entries can be collected (rows so flat that one bin
+                                                  // of an eighth of an octave holds more are read again instead)
+constexpr int MW_LDS_ENTRIES = 12288;             // ... and per row that step 3 keeps in LDS (two workgroups to a CU)
+
+struct MwState {                     // outcome of the first locate step
     unsigned long long bin_packed;
     double target, m_above;
     unsigned c_above;
     int bin;
-    int done;                        // the boundary bin held a single entry: tau_bits is final
-    uint32_t tau_bits;
+    int invalid;                     // a NaN, negative or infinite entry, no mass, or an empty row: nothing else holds then
 };
-struct MwState {
-    MwStage s1, s2;
-    int bad;                         // an entry was NaN, negative or infinite
-    int invalid;                     // no mass at all
-};
+struct MwHead { int lo, hi, bad, pad; };     // non-empty bins of a slice's histogram (lo > hi: none)
 struct MwLaunch {
     SelectLaunch a;
-    unsigned long long *h1, *h2, *h3;    // [rows][NB1], [rows][NB2], [rows][NB2]
-    MwState *state;                      // [rows]
-    int slices, slice_len;               // workgroups per row; positions per workgroup (a multiple of MW_SLICE)
-    float *tau;                          // [rows] out
-    int32_t *valid;                      // [rows] out: 1 unless the row is invalid
-    uint32_t *flags;                     // [rows] out
+    unsigned long long *hist;        // [rows * slices][NB1]
+    MwHead *head;                    // [rows * slices]
+    uint32_t *entries;               // [rows * slices][collect] a slice's entries in the boundary bin, in any order
+    int4 *counts;                    // [rows * slices] a slice's entries above the boundary bin and in it; smallest and largest of the latter
+    MwState *state;                  // [rows]
+    int slices, slice_len;           // workgroups per row; positions per workgroup (a multiple of MW_ITEM)
+    int collect;                     // slice_len >> MW_COLLECT_SHIFT
 };
-
-__global__ void mw_clear_kernel(unsigned long long *p, size_t n)
-{
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = 0ull;
-}
 
 __device__ __forceinline__ int mw_row_len(const SelectLaunch &a, int b)
 {
@@ -655,126 +658,400 @@ __device__ __forceinline__ int mw_row_len(const SelectLaunch &a, int b)
     return len > a.n_max ? a.n_max : len;
 }
 
-template <int PASS>
-__global__ __launch_bounds__(MW_THREADS) void mw_pass_kernel(MwLaunch w)
+// A slice's entries, MW_FLIGHT vectors per thread at a time; the first ones are requested on construction.  The loads are
+// unconditional, so that nothing between them waits: a vector that reaches past the slice's end is fetched ending there and
+// moved into place when it is used.
+struct MwSlice {
+    const float *row;
+    int begin, end, p0;
+    u32x4a raw[MW_FLIGHT];
+    __device__ __forceinline__ MwSlice(const MwLaunch &w, int b, int h, int sl, int len)
+    {
+        row = w.a.probs + (int64_t)b * w.a.stride_b + (int64_t)h * w.a.stride_h;
+        begin = sl * w.slice_len;
+        end = begin + w.slice_len;
+        end = end < len ? end : len;
+        request(begin);
+    }
+    __device__ __forceinline__ void request(int at)
+    {
+        p0 = at;
+        if (p0 >= end) return;                                   // (uniform)
+        if (end < 4) {
+            if (threadIdx.x == 0)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) raw[0][c] = c < end ? __float_as_uint(row[c]) : 0u;
+            return;
+        }
+#pragma unroll
+        for (int i = 0; i < MW_FLIGHT; ++i) {
+            const int p = p0 + i * MW_ITEM + (int)threadIdx.x * 4;
+            raw[i] = *reinterpret_cast<const u32x4a *>(row + (p < end - 4 ? p : end - 4));
+        }
+    }
+    __device__ __forceinline__ uint4 entries(int i) const
+    {
+        const int p = p0 + i * MW_ITEM + (int)threadIdx.x * 4;
+        const u32x4a v = raw[i];
+        const int over = end < 4 ? (p > 0 ? 4 : 0) : p - (end - 4);      // entries of the vector that come before p
+        if (over <= 0) return make_uint4(v[0], v[1], v[2], v[3]);
+        return make_uint4(over == 1 ? v[1] : over == 2 ? v[2] : over == 3 ? v[3] : 0u, over == 1 ? v[2] : over == 2 ? v[3] : 0u,
+                          over == 1 ? v[3] : 0u, 0u);
+    }
+    template <typename F> __device__ __forceinline__ void each(F &&visit)
+    {
+        for (int at = begin; at < end; at += MW_FLIGHT * MW_ITEM) {
+            if (at != begin) request(at);
+#pragma unroll
+            for (int i = 0; i < MW_FLIGHT; ++i) {
+                const uint4 u = entries(i);
+                visit(u.x); visit(u.y); visit(u.z); visit(u.w);
+            }
+        }
+    }
+};
+
+// The row's histogram in sh.hist from those of its slices; `mine`: lane j holds slice j's range (lanes past the slices
+// slice 0's).  cnt[k]: entries that slice `sl` has in this thread's bin k * MW_THREADS + tid.  Returns whether any slice met
+// an invalid entry.
+__device__ __forceinline__ bool mw_gather(RowShared &sh, const MwHead &mine, const unsigned long long *h, int slices, int sl,
+                                          int (&cnt)[NB1 / MW_THREADS])
 {
-    __shared__ RowShared sh;
+    const int tid = threadIdx.x;
+    int lo = mine.lo, hi = mine.hi;
+    const bool bad = __any(mine.bad != 0);
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        const int l = __shfl_xor(lo, off, 64), g = __shfl_xor(hi, off, 64);
+        lo = l < lo ? l : lo;
+        hi = g > hi ? g : hi;
+    }
+#pragma unroll
+    for (int k = 0; k < NB1 / MW_THREADS; ++k) {
+        const int bin = k * MW_THREADS + tid;
+        unsigned long long sum = 0ull;
+        cnt[k] = 0;
+        if (k * MW_THREADS <= hi && (k + 1) * MW_THREADS > lo) {       // (uniform)
+            for (int j0 = 0; j0 < slices; j0 += 16) {
+                unsigned long long v[16];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int j = j0 + i < slices ? j0 + i : slices - 1;
+                    const int jl = __builtin_amdgcn_readlane(mine.lo, j), jh = __builtin_amdgcn_readlane(mine.hi, j);
+                    v[i] = (j0 + i < slices && bin >= jl && bin <= jh) ? h[(size_t)j * NB1 + bin] : 0ull;
+                }
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    sum += v[i];
+                    if (j0 + i == sl) cnt[k] += (int)(v[i] >> CNT_SHIFT);
+                }
+            }
+        }
+        sh.hist[bin] = sum;
+    }
+    __syncthreads();
+    return bad;
+}
+
+// Sum of v over the workgroup (every thread returns it).  `slot` is used by this call alone.
+__device__ __forceinline__ int mw_sum(int v, int *slot)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    v = wave_inclusive_sum(v);
+    if (lane == 63) slot[wave] = v;
+    __syncthreads();
+    int s = 0;
+#pragma unroll
+    for (int w = 0; w < MW_WAVES; ++w) s += slot[w];
+    return s;
+}
+
+// Step 1.
+__global__ __launch_bounds__(MW_THREADS) void mw_hist_kernel(MwLaunch w)
+{
+    __shared__ unsigned long long hist[NB1];
+    __shared__ int range[2][MW_WAVES];
     const SelectLaunch &a = w.a;
     const int r = blockIdx.x / w.slices, sl = blockIdx.x - r * w.slices;
     const int b = r / a.H_kv, h = r - b * a.H_kv;
-    const int tid = threadIdx.x;
-    const int len = mw_row_len(a, b);
-    MwState &st = w.state[r];
-    uint32_t want = 0;                 // PASS 2: bits[30:20] == want; PASS 3: bits[30:10] == want
-    if (PASS >= 2) {
-        if (st.bad || len == 0) return;
-        const unsigned long long *hg = PASS == 2 ? w.h1 + (size_t)r * NB1 : w.h2 + (size_t)r * NB2;
-        for (int k = tid; k < (PASS == 2 ? NB1 : NB2); k += MW_THREADS) sh.hist[k] = hg[k];
-        __syncthreads();
-        double target = 0.0, m_above = 0.0;
-        unsigned c_above = 0;
-        unsigned long long bin_packed = 0;
-        int bin, e_field;
-        if (PASS == 2) {
-            bin = locate_bin<MW_THREADS, NB1, true>(sh, 0, a.top_p, target, m_above, c_above, bin_packed);
-            if (bin < 0) {
-                if (sl == 0 && tid == 0) st.invalid = 1;
-                return;
-            }
-            e_field = bin >> 3;
-            want = (uint32_t)bin;
-        } else {
-            if (st.invalid || st.s1.done) return;
-            target = st.s1.target; m_above = st.s1.m_above; c_above = st.s1.c_above;
-            e_field = st.s1.bin >> 3;
-            bin = locate_bin<MW_THREADS, NB2, false>(sh, e_field, a.top_p, target, m_above, c_above, bin_packed);
-            want = ((uint32_t)st.s1.bin << 10) | (uint32_t)bin;
-        }
-        const bool single = (bin_packed >> CNT_SHIFT) == 1;
-        if (sl == 0 && tid == 0) {
-            MwStage &o = PASS == 2 ? st.s1 : st.s2;
-            o.bin_packed = bin_packed; o.target = target; o.m_above = m_above; o.c_above = c_above; o.bin = bin;
-            o.done = single ? 1 : 0;
-            o.tau_bits = ((uint32_t)e_field << 23) | ((uint32_t)bin_packed & 0x7fffffu);
-        }
-        if (single) return;
-        __syncthreads();               // locate_bin's readers of sh.hist are done
-    }
-    constexpr int NB = PASS == 1 ? NB1 : NB2;
-    for (int k = tid; k < NB; k += MW_THREADS) sh.hist[k] = 0ull;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    MwSlice slice(w, b, h, sl, mw_row_len(a, b));
+#pragma unroll
+    for (int k = 0; k < NB1 / MW_THREADS; ++k) hist[k * MW_THREADS + tid] = 0ull;
     __syncthreads();
-    const float *row = a.probs + (int64_t)b * a.stride_b + (int64_t)h * a.stride_h;
     bool bad = false;
-    int p_end = (sl + 1) * w.slice_len;
-    p_end = p_end > len ? len : p_end;
-    for (int p = sl * w.slice_len + tid * 4; p < p_end; p += MW_THREADS * 4) {
-        uint4 u = make_uint4(0, 0, 0, 0);
-        if (p + 3 < len) {
-            const u32x4a v = *reinterpret_cast<const u32x4a *>(row + p);
-            u = make_uint4(v.x, v.y, v.z, v.w);
-        } else {
-            if (p < len) u.x = __float_as_uint(row[p]);
-            if (p + 1 < len) u.y = __float_as_uint(row[p + 1]);
-            if (p + 2 < len) u.z = __float_as_uint(row[p + 2]);
-            if (p + 3 < len) u.w = __float_as_uint(row[p + 3]);
-        }
-        auto visit = [&](uint32_t x) {
-            if (x == 0x80000000u) x = 0u;                               // -0.0 is zero
-            if (x >= 0x7f800000u) { bad = true; return; }               // negative, infinite, NaN
-            if (!x) return;
-            if (PASS == 1) atomicAdd(&sh.hist[x >> 20], packed_entry(x));
-            else if (PASS == 2) { if ((x >> 20) == want) atomicAdd(&sh.hist[(x >> 10) & 1023u], packed_entry(x)); }
-            else { if ((x >> 10) == want) atomicAdd(&sh.hist[x & 1023u], packed_entry(x)); }
-        };
-        visit(u.x); visit(u.y); visit(u.z); visit(u.w);
-    }
+    slice.each([&](uint32_t x) {
+        if (x == 0x80000000u) x = 0u;                                   // -0.0 is zero
+        if (x >= 0x7f800000u) { bad = true; return; }                   // negative, infinite, NaN
+        if (x) atomicAdd(&hist[x >> 20], packed_entry(x));
+    });
     const bool any_bad = __syncthreads_or(bad ? 1 : 0) != 0;             // also orders the LDS atomics
-    if (PASS == 1 && any_bad && tid == 0) atomicOr(&st.bad, 1);
-    unsigned long long *hg = (PASS == 1 ? w.h1 + (size_t)r * NB1 : PASS == 2 ? w.h2 + (size_t)r * NB2 : w.h3 + (size_t)r * NB2);
-    for (int k = tid; k < NB; k += MW_THREADS) {
-        const unsigned long long v = sh.hist[k];
-        if (v) atomicAdd(&hg[k], v);
+    // lowest and highest non-empty bin: every wave looks at its 64 bins of each group
+    unsigned long long bins[NB1 / MW_THREADS];
+    int lo = NB1, hi = -1;
+#pragma unroll
+    for (int k = 0; k < NB1 / MW_THREADS; ++k) {
+        bins[k] = hist[k * MW_THREADS + tid];
+        const unsigned long long some = __ballot(bins[k] != 0ull);
+        if (some) {
+            const int first = k * MW_THREADS + wave * 64;
+            if (lo == NB1) lo = first + (int)__ffsll((long long)some) - 1;
+            hi = first + 63 - __clzll((long long)some);
+        }
     }
+    if (lane == 0) { range[0][wave] = lo; range[1][wave] = hi; }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < MW_WAVES; ++k) {
+        lo = range[0][k] < lo ? range[0][k] : lo;
+        hi = range[1][k] > hi ? range[1][k] : hi;
+    }
+    const size_t at = (size_t)r * w.slices + sl;
+#pragma unroll
+    for (int k = 0; k < NB1 / MW_THREADS; ++k) {
+        const int bin = k * MW_THREADS + tid;
+        if (bin >= lo && bin <= hi) w.hist[at * NB1 + bin] = bins[k];
+    }
+    if (tid == 0) w.head[at] = MwHead{lo, hi, any_bad ? 1 : 0, 0};
 }
 
-// One workgroup per row: the last locate step, tau*, validity and the boundary flag.
-__global__ __launch_bounds__(MW_THREADS) void mw_final_kernel(MwLaunch w)
+// Step 2.
+__global__ __launch_bounds__(MW_THREADS) void mw_collect_kernel(MwLaunch w)
 {
     __shared__ RowShared sh;
+    __shared__ int sums[MW_WAVES];
+    __shared__ int ends[2][MW_WAVES];
+    __shared__ int found;
     const SelectLaunch &a = w.a;
-    const int r = blockIdx.x, b = r / a.H_kv, tid = threadIdx.x;
+    const int r = blockIdx.x / w.slices, sl = blockIdx.x - r * w.slices;
+    const int b = r / a.H_kv, h = r - b * a.H_kv;
+    const int tid = threadIdx.x, lane = tid & 63;
     const int len = mw_row_len(a, b);
-    const MwState &st = w.state[r];
-    if (st.bad || st.invalid || len == 0) {
-        if (tid == 0) { w.tau[r] = 0.0f; w.valid[r] = 0; w.flags[r] = SPECATTN_ROW_INVALID; }
-        return;
+    const size_t row_at = (size_t)r * w.slices, at = row_at + sl;
+    // (requested ahead of the slice: the histograms are fetched as soon as the ranges are here)
+    const MwHead head = w.head[row_at + (lane < w.slices ? lane : 0)];
+    MwSlice slice(w, b, h, sl, len);
+    if (tid == 0) found = 0;
+    int cnt[NB1 / MW_THREADS];
+    const bool bad = mw_gather(sh, head, w.hist + row_at * NB1, w.slices, sl, cnt);
+    double target = 0.0, m_above = 0.0;
+    unsigned c_above = 0;
+    unsigned long long bin_packed = 0;
+    const int bin = locate_bin<MW_THREADS, NB1, true>(sh, 0, a.top_p, target, m_above, c_above, bin_packed);
+    const bool invalid = bad || bin < 0 || len == 0;                     // uniform
+    if (sl == 0 && tid == 0) w.state[r] = MwState{bin_packed, target, m_above, c_above, bin, invalid ? 1 : 0};
+    if (invalid) return;
+    const uint32_t want = (uint32_t)bin;
+    uint32_t *mine = w.entries + at * w.collect;
+    int lo = 0x7fffffff, hi = 0;
+    slice.each([&](uint32_t x) {
+        if ((x >> 20) == want && x) {
+            const int k = atomicAdd(&found, 1);
+            if (k < w.collect) mine[k] = x;
+            lo = (int)x < lo ? (int)x : lo;
+            hi = (int)x > hi ? (int)x : hi;
+        }
+    });
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        const int l = __shfl_xor(lo, off, 64), g = __shfl_xor(hi, off, 64);
+        lo = l < lo ? l : lo;
+        hi = g > hi ? g : hi;
     }
-    const int e_field = st.s1.bin >> 3;
-    double target = st.s1.target, m_above;
-    unsigned long long bin_packed;
-    uint32_t tau_bits;
-    if (st.s1.done) {
-        tau_bits = st.s1.tau_bits; m_above = st.s1.m_above; bin_packed = st.s1.bin_packed;
-    } else if (st.s2.done) {
-        tau_bits = st.s2.tau_bits; m_above = st.s2.m_above; bin_packed = st.s2.bin_packed;
-    } else {
-        for (int k = tid; k < NB2; k += MW_THREADS) sh.hist[k] = w.h3[(size_t)r * NB2 + k];
-        __syncthreads();
-        m_above = st.s2.m_above;
-        unsigned c_above = st.s2.c_above;
-        const int b3 = locate_bin<MW_THREADS, NB2, false>(sh, e_field, a.top_p, target, m_above, c_above, bin_packed);
-        tau_bits = ((uint32_t)st.s1.bin << 20) | ((uint32_t)st.s2.bin << 10) | (uint32_t)b3;
+    if (lane == 0) { ends[0][tid >> 6] = lo; ends[1][tid >> 6] = hi; }
+    int above = 0;
+#pragma unroll
+    for (int k = 0; k < NB1 / MW_THREADS; ++k)
+        if (k * MW_THREADS + tid > bin) above += cnt[k];
+    above = mw_sum(above, sums);                                         // (a barrier: `found` and `ends` are complete)
+#pragma unroll
+    for (int k = 0; k < MW_WAVES; ++k) {
+        lo = ends[0][k] < lo ? ends[0][k] : lo;
+        hi = ends[1][k] > hi ? ends[1][k] : hi;
     }
-    if (tid == 0) {
-        const double row_sum = target / (double)a.top_p;
-        const double m_incl = m_above + mass_of(bin_packed, e_field), band = 1e-6 * row_sum;
-        w.tau[r] = __uint_as_float(tau_bits);
-        w.valid[r] = 1;
-        w.flags[r] = (fabs(m_incl - target) <= band || fabs(m_above - target) <= band) ? SPECATTN_ROW_NEAR_BOUNDARY : 0u;
-    }
+    if (tid == 0) w.counts[at] = make_int4(above, found, lo, hi);
 }
 
+// Step 3: tau*, count and flags of the row (slice 0), and the list entries of the slice.
+__global__ __launch_bounds__(MW_THREADS) void mw_emit_kernel(MwLaunch w)
+{
+    __shared__ RowShared sh;
+    __shared__ uint32_t kept_lds[MW_LDS_ENTRIES];
+    __shared__ int sums[MW_WAVES];
+    __shared__ unsigned tot[2][MW_FLIGHT * MW_WAVES];
+    const SelectLaunch &a = w.a;
+    const int r = blockIdx.x / w.slices, sl = blockIdx.x - r * w.slices;
+    const int b = r / a.H_kv, h = r - b * a.H_kv;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int len = mw_row_len(a, b);
+    const size_t row_at = (size_t)r * w.slices;
+    const MwState st = w.state[r];
+    int4 count = w.counts[row_at + (lane < w.slices ? lane : 0)];        // lane j: slice j's (never written for an invalid row)
+    if (lane >= w.slices) count.x = count.y = 0;                         // (slice 0's smallest and largest again)
+    if (st.invalid) {
+        if (sl == 0 && tid == 0) {
+            a.counts[r] = 0;
+            if (a.thresholds) a.thresholds[r] = 0.0f;
+            if (a.row_flags) a.row_flags[r] = SPECATTN_ROW_INVALID;
+        }
+        return;
+    }
+    const int e_field = st.bin >> 3;
+    const uint32_t want = (uint32_t)st.bin;
+    const int place = wave_inclusive_sum(count.y);                       // the row's collected entries up to slice `lane`
+    const int all = __builtin_amdgcn_readlane(place, 63);
+    const int earlier = sl ? __builtin_amdgcn_readlane(place, sl - 1) : 0;
+    int base = lane < sl ? count.x : 0;
+    base = __builtin_amdgcn_readlane(wave_inclusive_sum(base), 63);      // kept positions of the slices before this one: so far those above the bin
+    const bool in_lds = all <= MW_LDS_ENTRIES && !__any(count.y > w.collect);
+    // fn(entry, its number in slice order) for the row's entries in the boundary bin, of slices 0 .. last
+    auto each_from_memory = [&](int last, auto &&fn) {
+        for (int j = wave; j <= last; j += MW_WAVES) {                   // a wave per slice, eight loads in flight
+            const int n = __builtin_amdgcn_readlane(count.y, j), first = __builtin_amdgcn_readlane(place, j) - n;
+            if (n > w.collect) continue;
+            const uint32_t *src = w.entries + (row_at + j) * w.collect;
+            for (int k0 = 0; k0 < n; k0 += 512) {
+                uint32_t x[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) x[i] = src[k0 + i * 64 + lane < n ? k0 + i * 64 + lane : n - 1];
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    if (k0 + i * 64 + lane < n) fn(x[i], first + k0 + i * 64 + lane);
+            }
+        }
+        if (in_lds) return;
+        for (int j = 0; j <= last; ++j) {                                // flat rows: the slice again (its entries have no numbers)
+            const int n = __builtin_amdgcn_readlane(count.y, j);
+            if (n <= w.collect) continue;
+            MwSlice other(w, b, h, j, len);
+            other.each([&](uint32_t x) { if ((x >> 20) == want && x) fn(x, 0); });
+        }
+    };
+    auto each_entry = [&](auto &&fn) {
+        if (in_lds) {
+            for (int k = tid; k < all; k += MW_THREADS) fn(kept_lds[k], k);
+        } else {
+            each_from_memory(w.slices - 1, fn);
+        }
+    };
+    // An entry into bin `at` of the histogram.  Lanes that hold the same value as the first one are added by that lane (a
+    // row of ties would otherwise queue up at one counter; both fields of a counter scale with the number of entries).
+    auto add = [&](uint32_t x, uint32_t at) {
+        const uint32_t lead = (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
+        const unsigned long long same = __ballot(x == lead);
+        if (x != lead) atomicAdd(&sh.hist[at], packed_entry(x));
+        else if (lane == (int)__ffsll((long long)same) - 1) atomicAdd(&sh.hist[at], packed_entry(x) * (unsigned long long)__popcll(same));
+    };
+    int lo = count.z, hi = count.w;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        const int l = __shfl_xor(lo, off, 64), g = __shfl_xor(hi, off, 64);
+        lo = l < lo ? l : lo;
+        hi = g > hi ? g : hi;
+    }
+    const bool tied = lo == hi;                                          // one entry, or entries of one value: that is tau*
+    double target = st.target, m_above = st.m_above;
+    unsigned c_above = st.c_above;
+    unsigned long long bin_packed = st.bin_packed;
+    uint32_t tau_bits = (uint32_t)lo;
+    if (in_lds && !tied) each_from_memory(w.slices - 1, [&](uint32_t x, int k) { kept_lds[k] = x; });
+    MwSlice slice(w, b, h, sl, len);
+    if (tied) {
+        base += earlier;
+    } else {
+        clear_hist<MW_THREADS, NB2>(sh);                                 // (its barrier: the entries are in LDS)
+        each_entry([&](uint32_t x, int) { add(x, (x >> 10) & 1023u); });
+        __syncthreads();
+        const int b2 = locate_bin<MW_THREADS, NB2, false>(sh, e_field, a.top_p, target, m_above, c_above, bin_packed);
+        const uint32_t prefix = (want << 10) | (uint32_t)b2;
+        if ((bin_packed >> CNT_SHIFT) == 1) {
+            tau_bits = ((uint32_t)e_field << 23) | ((uint32_t)bin_packed & 0x7fffffu);
+        } else {
+            __syncthreads();                                             // locate_bin's readers of sh.hist are done
+            clear_hist<MW_THREADS, NB2>(sh);
+            each_entry([&](uint32_t x, int) { if ((x >> 10) == prefix) add(x, x & 1023u); });
+            __syncthreads();
+            const int b3 = locate_bin<MW_THREADS, NB2, false>(sh, e_field, a.top_p, target, m_above, c_above, bin_packed);
+            tau_bits = (prefix << 10) | (uint32_t)b3;
+        }
+        int mine = 0;
+        if (in_lds) {
+            for (int k = tid; k < earlier; k += MW_THREADS) mine += kept_lds[k] >= tau_bits ? 1 : 0;
+        } else {
+            each_from_memory(sl - 1, [&](uint32_t x, int) { mine += x >= tau_bits ? 1 : 0; });
+        }
+        base += mw_sum(mine, sums);
+    }
+    if (sl == 0 && tid == 0) {
+        const unsigned kept = c_above + (unsigned)(bin_packed >> CNT_SHIFT);
+        a.counts[r] = (int32_t)kept;
+        if (a.thresholds) a.thresholds[r] = __uint_as_float(tau_bits);
+        if (a.row_flags) {
+            const double row_sum = target / (double)a.top_p;
+            const double m_incl = m_above + mass_of(bin_packed, e_field), band = 1e-6 * row_sum;
+            uint32_t f = (fabs(m_incl - target) <= band || fabs(m_above - target) <= band) ? SPECATTN_ROW_NEAR_BOUNDARY : 0u;
+            if (kept > (unsigned)a.idx_capacity) f |= SPECATTN_ROW_OVERFLOW;
+            a.row_flags[r] = f;
+        }
+    }
+    int32_t *out = a.indices + (int64_t)r * a.idx_stride;
+    const int32_t *ptab = (a.emit_physical && a.page_table) ? a.page_table + (int64_t)b * a.max_pages : nullptr;
+    int turn = 0;
+    for (int p0 = slice.begin; p0 < slice.end; p0 += MW_FLIGHT * MW_ITEM, turn ^= 1) {
+        if (p0 != slice.begin) slice.request(p0);
+        // (compared as signed integers: -0.0, the only signed value of a valid row, is below any threshold)
+        unsigned before[MW_FLIGHT], keep[MW_FLIGHT];
+#pragma unroll
+        for (int i = 0; i < MW_FLIGHT; ++i) {
+            const int t = (int)tau_bits;
+            const uint4 u = slice.entries(i);
+            const bool f0 = (int)u.x >= t, f1 = (int)u.y >= t, f2 = (int)u.z >= t, f3 = (int)u.w >= t;
+            const unsigned long long m0 = __ballot(f0), m1 = __ballot(f1), m2 = __ballot(f2), m3 = __ballot(f3);
+            const unsigned long long below = (1ull << lane) - 1ull;
+            before[i] = __popcll(m0 & below) + __popcll(m1 & below) + __popcll(m2 & below) + __popcll(m3 & below);
+            keep[i] = (f0 ? 1u : 0u) | (f1 ? 2u : 0u) | (f2 ? 4u : 0u) | (f3 ? 8u : 0u);
+            if (lane == 0) tot[turn][i * MW_WAVES + wave] = __popcll(m0) + __popcll(m1) + __popcll(m2) + __popcll(m3);
+        }
+        __syncthreads();
+        const int part = lane < MW_FLIGHT * MW_WAVES ? (int)tot[turn][lane] : 0;
+        const int inc = wave_inclusive_sum(part);
+#pragma unroll
+        for (int i = 0; i < MW_FLIGHT; ++i) {
+            int o = base + __shfl(inc - part, i * MW_WAVES + wave, 64) + (int)before[i];
+            const int p = p0 + i * MW_ITEM + tid * 4;
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if ((keep[i] >> c) & 1u) {
+                    const int pos = p + c;
+                    if (o < a.idx_capacity)
+                        out[o] = ptab ? ((ptab[pos >> a.page_shift] << a.page_shift) | (pos & ((1 << a.page_shift) - 1))) : pos;
+                    ++o;
+                }
+        }
+        base += __builtin_amdgcn_readlane(inc, 63);
+    }
+}
+static_assert(MW_FLIGHT * MW_WAVES <= 64, "a wave scans the totals of a round");
+
 inline size_t mw_align(size_t x) { return (x + 255) & ~(size_t)255; }
+
+struct MwPlan { int slices, slice_len; };
+MwPlan mw_plan(int rows, int n)
+{
+    MwPlan p;
+    // One workgroup per CU while it gets its slice with one round of loads (8192 positions), else two; at most 16 slices of
+    // up to 8192 positions each (added up with 16 loads in flight), 32 for longer rows.  Measured with one / two per CU: 32 rows of
+    // 65536 21.8 / 26.2 us, 64 of 32768 20.9 / 25.2, 32 of 131072 29.0 / 28.6, 64 of 131072 40.9 / 36.1; 8 rows of 65536 with
+    // 16 / 32 slices 20.4 / 22.8, 8 of 200001 30.0 / 26.5.
+    constexpr int ONE_ROUND = MW_FLIGHT * MW_ITEM;
+    const int per_cu = (int64_t)rows * n <= (int64_t)ONE_ROUND * cu_count() ? 1 : 2;
+    const int most = n <= MW_MOST_SLICES / 2 * ONE_ROUND ? MW_MOST_SLICES / 2 : MW_MOST_SLICES;
+    int want = (per_cu * cu_count() + rows - 1) / rows;
+    want = want > most ? most : want;
+    p.slice_len = ((n + want - 1) / want + MW_ITEM - 1) / MW_ITEM * MW_ITEM;
+    p.slices = (n + p.slice_len - 1) / p.slice_len;
+    return p;
+}
 
 // One thread per (row, chunk): the chunk's entries are added up in fp64 in ascending position order and
 // the sum is rounded once to fp32 (Section 4: chunk-granular selection; the score of a chunk is its mass).
@@ -829,52 +1106,48 @@ specattn_status launch_chunk_masses(const float *probs, int64_t stride_b, int64_
 
 bool select_multi_wg_preferred(int rows, int n)
 {
-    // One workgroup per row leaves most of the chip idle when there are few rows, and rows beyond 65536
-    // entries do not fit its registers; the split path costs six more launches and re-reads the rows from
-    // L2 in every pass.  Measured crossover: 32 rows at 65536 entries, 64 at 131072, 128 at 262144.
-    return n >= 65536 && (int64_t)rows * 2048 <= n;
+    // One workgroup per row leaves most of the chip idle when there are few rows, takes a CU to itself beyond 32768 entries
+    // and streams the row in every pass beyond 65536; the split costs two more launches.  Measured, one workgroup per row /
+    // split, us: 32 rows of 24001 18.2 / 20.3, of 32768 22.7 / 20.4, of 50001 34.5 / 22.1; 128 of 32768 23.7 / 26.4, of 50001
+    // 37.4 / 34.7; 256 (a CU for every row) of 50001 40.7 / 52.3, of 65536 54.8 / 54.0, of 131072 109 / 89; 512 of 40000
+    // 69.7 / 62.2, 1024 of 65536 196 / 183, 1536 of 65536 286 / 294.
+    const int cus = cu_count();
+    if (n <= 30000 || rows > 4 * cus) return false;
+    if (n <= 32768) return rows <= cus / 4;
+    if (n <= 65536) return rows <= cus / 2 || rows > cus;
+    return true;
 }
 
 size_t select_multi_wg_bytes(int rows, int n)
 {
-    const size_t R = (size_t)rows;
-    return mw_align(R * NB1 * 8) + 2 * mw_align(R * NB2 * 8) + mw_align(R * sizeof(MwState));
+    const MwPlan plan = mw_plan(rows, n);
+    const size_t S = (size_t)rows * plan.slices;
+    return mw_align(S * NB1 * 8) + mw_align(S * (plan.slice_len >> MW_COLLECT_SHIFT) * 4) + mw_align(S * sizeof(MwHead)) + mw_align(S * sizeof(int4)) +
+           mw_align((size_t)rows * sizeof(MwState));
 }
 
-// tau / valid / flags of every row by the split path; `scratch` holds select_multi_wg_bytes
-specattn_status launch_select_multi_wg(const SelectLaunch &a, void *scratch, float *tau, int32_t *valid, uint32_t *flags,
-                                       hipStream_t stream)
+// `scratch` holds select_multi_wg_bytes
+specattn_status launch_select_multi_wg(const SelectLaunch &a, void *scratch, hipStream_t stream)
 {
     const int rows = a.B * a.H_kv;
-    const size_t R = (size_t)rows;
+    const MwPlan plan = mw_plan(rows, a.n_max);
+    const size_t S = (size_t)rows * plan.slices;
     MwLaunch w;
     w.a = a;
+    w.slices = plan.slices;
+    w.slice_len = plan.slice_len;
+    w.collect = plan.slice_len >> MW_COLLECT_SHIFT;
     char *p = static_cast<char *>(scratch);
-    w.h1 = reinterpret_cast<unsigned long long *>(p); p += mw_align(R * NB1 * 8);
-    w.h2 = reinterpret_cast<unsigned long long *>(p); p += mw_align(R * NB2 * 8);
-    w.h3 = reinterpret_cast<unsigned long long *>(p); p += mw_align(R * NB2 * 8);
+    w.hist = reinterpret_cast<unsigned long long *>(p); p += mw_align(S * NB1 * 8);
+    w.entries = reinterpret_cast<uint32_t *>(p); p += mw_align(S * w.collect * 4);
+    w.head = reinterpret_cast<MwHead *>(p); p += mw_align(S * sizeof(MwHead));
+    w.counts = reinterpret_cast<int4 *>(p); p += mw_align(S * sizeof(int4));
     w.state = reinterpret_cast<MwState *>(p);
-    {
-        const int blocks = (a.n_max + MW_SLICE - 1) / MW_SLICE;
-        int k = (int)((R * blocks + 2 * cu_count() - 1) / (2 * cu_count()));      // blocks per workgroup
-        k = k < 1 ? 1 : (k > 16 ? 16 : k);
-        w.slice_len = k * MW_SLICE;
-        w.slices = (a.n_max + w.slice_len - 1) / w.slice_len;
-    }
-    w.tau = tau; w.valid = valid; w.flags = flags;
-    const size_t words = select_multi_wg_bytes(rows, a.n_max) / 8;
-    hipLaunchKernelGGL(mw_clear_kernel, dim3((unsigned)((words + 1023) / 1024 < 2048 ? (words + 1023) / 1024 : 2048)), dim3(256), 0,
-                       stream, w.h1, words);
-    specattn_status st = check_launch("mw_clear_kernel");
-    if (st != SPECATTN_OK) return st;
-    const dim3 grid((unsigned)(R * w.slices));
-    hipLaunchKernelGGL(mw_pass_kernel<1>, grid, dim3(MW_THREADS), 0, stream, w);
-    hipLaunchKernelGGL(mw_pass_kernel<2>, grid, dim3(MW_THREADS), 0, stream, w);
-    hipLaunchKernelGGL(mw_pass_kernel<3>, grid, dim3(MW_THREADS), 0, stream, w);
-    st = check_launch("mw_pass_kernel");
-    if (st != SPECATTN_OK) return st;
-    hipLaunchKernelGGL(mw_final_kernel, dim3(rows), dim3(MW_THREADS), 0, stream, w);
-    return check_launch("mw_final_kernel");
+    const dim3 grid((unsigned)S);
+    hipLaunchKernelGGL(mw_hist_kernel, grid, dim3(MW_THREADS), 0, stream, w);
+    hipLaunchKernelGGL(mw_collect_kernel, grid, dim3(MW_THREADS), 0, stream, w);
+    hipLaunchKernelGGL(mw_emit_kernel, grid, dim3(MW_THREADS), 0, stream, w);
+    return check_launch("mw_emit_kernel");
 }
 
 specattn_status launch_select(const SelectLaunch &a, hipStream_t stream)

@@ -270,3 +270,25 @@ def test_thread_shapes_and_rows_at_any_address(rows, n):
     assert np.array_equal(kept.reshape(rows, blocks, 1024).sum(2), bc.cpu().numpy())
     for r in (0, 1, 2, rows - 1):
         assert np.array_equal(np.flatnonzero(kept[r]), got["indices"][r, :got["counts"][r]])
+
+
+@pytest.mark.parametrize("rows,n", [(2, 65537), (9, 131075), (40, 200003)])
+def test_split_path_flat_rows(rows, n):
+    """Rows whose boundary bin holds from a few entries to all of them: kept in LDS, fetched again, or (more than 4096 in
+    a slice) read again from the rows; against the path with one workgroup per row."""
+    rng = np.random.default_rng(rows)
+    spread = np.geomspace(1e-3, 3.0, rows)[:, None]
+    logit = spread * rng.standard_normal((rows, n))
+    probs = np.exp(logit - logit.max(1, keepdims=True)).astype(np.float32)
+    probs /= probs.sum(1, keepdims=True)
+    probs[1, ::2] = 0.0
+    probs[1, :n // 2] *= np.float32(1e-40) / np.float32(probs[1].max())      # subnormal entries
+    probs[0, n - 1] = -0.0
+    probs[rows - 1, :] = np.float32(1.0 / n)                   # ties
+    for p in (0.6, 0.95):
+        got = gpu_select(probs.reshape(1, rows, n), p)
+        one = gpu_select(probs.reshape(1, rows, n), p, split=False)
+        assert got["split"]
+        for k in ("counts", "tau", "flags"):
+            assert np.array_equal(got[k], one[k]), k
+        assert np.array_equal(got["indices"], one["indices"])
