@@ -26,27 +26,23 @@ constexpr unsigned long long SIG_MASK = CNT_ONE - 1;
 
 typedef uint32_t u32x4a __attribute__((ext_vector_type(4), aligned(4)));   // 16-byte load from any float's address
 
-struct LocSlot {                 // a candidate outcome of one locate step
+// Histograms in LDS leave a counter free after every NB / 64 bins: the rows of bins that the lanes of the locating wave
+// add up then start two banks apart, and neighbouring bins, which are the busy ones, still lie in neighbouring banks.
+template <int NB> __device__ __forceinline__ uint32_t hist_slot(uint32_t bin) { return bin + bin / (NB / 64); }
+constexpr int HIST1 = NB1 + 64, HIST2 = NB2 + 64;
+
+struct Located {                 // outcome of one locate step
+    double target, m_above;
     unsigned long long packed;
-    double m_above;
     unsigned c_above;
     int bin;
 };
 
 struct RowShared {
-    unsigned long long hist[NB1];
-    LocSlot loc[16];
-    int loc_state[16];
-    double wave_m[16];
+    Located found;
     unsigned wave_c[16];
     unsigned wave_tot[2][16];
     unsigned wt[256];            // kept entries per (item, wave), then their exclusive prefix
-    double total_m;
-    double m_above;
-    unsigned c_above;
-    unsigned long long bin_packed;
-    int best;
-    int lowest;
     unsigned running;
 };
 
@@ -93,6 +89,11 @@ __device__ __forceinline__ void wave_prefix(double &m, unsigned &c)
 #undef SPECATTN_SCAN_STEP
 }
 
+__device__ __forceinline__ double read_lane(double v, int lane)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane), __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+
 // Kept-position mask: every lane holds the keep flags of four consecutive positions (bit c = position 4 * lane + c
 // of a run of 256); the eight lanes that share a 32-position word combine their nibbles on the vector ALU
 // (neighbour, pair and half-row exchanges), after which each of them holds the whole word.
@@ -105,138 +106,126 @@ __device__ __forceinline__ uint32_t mask_word(uint32_t nibble, int lane)
     return (uint32_t)v;
 }
 
-// One radix pass decision.  hist[0..NB) holds the packed counters of this pass.
+// One radix pass decision.  `hist` holds the packed counters of this pass (bin b at hist_slot<NB>(b)).
 // On return (uniform over the block): bin = highest non-empty bin b with
-// m_above + mass(bins >= b) >= target (lowest non-empty bin if rounding leaves none),
+// m_above + mass(bins >= b) >= target (lowest non-empty bin if rounding leaves none; -1 without any mass),
 // and m_above / c_above advanced to cover the bins above it.
-// Threads own bins from the top down (thread 0 the highest BPT bins), so "the bins above mine" is a
-// prefix over threads: a wave-wide scan, the wave totals through LDS, and every thread knows the mass
-// above its own bins; the one thread whose bins hold the boundary finds it among them.
-template <int THREADS, int NB, bool FIRST>
-__device__ __forceinline__ int locate_bin(RowShared &sh, int e_field_fixed, float top_p, double &target,
-                                          double &m_above, unsigned &c_above,
-                                          unsigned long long &bin_packed)
+// A row's total is what fp64 leaves when its entries are added from the largest down: entries below half a unit in the
+// last place of the total add nothing, and their octaves count as empty.  With top_p = 1 the boundary is therefore the lowest
+// bin that is left, whatever the rounding of the sums above it.
+// The first wave does it alone and the others wait at the one barrier: its lanes own NB / 64 bins each from the top down (lane
+// 0 the highest), add them up as integers (bins of one exponent add exactly), and a prefix over the lanes tells every lane the
+// mass above its bins; the bins of the lane that holds the boundary are then searched one per lane.  All waves together, with
+// the totals of the waves through LDS and two barriers, a step took 2.1 us (2048 bins, 512 threads): a row of 8192 positions
+// 10.7 us then and 8.0 us now, 64 rows of 13001 14.2 and 10.7, 1024 rows of 32768 73.7 and 69.3 us.
+template <int NB, bool FIRST>
+__device__ __forceinline__ int locate_bin(const unsigned long long *hist, Located &found, int e_field_fixed, float top_p, double &target,
+                                          double &m_above, unsigned &c_above, unsigned long long &bin_packed)
 {
-    constexpr int NW = THREADS / 64;
-    constexpr int BPT = NB / THREADS;
-    static_assert(BPT >= 1, "more threads than bins");
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int top = NB - 1 - (int)threadIdx.x * BPT;           // this thread's highest bin
-    // (bins are re-read from LDS wherever they are needed again, rather than kept in registers: the caller holds
-    // the whole row in registers and has none to spare)
-    auto bin_entry = [&](int j) -> unsigned long long { return sh.hist[top - j]; };
-    auto bin_mass = [&](int j, unsigned long long hj) -> double {
-        return mass_of(hj, FIRST ? ((top - j) >> 3) : e_field_fixed);
-    };
-    double lm = 0.0;
-    unsigned lc = 0;
+    constexpr int BPL = NB / 64;
+    constexpr int RUN = FIRST ? 8 : BPL;                       // bins of one exponent
+    constexpr int RUNS = BPL / RUN;
+    if (threadIdx.x < 64) {
+        const int lane = threadIdx.x;
+        const unsigned long long *mine = hist + (63 - lane) * (BPL + 1);       // this lane's lowest bin
+        unsigned long long sum[RUNS];
 #pragma unroll
-    for (int j = 0; j < BPT; ++j) {
-        const unsigned long long hj = bin_entry(j);
-        lm += bin_mass(j, hj);
-        lc += (unsigned)(hj >> CNT_SHIFT);
-    }
-    double incl_m = lm;
-    unsigned incl_c = lc;
-    wave_prefix(incl_m, incl_c);
-    if (lane == 63) { sh.wave_m[wave] = incl_m; sh.wave_c[wave] = incl_c; }
-    // mass and count of the lanes before this one (wave_shr:1)
-    double above = dpp_double<0x138, 0xf>(incl_m);
-    unsigned above_c = (unsigned)dpp_int<0x138, 0xf>((int)incl_c);
-    __syncthreads();
-    double total = 0.0;
+        for (int g = 0; g < RUNS; ++g) {
+            sum[g] = 0ull;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        const double wm = sh.wave_m[w];
-        if (w < wave) { above += wm; above_c += sh.wave_c[w]; }
-        total += wm;
-    }
-    if (FIRST) target = (double)top_p * total;     // Algorithm 2: M_target = p * sum a
-    if (FIRST && !(total > 0.0)) return -1;        // no mass at all (uniform decision)
-
-    // Masses are non-negative, so the running sum over a thread's bins never decreases: the thread holds a
-    // feasible non-empty bin exactly if the sum after its last bin reaches the target.
-    double run_end = above;
+            for (int j = 0; j < RUN; ++j) sum[g] += mine[g * RUN + j];
+            __builtin_amdgcn_sched_barrier(0);                 // (not all loads at once: the caller's registers hold the row)
+        }
+        auto exponent = [&](int g) { return FIRST ? (63 - lane) * RUNS + g : e_field_fixed; };
+        int cut = -1;                                          // exponent fields up to this one count as empty
+        double lm, incl_m;
+        unsigned lc, incl_c;
+        auto add_up = [&]() {
+            lm = 0.0;
+            lc = 0;
 #pragma unroll
-    for (int j = 0; j < BPT; ++j) run_end += bin_mass(j, bin_entry(j));
-    const bool holds = lc > 0 && (m_above + run_end) >= target;
-    const unsigned long long has = __ballot(holds);
-    // per wave: the first lane (highest bins) that holds a feasible bin looks for the highest one among its own
-    if (has && lane == __ffsll((unsigned long long)has) - 1) {
-        double run = above;
-        unsigned runc = above_c;
-        bool found = false;
+            for (int g = 0; g < RUNS; ++g)
+                if (exponent(g) > cut) { lm += mass_of(sum[g], exponent(g)); lc += (unsigned)(sum[g] >> CNT_SHIFT); }
+            incl_m = lm;
+            incl_c = lc;
+            wave_prefix(incl_m, incl_c);
+        };
+        add_up();
+        double total = read_lane(incl_m, 63);
+        if (FIRST) {
+            cut = ((__double2hiint(total) >> 20) & 0x7ff) - 1023 + 73;         // 2^(field - 126) <= 2^(exponent of total - 53)
+            bool some = false;
 #pragma unroll
-        for (int j = 0; j < BPT; ++j) {
-            const unsigned long long hj = bin_entry(j);
-            const double mj = bin_mass(j, hj);
-            const unsigned cj = (unsigned)(hj >> CNT_SHIFT);
-            if (!found && cj && (m_above + (run + mj)) >= target) {
-                found = true;
-                sh.loc[wave].bin = top - j; sh.loc[wave].m_above = run; sh.loc[wave].c_above = runc; sh.loc[wave].packed = hj;
+            for (int g = 0; g < RUNS; ++g) some |= sum[g] != 0ull && exponent(g) <= cut;
+            if (total > 0.0 && __any(some)) {                  // (rare)
+                add_up();
+                total = read_lane(incl_m, 63);
             }
-            run += mj;
-            runc += cj;
         }
-    }
-    if (lane == 0) sh.loc_state[wave] = has ? 1 : 0;
-    __syncthreads();
-    int pick = -1;                                 // first wave with a feasible bin
-#pragma unroll
-    for (int w = NW - 1; w >= 0; --w)
-        if (sh.loc_state[w]) pick = w;
-    if (pick < 0) {
-        // Rounding left no feasible bin (the row total itself fell short of the target by an ulp): take the
-        // lowest non-empty bin.  Uniform over the block, and rare.
-        int low = -1;
-        double run = above, low_above = 0.0;
-        unsigned runc = above_c, low_c = 0;
-        unsigned long long low_h = 0;
-#pragma unroll
-        for (int j = 0; j < BPT; ++j) {
-            const unsigned long long hj = bin_entry(j);
+        // mass and count of the lanes before this one (wave_shr:1)
+        const double before = dpp_double<0x138, 0xf>(incl_m);
+        const unsigned before_c = (unsigned)dpp_int<0x138, 0xf>((int)incl_c);
+        Located out = {FIRST ? (double)top_p * total : target, m_above, 0ull, c_above, -1};    // Algorithm 2: M_target = p * sum a
+        const double goal = top_p < 1.0f ? out.target : INFINITY;
+        if (!FIRST || total > 0.0) {
+            // Masses are non-negative, so the running sum never decreases: the first lane whose sum reaches the target holds
+            // the boundary.  (If rounding leaves none, the row total itself fell short by an ulp: the lowest entries do.)
+            const unsigned long long some = __ballot(lc > 0), holds = __ballot(lc > 0 && m_above + (before + lm) >= goal);
+            const int at = holds ? (int)__ffsll((long long)holds) - 1 : 63 - __clzll((long long)some);
+            const double above = read_lane(before, at);
+            const unsigned above_c = (unsigned)__builtin_amdgcn_readlane((int)before_c, at);
+            const int low = (63 - at) * BPL;                   // the boundary lane's lowest bin
+            const int bin = low + BPL - 1 - lane;              // lane 0 looks at its highest
+            const int e_bin = FIRST ? bin >> 3 : e_field_fixed;
+            const unsigned long long hj = lane < BPL && (!FIRST || e_bin > cut) ? hist[hist_slot<NB>(low) + BPL - 1 - lane] : 0ull;
             const unsigned cj = (unsigned)(hj >> CNT_SHIFT);
-            if (cj) { low = top - j; low_above = run; low_c = runc; low_h = hj; }
-            run += bin_mass(j, hj);
-            runc += cj;
+            double run = cj ? mass_of(hj, e_bin) : 0.0;
+            unsigned runc = cj;
+            wave_prefix(run, runc);
+            const unsigned long long filled = __ballot(cj > 0), ok = __ballot(cj > 0 && m_above + (above + run) >= goal);
+            const int pick = ok ? (int)__ffsll((long long)ok) - 1 : 63 - __clzll((long long)filled);
+            const double inside = pick ? read_lane(run, pick - 1) : 0.0;
+            const unsigned inside_c = pick ? (unsigned)__builtin_amdgcn_readlane((int)runc, pick - 1) : 0u;
+            out.m_above = m_above + (above + inside);
+            out.c_above = c_above + above_c + inside_c;
+            out.packed = (unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(hj >> 32), pick) << 32 |
+                         (unsigned)__builtin_amdgcn_readlane((int)(uint32_t)hj, pick);
+            out.bin = low + BPL - 1 - pick;
         }
-        const unsigned long long has_low = __ballot(low >= 0);
-        if (has_low && lane == 63 - __clzll(has_low)) {
-            sh.loc[wave].bin = low; sh.loc[wave].m_above = low_above; sh.loc[wave].c_above = low_c; sh.loc[wave].packed = low_h;
-        }
-        __syncthreads();                           // every thread has read loc_state
-        if (lane == 0) sh.loc_state[wave] = has_low ? 1 : 0;
-        __syncthreads();
-#pragma unroll
-        for (int w = 0; w < NW; ++w)
-            if (sh.loc_state[w]) pick = w;         // last wave (lowest bins) with any entry
+        if (lane == 0) found = out;
     }
-    const LocSlot &slot = sh.loc[pick];
-    const int bin = slot.bin;
-    m_above += slot.m_above;
-    c_above += slot.c_above;
-    bin_packed = slot.packed;
-    return bin;
+    __syncthreads();
+    target = found.target;
+    m_above = found.m_above;
+    c_above = found.c_above;
+    bin_packed = found.packed;
+    return found.bin;
 }
 
-template <int THREADS, int NB>
-__device__ __forceinline__ void clear_hist(RowShared &sh)
+template <int THREADS, int N>
+__device__ __forceinline__ void clear_hist(unsigned long long *hist)
 {
-    for (int b = threadIdx.x; b < NB; b += THREADS) sh.hist[b] = 0ull;
-    __syncthreads();
+#pragma unroll
+    for (int b = 0; b < N; b += THREADS)
+        if (b + (int)threadIdx.x < N) hist[b + threadIdx.x] = 0ull;
 }
 
 // THREADS threads per row; RESIDENT: the row sits in NV4 uint4 registers per thread.
-// Entries of the buffer in which a row's list is staged in list order for contiguous stores (dynamic LDS, so that
-// the small workgroups, which are meant to run four to a CU, are not held to three by a buffer sized for the large
-// ones; longer lists take several rounds).
+// Dynamic LDS: the histograms (one of the first pass, which the third takes over, and one of the second), and afterwards in
+// their place the buffer in which a row's list is put together in list order for contiguous stores (smaller for the small
+// workgroups, several of which share a CU; longer lists take several rounds).
 constexpr unsigned stage_entries(int threads) { return threads <= 256 ? 4096u : 8192u; }
+constexpr unsigned select_lds(int threads)
+{
+    return stage_entries(threads) * 4 > (HIST1 + HIST2) * 8 ? stage_entries(threads) * 4 : (HIST1 + HIST2) * 8;
+}
 
 template <int THREADS, int NV4, bool RESIDENT>
 __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
 {
     __shared__ RowShared sh;
-    extern __shared__ __align__(16) int32_t stage_dyn[];
+    extern __shared__ __align__(16) unsigned long long select_dyn[];
+    unsigned long long *hist1 = select_dyn, *hist2 = select_dyn + HIST1;
     constexpr int NW = THREADS / 64;
     constexpr int ITEM = THREADS * 4;                 // positions per item (one uint4 per thread)
     const int r = blockIdx.x;
@@ -306,8 +295,9 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
             for (int i = 0; i < NV4; ++i) data[i] = (i < n_items) ? load_item(i) : make_uint4(0, 0, 0, 0);
         }
     }
-    // the histogram is cleared while the loads are in flight
-    clear_hist<THREADS, NB1>(sh);
+    // the histograms are cleared while the loads are in flight
+    clear_hist<THREADS, HIST1 + HIST2>(hist1);
+    __syncthreads();
     if (RESIDENT && vec_ok) {
         // Common case first: no sign bit among the thread's entries.  Then nothing needs cleaning, an entry is invalid
         // exactly if its exponent field is all ones, and every bin index stays below NB1 - one OR and one maximum per
@@ -360,17 +350,17 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
     // (one histogram per pair of waves instead of one per workgroup measured slower: the atomics of a row's few
     // dozen busy bins are not what bounds this pass)
     for_items([&](int, uint4 u) {
-        if (u.x) atomicAdd(&sh.hist[u.x >> 20], packed_entry(u.x));
-        if (u.y) atomicAdd(&sh.hist[u.y >> 20], packed_entry(u.y));
-        if (u.z) atomicAdd(&sh.hist[u.z >> 20], packed_entry(u.z));
-        if (u.w) atomicAdd(&sh.hist[u.w >> 20], packed_entry(u.w));
+        if (u.x) atomicAdd(&hist1[hist_slot<NB1>(u.x >> 20)], packed_entry(u.x));
+        if (u.y) atomicAdd(&hist1[hist_slot<NB1>(u.y >> 20)], packed_entry(u.y));
+        if (u.z) atomicAdd(&hist1[hist_slot<NB1>(u.z >> 20)], packed_entry(u.z));
+        if (u.w) atomicAdd(&hist1[hist_slot<NB1>(u.w >> 20)], packed_entry(u.w));
     });
     const bool any_bad = __syncthreads_or(worst >= 0x7f800000u ? 1 : 0) != 0;     // also orders the atomics
 
     double target = 0.0, m_above = 0.0;
     unsigned c_above = 0;
     unsigned long long bin_packed = 0;
-    const int b1 = locate_bin<THREADS, NB1, true>(sh, 0, a.top_p, target, m_above, c_above, bin_packed);
+    const int b1 = locate_bin<NB1, true>(hist1, sh.found, 0, a.top_p, target, m_above, c_above, bin_packed);
     const double row_sum = (double)target / (double)a.top_p;     // only used for the boundary flag
     if (any_bad || b1 < 0 || len == 0) {
         if (tid == 0) {
@@ -397,29 +387,27 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
         tau_bits = single_entry_bits(bin_packed);
     } else {
         // ---- pass 2: bits[19:10] inside bin b1 -----------------------------------------------
-        clear_hist<THREADS, NB2>(sh);
-        for_items([&](int, uint4 u) {
-            if ((u.x >> 20) == (uint32_t)b1 && u.x) atomicAdd(&sh.hist[(u.x >> 10) & 1023u], packed_entry(u.x));
-            if ((u.y >> 20) == (uint32_t)b1 && u.y) atomicAdd(&sh.hist[(u.y >> 10) & 1023u], packed_entry(u.y));
-            if ((u.z >> 20) == (uint32_t)b1 && u.z) atomicAdd(&sh.hist[(u.z >> 10) & 1023u], packed_entry(u.z));
-            if ((u.w >> 20) == (uint32_t)b1 && u.w) atomicAdd(&sh.hist[(u.w >> 10) & 1023u], packed_entry(u.w));
-        });
-        __syncthreads();
-        const int b2 = locate_bin<THREADS, NB2, false>(sh, e_field, a.top_p, target, m_above, c_above, bin_packed);
+        // (as a range of bit patterns that leaves zeros out; the first pass's counters are cleared for the third on the way)
+        auto refine = [&](uint32_t first, uint32_t width, auto &&count) {
+            const uint32_t lo = first ? first : 1u, n = first ? width : width - 1u;
+            for_items([&](int, uint4 u) {
+                if (u.x - lo < n) count(u.x);
+                if (u.y - lo < n) count(u.y);
+                if (u.z - lo < n) count(u.z);
+                if (u.w - lo < n) count(u.w);
+            });
+            __syncthreads();
+        };
+        clear_hist<THREADS, HIST2>(hist1);
+        refine((uint32_t)b1 << 20, 1u << 20, [&](uint32_t x) { atomicAdd(&hist2[hist_slot<NB2>((x >> 10) & 1023u)], packed_entry(x)); });
+        const int b2 = locate_bin<NB2, false>(hist2, sh.found, e_field, a.top_p, target, m_above, c_above, bin_packed);
         const uint32_t prefix = ((uint32_t)b1 << 10) | (uint32_t)b2;
         if ((bin_packed >> CNT_SHIFT) == 1) {
             tau_bits = single_entry_bits(bin_packed);
         } else {
             // ---- pass 3: bits[9:0] inside (b1, b2) -------------------------------------------
-            clear_hist<THREADS, NB2>(sh);
-            for_items([&](int, uint4 u) {
-                if ((u.x >> 10) == prefix && u.x) atomicAdd(&sh.hist[u.x & 1023u], packed_entry(u.x));
-                if ((u.y >> 10) == prefix && u.y) atomicAdd(&sh.hist[u.y & 1023u], packed_entry(u.y));
-                if ((u.z >> 10) == prefix && u.z) atomicAdd(&sh.hist[u.z & 1023u], packed_entry(u.z));
-                if ((u.w >> 10) == prefix && u.w) atomicAdd(&sh.hist[u.w & 1023u], packed_entry(u.w));
-            });
-            __syncthreads();
-            const int b3 = locate_bin<THREADS, NB2, false>(sh, e_field, a.top_p, target, m_above, c_above, bin_packed);
+            refine(prefix << 10, 1u << 10, [&](uint32_t x) { atomicAdd(&hist1[hist_slot<NB2>(x & 1023u)], packed_entry(x)); });
+            const int b3 = locate_bin<NB2, false>(hist1, sh.found, e_field, a.top_p, target, m_above, c_above, bin_packed);
             tau_bits = (prefix << 10) | (uint32_t)b3;             // >= 1: zeros never enter a bin
         }
     }
@@ -529,12 +517,7 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
             }
         }
         if (out) {
-            unsigned v = tid < NE ? sh.wt[tid] : 0u, inc = v;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const unsigned o = __shfl_up(inc, off, 64);
-                if (lane >= off) inc += o;
-            }
+            const unsigned v = tid < NE ? sh.wt[tid] : 0u, inc = (unsigned)wave_inclusive_sum((int)v);
             if (lane == 63) sh.wave_c[wave] = inc;
             __syncthreads();
             if (tid < NE) {
@@ -548,7 +531,7 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
             // out with contiguous stores over the whole workgroup: whole cache lines, whatever the kept counts of the
             // single waves are.  Lists longer than the buffer take several rounds.
             constexpr unsigned CH = stage_entries(THREADS);
-            int32_t *stage = stage_dyn;
+            int32_t *stage = reinterpret_cast<int32_t *>(select_dyn);
             const unsigned cap = kept < (unsigned)a.idx_capacity ? kept : (unsigned)a.idx_capacity;
             const unsigned my_base = lane < NV4 ? sh.wt[lane * NW + wave] : 0u;    // lane i: this wave's place for item i
             for (unsigned c0 = 0; c0 < cap; c0 += CH) {
@@ -605,8 +588,7 @@ template <int THREADS, int NV4, bool RESIDENT>
 specattn_status launch_one(const SelectLaunch &a, hipStream_t stream)
 {
     const int rows = a.B * a.H_kv;
-    hipLaunchKernelGGL((topp_select_kernel<THREADS, NV4, RESIDENT>), dim3(rows), dim3(THREADS), stage_entries(THREADS) * sizeof(int32_t),
-                       stream, a);
+    hipLaunchKernelGGL((topp_select_kernel<THREADS, NV4, RESIDENT>), dim3(rows), dim3(THREADS), select_lds(THREADS), stream, a);
     return check_launch("topp_select_kernel");
 }
 
@@ -618,7 +600,7 @@ specattn_status launch_one(const SelectLaunch &a, hipStream_t stream)
 //      how many of its slice's entries lie above that bin and collects those that lie in it - a few per cent;
 //   3. every workgroup finishes the search on the row's collected entries alone, in LDS, knows from the counts where its
 //      slice's part of the list begins, and writes it.
-// Nothing has to be cleared, no atomic goes to memory, and no pass only counts.  32 rows of 131072: 29 us; three
+// Nothing has to be cleared, no atomic goes to memory, and no pass only counts.  32 rows of 131072: 28 us; three
 // histogram passes that added up by atomics in memory, with a launch to clear them, one for the threshold and the mask and
 // compaction passes of the union, took 50 us.  Bound by the trips to memory of each launch (ranges, then
 // histograms, then entries, about a microsecond each) and the locate steps (2 us each), not by the row's bytes.
@@ -711,10 +693,10 @@ struct MwSlice {
     }
 };
 
-// The row's histogram in sh.hist from those of its slices; `mine`: lane j holds slice j's range (lanes past the slices
+// The row's histogram in `hist` from those of its slices; `mine`: lane j holds slice j's range (lanes past the slices
 // slice 0's).  cnt[k]: entries that slice `sl` has in this thread's bin k * MW_THREADS + tid.  Returns whether any slice met
 // an invalid entry.
-__device__ __forceinline__ bool mw_gather(RowShared &sh, const MwHead &mine, const unsigned long long *h, int slices, int sl,
+__device__ __forceinline__ bool mw_gather(unsigned long long *hist, const MwHead &mine, const unsigned long long *h, int slices, int sl,
                                           int (&cnt)[NB1 / MW_THREADS])
 {
     const int tid = threadIdx.x;
@@ -747,7 +729,7 @@ __device__ __forceinline__ bool mw_gather(RowShared &sh, const MwHead &mine, con
                 }
             }
         }
-        sh.hist[bin] = sum;
+        hist[hist_slot<NB1>(bin)] = sum;
     }
     __syncthreads();
     return bad;
@@ -818,7 +800,8 @@ __global__ __launch_bounds__(MW_THREADS) void mw_hist_kernel(MwLaunch w)
 // Step 2.
 __global__ __launch_bounds__(MW_THREADS) void mw_collect_kernel(MwLaunch w)
 {
-    __shared__ RowShared sh;
+    __shared__ unsigned long long hist[HIST1];
+    __shared__ Located located;
     __shared__ int sums[MW_WAVES];
     __shared__ int ends[2][MW_WAVES];
     __shared__ int found;
@@ -833,11 +816,11 @@ __global__ __launch_bounds__(MW_THREADS) void mw_collect_kernel(MwLaunch w)
     MwSlice slice(w, b, h, sl, len);
     if (tid == 0) found = 0;
     int cnt[NB1 / MW_THREADS];
-    const bool bad = mw_gather(sh, head, w.hist + row_at * NB1, w.slices, sl, cnt);
+    const bool bad = mw_gather(hist, head, w.hist + row_at * NB1, w.slices, sl, cnt);
     double target = 0.0, m_above = 0.0;
     unsigned c_above = 0;
     unsigned long long bin_packed = 0;
-    const int bin = locate_bin<MW_THREADS, NB1, true>(sh, 0, a.top_p, target, m_above, c_above, bin_packed);
+    const int bin = locate_bin<NB1, true>(hist, located, 0, a.top_p, target, m_above, c_above, bin_packed);
     const bool invalid = bad || bin < 0 || len == 0;                     // uniform
     if (sl == 0 && tid == 0) w.state[r] = MwState{bin_packed, target, m_above, c_above, bin, invalid ? 1 : 0};
     if (invalid) return;
@@ -875,7 +858,8 @@ __global__ __launch_bounds__(MW_THREADS) void mw_collect_kernel(MwLaunch w)
 // Step 3: tau*, count and flags of the row (slice 0), and the list entries of the slice.
 __global__ __launch_bounds__(MW_THREADS) void mw_emit_kernel(MwLaunch w)
 {
-    __shared__ RowShared sh;
+    __shared__ unsigned long long hist2[HIST2], hist3[HIST2];
+    __shared__ Located located;
     __shared__ uint32_t kept_lds[MW_LDS_ENTRIES];
     __shared__ int sums[MW_WAVES];
     __shared__ unsigned tot[2][MW_FLIGHT * MW_WAVES];
@@ -934,13 +918,14 @@ __global__ __launch_bounds__(MW_THREADS) void mw_emit_kernel(MwLaunch w)
             each_from_memory(w.slices - 1, fn);
         }
     };
-    // An entry into bin `at` of the histogram.  Lanes that hold the same value as the first one are added by that lane (a
+    // An entry into its bin of a histogram.  Lanes that hold the same value as the first one are added by that lane (a
     // row of ties would otherwise queue up at one counter; both fields of a counter scale with the number of entries).
-    auto add = [&](uint32_t x, uint32_t at) {
+    auto add = [&](unsigned long long *hist, uint32_t x, uint32_t bin) {
+        const uint32_t at = hist_slot<NB2>(bin);
         const uint32_t lead = (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
         const unsigned long long same = __ballot(x == lead);
-        if (x != lead) atomicAdd(&sh.hist[at], packed_entry(x));
-        else if (lane == (int)__ffsll((long long)same) - 1) atomicAdd(&sh.hist[at], packed_entry(x) * (unsigned long long)__popcll(same));
+        if (x != lead) atomicAdd(&hist[at], packed_entry(x));
+        else if (lane == (int)__ffsll((long long)same) - 1) atomicAdd(&hist[at], packed_entry(x) * (unsigned long long)__popcll(same));
     };
     int lo = count.z, hi = count.w;
 #pragma unroll
@@ -959,19 +944,19 @@ __global__ __launch_bounds__(MW_THREADS) void mw_emit_kernel(MwLaunch w)
     if (tied) {
         base += earlier;
     } else {
-        clear_hist<MW_THREADS, NB2>(sh);                                 // (its barrier: the entries are in LDS)
-        each_entry([&](uint32_t x, int) { add(x, (x >> 10) & 1023u); });
+        clear_hist<MW_THREADS, HIST2>(hist2);
+        clear_hist<MW_THREADS, HIST2>(hist3);
+        __syncthreads();                                                 // (also: the entries are in LDS)
+        each_entry([&](uint32_t x, int) { add(hist2, x, (x >> 10) & 1023u); });
         __syncthreads();
-        const int b2 = locate_bin<MW_THREADS, NB2, false>(sh, e_field, a.top_p, target, m_above, c_above, bin_packed);
+        const int b2 = locate_bin<NB2, false>(hist2, located, e_field, a.top_p, target, m_above, c_above, bin_packed);
         const uint32_t prefix = (want << 10) | (uint32_t)b2;
         if ((bin_packed >> CNT_SHIFT) == 1) {
             tau_bits = ((uint32_t)e_field << 23) | ((uint32_t)bin_packed & 0x7fffffu);
         } else {
-            __syncthreads();                                             // locate_bin's readers of sh.hist are done
-            clear_hist<MW_THREADS, NB2>(sh);
-            each_entry([&](uint32_t x, int) { if ((x >> 10) == prefix) add(x, x & 1023u); });
+            each_entry([&](uint32_t x, int) { if ((x >> 10) == prefix) add(hist3, x, x & 1023u); });
             __syncthreads();
-            const int b3 = locate_bin<MW_THREADS, NB2, false>(sh, e_field, a.top_p, target, m_above, c_above, bin_packed);
+            const int b3 = locate_bin<NB2, false>(hist3, located, e_field, a.top_p, target, m_above, c_above, bin_packed);
             tau_bits = (prefix << 10) | (uint32_t)b3;
         }
         int mine = 0;
@@ -1108,14 +1093,13 @@ bool select_multi_wg_preferred(int rows, int n)
 {
     // One workgroup per row leaves most of the chip idle when there are few rows, takes a CU to itself beyond 32768 entries
     // and streams the row in every pass beyond 65536; the split costs two more launches.  Measured, one workgroup per row /
-    // split, us: 32 rows of 24001 18.2 / 20.3, of 32768 22.7 / 20.4, of 50001 34.5 / 22.1; 128 of 32768 23.7 / 26.4, of 50001
-    // 37.4 / 34.7; 256 (a CU for every row) of 50001 40.7 / 52.3, of 65536 54.8 / 54.0, of 131072 109 / 89; 512 of 40000
-    // 69.7 / 62.2, 1024 of 65536 196 / 183, 1536 of 65536 286 / 294.
+    // split, us: 32 rows of 28001 17.8 / 19.4, of 32768 19.6 / 19.4, of 40000 27.1 / 19.9; 128 of 40000 28.4 / 30.8, of 50001
+    // 32.9 / 32.3, of 65536 42.4 / 32.9; 256 (a CU for every row) of 65536 49.7 / 51.9, of 131072 104 / 86; 512 of 50001
+    // 73.3 / 74.8, of 65536 96.4 / 85.2; 1024 of 65536 180 / 171, 1536 of 65536 264 / 300.
     const int cus = cu_count();
-    if (n <= 30000 || rows > 4 * cus) return false;
-    if (n <= 32768) return rows <= cus / 4;
-    if (n <= 65536) return rows <= cus / 2 || rows > cus;
-    return true;
+    if (n <= 32768 || rows > 4 * cus) return false;
+    if (n > 65536 || rows <= cus / 4) return true;
+    return rows <= cus / 2 ? n >= 50000 : rows > cus && n >= 60000;
 }
 
 size_t select_multi_wg_bytes(int rows, int n)
@@ -1153,22 +1137,25 @@ specattn_status launch_select_multi_wg(const SelectLaunch &a, void *scratch, hip
 specattn_status launch_select(const SelectLaunch &a, hipStream_t stream)
 {
     const int n = a.n_max, rows = a.B * a.H_kv, cus = cu_count();
-    // Workgroups of 256 / 512 / 1024 threads run four (at up to 8 vectors a thread) / three to two / one to a CU.  Few rows:
-    // as many threads as shorten a row's passes (512; 1024 from 8193 entries on, while every row has a CU of its own).
-    // Many rows: the shape that fits most rows on the chip at once, so that one row's load overlaps another row's passes.
+    // Few rows: as many threads as shorten a row's passes (512 up to 4096 entries, 1024 beyond while every row has a CU of its
+    // own).  Many rows: the shape that fits most rows on the chip at once, so that one row's load overlaps another row's
+    // passes (workgroups of 256 / 512 / 1024 threads: four / three, two from 8 vectors a thread on / one to a CU).
     // Block counts are per 1024 positions, so every variant has THREADS*4 a multiple of 1024.
     // Measured, us (256 CUs; shape: time):
-    //   2044 x 64 rows      512x1 8.1, 256x2 8.9;        2044 x 1024   512x1 16.1, 256x2 13.2
-    //   4096 x 128          512x2 9.2, 256x4 10.9;       4096 x 1024   512x2 18.9, 256x4 17.2
-    //   8192 x 512          512x4 14.9, 256x8 16.8;      6001 x 1024   512x4 22.1, 256x8 21.3 (one round of four to a CU);
-    //   8192 x 1536         512x4 32.0, 256x8 35.5
-    //   16384 x 256         1024x4 15.5, 512x8 16.0;     13001 x 384   1024x4 25.3, 512x8 19.0, 256x16 23.6
-    //   13001 x 2048        512x8 62.6, 256x16 58.1;     16384 x 2048  512x8 69.5, 256x16 72.6 (no vector of 512x8 idle)
-    //   32768 x 256         1024x8 25.2, 512x16 29.7;    32768 x 512   1024x8 49.1, 512x16 39.9
+    //   2044 x 64 rows      512x1 6.3, 256x2 6.9;        2044 x 1024   512x1 9.6, 256x2 9.2
+    //   4096 x 128          512x2 7.3, 256x4 8.8;        4096 x 1024   512x2 15.0, 256x4 12.2
+    //   8192 x 128          1024x2 8.8, 512x4 9.2;       8192 x 512    512x4 12.0, 256x8 14.1, 1024x2 16.9
+    //   6001 x 1024         256x8 16.3, 512x4 17.7 (one round of four to a CU);  8192 x 768  512x4 14.3, 256x8 16.3
+    //   16384 x 256         1024x4 12.0, 512x8 13.8;     13001 x 384   1024x4 19.6, 512x8 16.1, 256x16 22.3
+    //   13001 x 2048        512x8 54.3, 256x16 50.0;     16384 x 2048  512x8 60.5, 256x16 64.7 (no vector of 512x8 idle)
+    //   32768 x 256         1024x8 21.6, 512x16 27.0;    32768 x 512   1024x8 43.2, 512x16 36.9
     if (n <= 1024) return launch_one<256, 1, true>(a, stream);
     if (n <= 2048) return rows <= 2 * cus ? launch_one<512, 1, true>(a, stream) : launch_one<256, 2, true>(a, stream);
     if (n <= 4096) return rows <= 2 * cus ? launch_one<512, 2, true>(a, stream) : launch_one<256, 4, true>(a, stream);
-    if (n <= 8192) return rows > 3 * cus && rows <= 4 * cus ? launch_one<256, 8, true>(a, stream) : launch_one<512, 4, true>(a, stream);
+    if (n <= 8192) {
+        if (rows <= cus) return launch_one<1024, 2, true>(a, stream);
+        return rows > 3 * cus && rows <= 4 * cus ? launch_one<256, 8, true>(a, stream) : launch_one<512, 4, true>(a, stream);
+    }
     if (n <= 16384) {
         if (rows <= cus) return launch_one<1024, 4, true>(a, stream);
         return rows <= 2 * cus || n > 15360 ? launch_one<512, 8, true>(a, stream) : launch_one<256, 16, true>(a, stream);
