@@ -254,9 +254,13 @@ specattn_status specattn_topp_select(const specattn_select_args *sel, void *work
                                       sel->idx_capacity, sel->counts, sel->row_flags, sel->page_table, sel->page_size,
                                       sel->max_pages_per_seq, sel->emit_physical, nullptr, hs);
     }
-    if (sel->chunk_size > 1) {                      // reduce to chunk masses, then select over those
+    if (sel->chunk_size > 1) {                      // the selection runs over chunk masses
         const int cs = log2i(sel->chunk_size);
         const int nc = (sel->n_max + sel->chunk_size - 1) >> cs;
+        l.n_max = nc;
+        l.chunk_shift = cs;
+        l.blocks_per_row = (nc + SEL_BLOCK - 1) / SEL_BLOCK;
+        if (select_takes_chunks(sel->B * sel->H_kv, sel->n_max, nc)) return launch_select_chunks(l, static_cast<hipStream_t>(stream));
         float *mass = static_cast<float *>(workspace);
         st = launch_chunk_masses(sel->probs, sel->probs_stride_b, sel->probs_stride_h, sel->B, sel->H_kv, sel->n_max,
                                  sel->seq_lens, cs, nc, mass, static_cast<hipStream_t>(stream));
@@ -264,9 +268,6 @@ specattn_status specattn_topp_select(const specattn_select_args *sel, void *work
         l.probs = mass;
         l.stride_b = (int64_t)sel->H_kv * nc;
         l.stride_h = nc;
-        l.n_max = nc;
-        l.chunk_shift = cs;
-        l.blocks_per_row = (nc + SEL_BLOCK - 1) / SEL_BLOCK;
     }
     return launch_select(l, static_cast<hipStream_t>(stream));
 }

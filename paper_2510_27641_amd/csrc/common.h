@@ -50,6 +50,9 @@ specattn_status launch_select(const SelectLaunch &a, hipStream_t stream);
 bool select_multi_wg_preferred(int rows, int n);
 size_t select_multi_wg_bytes(int rows, int n);
 specattn_status launch_select_multi_wg(const SelectLaunch &a, void *scratch, hipStream_t stream);
+// Chunk-granular selection straight from rows of positions (n_max counts chunks), for the shapes select_takes_chunks accepts
+bool select_takes_chunks(int rows, int n_tokens, int n_chunks);
+specattn_status launch_select_chunks(const SelectLaunch &a, hipStream_t stream);
 // mass[r][c] = fp32(sum in fp64 of the entries of chunk c of row r), NaN if the chunk holds an invalid entry
 specattn_status launch_chunk_masses(const float *probs, int64_t stride_b, int64_t stride_h, int B, int H, int n_tokens,
                                     const int32_t *seq_lens, int chunk_shift, int n_chunks, float *mass,

@@ -220,7 +220,36 @@ constexpr unsigned select_lds(int threads)
     return stage_entries(threads) * 4 > (HIST1 + HIST2) * 8 ? stage_entries(threads) * 4 : (HIST1 + HIST2) * 8;
 }
 
-template <int THREADS, int NV4, bool RESIDENT>
+// The mass of chunk c of a row of `len` positions (Section 4: chunk-granular selection; the score of a chunk is its mass):
+// its entries added up in fp64 in ascending position order, rounded once to fp32; NaN if one of them is invalid.
+__device__ __forceinline__ float chunk_mass(const float *row, int len, int c, int chunk_shift)
+{
+    const int chunk = 1 << chunk_shift;
+    const int p0 = c << chunk_shift;
+    int p1 = p0 + chunk;
+    p1 = p1 > len ? len : p1;
+    double sum = 0.0;
+    bool bad = false;
+    auto add = [&](float x) {
+        const uint32_t u = __float_as_uint(x);
+        if (u > 0x80000000u || (u & 0x7fffffffu) >= 0x7f800000u) bad = true;     // negative, infinite or NaN
+        sum += (double)x;
+    };
+    if (p1 == p0 + chunk && chunk >= 4) {
+        typedef float f32x4a __attribute__((ext_vector_type(4), aligned(4)));
+#pragma unroll 4
+        for (int p = p0; p < p1; p += 4) {
+            const f32x4a v = *reinterpret_cast<const f32x4a *>(row + p);
+            add(v.x); add(v.y); add(v.z); add(v.w);
+        }
+    } else {
+        for (int p = p0; p < p1; ++p) add(row[p]);
+    }
+    return bad ? __uint_as_float(0x7fc00000u) : (float)sum;
+}
+
+// CHUNKED: a.probs are rows of positions; the workgroup adds the chunks up itself, into the LDS that the histograms take over.
+template <int THREADS, int NV4, bool RESIDENT, bool CHUNKED = false>
 __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
 {
     __shared__ RowShared sh;
@@ -233,6 +262,7 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     int len = a.seq_lens ? a.seq_lens[b] : a.n_tokens;
     len = len < 0 ? 0 : (len > a.n_tokens ? a.n_tokens : len);
+    const int positions = len;
     len = (len + (1 << a.chunk_shift) - 1) >> a.chunk_shift;     // rows of chunk masses: length in chunks
     len = len > a.n_max ? a.n_max : len;
     const float *row = a.probs + (int64_t)b * a.stride_b + (int64_t)h * a.stride_h;
@@ -264,11 +294,11 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
     // 14.5 us now).  An item that reaches past the row's end loads the
     // row's last whole vector instead (in bounds) and is masked afterwards; the at most three entries behind
     // the last whole vector are fetched once, by the thread that owns them.
-    const bool vec_ok = len >= 4;                              // uniform
+    const bool vec_ok = CHUNKED || len >= 4;                   // uniform
     const int last4 = (len - 4) & ~3;                          // start of the row's last whole vector
     const int tail_p = (len & 3) ? (len & ~3) : -1;            // start of the partial vector, if any
     uint4 tailv = make_uint4(0, 0, 0, 0);
-    if (vec_ok && tail_p >= 0 && tid == (tail_p % ITEM) / 4) {
+    if (!CHUNKED && vec_ok && tail_p >= 0 && tid == (tail_p % ITEM) / 4) {
         tailv.x = __float_as_uint(row[tail_p]);
         if (tail_p + 1 < len) tailv.y = __float_as_uint(row[tail_p + 1]);
         if (tail_p + 2 < len) tailv.z = __float_as_uint(row[tail_p + 2]);
@@ -286,7 +316,15 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
     };
 
     uint4 data[RESIDENT ? NV4 : 1];
-    if (RESIDENT) {
+    if constexpr (CHUNKED) {
+        static_assert(RESIDENT && ITEM * NV4 * 4 <= (int)select_lds(THREADS), "a row's masses wait in dynamic LDS");
+        float *mass = reinterpret_cast<float *>(select_dyn);
+        for (int c = tid; c < ITEM * NV4; c += THREADS) mass[c] = c < len ? chunk_mass(row, positions, c, a.chunk_shift) : 0.0f;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < NV4; ++i) data[i] = reinterpret_cast<const uint4 *>(mass)[i * THREADS + tid];
+        __syncthreads();
+    } else if (RESIDENT) {
         if (vec_ok) {
 #pragma unroll
             for (int i = 0; i < NV4; ++i) data[i] = raw_load(i);
@@ -307,7 +345,7 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
         for (int i = 0; i < NV4; ++i) {
             const int p = (i * THREADS + tid) * 4;
             uint4 u = data[i];
-            if (p + 3 >= len) u = (p == tail_p) ? tailv : make_uint4(0, 0, 0, 0);
+            if (!CHUNKED && p + 3 >= len) u = (p == tail_p) ? tailv : make_uint4(0, 0, 0, 0);
             data[i] = u;
             any |= u.x | u.y | u.z | u.w;
             const uint32_t m01 = u.x > u.y ? u.x : u.y, m23 = u.z > u.w ? u.z : u.w;
@@ -584,11 +622,11 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
         for (int k = (RESIDENT ? NV4 : n_items) * (ITEM / 32) + tid; k < mask_words; k += THREADS) mask_out[k] = 0u;
 }
 
-template <int THREADS, int NV4, bool RESIDENT>
+template <int THREADS, int NV4, bool RESIDENT, bool CHUNKED = false>
 specattn_status launch_one(const SelectLaunch &a, hipStream_t stream)
 {
     const int rows = a.B * a.H_kv;
-    hipLaunchKernelGGL((topp_select_kernel<THREADS, NV4, RESIDENT>), dim3(rows), dim3(THREADS), select_lds(THREADS), stream, a);
+    hipLaunchKernelGGL((topp_select_kernel<THREADS, NV4, RESIDENT, CHUNKED>), dim3(rows), dim3(THREADS), select_lds(THREADS), stream, a);
     return check_launch("topp_select_kernel");
 }
 
@@ -1038,8 +1076,7 @@ MwPlan mw_plan(int rows, int n)
     return p;
 }
 
-// One thread per (row, chunk): the chunk's entries are added up in fp64 in ascending position order and
-// the sum is rounded once to fp32 (Section 4: chunk-granular selection; the score of a chunk is its mass).
+// One thread per (row, chunk), where the selection does not add the chunks up itself (select_takes_chunks).
 __global__ __launch_bounds__(256) void chunk_mass_kernel(const float *__restrict__ probs, int64_t stride_b,
                                                          int64_t stride_h, int H, int n_tokens,
                                                          const int32_t *__restrict__ seq_lens, int chunk_shift,
@@ -1052,28 +1089,7 @@ __global__ __launch_bounds__(256) void chunk_mass_kernel(const float *__restrict
     const int b = (int)(r / H), h = (int)(r - (int64_t)b * H);
     int len = seq_lens ? seq_lens[b] : n_tokens;
     len = len < 0 ? 0 : (len > n_tokens ? n_tokens : len);
-    const float *row = probs + (int64_t)b * stride_b + (int64_t)h * stride_h;
-    const int chunk = 1 << chunk_shift;
-    const int p0 = c << chunk_shift;
-    int p1 = p0 + chunk;
-    p1 = p1 > len ? len : p1;
-    double sum = 0.0;
-    bool bad = false;
-    auto add = [&](float x) {
-        const uint32_t u = __float_as_uint(x);
-        if (u > 0x80000000u || (u & 0x7fffffffu) >= 0x7f800000u) bad = true;     // negative, infinite or NaN
-        sum += (double)x;
-    };
-    if (p1 == p0 + chunk && chunk >= 4) {
-        typedef float f32x4a __attribute__((ext_vector_type(4), aligned(4)));
-        for (int p = p0; p < p1; p += 4) {
-            const f32x4a v = *reinterpret_cast<const f32x4a *>(row + p);
-            add(v.x); add(v.y); add(v.z); add(v.w);
-        }
-    } else {
-        for (int p = p0; p < p1; ++p) add(row[p]);
-    }
-    mass[gid] = bad ? __uint_as_float(0x7fc00000u) : (float)sum;
+    mass[gid] = chunk_mass(probs + (int64_t)b * stride_b + (int64_t)h * stride_h, len, c, chunk_shift);
 }
 
 }  // namespace
@@ -1132,6 +1148,26 @@ specattn_status launch_select_multi_wg(const SelectLaunch &a, void *scratch, hip
     hipLaunchKernelGGL(mw_collect_kernel, grid, dim3(MW_THREADS), 0, stream, w);
     hipLaunchKernelGGL(mw_emit_kernel, grid, dim3(MW_THREADS), 0, stream, w);
     return check_launch("mw_emit_kernel");
+}
+
+bool select_takes_chunks(int rows, int n_tokens, int n_chunks)
+{
+    // A launch and the masses' way through memory less, and with many rows a row's reads overlap other rows' passes; few
+    // long rows are read faster by more workgroups than they have.  Measured, us, masses by a kernel of their own / added
+    // up in the selection (rows x positions / chunk): 32 x 2044 / 16 11.1 / 7.4, 64 x 16384 / 8 12.1 / 9.0, 8 x 32768 / 8 13.1 / 11.9, 384 x 32768 / 16
+    // 24.3 / 15.1, 2048 x 32768 / 8 91.4 / 75.3; 8 x 40000 / 32 12.2 / 10.2, x 65536 / 32 12.6 / 13.6, x 131072 / 64 14.4 / 20.6;
+    // 32 x 65536 / 32 13.3 / 13.8; 128 x 65536 / 32 22.7 / 14.8, x 131072 / 64 34.7 / 25.5; 512 x 65536 / 32 143 / 34.7.
+    return n_chunks <= 4096 && (n_tokens < 60000 || rows > cu_count() / 4);
+}
+
+// a.probs: rows of positions, a.n_max: chunks of a row.  Workgroups as launch_select takes them, but 512 threads for the
+// shortest rows too: adding the chunks up is most of their work.
+specattn_status launch_select_chunks(const SelectLaunch &a, hipStream_t stream)
+{
+    const bool few = a.B * a.H_kv <= 2 * cu_count();
+    if (a.n_max > 2048) return few ? launch_one<512, 2, true, true>(a, stream) : launch_one<256, 4, true, true>(a, stream);
+    if (few) return launch_one<512, 1, true, true>(a, stream);
+    return a.n_max <= 1024 ? launch_one<256, 1, true, true>(a, stream) : launch_one<256, 2, true, true>(a, stream);
 }
 
 specattn_status launch_select(const SelectLaunch &a, hipStream_t stream)

@@ -104,3 +104,32 @@ def test_tiny_fp32_chunks_through_the_portable_kernel():
     torch.cuda.synchronize()
     o_ref, _ = oracle_attention(w, mask)
     assert row_rel_err(out.cpu().numpy(), o_ref) <= TOL["f32"]
+
+
+@pytest.mark.parametrize("rows", [3, 600])
+@pytest.mark.parametrize("n, chunk", [(1, 2), (7, 2), (2049, 2), (4095, 2), (4097, 2), (8191, 2), (8192, 2), (8193, 2), (16383, 16)])
+def test_rows_at_the_edges_of_the_chunk_summing_selection(rows, n, chunk):
+    """Up to 4096 chunks the selection adds the chunks up itself, one more and they come through memory; few and many rows
+    take different workgroups; last chunks are partial, rows start off 16-byte boundaries, one row is invalid."""
+    rng = np.random.default_rng(n + rows)
+    lens = rng.integers(0, n + 1, size=rows).astype(np.int32)
+    lens[0] = n
+    probs = W.draft_probs(rng, rows, n, lens=np.maximum(lens, 1))
+    probs[1, 0] = -1.0
+    lens[1] = n
+    got = gpu_select_chunks(probs.reshape(rows, 1, n), 0.95, chunk, seq_lens=lens)
+    ref = oracle.topp_select_chunks(probs, 0.95, chunk, lens=lens)
+    flagged, mism = compare_select(got, ref)
+    assert mism == 0
+    assert got["flags"][1] & sa.ROW_INVALID and got["counts"][1] == 0
+
+
+@pytest.mark.parametrize("rows", [3, 80])
+def test_few_long_rows_of_chunks_come_through_memory(rows):
+    """Rows of 60000 positions or more: their masses come through memory unless there are many of them."""
+    n, chunk = 60001, 32
+    probs = W.draft_probs(np.random.default_rng(rows), rows, n)
+    got = gpu_select_chunks(probs.reshape(rows, 1, n), 0.9, chunk)
+    ref = oracle.topp_select_chunks(probs, 0.9, chunk)
+    flagged, mism = compare_select(got, ref)
+    assert mism == 0
