@@ -520,8 +520,8 @@ def main():
     pmc = os.path.join(ROOT, "profiles", "sparse_decode_attn_config3_pmc.txt")
     if os.path.exists(pmc):
         import hashlib
-        src = os.path.join(ROOT, "paper_2510_27641_amd", "csrc", "attn_mfma.hip")
-        digest = hashlib.sha256(open(src, "rb").read()).hexdigest()[:16]
+        src = [os.path.join(ROOT, "paper_2510_27641_amd", "csrc", f) for f in ("attn_mfma.hip", "attn_mfma_kernel.h")]
+        digest = hashlib.sha256(b"".join(open(f, "rb").read() for f in src)).hexdigest()[:16]
         found, val = None, None
         for ln in open(pmc):
             if ln.startswith("traffic_bytes_per_launch:"):
