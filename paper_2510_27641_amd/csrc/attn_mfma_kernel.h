@@ -53,13 +53,19 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 // The two 16-bit element types the matrix cores take here.  Both contractions use the 16x16x32 shape;
 // the softmax weights are handed over as a high part (the weight rounded to the element type) and a low
 // part (the rounding error, rounded again), so that the type's short significand costs no accuracy.
+// A tile's weights are taken in units of 2^ref, its query row's running reference: the largest weight of a tile lies between
+// 2^LO and 2^HI of them, and a reference chosen anew puts it at 2^HEAD.  bf16 has the exponents of fp32, so its reference only
+// has to follow the maximum up.  fp16 ends at 2^-24: there the reference follows it down as well, or the weights that lie far
+// below a row's one large one (an attention sink) would be lost to the products but not to the sum of the weights.
 template <bool F16> struct Half;
 template <> struct Half<false> {
+    static constexpr float HEAD = 0.0f, HI = 8.0f;
     typedef bf16x8 x8;
     typedef bf16x2 x2;
     static __device__ __forceinline__ f32x4 mfma(x8 a, x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
 };
 template <> struct Half<true> {
+    static constexpr float HEAD = 12.0f, HI = 15.0f, LO = 8.0f;
     typedef f16x8 x8;
     typedef f16x2 x2;
     static __device__ __forceinline__ f32x4 mfma(x8 a, x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
@@ -95,7 +101,6 @@ constexpr int MAX_BLOCKS = SPECATTN_MAX_N / SEL_BLOCK;   // selection blocks per
 constexpr int SLOT_BYTES = 256;       // one wave-wide LDS-DMA of 4 bytes per lane
 constexpr int KV_AUX = 2;             // cache policy of the K/V gathers: non-temporal (each row is used once)
 constexpr int SEG_COST = 12;          // cost of picking a row up, in tiles
-constexpr float RESCALE_SLACK = 8.0f; // log2 units the running max may exceed the reference by
 
 // dynamic LDS, in bytes from the start
 constexpr int OFF_WSUM = NW * WAVE_LDS;                         // int[NW]
@@ -518,9 +523,9 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
     constexpr int QTP = NQT * 16;
     constexpr int QCH = NQT * 16 * LPR;                                 // 16-byte chunks of the Q tile
     constexpr int QROUNDS = (QCH + THREADS - 1) / THREADS;              // chunks per thread
-    // Parts the softmax weights are handed over in: 16 significant bits with two of bf16, 24 with three (d = 64, where
-    // the products have time to spare), 22 with two of fp16.
-    constexpr int NP = (D == 64 && !F16) ? 3 : 2;
+    // Parts the softmax weights are handed over in: 16 significant bits with two of bf16, 22 with two of fp16, 24 with three
+    // (d = 64, where the products have time to spare).
+    constexpr int NP = D == 64 ? 3 : 2;
     constexpr bool TIGHT = NQT >= 3;                                    // registers are short: what the tile loop can fetch again is not held
     constexpr int QG = NQT <= 2 ? NQT : 1;                              // query tiles whose scores are held at a time
     const int rows = a.B * a.H_kv;
@@ -927,10 +932,30 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
                                 mloc = fmaxf(mloc, fmaxf(fmaxf(fmaxf(x[8], x[9]), fmaxf(x[10], x[11])),
                                                          fmaxf(fmaxf(x[12], x[13]), fmaxf(x[14], x[15]))));
                             mloc *= scale2;
-                            if (__any(mloc > m_ref[qt] + RESCALE_SLACK)) {     // first tile, then rare
+                            const bool above = __any(mloc > m_ref[qt] + Half<F16>::HI);     // first tile, then rare
+                            bool below = false;
+                            if constexpr (F16) {                       // (a query row's scores are in four lanes)
+                                unsigned long long low = __ballot(mloc < m_ref[qt] + Half<F16>::LO);
+                                low &= low >> 32;
+                                low &= low >> 16;
+                                below = (low & 0xffffull) != 0ull;
+                            }
+                            if (above || below) {
                                 float mx = fmaxf(mloc, __shfl_xor(mloc, 16, 64));
                                 mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-                                const float mnew = fmaxf(m_ref[qt], mx);
+                                float mnew = fmaxf(m_ref[qt], mx);
+                                if constexpr (F16) {
+                                    const float want = floorf(mx) - Half<F16>::HEAD;       // (whole numbers: rescaling is exact)
+                                    mnew = mx > m_ref[qt] + Half<F16>::HI ? want : m_ref[qt];
+                                    if (below) {
+                                        // Down only as far as the sums stay well inside the range of fp32: beyond that a
+                                        // tile adds nothing to them.
+                                        float sum = l_sum[qt] + __shfl_xor(l_sum[qt], 16, 64);
+                                        sum += __shfl_xor(sum, 32, 64);
+                                        const float least = m_ref[qt] + (float)(__builtin_amdgcn_frexp_expf(sum) - 80);
+                                        if (mx < m_ref[qt] + Half<F16>::LO && mx > -INFINITY) mnew = fminf(fmaxf(want, least), m_ref[qt]);
+                                    }
+                                }
                                 const float alpha = (m_ref[qt] == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(m_ref[qt] - mnew);
                                 l_sum[qt] *= alpha;
 #pragma unroll

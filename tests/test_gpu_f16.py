@@ -86,6 +86,53 @@ def test_half_with_new_tokens_and_large_values():
     assert row_rel_err(out, o_ref) <= TOL["f16"]
 
 
+SCORES = {   # of position j of n (natural units); the first three: one position far above all others
+    "sink first": lambda j, n: np.where(j == 0, 0.0, -17.4),
+    "sink inside": lambda j, n: np.where(j == n // 2 + 5, 0.0, -17.4),
+    "sink last": lambda j, n: np.where(j == n - 1, 0.0, -17.4),
+    "falling": lambda j, n: -70.0 * j / n,
+    "rising": lambda j, n: 70.0 * j / n - 70.0,
+    "two levels": lambda j, n: np.where(j < n // 2, 0.0, -75.0) - 9.0 * (j % 3 == 0),
+}
+
+
+@pytest.mark.parametrize("source", ["list", "mask"])
+@pytest.mark.parametrize("dtype,d", [("f16", 64), ("f16", 128), ("bf16", 64)])
+@pytest.mark.parametrize("G,T", [(1, 1), (4, 5), (6, 8), (8, 8)])
+def test_weights_far_below_the_largest_one(G, T, dtype, d, source):
+    """Every workgroup holds one long row (256 rows over the same K and V).  Weights that fp16 would round to zero next to
+    the largest one count in the output as in the sum they are divided by.  Bound: fp32 sums of 131072 weighted values,
+    taken by eight waves in tiles of 32 or 64 (some 500 additions in a chain, each rounded by 2^-24 at most): 3e-5."""
+    if source == "mask" and (d == 64 or G * T > 48):
+        pytest.skip("not built")
+    n, B, H = 131072, 32, 8
+    dt = {"f16": torch.float16, "bf16": torch.bfloat16}[dtype]
+    g = torch.Generator(device="cuda").manual_seed(G * T)
+    v1 = (1.0 + torch.randn((n, d), generator=g, device="cuda")).to(dt)
+    q = torch.zeros((B, H * G, T, d), dtype=dt, device="cuda")
+    q[..., 0] = 1.0
+    k1 = torch.zeros((n, d), dtype=dt, device="cuda")
+    k, v = (x.expand(B, H, n, d) for x in (k1, v1))
+    out = torch.empty(q.shape, dtype=torch.float32, device="cuda")
+    att, sel = sa.attn_args(q, k, v, out=out, sm_scale=1.0), None
+    if source == "mask":                                       # every position kept
+        probs, counts, bc, bits = (torch.full((B * H, m), x, dtype=torch.int32, device="cuda")
+                                   for m, x in ((n, 0), (1, n), (n // 1024, 1024), (n // 32, -1)))
+        sel = sa.select_args(probs.view(torch.float32).view(B, H, n), 0.9, indices=None, counts=counts, block_counts=bc,
+                             kept_mask=bits, reuse_selection=True)
+    ws = sa.alloc_workspace(sa.specattn_workspace_size(sel, att))
+    att.workspace, att.workspace_bytes = ws.data_ptr(), ws.numel()
+    for name, score in SCORES.items():
+        k1[:, 0] = torch.from_numpy(score(np.arange(n), n)).cuda().to(dt)
+        out.fill_(float("nan"))
+        sa.specattn_fused(sel, att) if sel is not None else sa.specattn_sparse_decode_attn(att)
+        torch.cuda.synchronize()
+        ref = (torch.softmax(k1[:, 0].double(), 0) @ v1.double()).expand(q.shape).cpu().numpy()
+        err = row_rel_err(out.cpu().numpy(), ref)
+        print(f"{name}: {err:.2e}")
+        assert err <= 3e-5, name
+
+
 def test_half_d64_on_the_portable_kernel():
     w = W.llama8b_layer(seed=74, B=2, n=1500, top_p=0.9, H_q=8, H_kv=2, T=5, d=64, dtype="f16")
     out, lse = run(w, mode="sparse")

@@ -2,8 +2,8 @@
 sizes where tiles begin and end.
 
 Bounds: 128-wide heads as everywhere (2e-3; the bf16 weights carry 16 bits).  64-wide heads hand their weights over
-with 22 bits (fp16) or 24 (bf16), so what is left is the fp32 accumulation over at most a few thousand terms, the bound
-of the fp32 route (1e-5)."""
+in three parts, 24 bits, so what is left is the fp32 accumulation over at most a few thousand terms, the bound of the fp32
+route (1e-5)."""
 import numpy as np
 import pytest
 import torch
