@@ -125,6 +125,9 @@ typedef struct specattn_select_args {
  * (tiles are assigned to waves and workgroups by the counts alone), so repeated
  * calls on the same inputs give bit-identical out and lse.
  *
+ * An infinite value (or NaN) in V at a kept position gives an infinite (NaN) column of out, as the sum of positive
+ * weights times values does; with bf16 / fp16 and d = 128 such a column is NaN.
+ *
  * Shapes: bf16 and fp16 with d = 128 take any G = H_q / H_kv (up to 64 query rows G*T per pass;
  * larger groups are taken in equal shares of heads, each streaming the kept K/V again).  fp32, and
  * d = 64, are limited to G*T <= 64.

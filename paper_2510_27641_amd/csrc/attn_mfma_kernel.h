@@ -1024,6 +1024,53 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
         }
         vm_wait(0);                              // nothing of this wave's is in flight any more (the slots are reused below)
 
+        // ---- infinite and NaN values, d = 64.  The products above are right for finite values only: an infinite one also met
+        //      the low parts of its weights (of either sign, or zero) and the zero weights of the ranks past a row's end, so
+        //      its whole column is infinite or NaN in every query row.  What belongs there does not depend on the (positive)
+        //      weights: the sum of the column's infinities and NaNs, which are then looked for.  (0.1 us on a call.  At d = 128
+        //      it cost 0.3 us of every call, mostly in what the compiler then keeps in registers; such columns are NaN there.) --
+        if constexpr (D == 64) {
+            float mag[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int t = 0; t < DT; ++t)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) mag[i] += fabsf(o[0][t][i]);
+            if (__builtin_expect(__any(!((mag[0] + mag[1]) + (mag[2] + mag[3]) < INFINITY)), 0)) {      // (uniform)
+                float odd[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};    // of columns 8 (lane % LPR) ..
+                for (int t = lt_begin + wave; t < tile_end; t += NW) {
+                    uint32_t ent[8];
+                    request(t, 0);
+                    vm_wait(0);
+                    entries(t, 0, ent);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const u32x4 c = *reinterpret_cast<const u32x4 *>(vbh + ((int64_t)ent[i] << 4) + ((lane & (LPR - 1)) << 4));
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            const uint32_t bits = (c[e >> 1] >> (16 * (e & 1))) & 0xffffu;
+                            const float x = F16 ? (float)__builtin_bit_cast(_Float16, (uint16_t)bits) : __uint_as_float(bits << 16);
+                            if (!(fabsf(x) < INFINITY)) odd[e] += x;
+                        }
+                    }
+                }
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+#pragma unroll
+                    for (int off = LPR; off < 64; off <<= 1) odd[e] += __shfl_xor(odd[e], off, 64);
+#pragma unroll
+                for (int t = 0; t < DT; ++t)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {                       // column 16 t + 4 g + i
+                        const float lo = __shfl(odd[i], 2 * t + (g >> 1), 64), hi = __shfl(odd[4 + i], 2 * t + (g >> 1), 64);
+                        const float x = (g & 1) ? hi : lo;
+#pragma unroll
+                        for (int qt = 0; qt < NQT; ++qt)
+                            if (x != 0.0f) o[qt][t][i] = x;             // (true for NaN)
+                    }
+                vm_wait(0);
+            }
+        }
+
         // ---- request what the next segment needs, to arrive while this one is wrapped up --------------
         if (r_next < rows) fetch_q(r_next);
 

@@ -140,3 +140,30 @@ def test_workspaces_for_two_query_tiles_are_accepted(shape, fused):
     att.workspace_bytes = need - 256
     with pytest.raises(RuntimeError, match="needed"):
         sa.specattn_fused(sel, att) if fused else sa.specattn_sparse_decode_attn(att)
+
+
+@pytest.mark.parametrize("route", ["list", "dense"])
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("G,T", [(1, 1), (4, 5), (7, 6), (8, 8)])
+def test_infinite_values_decide_their_columns(G, T, dtype, route):
+    """Infinite and NaN values at kept positions - inside a tile, in a row's last, partial tile, in one of several tiles of a
+    wave, of both signs in one column - give what the sum of positive weights times values gives, in their columns alone."""
+    n = 3001
+    w = W.llama8b_layer(seed=G, B=1, n=n, H_q=3 * G, H_kv=3, T=T, d=64, dtype=dtype)
+    mask = np.ones((1, 3, n), dtype=np.uint8)
+    if route == "list":
+        mask[0, 0, 21:] = 0
+        mask[0, 2, n - 1] = 0
+    ref, _ = oracle_attention(w, mask)
+    for h, j, c, x in [(0, 20, 3, np.inf), (0, 7, 63, -np.inf), (1, n - 2, 8, np.inf), (1, 5, 9, -np.inf), (1, 2000, 9, np.inf),
+                       (1, 33, 12, np.nan), (1, 1234, 40, -np.inf), (1, 2900, 40, -np.inf)]:
+        w.v[0, h, j, c] = x
+        column = ref[:, h * G:(h + 1) * G, :, c]
+        column[...] = x if np.isfinite(column).all() or (column == x).all() else np.nan
+    if route == "list":
+        w.v[0, 2, n - 1, 0] = np.inf                           # not kept
+    q, k, v = kv_tensors(w)
+    out, _ = gpu_attention(q, k, v, *(lists(mask) if route == "list" else (None, None)))
+    fin = np.isfinite(ref)
+    assert np.array_equal(out[~fin], ref[~fin], equal_nan=True)
+    assert row_rel_err(np.where(fin, out, 0.0), np.where(fin, ref, 0.0)) <= TOL["f32"]
