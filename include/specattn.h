@@ -57,7 +57,9 @@ typedef enum specattn_dtype { SPECATTN_F32 = 0, SPECATTN_BF16 = 1, SPECATTN_F16 
  * For every row the call finds tau* = max{ t : sum of probs >= t is at least
  * top_p * (row sum) } exactly - tau* is always one of the row's values - and
  * emits { j : probs[j] >= tau* } in ascending j.  Entries tied with tau* are
- * all kept.  Exact zeros are never kept.  No sort is performed.
+ * all kept.  Exact zeros are never kept.  No sort is performed.  Sums are fp64:
+ * top_p = 1 keeps every entry above 0 but those, from the smallest up, that
+ * together add less than 2^-52 of the row sum.
  */
 typedef struct specattn_select_args {
     const float *probs;          /* [B][H_kv][n_max] fp32, non-negative; need not be normalised */

@@ -110,9 +110,9 @@ __device__ __forceinline__ uint32_t mask_word(uint32_t nibble, int lane)
 // On return (uniform over the block): bin = highest non-empty bin b with
 // m_above + mass(bins >= b) >= target (lowest non-empty bin if rounding leaves none; -1 without any mass),
 // and m_above / c_above advanced to cover the bins above it.
-// A row's total is what fp64 leaves when its entries are added from the largest down: entries below half a unit in the
-// last place of the total add nothing, and their octaves count as empty.  With top_p = 1 the boundary is therefore the lowest
-// bin that is left, whatever the rounding of the sums above it.
+// With top_p = 1 the boundary is the lowest non-empty bin, whatever the rounding of the sums above it.  Bins count as empty
+// there from the octave down from which on the entries all together add less than one unit in the last place of the row's
+// total: fp64 sums taken in another order differ by as much.
 // The first wave does it alone and the others wait at the one barrier: its lanes own NB / 64 bins each from the top down (lane
 // 0 the highest), add them up as integers (bins of one exponent add exactly), and a prefix over the lanes tells every lane the
 // mass above its bins; the bins of the lane that holds the boundary are then searched one per lane.  All waves together, with
@@ -151,16 +151,22 @@ __device__ __forceinline__ int locate_bin(const unsigned long long *hist, Locate
             wave_prefix(incl_m, incl_c);
         };
         add_up();
-        double total = read_lane(incl_m, 63);
-        if (FIRST) {
-            cut = ((__double2hiint(total) >> 20) & 0x7ff) - 1023 + 73;         // 2^(field - 126) <= 2^(exponent of total - 53)
-            bool some = false;
+        const double total = read_lane(incl_m, 63);
+        if (FIRST && !(top_p < 1.0f) && total > 0.0) {
+            // sums from the bottom up: the lanes in reverse order, then each lane's octaves
+            double tail = __shfl(lm, 63 - lane, 64);
+            unsigned none = 0;
+            wave_prefix(tail, none);
+            tail = __shfl(dpp_double<0x138, 0xf>(tail), 63 - lane, 64);
+            const double ulp = __hiloint2double((((__double2hiint(total) >> 20) & 0x7ff) - 52) << 20, 0);
+            int fields = 0;
 #pragma unroll
-            for (int g = 0; g < RUNS; ++g) some |= sum[g] != 0ull && exponent(g) <= cut;
-            if (total > 0.0 && __any(some)) {                  // (rare)
-                add_up();
-                total = read_lane(incl_m, 63);
+            for (int g = 0; g < RUNS; ++g) {
+                tail += mass_of(sum[g], exponent(g));
+                fields += __popcll(__ballot(tail < ulp));
             }
+            cut = fields - 1;
+            add_up();
         }
         // mass and count of the lanes before this one (wave_shr:1)
         const double before = dpp_double<0x138, 0xf>(incl_m);

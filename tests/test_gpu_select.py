@@ -79,12 +79,36 @@ def test_heavy_tailed_rows_with_underflowed_zeros():
     assert (w.probs == 0).any()
     for p in (0.8, 0.99):
         _check(w.probs, p)
-    # p = 1 on a row whose tail lies below 2^-53 of the row sum: which of those entries still
-    # "add mass" depends on the order of the fp64 sums, so only the flagged-row contract holds
+    # p = 1 on a row whose tail lies below 2^-53 of the row sum: the oracle adds its entries one by one and stops where
+    # none of them moves the sum, the library where all that are left add less than one unit in its last place
     _check(w.probs, 1.0, allow_flagged_mismatch=True)
     w = W.long_context(seed=1, B=1, n=32768, H_kv=4, logit_clip=8.0, with_kv=False)
     for p in (0.8, 0.9, 0.95, 0.99):
         _check(w.probs, p)
+
+
+@pytest.mark.parametrize("split", [True, False])
+@pytest.mark.parametrize("n", [1000, 4096, 20000, 40000, 100001])
+def test_top_p_one_keeps_small_entries_that_add_up(n, split):
+    """Entries that are nothing next to the largest one, one by one, but together move the fp64 sum of the row: kept.
+    Entries that add less than a unit in its last place (2^-52 of 1.0) all together: not kept."""
+    rng = np.random.default_rng(n)
+    probs = np.full((1, 6, n), 2.0 ** -54)
+    probs[0, 1] = 2.0 ** -70                                   # n of them: below 2^-53
+    probs[0, 2, 300:] = 2.0 ** -62                             # 300 of 2^-54 (minus the large one), the others below 2^-46: kept too
+    probs[0, 3, 300:] = 2.0 ** -90                             # ... below 2^-73: not kept
+    probs[0, 4] = np.where(np.arange(n) < 2, 2.0 ** -54, 0.0)  # 2^-54 or 2^-53: not kept
+    probs[0, 5] = np.where(np.arange(n) < 10, 2.0 ** -55, 2.0 ** -140)     # at least 9 * 2^-55, more than 2^-52: kept
+    at = rng.integers(0, n, size=6)
+    at[2:] = 1
+    for r in range(6):
+        probs[0, r, at[r]] = 1.0
+    got = gpu_select(probs.astype(np.float32), 1.0, split=split)
+    want = [n, 1, n if (n - 300) * 2.0 ** -62 >= 2.0 ** -52 else 300, 300, 1, 10]
+    assert got["counts"].tolist() == want
+    for r in range(6):
+        keep = probs[0, r] >= got["tau"][r]
+        assert keep.sum() == want[r] and np.array_equal(got["indices"][r, :want[r]], np.flatnonzero(keep))
 
 
 def test_ties_zeros_denormals_and_scaling():
