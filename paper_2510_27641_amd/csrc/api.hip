@@ -151,6 +151,12 @@ size_t select_split_asked_bytes(const specattn_select_args *s)
     return union_workspace_bytes(s->B, s->H_kv, 1, s->n_max) + rows * 32768 + ((rows * 88 + 255) & ~(size_t)255);
 }
 size_t a256(size_t x) { return (x + 255) & ~(size_t)255; }
+// Positions that the list of a fused call over rows of n positions can stand for: the row, rounded up to whole chunks.
+int fused_positions(const specattn_select_args *s, int n)
+{
+    const int64_t chunk = s->chunk_size > 1 ? s->chunk_size : 1;
+    return (int)std::min<int64_t>((n + chunk - 1) / chunk * chunk, INT32_MAX);
+}
 
 SelectLaunch make_select(const specattn_select_args *s)
 {
@@ -364,7 +370,7 @@ specattn_status specattn_fused(const specattn_select_args *sel, const specattn_a
     if (st != SPECATTN_OK) return st;
     const int rows = sel->B * sel->H_kv;
     const bool full = attn->workspace_bytes >= workspace_bytes(sel, attn, true);
-    const size_t attn_bytes = (full ? attn_workspace_bytes : attn_workspace_accepted_bytes)(rows, attn->H_q / attn->H_kv, attn->T, attn->d, attn->n_max);
+    const size_t attn_bytes = (full ? attn_workspace_bytes : attn_workspace_accepted_bytes)(rows, attn->H_q / attn->H_kv, attn->T, attn->d, fused_positions(sel, attn->n_max));
     if (!fused_on_chip(sel, attn)) {
         // selection into the workspace, then attention over that list
         if (sel->reuse_selection || sel->block_counts || sel->kept_mask) {
@@ -449,7 +455,7 @@ static size_t workspace_bytes(const specattn_select_args *sel, const specattn_at
     if (attn->H_q % attn->H_kv) return 0;
     const int rows = attn->B * attn->H_kv;
     const bool dense = !attn->indices && !attn->counts;
-    const int cap = (sel || dense) ? attn->n_max : attn->idx_capacity * (attn->chunk_size > 1 ? attn->chunk_size : 1);
+    const int cap = sel ? fused_positions(sel, attn->n_max) : dense ? attn->n_max : attn->idx_capacity * (attn->chunk_size > 1 ? attn->chunk_size : 1);
     if (cap <= 0) return 0;
     size_t bytes = (full ? attn_workspace_bytes : attn_workspace_accepted_bytes)(rows, attn->H_q / attn->H_kv, attn->T, attn->d, cap);
     if (sel && !fused_on_chip(sel, attn)) {           // fused by way of a list in the workspace

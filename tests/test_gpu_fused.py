@@ -209,6 +209,27 @@ def test_chunk_granular_selection_through_the_fused_entry(chunk):
     assert row_rel_err(out.cpu().numpy(), o) <= TOL["bf16"]
 
 
+@pytest.mark.parametrize("n,chunk", [(1030, 1024), (1025, 512), (1279, 256), (1280, 256)])
+def test_rows_just_above_whole_chunks_run_in_the_size_asked_for(n, chunk):
+    """A list of whole chunks stands for more positions than the row has, and its splits for more partials."""
+    w = W.llama8b_layer(seed=n, B=8, n=n, H_q=64, H_kv=8, T=2, d=64, dtype="f32", top_p=0.9)
+    q, k, v = kv_tensors(w)
+    R = w.B * w.H_kv
+    counts = torch.full((R,), -7, dtype=torch.int32, device="cuda")
+    out = torch.full(q.shape, float("nan"), dtype=torch.float32, device="cuda")
+    probs = dev(w.probs)
+    sel = sa.select_args(probs, w.top_p, indices=None, counts=counts, chunk_size=chunk)
+    att = sa.attn_args(q, k, v, out=out, n_max=n)
+    ws = sa.alloc_workspace(sa.specattn_workspace_size(sel, att))
+    att.workspace, att.workspace_bytes = ws.data_ptr(), ws.numel()
+    sa.specattn_fused(sel, att)
+    torch.cuda.synchronize()
+    ref = oracle.topp_select_chunks(w.probs.reshape(-1, n), w.top_p, chunk)
+    assert np.array_equal(counts.cpu().numpy(), ref.counts)
+    mask = oracle.chunk_token_mask(ref, chunk, n, np.full(R, n, dtype=np.int32)).reshape(w.B, w.H_kv, n)
+    assert row_rel_err(out.cpu().numpy(), oracle_attention(w, mask)[0]) <= TOL["f32"]
+
+
 def test_physical_indices_do_not_apply_to_the_fused_entry():
     w = W.ragged_paged(seed=4, B=2, len_lo=50, len_hi=900)
     q, k, v = kv_tensors(w)
