@@ -132,7 +132,8 @@ typedef struct specattn_select_args {
  *
  * Shapes: bf16 and fp16 with d = 128 take any G = H_q / H_kv (up to 64 query rows G*T per pass;
  * larger groups are taken in equal shares of heads, each streaming the kept K/V again).  fp32, and
- * d = 64, are limited to G*T <= 64.
+ * d = 64, are limited to G*T <= 64.  With bf16 / fp16 and d = 128 the rows of a kv head have to lie within
+ * 64 GiB of its first one (contiguous: of a sequence, pools: of the pool); the others may lie anywhere.
  *
  * Dense layers (Section 4 keeps the first layers of the verifier dense): with
  * indices == NULL and counts == NULL every position below seq_lens[b] (n_max

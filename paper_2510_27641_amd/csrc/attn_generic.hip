@@ -1,6 +1,6 @@
 // Sparse decode attention over a selected index list (Section 3.1.2, Eq. 2-3; Section 3.5): the variant that
 // computes both contractions in fp32, for every element type - fp32 inputs, and what the 16-bit matrix-core kernel
-// does not take (more than 512 kv heads, workspaces too small for its partials).
+// does not take (more than 512 kv heads; at d = 64 workspaces too small for its partials and strides beyond its offsets).
 //
 // Work split: one workgroup of eight waves per (row, split); a split is a contiguous run of the row's kept positions
 // and tile k of 16 positions goes to wave k mod 8.  Each wave keeps the running softmax state (max m, sum l,
@@ -451,13 +451,20 @@ size_t attn_workspace_accepted_bytes(int rows, int G, int T, int d, int idx_capa
     return d == 64 ? bytes : std::max(bytes, attn_mfma_workspace_narrow_bytes(rows, G, T, d));
 }
 
+// d = 64 on the 16-bit kernel: its partials have to fit the workspace (a call is accepted with one that holds this file's
+// partials only), and the row offsets 32 bits: in pools in units of 128 bytes, contiguous rows in units of 16.
+static bool attn_mfma_takes_64(const AttnLaunch &a)
+{
+    if (a.workspace_bytes < attn_mfma_workspace_min_bytes(a.B * a.H_kv, a.H_q / a.H_kv, a.T, a.d)) return false;
+    if (a.page_table || a.indices_are_physical) return a.kv_stride_n % 64 == 0 && a.kv_stride_page % 64 == 0;
+    return a.kv_stride_n <= ((int64_t)1 << 35) / a.n_max;
+}
+
 specattn_status launch_attn(const AttnLaunch &a, hipStream_t stream)
 {
     const int rows = a.B * a.H_kv;
     const int G = a.H_q / a.H_kv;
-    // (at d = 64 a call is accepted with a workspace that holds this kernel's partials only)
-    if (attn_mfma_supported(a) && (a.d == 128 || a.workspace_bytes >= attn_mfma_workspace_min_bytes(rows, G, a.T, a.d)))
-        return launch_attn_mfma(a, stream);
+    if (attn_mfma_supported(a) && (a.d == 128 || attn_mfma_takes_64(a))) return launch_attn_mfma(a, stream);
     const int QT = G * a.T, nqt = (QT + 15) / 16;
     int ns = splits(rows, a.idx_capacity << a.chunk_shift, nqt, a.d);
     const void *fn = variant(a.dtype, a.d, nqt);

@@ -139,16 +139,20 @@ enum Layout { CONTIGUOUS = 0, PAGE_TABLE = 1, PHYSICAL = 2 };
 // have no list at all), or the kept-position mask and per-block counts of the selection (fused call).
 enum Source { LIST = 0, MASK = 1 };
 
+// Row offsets are held in 32 bits, in units of 2^unit_shift bytes.  Rows of 64 elements in pools: whole rows of 128 bytes
+// (512 GiB, more than a GPU has); the host sends strides that are no multiple of a row to the fp32 kernel.
+template <int D, int LAYOUT> constexpr int unit_shift() { return D == 64 && LAYOUT != CONTIGUOUS ? 7 : 4; }
+
 struct KvMap {
     int64_t base, stride_n, stride_page;
     const int32_t *ptab;
     int page_shift;
-    // row offsets (16-byte units, relative to `base`) of N positions, the page-table loads (if any) in flight together
-    template <int LAYOUT, int N> __device__ __forceinline__ void rel_n(const int (&idx)[N], uint32_t (&off16)[N]) const
+    // row offsets (units of 2^UNIT bytes, relative to `base`) of N positions, the page-table loads (if any) in flight together
+    template <int LAYOUT, int UNIT, int N> __device__ __forceinline__ void rel_n(const int (&idx)[N], uint32_t (&off)[N]) const
     {
         if (LAYOUT == CONTIGUOUS) {
 #pragma unroll
-            for (int i = 0; i < N; ++i) off16[i] = (uint32_t)(((int64_t)idx[i] * stride_n) >> 3);
+            for (int i = 0; i < N; ++i) off[i] = (uint32_t)(((int64_t)idx[i] * stride_n) >> (UNIT - 1));
             return;
         }
         const int mask = (1 << page_shift) - 1;
@@ -156,7 +160,7 @@ struct KvMap {
 #pragma unroll
         for (int i = 0; i < N; ++i) page[i] = LAYOUT == PAGE_TABLE ? ptab[idx[i] >> page_shift] : (idx[i] >> page_shift);
 #pragma unroll
-        for (int i = 0; i < N; ++i) off16[i] = (uint32_t)(((int64_t)page[i] * stride_page + (int64_t)(idx[i] & mask) * stride_n) >> 3);
+        for (int i = 0; i < N; ++i) off[i] = (uint32_t)(((int64_t)page[i] * stride_page + (int64_t)(idx[i] & mask) * stride_n) >> (UNIT - 1));
     }
 };
 
@@ -520,6 +524,7 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
     typedef Geo<D> GEO;
     typedef Tables<NQT, D> TAB;
     constexpr int TILE = GEO::TILE, ROW_BYTES = GEO::ROW_BYTES, LPR = GEO::LPR, RPI = GEO::RPI, PT = GEO::PT, KS = GEO::KS, PB = GEO::PB, DT = GEO::DT;
+    constexpr int UNIT = unit_shift<D, LAYOUT>();
     constexpr int QTP = NQT * 16;
     constexpr int QCH = NQT * 16 * LPR;                                 // 16-byte chunks of the Q tile
     constexpr int QROUNDS = (QCH + THREADS - 1) / THREADS;              // chunks per thread
@@ -792,7 +797,7 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
                 lds_wait();
             }
         };
-        // Row offsets (16-byte units) of the 8 rows this lane helps to fetch for tile t, whose list words (or decoded
+        // Row offsets (in units) of the 8 rows this lane helps to fetch for tile t, whose list words (or decoded
         // positions) are in slot / table s.
         auto entries = [&](int t, int s, uint32_t (&ent)[8]) {
             int pos[8], jj[8];
@@ -817,7 +822,7 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
 #pragma unroll
                 for (int i = 0; i < 8; ++i) pos[i] = (int)(e[i] << cs) | (jj[i] & low);
             }
-            map.rel_n<LAYOUT>(pos, ent);
+            map.rel_n<LAYOUT, UNIT>(pos, ent);
         };
         // Where a tile's row offsets wait for the V gathers when they are not held in registers: the position tables, which
         // only the mask source uses, or (mask source) the slot whose words have been decoded.
@@ -826,7 +831,7 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
         auto issue = [&](const char *base, char *buf, const uint32_t (&ent)[8]) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                const char *src = base + ((int64_t)ent[i] << 4) + (lane_chunk ^ chunk_flip(i));
+                const char *src = base + ((int64_t)ent[i] << UNIT) + (lane_chunk ^ chunk_flip(i));
                 __builtin_amdgcn_global_load_lds(GLOBAL_PTR(src), LDS_PTR(void, buf + i * 1024), 16, 0, KV_AUX);
             }
         };
@@ -1044,7 +1049,7 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
                     entries(t, 0, ent);
 #pragma unroll
                     for (int i = 0; i < 8; ++i) {
-                        const u32x4 c = *reinterpret_cast<const u32x4 *>(vbh + ((int64_t)ent[i] << 4) + ((lane & (LPR - 1)) << 4));
+                        const u32x4 c = *reinterpret_cast<const u32x4 *>(vbh + ((int64_t)ent[i] << UNIT) + ((lane & (LPR - 1)) << 4));
 #pragma unroll
                         for (int e = 0; e < 8; ++e) {
                             const uint32_t bits = (c[e >> 1] >> (16 * (e & 1))) & 0xffffu;

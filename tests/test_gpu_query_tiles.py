@@ -88,6 +88,47 @@ def test_paged_layouts(mode, d, H_q):
     assert row_rel_err(out, want) <= tol(w)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("layout", ["table", "physical", "odd stride", "contiguous"])
+def test_rows_beyond_64_gib(layout, dtype):
+    """64-wide heads in pools of more than 64 GiB (row offsets of 16 bytes would need more than 32 bits), with pages whose
+    stride is no multiple of a row, and in a contiguous cache whose positions lie that far apart."""
+    if torch.cuda.mem_get_info()[0] < 100 << 30:
+        pytest.skip("needs 80 GiB")
+    dt = {"bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    n, H, T = 600, 2, 5
+    w = W.llama8b_layer(seed=6, B=1, n=n, H_q=4 * H, H_kv=H, T=T, d=64, dtype=dtype)
+    mask = oracle.topp_select(w.probs.reshape(-1, n), w.top_p).mask().reshape(1, H, n)
+    idx, cnt = lists(mask)
+    q, k, v = kv_tensors(w)
+    kw = dict(n_max=n)
+    if layout == "contiguous":
+        stride = 36 * 2 ** 30 // n // 64 * 64                  # elements: n rows over 72 GiB
+        buf = torch.empty(n * stride + 4 * n * 64, dtype=dt, device="cuda")
+        kp, vp = (buf[at:].as_strided((1, H, n, 64), (2 * stride, 64, stride, 1)) for at in (0, 256))
+        kp.copy_(k), vp.copy_(v)
+    else:
+        page, extra = 16, 8 if layout == "odd stride" else 0   # a page's rows, then 16 bytes of something else
+        per = H * page * 64 + extra
+        pages = 36 * 2 ** 30 // (2 * per)                       # of K and V, 72 GiB
+        buf = torch.empty(pages * 2 * per, dtype=dt, device="cuda")
+        kp, vp = (buf[at:].as_strided((pages, H, page, 64), (2 * per, page * 64, 64, 1)) for at in (0, per))
+        at = np.linspace(0, pages - 1, -(-n // page)).astype(np.int32)[::-1].copy()
+        for i, p in enumerate(at):
+            m = min(page, n - i * page)
+            kp[p, :, :m], vp[p, :, :m] = k[0, :, i * page:i * page + m], v[0, :, i * page:i * page + m]
+        kw.update(page_size=page)
+        if layout == "physical":
+            idx = (dev(at)[(idx // page).long()] * page + idx % page).to(torch.int32)
+            kw.update(physical=True)
+        else:
+            kw.update(page_table=dev(at.reshape(1, -1)))
+    out, _ = gpu_attention(q, kp, vp, idx, cnt, **kw)
+    del buf, kp, vp
+    torch.cuda.empty_cache()
+    assert row_rel_err(out, oracle_attention(w, mask)[0]) <= TOL["f32"]
+
+
 @pytest.mark.parametrize("shape", [dict(B=40, n=250, H_q=64, H_kv=8, T=8), dict(B=1, n=60, H_q=7 * 512, H_kv=512, T=7)])
 def test_small_workspace(shape):
     """The built-in 16 MiB do not hold partials of 64 query rows for all rows of these calls: the first goes out in
