@@ -33,9 +33,10 @@ constexpr int MAP_THREADS = 1024;      // most draft layers the alignment kernel
 constexpr int MAP_LDS_BACK = 24576;    // back pointers kept in LDS (16 bits each); larger tables use the workspace
 
 // What stands for log(q) where there is none: a draft entry of 0 makes the divergence infinite as soon as a verifier
-// entry above 0 meets it (p >= 2^-149 leaves at least 1e155 in the sum, far beyond any finite divergence) and must not
-// disturb the sum otherwise (0 * -infinity would); negative and NaN entries likewise end as NaN.
-constexpr double LOG_OF_ZERO = -1e200, LOG_OF_INVALID = 1e290, DIVERGENCE_LIMIT = 1e100;
+// entry above 0 meets it (p >= 2^-149 leaves at least 1e115 in the sum, far beyond any finite divergence) and must not
+// disturb the sum otherwise (0 * -infinity would).  Entries that are no probabilities (negative, infinite, NaN) drown
+// everything else (at least 1e245, against 4e210 of the zeros); the finish kernel adds such pairs up term by term.
+constexpr double LOG_OF_ZERO = -1e160, LOG_OF_INVALID = 1e290, DIVERGENCE_LIMIT = 1e100;
 
 // Natural logarithm in fp64 of a positive fp32 value, table-driven (P. T. P. Tang, "Table-driven implementation of the
 // logarithm function in IEEE floating-point arithmetic", 1990): x = 2^e z with z in [0.6875, 1.375), table entry i
@@ -189,27 +190,43 @@ __global__ __launch_bounds__(KL_THREADS) void layer_kl_kernel(const float *__res
     }
 }
 
-// Eight pairs per workgroup: 64 threads per pair add its chunks in a fixed order.
-__global__ __launch_bounds__(512) void layer_kl_finish_kernel(const double *__restrict__ partial, int pairs, int chunks, double rows,
+// Eight pairs per workgroup: 64 threads per pair add its chunks in a fixed order.  A sum that met an entry that is no
+// probability is taken again term by term, with the logarithms of the entries as they are.
+__global__ __launch_bounds__(512) void layer_kl_finish_kernel(const double *__restrict__ partial, int m, int n, int chunks, double rows,
+                                                              const float *__restrict__ ad, const float *__restrict__ av, int64_t per_layer,
                                                               double *__restrict__ S)
 {
     __shared__ double red[64][8];
     const int pp = threadIdx.x & 7, cl = threadIdx.x >> 3;
-    const int pair = blockIdx.x * 8 + pp;
+    const int pairs = m * n, pair = blockIdx.x * 8 + pp;
+    auto sum_of_threads = [&](double s) -> double {
+        red[cl][pp] = s;
+        __syncthreads();
+#pragma unroll
+        for (int half = 32; half >= 1; half >>= 1) {
+            if (cl < half) red[cl][pp] += red[cl + half][pp];
+            __syncthreads();
+        }
+        return red[0][pp];
+    };
     double s = 0.0;
     if (pair < pairs)
         for (int c = cl; c < chunks; c += 64) s += partial[(int64_t)c * pairs + pair];
-    red[cl][pp] = s;
-    __syncthreads();
-#pragma unroll
-    for (int half = 32; half >= 1; half >>= 1) {
-        if (cl < half) red[cl][pp] += red[cl + half][pp];
-        __syncthreads();
+    s = sum_of_threads(s);
+    const bool odd = pair < pairs && !(s > -DIVERGENCE_LIMIT && s < INFINITY);
+    if (cl == 0 && pair < pairs && !odd) S[pair] = s > DIVERGENCE_LIMIT ? -INFINITY : -s / rows;
+    if (!__syncthreads_or(odd ? 1 : 0)) return;
+    s = 0.0;
+    if (odd) {
+        const int i = pair / n, j = pair - i * n;
+        const float *pd = ad + (int64_t)i * per_layer, *pv = av + (int64_t)j * per_layer;
+        for (int64_t k = cl; k < per_layer; k += 64) {
+            const double p = pv[k];
+            if (p > 0.0) s += p * (log(p) - log((double)pd[k]));
+        }
     }
-    if (cl == 0 && pair < pairs) {
-        s = red[0][pp];
-        S[pair] = s > DIVERGENCE_LIMIT ? -INFINITY : (s < -DIVERGENCE_LIMIT ? __longlong_as_double(0x7ff8000000000000ll) : -s / rows);
-    }
+    s = sum_of_threads(s);
+    if (cl == 0 && odd) S[pair] = -s / rows;
 }
 
 struct Best { double val; int idx; };
@@ -396,7 +413,8 @@ specattn_status specattn_layer_similarity(const float *attn_draft, const float *
                        m, n, per_layer, plan.iters, partial);
     st = check_launch("layer_kl_kernel");
     if (st != SPECATTN_OK) return st;
-    hipLaunchKernelGGL(layer_kl_finish_kernel, dim3((pairs + 7) / 8), dim3(512), 0, hs, partial, pairs, plan.chunks, (double)rows, S);
+    hipLaunchKernelGGL(layer_kl_finish_kernel, dim3((pairs + 7) / 8), dim3(512), 0, hs, partial, m, n, plan.chunks, (double)rows,
+                       attn_draft, attn_verifier, per_layer, S);
     return check_launch("layer_kl_finish_kernel");
 }
 

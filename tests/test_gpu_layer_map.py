@@ -63,6 +63,30 @@ def test_similarity_zeros_and_minus_infinity():
     assert rng is not None
 
 
+@pytest.mark.parametrize("rows,L", [(1, 40), (3, 700)])
+def test_similarity_of_entries_that_are_no_probabilities(rows, L):
+    """What the plain sum over p > 0 of p (log p - log q) gives: an infinite draft entry +infinity (NaN beside a zero),
+    negative and NaN ones NaN, an infinite verifier entry -infinity; nothing where the verifier has no mass."""
+    ad, av = W.layer_attention_maps(seed=20, m=10, n=4, rows=rows, L=L)
+    av[:, 0, :12] = np.maximum(av[:, 0, :12], np.float32(1e-30))
+    av[1:, 0, 2] = 0.0                                        # only verifier layer 0 has mass at position 2
+    ad[0, 0, 2] = np.inf
+    ad[1, 0, 3] = np.inf
+    ad[2, 0, 3], ad[2, 0, 5] = np.inf, 0.0
+    ad[3, 0, 3] = -0.25
+    ad[4, 0, 3] = np.nan
+    ad[5, 0, 5] = 0.0
+    ad[6, 0, 7] = 1.0                                         # under the infinite verifier entry: log q = 0 and above
+    ad[7, 0, 7] = 3.0
+    ad[8, 0, 2] = np.nan
+    av[3, 0, 7] = np.inf
+    ref, got = oracle.layer_similarity_fast(ad, av), gpu_similarity(ad, av)
+    assert np.isposinf(ref[1, :3]).all() and np.isnan(ref[2]).all() and np.isneginf(ref[[0, 5, 6, 7, 9], 3]).all()
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isposinf(got), np.isposinf(ref))
+    some = ~np.isnan(ref) & ~np.isposinf(ref)
+    close(got[some], ref[some])
+
+
 @pytest.mark.parametrize("m,n,rows,L", [(16, 16, 1, 63), (17, 15, 1, 64), (33, 31, 1, 65), (32, 33, 1, 511), (31, 65, 3, 171),
                                         (1, 32, 1, 4611), (3, 2, 1, 131072 * 2 + 512 * 3 + 1)])
 def test_similarity_tile_edges(m, n, rows, L):
