@@ -28,7 +28,8 @@ constexpr int KL_ITER_K = KL_WAVES * KL_WAVE_K;
 constexpr int KL_TI = 32, KL_TJ = 32;                // draft and verifier layers per workgroup
 constexpr int KL_ROW = KL_WAVE_K + 2;                // doubles per staged row: rows start four banks apart
 constexpr int KL_WAVE_LDS = KL_TI * KL_ROW;          // doubles
-constexpr int KL_LDS_BYTES = (KL_WAVES * KL_WAVE_LDS + 2 * 128) * (int)sizeof(double);
+constexpr int LOG_FIRST = 90, LOG_ENTRIES = 92;      // table of logarithms: of 90/128 to 181/128
+constexpr int KL_LDS_BYTES = (KL_WAVES * KL_WAVE_LDS + 2 * LOG_ENTRIES) * (int)sizeof(double);
 constexpr int MAP_THREADS = 1024;      // most draft layers the alignment kernel takes
 constexpr int MAP_LDS_BACK = 24576;    // back pointers kept in LDS (16 bits each); larger tables use the workspace
 
@@ -38,21 +39,24 @@ constexpr int MAP_LDS_BACK = 24576;    // back pointers kept in LDS (16 bits eac
 // everything else (at least 1e245, against 4e210 of the zeros); the finish kernel adds such pairs up term by term.
 constexpr double LOG_OF_ZERO = -1e160, LOG_OF_INVALID = 1e290, DIVERGENCE_LIMIT = 1e100;
 
-// Natural logarithm in fp64 of a positive fp32 value, table-driven (P. T. P. Tang, "Table-driven implementation of the
-// logarithm function in IEEE floating-point arithmetic", 1990): x = 2^e z with z in [0.6875, 1.375), table entry i
-// holds 1/c and log c of the interval of z, log x = e log 2 + log c + log1p(z/c - 1) with a series of degree 8
-// (|z/c - 1| <= 2^-7: remainder below 2^-59 of it).  The intervals next to 1 have c = 1, so that values near 1 keep
-// their relative accuracy.  About 25 instructions, against more than 100 of the general fp64 logarithm.
-constexpr uint32_t LOG_OFF = 0x3fe60000u;            // upper half of 0.6875
+// Natural logarithm in fp64 of a positive finite fp32 value from a table of logarithms (P. T. P. Tang, "Table-driven
+// implementation of the logarithm function in IEEE floating-point arithmetic", 1990).  x = 2^e y with y in
+// [sqrt(1/2), sqrt(2)), j the integer next to 128 y: log x = e log 2 + log(j / 128) + log1p((128 y - j) / j).  e, y, j and
+// the difference are exact in fp32, so the reduction runs there; the table holds 1/j and log(j / 128), the series has degree
+// 8 (|r| <= 2^-7.5: remainder below 2^-63 of it).  Next to 1, j is 128 and the result r's series alone.  Within 1.4
+// units in the last place over all of fp32; about 25 instructions, against more than 100 of the general fp64 logarithm.
+// Values that have no logarithm are taken as the nearest one that has.
 __device__ __forceinline__ double log_positive(float x, const f64x2 *tab)
 {
-    const double d = (double)x;
-    const uint32_t hi = (uint32_t)__double2hiint(d);
-    const uint32_t tmp = hi - LOG_OFF;
-    const double e = (double)((int32_t)tmp >> 20);
-    const double z = __hiloint2double((int)(hi - (tmp & 0xfff00000u)), __double2loint(d));
-    const f64x2 t = tab[(tmp >> 13) & 127u];
-    const double r = fma(z, t[0], -1.0);
+    x = __builtin_amdgcn_fmed3f(x, 1.4012985e-45f, 3.4028235e38f);
+    float y = __builtin_amdgcn_frexp_mantf(x);        // [1/2, 1), also of subnormal values
+    int e = __builtin_amdgcn_frexp_expf(x);
+    const bool low = y < 0.70710678f;
+    y *= low ? 256.0f : 128.0f;
+    e -= low ? 1 : 0;
+    const float j = rintf(y);
+    const f64x2 t = tab[(int)j - LOG_FIRST];
+    const double r = (double)(y - j) * t[0];
     double p = fma(r, -1.0 / 8, 1.0 / 7);
     p = fma(p, r, -1.0 / 6);
     p = fma(p, r, 1.0 / 5);
@@ -60,12 +64,13 @@ __device__ __forceinline__ double log_positive(float x, const f64x2 *tab)
     p = fma(p, r, 1.0 / 3);
     p = fma(p, r, -0.5);
     p = fma(p * r, r, r);
-    return fma(e, 0.69314718055994530942, t[1]) + p;
+    return fma((double)e, 0.69314718055994530942, t[1]) + p;
 }
+__device__ __forceinline__ bool has_log(float q) { return q > 0.0f && q < INFINITY; }
 __device__ __forceinline__ double log_draft(float q, const f64x2 *tab)
 {
     const double l = log_positive(q, tab);
-    return q > 0.0f && q < INFINITY ? l : (q == 0.0f ? LOG_OF_ZERO : LOG_OF_INVALID);
+    return has_log(q) ? l : (q == 0.0f ? LOG_OF_ZERO : LOG_OF_INVALID);
 }
 
 // Entries k .. k+3 of a layer, zero at and beyond `end`.
@@ -106,11 +111,9 @@ __global__ __launch_bounds__(KL_THREADS) void layer_kl_kernel(const float *__res
     const int l16 = lane & 15, g = lane >> 4;
     const int i0 = blockIdx.y * KL_TI, j0 = blockIdx.z * KL_TJ;
     double *lq = kl_lds + wave * KL_WAVE_LDS;
-    if (tid < 128) {
-        const double lo = __hiloint2double((int)(LOG_OFF + ((uint32_t)tid << 13)), 0);
-        const double up = __hiloint2double((int)(LOG_OFF + ((uint32_t)(tid + 1) << 13)), 0);
-        const double inv = (lo == 1.0 || up == 1.0) ? 1.0 : 2.0 / (lo + up);
-        tab[tid] = (f64x2){inv, -log(inv)};
+    if (tid < LOG_ENTRIES) {
+        const double j = (double)(LOG_FIRST + tid);
+        tab[tid] = (f64x2){1.0 / j, log(j / 128.0)};
     }
     __syncthreads();
     f64x4 acc[2][3];                                  // [verifier tile][draft tile 0, 1, the verifier's own logarithms]
@@ -154,10 +157,9 @@ __global__ __launch_bounds__(KL_THREADS) void layer_kl_kernel(const float *__res
                 if (j0 + 16 * a >= n) continue;       // (uniform)
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
-                    // 0 * log(0 / q) = 0: entries that are not above 0 add nothing
-                    const bool some = p[a][s][c] > 0.0f;
-                    const double x = some ? (double)p[a][s][c] : 0.0;
-                    const double lp = some ? (p[a][s][c] < INFINITY ? log_positive(p[a][s][c], tab) : INFINITY) : 0.0;
+                    // 0 * log(0 / q) = 0: entries that are not above 0 add nothing (nor do their logarithms)
+                    const double x = fmaxf(p[a][s][c], 0.0f);
+                    const double lp = log_positive(p[a][s][c], tab);
                     acc[a][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0[c >> 1][c & 1], x, acc[a][0], 0, 0, 0);
                     acc[a][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1[c >> 1][c & 1], x, acc[a][1], 0, 0, 0);
                     acc[a][2] = __builtin_amdgcn_mfma_f64_16x16x4f64(lp, x, acc[a][2], 0, 0, 0);

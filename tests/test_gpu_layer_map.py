@@ -80,6 +80,7 @@ def test_similarity_of_entries_that_are_no_probabilities(rows, L):
     ad[7, 0, 7] = 3.0
     ad[8, 0, 2] = np.nan
     av[3, 0, 7] = np.inf
+    av[2, 0, 9], av[2, 0, 10] = np.nan, -0.5                  # (not above 0)
     ref, got = oracle.layer_similarity_fast(ad, av), gpu_similarity(ad, av)
     assert np.isposinf(ref[1, :3]).all() and np.isnan(ref[2]).all() and np.isneginf(ref[[0, 5, 6, 7, 9], 3]).all()
     assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isposinf(got), np.isposinf(ref))
