@@ -222,7 +222,9 @@ size_t specattn_union_workspace_size(const specattn_union_args *args);
 /* Selection alone.  The plain selection (single positions, exact tau*) never needs a workspace: without one
    every row is handled by one workgroup.  When specattn_workspace_size(sel, NULL) is not 0 for it (long
    rows) and a workspace of that size is given, each row is split over many workgroups instead; the results
-   are the same (with kept_mask rows are not split).  The chunk and bisection modes need their workspace (SPECATTN_EWORKSPACE otherwise). */
+   are the same (with kept_mask rows are not split).  Few rows of 65536 positions or more (n_max / 2048 of them at most)
+   are split with a smaller workspace too, at a microsecond or two more: 36 KiB and a bit per position (n_max rounded up to
+   4096) for every row are enough.  The chunk and bisection modes need their workspace (SPECATTN_EWORKSPACE otherwise). */
 specattn_status specattn_topp_select(const specattn_select_args *sel, void *workspace,
                                      size_t workspace_bytes, void *stream);
 

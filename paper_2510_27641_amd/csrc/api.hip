@@ -141,9 +141,10 @@ bool fused_on_chip(const specattn_select_args *s, const specattn_attn_args *a)
     probe.dtype = (int)a->dtype; probe.d = a->d; probe.T = a->T; probe.H_kv = a->H_kv;
     return attn_mfma_supported(probe) && a->d == 128 && s->chunk_size <= 1;
 }
-// The workspace from which on a selection of few long rows counts as asking for the split, which leaves no bits: thresholds,
-// ballots and 32 KiB of bins per row.  (Other shapes are split as well where there is room, but only calls of these
-// shapes were ever refused for asking for bits.)
+// The least workspace with which a selection of few long rows is split over many workgroups: 32 KiB of counters and a bit
+// per position for every row (what such a call asked for when its row histograms were added up in memory).  From it up to
+// what specattn_workspace_size asks for, the slices of a row share one histogram.  With less, and for the other shapes
+// that are split with less than is asked for, every row is handled by one workgroup.
 size_t select_split_asked_bytes(const specattn_select_args *s)
 {
     const size_t rows = (size_t)s->B * s->H_kv;
@@ -237,14 +238,15 @@ specattn_status specattn_topp_select(const specattn_select_args *sel, void *work
     const size_t need = specattn_workspace_size(sel, nullptr);
     // the plain selection works without a workspace; with one, few long rows are split over many workgroups
     const bool given = plain && need > 0 && workspace && aligned(workspace, 256);
-    const bool split = given && workspace_bytes >= need;
-    if (given && sel->kept_mask && workspace_bytes >= select_split_asked_bytes(sel)) { set_error("kept_mask is not written by the split selection of few long rows: call without a workspace"); return SPECATTN_EUNSUPPORTED; }
+    const bool asked = given && workspace_bytes >= select_split_asked_bytes(sel);
+    const bool split = asked || (given && workspace_bytes >= need);
+    if (asked && sel->kept_mask) { set_error("kept_mask is not written by the split selection of few long rows: call without a workspace"); return SPECATTN_EUNSUPPORTED; }
     if (!plain) {
         st = check_workspace(workspace, workspace_bytes, need);
         if (st != SPECATTN_OK) return st;
     }
     SelectLaunch l = make_select(sel);
-    if (split && !sel->kept_mask) return launch_select_multi_wg(l, workspace, static_cast<hipStream_t>(stream));
+    if (split && !sel->kept_mask) return launch_select_multi_wg(l, workspace, workspace_bytes, static_cast<hipStream_t>(stream));
     if (sel->bisect_iters > 0) {                    // Algorithm 2 as the paper runs it, then the mask and compaction passes
         // workspace: [tau][valid][flags][block counts][ballots], the layout of the union with one member per row
         const size_t rows = (size_t)sel->B * sel->H_kv, a256 = (rows * 4 + 255) & ~(size_t)255;

@@ -46,10 +46,11 @@ struct SelectLaunch {
     uint32_t *kept_mask;     // may be null; [rows][blocks_per_row * SEL_BLOCK / 32]: bit i of word w = position 32 w + i kept
 };
 specattn_status launch_select(const SelectLaunch &a, hipStream_t stream);
-// Few long rows: each row split over many workgroups, lists written.  `scratch` holds select_multi_wg_bytes(rows, n_max).
+// Few long rows: each row split over many workgroups, lists written.  `scratch` holds select_multi_wg_bytes(rows, n_max), or
+// less, down to 20 KiB per row, at some cost in time.
 bool select_multi_wg_preferred(int rows, int n);
 size_t select_multi_wg_bytes(int rows, int n);
-specattn_status launch_select_multi_wg(const SelectLaunch &a, void *scratch, hipStream_t stream);
+specattn_status launch_select_multi_wg(const SelectLaunch &a, void *scratch, size_t scratch_bytes, hipStream_t stream);
 // Chunk-granular selection straight from rows of positions (n_max counts chunks), for the shapes select_takes_chunks accepts
 bool select_takes_chunks(int rows, int n_tokens, int n_chunks);
 specattn_status launch_select_chunks(const SelectLaunch &a, hipStream_t stream);

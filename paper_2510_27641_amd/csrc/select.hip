@@ -648,6 +648,10 @@ specattn_status launch_one(const SelectLaunch &a, hipStream_t stream)
 // histogram passes that added up by atomics in memory, with a launch to clear them, one for the threshold and the mask and
 // compaction passes of the union, took 50 us.  Bound by the trips to memory of each launch (ranges, then
 // histograms, then entries, about a microsecond each) and the locate steps (2 us each), not by the row's bytes.
+// With less workspace than that asks for (a histogram per slice), the slices of a row add theirs up in one histogram of
+// the row, by atomics in memory after a launch that clears it (integers: any order gives the same sums), and as many of the
+// boundary bin's entries are collected as there is room for: 32 rows of 131072 in an eighth of the workspace 24.4 us
+// (24.1 with all of it, 71 without any), 8 of 65536 20.8 (19.2, 26.7).
 constexpr int MW_THREADS = 512;
 constexpr int MW_WAVES = MW_THREADS / 64;
 constexpr int MW_ITEM = MW_THREADS * 4;           // positions a workgroup loads with one instruction
@@ -668,13 +672,13 @@ struct MwState {                     // outcome of the first locate step
 struct MwHead { int lo, hi, bad, pad; };     // non-empty bins of a slice's histogram (lo > hi: none)
 struct MwLaunch {
     SelectLaunch a;
-    unsigned long long *hist;        // [rows * slices][NB1]
-    MwHead *head;                    // [rows * slices]
+    unsigned long long *hist;        // [rows * slices][NB1]; LEAN: [rows][NB1]
+    MwHead *head;                    // [rows * slices]; LEAN: [rows], all bins
     uint32_t *entries;               // [rows * slices][collect] a slice's entries in the boundary bin, in any order
     int4 *counts;                    // [rows * slices] a slice's entries above the boundary bin and in it; smallest and largest of the latter
     MwState *state;                  // [rows]
     int slices, slice_len;           // workgroups per row; positions per workgroup (a multiple of MW_ITEM)
-    int collect;                     // slice_len >> MW_COLLECT_SHIFT
+    int collect;                     // entries of a slice that can be collected: slice_len >> MW_COLLECT_SHIFT; LEAN: at most
 };
 
 __device__ __forceinline__ int mw_row_len(const SelectLaunch &a, int b)
@@ -793,7 +797,7 @@ __device__ __forceinline__ int mw_sum(int v, int *slot)
 }
 
 // Step 1.
-__global__ __launch_bounds__(MW_THREADS) void mw_hist_kernel(MwLaunch w)
+template <bool LEAN> __device__ __forceinline__ void mw_hist(const MwLaunch &w)
 {
     __shared__ unsigned long long hist[NB1];
     __shared__ int range[2][MW_WAVES];
@@ -812,6 +816,16 @@ __global__ __launch_bounds__(MW_THREADS) void mw_hist_kernel(MwLaunch w)
         if (x) atomicAdd(&hist[x >> 20], packed_entry(x));
     });
     const bool any_bad = __syncthreads_or(bad ? 1 : 0) != 0;             // also orders the LDS atomics
+    if constexpr (LEAN) {
+#pragma unroll
+        for (int k = 0; k < NB1 / MW_THREADS; ++k) {
+            const int bin = k * MW_THREADS + tid;
+            const unsigned long long v = hist[bin];
+            if (v) atomicAdd(&w.hist[(size_t)r * NB1 + bin], v);
+        }
+        if (any_bad && tid == 0) w.head[r].bad = 1;
+        return;
+    }
     // lowest and highest non-empty bin: every wave looks at its 64 bins of each group
     unsigned long long bins[NB1 / MW_THREADS];
     int lo = NB1, hi = -1;
@@ -841,8 +855,10 @@ __global__ __launch_bounds__(MW_THREADS) void mw_hist_kernel(MwLaunch w)
     if (tid == 0) w.head[at] = MwHead{lo, hi, any_bad ? 1 : 0, 0};
 }
 
+__global__ __launch_bounds__(MW_THREADS) void mw_hist_kernel(MwLaunch w) { mw_hist<false>(w); }
+
 // Step 2.
-__global__ __launch_bounds__(MW_THREADS) void mw_collect_kernel(MwLaunch w)
+template <bool LEAN> __device__ __forceinline__ void mw_collect(const MwLaunch &w)
 {
     __shared__ unsigned long long hist[HIST1];
     __shared__ Located located;
@@ -856,11 +872,11 @@ __global__ __launch_bounds__(MW_THREADS) void mw_collect_kernel(MwLaunch w)
     const int len = mw_row_len(a, b);
     const size_t row_at = (size_t)r * w.slices, at = row_at + sl;
     // (requested ahead of the slice: the histograms are fetched as soon as the ranges are here)
-    const MwHead head = w.head[row_at + (lane < w.slices ? lane : 0)];
+    const MwHead head = w.head[LEAN ? (size_t)r : row_at + (lane < w.slices ? lane : 0)];
     MwSlice slice(w, b, h, sl, len);
     if (tid == 0) found = 0;
     int cnt[NB1 / MW_THREADS];
-    const bool bad = mw_gather(hist, head, w.hist + row_at * NB1, w.slices, sl, cnt);
+    const bool bad = mw_gather(hist, head, w.hist + (LEAN ? (size_t)r : row_at) * NB1, LEAN ? 1 : w.slices, LEAN ? 0 : sl, cnt);
     double target = 0.0, m_above = 0.0;
     unsigned c_above = 0;
     unsigned long long bin_packed = 0;
@@ -870,8 +886,9 @@ __global__ __launch_bounds__(MW_THREADS) void mw_collect_kernel(MwLaunch w)
     if (invalid) return;
     const uint32_t want = (uint32_t)bin;
     uint32_t *mine = w.entries + at * w.collect;
-    int lo = 0x7fffffff, hi = 0;
+    int lo = 0x7fffffff, hi = 0, counted = 0;
     slice.each([&](uint32_t x) {
+        if constexpr (LEAN) counted += ((int)x >> 20) > bin ? 1 : 0;     // (-0.0 is below every bin)
         if ((x >> 20) == want && x) {
             const int k = atomicAdd(&found, 1);
             if (k < w.collect) mine[k] = x;
@@ -886,10 +903,12 @@ __global__ __launch_bounds__(MW_THREADS) void mw_collect_kernel(MwLaunch w)
         hi = g > hi ? g : hi;
     }
     if (lane == 0) { ends[0][tid >> 6] = lo; ends[1][tid >> 6] = hi; }
-    int above = 0;
+    int above = counted;
+    if constexpr (!LEAN) {
 #pragma unroll
-    for (int k = 0; k < NB1 / MW_THREADS; ++k)
-        if (k * MW_THREADS + tid > bin) above += cnt[k];
+        for (int k = 0; k < NB1 / MW_THREADS; ++k)
+            if (k * MW_THREADS + tid > bin) above += cnt[k];
+    }
     above = mw_sum(above, sums);                                         // (a barrier: `found` and `ends` are complete)
 #pragma unroll
     for (int k = 0; k < MW_WAVES; ++k) {
@@ -898,6 +917,8 @@ __global__ __launch_bounds__(MW_THREADS) void mw_collect_kernel(MwLaunch w)
     }
     if (tid == 0) w.counts[at] = make_int4(above, found, lo, hi);
 }
+
+__global__ __launch_bounds__(MW_THREADS) void mw_collect_kernel(MwLaunch w) { mw_collect<false>(w); }
 
 // Step 3: tau*, count and flags of the row (slice 0), and the list entries of the slice.
 __global__ __launch_bounds__(MW_THREADS) void mw_emit_kernel(MwLaunch w)
@@ -1062,6 +1083,17 @@ __global__ __launch_bounds__(MW_THREADS) void mw_emit_kernel(MwLaunch w)
 }
 static_assert(MW_FLIGHT * MW_WAVES <= 64, "a wave scans the totals of a round");
 
+// The lean form.  (These kernels stand behind the three above: between them they cost those half a microsecond of 50,
+// by where the code then lies.)  Clears a row per workgroup.
+__global__ __launch_bounds__(MW_THREADS) void mw_clear_kernel(MwLaunch w)
+{
+#pragma unroll
+    for (int k = 0; k < NB1 / MW_THREADS; ++k) w.hist[(size_t)blockIdx.x * NB1 + k * MW_THREADS + threadIdx.x] = 0ull;
+    if (threadIdx.x == 0) w.head[blockIdx.x] = MwHead{0, NB1 - 1, 0, 0};
+}
+__global__ __launch_bounds__(MW_THREADS) void mw_hist_lean_kernel(MwLaunch w) { mw_hist<true>(w); }
+__global__ __launch_bounds__(MW_THREADS) void mw_collect_lean_kernel(MwLaunch w) { mw_collect<true>(w); }
+
 inline size_t mw_align(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct MwPlan { int slices, slice_len; };
@@ -1132,26 +1164,40 @@ size_t select_multi_wg_bytes(int rows, int n)
            mw_align((size_t)rows * sizeof(MwState));
 }
 
-// `scratch` holds select_multi_wg_bytes
-specattn_status launch_select_multi_wg(const SelectLaunch &a, void *scratch, hipStream_t stream)
+// `scratch` holds select_multi_wg_bytes, or at least 20 KiB per row
+specattn_status launch_select_multi_wg(const SelectLaunch &a, void *scratch, size_t scratch_bytes, hipStream_t stream)
 {
     const int rows = a.B * a.H_kv;
     const MwPlan plan = mw_plan(rows, a.n_max);
     const size_t S = (size_t)rows * plan.slices;
+    const bool lean = scratch_bytes < select_multi_wg_bytes(rows, a.n_max);
+    const size_t hists = lean ? (size_t)rows : S;
     MwLaunch w;
     w.a = a;
     w.slices = plan.slices;
     w.slice_len = plan.slice_len;
     w.collect = plan.slice_len >> MW_COLLECT_SHIFT;
+    if (lean) {
+        const size_t fixed = mw_align(hists * NB1 * 8) + mw_align(hists * sizeof(MwHead)) + mw_align(S * sizeof(int4)) + mw_align((size_t)rows * sizeof(MwState));
+        if (scratch_bytes < fixed) { set_error("workspace has %zu bytes, too few for the split selection", scratch_bytes); return SPECATTN_EWORKSPACE; }
+        const size_t room = ((scratch_bytes - fixed) & ~(size_t)255) / 4 / S;
+        if (room < (size_t)w.collect) w.collect = (int)room;
+    }
     char *p = static_cast<char *>(scratch);
-    w.hist = reinterpret_cast<unsigned long long *>(p); p += mw_align(S * NB1 * 8);
+    w.hist = reinterpret_cast<unsigned long long *>(p); p += mw_align(hists * NB1 * 8);
     w.entries = reinterpret_cast<uint32_t *>(p); p += mw_align(S * w.collect * 4);
-    w.head = reinterpret_cast<MwHead *>(p); p += mw_align(S * sizeof(MwHead));
+    w.head = reinterpret_cast<MwHead *>(p); p += mw_align(hists * sizeof(MwHead));
     w.counts = reinterpret_cast<int4 *>(p); p += mw_align(S * sizeof(int4));
     w.state = reinterpret_cast<MwState *>(p);
     const dim3 grid((unsigned)S);
-    hipLaunchKernelGGL(mw_hist_kernel, grid, dim3(MW_THREADS), 0, stream, w);
-    hipLaunchKernelGGL(mw_collect_kernel, grid, dim3(MW_THREADS), 0, stream, w);
+    if (lean) {
+        hipLaunchKernelGGL(mw_clear_kernel, dim3(rows), dim3(MW_THREADS), 0, stream, w);
+        hipLaunchKernelGGL(mw_hist_lean_kernel, grid, dim3(MW_THREADS), 0, stream, w);
+        hipLaunchKernelGGL(mw_collect_lean_kernel, grid, dim3(MW_THREADS), 0, stream, w);
+    } else {
+        hipLaunchKernelGGL(mw_hist_kernel, grid, dim3(MW_THREADS), 0, stream, w);
+        hipLaunchKernelGGL(mw_collect_kernel, grid, dim3(MW_THREADS), 0, stream, w);
+    }
     hipLaunchKernelGGL(mw_emit_kernel, grid, dim3(MW_THREADS), 0, stream, w);
     return check_launch("mw_emit_kernel");
 }

@@ -37,7 +37,8 @@ def gpu_select(probs: np.ndarray, top_p: float, *, seq_lens=None, capacity=None,
                page_size=0, emit_physical=False, probs_dev=None, split=True):
     """Run specattn_topp_select; returns dict of numpy results (+ device tensors).
 
-    split: hand over the optional workspace, with which few long rows are split over many workgroups."""
+    split: hand over the optional workspace, with which few long rows are split over many workgroups (a number: of so many
+    bytes)."""
     p = dev(probs) if probs_dev is None else probs_dev
     B, H, n = p.shape
     R = B * H
@@ -50,7 +51,7 @@ def gpu_select(probs: np.ndarray, top_p: float, *, seq_lens=None, capacity=None,
     pt = None if page_table is None else dev(np.asarray(page_table, dtype=np.int32))
     args = sa.select_args(p, top_p, indices=idx, counts=counts, thresholds=tau, row_flags=flags,
                           seq_lens=sl, page_table=pt, page_size=page_size, emit_physical=emit_physical)
-    need = sa.specattn_workspace_size(args, None) if split else 0
+    need = (sa.specattn_workspace_size(args, None) if split is True else split) if split else 0
     ws = sa.alloc_workspace(need) if need else None
     sa.specattn_topp_select(args, ws)
     torch.cuda.synchronize()

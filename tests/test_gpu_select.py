@@ -316,3 +316,50 @@ def test_split_path_flat_rows(rows, n):
         for k in ("counts", "tau", "flags"):
             assert np.array_equal(got[k], one[k]), k
         assert np.array_equal(got["indices"], one["indices"])
+
+
+def least_split_bytes(rows, n):
+    """32 KiB of counters and a bit per position for every row, with the alignment of each part."""
+    a256 = lambda x: -(-x // 256) * 256
+    blocks = -(-n // 4096)
+    return 3 * a256(rows * 4) + a256(rows * blocks * 4) + a256(rows * blocks * 512) + rows * 32768 + a256(rows * 88)
+
+
+@pytest.mark.parametrize("rows,n", [(1, 65536), (5, 65539), (32, 131072), (9, 200003), (130, 266241)])
+def test_split_path_in_the_least_workspace(rows, n):
+    """Less room than is asked for: one histogram per row, and as many collected entries as fit (the flat rows' do not).  The
+    results are the same; nothing is written behind the workspace."""
+    rng = np.random.default_rng(rows + 1)
+    few = min(rows, 12)
+    spread = np.geomspace(1e-3, 3.0, few)[:, None]
+    logit = spread * rng.standard_normal((few, n), dtype=np.float32)
+    probs = np.exp(logit - logit.max(1, keepdims=True)).astype(np.float32)
+    probs /= probs.sum(1, keepdims=True)
+    probs[0, n - 1] = -0.0
+    if few > 4:
+        probs[1, ::2] = 0.0
+        probs[1, :n // 2] *= np.float32(1e-40) / np.float32(probs[1].max())  # subnormal entries
+        probs[2, 77] = np.nan
+        probs[3, :] = np.float32(1.0 / n)                                    # ties
+    probs = np.resize(probs, (1, rows, n))
+    lens = np.array([n - 3], dtype=np.int32)
+    least = least_split_bytes(rows, n)
+    ws = torch.full((least + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+    pr, sl = dev(probs), dev(lens)
+    for p in (0.6, 1.0):
+        one = gpu_select(None, p, probs_dev=pr, split=False, seq_lens=lens)
+        got = gpu_select(None, p, probs_dev=pr, split=least, seq_lens=lens)
+        for k in ("counts", "tau", "flags", "indices"):
+            assert np.array_equal(got[k], one[k]), k
+    idx = torch.full((rows, n), -7, dtype=torch.int32, device="cuda")
+    counts = torch.full((rows,), -7, dtype=torch.int32, device="cuda")
+    sa.specattn_topp_select(sa.select_args(pr, 1.0, indices=idx, counts=counts, seq_lens=sl), ws[:least])
+    torch.cuda.synchronize()
+    assert np.array_equal(idx.cpu().numpy(), one["indices"]) and (ws[least:] == 0xA5).all().item()
+    bits = torch.zeros((rows, -(-n // 1024) * 32), dtype=torch.int32, device="cuda")
+    args = sa.select_args(pr, 1.0, indices=idx, counts=counts, seq_lens=sl, kept_mask=bits)
+    with pytest.raises(RuntimeError, match="kept_mask"):
+        sa.specattn_topp_select(args, ws[:least])
+    sa.specattn_topp_select(args, ws[:least // 256 * 256 - 256])             # (not split)
+    torch.cuda.synchronize()
+    assert np.array_equal(counts.cpu().numpy(), one["counts"])
