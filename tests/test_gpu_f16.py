@@ -1,5 +1,5 @@
 """IEEE half K/V/Q through every attention route (the paper's own models run in fp16): list, fused, dense,
-new tokens, paged, large GQA groups on the matrix-core kernel; d = 64 on the portable one."""
+new tokens, paged, large GQA groups, d = 64."""
 import numpy as np
 import pytest
 import torch
@@ -133,7 +133,7 @@ def test_weights_far_below_the_largest_one(G, T, dtype, d, source):
         assert err <= 3e-5, name
 
 
-def test_half_d64_on_the_portable_kernel():
+def test_half_d64():
     w = W.llama8b_layer(seed=74, B=2, n=1500, top_p=0.9, H_q=8, H_kv=2, T=5, d=64, dtype="f16")
     out, lse = run(w, mode="sparse")
     o_ref, l_ref = reference(w, "sparse")

@@ -208,3 +208,69 @@ def test_infinite_values_decide_their_columns(G, T, dtype, route):
     fin = np.isfinite(ref)
     assert np.array_equal(out[~fin], ref[~fin], equal_nan=True)
     assert row_rel_err(np.where(fin, out, 0.0), np.where(fin, ref, 0.0)) <= TOL["f32"]
+
+
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("mode", ["list", "dense", "chunks", "fused", "fused chunks"])
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("d,G,T", [(64, 4, 5), (64, 8, 8), (128, 7, 6), (128, 8, 8)])
+def test_options_together(d, G, T, dtype, mode, paged):
+    """Ragged lengths (an empty sequence, partial chunks), lists of positions or chunks, dense calls and the fused call, in
+    both layouts, each without and with new tokens behind the cache and the copy of the output in the inputs' type; 64-wide
+    heads, and three and four query tiles.  Every chunk list ends in the partial chunk of its row (the recency band)."""
+    w = W.ragged_paged(seed=d + G, B=4, len_lo=33, len_hi=2300, H_q=2 * G, H_kv=2, T=T, d=d)
+    w.seq_lens[2] = 0
+    w.probs[2] = 0.0
+    B, H, n = w.probs.shape
+    rng = np.random.default_rng(9)
+    k_new, v_new = (rng.standard_normal((B, H, T, d), dtype=np.float32) for _ in range(2))
+    if dtype == "f16":
+        w.dtype = "f16"
+        w.q, w.k, w.v = (a.astype(np.float16).astype(np.float32) for a in (w.q, w.k, w.v))
+        bits = lambda a: a.astype(np.float16).view(np.uint16)
+    else:
+        bits = lambda a: W.round_to_bf16_bits(a).reshape(a.shape)
+    lens, chunk = w.row_lens(), 16 if "chunks" in mode else 0
+    if mode == "dense":
+        mask = np.arange(n) < lens[:, None]
+    elif chunk:
+        ref = oracle.topp_select_chunks(w.probs.reshape(-1, n), w.top_p, chunk, lens=lens)
+        mask = oracle.chunk_token_mask(ref, chunk, n, lens)
+    else:
+        ref = oracle.topp_select(w.probs.reshape(-1, n), w.top_p, lens)
+        mask = ref.mask()
+    mask = mask.reshape(B, H, n).astype(np.uint8)
+    dt = {"bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    kw = dict(seq_lens=dev(w.seq_lens))
+    if paged:
+        kw.update(page_table=dev(w.page_table), page_size=W.PAGE_SIZE, n_max=n)
+        q, k, v = kv_tensors(w)
+    else:
+        q, k, v = (dev(a, dt) for a in (w.q, w.k, w.v))
+    sel, call = None, sa.specattn_sparse_decode_attn
+    counts = torch.zeros(B * H, dtype=torch.int32, device="cuda")
+    if mode in ("list", "chunks"):
+        cap = -(-n // chunk) if chunk else n
+        kw.update(indices=dev(np.ascontiguousarray(ref.indices[:, :cap])), counts=dev(ref.counts), chunk_size=chunk)
+    elif mode != "dense":
+        probs = dev(w.probs)
+        sel = sa.select_args(probs, w.top_p, indices=None, counts=counts, seq_lens=kw["seq_lens"], chunk_size=chunk)
+        call = lambda a: sa.specattn_fused(sel, a)
+    for more in (False, True):
+        out = torch.full(q.shape, float("nan"), dtype=torch.float32, device="cuda")
+        lse = torch.full(q.shape[:3], float("nan"), dtype=torch.float32, device="cuda")
+        low = torch.full(q.shape, float("nan"), dtype=dt, device="cuda")
+        new = dict(k_new=dev(k_new, dt), v_new=dev(v_new, dt), out_lowp=low) if more else {}
+        att = sa.attn_args(q, k, v, out=out, lse=lse, **kw, **new)
+        ws = sa.alloc_workspace(sa.specattn_workspace_size(sel, att))
+        att.workspace, att.workspace_bytes = ws.data_ptr(), ws.numel()
+        call(att)
+        torch.cuda.synchronize()
+        want, want_lse = oracle.masked_attention(bits(w.q), bits(w.k), bits(w.v), mask, bf16=dtype == "bf16", f16=dtype == "f16",
+                                                 lens=w.seq_lens, **(dict(k_new=bits(k_new), v_new=bits(v_new)) if more else {}))
+        assert row_rel_err(out.cpu().numpy(), want) <= tol(w)
+        fin = np.isfinite(want_lse)
+        got = lse.cpu().numpy()
+        assert np.array_equal(np.isneginf(got), ~fin) and np.abs(got[fin] - want_lse[fin]).max() <= 1e-3
+        if more:
+            assert torch.equal(low, out.to(dt))
