@@ -18,7 +18,8 @@
 //                   4g + c are what the score product left in this very lane.
 // What bounds it: small calls, latency (list word -> K and V rows -> eight states); large ones, HBM or, from two
 // query tiles on, the fp32 matrix rate.  The kernel before it fed the vector ALU from LDS, four barriers per 32 positions:
-// selection and attention of 8 rows of 1024 positions (d = 64, 5 tokens) 26.9 us then, 13.9 us now; 32 rows of 424 (d =
+// selection and attention of 8 rows of 1024 positions (d = 64, 5 tokens) 26.9 us then, 13.9 us now (12.5 with the
+// selection as it has become); 32 rows of 424 (d =
 // 128, 28 query rows) 67 and 22 us; 8 rows of 5039 (d = 64) 54 and 22 us; error against 64 bits 2.4e-7 .. 4.5e-7 then,
 // 1.7e-7 .. 2.7e-7 now.
 #include "common.h"

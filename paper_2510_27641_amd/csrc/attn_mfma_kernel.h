@@ -24,9 +24,9 @@
 // V has been consumed.  The list words of a tile (or the words of the kept mask) are fetched the same way,
 // by LDS-DMA into two small slots per wave, one iteration ahead of the gathers that need them: nothing a
 // tile needs is waited for when its turn comes, and no barrier separates the tiles of a share.
-//   S^T = K Q^T    : mfma 16x16x32 bf16, A = K fragment (ds_read_b128), B = Q fragment (Q tile in LDS)
-//   softmax        : running reference max per query row, rescaled only when exceeded by 2^8
-//   O^T += V^T P^T : A = V^T fragment (ds_read_b64_tr_b16), B = P split into bf16 hi + lo parts
+//   S^T = K Q^T    : mfma 16x16x32, A = K fragment (ds_read_b128), B = Q fragment (Q tile in LDS)
+//   softmax        : running reference max per query row, rescaled only when a tile leaves its range (Half)
+//   O^T += V^T P^T : A = V^T fragment (ds_read_b64_tr_b16), B = P split into parts of the element type (two, at d = 64 three)
 // Query rows come in tiles of 16, up to four per launch: a kept K/V row is fetched once for all of them.  (Groups of
 // more than 32 query rows used to take a launch per 32 and fetch everything again: 8 heads x 5 tokens, 64 rows x 4500
 // kept positions, 69 us of attention against 40 us.)  d = 64 keeps bytes per tile, requests in flight and the
@@ -282,13 +282,6 @@ __device__ __forceinline__ void lds_write_word(uint32_t addr, uint32_t v)
     asm volatile("ds_write_b32 %0, %1" ::"v"(addr), "v"(v) : "memory");
 }
 __device__ __forceinline__ void lds_wait() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
-// value of `v` in lane `src_lane` (a cross-lane read through the LDS crossbar; no memory is touched)
-__device__ __forceinline__ uint32_t lane_read(uint32_t v, int src_lane)
-{
-    uint32_t r;
-    asm volatile("ds_bpermute_b32 %0, %1, %2\n s_waitcnt lgkmcnt(0)" : "=&v"(r) : "v"(src_lane << 2), "v"(v) : "memory");
-    return r;
-}
 // One word from global memory, waited for on the spot.  Written out because a load the compiler tracks makes it wait
 // for everything in flight (the gathers included) wherever the loaded value may be used, taken or not.
 __device__ __forceinline__ uint32_t global_read_word(const uint32_t *p)
@@ -297,7 +290,8 @@ __device__ __forceinline__ uint32_t global_read_word(const uint32_t *p)
     asm volatile("global_load_dword %0, %1, off\n s_waitcnt vmcnt(0)" : "=&v"(r) : "v"(p) : "memory");
     return r;
 }
-// The same for two values at once (one round trip through the crossbar instead of two).
+// The values of `a` and `b` in lane `src_lane` (cross-lane reads through the LDS crossbar, one round trip for both; no
+// memory is touched).
 __device__ __forceinline__ void lane_read2(uint32_t a, uint32_t b, int src_lane, uint32_t &ra, uint32_t &rb)
 {
     asm volatile("ds_bpermute_b32 %0, %2, %3\n ds_bpermute_b32 %1, %2, %4\n s_waitcnt lgkmcnt(0)"

@@ -650,7 +650,7 @@ specattn_status launch_one(const SelectLaunch &a, hipStream_t stream)
 // histograms, then entries, about a microsecond each) and the locate steps (2 us each), not by the row's bytes.
 // With less workspace than that asks for (a histogram per slice), the slices of a row add theirs up in one histogram of
 // the row, by atomics in memory after a launch that clears it (integers: any order gives the same sums), and as many of the
-// boundary bin's entries are collected as there is room for: 32 rows of 131072 in an eighth of the workspace 24.4 us
+// boundary bin's entries are collected as there is room for: 32 heavy-tailed rows of 131072 in an eighth of the workspace 24.4 us
 // (24.1 with all of it, 71 without any), 8 of 65536 20.8 (19.2, 26.7).
 constexpr int MW_THREADS = 512;
 constexpr int MW_WAVES = MW_THREADS / 64;

@@ -6,9 +6,8 @@
 // while the row is still in its registers; then a pass over those bits alone (a thirty-second of the rows) in which every
 // workgroup combines the members' words of one segment of a row and numbers its kept positions.
 //
-// Rows whose thresholds come from elsewhere (the split selection of few long rows, the bisection), and unions with a
-// workspace that does not hold the members' bits, take a mask pass that compares the rows with their thresholds again and
-// a compaction pass over its ballots.
+// Rows whose thresholds come from elsewhere (the bisection), and unions with a workspace that does not hold the members'
+// bits, take a mask pass that compares the rows with their thresholds again and a compaction pass over its ballots.
 #include <hip/hip_runtime.h>
 
 #include "common.h"
