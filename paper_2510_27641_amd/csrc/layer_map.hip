@@ -28,7 +28,7 @@ constexpr int KL_ITER_K = KL_WAVES * KL_WAVE_K;
 constexpr int KL_TI = 32, KL_TJ = 32;                // draft and verifier layers per workgroup
 constexpr int KL_ROW = KL_WAVE_K + 2;                // doubles per staged row: rows start four banks apart
 constexpr int KL_WAVE_LDS = KL_TI * KL_ROW;          // doubles
-constexpr int LOG_FIRST = 90, LOG_ENTRIES = 92;      // table of logarithms: of 90/128 to 181/128
+constexpr int LOG_FIRST = 64, LOG_ENTRIES = 118;     // table of logarithms: of 64/128 to 181/128
 constexpr int KL_LDS_BYTES = (KL_WAVES * KL_WAVE_LDS + 2 * LOG_ENTRIES) * (int)sizeof(double);
 constexpr int MAP_THREADS = 1024;      // most draft layers the alignment kernel takes
 constexpr int MAP_LDS_BACK = 24576;    // back pointers kept in LDS (16 bits each); larger tables use the workspace
@@ -40,20 +40,17 @@ constexpr int MAP_LDS_BACK = 24576;    // back pointers kept in LDS (16 bits eac
 constexpr double LOG_OF_ZERO = -1e160, LOG_OF_INVALID = 1e290, DIVERGENCE_LIMIT = 1e100;
 
 // Natural logarithm in fp64 of a positive finite fp32 value from a table of logarithms (P. T. P. Tang, "Table-driven
-// implementation of the logarithm function in IEEE floating-point arithmetic", 1990).  x = 2^e y with y in
-// [sqrt(1/2), sqrt(2)), j the integer next to 128 y: log x = e log 2 + log(j / 128) + log1p((128 y - j) / j).  e, y, j and
-// the difference are exact in fp32, so the reduction runs there; the table holds 1/j and log(j / 128), the series has degree
-// 8 (|r| <= 2^-7.5: remainder below 2^-63 of it).  Next to 1, j is 128 and the result r's series alone.  Within 1.4
-// units in the last place over all of fp32; about 25 instructions, against more than 100 of the general fp64 logarithm.
-// Values that have no logarithm are taken as the nearest one that has.
+// implementation of the logarithm function in IEEE floating-point arithmetic", 1990).  x = 2^e y / 128 with y / 128 in
+// [sqrt(1/2), sqrt(2)) (the last subnormal values: from 1/2 on), j the integer next to y: log x = e log 2 + log(j / 128) +
+// log1p((y - j) / j).  e, y, j and the difference are exact in fp32, so the reduction runs there; the table holds 1/j and
+// log(j / 128), the series has degree 8 (|r| <= 2^-7.5: remainder below 2^-63 of it).  Next to 1, j is 128 and the result
+// r's series alone.  Within 1.4 units in the last place over all of fp32; about 25 instructions, against more than 100 of the
+// general fp64 logarithm.  Values that have no logarithm are taken as the nearest one that has.
 __device__ __forceinline__ double log_positive(float x, const f64x2 *tab)
 {
     x = __builtin_amdgcn_fmed3f(x, 1.4012985e-45f, 3.4028235e38f);
-    float y = __builtin_amdgcn_frexp_mantf(x);        // [1/2, 1), also of subnormal values
-    int e = __builtin_amdgcn_frexp_expf(x);
-    const bool low = y < 0.70710678f;
-    y *= low ? 256.0f : 128.0f;
-    e -= low ? 1 : 0;
+    const int e = __builtin_amdgcn_frexp_expf(x * 0.70710678f);
+    const float y = __builtin_amdgcn_ldexpf(x, 7 - e);
     const float j = rintf(y);
     const f64x2 t = tab[(int)j - LOG_FIRST];
     const double r = (double)(y - j) * t[0];
@@ -155,14 +152,19 @@ __global__ __launch_bounds__(KL_THREADS) void layer_kl_kernel(const float *__res
 #pragma unroll
             for (int a = 0; a < 2; ++a) {
                 if (j0 + 16 * a >= n) continue;       // (uniform)
+                // 0 * log(0 / q) = 0: entries that are not above 0 add nothing (nor do their logarithms).  Where a causal
+                // row has ended, whole waves have nothing to do.
+                const f32x4u v = p[a][s];
+                double lp[4] = {0.0, 0.0, 0.0, 0.0};
+                if (fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])) > 0.0f)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) lp[c] = log_positive(v[c], tab);
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
-                    // 0 * log(0 / q) = 0: entries that are not above 0 add nothing (nor do their logarithms)
-                    const double x = fmaxf(p[a][s][c], 0.0f);
-                    const double lp = log_positive(p[a][s][c], tab);
+                    const double x = fmaxf(v[c], 0.0f);
                     acc[a][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0[c >> 1][c & 1], x, acc[a][0], 0, 0, 0);
                     acc[a][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1[c >> 1][c & 1], x, acc[a][1], 0, 0, 0);
-                    acc[a][2] = __builtin_amdgcn_mfma_f64_16x16x4f64(lp, x, acc[a][2], 0, 0, 0);
+                    acc[a][2] = __builtin_amdgcn_mfma_f64_16x16x4f64(lp[c], x, acc[a][2], 0, 0, 0);
                 }
             }
         }
@@ -215,9 +217,14 @@ __global__ __launch_bounds__(512) void layer_kl_finish_kernel(const double *__re
     if (pair < pairs)
         for (int c = cl; c < chunks; c += 64) s += partial[(int64_t)c * pairs + pair];
     s = sum_of_threads(s);
-    const bool odd = pair < pairs && !(s > -DIVERGENCE_LIMIT && s < INFINITY);
+    auto is_odd = [&](double x) { return !(x > -DIVERGENCE_LIMIT && x < INFINITY); };
+    const bool odd = pair < pairs && is_odd(s);
     if (cl == 0 && pair < pairs && !odd) S[pair] = s > DIVERGENCE_LIMIT ? -INFINITY : -s / rows;
-    if (!__syncthreads_or(odd ? 1 : 0)) return;
+    bool any = false;                                 // (all eight sums: the same answer in every thread)
+#pragma unroll
+    for (int k = 0; k < 8; ++k) any |= is_odd(red[0][k]);
+    if (!any) return;
+    __syncthreads();                                  // everyone has read them
     s = 0.0;
     if (odd) {
         const int i = pair / n, j = pair - i * n;
