@@ -21,15 +21,13 @@ typedef double f64x2 __attribute__((ext_vector_type(2)));
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));   // layers start at any multiple of four bytes
 
-constexpr int KL_WAVES = 8;
-constexpr int KL_THREADS = KL_WAVES * 64;
+constexpr int KL_WAVES = 8, KL_FEW_WAVES = 4;        // per workgroup (kl_plan)
 constexpr int KL_WAVE_K = 64;                        // entries of a layer one wave takes per iteration
-constexpr int KL_ITER_K = KL_WAVES * KL_WAVE_K;
 constexpr int KL_TI = 32, KL_TJ = 32;                // draft and verifier layers per workgroup
 constexpr int KL_ROW = KL_WAVE_K + 2;                // doubles per staged row: rows start four banks apart
 constexpr int KL_WAVE_LDS = KL_TI * KL_ROW;          // doubles
 constexpr int LOG_FIRST = 64, LOG_ENTRIES = 118;     // table of logarithms: of 64/128 to 181/128
-constexpr int KL_LDS_BYTES = (KL_WAVES * KL_WAVE_LDS + 2 * LOG_ENTRIES) * (int)sizeof(double);
+constexpr int kl_lds_bytes(int waves) { return (waves * KL_WAVE_LDS + 2 * LOG_ENTRIES) * (int)sizeof(double); }
 constexpr int MAP_THREADS = 1024;      // most draft layers the alignment kernel takes
 constexpr int MAP_LDS_BACK = 24576;    // back pointers kept in LDS (16 bits each); larger tables use the workspace
 
@@ -70,12 +68,11 @@ __device__ __forceinline__ double log_draft(float q, const f64x2 *tab)
     return has_log(q) ? l : (q == 0.0f ? LOG_OF_ZERO : LOG_OF_INVALID);
 }
 
-// Entries k .. k+3 of a layer, zero at and beyond `end`.
-__device__ __forceinline__ f32x4u load4(const float *layer, int64_t k, int64_t end, bool live)
+// Entries k .. k+3 of a layer, zero at and beyond `end`; `whole`: none of the wave's lanes reaches that far.
+__device__ __forceinline__ f32x4u load4(const float *layer, int64_t k, int64_t end, bool whole)
 {
+    if (whole) return *reinterpret_cast<const f32x4u *>(layer + k);
     f32x4u v = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (!live) return v;
-    if (k + 3 < end) return *reinterpret_cast<const f32x4u *>(layer + k);
 #pragma unroll
     for (int c = 0; c < 4; ++c)
         if (k + c < end) v[c] = layer[k + c];
@@ -90,24 +87,45 @@ __device__ __forceinline__ void wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Workgroup (chunk, draft group, verifier group): partial sums of 32 x 32 layer pairs over `iters` runs of 512 entries.
+// Workgroup (chunk, draft group, verifier group): partial sums of 32 x 32 layer pairs over `iters` runs of 64 entries per wave.
 // Every wave works on 64 entries of its own and meets the others only at the end: it takes the logarithms of its
 // draft entries into its part of LDS ([layer][entry], fp64), then goes through its verifier entries, 16 layers x 16
 // entries at a time, straight from memory: lane l holds entries 4 * (l / 16) .. + 3 of layer l % 16, which is
 // a B operand of four matrix instructions; their logarithms are the A operand of a third product whose diagonal is
 // sum p log p - taken in the same order as the other sums, so that a layer compared with itself gives exactly zero.
 // Bound by the logarithms (25 instructions each, m + n of them per entry) behind one unhidden trip to memory: 22 x 32
-// layers, 64 rows x 2048 positions (28 MB, 92 M terms) in 21 us; two general logarithms per term, one workgroup per
+// layers, 64 rows x 2048 positions (28 MB, 92 M terms) in 19 us; two general logarithms per term, one workgroup per
 // layer pair and chunk, took 329 us.
-__global__ __launch_bounds__(KL_THREADS) void layer_kl_kernel(const float *__restrict__ ad, const float *__restrict__ av, int m,
-                                                              int n, int64_t per_layer, int iters, double *__restrict__ partial)
+__global__ __launch_bounds__(KL_WAVES * 64) void layer_kl_kernel(const float *__restrict__ ad, const float *__restrict__ av, int m,
+                                                                 int n, int64_t per_layer, int iters, double *__restrict__ partial)
 {
     extern __shared__ __align__(16) double kl_lds[];
-    f64x2 *tab = reinterpret_cast<f64x2 *>(kl_lds + KL_WAVES * KL_WAVE_LDS);
+    const int waves = blockDim.x >> 6;
+    f64x2 *tab = reinterpret_cast<f64x2 *>(kl_lds + waves * KL_WAVE_LDS);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l16 = lane & 15, g = lane >> 4;
     const int i0 = blockIdx.y * KL_TI, j0 = blockIdx.z * KL_TJ;
     double *lq = kl_lds + wave * KL_WAVE_LDS;
+    f32x4u q[8], p[2][4];
+    // (Layers past the last one repeat it: their sums are not read.)
+    auto request = [&](int64_t k0) {
+        if (k0 >= per_layer) return;                  // (uniform over the wave)
+        const bool whole = k0 + KL_WAVE_K <= per_layer;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const int i = i0 + 4 * t + g;
+            q[t] = load4(ad + (int64_t)(i < m ? i : m - 1) * per_layer, k0 + 4 * l16, per_layer, whole);
+        }
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const int j = j0 + 16 * a + l16;
+                p[a][s] = load4(av + (int64_t)(j < n ? j : n - 1) * per_layer, k0 + 16 * s + 4 * g, per_layer, whole);
+            }
+    };
+    const int64_t step = waves * KL_WAVE_K, first = (int64_t)blockIdx.x * iters * step + wave * KL_WAVE_K;
+    request(first);                                   // (on its way while the table is made)
     if (tid < LOG_ENTRIES) {
         const double j = (double)(LOG_FIRST + tid);
         tab[tid] = (f64x2){1.0 / j, log(j / 128.0)};
@@ -119,23 +137,12 @@ __global__ __launch_bounds__(KL_THREADS) void layer_kl_kernel(const float *__res
 #pragma unroll
         for (int t = 0; t < 3; ++t) acc[a][t] = (f64x4){0.0, 0.0, 0.0, 0.0};
     for (int it = 0; it < iters; ++it) {
-        const int64_t k0 = ((int64_t)blockIdx.x * iters + it) * KL_ITER_K + wave * KL_WAVE_K;
+        const int64_t k0 = first + it * step;
         if (k0 >= per_layer) break;                   // (uniform over the wave)
-        f32x4u q[8], p[2][4];
+        if (it) request(k0);
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
-            const int i = i0 + 4 * t + g;
-            q[t] = load4(ad + (int64_t)i * per_layer, k0 + 4 * l16, per_layer, i < m);
-        }
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const int j = j0 + 16 * a + l16;
-                p[a][s] = load4(av + (int64_t)j * per_layer, k0 + 16 * s + 4 * g, per_layer, j < n);
-            }
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
+            if (i0 + 4 * t >= m) break;               // (uniform)
             f64x2 *dst = reinterpret_cast<f64x2 *>(lq + (4 * t + g) * KL_ROW + 4 * l16);
             dst[0] = (f64x2){log_draft(q[t][0], tab), log_draft(q[t][1], tab)};
             dst[1] = (f64x2){log_draft(q[t][2], tab), log_draft(q[t][3], tab)};
@@ -163,7 +170,7 @@ __global__ __launch_bounds__(KL_THREADS) void layer_kl_kernel(const float *__res
                 for (int c = 0; c < 4; ++c) {
                     const double x = fmaxf(v[c], 0.0f);
                     acc[a][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0[c >> 1][c & 1], x, acc[a][0], 0, 0, 0);
-                    acc[a][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1[c >> 1][c & 1], x, acc[a][1], 0, 0, 0);
+                    if (i0 + 16 < m) acc[a][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1[c >> 1][c & 1], x, acc[a][1], 0, 0, 0);
                     acc[a][2] = __builtin_amdgcn_mfma_f64_16x16x4f64(lp[c], x, acc[a][2], 0, 0, 0);
                 }
             }
@@ -179,13 +186,12 @@ __global__ __launch_bounds__(KL_THREADS) void layer_kl_kernel(const float *__res
 #pragma unroll
             for (int v = 0; v < 4; ++v) lq[((a * 3 + t) * 16 + 4 * v + g) * 16 + l16] = acc[a][t][v];
     __syncthreads();
-    for (int e = tid; e < KL_TI * KL_TJ; e += KL_THREADS) {
+    for (int e = tid; e < KL_TI * KL_TJ; e += (int)blockDim.x) {
         const int i = e >> 5, j = e & 31;
         if (i0 + i >= m || j0 + j >= n) continue;
         const int a = j >> 4, jj = j & 15;
         double own = 0.0, cross = 0.0;
-#pragma unroll
-        for (int w = 0; w < KL_WAVES; ++w) {
+        for (int w = 0; w < waves; ++w) {
             const double *src = kl_lds + w * KL_WAVE_LDS;
             own += src[((a * 3 + 2) * 16 + jj) * 16 + jj];
             cross += src[((a * 3 + (i >> 4)) * 16 + (i & 15)) * 16 + jj];
@@ -200,31 +206,28 @@ __global__ __launch_bounds__(512) void layer_kl_finish_kernel(const double *__re
                                                               const float *__restrict__ ad, const float *__restrict__ av, int64_t per_layer,
                                                               double *__restrict__ S)
 {
-    __shared__ double red[64][8];
-    const int pp = threadIdx.x & 7, cl = threadIdx.x >> 3;
+    __shared__ double red[2][8][8];
+    const int pp = threadIdx.x & 7, cl = threadIdx.x >> 3, wave = threadIdx.x >> 6;
     const int pairs = m * n, pair = blockIdx.x * 8 + pp;
-    auto sum_of_threads = [&](double s) -> double {
-        red[cl][pp] = s;
-        __syncthreads();
+    // sums over the threads of a pair: of its eight lanes of a wave, then of the waves
+    auto sum_of_threads = [&](double s, double (&part)[8][8]) -> double {
 #pragma unroll
-        for (int half = 32; half >= 1; half >>= 1) {
-            if (cl < half) red[cl][pp] += red[cl + half][pp];
-            __syncthreads();
-        }
-        return red[0][pp];
+        for (int off = 8; off < 64; off <<= 1) s += __shfl_xor(s, off, 64);
+        if ((threadIdx.x & 63) < 8) part[wave][pp] = s;
+        __syncthreads();
+        s = 0.0;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) s += part[w][pp];
+        return s;
     };
     double s = 0.0;
     if (pair < pairs)
         for (int c = cl; c < chunks; c += 64) s += partial[(int64_t)c * pairs + pair];
-    s = sum_of_threads(s);
+    s = sum_of_threads(s, red[0]);
     auto is_odd = [&](double x) { return !(x > -DIVERGENCE_LIMIT && x < INFINITY); };
     const bool odd = pair < pairs && is_odd(s);
     if (cl == 0 && pair < pairs && !odd) S[pair] = s > DIVERGENCE_LIMIT ? -INFINITY : -s / rows;
-    bool any = false;                                 // (all eight sums: the same answer in every thread)
-#pragma unroll
-    for (int k = 0; k < 8; ++k) any |= is_odd(red[0][k]);
-    if (!any) return;
-    __syncthreads();                                  // everyone has read them
+    if (!__any(odd)) return;                          // (every wave holds all eight sums)
     s = 0.0;
     if (odd) {
         const int i = pair / n, j = pair - i * n;
@@ -234,7 +237,7 @@ __global__ __launch_bounds__(512) void layer_kl_finish_kernel(const double *__re
             if (p > 0.0) s += p * (log(p) - log((double)pd[k]));
         }
     }
-    s = sum_of_threads(s);
+    s = sum_of_threads(s, red[1]);
     if (cl == 0 && odd) S[pair] = -s / rows;
 }
 
@@ -328,16 +331,20 @@ __global__ __launch_bounds__(MAP_THREADS) void layer_map_kernel(const double *__
     }
 }
 
-// Runs of 512 entries per workgroup, and workgroups along the entries: one workgroup per CU (its LDS allows no second) as
-// soon as there are that many runs.
-struct KlPlan { int iters, chunks, gi, gj; };
+// Runs of 512 or 256 entries per workgroup, and workgroups along the entries: one per CU as soon as there are that many
+// runs (the LDS of eight waves allows no second).
+// Few runs go out half as long: a SIMD then has one wave's logarithms and products to do instead of two.  (2 x 3 layers
+// of 400 entries 10.0 us instead of 11.9, 8 x 12 of 512 9.6 and 10.9, 4 x 40 of 8192 10.9 and 14.4.)
+struct KlPlan { int waves, iters, chunks, gi, gj; };
 KlPlan kl_plan(int m, int n, int64_t per_layer, int64_t most_chunks)
 {
     KlPlan p;
     p.gi = (m + KL_TI - 1) / KL_TI;
     p.gj = (n + KL_TJ - 1) / KL_TJ;
-    const int64_t runs = (per_layer + KL_ITER_K - 1) / KL_ITER_K;
-    int64_t want = cu_count() / ((int64_t)p.gi * p.gj);
+    int64_t run = KL_WAVES * KL_WAVE_K, want = cu_count() / ((int64_t)p.gi * p.gj);
+    p.waves = KL_WAVES;
+    if (2 * ((per_layer + run - 1) / run) <= want) { p.waves = KL_FEW_WAVES; run = KL_FEW_WAVES * KL_WAVE_K; }
+    const int64_t runs = (per_layer + run - 1) / run;
     want = want > most_chunks ? most_chunks : want;
     want = want < 1 ? 1 : want;
     p.iters = (int)((runs + want - 1) / want);
@@ -375,9 +382,9 @@ specattn_status layer_map_configure()
     }
     std::lock_guard<std::mutex> lock(mu);
     if (done[dev]) return SPECATTN_OK;
-    if (hipFuncSetAttribute(reinterpret_cast<const void *>(&layer_kl_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, KL_LDS_BYTES) != hipSuccess) {
+    if (hipFuncSetAttribute(reinterpret_cast<const void *>(&layer_kl_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kl_lds_bytes(KL_WAVES)) != hipSuccess) {
         (void)hipGetLastError();
-        set_error("cannot reserve %d bytes of LDS", KL_LDS_BYTES);
+        set_error("cannot reserve %d bytes of LDS", kl_lds_bytes(KL_WAVES));
         return SPECATTN_EHIP;
     }
     done[dev] = true;
@@ -418,7 +425,7 @@ specattn_status specattn_layer_similarity(const float *attn_draft, const float *
     if (st != SPECATTN_OK) return st;
     hipStream_t hs = static_cast<hipStream_t>(stream);
     double *partial = static_cast<double *>(workspace);
-    hipLaunchKernelGGL(layer_kl_kernel, dim3(plan.chunks, plan.gi, plan.gj), dim3(KL_THREADS), KL_LDS_BYTES, hs, attn_draft, attn_verifier,
+    hipLaunchKernelGGL(layer_kl_kernel, dim3(plan.chunks, plan.gi, plan.gj), dim3(plan.waves * 64), kl_lds_bytes(plan.waves), hs, attn_draft, attn_verifier,
                        m, n, per_layer, plan.iters, partial);
     st = check_launch("layer_kl_kernel");
     if (st != SPECATTN_OK) return st;
