@@ -45,6 +45,7 @@ struct SelectLaunch {
     int chunk_shift;         // log2 of the chunk size when the row holds chunk masses, else 0
     uint32_t *kept_mask;     // may be null; [rows][blocks_per_row * SEL_BLOCK / 32]: bit i of word w = position 32 w + i kept
 };
+constexpr int SELECT_RESIDENT = 65536;    // rows up to this length are read once (one workgroup holds them in registers)
 specattn_status launch_select(const SelectLaunch &a, hipStream_t stream);
 // Few long rows: each row split over many workgroups, lists written.  `scratch` holds select_multi_wg_bytes(rows, n_max), or
 // less, down to 20 KiB per row, at some cost in time.

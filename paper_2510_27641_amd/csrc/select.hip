@@ -1250,7 +1250,7 @@ specattn_status launch_select(const SelectLaunch &a, hipStream_t stream)
         return rows <= 2 * cus || n > 15360 ? launch_one<512, 8, true>(a, stream) : launch_one<256, 16, true>(a, stream);
     }
     if (n <= 32768) return rows > cus ? launch_one<512, 16, true>(a, stream) : launch_one<1024, 8, true>(a, stream);
-    if (n <= 65536) return launch_one<1024, 16, true>(a, stream);
+    if (n <= SELECT_RESIDENT) return launch_one<1024, 16, true>(a, stream);
     return launch_one<1024, 1, false>(a, stream);
 }
 

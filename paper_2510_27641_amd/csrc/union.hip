@@ -6,8 +6,9 @@
 // while the row is still in its registers; then a pass over those bits alone (a thirty-second of the rows) in which every
 // workgroup combines the members' words of one segment of a row and numbers its kept positions.
 //
-// Rows whose thresholds come from elsewhere (the bisection), and unions with a workspace that does not hold the members'
-// bits, take a mask pass that compares the rows with their thresholds again and a compaction pass over its ballots.
+// Rows whose thresholds come from elsewhere (the bisection), rows that the selection does not hold in registers, and unions
+// with a workspace that does not hold the members' bits, take a mask pass that compares the rows with their thresholds again
+// and a compaction pass over its ballots.
 #include <hip/hip_runtime.h>
 
 #include "common.h"
@@ -45,7 +46,7 @@ struct UnionLaunch {
 
 // one workgroup per (row, block): kept bits of positions [blk * U_BLOCK, (blk + 1) * U_BLOCK) of row r.
 // Position of (iter, thread, component): blk * U_BLOCK + iter * U_THREADS * 4 + thread * 4 + component.
-__global__ __launch_bounds__(U_THREADS) void union_mask_kernel(UnionLaunch a)
+template <int U_MEMBERS> __global__ __launch_bounds__(U_THREADS) void union_mask_kernel(UnionLaunch a)
 {
     __shared__ int wave_cnt[U_WAVES];
     const int r = blockIdx.x / a.blocks, blk = blockIdx.x - r * a.blocks;
@@ -56,27 +57,59 @@ __global__ __launch_bounds__(U_THREADS) void union_mask_kernel(UnionLaunch a)
     const float *rows = a.probs + (int64_t)b * a.stride_b + (int64_t)h * a.M * a.stride_m;
     const int64_t m0 = (int64_t)r * a.M;
     unsigned keep[U_ITERS] = {0u, 0u, 0u, 0u};                // 4 bits per iteration
-    for (int m = 0; m < a.M; ++m) {
-        if (a.mcounts[m0 + m] <= 0) continue;                 // invalid member rows keep nothing (uniform)
-        const int t = __float_as_int(a.tau[m0 + m]);         // > 0 for every valid row: zeros are never kept
-        const float *row = rows + (int64_t)m * a.stride_m;
+    // compared as integers, like the selection itself: non-negative floats order like their bit
+    // patterns; -0.0 (the only signed value a valid row can hold) counts as zero
+    auto bits = [](float f) { const int i = __float_as_int(f); return i == (int)0x80000000 ? 0 : i; };
+    auto compare = [&](int it, const f32x4a &v, int t) {
+        const int x = bits(v.x), y = bits(v.y), z = bits(v.z), w = bits(v.w);
+        keep[it] |= (x >= t ? 1u : 0u) | (y >= t ? 2u : 0u) | (z >= t ? 4u : 0u) | (w >= t ? 8u : 0u);
+    };
+    const bool whole = (blk + 1) * U_BLOCK <= len;             // uniform
+    for (int mc = 0; mc < a.M; mc += 64) {
+        const int ms = a.M - mc < 64 ? a.M - mc : 64;
+        // lane m: the threshold of member mc + m, negative where it keeps nothing.  (Exact thresholds are above 0; a
+        // bisection's may be 0 and keeps zeros, too.)
+        const int64_t at = m0 + mc + (lane < ms ? lane : 0);
+        const int tau = a.mcounts[at] > 0 ? __float_as_int(a.tau[at]) : -1;
+        const float *first = rows + (int64_t)mc * a.stride_m;
+        int m = 0;
+        if (whole) {
+            // four members at a time: their thresholds are here and all of their loads in flight together (one after the
+            // other, with a trip for each threshold, 8 rows of 66000 with 24 members each A)
+            for (; m + U_MEMBERS <= ms; m += U_MEMBERS) {
+                f32x4a v[U_MEMBERS][U_ITERS];
 #pragma unroll
-        for (int it = 0; it < U_ITERS; ++it) {
-            const int p = blk * U_BLOCK + it * U_THREADS * 4 + tid * 4;
-            f32x4a v = {-1.f, -1.f, -1.f, -1.f};              // positions past the row's end: below any threshold
-            if (p + 3 < len) {
-                v = *reinterpret_cast<const f32x4a *>(row + p);
-            } else {
-                if (p < len) v.x = row[p];
-                if (p + 1 < len) v.y = row[p + 1];
-                if (p + 2 < len) v.z = row[p + 2];
-                if (p + 3 < len) v.w = row[p + 3];
+                for (int k = 0; k < U_MEMBERS; ++k)
+#pragma unroll
+                    for (int it = 0; it < U_ITERS; ++it)
+                        v[k][it] = *reinterpret_cast<const f32x4a *>(first + (m + k) * a.stride_m + blk * U_BLOCK + it * U_THREADS * 4 + tid * 4);
+#pragma unroll
+                for (int k = 0; k < U_MEMBERS; ++k) {
+                    const int t = __builtin_amdgcn_readlane(tau, m + k);
+                    if (t < 0) continue;                      // (uniform) an invalid row's entries may compare anyhow
+#pragma unroll
+                    for (int it = 0; it < U_ITERS; ++it) compare(it, v[k][it], t);
+                }
             }
-            // compared as integers, like the selection itself: non-negative floats order like their bit
-            // patterns; -0.0 (the only signed value a valid row can hold) counts as zero
-            auto bits = [](float f) { const int i = __float_as_int(f); return i == (int)0x80000000 ? 0 : i; };
-            const int x = bits(v.x), y = bits(v.y), z = bits(v.z), w = bits(v.w);
-            keep[it] |= (x >= t ? 1u : 0u) | (y >= t ? 2u : 0u) | (z >= t ? 4u : 0u) | (w >= t ? 8u : 0u);
+        }
+        for (; m < ms; ++m) {
+            const int t = __builtin_amdgcn_readlane(tau, m);
+            if (t < 0) continue;
+            const float *row = first + m * a.stride_m;
+#pragma unroll
+            for (int it = 0; it < U_ITERS; ++it) {
+                const int p = blk * U_BLOCK + it * U_THREADS * 4 + tid * 4;
+                f32x4a v = {-1.f, -1.f, -1.f, -1.f};          // positions past the row's end: below any threshold
+                if (p + 3 < len) {
+                    v = *reinterpret_cast<const f32x4a *>(row + p);
+                } else {
+                    if (p < len) v.x = row[p];
+                    if (p + 1 < len) v.y = row[p + 1];
+                    if (p + 2 < len) v.z = row[p + 2];
+                    if (p + 3 < len) v.w = row[p + 3];
+                }
+                compare(it, v, t);
+            }
         }
     }
     unsigned long long *words = a.ballots + ((int64_t)r * a.blocks + blk) * U_WORDS;
@@ -304,14 +337,18 @@ specattn_status launch_threshold_union(const float *probs, int64_t stride_b, int
         return check_launch("union_words_kernel");
     }
     const dim3 grid((unsigned)(blocks * rows));
-    hipLaunchKernelGGL(union_mask_kernel, grid, dim3(U_THREADS), 0, stream, a);
+    if (M >= 8) hipLaunchKernelGGL(union_mask_kernel<4>, grid, dim3(U_THREADS), 0, stream, a);
+    else if (M >= 2) hipLaunchKernelGGL(union_mask_kernel<2>, grid, dim3(U_THREADS), 0, stream, a);
+    else hipLaunchKernelGGL(union_mask_kernel<1>, grid, dim3(U_THREADS), 0, stream, a);
     specattn_status st = check_launch("union_mask_kernel");
     if (st != SPECATTN_OK) return st;
     hipLaunchKernelGGL(union_compact_kernel, grid, dim3(U_THREADS), 0, stream, a);
     return check_launch("union_compact_kernel");
 }
 
-// Kept bits of all member rows, behind union_workspace_bytes.
+// Kept bits of all member rows, behind union_workspace_bytes.  Only of rows that stay in the selection's registers: a longer
+// row's bits take the selection a fourth pass over it, with one workgroup, where the mask pass reads it with the whole chip
+// (us, with bits / without: B).
 size_t union_masks_bytes(int B, int H_kv, int M, int n_max)
 {
     return align256((size_t)B * H_kv * M * ((n_max + SEL_BLOCK - 1) / SEL_BLOCK) * (SEL_BLOCK / 32) * sizeof(uint32_t));
@@ -324,8 +361,8 @@ specattn_status launch_union(const specattn_union_args *u, void *workspace, size
     const size_t members = (size_t)u->B * u->H_kv * M;
     char *ws = static_cast<char *>(workspace);
     const size_t before_masks = union_workspace_bytes(u->B, u->H_kv, M, u->n_max);
-    uint32_t *masks = workspace_bytes >= before_masks + union_masks_bytes(u->B, u->H_kv, M, u->n_max)
-                          ? reinterpret_cast<uint32_t *>(ws + before_masks) : nullptr;
+    const bool room = workspace_bytes >= before_masks + union_masks_bytes(u->B, u->H_kv, M, u->n_max);
+    uint32_t *masks = u->n_max <= SELECT_RESIDENT && room ? reinterpret_cast<uint32_t *>(ws + before_masks) : nullptr;
     float *tau = u->member_thresholds ? u->member_thresholds : reinterpret_cast<float *>(ws);
     ws += align256(members * 4);
     int32_t *mcounts = u->member_counts ? u->member_counts : reinterpret_cast<int32_t *>(ws);

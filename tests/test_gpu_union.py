@@ -152,3 +152,19 @@ def test_both_routes_give_the_same_lists(n, S, H_d, capacity):
         assert (got[0][1] > 0).all()
         with pytest.raises(RuntimeError, match="needed"):
             sa.specattn_topp_select_union(a, ws[:ws.numel() - 256])
+
+
+@pytest.mark.parametrize("S,H_d", [(1, 2), (3, 4), (9, 2), (33, 4)])
+def test_members_of_long_rows(S, H_d):
+    """Rows longer than the selection holds: the mask pass takes members one, two and four at a time, 64 thresholds ahead (1, 6, 9
+    and 66 members of a row).  Invalid members, whose entries may compare as anything, add nothing."""
+    n, lens = 66011, np.array([66011, 65536], dtype=np.int32)
+    probs = W.draft_step_probs(np.random.default_rng(S), 2, H_d, S, n, lens=lens)
+    if S * H_d > 2:
+        probs[0, 0, S // 2].view(np.uint32)[7] = 0x7FFFFFFF                  # the NaN above all others
+        probs[1, H_d - 1, 0, 65000] = -1.0
+        probs[0, H_d - 1, S - 1] = 0.0
+        probs[1, 0, S - 1, 9:99] = -0.0
+    got = gpu_union(probs, 0.9, 2, seq_lens=lens, capacity=n)
+    ref = oracle.topp_select_union(probs, 0.9, 2, lens=lens)
+    assert compare(got, ref)[1] == 0
