@@ -1,6 +1,6 @@
 // Sparse decode attention over a selected index list (Section 3.1.2, Eq. 2-3; Section 3.5): the variant that
 // computes both contractions in fp32, for every element type - fp32 inputs, and what the 16-bit matrix-core kernel
-// does not take (more than 512 kv heads; at d = 64 workspaces too small for its partials and strides beyond its offsets).
+// does not take (more than 512 kv heads; at d = 64 short lists, workspaces too small for its partials and strides beyond its offsets).
 //
 // Work split: one workgroup of eight waves per (row, split); a split is a contiguous run of the row's kept positions
 // and tile k of 16 positions goes to wave k mod 8.  Each wave keeps the running softmax state (max m, sum l,
@@ -453,9 +453,14 @@ size_t attn_workspace_accepted_bytes(int rows, int G, int T, int d, int idx_capa
 }
 
 // d = 64 on the 16-bit kernel: its partials have to fit the workspace (a call is accepted with one that holds this file's
-// partials only), and the row offsets 32 bits: in pools in units of 128 bytes, contiguous rows in units of 16.
+// partials only), and the row offsets 32 bits: in pools in units of 128 bytes, contiguous rows in units of 16.  Lists of at most
+// 128 positions are finished here, by one workgroup per row in one launch (us, 16-bit kernel / here, without and with new tokens:
+// 8 rows of 128 with 20 query rows 10.6 / 8.2 and 14.8 / 9.9, 1024 rows of 20 with 4 20.4 / 8.6 and 25.0 / 10.3, of 128 22.0 / 15.4
+// and 26.9 / 16.9; 64 rows with 64 query rows, of 128 13.6 / 13.0 and 21.3 / 17.5, but of 256 13.8 / 18.3 without new tokens).
+constexpr int SHORT_64 = 128;
 static bool attn_mfma_takes_64(const AttnLaunch &a)
 {
+    if (((int64_t)a.idx_capacity << a.chunk_shift) <= SHORT_64) return false;
     if (a.workspace_bytes < attn_mfma_workspace_min_bytes(a.B * a.H_kv, a.H_q / a.H_kv, a.T, a.d)) return false;
     if (a.page_table || a.indices_are_physical) return a.kv_stride_n % 64 == 0 && a.kv_stride_page % 64 == 0;
     return a.kv_stride_n <= ((int64_t)1 << 35) / a.n_max;

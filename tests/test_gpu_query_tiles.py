@@ -68,6 +68,35 @@ def test_counts_around_the_tiles_of_64_wide_heads(count, G):
         assert (out == 0).all() and np.isneginf(lse).all()
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("G,T", [(1, 1), (4, 5), (8, 8)])
+@pytest.mark.parametrize("capacity", [1, 17, 128, 129])
+def test_short_lists_of_64_wide_heads(capacity, G, T, dtype):
+    """On both sides of the line from which on such lists leave the kernel that finishes a row in one launch."""
+    w = W.llama8b_layer(seed=capacity, B=2, n=700, H_q=3 * G, H_kv=3, T=T, d=64, dtype=dtype)
+    rng = np.random.default_rng(capacity)
+    mask = np.zeros((2, 3, w.n), dtype=np.uint8)
+    for r, count in enumerate((0, 1, capacity, max(1, capacity // 2), capacity, capacity - 1)):
+        mask[r // 3, r % 3, rng.choice(w.n, size=count, replace=False)] = 1
+    k_new, v_new = (rng.standard_normal((2, 3, T, 64), dtype=np.float32) for _ in range(2))
+    dt = {"bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    bits = W.round_to_bf16_bits if dtype == "bf16" else lambda a: a.astype(np.float16).view(np.uint16)
+    q, k, v = kv_tensors(w)
+    idx, cnt = lists(mask)
+    for new in ({}, dict(k_new=dev(k_new, dt), v_new=dev(v_new, dt))):
+        out, lse = torch.full(q.shape, float("nan"), device="cuda"), torch.full(q.shape[:3], float("nan"), device="cuda")
+        att = sa.attn_args(q, k, v, out=out, lse=lse, indices=idx[:, :capacity].contiguous(), counts=cnt, **new)
+        ws = sa.alloc_workspace(sa.specattn_workspace_size(None, att))
+        att.workspace, att.workspace_bytes = ws.data_ptr(), ws.numel()
+        sa.specattn_sparse_decode_attn(att)
+        torch.cuda.synchronize()
+        ref, ref_lse = oracle.masked_attention(*(bits(a).reshape(a.shape) for a in (w.q, w.k, w.v)), mask, bf16=dtype == "bf16", f16=dtype == "f16",
+                                               **(dict(k_new=bits(k_new).reshape(k_new.shape), v_new=bits(v_new).reshape(v_new.shape)) if new else {}))
+        assert row_rel_err(out.cpu().numpy(), ref) <= TOL["f32"]
+        fin, got = np.isfinite(ref_lse), lse.cpu().numpy()
+        assert np.array_equal(np.isneginf(got), ~fin) and np.abs(got[fin] - ref_lse[fin]).max() <= 1e-3
+
+
 @pytest.mark.parametrize("mode", ["table", "physical"])
 @pytest.mark.parametrize("d,H_q", [(64, 16), (64, 24), (128, 24), (128, 32)])
 def test_paged_layouts(mode, d, H_q):
