@@ -3,6 +3,7 @@
 #include "attn_mfma_kernel.h"
 
 #include <mutex>
+#include <type_traits>
 
 namespace specattn {
 namespace {
@@ -11,7 +12,12 @@ namespace {
 // their partials (r, w) combined; rows without any kept position get out = 0, lse = -inf.  When the
 // caller gave the new tokens behind the cache, every row goes through here (the main kernel then
 // leaves partials only) and query t also attends to new tokens 0..t.
-__global__ void merge_partials_kernel(AttnLaunch a, Plan plan, int qtp)
+// Bound by latency: the cost prefix, then a trip to memory and a chain of sums per eight partials.  The head dimension is a
+// constant and every load of a trip is requested before the first partial is used; a short rest asks for two or five, since
+// eight are a chain too long there.  With the dimension read at run time / now, us for main kernel and merge: 8 rows of 8000 kept
+// positions (32 partials each) 14.7 / 13.7, of 500 10.3 / 9.7, of 20 8.1 / 8.1; 64 rows of 7500 (up to five) 49.4 / 49.2, and 49.8
+// with eight at a time throughout.
+template <int D> __global__ void merge_partials_kernel(AttnLaunch a, Plan plan, int qtp)
 {
     __shared__ float red[2 * SPECATTN_MAX_T];
     const int G = attn_group_heads(a);
@@ -21,7 +27,7 @@ __global__ void merge_partials_kernel(AttnLaunch a, Plan plan, int qtp)
     const int b = r / a.H_kv, h = r - b * a.H_kv;
     const int gh = q / a.T, t = q - gh * a.T;
     const int64_t orow = ((int64_t)b * a.H_q + attn_query_head(a, h, gh)) * a.T + t;
-    const int dv = threadIdx.x, D = a.d;
+    const int dv = threadIdx.x;
     const bool tail = a.k_new != nullptr;
     const int total = plan.cost_prefix[rows];
     const int p0 = plan.cost_prefix[r], p1 = plan.cost_prefix[r + 1];
@@ -35,19 +41,32 @@ __global__ void merge_partials_kernel(AttnLaunch a, Plan plan, int qtp)
     if (p0 != p1) {
         const int w0 = share_of(total, plan.n_wg, p0 + SEG_COST), w1 = share_of(total, plan.n_wg, p1 - 1);
         if (w0 == w1 && !tail) return;              // finished by its only workgroup
-        for (int wb = w0; wb <= w1; wb += 8) {      // eight partials per round trip
-            float mw[8], lw[8], ow[8];
+        auto trip = [&](int wb, auto most) {        // partials wb .. w1, at most N
+            constexpr int N = decltype(most)::value;
+            float mw[N], lw[N], ow[N];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const int64_t s = (int64_t)(wb + k + r) * qtp + q;
-                const bool ok = wb + k <= w1;
-                mw[k] = ok ? plan.part_ml[s * 2] : -INFINITY;
-                lw[k] = ok ? plan.part_ml[s * 2 + 1] : 0.0f;
-                ow[k] = ok ? plan.part_o[s * D + dv] : 0.0f;
+            for (int k = 0; k < N; ++k) {           // (behind the last share: that one's again)
+                const uint32_t s = (uint32_t)((min(wb + k, w1) + r) * qtp + q);
+                const float2 ml = reinterpret_cast<const float2 *>(plan.part_ml)[s];
+                mw[k] = ml.x;
+                lw[k] = ml.y;
+                ow[k] = plan.part_o[s * D + dv];
+            }
+            __builtin_amdgcn_sched_barrier(0);      // all requested before the first is used
+#pragma unroll
+            for (int k = 0; k < N; ++k) {           // (a weight of zero must not meet an infinite value)
+                mw[k] = wb + k <= w1 ? mw[k] : -INFINITY;
+                ow[k] = wb + k <= w1 ? ow[k] : 0.0f;
             }
 #pragma unroll
-            for (int k = 0; k < 8; ++k) acc.add(mw[k], lw[k], ow[k]);
-        }
+            for (int k = 0; k < N; ++k) acc.add(mw[k], lw[k], ow[k]);
+        };
+        int wb = w0;
+        for (; wb + 7 <= w1; wb += 8) trip(wb, std::integral_constant<int, 8>{});
+        const int left = w1 - wb + 1;
+        if (left > 5) trip(wb, std::integral_constant<int, 8>{});
+        else if (left > 2) trip(wb, std::integral_constant<int, 5>{});
+        else if (left > 0) trip(wb, std::integral_constant<int, 2>{});
     }
     if (tail) {
         float dots[SPECATTN_MAX_T];
@@ -181,7 +200,8 @@ static specattn_status launch_chunk(const AttnLaunch &a, hipStream_t stream)
     }
     st = check_launch("attn_mfma_kernel");
     if (st != SPECATTN_OK) return st;
-    hipLaunchKernelGGL(merge_partials_kernel, dim3(rows * QT), dim3(a.d), 0, stream, a, plan, qtp);
+    const auto merge = a.d == 64 ? merge_partials_kernel<64> : merge_partials_kernel<128>;
+    hipLaunchKernelGGL(merge, dim3(rows * QT), dim3(a.d), 0, stream, a, plan, qtp);
     return check_launch("merge_partials_kernel");
 }
 
