@@ -165,7 +165,9 @@ typedef struct specattn_attn_args {
 
     float *out;                  /* [B][H_q][T][d] fp32, contiguous */
     float *lse;                  /* [B][H_q][T] log-sum-exp of the kept scaled scores; optional */
-    void *workspace;             /* split partials; 256-byte aligned */
+    void *workspace;             /* split partials; 256-byte aligned.  With bf16 / fp16 and d = 64 it also decides the
+                                    kernel: one that is accepted but too small for the matrix-core kernel's partials
+                                    runs the call on the slower fp32 kernel (results agree to fp32 rounding) */
     size_t workspace_bytes;
 
     /* optional: keys and values of the T tokens being verified (Algorithm 1 feeds the gamma draft
