@@ -118,7 +118,7 @@ __global__ __launch_bounds__(GEN_THREADS, 1) void attn_f32_kernel(AttnLaunch a, 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, g = lane >> 4;
     const float scale2 = a.sm_scale * 1.4426950408889634f;            // scores in log2 units
-    const int count = attn_row_count(a, r);
+    const int count = attn_row_count(a, r, b);
     const int tiles = (count + GEN_TILE - 1) / GEN_TILE;
     const int per = (tiles + n_splits - 1) / n_splits;
     const int t_end = (s + 1) * per < tiles ? (s + 1) * per : tiles;

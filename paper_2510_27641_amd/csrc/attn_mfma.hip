@@ -8,38 +8,54 @@
 namespace specattn {
 namespace {
 
-// After the main kernel, one workgroup per (row, query row): rows shared by several workgroups get
+// Sum of v over the wave, in every lane.
+__device__ __forceinline__ float wave_sum(float v)
+{
+#define SPECATTN_SUM_STEP(CTRL, RM) v += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), CTRL, RM, 0xf, false))
+    SPECATTN_SUM_STEP(0x111, 0xf);    // row_shr:1
+    SPECATTN_SUM_STEP(0x112, 0xf);    // row_shr:2
+    SPECATTN_SUM_STEP(0x114, 0xf);    // row_shr:4
+    SPECATTN_SUM_STEP(0x118, 0xf);    // row_shr:8
+    SPECATTN_SUM_STEP(0x142, 0xa);    // row_bcast:15 into rows 1 and 3
+    SPECATTN_SUM_STEP(0x143, 0xc);    // row_bcast:31 into rows 2 and 3
+#undef SPECATTN_SUM_STEP
+    return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), 63));
+}
+
+// After the main kernel, one workgroup per (query row, row): rows shared by several workgroups get
 // their partials (r, w) combined; rows without any kept position get out = 0, lse = -inf.  When the
 // caller gave the new tokens behind the cache, every row goes through here (the main kernel then
 // leaves partials only) and query t also attends to new tokens 0..t.
-// Bound by latency: the cost prefix, then a trip to memory and a chain of sums per eight partials.  The head dimension is a
-// constant and every load of a trip is requested before the first partial is used; a short rest asks for two or five, since
-// eight are a chain too long there.  With the dimension read at run time / now, us for main kernel and merge: 8 rows of 8000 kept
-// positions (32 partials each) 14.7 / 13.7, of 500 10.3 / 9.7, of 20 8.1 / 8.1; 64 rows of 7500 (up to five) 49.4 / 49.2, and 49.8
-// with eight at a time throughout.
-template <int D> __global__ void merge_partials_kernel(AttnLaunch a, Plan plan, int qtp)
+// Bound by latency: the row's shares, then a trip to memory and a chain of sums per eight partials.  The head dimension is a
+// constant, the grid and the plan leave no division, and every load of a trip is requested before the first partial is used; a short
+// rest asks for two or five, since eight are a chain too long there.  What the new tokens need is requested ahead of the shares.
+// A pass of selection, attention and merge with every divisor and share worked out here from the cost line / with them handed over, us:
+// 32 rows of 2044 positions in chunks with new tokens 24.6 / 21.9, 32 rows of 8192 (d = 64) 22.6 / 21.2, 16 layers of 64 rows of 32768
+// 867 / 839 (the start of the main kernel, below, among it).
+template <int D> __global__ __launch_bounds__(D) void merge_partials_kernel(AttnLaunch a, Plan plan, int qtp)
 {
     __shared__ float red[2 * SPECATTN_MAX_T];
-    const int G = attn_group_heads(a);
-    const int QT = G * a.T;
-    const int rows = a.B * a.H_kv;
-    const int r = blockIdx.x / QT, q = blockIdx.x - r * QT;
-    const int b = r / a.H_kv, h = r - b * a.H_kv;
-    const int gh = q / a.T, t = q - gh * a.T;
-    const int64_t orow = ((int64_t)b * a.H_q + attn_query_head(a, h, gh)) * a.T + t;
+    const int q = blockIdx.x, r = blockIdx.y;
+    const int b = div_h(plan, r), h = r - b * a.H_kv;
+    const int gh = div_t(plan, q), t = q - gh * a.T;
+    const int head = attn_query_head(a, plan.heads, h, gh);
+    const int64_t orow = ((int64_t)b * a.H_q + head) * a.T + t;
     const int dv = threadIdx.x;
     const bool tail = a.k_new != nullptr;
-    const int total = plan.cost_prefix[rows];
-    const int p0 = plan.cost_prefix[r], p1 = plan.cost_prefix[r + 1];
-    if (p0 == p1 && !tail) {
-        a.out[orow * D + dv] = 0.0f;
-        if (a.out_lowp) st_lowp(a.out_lowp, orow * D + dv, 0.0f, a.dtype);
-        if (a.lse && dv == 0) a.lse[orow] = -INFINITY;
-        return;
+    const uint32_t parts = plan.row_parts[r];
+    float qe = 0.0f, ke[SPECATTN_MAX_T], ve[SPECATTN_MAX_T];
+    if (tail) {
+        const int64_t noff = (int64_t)r * a.T * D + dv;
+        qe = ld_elem(a.q, (int64_t)b * a.q_stride_b + (int64_t)head * a.q_stride_h + (int64_t)t * a.q_stride_t + dv, a.dtype);
+#pragma unroll
+        for (int p = 0; p < SPECATTN_MAX_T; ++p) {
+            ke[p] = p <= t ? ld_elem(a.k_new, noff + (int64_t)p * D, a.dtype) : 0.0f;
+            ve[p] = p <= t ? ld_elem(a.v_new, noff + (int64_t)p * D, a.dtype) : 0.0f;
+        }
     }
     Merge acc;
-    if (p0 != p1) {
-        const int w0 = share_of(total, plan.n_wg, p0 + SEG_COST), w1 = share_of(total, plan.n_wg, p1 - 1);
+    if (parts != ROW_EMPTY) {
+        const int w0 = parts & 0xffffu, w1 = parts >> 16;
         if (w0 == w1 && !tail) return;              // finished by its only workgroup
         auto trip = [&](int wb, auto most) {        // partials wb .. w1, at most N
             constexpr int N = decltype(most)::value;
@@ -69,13 +85,19 @@ template <int D> __global__ void merge_partials_kernel(AttnLaunch a, Plan plan, 
         else if (left > 0) trip(wb, std::integral_constant<int, 2>{});
     }
     if (tail) {
-        float dots[SPECATTN_MAX_T];
-        tail_dots(a, b, attn_query_head(a, h, gh), t, red, dots);
+        // scores of the query row against new tokens 0..t, over all threads of the workgroup
+        const int lane = dv & 63, wave = dv >> 6;
+#pragma unroll
+        for (int p = 0; p < SPECATTN_MAX_T; ++p) {
+            if (p > t) break;                       // (uniform)
+            const float x = wave_sum(qe * ke[p]);
+            if (lane == 0) red[wave * SPECATTN_MAX_T + p] = x;
+        }
+        __syncthreads();
         const float scale2 = a.sm_scale * 1.4426950408889634f;       // m is in log2 units
-        const int64_t noff = ((int64_t)b * a.H_kv + h) * a.T * D;
 #pragma unroll
         for (int p = 0; p < SPECATTN_MAX_T; ++p)
-            if (p <= t) acc.add(dots[p] * scale2, 1.0f, ld_elem(a.v_new, noff + (int64_t)p * D + dv, a.dtype));
+            if (p <= t) acc.add((red[p] + (D > 64 ? red[SPECATTN_MAX_T + p] : 0.0f)) * scale2, 1.0f, ve[p]);
     }
     const float res = acc.l > 0.0f ? acc.o / acc.l : 0.0f;
     a.out[orow * D + dv] = res;
@@ -146,7 +168,7 @@ constexpr int WIDE = 64, WIDE_MASK = 48, NARROW = 32;        // query rows a lau
 static size_t workspace_for(int rows, int nqt, int d)
 {
     const size_t slots = (size_t)attn_mfma_workgroups() + rows;
-    size_t bytes = align256(((size_t)rows + 1) * sizeof(int32_t));                        // cost prefix
+    size_t bytes = align256(((size_t)rows + 1) * sizeof(int32_t));                        // the rows' shares
     bytes += slots * nqt * 16 * (d + 2) * sizeof(float);
     return align256(bytes);
 }
@@ -174,6 +196,10 @@ static specattn_status launch_chunk(const AttnLaunch &a, hipStream_t stream)
     const int nqt = (QT + 15) / 16, qtp = nqt * 16;
     Plan plan;
     plan.n_wg = attn_mfma_workgroups();
+    plan.heads = a.H_q / a.H_kv;
+    plan.group = G;
+    plan.per_h = (uint32_t)((((uint64_t)1 << 31) + a.H_kv - 1) / a.H_kv);
+    plan.per_t = (65536u + a.T - 1) / a.T;
     const size_t slots = (size_t)plan.n_wg + rows;
     // every workgroup may leave a partial in slot (workgroup + row): never launch over a workspace that cannot hold them
     if (!a.workspace || a.workspace_bytes < workspace_for(rows, nqt, a.d)) {
@@ -181,7 +207,7 @@ static specattn_status launch_chunk(const AttnLaunch &a, hipStream_t stream)
         return SPECATTN_EWORKSPACE;
     }
     char *ws = static_cast<char *>(a.workspace);
-    plan.cost_prefix = reinterpret_cast<int32_t *>(ws);
+    plan.row_parts = reinterpret_cast<uint32_t *>(ws);
     ws += align256(((size_t)rows + 1) * sizeof(int32_t));
     plan.part_ml = reinterpret_cast<float *>(ws);
     plan.part_o = plan.part_ml + slots * qtp * 2;
@@ -201,7 +227,7 @@ static specattn_status launch_chunk(const AttnLaunch &a, hipStream_t stream)
     st = check_launch("attn_mfma_kernel");
     if (st != SPECATTN_OK) return st;
     const auto merge = a.d == 64 ? merge_partials_kernel<64> : merge_partials_kernel<128>;
-    hipLaunchKernelGGL(merge, dim3(rows * QT), dim3(a.d), 0, stream, a, plan, qtp);
+    hipLaunchKernelGGL(merge, dim3(QT, rows), dim3(a.d), 0, stream, a, plan, qtp);
     return check_launch("merge_partials_kernel");
 }
 

@@ -147,20 +147,23 @@ struct KvMap {
     int64_t base, stride_n, stride_page;
     const int32_t *ptab;
     int page_shift;
-    // row offsets (units of 2^UNIT bytes, relative to `base`) of N positions, the page-table loads (if any) in flight together
+    // row offsets (units of 2^UNIT bytes, relative to `base`) of N positions, the page-table loads (if any) in flight together.
+    // (Strides are whole units, so 32-bit products give the offsets' 32 bits: an eighth of the instructions of 64-bit ones.)
     template <int LAYOUT, int UNIT, int N> __device__ __forceinline__ void rel_n(const int (&idx)[N], uint32_t (&off)[N]) const
     {
+        const uint32_t step = (uint32_t)(stride_n >> (UNIT - 1));
         if (LAYOUT == CONTIGUOUS) {
 #pragma unroll
-            for (int i = 0; i < N; ++i) off[i] = (uint32_t)(((int64_t)idx[i] * stride_n) >> (UNIT - 1));
+            for (int i = 0; i < N; ++i) off[i] = (uint32_t)idx[i] * step;
             return;
         }
+        const uint32_t page_step = (uint32_t)(stride_page >> (UNIT - 1));
         const int mask = (1 << page_shift) - 1;
         int page[N];
 #pragma unroll
         for (int i = 0; i < N; ++i) page[i] = LAYOUT == PAGE_TABLE ? ptab[idx[i] >> page_shift] : (idx[i] >> page_shift);
 #pragma unroll
-        for (int i = 0; i < N; ++i) off[i] = (uint32_t)(((int64_t)page[i] * stride_page + (int64_t)(idx[i] & mask) * stride_n) >> (UNIT - 1));
+        for (int i = 0; i < N; ++i) off[i] = (uint32_t)page[i] * page_step + (uint32_t)(idx[i] & mask) * step;
     }
 };
 
@@ -343,34 +346,28 @@ __device__ __forceinline__ void vm_wait(int n)
     }
 }
 
+// What a launch hands to both kernels.  The divisors are known on the host, so the divisions by them are multiplications here.
 struct Plan {
     float *part_ml;           // [slots][16 * NQT][2]
     float *part_o;            // [slots][16 * NQT][d]
-    int32_t *cost_prefix;     // [rows + 1] in the workspace (written by workgroup 0, read by the merge kernel)
+    uint32_t *row_parts;      // [rows] in the workspace: the shares that hold a row's first (low half) and last tile, or ROW_EMPTY
     int n_wg;
+    int heads, group;         // query heads per kv head: in all, and in this launch
+    uint32_t per_h, per_t;    // 2^31 / H_kv and 2^16 / T, rounded up
 };
+constexpr uint32_t ROW_EMPTY = 0xffffffffu;
+// r / H_kv for r < 2^20, H_kv < 2^11, and q / T for q < 2^12, T < 2^4 (the rounding of the reciprocal stays below one part)
+__device__ __forceinline__ int div_h(const Plan &p, int r) { return (int)__umulhi((uint32_t)r << 1, p.per_h); }
+__device__ __forceinline__ int div_t(const Plan &p, int q) { return (int)(((uint32_t)q * p.per_t) >> 16); }
 
 // Cost of a row on the line the workgroups share out: its tiles, plus SEG_COST for picking the row up
 // (fresh Q, partial write), so that workgroups holding many short rows get fewer tiles.
 template <int TILE> __device__ __forceinline__ int row_cost(int count) { return count > 0 ? (count + TILE - 1) / TILE + SEG_COST : 0; }
 
-// Exclusive prefix of the row costs into pre[0..rows], every workgroup for itself.
-template <int TILE, int TABLE_ROWS> __device__ __forceinline__ void cost_prefix(const AttnLaunch &a, int rows, int *pre, int *cnt, int *wsum)
+// Exclusive prefix of the row costs into pre[0..rows], every workgroup for itself (more than FEW_ROWS rows).
+template <int TILE, int TABLE_ROWS> __device__ __forceinline__ void cost_prefix(const AttnLaunch &a, const Plan &plan, int rows, int *pre, int *cnt, int *wsum)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (rows <= FEW_ROWS) {
-        // Few rows: every wave scans all of them by itself and writes the (identical) tables; a wave reads
-        // back only after its own writes (LDS operations of a wave complete in order), so no barrier is needed.
-        const int c = lane < rows ? attn_row_count(a, lane) : 0;
-        const int cost = row_cost<TILE>(c);
-        const int inc = wave_inclusive_sum(cost);
-        if (lane < rows) { cnt[lane] = c; pre[lane] = inc - cost; }
-        if (lane == 63) pre[rows] = inc;                  // lanes past the last row add nothing
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        return;
-    }
     // Many rows: THREADS rows per round (the counts of all rounds are requested at once), a wave-wide scan, the
     // wave totals through LDS, the rounds before carried along.
     constexpr int ROUNDS = (TABLE_ROWS + THREADS - 1) / THREADS;
@@ -378,7 +375,7 @@ template <int TILE, int TABLE_ROWS> __device__ __forceinline__ void cost_prefix(
 #pragma unroll
     for (int k = 0; k < ROUNDS; ++k) {
         const int rr = k * THREADS + tid;
-        c[k] = rr < rows ? attn_row_count(a, rr) : 0;
+        c[k] = rr < rows ? attn_row_count(a, rr, div_h(plan, rr)) : 0;
     }
     int carry = 0;
 #pragma unroll
@@ -453,8 +450,9 @@ __device__ __forceinline__ int share_start(int total, int n_wg, int w)
 {
     const int n = n_wg < total ? n_wg : total;
     if (w >= n) return total;
-    // (a power of two - the usual 256 workgroups - divides exactly in any arithmetic: a shift then gives the same
-    // floor as the division below at a tenth of the instructions, on the way to a workgroup's first request)
+    // (fewer units than workgroups: one each; a power of two - the usual 256 workgroups - divides exactly in any arithmetic: a
+    // shift then gives the same floor as the division below at a tenth of the instructions, on the way to a workgroup's first request)
+    if (n == total) return w;
     if ((n & (n - 1)) == 0) return (int)(((int64_t)w * total) >> (31 - __clz(n)));
     return floor_div((int64_t)w * total, n);
 }
@@ -465,13 +463,6 @@ template <int TILE> __device__ __forceinline__ Share<TILE> make_share(int total,
     s.c1 = share_start(total, n_wg, w + 1);
     return s;
 }
-// the workgroup whose share holds cost position c (0 <= c < total)
-__device__ __forceinline__ int share_of(int total, int n_wg, int c)
-{
-    const int n = n_wg < total ? n_wg : total;
-    return floor_div(((int64_t)c + 1) * n - 1, total);
-}
-
 // Which share of the line a workgroup takes.  The hardware deals workgroup i to XCD i mod 8; the owners of
 // four consecutive shares (the usual team of a row) are four workgroups on four different XCDs, and the sets
 // {x, x+1, x+3, x+6} rotate from team to team, so that every XCD serves half of the teams and a difference in
@@ -480,7 +471,7 @@ __device__ __forceinline__ int share_index(int wg, int n_wg)
 {
     if (n_wg & 31) return wg;
     const int x = wg & 7, c = wg >> 3, m = c & 3;
-    const int off = m == 0 ? 0 : (m == 1 ? 1 : (m == 2 ? 3 : 6));
+    const int off = (0x6310 >> (4 * m)) & 7;
     const int team = ((c >> 2) << 3) | ((x - off) & 7);
     return (team << 2) | m;
 }
@@ -526,6 +517,7 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
     // (d = 64, where the products have time to spare).
     constexpr int NP = D == 64 ? 3 : 2;
     constexpr bool TIGHT = NQT >= 3;                                    // registers are short: what the tile loop can fetch again is not held
+    constexpr bool FOLD = !TIGHT && UNIT == 4;                          // a lane's chunk of a row is part of the row offset it holds
     constexpr int QG = NQT <= 2 ? NQT : 1;                              // query tiles whose scores are held at a time
     const int rows = a.B * a.H_kv;
     int *pre = reinterpret_cast<int *>(smem + TAB::OFF_TAB);
@@ -572,10 +564,10 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
     SPECATTN_PRELOAD(a.q_stride_b); SPECATTN_PRELOAD(a.q_stride_h); SPECATTN_PRELOAD(a.q_stride_t);
     SPECATTN_PRELOAD(a.kv_stride_b); SPECATTN_PRELOAD(a.kv_stride_h); SPECATTN_PRELOAD(a.kv_stride_n);
     SPECATTN_PRELOAD(a.counts); SPECATTN_PRELOAD(a.idx_capacity); SPECATTN_PRELOAD(a.dense); SPECATTN_PRELOAD(a.chunk_shift);
-    SPECATTN_PRELOAD(a.g_first); SPECATTN_PRELOAD(a.g_count); SPECATTN_PRELOAD(a.k_new);
+    SPECATTN_PRELOAD(a.g_first); SPECATTN_PRELOAD(a.k_new);
     SPECATTN_PRELOAD(a.out); SPECATTN_PRELOAD(a.out_lowp); SPECATTN_PRELOAD(a.lse);
-    SPECATTN_PRELOAD(plan.part_ml); SPECATTN_PRELOAD(plan.part_o); SPECATTN_PRELOAD(plan.cost_prefix);
-    SPECATTN_PRELOAD(plan.n_wg);
+    SPECATTN_PRELOAD(plan.part_ml); SPECATTN_PRELOAD(plan.part_o); SPECATTN_PRELOAD(plan.row_parts);
+    SPECATTN_PRELOAD(plan.n_wg); SPECATTN_PRELOAD(plan.heads); SPECATTN_PRELOAD(plan.group); SPECATTN_PRELOAD(plan.per_h); SPECATTN_PRELOAD(plan.per_t);
     if (LAYOUT != CONTIGUOUS) { SPECATTN_PRELOAD(a.page_table); SPECATTN_PRELOAD(a.page_shift); SPECATTN_PRELOAD(a.max_pages); SPECATTN_PRELOAD(a.kv_stride_page); }
     if (SRC == LIST) { SPECATTN_PRELOAD(a.indices); SPECATTN_PRELOAD(a.idx_stride); }
     if (SRC == MASK) { SPECATTN_PRELOAD(a.kept_mask); SPECATTN_PRELOAD(a.block_counts); SPECATTN_PRELOAD(a.blocks_per_row); SPECATTN_PRELOAD(a.n_max); }
@@ -593,15 +585,29 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
             bc_pf[k] = a.block_counts[j < rows * a.blocks_per_row ? j : 0];
         }
     }
-    cost_prefix<TILE, TAB::ROWS>(a, rows, pre, cnt_lds, wsum);
-    if (blockIdx.x == 0)
-        for (int rr = tid; rr <= rows; rr += THREADS) plan.cost_prefix[rr] = pre[rr];
+    // Every workgroup finds the cost line by itself.  Up to 64 rows, lane i of every wave holds row i: counts, prefix, share and
+    // every row's local tile range without a table, a barrier or a search; more rows go through tables in LDS.
+    const bool few_rows = rows <= FEW_ROWS;              // uniform
+    int row_lo = 0, row_cnt = 0, total;                  // few rows: cost prefix and kept count of row `lane`
+    if (__builtin_expect(few_rows, 1)) {
+        row_cnt = lane < rows ? attn_row_count(a, lane, div_h(plan, lane)) : 0;
+        const int cost = row_cost<TILE>(row_cnt), inc = wave_inclusive_sum(cost);
+        row_lo = inc - cost;
+        total = __builtin_amdgcn_readlane(inc, 63);      // (lanes past the last row add nothing)
+        if (TIGHT) { pre[lane] = row_lo; cnt_lds[lane] = row_cnt; }     // (every wave the same values, and a wave reads behind its own)
+        if (blockIdx.x == 0 && tid < rows && row_cnt == 0) plan.row_parts[tid] = ROW_EMPTY;
+    } else {
+        cost_prefix<TILE, TAB::ROWS>(a, plan, rows, pre, cnt_lds, wsum);
+        total = pre[rows];
+        if (blockIdx.x == 0)
+            for (int rr = tid; rr < rows; rr += THREADS)
+                if (cnt_lds[rr] == 0) plan.row_parts[rr] = ROW_EMPTY;
+    }
     if (bc_all) {
 #pragma unroll
         for (int k = 0; k < BC_PT; ++k) bc_lds[tid + k * THREADS] = bc_pf[k];   // (read behind the first segment's barrier)
     }
-    const int G = attn_group_heads(a);
-    const int QT = G * a.T;
+    const int QT = plan.group * a.T;
     const float scale2 = a.sm_scale * 1.4426950408889634f;            // scores in log2 units
 
     // ---- per-segment inputs that are fetched ahead of time -------------------------------------------
@@ -609,15 +615,15 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
     // ahead of time and stores it (swizzled like a K row) when the segment starts.
     u32x4 q_pf[QROUNDS];
     auto fetch_q = [&](int rr) {
-        const int b = rr / a.H_kv, h = rr - b * a.H_kv;
+        const int b = div_h(plan, rr), h = rr - b * a.H_kv;
 #pragma unroll
         for (int k = 0; k < QROUNDS; ++k) {
             const int qi = tid / LPR + k * (THREADS / LPR), ch = tid & (LPR - 1);
             q_pf[k] = (u32x4){0u, 0u, 0u, 0u};
             if (qi < QT) {
-                const int gh = qi / a.T, tt = qi - gh * a.T;
+                const int gh = div_t(plan, qi), tt = qi - gh * a.T;
                 const uint16_t *qp = static_cast<const uint16_t *>(a.q) + (int64_t)b * a.q_stride_b +
-                                     (int64_t)attn_query_head(a, h, gh) * a.q_stride_h + (int64_t)tt * a.q_stride_t;
+                                     (int64_t)attn_query_head(a, plan.heads, h, gh) * a.q_stride_h + (int64_t)tt * a.q_stride_t;
                 q_pf[k] = *reinterpret_cast<const u32x4 *>(qp + ch * 8);
             }
         }
@@ -630,18 +636,7 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
         }
     };
 
-    // This workgroup's share of the cost line, and the rows of which it holds tiles.  Up to 64 rows, lane i looks
-    // at row i: one LDS round trip, the share, every row's local tile range at once and a ballot, instead of a
-    // binary search and a row-by-row walk over the table, each step of which waits for an LDS read.
-    const bool few_rows = rows <= FEW_ROWS;              // uniform
-    int row_lo = 0, row_cnt = 0, row_hi = 0;
-    auto read_rows = [&]() {
-        row_lo = lane < rows ? pre[lane] : 0;
-        row_hi = lane < rows ? pre[lane + 1] : 0;
-        row_cnt = lane < rows ? cnt_lds[lane] : 0;
-    };
-    if (few_rows) read_rows();
-    const int total = few_rows ? __builtin_amdgcn_readlane(row_hi, rows - 1) : pre[rows];
+    // This workgroup's share of the cost line, and the rows of which it holds tiles
     const int my_share = share_index(blockIdx.x, plan.n_wg);
     const Share<TILE> sh = make_share<TILE>(total, plan.n_wg, my_share);
     const int c0 = sh.c0, c1 = sh.c1;
@@ -678,17 +673,40 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
     int r = few_rows ? next_seg(0) : sh.first_seg(pre, cnt_lds, rows);
 
     bool first_seg = true;
-    if (r < rows) fetch_q(r);
+    // The list words of the wave's first two tiles, ahead of everything else: the first gathers wait for them (counts -> list words ->
+    // K/V rows are three dependent trips to memory), and what the compiler computes ahead of the loop then runs while they fly.
+    // (With the request inside the loop, behind the divisions and some 180 such instructions, a layer took 1.2 us longer.)
+    auto row_count = [&](int r) { return few_rows ? __builtin_amdgcn_readlane(row_cnt, __builtin_amdgcn_readfirstlane(r)) : cnt_lds[r]; };
+    // (ranks past the row's end read the last word again)
+    auto request_words = [&](const int32_t *idx_row, int count, int t, int s) {
+        int jj = t * TILE + (lane & (TILE - 1));
+        jj = jj < count ? jj : count - 1;
+        __builtin_amdgcn_global_load_lds(GLOBAL_PTR(idx_row + (jj >> a.chunk_shift)), LDS_PTR(void, slot_lds + s * SLOT_BYTES), 4, 0, 0);
+    };
+    if (r < rows) {
+        if (SRC == LIST && !a.dense) {
+            int lt_begin, lt_end;
+            seg_range(r, lt_begin, lt_end);
+            if (lt_begin + wave < lt_end) {
+                const int32_t *idx_row = a.indices + (int64_t)r * a.idx_stride;
+                request_words(idx_row, row_count(r), lt_begin + wave, 0);
+                request_words(idx_row, row_count(r), lt_begin + wave + NW, 1);
+            }
+        }
+        fetch_q(r);
+    }
 
     while (r < rows) {
         int lt_begin, lt_end;
-        if (TIGHT && few_rows && !first_seg) { read_rows(); local_tiles(); }   // (not held in registers through the tile loop)
+        if (TIGHT && few_rows && !first_seg) {           // (not held in registers through the tile loop)
+            row_lo = pre[lane];
+            row_cnt = cnt_lds[lane];
+            local_tiles();
+        }
         seg_range(r, lt_begin, lt_end);
         const int r_next = next_seg(r + 1);
-        const int b = r / a.H_kv, h = r - b * a.H_kv;
-        const int count = few_rows ? __builtin_amdgcn_readlane(row_cnt, __builtin_amdgcn_readfirstlane(r)) : cnt_lds[r];
-        const int p_lo = few_rows ? __builtin_amdgcn_readlane(row_lo, __builtin_amdgcn_readfirstlane(r)) : pre[r];
-        const int p_hi = few_rows ? __builtin_amdgcn_readlane(row_hi, __builtin_amdgcn_readfirstlane(r)) : pre[r + 1];
+        const int b = div_h(plan, r), h = r - b * a.H_kv;
+        const int count = row_count(r);
         const int tiles = (count + TILE - 1) / TILE;
         const int tile_end = lt_end;             // the tiles [lt_begin, lt_end) of the row are this workgroup's
         const KvMap map = make_map<LAYOUT>(a, b, h);
@@ -733,10 +751,7 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
                 w = w < nw ? w : nw - 1;
                 __builtin_amdgcn_global_load_lds(GLOBAL_PTR(mask_row + w), LDS_PTR(void, slot_lds + s * SLOT_BYTES), 4, 0, 0);
             } else if (!a.dense) {
-                int jj = t * TILE + (lane & (TILE - 1));
-                jj = jj < count ? jj : count - 1;
-                __builtin_amdgcn_global_load_lds(GLOBAL_PTR(idx_row + (jj >> a.chunk_shift)),
-                                                 LDS_PTR(void, slot_lds + s * SLOT_BYTES), 4, 0, 0);
+                request_words(idx_row, count, t, s);
             }
         };
         // Mask source: turns the 64 mask words in slot s into the 32 positions of tile t (table s of the wave).  The
@@ -794,12 +809,11 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
         // Row offsets (in units) of the 8 rows this lane helps to fetch for tile t, whose list words (or decoded
         // positions) are in slot / table s.
         auto entries = [&](int t, int s, uint32_t (&ent)[8]) {
-            int pos[8], jj[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                jj[i] = t * TILE + RPI * i + lrow;
-                jj[i] = jj[i] < count ? jj[i] : count - 1;              // ranks past the end repeat the last kept position
-            }
+            int pos[8];
+            auto rank = [&](int i) -> int {                             // ranks past the end repeat the last kept position
+                const int jj = t * TILE + RPI * i + lrow;
+                return jj < count ? jj : count - 1;
+            };
             if (SRC == MASK) {
                 uint32_t e[8];
                 lds_read_entries<RPI>(e, scat_addr + (uint32_t)(s * 128 + lrow * 4));
@@ -808,15 +822,23 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
                 for (int i = 0; i < 8; ++i) pos[i] = e[i] < (uint32_t)a.n_max ? (int)e[i] : a.n_max - 1;
             } else if (a.dense) {
 #pragma unroll
-                for (int i = 0; i < 8; ++i) pos[i] = jj[i];
+                for (int i = 0; i < 8; ++i) pos[i] = rank(i);
             } else {
                 uint32_t e[8];
                 lds_read_entries<RPI>(e, slot_addr + (uint32_t)(s * SLOT_BYTES + lrow * 4));
                 const int cs = a.chunk_shift, low = (1 << cs) - 1;
 #pragma unroll
-                for (int i = 0; i < 8; ++i) pos[i] = (int)(e[i] << cs) | (jj[i] & low);
+                for (int i = 0; i < 8; ++i) pos[i] = (int)e[i];
+                if (cs) {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) pos[i] = (int)(e[i] << cs) | (rank(i) & low);
+                }
             }
             map.rel_n<LAYOUT, UNIT>(pos, ent);
+            if constexpr (FOLD) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) ent[i] += (lane_chunk ^ chunk_flip(i)) >> 4;
+            }
         };
         // Where a tile's row offsets wait for the V gathers when they are not held in registers: the position tables, which
         // only the mask source uses, or (mask source) the slot whose words have been decoded.
@@ -825,7 +847,7 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
         auto issue = [&](const char *base, char *buf, const uint32_t (&ent)[8]) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                const char *src = base + ((int64_t)ent[i] << UNIT) + (lane_chunk ^ chunk_flip(i));
+                const char *src = base + ((int64_t)ent[i] << UNIT) + (FOLD ? 0u : lane_chunk ^ chunk_flip(i));
                 __builtin_amdgcn_global_load_lds(GLOBAL_PTR(src), LDS_PTR(void, buf + i * 1024), 16, 0, KV_AUX);
             }
         };
@@ -852,7 +874,7 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
                 lds_barrier();
             }
         }
-        if (t_cur < tile_end) { request(t_cur, 0); request(t_nxt, 1); }
+        if ((SRC == MASK || !first_seg) && t_cur < tile_end) { request(t_cur, 0); request(t_nxt, 1); }
         store_q();
         lds_barrier();
 
@@ -1043,7 +1065,7 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
                     entries(t, 0, ent);
 #pragma unroll
                     for (int i = 0; i < 8; ++i) {
-                        const u32x4 c = *reinterpret_cast<const u32x4 *>(vbh + ((int64_t)ent[i] << UNIT) + ((lane & (LPR - 1)) << 4));
+                        const u32x4 c = *reinterpret_cast<const u32x4 *>(vbh + ((int64_t)ent[i] << UNIT) - (FOLD ? lane_chunk ^ chunk_flip(i) : 0u) + ((lane & (LPR - 1)) << 4));
 #pragma unroll
                         for (int e = 0; e < 8; ++e) {
                             const uint32_t bits = (c[e >> 1] >> (16 * (e & 1))) & 0xffffu;
@@ -1080,10 +1102,14 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
         //      wave's word slots. ---------------------------------------------------------------------------
         // (a wave's buffers hold 16 blocks: two query tiles at d = 128, four at d = 64; more go over in rounds)
         constexpr int RQ = 16 / DT < NQT ? 16 / DT : NQT;                      // query tiles per round
-        // Workgroups w_first..w_last share row r: a row owned by one workgroup is finished here; otherwise the
-        // partial goes to slot (share + r) for the merge kernel.
-        const int w_first = share_of(total, plan.n_wg, p_lo + SEG_COST), w_last = share_of(total, plan.n_wg, p_hi - 1);
-        const bool final_here = w_first == w_last && !a.k_new;
+        // A row owned by one workgroup is finished here; otherwise the partial goes to slot (share + r) for the merge kernel, which
+        // learns from the owners of the row's first and last tile which shares those are.
+        const bool final_here = lt_begin == 0 && lt_end == tiles && !a.k_new;
+        if (tid == 0) {
+            uint16_t *parts = reinterpret_cast<uint16_t *>(plan.row_parts + r);
+            if (lt_begin == 0) parts[0] = (uint16_t)my_share;
+            if (lt_end == tiles) parts[1] = (uint16_t)my_share;
+        }
         static_for<(NQT + RQ - 1) / RQ>([&](auto round) {
             constexpr int Q0 = decltype(round)::value * RQ;
             constexpr int QN = NQT - Q0 < RQ ? NQT - Q0 : RQ;
@@ -1130,8 +1156,8 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
                 const int q = qt * 16 + l16;
                 if (q < QT) {
                     if (final_here) {
-                        const int gh = q / a.T, tt = q - gh * a.T;
-                        const int64_t orow = ((int64_t)b * a.H_q + attn_query_head(a, h, gh)) * a.T + tt;
+                        const int gh = div_t(plan, q), tt = q - gh * a.T;
+                        const int64_t orow = ((int64_t)b * a.H_q + attn_query_head(a, plan.heads, h, gh)) * a.T + tt;
                         const f32x4 res = l > 0.0f ? acc / l : (f32x4){0.f, 0.f, 0.f, 0.f};
                         *reinterpret_cast<f32x4 *>(a.out + orow * D + 16 * t + 4 * g) = res;
                         if (a.out_lowp) {

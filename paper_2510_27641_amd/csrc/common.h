@@ -108,12 +108,8 @@ struct AttnLaunch {
     const int32_t *block_counts; // [rows][blocks_per_row]
     int blocks_per_row;
 };
-__device__ __forceinline__ int attn_group_heads(const AttnLaunch &a) { return a.g_count ? a.g_count : a.H_q / a.H_kv; }
-// query head behind head gh of this launch's share of kv head h's group
-__device__ __forceinline__ int attn_query_head(const AttnLaunch &a, int h, int gh)
-{
-    return h * (a.H_q / a.H_kv) + a.g_first + gh;
-}
+// query head behind head gh of this launch's share of kv head h's group (`heads` query heads in all)
+__device__ __forceinline__ int attn_query_head(const AttnLaunch &a, int heads, int h, int gh) { return h * heads + a.g_first + gh; }
 
 // Inclusive prefix sum over the 64 lanes of a wave on the vector ALU (no LDS traffic): shifts by 1, 2, 4, 8 inside
 // each row of 16 lanes, then lane 15 of rows 0 and 2 into rows 1 and 3, then lane 31 into rows 2 and 3.
@@ -128,15 +124,15 @@ __device__ __forceinline__ int wave_inclusive_sum(int v)
     return v;
 }
 
-// Number of positions row r attends to: the kept count (clamped to the list capacity), or the
+// Number of positions row r (of sequence b) attends to: the kept count (clamped to the list capacity), or the
 // sequence length when there is no list.  With a chunk list: the kept chunks' positions, less the
 // part of the last kept chunk that lies past the sequence length (the list is ascending, so only
 // the last entry can be the partial chunk).
-__device__ __forceinline__ int attn_row_count(const AttnLaunch &a, int r)
+__device__ __forceinline__ int attn_row_count(const AttnLaunch &a, int r, int b)
 {
     int len = a.n_max;
     if (a.dense || a.chunk_shift) {
-        len = a.seq_lens ? a.seq_lens[r / a.H_kv] : a.n_max;
+        len = a.seq_lens ? a.seq_lens[b] : a.n_max;
         len = len < 0 ? 0 : (len > a.n_max ? a.n_max : len);
     }
     if (a.dense) return len;
@@ -177,30 +173,6 @@ __device__ __forceinline__ void st_lowp(void *p, int64_t i, float x, int dtype)
     } else {
         static_cast<float *>(p)[i] = x;
     }
-}
-
-// Scores of query row (b, hq, t) against the keys of new tokens 0..t (unscaled dot products), computed
-// by all threads of a workgroup of blockDim.x = max(64, d) threads together; `red` is LDS scratch of
-// 2 * SPECATTN_MAX_T floats.  Every thread returns with all t + 1 values.  Contains a barrier.
-__device__ __forceinline__ void tail_dots(const AttnLaunch &a, int b, int hq, int t, float *red,
-                                          float (&dots)[SPECATTN_MAX_T])
-{
-    const int e = threadIdx.x, lane = e & 63, wave = e >> 6;
-    const int hk = hq / (a.H_q / a.H_kv);
-    const int64_t qoff = (int64_t)b * a.q_stride_b + (int64_t)hq * a.q_stride_h + (int64_t)t * a.q_stride_t;
-    const int64_t noff = ((int64_t)b * a.H_kv + hk) * a.T * a.d;
-    const float qe = e < a.d ? ld_elem(a.q, qoff + e, a.dtype) : 0.0f;
-#pragma unroll
-    for (int p = 0; p < SPECATTN_MAX_T; ++p) {
-        float x = (p <= t && e < a.d) ? qe * ld_elem(a.k_new, noff + (int64_t)p * a.d + e, a.dtype) : 0.0f;
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
-        if (lane == 0 && wave < 2) red[wave * SPECATTN_MAX_T + p] = x;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int p = 0; p < SPECATTN_MAX_T; ++p)
-        dots[p] = red[p] + (blockDim.x > 64 ? red[SPECATTN_MAX_T + p] : 0.0f);
 }
 
 // number of splits per row the attention launch will use for this shape

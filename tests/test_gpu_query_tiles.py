@@ -303,3 +303,35 @@ def test_options_together(d, G, T, dtype, mode, paged):
         assert np.array_equal(np.isneginf(got), ~fin) and np.abs(got[fin] - want_lse[fin]).max() <= 1e-3
         if more:
             assert torch.equal(low, out.to(dt))
+
+
+@pytest.mark.parametrize("new_tokens", [False, True])
+@pytest.mark.parametrize("B,H_kv,G,T", [(1, 1, 1, 1), (4, 16, 3, 3), (13, 5, 5, 7), (9, 7, 9, 6), (2, 33, 2, 5)])
+def test_rows_and_their_shares(B, H_kv, G, T, new_tokens):
+    """63, 64 and 65 rows and few ones, head and token counts that are no powers of two, empty rows among full ones, rows inside
+    one workgroup and over many, in a workspace that holds anything."""
+    n, d = 700, 128
+    rng = np.random.default_rng(B * 100 + H_kv)
+    w = W.llama8b_layer(seed=G, B=B, n=n, H_q=G * H_kv, H_kv=H_kv, T=T, d=d, dtype="f16")
+    keep = rng.integers(0, n + 1, size=(B, H_kv)) * (rng.random((B, H_kv)) < 0.8)
+    keep[0, 0] = n
+    mask = (np.arange(n) < keep[..., None]).astype(np.uint8)
+    q, k, v = kv_tensors(w)
+    idx, cnt = lists(mask)
+    out = torch.full(q.shape, float("nan"), dtype=torch.float32, device="cuda")
+    extra, ref = {}, None
+    if new_tokens:
+        nk, nv = (rng.standard_normal((B, H_kv, T, d)).astype(np.float16) for _ in range(2))
+        extra = dict(k_new=dev(nk), v_new=dev(nv))
+        ref, _ = oracle.masked_attention(*(x.astype(np.float16).view(np.uint16) for x in (w.q, w.k, w.v)), mask, f16=True,
+                                         k_new=nk.view(np.uint16), v_new=nv.view(np.uint16))
+    else:
+        ref, _ = oracle_attention(w, mask)
+    att = sa.attn_args(q, k, v, out=out, indices=idx, counts=cnt, **extra)
+    ws = sa.alloc_workspace(sa.specattn_workspace_size(None, att))
+    ws.copy_(torch.from_numpy(rng.integers(0, 256, size=ws.numel(), dtype=np.uint8)))
+    att.workspace, att.workspace_bytes = ws.data_ptr(), ws.numel()
+    for _ in range(2):                                         # the second pass finds what the first one left
+        sa.specattn_sparse_decode_attn(att)
+        torch.cuda.synchronize()
+        assert row_rel_err(out.cpu().numpy(), ref) <= TOL["f16"]
