@@ -637,8 +637,8 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
     };
 
     // This workgroup's share of the cost line, and the rows of which it holds tiles
-    const int my_share = share_index(blockIdx.x, plan.n_wg);
-    const Share<TILE> sh = make_share<TILE>(total, plan.n_wg, my_share);
+    const int my_share = __builtin_amdgcn_readfirstlane(share_index(blockIdx.x, plan.n_wg));
+    const Share<TILE> sh = make_share<TILE>(__builtin_amdgcn_readfirstlane(total), plan.n_wg, my_share);
     const int c0 = sh.c0, c1 = sh.c1;
     if (c0 >= c1) return;                                // more workgroups than units of work
     int my_lb = 0, my_le = 0;                            // few rows: local tile range of row `lane`
@@ -670,12 +670,11 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
         }
         return sh.next_seg(pre, cnt_lds, rows, r);
     };
-    int r = few_rows ? next_seg(0) : sh.first_seg(pre, cnt_lds, rows);
+    int r = __builtin_amdgcn_readfirstlane(few_rows ? next_seg(0) : sh.first_seg(pre, cnt_lds, rows));
 
     bool first_seg = true;
     // The list words of the wave's first two tiles, ahead of everything else: the first gathers wait for them (counts -> list words ->
     // K/V rows are three dependent trips to memory), and what the compiler computes ahead of the loop then runs while they fly.
-    // (With the request inside the loop, behind the divisions and some 180 such instructions, a layer took 1.2 us longer.)
     auto row_count = [&](int r) { return few_rows ? __builtin_amdgcn_readlane(row_cnt, __builtin_amdgcn_readfirstlane(r)) : cnt_lds[r]; };
     // (ranks past the row's end read the last word again)
     auto request_words = [&](const int32_t *idx_row, int count, int t, int s) {
@@ -704,7 +703,7 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
             local_tiles();
         }
         seg_range(r, lt_begin, lt_end);
-        const int r_next = next_seg(r + 1);
+        const int r_next = __builtin_amdgcn_readfirstlane(next_seg(r + 1));
         const int b = div_h(plan, r), h = r - b * a.H_kv;
         const int count = row_count(r);
         const int tiles = (count + TILE - 1) / TILE;
