@@ -1,18 +1,18 @@
 // Sorting-free exact top-p selection (Section 3.4, Algorithm 2; objective Appendix A, Eq. 8).
 //
 // Algorithm 2 bisects the threshold in value space and evaluates the kept mass once per step.
-// This kernel reaches the exact threshold tau* = max{t : mass{a >= t} >= p * sum a} with three
-// radix passes over the fp32 bit pattern instead (non-negative floats order like their bits):
-//   pass 1: 2048 bins on bits[30:20], pass 2: 1024 bins on bits[19:10] inside the boundary bin,
-//   pass 3: 1024 bins on bits[9:0]  ->  all 31 bits of tau*.
+// The kernels here reach the exact threshold tau* = max{t : mass{a >= t} >= p * sum a} with radix passes over the
+// fp32 bit pattern instead (non-negative floats order like their bits).
 // All entries of one bin share their exponent, so a bin's mass is kept as an exact integer sum
-// of 24-bit significands next to the count in one 64-bit LDS counter; bin masses are therefore
+// of significands next to the count in one 64-bit LDS counter; bin masses are therefore
 // independent of summation order and the result is deterministic.  fp64 appears only in the
-// suffix sums over bins.  The kept positions are then written in ascending order by
-// ballot + popcount prefix (no dense mask, no CSR conversion as in Section 3.5).
+// suffix sums over bins.  The kept positions are then written in ascending order (no dense mask, no CSR conversion as in
+// Section 3.5).
 //
-// One workgroup owns one row.  Rows up to THREADS*4*NV4 entries live in registers for all four
-// passes (one HBM read); longer rows are re-read from L2/HBM each pass.
+// Rows of up to 65536 entries: one workgroup per row, which holds it in registers for all passes (one HBM read;
+// select_resident.h).  Few long rows: split over many workgroups.  Many long rows: one workgroup streams the row in every pass.
+// The latter two take pass 1: 2048 bins on bits[30:20], pass 2: 1024 bins on bits[19:10] inside the boundary bin,
+// pass 3: 1024 bins on bits[9:0].
 #include "common.h"
 
 namespace specattn {
@@ -36,14 +36,6 @@ struct Located {                 // outcome of one locate step
     unsigned long long packed;
     unsigned c_above;
     int bin;
-};
-
-struct RowShared {
-    Located found;
-    unsigned wave_c[16];
-    unsigned wave_tot[2][16];
-    unsigned wt[256];            // kept entries per (item, wave), then their exclusive prefix
-    unsigned running;
 };
 
 // What an entry adds to its bin's counter: one to the count, and its 23 significand bits with bit 23 set.  For
@@ -216,16 +208,6 @@ __device__ __forceinline__ void clear_hist(unsigned long long *hist)
         if (b + (int)threadIdx.x < N) hist[b + threadIdx.x] = 0ull;
 }
 
-// THREADS threads per row; RESIDENT: the row sits in NV4 uint4 registers per thread.
-// Dynamic LDS: the histograms (one of the first pass, which the third takes over, and one of the second), and afterwards in
-// their place the buffer in which a row's list is put together in list order for contiguous stores (smaller for the small
-// workgroups, several of which share a CU; longer lists take several rounds).
-constexpr unsigned stage_entries(int threads) { return threads <= 256 ? 4096u : 8192u; }
-constexpr unsigned select_lds(int threads)
-{
-    return stage_entries(threads) * 4 > (HIST1 + HIST2) * 8 ? stage_entries(threads) * 4 : (HIST1 + HIST2) * 8;
-}
-
 // The mass of chunk c of a row of `len` positions (Section 4: chunk-granular selection; the score of a chunk is its mass):
 // its entries added up in fp64 in ascending position order, rounded once to fp32; NaN if one of them is invalid.
 __device__ __forceinline__ float chunk_mass(const float *row, int len, int c, int chunk_shift)
@@ -254,25 +236,26 @@ __device__ __forceinline__ float chunk_mass(const float *row, int len, int c, in
     return bad ? __uint_as_float(0x7fc00000u) : (float)sum;
 }
 
-// CHUNKED: a.probs are rows of positions; the workgroup adds the chunks up itself, into the LDS that the histograms take over.
-template <int THREADS, int NV4, bool RESIDENT, bool CHUNKED = false>
-__global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
+#include "select_resident.h"
+
+// Rows too long for the registers: one workgroup per row, which streams it in every pass.
+constexpr int STREAM_THREADS = 1024, STREAM_WAVES = STREAM_THREADS / 64, STREAM_ITEM = STREAM_THREADS * 4;
+__global__ __launch_bounds__(STREAM_THREADS, 4) void topp_select_stream_kernel(SelectLaunch a)
 {
-    __shared__ RowShared sh;
-    extern __shared__ __align__(16) unsigned long long select_dyn[];
-    unsigned long long *hist1 = select_dyn, *hist2 = select_dyn + HIST1;
-    constexpr int NW = THREADS / 64;
-    constexpr int ITEM = THREADS * 4;                 // positions per item (one uint4 per thread)
+    __shared__ Located found;
+    __shared__ unsigned wave_tot[2][STREAM_WAVES];
+    __shared__ unsigned running;
+    __shared__ unsigned long long hist1[HIST1 + HIST2];
+    unsigned long long *hist2 = hist1 + HIST1;
     const int r = blockIdx.x;
     const int b = r / a.H_kv, h = r - b * a.H_kv;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     int len = a.seq_lens ? a.seq_lens[b] : a.n_tokens;
     len = len < 0 ? 0 : (len > a.n_tokens ? a.n_tokens : len);
-    const int positions = len;
     len = (len + (1 << a.chunk_shift) - 1) >> a.chunk_shift;     // rows of chunk masses: length in chunks
     len = len > a.n_max ? a.n_max : len;
     const float *row = a.probs + (int64_t)b * a.stride_b + (int64_t)h * a.stride_h;
-    const int n_items = (len + ITEM - 1) / ITEM;
+    const int n_items = (len + STREAM_ITEM - 1) / STREAM_ITEM;
 
     // -0.0 is zero; negative, infinite and NaN entries make the row invalid.  Branch-free: the largest bit pattern
     // seen is tested once per thread, and an invalid entry is clamped to the largest finite value so that its bin
@@ -286,7 +269,7 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
     auto clean4 = [&](uint4 u) -> uint4 { return make_uint4(clean(u.x), clean(u.y), clean(u.z), clean(u.w)); };
     // Slow form of an item's load (rows of fewer than four entries).
     auto load_item = [&](int i) -> uint4 {
-        const int p = (i * THREADS + tid) * 4;
+        const int p = (i * STREAM_THREADS + tid) * 4;
         uint4 u = make_uint4(0, 0, 0, 0);
         if (p < len) u.x = __float_as_uint(row[p]);
         if (p + 1 < len) u.y = __float_as_uint(row[p + 1]);
@@ -294,105 +277,48 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
         if (p + 3 < len) u.w = __float_as_uint(row[p + 3]);
         return clean4(u);
     };
-    // Fast form: every thread issues plain 16-byte loads with nothing between them that waits for data, so
-    // all of a thread's loads are in flight together.  They need no more than the 4-byte alignment of a float: the rows
-    // of an odd length start anywhere (entry by entry, as such rows used to be read, 64 rows of 13001 took 16.6 us, and
-    // 14.5 us now).  An item that reaches past the row's end loads the
-    // row's last whole vector instead (in bounds) and is masked afterwards; the at most three entries behind
-    // the last whole vector are fetched once, by the thread that owns them.
-    const bool vec_ok = CHUNKED || len >= 4;                   // uniform
+    // Fast form: plain 16-byte loads from any float's address.  An item that reaches past the row's end loads the row's last
+    // whole vector instead (in bounds) and is masked afterwards; the at most three entries behind it are fetched once.
+    const bool vec_ok = len >= 4;                              // uniform
     const int last4 = (len - 4) & ~3;                          // start of the row's last whole vector
     const int tail_p = (len & 3) ? (len & ~3) : -1;            // start of the partial vector, if any
     uint4 tailv = make_uint4(0, 0, 0, 0);
-    if (!CHUNKED && vec_ok && tail_p >= 0 && tid == (tail_p % ITEM) / 4) {
+    if (vec_ok && tail_p >= 0 && tid == (tail_p % STREAM_ITEM) / 4) {
         tailv.x = __float_as_uint(row[tail_p]);
         if (tail_p + 1 < len) tailv.y = __float_as_uint(row[tail_p + 1]);
         if (tail_p + 2 < len) tailv.z = __float_as_uint(row[tail_p + 2]);
     }
     auto raw_load = [&](int i) -> uint4 {
-        const int p = (i * THREADS + tid) * 4;
-        // streaming load: a row is read once and should not displace anything in the caches
+        const int p = (i * STREAM_THREADS + tid) * 4;
         const u32x4a v = __builtin_nontemporal_load(reinterpret_cast<const u32x4a *>(row + (p < last4 ? p : last4)));
         return make_uint4(v.x, v.y, v.z, v.w);
     };
     auto finish_item = [&](int i, uint4 u) -> uint4 {
-        const int p = (i * THREADS + tid) * 4;
+        const int p = (i * STREAM_THREADS + tid) * 4;
         if (p + 3 >= len) u = (p == tail_p) ? tailv : make_uint4(0, 0, 0, 0);
         return clean4(u);
     };
-
-    uint4 data[RESIDENT ? NV4 : 1];
-    if constexpr (CHUNKED) {
-        static_assert(RESIDENT && ITEM * NV4 * 4 <= (int)select_lds(THREADS), "a row's masses wait in dynamic LDS");
-        float *mass = reinterpret_cast<float *>(select_dyn);
-        for (int c = tid; c < ITEM * NV4; c += THREADS) mass[c] = c < len ? chunk_mass(row, positions, c, a.chunk_shift) : 0.0f;
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < NV4; ++i) data[i] = reinterpret_cast<const uint4 *>(mass)[i * THREADS + tid];
-        __syncthreads();
-    } else if (RESIDENT) {
-        if (vec_ok) {
-#pragma unroll
-            for (int i = 0; i < NV4; ++i) data[i] = raw_load(i);
-        } else {
-#pragma unroll
-            for (int i = 0; i < NV4; ++i) data[i] = (i < n_items) ? load_item(i) : make_uint4(0, 0, 0, 0);
-        }
-    }
-    // the histograms are cleared while the loads are in flight
-    clear_hist<THREADS, HIST1 + HIST2>(hist1);
+    clear_hist<STREAM_THREADS, HIST1 + HIST2>(hist1);
     __syncthreads();
-    if (RESIDENT && vec_ok) {
-        // Common case first: no sign bit among the thread's entries.  Then nothing needs cleaning, an entry is invalid
-        // exactly if its exponent field is all ones, and every bin index stays below NB1 - one OR and one maximum per
-        // entry instead of a compare, two selects and a maximum.
-        uint32_t any = 0u, top = 0u;
-#pragma unroll
-        for (int i = 0; i < NV4; ++i) {
-            const int p = (i * THREADS + tid) * 4;
-            uint4 u = data[i];
-            if (!CHUNKED && p + 3 >= len) u = (p == tail_p) ? tailv : make_uint4(0, 0, 0, 0);
-            data[i] = u;
-            any |= u.x | u.y | u.z | u.w;
-            const uint32_t m01 = u.x > u.y ? u.x : u.y, m23 = u.z > u.w ? u.z : u.w;
-            const uint32_t m = m01 > m23 ? m01 : m23;
-            top = top > m ? top : m;
-        }
-        if (any & 0x80000000u) {                 // -0.0 or a negative entry somewhere
-#pragma unroll
-            for (int i = 0; i < NV4; ++i) data[i] = clean4(data[i]);
-        } else {
-            worst = top;
-        }
-    }
     auto for_items = [&](auto &&fn) {
-        if (RESIDENT) {
+        for (int i0 = 0; i0 < n_items; i0 += 4) {              // four loads in flight per thread
+            uint4 u[4];
+            if (vec_ok) {
 #pragma unroll
-            for (int i = 0; i < NV4; ++i)
-                if (i < n_items) fn(i, data[i]);
-        } else {
-            // rows too long for the registers: stream them, four loads in flight per thread
-            for (int i0 = 0; i0 < n_items; i0 += 4) {
-                uint4 u[4];
-                if (vec_ok) {
+                for (int k = 0; k < 4; ++k) u[k] = raw_load(i0 + k);
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) u[k] = raw_load(i0 + k);
+                for (int k = 0; k < 4; ++k) u[k] = finish_item(i0 + k, u[k]);
+            } else {
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) u[k] = finish_item(i0 + k, u[k]);
-                } else {
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) u[k] = (i0 + k < n_items) ? load_item(i0 + k) : make_uint4(0, 0, 0, 0);
-                }
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    if (i0 + k < n_items) fn(i0 + k, u[k]);
+                for (int k = 0; k < 4; ++k) u[k] = (i0 + k < n_items) ? load_item(i0 + k) : make_uint4(0, 0, 0, 0);
             }
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (i0 + k < n_items) fn(i0 + k, u[k]);
         }
     };
 
     // ---- pass 1: bits[30:20] -----------------------------------------------------------------
-    // (one histogram per pair of waves instead of one per workgroup measured slower: the atomics of a row's few
-    // dozen busy bins are not what bounds this pass)
     for_items([&](int, uint4 u) {
         if (u.x) atomicAdd(&hist1[hist_slot<NB1>(u.x >> 20)], packed_entry(u.x));
         if (u.y) atomicAdd(&hist1[hist_slot<NB1>(u.y >> 20)], packed_entry(u.y));
@@ -404,7 +330,7 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
     double target = 0.0, m_above = 0.0;
     unsigned c_above = 0;
     unsigned long long bin_packed = 0;
-    const int b1 = locate_bin<NB1, true>(hist1, sh.found, 0, a.top_p, target, m_above, c_above, bin_packed);
+    const int b1 = locate_bin<NB1, true>(hist1, found, 0, a.top_p, target, m_above, c_above, bin_packed);
     const double row_sum = (double)target / (double)a.top_p;     // only used for the boundary flag
     if (any_bad || b1 < 0 || len == 0) {
         if (tid == 0) {
@@ -413,9 +339,9 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
             if (a.row_flags) a.row_flags[r] = SPECATTN_ROW_INVALID;
         }
         if (a.block_counts)
-            for (int k = tid; k < a.blocks_per_row; k += THREADS) a.block_counts[(int64_t)r * a.blocks_per_row + k] = 0;
+            for (int k = tid; k < a.blocks_per_row; k += STREAM_THREADS) a.block_counts[(int64_t)r * a.blocks_per_row + k] = 0;
         if (a.kept_mask)
-            for (int k = tid; k < a.blocks_per_row * (SEL_BLOCK / 32); k += THREADS)
+            for (int k = tid; k < a.blocks_per_row * (SEL_BLOCK / 32); k += STREAM_THREADS)
                 a.kept_mask[(int64_t)r * a.blocks_per_row * (SEL_BLOCK / 32) + k] = 0u;
         return;
     }
@@ -442,16 +368,16 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
             });
             __syncthreads();
         };
-        clear_hist<THREADS, HIST2>(hist1);
+        clear_hist<STREAM_THREADS, HIST2>(hist1);
         refine((uint32_t)b1 << 20, 1u << 20, [&](uint32_t x) { atomicAdd(&hist2[hist_slot<NB2>((x >> 10) & 1023u)], packed_entry(x)); });
-        const int b2 = locate_bin<NB2, false>(hist2, sh.found, e_field, a.top_p, target, m_above, c_above, bin_packed);
+        const int b2 = locate_bin<NB2, false>(hist2, found, e_field, a.top_p, target, m_above, c_above, bin_packed);
         const uint32_t prefix = ((uint32_t)b1 << 10) | (uint32_t)b2;
         if ((bin_packed >> CNT_SHIFT) == 1) {
             tau_bits = single_entry_bits(bin_packed);
         } else {
             // ---- pass 3: bits[9:0] inside (b1, b2) -------------------------------------------
             refine(prefix << 10, 1u << 10, [&](uint32_t x) { atomicAdd(&hist1[hist_slot<NB2>(x & 1023u)], packed_entry(x)); });
-            const int b3 = locate_bin<NB2, false>(hist1, sh.found, e_field, a.top_p, target, m_above, c_above, bin_packed);
+            const int b3 = locate_bin<NB2, false>(hist1, found, e_field, a.top_p, target, m_above, c_above, bin_packed);
             tau_bits = (prefix << 10) | (uint32_t)b3;             // >= 1: zeros never enter a bin
         }
     }
@@ -468,16 +394,16 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
             if (a.indices && kept > (unsigned)a.idx_capacity) f |= SPECATTN_ROW_OVERFLOW;
             a.row_flags[r] = f;
         }
-        sh.running = 0;
+        running = 0;
     }
     if (!a.indices && !a.block_counts && !a.kept_mask) return;
     uint32_t *mask_out = a.kept_mask ? a.kept_mask + (int64_t)r * a.blocks_per_row * (SEL_BLOCK / 32) : nullptr;
     const int mask_words = a.blocks_per_row * (SEL_BLOCK / 32);
-    // word (i * THREADS + tid) / 8 of the mask covers this thread's four positions of item i; the lane that
+    // word (i * STREAM_THREADS + tid) / 8 of the mask covers this thread's four positions of item i; the lane that
     // holds the word's first nibble stores it
     auto emit_mask = [&](int i, uint32_t nibble) {
         const uint32_t word = mask_word(nibble, lane);
-        const int w = (i * THREADS + tid) >> 3;
+        const int w = (i * STREAM_THREADS + tid) >> 3;
         if ((lane & 7) == 0 && w < mask_words) mask_out[w] = word;
     };
 
@@ -495,28 +421,28 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
         const unsigned wtot = __popcll(m0) + __popcll(m1) + __popcll(m2) + __popcll(m3);
         if (mask_out) emit_mask(i, (f0 ? 1u : 0u) | (f1 ? 2u : 0u) | (f2 ? 4u : 0u) | (f3 ? 8u : 0u));
         const int buf = it & 1;
-        if (lane == 0) sh.wave_tot[buf][wave] = wtot;
+        if (lane == 0) wave_tot[buf][wave] = wtot;
         __syncthreads();
-        unsigned base = sh.running, all = 0;
+        unsigned base = running, all = 0;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            const unsigned t = sh.wave_tot[buf][w];
+        for (int w = 0; w < STREAM_WAVES; ++w) {
+            const unsigned t = wave_tot[buf][w];
             if (w < wave) base += t;
             all += t;
         }
         if (a.block_counts) {
-            constexpr int BPI = ITEM / SEL_BLOCK;              // selection blocks per item
-            constexpr int WPB = NW / BPI;                      // waves per block
+            constexpr int BPI = STREAM_ITEM / SEL_BLOCK;              // selection blocks per item
+            constexpr int WPB = STREAM_WAVES / BPI;                      // waves per block
             if (tid < BPI) {
                 unsigned c = 0;
-                for (int w = 0; w < WPB; ++w) c += sh.wave_tot[buf][tid * WPB + w];
+                for (int w = 0; w < WPB; ++w) c += wave_tot[buf][tid * WPB + w];
                 const int blk = i * BPI + tid;
                 if (blk < a.blocks_per_row) a.block_counts[(int64_t)r * a.blocks_per_row + blk] = (int32_t)c;
             }
         }
         if (out) {
             unsigned o = base + before;
-            const int p = (i * THREADS + tid) * 4;
+            const int p = (i * STREAM_THREADS + tid) * 4;
             auto emit = [&](bool f, int pos) {
                 if (f) {
                     if (o < (unsigned)a.idx_capacity) {
@@ -530,109 +456,22 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
             emit(f0, p); emit(f1, p + 1); emit(f2, p + 2); emit(f3, p + 3);
         }
         __syncthreads();                                       // everyone has read `running`
-        if (tid == 0) sh.running = base + all;                 // wave 0: base == running
+        if (tid == 0) running = base + all;                 // wave 0: base == running
         ++it;
     };
-    if (RESIDENT) {
-        // All items at once.  First only counts: every wave's kept entries per item (four compares and four scalar
-        // bit counts; the keep flags are not stored anywhere - comparing again later is cheaper than packing
-        // them away and unpacking them), then one workgroup-wide exclusive prefix over the (item, wave) counts,
-        // which gives every wave its place in the list.
-        constexpr int NE = NV4 * NW;
-        static_assert(NE <= 256 && NE <= THREADS && NV4 <= 64, "prefix table too small");
-        unsigned my_tot = 0;                                   // lane i: this wave's kept entries of item i
-#pragma unroll
-        for (int i = 0; i < NV4; ++i) {
-            const uint4 u = data[i];
-            const bool f0 = u.x >= tau_bits, f1 = u.y >= tau_bits, f2 = u.z >= tau_bits, f3 = u.w >= tau_bits;
-            const unsigned wtot = __popcll(__ballot(f0)) + __popcll(__ballot(f1)) + __popcll(__ballot(f2)) + __popcll(__ballot(f3));
-            if (lane == i) my_tot = wtot;
-            if (mask_out) emit_mask(i, (f0 ? 1u : 0u) | (f1 ? 2u : 0u) | (f2 ? 4u : 0u) | (f3 ? 8u : 0u));
-        }
-        if (lane < NV4) sh.wt[lane * NW + wave] = my_tot;
-        __syncthreads();
-        if (a.block_counts) {
-            constexpr int BPI = ITEM / SEL_BLOCK;              // selection blocks per item
-            constexpr int WPB = NW / BPI;                      // waves per block
-            for (int blk = tid; blk < NV4 * BPI && blk < a.blocks_per_row; blk += THREADS) {
-                unsigned c = 0;
-                for (int w = 0; w < WPB; ++w) c += sh.wt[(blk / BPI) * NW + (blk % BPI) * WPB + w];
-                a.block_counts[(int64_t)r * a.blocks_per_row + blk] = (int32_t)c;
-            }
-        }
-        if (out) {
-            const unsigned v = tid < NE ? sh.wt[tid] : 0u, inc = (unsigned)wave_inclusive_sum((int)v);
-            if (lane == 63) sh.wave_c[wave] = inc;
-            __syncthreads();
-            if (tid < NE) {
-                unsigned base = 0;
-                for (int w = 0; w < wave; ++w) base += sh.wave_c[w];
-                sh.wt[tid] = base + inc - v;
-            }
-            __syncthreads();
-            // The row's list is put together in LDS, in list order (a kept entry's rank is its wave's place for the
-            // item, plus the kept entries of the lanes before, plus the kept ones before it in its own lane), and goes
-            // out with contiguous stores over the whole workgroup: whole cache lines, whatever the kept counts of the
-            // single waves are.  Lists longer than the buffer take several rounds.
-            constexpr unsigned CH = stage_entries(THREADS);
-            int32_t *stage = reinterpret_cast<int32_t *>(select_dyn);
-            const unsigned cap = kept < (unsigned)a.idx_capacity ? kept : (unsigned)a.idx_capacity;
-            const unsigned my_base = lane < NV4 ? sh.wt[lane * NW + wave] : 0u;    // lane i: this wave's place for item i
-            for (unsigned c0 = 0; c0 < cap; c0 += CH) {
-                if (c0) __syncthreads();                               // the round before has been read out
-                const bool one_round = kept <= CH;                     // (uniform) every rank of the row fits the buffer,
-                                                                       // also those beyond a smaller capacity
-#pragma unroll
-                for (int i = 0; i < NV4; ++i) {
-                    const uint4 u = data[i];
-                    const bool f0 = u.x >= tau_bits, f1 = u.y >= tau_bits, f2 = u.z >= tau_bits, f3 = u.w >= tau_bits;
-                    const unsigned long long m0 = __ballot(f0), m1 = __ballot(f1), m2 = __ballot(f2), m3 = __ballot(f3);
-                    if ((m0 | m1 | m2 | m3) == 0ull) continue;         // (uniform over the wave)
-                    const unsigned before = __builtin_amdgcn_mbcnt_hi((uint32_t)(m3 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m3,
-                                            __builtin_amdgcn_mbcnt_hi((uint32_t)(m2 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m2,
-                                            __builtin_amdgcn_mbcnt_hi((uint32_t)(m1 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m1,
-                                            __builtin_amdgcn_mbcnt_hi((uint32_t)(m0 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m0, 0u))))))));
-                    const unsigned o0 = (unsigned)__builtin_amdgcn_readlane((int)my_base, i) - c0 + before;   // (wraps around below c0)
-                    const unsigned o1 = o0 + (f0 ? 1u : 0u), o2 = o1 + (f1 ? 1u : 0u), o3 = o2 + (f2 ? 1u : 0u);
-                    const int p = (i * THREADS + tid) * 4;
-                    if (one_round) {
-                        if (f0) stage[o0] = p;
-                        if (f1) stage[o1] = p + 1;
-                        if (f2) stage[o2] = p + 2;
-                        if (f3) stage[o3] = p + 3;
-                    } else {
-                        if (f0 && o0 < CH) stage[o0] = p;
-                        if (f1 && o1 < CH) stage[o1] = p + 1;
-                        if (f2 && o2 < CH) stage[o2] = p + 2;
-                        if (f3 && o3 < CH) stage[o3] = p + 3;
-                    }
-                }
-                __syncthreads();
-                const unsigned nround = (cap - c0) < CH ? (cap - c0) : CH;
-                for (unsigned k = tid; k < nround; k += THREADS) {
-                    int32_t val = stage[k];
-                    if (ptab) val = (ptab[val >> a.page_shift] << a.page_shift) | (val & ((1 << a.page_shift) - 1));
-                    out[c0 + k] = val;
-                }
-            }
-        }
-    } else {
-        for_items(compact_item);
-    }
+    for_items(compact_item);
     if (a.block_counts) {                                      // blocks past the row's end
-        constexpr int BPI = ITEM / SEL_BLOCK;
-        for (int k = (RESIDENT ? NV4 : n_items) * BPI + tid; k < a.blocks_per_row; k += THREADS)
+        constexpr int BPI = STREAM_ITEM / SEL_BLOCK;
+        for (int k = n_items * BPI + tid; k < a.blocks_per_row; k += STREAM_THREADS)
             a.block_counts[(int64_t)r * a.blocks_per_row + k] = 0;
     }
     if (mask_out)                                              // words past the last item
-        for (int k = (RESIDENT ? NV4 : n_items) * (ITEM / 32) + tid; k < mask_words; k += THREADS) mask_out[k] = 0u;
+        for (int k = n_items * (STREAM_ITEM / 32) + tid; k < mask_words; k += STREAM_THREADS) mask_out[k] = 0u;
 }
 
-template <int THREADS, int NV4, bool RESIDENT, bool CHUNKED = false>
-specattn_status launch_one(const SelectLaunch &a, hipStream_t stream)
+template <int THREADS, int NV4, bool CHUNKED = false> specattn_status launch_one(const SelectLaunch &a, hipStream_t stream)
 {
-    const int rows = a.B * a.H_kv;
-    hipLaunchKernelGGL((topp_select_kernel<THREADS, NV4, RESIDENT, CHUNKED>), dim3(rows), dim3(THREADS), select_lds(THREADS), stream, a);
+    hipLaunchKernelGGL((topp_select_kernel<THREADS, NV4, CHUNKED>), dim3(a.B * a.H_kv), dim3(THREADS), select_lds(THREADS), stream, a);
     return check_launch("topp_select_kernel");
 }
 
@@ -1147,13 +986,12 @@ bool select_multi_wg_preferred(int rows, int n)
 {
     // One workgroup per row leaves most of the chip idle when there are few rows, takes a CU to itself beyond 32768 entries
     // and streams the row in every pass beyond 65536; the split costs two more launches.  Measured, one workgroup per row /
-    // split, us: 32 rows of 28001 17.8 / 19.4, of 32768 19.6 / 19.4, of 40000 27.1 / 19.9; 128 of 40000 28.4 / 30.8, of 50001
-    // 32.9 / 32.3, of 65536 42.4 / 32.9; 256 (a CU for every row) of 65536 49.7 / 51.9, of 131072 104 / 86; 512 of 50001
-    // 73.3 / 74.8, of 65536 96.4 / 85.2; 1024 of 65536 180 / 171, 1536 of 65536 264 / 300.
+    // split, us: 8 rows of 33000 16.8 / 18.6, of 40000 21.2 / 18.5, of 65536 24.7 / 20.0; 32 of 33000 18.8 / 19.2, of 40000 22.1 / 19.2, of
+    // 65536 28.1 / 20.9; 64 of 33000 19.6 / 23.5, of 40000 24.0 / 23.3, of 65536 29.5 / 25.1; 96 of 60000 29.8 / 44.1; 128 of 65536 30.9 /
+    // 34.0; 512 of 65536 69.5 / 92.4; 256 of 131072 104 / 86.
     const int cus = cu_count();
-    if (n <= 32768 || rows > 4 * cus) return false;
-    if (n > 65536 || rows <= cus / 4) return true;
-    return rows <= cus / 2 ? n >= 50000 : rows > cus && n >= 60000;
+    if (n <= SELECT_RESIDENT) return n >= 36864 && rows <= cus / 4;
+    return rows <= 4 * cus;
 }
 
 size_t select_multi_wg_bytes(int rows, int n)
@@ -1218,40 +1056,39 @@ bool select_takes_chunks(int rows, int n_tokens, int n_chunks)
 specattn_status launch_select_chunks(const SelectLaunch &a, hipStream_t stream)
 {
     const bool few = a.B * a.H_kv <= 2 * cu_count();
-    if (a.n_max > 2048) return few ? launch_one<512, 2, true, true>(a, stream) : launch_one<256, 4, true, true>(a, stream);
-    if (few) return launch_one<512, 1, true, true>(a, stream);
-    return a.n_max <= 1024 ? launch_one<256, 1, true, true>(a, stream) : launch_one<256, 2, true, true>(a, stream);
+    if (a.n_max > 2048) return few ? launch_one<512, 2, true>(a, stream) : launch_one<256, 4, true>(a, stream);
+    if (few) return launch_one<512, 1, true>(a, stream);
+    return a.n_max <= 1024 ? launch_one<256, 1, true>(a, stream) : launch_one<256, 2, true>(a, stream);
 }
 
 specattn_status launch_select(const SelectLaunch &a, hipStream_t stream)
 {
     const int n = a.n_max, rows = a.B * a.H_kv, cus = cu_count();
-    // Few rows: as many threads as shorten a row's passes (512 up to 4096 entries, 1024 beyond while every row has a CU of its
+    // Few rows: as many threads as shorten a row's passes (512 up to 8192 entries, 1024 beyond while every row has a CU of its
     // own).  Many rows: the shape that fits most rows on the chip at once, so that one row's load overlaps another row's
-    // passes (workgroups of 256 / 512 / 1024 threads: four / three, two from 8 vectors a thread on / one to a CU).
+    // passes (workgroups of 256 / 512 / 1024 threads: four to six / two or three / one to a CU).
     // Block counts are per 1024 positions, so every variant has THREADS*4 a multiple of 1024.
     // Measured, us (256 CUs; shape: time):
-    //   2044 x 64 rows      512x1 6.3, 256x2 6.9;        2044 x 1024   512x1 9.6, 256x2 9.2
-    //   4096 x 128          512x2 7.3, 256x4 8.8;        4096 x 1024   512x2 15.0, 256x4 12.2
-    //   8192 x 128          1024x2 8.8, 512x4 9.2;       8192 x 512    512x4 12.0, 256x8 14.1, 1024x2 16.9
-    //   6001 x 1024         256x8 16.3, 512x4 17.7 (one round of four to a CU);  8192 x 768  512x4 14.3, 256x8 16.3
-    //   16384 x 256         1024x4 12.0, 512x8 13.8;     13001 x 384   1024x4 19.6, 512x8 16.1, 256x16 22.3
-    //   13001 x 2048        512x8 54.3, 256x16 50.0;     16384 x 2048  512x8 60.5, 256x16 64.7 (no vector of 512x8 idle)
-    //   32768 x 256         1024x8 21.6, 512x16 27.0;    32768 x 512   1024x8 43.2, 512x16 36.9
-    if (n <= 1024) return launch_one<256, 1, true>(a, stream);
-    if (n <= 2048) return rows <= 2 * cus ? launch_one<512, 1, true>(a, stream) : launch_one<256, 2, true>(a, stream);
-    if (n <= 4096) return rows <= 2 * cus ? launch_one<512, 2, true>(a, stream) : launch_one<256, 4, true>(a, stream);
-    if (n <= 8192) {
-        if (rows <= cus) return launch_one<1024, 2, true>(a, stream);
-        return rows > 3 * cus && rows <= 4 * cus ? launch_one<256, 8, true>(a, stream) : launch_one<512, 4, true>(a, stream);
-    }
+    //   2044 x 64 rows      512x1 5.9, 256x2 6.4;        2044 x 1024   256x2 8.2, 512x1 9.1
+    //   4096 x 512          512x2 8.5, 256x4 8.7;        4096 x 1024   256x4 11.1, 512x2 13.7
+    //   8192 x 128          512x4 8.3, 1024x2 8.6;       8192 x 512    512x4 11.5, 256x8 11.8
+    //   8192 x 768          256x8 13.7, 512x4 13.9;      8192 x 1024   256x8 15.8, 512x4 18.1
+    //   13001 x 64          1024x4 10.4, 512x8 10.9;     16384 x 256   1024x4 12.7, 512x8 12.8
+    //   16384 x 512         512x8 17.4, 256x16 19.9;     13001 x 1024  256x16 25.1, 512x8 28.6
+    //   16384 x 2048        256x16 41.1, 512x8 52.4
+    //   32768 x 256         1024x8 19.6, 512x16 21.7;    32768 x 384   512x16 27.3, 1024x8 33.2
+    if (n <= 1024) return launch_one<256, 1>(a, stream);
+    if (n <= 2048) return rows <= 2 * cus ? launch_one<512, 1>(a, stream) : launch_one<256, 2>(a, stream);
+    if (n <= 4096) return rows <= 2 * cus ? launch_one<512, 2>(a, stream) : launch_one<256, 4>(a, stream);
+    if (n <= 8192) return rows <= 2 * cus ? launch_one<512, 4>(a, stream) : launch_one<256, 8>(a, stream);
     if (n <= 16384) {
-        if (rows <= cus) return launch_one<1024, 4, true>(a, stream);
-        return rows <= 2 * cus || n > 15360 ? launch_one<512, 8, true>(a, stream) : launch_one<256, 16, true>(a, stream);
+        if (rows <= cus) return launch_one<1024, 4>(a, stream);
+        return rows <= 2 * cus ? launch_one<512, 8>(a, stream) : launch_one<256, 16>(a, stream);
     }
-    if (n <= 32768) return rows > cus ? launch_one<512, 16, true>(a, stream) : launch_one<1024, 8, true>(a, stream);
-    if (n <= SELECT_RESIDENT) return launch_one<1024, 16, true>(a, stream);
-    return launch_one<1024, 1, false>(a, stream);
+    if (n <= 32768) return rows > cus ? launch_one<512, 16>(a, stream) : launch_one<1024, 8>(a, stream);
+    if (n <= SELECT_RESIDENT) return launch_one<1024, 16>(a, stream);
+    hipLaunchKernelGGL(topp_select_stream_kernel, dim3(rows), dim3(STREAM_THREADS), 0, stream, a);
+    return check_launch("topp_select_stream_kernel");
 }
 
 }  // namespace specattn

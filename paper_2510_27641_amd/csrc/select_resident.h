@@ -1,0 +1,578 @@
+// Selection of rows that one workgroup holds in its registers (up to THREADS * 4 * NV4 entries; read once from memory).  Part of
+// select.hip, which has the method.
+//
+// The passes over the registers are bound by instruction issue and by the LDS unit's 64-bit atomics, and short rows by the chain of
+// barriers and locate steps, so the digits are chosen for few and cheap passes: the first one covers the 32 octaves below the row's
+// largest entry with 64 bins each (2048 bins, and a bin per octave for what lies below them), so that the boundary bin holds three
+// entries of a thousand instead of thirty.  The second pass, over ten more bits, then finds few entries and nearly always leaves a bin
+// with a single one, which is tau*.  With eight bins per octave over all exponents, as the split selection has them, every wave met
+// entries of the boundary bin in nearly every vector of the second pass, and every other row took a third one.
+// Compaction works on words of 32 kept bits, which costs two instructions per entry, instead of on ranks of single entries.
+// Rows x entries with that and eight bins per octave / now, us: 1024 x 32768 60.0 / 48.3 (23 vector instructions per entry and lane
+// before the last step, 38 then; the LDS unit is busy 45 % of the time, the vector ALU 50 %), 2048 x 32768 107.8 / 84.0, 512 x 65536 98 / 69.5,
+// 2048 x 16384 60.2 / 41.1, 128 x 4096 7.3 / 6.3, 8 x 8192 7.9 / 7.2, 8 x 1024 5.6 / 5.0.
+#pragma once
+
+// Bins of the first pass: FINE of them from the lowest exponent of the window up, then one per exponent field (COARSE) for the entries
+// below the window.  A bin's entries share their exponent, so its mass is an exact integer sum.
+constexpr int FINE_OCTAVES = 32, FINE_SHIFT = 17, FINE = FINE_OCTAVES << (23 - FINE_SHIFT), COARSE = 256;
+constexpr int DIGIT = 10, DIGIT_BINS = 1 << DIGIT;               // later passes
+constexpr int RES_HIST = FINE + COARSE + DIGIT_BINS;
+
+// Counters here hold the count and the sum of the 23 fraction bits; the hidden bits are put back where a mass is read.
+__device__ __forceinline__ unsigned long long fraction_entry(uint32_t u) { return CNT_ONE | (u & 0x7fffffu); }
+__device__ __forceinline__ double fraction_mass(unsigned long long packed, int e_field)
+{
+    const unsigned long long hidden = e_field > 0 ? (packed >> CNT_SHIFT) << 23 : 0ull;
+    const double s = (double)(long long)((packed & SIG_MASK) + hidden);
+    return s * __hiloint2double((1023 + (e_field > 0 ? e_field : 1) - 150) << 20, 0);
+}
+
+struct Place {                   // outcome of a locate step
+    double target, m_above;      // p * (row sum); mass above the boundary bin
+    unsigned long long packed;   // the boundary bin's counter
+    unsigned c_above;            // entries above it
+    uint32_t lo;                 // its lowest bit pattern, and how many bits it leaves open; bits < 0: no mass at all
+    int bits;
+};
+
+struct ResidentShared {
+    Place place;
+    uint32_t top[16];            // largest entry of every wave; all ones: an invalid one
+    unsigned wave_sum[16];
+};
+
+// Sum of BPL counters of a lane's row of bins.  Rows start 128 or 256 bytes apart: every lane takes them in an order of its own, so
+// that the lanes of a read fall on different banks.
+template <int BPL> __device__ __forceinline__ unsigned long long row_of_bins(const unsigned long long *row, int swizzle)
+{
+    unsigned long long sum = 0ull;
+#pragma unroll
+    for (int j0 = 0; j0 < BPL; j0 += 8) {
+        unsigned long long v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = row[(j0 + j) ^ swizzle];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) sum += v[j];
+        __builtin_amdgcn_sched_barrier(0);                 // (not all loads at once: the caller's registers hold the row)
+    }
+    return sum;
+}
+
+// The bin among 64 or fewer, one per lane from the highest down, whose mass takes the sum above it to the goal (the last non-empty
+// one if rounding leaves none).  `counter` is zero for lanes that hold none.
+__device__ __forceinline__ int pick_bin(unsigned long long counter, int e_field, double goal, double &m_above, unsigned &c_above, unsigned long long &packed)
+{
+    const unsigned c = (unsigned)(counter >> CNT_SHIFT);
+    double run = c ? fraction_mass(counter, e_field) : 0.0;
+    unsigned runc = c;
+    wave_prefix(run, runc);
+    const unsigned long long filled = __ballot(c > 0), ok = __ballot(c > 0 && m_above + run >= goal);
+    const int pick = ok ? (int)__ffsll((long long)ok) - 1 : 63 - __clzll((long long)filled);
+    if (pick) { m_above += read_lane(run, pick - 1); c_above += (unsigned)__builtin_amdgcn_readlane((int)runc, pick - 1); }
+    packed = (unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(counter >> 32), pick) << 32 |
+             (unsigned)__builtin_amdgcn_readlane((int)(uint32_t)counter, pick);
+    return pick;
+}
+
+// Decision of the first pass, by the first wave alone.  Its lanes own half an octave of the window each, lane 0 the highest, and four
+// of the octaves below.  top_p = 1 takes the lowest non-empty bin, whatever the rounding of the sums above it; octaves below the window
+// count as empty there from the one down from which on the entries all together add less than one unit in the last place of
+// the row's total (a non-empty half octave of the window always adds more: it lies within 2^-32 of the largest of at most 65536 entries).
+__device__ __forceinline__ void locate_first(const unsigned long long *fine, int e_low, float top_p, Place &out)
+{
+    const int lane = threadIdx.x;
+    const unsigned long long *coarse = fine + FINE;
+    unsigned long long low4[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) low4[g] = coarse[(63 - lane) * 4 + g];
+    const unsigned long long sum = row_of_bins<FINE / 64>(fine + (63 - lane) * (FINE / 64), lane & 31);
+    const double lm = fraction_mass(sum, e_low + ((63 - lane) >> 1));
+    const unsigned lc = (unsigned)(sum >> CNT_SHIFT);
+    double incl = lm, incl_low = 0.0, lm_low = 0.0;
+    unsigned inclc = lc, inclc_low = 0, lc_low = 0;
+    wave_prefix(incl, inclc);
+    double total = read_lane(incl, 63);
+    const double total_fine = total;
+    int cut = -1;                                              // exponent fields below the window up to this one count as empty
+    const bool below = __any((low4[0] | low4[1] | low4[2] | low4[3]) != 0ull);
+    if (below) {                                               // (uniform) rare
+        auto add_up = [&]() {
+            lm_low = 0.0;
+            lc_low = 0;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int e = (63 - lane) * 4 + g;
+                if (e > cut) { lm_low += fraction_mass(low4[g], e); lc_low += (unsigned)(low4[g] >> CNT_SHIFT); }
+            }
+            incl_low = lm_low;
+            inclc_low = lc_low;
+            wave_prefix(incl_low, inclc_low);
+        };
+        add_up();
+        total += read_lane(incl_low, 63);
+        if (!(top_p < 1.0f) && total > 0.0) {
+            // sums from the bottom up: the lanes in reverse order, then each lane's octaves
+            double tail = __shfl(lm_low, 63 - lane, 64);
+            unsigned none = 0;
+            wave_prefix(tail, none);
+            tail = __shfl(dpp_double<0x138, 0xf>(tail), 63 - lane, 64);
+            const double ulp = __hiloint2double((((__double2hiint(total) >> 20) & 0x7ff) - 52) << 20, 0);
+            int fields = 0;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                tail += fraction_mass(low4[g], (63 - lane) * 4 + g);
+                fields += __popcll(__ballot(tail < ulp));
+            }
+            cut = fields - 1;
+            add_up();
+        }
+    }
+    out.target = (double)top_p * total;                        // Algorithm 2: M_target = p * sum a
+    out.bits = -1;
+    out.packed = 0ull;
+    out.c_above = 0;
+    out.m_above = 0.0;
+    out.lo = 0u;
+    if (!(total > 0.0)) return;
+    const double goal = top_p < 1.0f ? out.target : INFINITY;
+    // mass and count of the lanes before this one (wave_shr:1)
+    const double before = dpp_double<0x138, 0xf>(incl);
+    const unsigned beforec = (unsigned)dpp_int<0x138, 0xf>((int)inclc);
+    // Masses are non-negative, so the running sum never decreases: the first lane whose sum reaches the target holds the boundary.
+    const unsigned long long some = __ballot(lc > 0), holds = __ballot(lc > 0 && before + lm >= goal);
+    unsigned long long some_low = 0ull;
+    if (below && !holds) some_low = __ballot(lc_low > 0);
+    if (some_low) {
+        const double before_low = total_fine + dpp_double<0x138, 0xf>(incl_low);
+        const unsigned beforec_low = (unsigned)__builtin_amdgcn_readlane((int)inclc, 63) + (unsigned)dpp_int<0x138, 0xf>((int)inclc_low);
+        const unsigned long long holds_low = __ballot(lc_low > 0 && before_low + lm_low >= goal);
+        const int at = holds_low ? (int)__ffsll((long long)holds_low) - 1 : 63 - __clzll((long long)some_low);
+        out.m_above = read_lane(before_low, at);
+        out.c_above = (unsigned)__builtin_amdgcn_readlane((int)beforec_low, at);
+        const int e = (63 - at) * 4 + 3 - lane;                // lane 0 looks at the lane's highest octave
+        out.lo = (uint32_t)((63 - at) * 4 + 3 - pick_bin(lane < 4 && e > cut ? coarse[e] : 0ull, e, goal, out.m_above, out.c_above, out.packed)) << 23;
+        out.bits = 23;
+        return;
+    }
+    const int at = holds ? (int)__ffsll((long long)holds) - 1 : 63 - __clzll((long long)some);
+    out.m_above = read_lane(before, at);
+    out.c_above = (unsigned)__builtin_amdgcn_readlane((int)beforec, at);
+    const int high = (63 - at) * (FINE / 64) + FINE / 64 - 1;  // the boundary lane's highest bin
+    const int pick = pick_bin(lane < FINE / 64 ? fine[high - lane] : 0ull, e_low + (high >> (23 - FINE_SHIFT)), goal, out.m_above, out.c_above, out.packed);
+    out.lo = ((uint32_t)e_low << 23) + ((uint32_t)(high - pick) << FINE_SHIFT);
+    out.bits = FINE_SHIFT;
+}
+
+// Decision of a later pass: DIGIT_BINS bins of 2^shift bit patterns each from `place.lo` up.
+__device__ __forceinline__ void locate_next(const unsigned long long *hist, int shift, float top_p, Place &place)
+{
+    constexpr int BPL = DIGIT_BINS / 64;
+    const int lane = threadIdx.x, e_field = (int)(place.lo >> 23);
+    const double goal = top_p < 1.0f ? place.target : INFINITY;
+    const unsigned long long sum = row_of_bins<BPL>(hist + (63 - lane) * BPL, (lane >> 1) & (BPL - 1));
+    const double lm = fraction_mass(sum, e_field);
+    const unsigned lc = (unsigned)(sum >> CNT_SHIFT);
+    double incl = lm;
+    unsigned inclc = lc;
+    wave_prefix(incl, inclc);
+    const double before = dpp_double<0x138, 0xf>(incl);
+    const unsigned beforec = (unsigned)dpp_int<0x138, 0xf>((int)inclc);
+    const unsigned long long some = __ballot(lc > 0), holds = __ballot(lc > 0 && place.m_above + (before + lm) >= goal);
+    const int at = holds ? (int)__ffsll((long long)holds) - 1 : 63 - __clzll((long long)some);
+    place.m_above += read_lane(before, at);
+    place.c_above += (unsigned)__builtin_amdgcn_readlane((int)beforec, at);
+    const int high = (63 - at) * BPL + BPL - 1;
+    const int pick = pick_bin(lane < BPL ? hist[high - lane] : 0ull, e_field, goal, place.m_above, place.c_above, place.packed);
+    place.lo += (uint32_t)(high - pick) << shift;
+    place.bits = shift;
+}
+
+__device__ __forceinline__ uint32_t median(uint32_t a, uint32_t b, uint32_t c)
+{
+    uint32_t m;
+    asm("v_med3_u32 %0, %1, %2, %3" : "=v"(m) : "v"(a), "v"(b), "v"(c));
+    return m;
+}
+
+// Largest v of the wave, in every lane.
+__device__ __forceinline__ uint32_t wave_max(uint32_t v)
+{
+    auto step = [&](uint32_t w) { v = v > w ? v : w; };
+    step((uint32_t)dpp_int<0x111, 0xf>((int)v));    // row_shr:1
+    step((uint32_t)dpp_int<0x112, 0xf>((int)v));    // row_shr:2
+    step((uint32_t)dpp_int<0x114, 0xf>((int)v));    // row_shr:4
+    step((uint32_t)dpp_int<0x118, 0xf>((int)v));    // row_shr:8
+    step((uint32_t)dpp_int<0x142, 0xa>((int)v));    // row_bcast:15 into rows 1 and 3
+    step((uint32_t)dpp_int<0x143, 0xc>((int)v));    // row_bcast:31 into rows 2 and 3
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// Eight lanes with eight nibbles each: lane l receives nibble l of every lane, of lane m in nibble m.  (Three exchanges on the vector ALU.)
+__device__ __forceinline__ uint32_t transpose_nibbles(uint32_t x, int lane)
+{
+    const bool b4 = lane & 4, b2 = lane & 2, b1 = lane & 1;
+    auto merge = [](uint32_t keep, uint32_t a, uint32_t b) { return (a & keep) | (b & ~keep); };
+    int y = __builtin_amdgcn_update_dpp(0, (int)x, 0x104, 0xf, 0x5, false);      // row_shl:4 into the lanes with bit 2 clear ...
+    y = __builtin_amdgcn_update_dpp(y, (int)x, 0x114, 0xf, 0xa, false);          // ... and row_shr:4 into the others: lane ^ 4
+    x = merge(b4 ? 0xffff0000u : 0x0000ffffu, x, __builtin_amdgcn_alignbit((uint32_t)y, (uint32_t)y, 16));
+    y = __builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xf, 0xf, false);           // quad_perm [2,3,0,1]: lane ^ 2
+    x = merge(b2 ? 0xff00ff00u : 0x00ff00ffu, x, __builtin_amdgcn_alignbit((uint32_t)y, (uint32_t)y, b2 ? 8 : 24));
+    y = __builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xf, 0xf, false);           // quad_perm [1,0,3,2]: lane ^ 1
+    return merge(b1 ? 0xf0f0f0f0u : 0x0f0f0f0fu, x, __builtin_amdgcn_alignbit((uint32_t)y, (uint32_t)y, b1 ? 4 : 28));
+}
+
+// Dynamic LDS: the histograms, and afterwards in their place the buffer in which a row's list is put together in list order for
+// contiguous stores (smaller for the small workgroups, several of which share a CU; longer lists take several rounds).
+constexpr unsigned stage_entries(int threads) { return threads <= 256 ? 4096u : 8192u; }
+constexpr unsigned select_lds(int threads)
+{
+    return stage_entries(threads) * 4 > RES_HIST * 8 ? stage_entries(threads) * 4 : RES_HIST * 8;
+}
+
+// CHUNKED: a.probs are rows of positions; the workgroup adds the chunks up itself, into the LDS that the histograms take over.
+template <int THREADS, int NV4, bool CHUNKED = false>
+__global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
+{
+    constexpr int NW = THREADS / 64;
+    constexpr int ITEM = THREADS * 4;                 // positions per item (one uint4 per thread)
+    constexpr bool WORDS = NV4 >= 8;                  // compaction by words of 32 positions instead of item by item
+    constexpr int TABLE = WORDS ? ITEM / 32 * NV4 : (NV4 * NW + 63) / 64 * 64;
+    __shared__ ResidentShared sh;
+    __shared__ __align__(16) unsigned table[TABLE + 4];   // kept entries per word, or per (item, wave), then their exclusive prefix
+    extern __shared__ __align__(16) unsigned long long select_dyn[];
+    unsigned long long *hist1 = select_dyn, *hist2 = select_dyn + FINE + COARSE;
+    const int r = blockIdx.x;
+    const int b = r / a.H_kv, h = r - b * a.H_kv;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int len = a.seq_lens ? a.seq_lens[b] : a.n_tokens;
+    len = len < 0 ? 0 : (len > a.n_tokens ? a.n_tokens : len);
+    const int positions = len;
+    len = (len + (1 << a.chunk_shift) - 1) >> a.chunk_shift;     // rows of chunk masses: length in chunks
+    len = len > a.n_max ? a.n_max : len;
+    const float *row = a.probs + (int64_t)b * a.stride_b + (int64_t)h * a.stride_h;
+    const int n_items = (len + ITEM - 1) / ITEM;
+
+    // Every thread issues plain 16-byte loads with nothing between them that waits for data, so all of a thread's loads are in
+    // flight together.  They need no more than the 4-byte alignment of a float: the rows of an odd length start anywhere (entry
+    // by entry, 64 rows of 13001 took 2 us longer).  An item that reaches past the row's end loads the row's last whole vector
+    // instead (in bounds) and is masked afterwards; the at most three entries behind the last whole vector are fetched once, by
+    // the thread that owns them.
+    uint4 data[NV4];
+    uint4 tailv = make_uint4(0, 0, 0, 0);
+    const int tail_p = (len & 3) ? (len & ~3) : -1;            // start of the partial vector, if any
+    if constexpr (CHUNKED) {
+        static_assert(ITEM * NV4 * 4 <= (int)select_lds(THREADS), "a row's masses wait in dynamic LDS");
+        float *mass = reinterpret_cast<float *>(select_dyn);
+        for (int c = tid; c < ITEM * NV4; c += THREADS) mass[c] = c < len ? chunk_mass(row, positions, c, a.chunk_shift) : 0.0f;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < NV4; ++i) data[i] = reinterpret_cast<const uint4 *>(mass)[i * THREADS + tid];
+        __syncthreads();
+    } else {
+        if (tail_p >= 0 && tid == (tail_p % ITEM) / 4) {
+            tailv.x = __float_as_uint(row[tail_p]);
+            if (tail_p + 1 < len) tailv.y = __float_as_uint(row[tail_p + 1]);
+            if (tail_p + 2 < len) tailv.z = __float_as_uint(row[tail_p + 2]);
+        }
+        const int last4 = (len - 4) & ~3;                      // start of the row's last whole vector
+        if (len >= 4) {
+#pragma unroll
+            for (int i = 0; i < NV4; ++i) {
+                const int p = (i * THREADS + tid) * 4;
+                // streaming load: a row is read once and should not displace anything in the caches
+                const u32x4a v = __builtin_nontemporal_load(reinterpret_cast<const u32x4a *>(row + (p < last4 ? p : last4)));
+                data[i] = make_uint4(v.x, v.y, v.z, v.w);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < NV4; ++i) data[i] = make_uint4(0, 0, 0, 0);
+        }
+    }
+    // the histograms are cleared while the loads are in flight
+    clear_hist<THREADS, RES_HIST>(hist1);
+
+    // Largest and smallest entry.  As an unsigned number a sign bit or an exponent of all ones makes an entry too large: then the thread
+    // looks closer (-0.0 is zero; negative, infinite and NaN entries make the row invalid).
+    uint32_t top = 0u, least = 0xffffffffu;
+    auto range = [&](const uint4 &u) {
+        const uint32_t x = u.x > u.y ? u.x : u.y, y = u.z > u.w ? u.z : u.w, v = u.x < u.y ? u.x : u.y, w = u.z < u.w ? u.z : u.w;
+        top = x > top ? x : top;
+        top = y > top ? y : top;
+        least = v < least ? v : least;
+        least = w < least ? w : least;
+    };
+#pragma unroll
+    for (int i = 0; i < NV4; ++i) {
+        if (!CHUNKED && (i + 1) * ITEM > len) {                // (uniform) an item that the row does not fill
+            const int p = (i * THREADS + tid) * 4;
+            if (p + 3 >= len) data[i] = p == tail_p ? tailv : make_uint4(0, 0, 0, 0);
+        }
+        if (i < n_items) range(data[i]);
+    }
+    if (top >= 0x7f800000u) {
+        bool bad = false;
+        auto clean = [&](uint32_t x) -> uint32_t {
+            x = x == 0x80000000u ? 0u : x;
+            bad = bad || x >= 0x7f800000u;
+            return x;
+        };
+        top = 0u;
+        least = 0xffffffffu;
+#pragma unroll
+        for (int i = 0; i < NV4; ++i) {
+            data[i] = make_uint4(clean(data[i].x), clean(data[i].y), clean(data[i].z), clean(data[i].w));
+            if (i < n_items) range(data[i]);
+        }
+        if (bad) top = 0xffffffffu;
+    }
+    const uint32_t wave_top = wave_max(top), wave_least = ~wave_max(~least);
+    if (lane == 0) sh.top[wave] = wave_top;
+    __syncthreads();                                           // (also: the histograms are clear)
+    uint32_t row_top = 0u;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) row_top = sh.top[w] > row_top ? sh.top[w] : row_top;
+    row_top = (uint32_t)__builtin_amdgcn_readfirstlane((int)row_top);
+    uint32_t *mask_out = a.kept_mask ? a.kept_mask + (int64_t)r * a.blocks_per_row * (SEL_BLOCK / 32) : nullptr;
+    const int mask_words = a.blocks_per_row * (SEL_BLOCK / 32);
+    if (row_top == 0u || row_top >= 0x7f800000u) {             // an invalid entry, or no mass at all
+        if (tid == 0) {
+            a.counts[r] = 0;
+            if (a.thresholds) a.thresholds[r] = 0.0f;
+            if (a.row_flags) a.row_flags[r] = SPECATTN_ROW_INVALID;
+        }
+        if (a.block_counts)
+            for (int k = tid; k < a.blocks_per_row; k += THREADS) a.block_counts[(int64_t)r * a.blocks_per_row + k] = 0;
+        if (mask_out)
+            for (int k = tid; k < mask_words; k += THREADS) mask_out[k] = 0u;
+        return;
+    }
+    auto for_entries = [&](auto &&fn) {
+#pragma unroll
+        for (int i = 0; i < NV4; ++i)
+            if (i < n_items) { fn(data[i].x); fn(data[i].y); fn(data[i].z); fn(data[i].w); }
+    };
+
+    // ---- first pass: 64 bins per octave from exponent field e_low up ----------------------------------------------
+    const int e_top = (int)(row_top >> 23), e_low = (e_top > FINE_OCTAVES ? e_top : FINE_OCTAVES) - (FINE_OCTAVES - 1);      // (>= 1)
+    {
+        unsigned long long *base = hist1 - (e_low << (23 - FINE_SHIFT));
+        if (wave_least >= (uint32_t)e_low << 23) {             // (uniform over the wave) no zeros, nothing below the window
+            for_entries([&](uint32_t x) { atomicAdd(base + (x >> FINE_SHIFT), fraction_entry(x)); });
+        } else {
+            for_entries([&](uint32_t x) {
+                if (x) atomicAdd((int)(x >> 23) >= e_low ? base + (x >> FINE_SHIFT) : hist1 + FINE + (x >> 23), fraction_entry(x));
+            });
+        }
+    }
+    __syncthreads();
+    if (wave == 0) {
+        Place p;
+        locate_first(hist1, e_low, a.top_p, p);
+        if (lane == 0) sh.place = p;
+    }
+    __syncthreads();
+    // ---- later passes, ten bits each, inside the boundary bin (zeros left out), until it holds a single entry or value ---
+    Place at = sh.place;
+    {
+        unsigned long long *cur = hist2, *used = hist1;
+        while (at.bits > 0 && (at.packed >> CNT_SHIFT) != 1) { // (uniform)
+            const int shift = at.bits > DIGIT ? at.bits - DIGIT : 0;
+            const uint32_t first = at.lo ? at.lo : 1u, width = (1u << at.bits) - (first - at.lo);
+            clear_hist<THREADS, DIGIT_BINS>(used);             // (read out; the next pass takes it)
+            uint32_t fraction = 0x7fffffu;
+            asm volatile("" : "+s"(fraction));                 // (keeps 64 masked entries from being computed ahead of the loop)
+            auto add = [&](uint32_t y) {                       // y: distance from `first`
+                const uint32_t z = y + (first - at.lo);
+                atomicAdd(&cur[z >> shift], CNT_ONE | ((at.lo + z) & fraction));
+            };
+            // A bin of few entries: no thread is likely to hold more than two of them, and those are its smallest distances, three
+            // instructions per entry and no branch (compared one by one, 64 entries took 3.1 us of 1024 rows' 24 per pair, now 1.9).
+            uint32_t y1 = 0xffffffffu, y2 = 0xffffffffu, y3 = 0xffffffffu;       // the three smallest, in order
+            bool one_by_one = (at.packed >> CNT_SHIFT) > THREADS / 2;            // (uniform)
+            if (!one_by_one) {
+                for_entries([&](uint32_t x) {
+                    const uint32_t y = x - first;
+                    y3 = median(y2, y3, y);
+                    y2 = median(y1, y2, y);
+                    y1 = y < y1 ? y : y1;
+                });
+                one_by_one = __any(y3 < width);                // (uniform over the wave)
+                if (!one_by_one) {
+                    if (y1 < width) add(y1);
+                    if (y2 < width) add(y2);
+                }
+            }
+            if (one_by_one)
+                for_entries([&](uint32_t x) { if (x - first < width) add(x - first); });
+            __syncthreads();
+            if (wave == 0) {
+                locate_next(cur, shift, a.top_p, at);
+                if (lane == 0) sh.place = at;
+            }
+            __syncthreads();
+            at = sh.place;
+            unsigned long long *const swap = cur;
+            cur = used;
+            used = swap;
+        }
+    }
+    // A boundary bin that holds a single entry pins tau*: the bin's fraction sum is that entry's fraction.
+    const uint32_t tau_bits = (uint32_t)__builtin_amdgcn_readfirstlane(
+        (int)(at.bits > 0 ? (at.lo & 0x7f800000u) | ((uint32_t)at.packed & 0x7fffffu) : at.lo));           // >= 1: zeros never enter a bin
+    const unsigned kept = at.c_above + (unsigned)(at.packed >> CNT_SHIFT);
+
+    if (tid == 0) {
+        a.counts[r] = (int32_t)kept;
+        if (a.thresholds) a.thresholds[r] = __uint_as_float(tau_bits);
+        if (a.row_flags) {
+            const double m_incl = at.m_above + fraction_mass(at.packed, (int)(at.lo >> 23));
+            const double band = 1e-6 * (at.target / (double)a.top_p);
+            uint32_t f = 0;
+            if (fabs(m_incl - at.target) <= band || fabs(at.m_above - at.target) <= band) f |= SPECATTN_ROW_NEAR_BOUNDARY;
+            if (a.indices && kept > (unsigned)a.idx_capacity) f |= SPECATTN_ROW_OVERFLOW;
+            a.row_flags[r] = f;
+        }
+    }
+    if (!a.indices && !a.block_counts && !a.kept_mask) return;
+
+    // ---- ordered compaction: {j : a_j >= tau*}, ascending (Algorithm 2, last step) -------------
+    int32_t *out = a.indices ? a.indices + (int64_t)r * a.idx_stride : nullptr;
+    const int32_t *ptab = (a.emit_physical && a.page_table) ? a.page_table + (int64_t)b * a.max_pages : nullptr;
+    // The list is put together in LDS, in list order, and goes out with contiguous stores over the whole workgroup: whole cache
+    // lines, whatever the kept counts of the single waves are.  Lists longer than the buffer take several rounds.
+    constexpr unsigned CH = stage_entries(THREADS);
+    int32_t *stage = reinterpret_cast<int32_t *>(select_dyn);
+    const unsigned cap = kept < (unsigned)a.idx_capacity ? kept : (unsigned)a.idx_capacity;
+    const bool one_round = kept <= CH;                         // (uniform) every rank of the row fits the buffer, also those beyond a smaller capacity
+    auto copy_out = [&](unsigned c0) {
+        __syncthreads();
+        const unsigned nround = (cap - c0) < CH ? (cap - c0) : CH;
+        for (unsigned k = tid; k < nround; k += THREADS) {
+            int32_t val = stage[k];
+            if (ptab) val = (ptab[val >> a.page_shift] << a.page_shift) | (val & ((1 << a.page_shift) - 1));
+            out[c0 + k] = val;
+        }
+    };
+    if constexpr (WORDS) {
+        // Long rows: one bit per entry, two instructions each, then the eight lanes that hold 32 consecutive positions of eight items
+        // exchange their nibbles, so that every lane holds whole words of the row's kept bits; what follows (counts, prefix,
+        // emission bit by bit) is work per word or per kept entry instead of per entry.
+        constexpr int GROUPS = NV4 / 8;
+        constexpr int WORDS_PER_ITEM = ITEM / 32;
+        uint32_t word[GROUPS];
+        int at_word[GROUPS];
+#pragma unroll
+        for (int gr = 0; gr < GROUPS; ++gr) {
+            uint32_t x = 0u;
+#pragma unroll
+            for (int i = 7; i >= 0; --i) {
+                const uint4 u = data[gr * 8 + i];
+                x = x + x + (u.w >= tau_bits ? 1u : 0u);
+                x = x + x + (u.z >= tau_bits ? 1u : 0u);
+                x = x + x + (u.y >= tau_bits ? 1u : 0u);
+                x = x + x + (u.x >= tau_bits ? 1u : 0u);
+            }
+            word[gr] = transpose_nibbles(x, lane);             // of item gr * 8 + lane % 8
+            at_word[gr] = (gr * 8 + (lane & 7)) * WORDS_PER_ITEM + wave * 8 + (lane >> 3);
+            table[at_word[gr]] = __popc(word[gr]);
+            if (mask_out && at_word[gr] < mask_words) mask_out[at_word[gr]] = word[gr];
+        }
+        if (mask_out)                                          // words past the last item
+            for (int k = NV4 * WORDS_PER_ITEM + tid; k < mask_words; k += THREADS) mask_out[k] = 0u;
+        if (!out && !a.block_counts) return;
+        __syncthreads();
+        unsigned c[GROUPS], sum = 0;
+#pragma unroll
+        for (int k = 0; k < GROUPS; ++k) { c[k] = table[tid * GROUPS + k]; sum += c[k]; }
+        const unsigned inc = (unsigned)wave_inclusive_sum((int)sum);
+        if (lane == 63) sh.wave_sum[wave] = inc;
+        __syncthreads();
+        unsigned base = inc - sum;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) base += w < wave ? sh.wave_sum[w] : 0u;
+#pragma unroll
+        for (int k = 0; k < GROUPS; ++k) { table[tid * GROUPS + k] = base; base += c[k]; }
+        if (tid == THREADS - 1) table[TABLE] = base;
+        __syncthreads();
+        if (a.block_counts)
+            for (int k = tid; k < a.blocks_per_row; k += THREADS) {
+                constexpr int WPB = SEL_BLOCK / 32;
+                a.block_counts[(int64_t)r * a.blocks_per_row + k] = k * WPB < TABLE ? (int32_t)(table[(k + 1) * WPB] - table[k * WPB]) : 0;
+            }
+        if (!out) return;
+        for (unsigned c0 = 0; c0 < cap; c0 += CH) {
+            if (c0) __syncthreads();                           // the round before has been read out
+#pragma unroll
+            for (int gr = 0; gr < GROUPS; ++gr) {
+                uint32_t left = word[gr];
+                unsigned rank = table[at_word[gr]] - c0;       // (wraps around below c0)
+                const int p = at_word[gr] * 32;
+                if (one_round) {
+                    for (; left; left &= left - 1, ++rank) stage[rank] = p + __ffs((int)left) - 1;
+                } else if (rank < CH || rank + 32u < CH + 32u) {
+                    for (; left; left &= left - 1, ++rank)
+                        if (rank < CH) stage[rank] = p + __ffs((int)left) - 1;
+                }
+            }
+            copy_out(c0);
+        }
+    } else {
+        // Short rows: item by item.  First only counts: every wave's kept entries per item (the compares are cheaper to repeat than to
+        // store), then every wave adds the (item, wave) counts up by itself, which gives it its place in the list.
+        static_assert(NV4 * NW <= 64, "a wave adds the counts up");
+        unsigned my_tot = 0;                                   // lane i: this wave's kept entries of item i
+        auto keep = [&](const uint4 &u, bool (&f)[4]) {
+            f[0] = u.x >= tau_bits; f[1] = u.y >= tau_bits; f[2] = u.z >= tau_bits; f[3] = u.w >= tau_bits;
+        };
+#pragma unroll
+        for (int i = 0; i < NV4; ++i) {
+            bool f[4];
+            keep(data[i], f);
+            const unsigned wtot = __popcll(__ballot(f[0])) + __popcll(__ballot(f[1])) + __popcll(__ballot(f[2])) + __popcll(__ballot(f[3]));
+            if (lane == i) my_tot = wtot;
+            if (mask_out) {                                    // word (i * THREADS + tid) / 8 covers this thread's four positions
+                const uint32_t word = mask_word((f[0] ? 1u : 0u) | (f[1] ? 2u : 0u) | (f[2] ? 4u : 0u) | (f[3] ? 8u : 0u), lane);
+                const int w = (i * THREADS + tid) >> 3;
+                if ((lane & 7) == 0 && w < mask_words) mask_out[w] = word;
+            }
+        }
+        if (mask_out)                                          // words past the last item
+            for (int k = NV4 * (ITEM / 32) + tid; k < mask_words; k += THREADS) mask_out[k] = 0u;
+        if (lane < NV4) table[lane * NW + wave] = my_tot;
+        __syncthreads();
+        if (a.block_counts) {
+            constexpr int BPI = ITEM / SEL_BLOCK;              // selection blocks per item
+            constexpr int WPB = NW / BPI;                      // waves per block
+            for (int blk = tid; blk < a.blocks_per_row; blk += THREADS) {
+                unsigned c = 0;
+                if (blk < NV4 * BPI)
+                    for (int w = 0; w < WPB; ++w) c += table[(blk / BPI) * NW + (blk % BPI) * WPB + w];
+                a.block_counts[(int64_t)r * a.blocks_per_row + blk] = (int32_t)c;
+            }
+        }
+        if (!out) return;
+        const unsigned v = lane < NV4 * NW ? table[lane] : 0u, excl = (unsigned)wave_inclusive_sum((int)v) - v;
+        for (unsigned c0 = 0; c0 < cap; c0 += CH) {
+            if (c0) __syncthreads();                           // the round before has been read out
+#pragma unroll
+            for (int i = 0; i < NV4; ++i) {
+                bool f[4];
+                keep(data[i], f);
+                const unsigned long long m0 = __ballot(f[0]), m1 = __ballot(f[1]), m2 = __ballot(f[2]), m3 = __ballot(f[3]);
+                const unsigned before = __builtin_amdgcn_mbcnt_hi((uint32_t)(m3 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m3,
+                                        __builtin_amdgcn_mbcnt_hi((uint32_t)(m2 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m2,
+                                        __builtin_amdgcn_mbcnt_hi((uint32_t)(m1 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m1,
+                                        __builtin_amdgcn_mbcnt_hi((uint32_t)(m0 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m0, 0u))))))));
+                unsigned o = (unsigned)__builtin_amdgcn_readlane((int)excl, i * NW + __builtin_amdgcn_readfirstlane(wave)) - c0 + before;      // (wraps around below c0)
+                const int p = (i * THREADS + tid) * 4;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    if (f[k] && (one_round || o < CH)) stage[o] = p + k;
+                    o += f[k] ? 1u : 0u;
+                }
+            }
+            copy_out(c0);
+        }
+    }
+}

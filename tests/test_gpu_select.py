@@ -363,3 +363,39 @@ def test_split_path_in_the_least_workspace(rows, n):
     sa.specattn_topp_select(args, ws[:least // 256 * 256 - 256])             # (not split)
     torch.cuda.synchronize()
     assert np.array_equal(counts.cpu().numpy(), one["counts"])
+
+
+# every workgroup shape at its edges: (rows, entries) as the launch chooses 256 / 512 / 1024 threads with 1 .. 16 vectors each
+SHAPES = [(9, 3), (9, 1024), (9, 1025), (520, 2047), (9, 4096), (515, 4093), (9, 4097), (515, 8192), (9, 8193), (257, 16384),
+          (515, 8201), (515, 16383), (9, 16385), (257, 32767), (9, 32769), (9, 36863), (70, 40001), (66, 65536)]
+
+
+@pytest.mark.parametrize("rows,n", SHAPES)
+def test_passes_over_rows_of_every_kind(rows, n):
+    """Rows that leave the first pass's window (entries far below the largest one, at and beyond the boundary), whose boundary bin
+    holds one, a few, many or all of the entries, or ties alone, subnormal and tiny rows, and zeros."""
+    rng = np.random.default_rng(rows + n)
+    z = rng.standard_normal((9, n))
+    kinds = np.empty((9, n))
+    kinds[0] = np.exp(2.0 * z[0])                              # the ordinary kind
+    kinds[1] = np.where(rng.random(n) < 0.3, 0.0, np.exp(12.0 * z[1]))        # over 32 octaves and more, zeros
+    kinds[2] = 2.0 ** -rng.integers(0, 60, n)                  # one value per octave, half of them below the window
+    kinds[3] = 1.0 + rng.random(n) * 2.0 ** -7                 # one bin of the first pass
+    kinds[4] = 1.0 + np.floor(rng.random(n) * 3) * 2.0 ** -20  # ... of three values
+    kinds[5] = 0.75                                            # ties alone
+    kinds[6] = np.exp(2.0 * z[6]) * 2.0 ** -135                # subnormal
+    kinds[7] = np.exp(3.0 * z[7]) * 2.0 ** -100                # the window ends at the smallest normal number
+    kinds[8] = np.where(np.arange(n) < max(1, n // 2), 1.0, 2.0 ** -40)       # the small half adds nothing to fp32, something to fp64
+    probs = np.repeat(kinds.astype(np.float32), -(-rows // 9), axis=0)[:rows].reshape(1, rows, n)
+    for p in (0.9, 0.2, 0.9999999):
+        sub = probs if p == 0.9 else probs[:, ::max(1, rows // 9)]
+        _check(np.ascontiguousarray(sub), p, allow_flagged_mismatch=True)
+    got = gpu_select(np.ascontiguousarray(probs[:, ::max(1, rows // 9)]), 1.0)
+    for r, row in enumerate(probs[0, ::max(1, rows // 9)].astype(np.float64)):
+        # all but the smallest octaves that together add less than a unit in the last place of the sum
+        e = np.frexp(np.maximum(row, 2.0 ** -127))[1]
+        tail = np.array([row[(e <= x)].sum() for x in range(-126, 129)])
+        cut = np.flatnonzero(tail < np.spacing(np.float64(row.sum())))
+        least = -126 + cut[-1] if cut.size else -127
+        keep = np.flatnonzero((row > 0) & (e > least))
+        assert got["counts"][r] == keep.size and np.array_equal(got["indices"][r, :keep.size], keep), r
