@@ -254,18 +254,30 @@ template <int CTRL, int ROW_MASK> __device__ __forceinline__ void scan_step(Best
     if (ix != 0x7fffffff && !(b.val > left)) { b.val = left; b.idx = ix; }
 }
 
-// One thread per draft layer.  A column is a prefix maximum inside every wave on the vector ALU and, with more than 64
-// draft layers, one over the wave totals through LDS (double-buffered: one barrier per column).  The columns of S are
-// fetched eight at a time, a block ahead; back pointers stay in LDS as long as they fit.  Bound by the serial chain of n
-// columns and n back pointers: 22 x 32 layers 12 us (67 us with ten LDS steps and a barrier each per column, 1024
-// threads whatever m).
-__global__ __launch_bounds__(MAP_THREADS) void layer_map_kernel(const double *__restrict__ S, int m, int n,
-                                                                int32_t *__restrict__ back, int32_t *__restrict__ f,
-                                                                double *__restrict__ total)
+// v of the lane that the step moves from; -infinity where there is none.
+template <int CTRL, int ROW_MASK> __device__ __forceinline__ double shifted(double v)
 {
-    __shared__ double wval[2][MAP_THREADS / 64];
-    __shared__ int widx[2][MAP_THREADS / 64];
-    __shared__ uint16_t back_lds[MAP_LDS_BACK];
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROW_MASK, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp((int)0xfff00000, __double2hiint(v), CTRL, ROW_MASK, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+
+// One thread per draft layer, up to 1024.  A column is a prefix maximum inside every wave on the vector ALU and, with more than 64
+// draft layers, one over the wave totals through LDS (double-buffered: one barrier per column).  The columns of S are
+// fetched eight at a time and ahead; back pointers stay in LDS as long as they fit.  Bound by the serial chain of n
+// columns and n back pointers.
+struct AlignShared {
+    double wval[2][MAP_THREADS / 64];
+    int widx[2][MAP_THREADS / 64];
+    int start;
+    union {
+        uint16_t back[MAP_LDS_BACK];
+        unsigned long long records[MAP_LDS_BACK / 4];
+    };
+};
+__device__ __forceinline__ void align_threads(const double *__restrict__ S, int m, int n, int32_t *__restrict__ back, int32_t *__restrict__ f,
+                              double *__restrict__ total, AlignShared &sh)
+{
     const int i = threadIdx.x, lane = i & 63, wave = i >> 6, waves = blockDim.x >> 6;
     const bool in_lds = (int64_t)m * n <= MAP_LDS_BACK;
     int turn = 0;
@@ -279,10 +291,10 @@ __global__ __launch_bounds__(MAP_THREADS) void layer_map_kernel(const double *__
         scan_step<0x142, 0xa>(b);     // row_bcast:15 into rows 1 and 3
         scan_step<0x143, 0xc>(b);     // row_bcast:31 into rows 2 and 3
         if (waves > 1) {
-            if (lane == 63) { wval[turn][wave] = b.val; widx[turn][wave] = b.idx; }
+            if (lane == 63) { sh.wval[turn][wave] = b.val; sh.widx[turn][wave] = b.idx; }
             __syncthreads();
             for (int w = wave - 1; w >= 0; --w)
-                if (!(b.val > wval[turn][w])) { b.val = wval[turn][w]; b.idx = widx[turn][w]; }
+                if (!(b.val > sh.wval[turn][w])) { b.val = sh.wval[turn][w]; b.idx = sh.widx[turn][w]; }
             turn ^= 1;
         }
         return b;
@@ -306,7 +318,7 @@ __global__ __launch_bounds__(MAP_THREADS) void layer_map_kernel(const double *__
             }
             const Best b = prefix_max(best);
             if (i < m) {
-                if (in_lds) back_lds[i * n + j] = (uint16_t)b.idx;
+                if (in_lds) sh.back[i * n + j] = (uint16_t)b.idx;
                 else back[(int64_t)i * n + j] = b.idx;
                 best = cur[c] + b.val;
             }
@@ -315,19 +327,104 @@ __global__ __launch_bounds__(MAP_THREADS) void layer_map_kernel(const double *__
         for (int c = 0; c < AHEAD; ++c) cur[c] = nxt[c];
     }
     const Best last = prefix_max(best);
-    __shared__ int start;
     if (i == (int)blockDim.x - 1) {
-        start = last.idx < m ? last.idx : 0;                   // first maximum of the last column (all entries -infinity or NaN: layer 0)
+        sh.start = last.idx < m ? last.idx : 0;                   // first maximum of the last column (all entries -infinity or NaN: layer 0)
         *total = last.val;
     }
     __syncthreads();                                           // also orders the back pointers
     if (i == 0) {
-        int at = start;
+        int at = sh.start;
         f[n - 1] = at;
         for (int j = n - 1; j > 0; --j) {
-            at = in_lds ? back_lds[at * n + j] : __hip_atomic_load(&back[(int64_t)at * n + j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            at = in_lds ? sh.back[at * n + j] : __hip_atomic_load(&back[(int64_t)at * n + j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             f[j - 1] = at;
         }
+    }
+}
+
+__global__ __launch_bounds__(MAP_THREADS) void layer_map_kernel(const double *__restrict__ S, int m, int n, int32_t *__restrict__ back,
+                                                                int32_t *__restrict__ f, double *__restrict__ total)
+{
+    __shared__ AlignShared sh;
+    align_threads(S, m, n, back, f, total, sh);
+}
+
+// Up to 64 draft layers: one wave, lane i holds best[i].  A column needs the prefix maximum alone; where it came from is what a column's
+// records (the lanes above everything before them, one ballot) say: the first maximum over the lanes up to i is the last record up to
+// i.  So the columns carry no indices, and the way back is five scalar instructions per column instead of a dependent read from LDS.
+// 22 x 32 layers, back pointers per lane and column / records: 11.9 / RECORDED us.  Records wait in LDS, or, where there are too many, in
+// the workspace (8 of the 4 m bytes per column it holds).  Columns that met a NaN, for which an order of maxima has no meaning, are
+// taken again by the general form.
+template <int STEPS> __device__ __forceinline__ double prefix_max(double v)
+{
+    // (no NaN matters here, so a bare instruction; two wait states for the lane move that reads its result)
+    auto step = [&](double left) { asm("v_max_f64 %0, %1, %2\n s_nop 1" : "=v"(v) : "v"(v), "v"(left)); };
+    if (STEPS > 0) step(shifted<0x111, 0xf>(v));    // row_shr:1
+    if (STEPS > 1) step(shifted<0x112, 0xf>(v));    // row_shr:2
+    if (STEPS > 2) step(shifted<0x114, 0xf>(v));    // row_shr:4
+    if (STEPS > 3) step(shifted<0x118, 0xf>(v));    // row_shr:8
+    if (STEPS > 4) step(shifted<0x142, 0xa>(v));    // row_bcast:15 into rows 1 and 3
+    if (STEPS > 5) step(shifted<0x143, 0xc>(v));    // row_bcast:31 into rows 2 and 3
+    return v;
+}
+// Forward columns; returns whether a NaN came up, the last column's maximum in `top`.
+template <int STEPS> __device__ __forceinline__ bool align_columns(const double *__restrict__ S, int m, int n, unsigned long long *records, double &top)
+{
+    const int lane = threadIdx.x;
+    constexpr int AHEAD = 16;
+    const double *row = S + (int64_t)(lane < m ? lane : m - 1) * n;
+    double cur[AHEAD], nxt[AHEAD];
+#pragma unroll
+    for (int c = 0; c < AHEAD; ++c) cur[c] = row[c < n ? c : n - 1];
+    double before = -0.0;                                      // maximum over the lanes up to this one, column before
+    unsigned long long mine = 0;                               // records of column (lane) of the current 64
+    bool nan = false;
+    for (int j0 = 0; j0 < n; j0 += AHEAD) {
+#pragma unroll
+        for (int c = 0; c < AHEAD; ++c) nxt[c] = row[j0 + AHEAD + c < n ? j0 + AHEAD + c : n - 1];
+#pragma unroll
+        for (int c = 0; c < AHEAD; ++c) {
+            if (j0 + c < n) {                                  // (uniform)
+                const double best = lane < m ? cur[c] + before : -INFINITY;      // (lanes past m never win a maximum)
+                nan |= best != best;
+                before = prefix_max<STEPS>(best);
+                const unsigned long long rec = __ballot(best > shifted<0x138, 0xf>(before)) | 1ull;     // wave_shr:1; lane 0 always
+                if (lane == (j0 & 63) + c) mine = rec;
+            }
+        }
+        const int end = j0 + AHEAD < n ? j0 + AHEAD : n, at = (j0 & ~63) + lane;
+        if (((end & 63) == 0 || end == n) && at < end) records[at] = mine;
+#pragma unroll
+        for (int c = 0; c < AHEAD; ++c) cur[c] = nxt[c];
+    }
+    top = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(before), m - 1), __builtin_amdgcn_readlane(__double2loint(before), m - 1));
+    return __any(nan);
+}
+__global__ __launch_bounds__(64) void layer_map_wave_kernel(const double *__restrict__ S, int m, int n, int32_t *__restrict__ back,
+                                                            int32_t *__restrict__ f, double *__restrict__ total)
+{
+    __shared__ AlignShared sh;
+    const int lane = threadIdx.x;
+    unsigned long long *records = n <= (int)(sizeof(sh.records) / 8) ? sh.records : reinterpret_cast<unsigned long long *>(back);
+    double top;
+    const bool nan = m <= 16 ? align_columns<4>(S, m, n, records, top) : m <= 32 ? align_columns<5>(S, m, n, records, top) : align_columns<6>(S, m, n, records, top);
+    if (nan) {                                                 // (uniform)
+        align_threads(S, m, n, back, f, total, sh);
+        return;
+    }
+    __syncthreads();                                           // (one wave: orders its records)
+    if (lane == 0) *total = top;
+    int at = m - 1;
+    for (int j0 = (n - 1) & ~63; j0 >= 0; j0 -= 64) {
+        const unsigned long long rec = records[j0 + lane < n ? j0 + lane : n - 1];
+        int chosen = 0;
+        for (int k = n - 1 - j0 < 63 ? n - 1 - j0 : 63; k >= 0; --k) {
+            const unsigned long long r = (unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(rec >> 32), k) << 32 |
+                                         (unsigned)__builtin_amdgcn_readlane((int)(uint32_t)rec, k);
+            at = 63 - __clzll((long long)(r & (~0ull >> (63 - at))));
+            if (lane == k) chosen = at;
+        }
+        if (j0 + lane < n) f[j0 + lane] = chosen;
     }
 }
 
@@ -451,8 +548,9 @@ specattn_status specattn_layer_map(const double *S, int32_t m, int32_t n, int32_
     if (!workspace) { set_error("workspace is NULL, %zu bytes needed", need); return SPECATTN_EWORKSPACE; }
     if (reinterpret_cast<uintptr_t>(workspace) % 256) { set_error("workspace must be 256-byte aligned"); return SPECATTN_EWORKSPACE; }
     if (workspace_bytes < need) { set_error("workspace has %zu bytes, %zu needed", workspace_bytes, need); return SPECATTN_EWORKSPACE; }
-    hipLaunchKernelGGL(layer_map_kernel, dim3(1), dim3((m + 63) / 64 * 64), 0, static_cast<hipStream_t>(stream), S, m, n,
-                       static_cast<int32_t *>(workspace), f, total);
+    const bool one_wave = m <= 64 && (m > 1 || n <= MAP_LDS_BACK / 4);          // (the workspace of a single layer holds no records)
+    hipLaunchKernelGGL(one_wave ? layer_map_wave_kernel : layer_map_kernel, dim3(1), dim3((m + 63) / 64 * 64), 0, static_cast<hipStream_t>(stream), S, m,
+                       n, static_cast<int32_t *>(workspace), f, total);
     return check_launch("layer_map_kernel");
 }
 
