@@ -25,7 +25,8 @@ constexpr int KL_WAVES = 8, KL_FEW_WAVES = 4;        // per workgroup (kl_plan)
 constexpr int KL_WAVE_K = 64;                        // entries of a layer one wave takes per iteration
 constexpr int KL_TI = 32, KL_TJ = 32;                // draft and verifier layers per workgroup
 constexpr int KL_ROW = KL_WAVE_K + 2;                // doubles per staged row: rows start four banks apart
-constexpr int KL_WAVE_LDS = KL_TI * KL_ROW;          // doubles
+constexpr int KL_SUMS = 4 * 256 + 2 * 64;            // doubles of a wave's sums: four tiles of pairs, two of the small products
+constexpr int KL_WAVE_LDS = KL_TI * KL_ROW > KL_SUMS ? KL_TI * KL_ROW : KL_SUMS;     // doubles
 constexpr int LOG_FIRST = 64, LOG_ENTRIES = 118;     // table of logarithms: of 64/128 to 181/128
 constexpr int kl_lds_bytes(int waves) { return (waves * KL_WAVE_LDS + 2 * LOG_ENTRIES) * (int)sizeof(double); }
 constexpr int MAP_THREADS = 1024;      // most draft layers the alignment kernel takes
@@ -91,11 +92,12 @@ __device__ __forceinline__ void wave_sync()
 // Every wave works on 64 entries of its own and meets the others only at the end: it takes the logarithms of its
 // draft entries into its part of LDS ([layer][entry], fp64), then goes through its verifier entries, 16 layers x 16
 // entries at a time, straight from memory: lane l holds entries 4 * (l / 16) .. + 3 of layer l % 16, which is
-// a B operand of four matrix instructions; their logarithms are the A operand of a third product whose diagonal is
-// sum p log p - taken in the same order as the other sums, so that a layer compared with itself gives exactly zero.
-// Bound by the logarithms (25 instructions each, m + n of them per entry) behind one unhidden trip to memory: 22 x 32
-// layers, 64 rows x 2048 positions (28 MB, 92 M terms) in 19 us; two general logarithms per term, one workgroup per
-// layer pair and chunk, took 329 us.
+// a B operand of four matrix instructions; their logarithms are the A operand of a third product, in four blocks of 4 x 4 layers, whose
+// diagonals are sum p log p - taken in the same order as the other sums, so that a layer compared with itself gives exactly zero.
+// Bound by the logarithms (25 instructions each, m + n of them per entry) and the fp64 products (64 cycles per 16 x 16 x 4), which overlap
+// only across the two waves of a SIMD, behind one unhidden trip to memory.  22 x 32 layers, 64 rows x 2048 positions (28 MB, 92 M
+// terms): the diagonal from 16 x 16 products, the sums in two rounds 19.6 us / now 17.8 us; two general logarithms per term, one
+// workgroup per layer pair and chunk, took 329 us.
 __global__ __launch_bounds__(KL_WAVES * 64) void layer_kl_kernel(const float *__restrict__ ad, const float *__restrict__ av, int m,
                                                                  int n, int64_t per_layer, int iters, double *__restrict__ partial)
 {
@@ -106,20 +108,23 @@ __global__ __launch_bounds__(KL_WAVES * 64) void layer_kl_kernel(const float *__
     const int l16 = lane & 15, g = lane >> 4;
     const int i0 = blockIdx.y * KL_TI, j0 = blockIdx.z * KL_TJ;
     double *lq = kl_lds + wave * KL_WAVE_LDS;
-    f32x4u q[8], p[2][4];
+    constexpr int VEC = KL_WAVE_K / 4, QROWS = 64 / VEC;  // lanes that load a draft layer's entries; layers per load
+    constexpr int QT = KL_TI / QROWS, PS = KL_WAVE_K / 16;    // vectors of draft and verifier entries per lane (and verifier tile)
+    const int lv = lane & (VEC - 1), gv = lane / VEC;
+    f32x4u q[QT], p[2][PS];
     // (Layers past the last one repeat it: their sums are not read.)
     auto request = [&](int64_t k0) {
         if (k0 >= per_layer) return;                  // (uniform over the wave)
         const bool whole = k0 + KL_WAVE_K <= per_layer;
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            const int i = i0 + 4 * t + g;
-            q[t] = load4(ad + (int64_t)(i < m ? i : m - 1) * per_layer, k0 + 4 * l16, per_layer, whole);
+        for (int t = 0; t < QT; ++t) {
+            const int i = i0 + QROWS * t + gv;
+            q[t] = load4(ad + (int64_t)(i < m ? i : m - 1) * per_layer, k0 + 4 * lv, per_layer, whole);
         }
 #pragma unroll
         for (int a = 0; a < 2; ++a)
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
+            for (int s = 0; s < PS; ++s) {
                 const int j = j0 + 16 * a + l16;
                 p[a][s] = load4(av + (int64_t)(j < n ? j : n - 1) * per_layer, k0 + 16 * s + 4 * g, per_layer, whole);
             }
@@ -131,25 +136,26 @@ __global__ __launch_bounds__(KL_WAVES * 64) void layer_kl_kernel(const float *__
         tab[tid] = (f64x2){1.0 / j, log(j / 128.0)};
     }
     __syncthreads();
-    f64x4 acc[2][3];                                  // [verifier tile][draft tile 0, 1, the verifier's own logarithms]
+    f64x4 acc[2][2];                                  // [verifier tile][draft tile]
+    double own[2] = {0.0, 0.0};                       // products with the verifier's own logarithms
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int t = 0; t < 3; ++t) acc[a][t] = (f64x4){0.0, 0.0, 0.0, 0.0};
+        for (int t = 0; t < 2; ++t) acc[a][t] = (f64x4){0.0, 0.0, 0.0, 0.0};
     for (int it = 0; it < iters; ++it) {
         const int64_t k0 = first + it * step;
         if (k0 >= per_layer) break;                   // (uniform over the wave)
         if (it) request(k0);
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            if (i0 + 4 * t >= m) break;               // (uniform)
-            f64x2 *dst = reinterpret_cast<f64x2 *>(lq + (4 * t + g) * KL_ROW + 4 * l16);
+        for (int t = 0; t < QT; ++t) {
+            if (i0 + QROWS * t >= m) break;           // (uniform)
+            f64x2 *dst = reinterpret_cast<f64x2 *>(lq + (QROWS * t + gv) * KL_ROW + 4 * lv);
             dst[0] = (f64x2){log_draft(q[t][0], tab), log_draft(q[t][1], tab)};
             dst[1] = (f64x2){log_draft(q[t][2], tab), log_draft(q[t][3], tab)};
         }
         wave_sync();
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
+        for (int s = 0; s < PS; ++s) {
             f64x2 a0[2], a1[2];
 #pragma unroll
             for (int c = 0; c < 2; ++c) {
@@ -171,32 +177,42 @@ __global__ __launch_bounds__(KL_WAVES * 64) void layer_kl_kernel(const float *__
                     const double x = fmaxf(v[c], 0.0f);
                     acc[a][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0[c >> 1][c & 1], x, acc[a][0], 0, 0, 0);
                     if (i0 + 16 < m) acc[a][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1[c >> 1][c & 1], x, acc[a][1], 0, 0, 0);
-                    acc[a][2] = __builtin_amdgcn_mfma_f64_16x16x4f64(lp[c], x, acc[a][2], 0, 0, 0);
+                    own[a] = __builtin_amdgcn_mfma_f64_4x4x4f64(lp[c], x, own[a], 0, 0, 0);
                 }
             }
         }
         wave_sync();
     }
-    // the waves' sums, in wave order.  Element (row 4 v + g, column l16) of a tile sits in register v of lane (g, l16).
+    // the waves' sums, in wave order.  Element (row 4 v + g, column l16) of a tile sits in register v of lane (g, l16), element (i, j) of
+    // block b of the small products in lane 16 i + 4 b + j.
+    constexpr int OWN = 4 * 256;
     __syncthreads();
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < 2; ++a) {
 #pragma unroll
-        for (int t = 0; t < 3; ++t)
+        for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) lq[((a * 3 + t) * 16 + 4 * v + g) * 16 + l16] = acc[a][t][v];
+            for (int v = 0; v < 4; ++v) lq[((a * 2 + t) * 16 + 4 * v + g) * 16 + l16] = acc[a][t][v];
+        lq[OWN + a * 64 + lane] = own[a];
+    }
     __syncthreads();
-    for (int e = tid; e < KL_TI * KL_TJ; e += (int)blockDim.x) {
-        const int i = e >> 5, j = e & 31;
-        if (i0 + i >= m || j0 + j >= n) continue;
-        const int a = j >> 4, jj = j & 15;
-        double own = 0.0, cross = 0.0;
-        for (int w = 0; w < waves; ++w) {
-            const double *src = kl_lds + w * KL_WAVE_LDS;
-            own += src[((a * 3 + 2) * 16 + jj) * 16 + jj];
-            cross += src[((a * 3 + (i >> 4)) * 16 + (i & 15)) * 16 + jj];
+    auto sum_of_waves = [&](const double *src) {
+        double s = 0.0;
+        for (int w0 = 0; w0 < waves; w0 += 8) {
+            double x[8];
+#pragma unroll
+            for (int w = 0; w < 8; ++w) x[w] = src[(w0 + w < waves ? w0 + w : w0) * KL_WAVE_LDS];
+#pragma unroll
+            for (int w = 0; w < 8; ++w) s += w0 + w < waves ? x[w] : 0.0;
         }
-        partial[((int64_t)blockIdx.x * m + i0 + i) * n + j0 + j] = own - cross;
+        return s;
+    };
+    for (int e = tid; e < KL_TI * KL_TJ; e += (int)blockDim.x) {
+        const int i = e >> 5, j = e & 31, a = j >> 4, jj = j & 15;
+        if (i0 + i >= m || j0 + j >= n) continue;
+        const double self = sum_of_waves(kl_lds + OWN + a * 64 + 16 * (jj & 3) + jj);
+        const double cross = sum_of_waves(kl_lds + (a * 32 + i) * 16 + jj);
+        partial[((int64_t)blockIdx.x * m + i0 + i) * n + j0 + j] = self - cross;
     }
 }
 
@@ -222,7 +238,13 @@ __global__ __launch_bounds__(512) void layer_kl_finish_kernel(const double *__re
     };
     double s = 0.0;
     if (pair < pairs)
-        for (int c = cl; c < chunks; c += 64) s += partial[(int64_t)c * pairs + pair];
+        for (int c0 = cl; c0 < chunks; c0 += 256) {   // four requests at a time
+            double x[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) x[k] = partial[(int64_t)(c0 + 64 * k < chunks ? c0 + 64 * k : c0) * pairs + pair];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) s += c0 + 64 * k < chunks ? x[k] : 0.0;
+        }
     s = sum_of_threads(s, red[0]);
     auto is_odd = [&](double x) { return !(x > -DIVERGENCE_LIMIT && x < INFINITY); };
     const bool odd = pair < pairs && is_odd(s);
@@ -352,7 +374,7 @@ __global__ __launch_bounds__(MAP_THREADS) void layer_map_kernel(const double *__
 // Up to 64 draft layers: one wave, lane i holds best[i].  A column needs the prefix maximum alone; where it came from is what a column's
 // records (the lanes above everything before them, one ballot) say: the first maximum over the lanes up to i is the last record up to
 // i.  So the columns carry no indices, and the way back is five scalar instructions per column instead of a dependent read from LDS.
-// 22 x 32 layers, back pointers per lane and column / records: 11.9 / RECORDED us.  Records wait in LDS, or, where there are too many, in
+// 22 x 32 layers, back pointers per lane and column / records: 11.9 / 7.2 us.  Records wait in LDS, or, where there are too many, in
 // the workspace (8 of the 4 m bytes per column it holds).  Columns that met a NaN, for which an order of maxima has no meaning, are
 // taken again by the general form.
 template <int STEPS> __device__ __forceinline__ double prefix_max(double v)

@@ -113,6 +113,23 @@ def test_alignment_scan_edges(m, n):
     assert v == v_ref and np.array_equal(f, f_ref)
 
 
+@pytest.mark.parametrize("m,n", [(16, 63), (17, 64), (32, 65), (33, 129), (64, 16), (1, 6145), (3, 6145)])
+def test_alignment_in_one_wave(m, n):
+    """Draft layers around the lane steps of one wave, columns around its blocks of 16 and 64 and the records LDS holds; ties,
+    entries of -infinity, and a NaN, for which the general form (more than 64 layers, the others -infinity) is the measure."""
+    rng = np.random.default_rng(m * 11 + n)
+    S = np.round(rng.normal(size=(m, n)) * 2)
+    S[rng.random(S.shape) < 0.1] = -np.inf
+    S[0, ::2] = np.where(np.isneginf(S[0, ::2]), -9.0, S[0, ::2])
+    f_ref, v_ref = oracle.layer_map(S)
+    f, v = gpu_map(S)
+    assert (v == v_ref or (np.isneginf(v) and np.isneginf(v_ref))) and np.array_equal(f, f_ref)
+    S[m // 2, n // 3] = np.nan
+    f, v = gpu_map(S)
+    f_ref, v_ref = gpu_map(np.vstack([S, np.full((65 - m, n), -np.inf)]))
+    assert np.array_equal([v], [v_ref], equal_nan=True) and np.array_equal(f, f_ref)
+
+
 def test_layers_compared_with_themselves():
     ad, _ = W.layer_attention_maps(seed=9, m=5, n=5, rows=4, L=128)
     S = gpu_similarity(ad, ad)
