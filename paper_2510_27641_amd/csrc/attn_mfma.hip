@@ -188,6 +188,22 @@ size_t attn_mfma_workspace_min_bytes(int rows, int G, int T, int d)
     return workspace_for(rows < MAX_ROWS ? rows : MAX_ROWS, query_tiles(G, T, NARROW), d);
 }
 
+// Shares that the cost line is cut into: as many as there are workgroups, but fewer where the rows are few and short.  There a share
+// is a few tiles, which the waves of a workgroup take at the same time anyway, and what counts is how many partials the merge has to go
+// through, eight to a trip to memory, and how many shares hold nothing but a row's start.  So 64, doubled where the shares are longer
+// than: 4 units where that leaves a row less than eight partials, 12 (4 where a tile is much work: 64 positions, two query tiles or
+// more) where it leaves it less than sixteen, 10 beyond; and one per workgroup where rows have no more than eight tiles, which is one trip
+// however they are shared out.  Measured with 64 / 128 / 256 shares, us for both launches: 4 rows of 300
+// units in all 12.3 / 13.3 / 15.5, of 1176 17.0 / 16.4 / 19.2; 8 rows of 600 13.0 / 13.2 / 14.3, of 1224 16.3 / 14.8 / 16.2 (but of 2200 and
+// 64 query rows, from memory, 1.3 more with 128 than with 256); 16 rows of 272 10.5 / 9.9 / 10.1, of 1200 16.0 / 14.1 / 14.6, of 2448 22.2 / 17.5 / 17.4; 32 rows of 544 10.5 / 10.5 / 10.4, of
+// 800 13.5 / 12.0 / 11.5; d = 64, 40 query rows: 8 rows of 152 11.0 / 11.0 / 10.8, 16 rows of 432 13.1 / 11.7 / 12.9, of 704 15.6 / 14.0 / 13.6.
+static void share_lines(Plan &plan, int rows, int nqt, int d)
+{
+    auto longest = [&](int n) { return n >= plan.n_wg ? 0 : n * (n < 8 * rows || (n < 16 * rows && d == 64 && nqt >= 2) ? 4 : n < 16 * rows ? 12 : 10); };
+    plan.line_64 = longest(64);
+    plan.line_128 = longest(128);
+}
+
 static specattn_status launch_chunk(const AttnLaunch &a, hipStream_t stream)
 {
     const int rows = a.B * a.H_kv;
@@ -196,6 +212,7 @@ static specattn_status launch_chunk(const AttnLaunch &a, hipStream_t stream)
     const int nqt = (QT + 15) / 16, qtp = nqt * 16;
     Plan plan;
     plan.n_wg = attn_mfma_workgroups();
+    share_lines(plan, rows, nqt, a.d);
     plan.heads = a.H_q / a.H_kv;
     plan.group = G;
     plan.per_h = (uint32_t)((((uint64_t)1 << 31) + a.H_kv - 1) / a.H_kv);

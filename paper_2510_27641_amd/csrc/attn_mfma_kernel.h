@@ -352,6 +352,7 @@ struct Plan {
     float *part_o;            // [slots][16 * NQT][d]
     uint32_t *row_parts;      // [rows] in the workspace: the shares that hold a row's first (low half) and last tile, or ROW_EMPTY
     int n_wg;
+    int line_64, line_128;    // lines of up to so many units are cut into 64 or 128 shares (share_lines)
     int heads, group;         // query heads per kv head: in all, and in this launch
     uint32_t per_h, per_t;    // 2^31 / H_kv and 2^16 / T, rounded up
 };
@@ -567,7 +568,7 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
     SPECATTN_PRELOAD(a.g_first); SPECATTN_PRELOAD(a.k_new);
     SPECATTN_PRELOAD(a.out); SPECATTN_PRELOAD(a.out_lowp); SPECATTN_PRELOAD(a.lse);
     SPECATTN_PRELOAD(plan.part_ml); SPECATTN_PRELOAD(plan.part_o); SPECATTN_PRELOAD(plan.row_parts);
-    SPECATTN_PRELOAD(plan.n_wg); SPECATTN_PRELOAD(plan.heads); SPECATTN_PRELOAD(plan.group); SPECATTN_PRELOAD(plan.per_h); SPECATTN_PRELOAD(plan.per_t);
+    SPECATTN_PRELOAD(plan.n_wg); SPECATTN_PRELOAD(plan.line_64); SPECATTN_PRELOAD(plan.line_128); SPECATTN_PRELOAD(plan.heads); SPECATTN_PRELOAD(plan.group); SPECATTN_PRELOAD(plan.per_h); SPECATTN_PRELOAD(plan.per_t);
     if (LAYOUT != CONTIGUOUS) { SPECATTN_PRELOAD(a.page_table); SPECATTN_PRELOAD(a.page_shift); SPECATTN_PRELOAD(a.max_pages); SPECATTN_PRELOAD(a.kv_stride_page); }
     if (SRC == LIST) { SPECATTN_PRELOAD(a.indices); SPECATTN_PRELOAD(a.idx_stride); }
     if (SRC == MASK) { SPECATTN_PRELOAD(a.kept_mask); SPECATTN_PRELOAD(a.block_counts); SPECATTN_PRELOAD(a.blocks_per_row); SPECATTN_PRELOAD(a.n_max); }
@@ -638,7 +639,8 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
 
     // This workgroup's share of the cost line, and the rows of which it holds tiles
     const int my_share = __builtin_amdgcn_readfirstlane(share_index(blockIdx.x, plan.n_wg));
-    const Share<TILE> sh = make_share<TILE>(__builtin_amdgcn_readfirstlane(total), plan.n_wg, my_share);
+    total = __builtin_amdgcn_readfirstlane(total);
+    const Share<TILE> sh = make_share<TILE>(total, total > plan.line_128 || total <= (8 + SEG_COST) * rows ? plan.n_wg : total <= plan.line_64 ? 64 : 128, my_share);
     const int c0 = sh.c0, c1 = sh.c1;
     if (c0 >= c1) return;                                // more workgroups than units of work
     int my_lb = 0, my_le = 0;                            // few rows: local tile range of row `lane`

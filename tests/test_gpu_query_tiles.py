@@ -306,11 +306,12 @@ def test_options_together(d, G, T, dtype, mode, paged):
 
 
 @pytest.mark.parametrize("new_tokens", [False, True])
-@pytest.mark.parametrize("B,H_kv,G,T", [(1, 1, 1, 1), (4, 16, 3, 3), (13, 5, 5, 7), (9, 7, 9, 6), (2, 33, 2, 5)])
-def test_rows_and_their_shares(B, H_kv, G, T, new_tokens):
+@pytest.mark.parametrize("B,H_kv,G,T,n", [(1, 1, 1, 1, 700), (4, 16, 3, 3, 700), (13, 5, 5, 7, 700), (9, 7, 9, 6, 700), (2, 33, 2, 5, 700),
+                                          (1, 3, 4, 5, 9001), (1, 4, 2, 5, 2500), (2, 4, 4, 4, 4100), (2, 8, 1, 8, 2600), (4, 8, 2, 3, 330)])
+def test_rows_and_their_shares(B, H_kv, G, T, n, new_tokens):
     """63, 64 and 65 rows and few ones, head and token counts that are no powers of two, empty rows among full ones, rows inside
-    one workgroup and over many, in a workspace that holds anything."""
-    n, d = 700, 128
+    one workgroup and over many, lines of 64, 128 and 256 shares, in a workspace that holds anything."""
+    d = 128
     rng = np.random.default_rng(B * 100 + H_kv)
     w = W.llama8b_layer(seed=G, B=B, n=n, H_q=G * H_kv, H_kv=H_kv, T=T, d=d, dtype="f16")
     keep = rng.integers(0, n + 1, size=(B, H_kv)) * (rng.random((B, H_kv)) < 0.8)
