@@ -338,9 +338,11 @@ __device__ __forceinline__ void vm_wait(int n)
 {
     switch (n) {
     case 0: asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); break;
+    case 1: asm volatile("s_waitcnt vmcnt(1)" ::: "memory"); break;
+    case 2: asm volatile("s_waitcnt vmcnt(2)" ::: "memory"); break;
     case 8: asm volatile("s_waitcnt vmcnt(8)" ::: "memory"); break;
     case 9: asm volatile("s_waitcnt vmcnt(9)" ::: "memory"); break;
-    case 10: asm volatile("s_waitcnt vmcnt(10)" ::: "memory"); break;
+    case 16: asm volatile("s_waitcnt vmcnt(16)" ::: "memory"); break;
     case 17: asm volatile("s_waitcnt vmcnt(17)" ::: "memory"); break;
     default: asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); break;
     }
@@ -611,31 +613,22 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
     const int QT = plan.group * a.T;
     const float scale2 = a.sm_scale * 1.4426950408889634f;            // scores in log2 units
 
-    // ---- per-segment inputs that are fetched ahead of time -------------------------------------------
-    // The Q tile of a segment goes through LDS: thread t fetches 16-byte chunk t%LPR of query rows t/LPR (+THREADS/LPR ...)
-    // ahead of time and stores it (swizzled like a K row) when the segment starts.
-    u32x4 q_pf[QROUNDS];
-    auto fetch_q = [&](int rr) {
+    // The Q tile of a segment goes straight into LDS: wave w fetches 16-byte slots 64 w .. of it (and of its second 8 KiB), swizzled like
+    // K rows.  Query rows past the last one repeat it: their results are not written.
+    auto load_q = [&](int rr) {
         const int b = div_h(plan, rr), h = rr - b * a.H_kv;
 #pragma unroll
         for (int k = 0; k < QROUNDS; ++k) {
-            const int qi = tid / LPR + k * (THREADS / LPR), ch = tid & (LPR - 1);
-            q_pf[k] = (u32x4){0u, 0u, 0u, 0u};
-            if (qi < QT) {
-                const int gh = div_t(plan, qi), tt = qi - gh * a.T;
-                const uint16_t *qp = static_cast<const uint16_t *>(a.q) + (int64_t)b * a.q_stride_b +
-                                     (int64_t)attn_query_head(a, plan.heads, h, gh) * a.q_stride_h + (int64_t)tt * a.q_stride_t;
-                q_pf[k] = *reinterpret_cast<const u32x4 *>(qp + ch * 8);
-            }
+            if (k * THREADS + wave * 64 >= QCH) break;   // (uniform over the wave)
+            const int row = k * (THREADS / LPR) + tid / LPR, qi = min(row, QT - 1);
+            const int gh = div_t(plan, qi), tt = qi - gh * a.T;
+            const uint16_t *qp = static_cast<const uint16_t *>(a.q) + (int64_t)b * a.q_stride_b +
+                                 (int64_t)attn_query_head(a, plan.heads, h, gh) * a.q_stride_h + (int64_t)tt * a.q_stride_t;
+            __builtin_amdgcn_global_load_lds(GLOBAL_PTR(qp + ((tid & (LPR - 1)) ^ GEO::swz(row & 15)) * 8),
+                                             LDS_PTR(void, q_lds + (k * THREADS + wave * 64) * 16), 16, 0, 0);
         }
     };
-    auto store_q = [&]() {
-#pragma unroll
-        for (int k = 0; k < QROUNDS; ++k) {
-            const int qi = tid / LPR + k * (THREADS / LPR), ch = tid & (LPR - 1);
-            if (qi < NQT * 16) *reinterpret_cast<u32x4 *>(q_lds + qi * ROW_BYTES + ((ch ^ GEO::swz(qi & 15)) << 4)) = q_pf[k];
-        }
-    };
+    const int n_q = wave * 64 >= QCH ? 0 : (QROUNDS == 1 || THREADS + wave * 64 >= QCH) ? 1 : 2;    // such loads of this wave
 
     // This workgroup's share of the cost line, and the rows of which it holds tiles
     const int my_share = __builtin_amdgcn_readfirstlane(share_index(blockIdx.x, plan.n_wg));
@@ -694,7 +687,7 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
                 request_words(idx_row, row_count(r), lt_begin + wave + NW, 1);
             }
         }
-        fetch_q(r);
+        if (SRC == LIST) load_q(r);
     }
 
     while (r < rows) {
@@ -875,9 +868,10 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
                 lds_barrier();
             }
         }
-        if ((SRC == MASK || !first_seg) && t_cur < tile_end) { request(t_cur, 0); request(t_nxt, 1); }
-        store_q();
-        lds_barrier();
+        if (SRC == MASK || !first_seg) {
+            if (t_cur < tile_end) { request(t_cur, 0); request(t_nxt, 1); }
+            load_q(r);
+        }
 
         f32x4 o[NQT][DT];                    // O^T[dv = 16t + 4g + i][q = l16]
         float m_ref[NQT], l_sum[NQT];        // reference max (log2 units) and sum of weights
@@ -889,17 +883,25 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
             for (int t = 0; t < DT; ++t) o[qt][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
         }
 
+        // The gathers and word requests are not tracked by the compiler's wait insertion; every wait on them is written out.  Order
+        // of issue per wave and iteration: K(next) ... V(next) words(third).  The first gathers go out as soon as the list words are
+        // there; Q, which the first product waits for, is waited for and shared behind them.  (Q through registers and a barrier ahead of the
+        // gathers: 0.2 to 0.6 us more per launch.)
+        uint32_t ent[8];
         if (t_cur < tile_end) {
-            // The gathers and word requests are not tracked by the compiler's wait insertion; every wait on them is
-            // written out.  Order of issue per wave and iteration: K(next) ... V(next) words(third).
-            uint32_t ent[8];
-            vm_wait(0);                                                 // the words of the first two tiles are there
+            vm_wait(n_q);                                               // the words of the first two tiles are there
             if (SRC == MASK) decode(t_cur, 0);
             entries(t_cur, 0, ent);
             issue(kbh, wave_lds, ent);
             issue(vbh, wave_lds + TILE_BYTES, ent);
             if (SRC == MASK) decode(t_nxt, 1);                          // (behind the first gathers, not ahead of them)
             request(t_nn, 0);
+            vm_wait(16 + n_idx);                                        // this wave's part of Q is there
+        } else {
+            vm_wait(0);
+        }
+        lds_barrier();
+        if (t_cur < tile_end) {
             int s_nxt = 1;                                              // slot with the words of t_nxt; t_nn's is the other
             while (t_cur < tile_end) {
                 const bool has_next = t_nxt < tile_end;
@@ -1093,8 +1095,6 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
             }
         }
 
-        // ---- request what the next segment needs, to arrive while this one is wrapped up --------------
-        if (r_next < rows) fetch_q(r_next);
 
         // ---- combine the waves of this workgroup: every wave hands its state over lane by lane through its
         //      own tile buffers, which are idle as soon as the wave itself has no tile left - before the barrier,
