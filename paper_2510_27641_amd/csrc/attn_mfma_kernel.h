@@ -502,6 +502,17 @@ struct Merge {
         m = mn;
     }
 };
+// Sum and largest over the four lanes l, l + 16, l + 32, l + 48, in each of them (exchanged on the vector ALU, not through LDS).
+template <typename F> __device__ __forceinline__ float over_rows(float x, F &&join)
+{
+    const auto v = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = join(__uint_as_float(v[0]), __uint_as_float(v[1]));
+    const auto w = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return join(__uint_as_float(w[0]), __uint_as_float(w[1]));
+}
+__device__ __forceinline__ float sum_of_rows(float x) { return over_rows(x, [](float a, float b) { return a + b; }); }
+__device__ __forceinline__ float max_of_rows(float x) { return over_rows(x, [](float a, float b) { return fmaxf(a, b); }); }
+
 template <int D, int NQT, int LAYOUT, int SRC, bool F16>
 __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunch a, Plan plan)
 {
@@ -965,8 +976,7 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
                                 below = (low & 0xffffull) != 0ull;
                             }
                             if (above || below) {
-                                float mx = fmaxf(mloc, __shfl_xor(mloc, 16, 64));
-                                mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+                                const float mx = max_of_rows(mloc);
                                 float mnew = fmaxf(m_ref[qt], mx);
                                 if constexpr (F16) {
                                     const float want = floorf(mx) - Half<F16>::HEAD;       // (whole numbers: rescaling is exact)
@@ -974,8 +984,7 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
                                     if (below) {
                                         // Down only as far as the sums stay well inside the range of fp32: beyond that a
                                         // tile adds nothing to them.
-                                        float sum = l_sum[qt] + __shfl_xor(l_sum[qt], 16, 64);
-                                        sum += __shfl_xor(sum, 32, 64);
+                                        const float sum = sum_of_rows(l_sum[qt]);
                                         const float least = m_ref[qt] + (float)(__builtin_amdgcn_frexp_expf(sum) - 80);
                                         if (mx < m_ref[qt] + Half<F16>::LO && mx > -INFINITY) mnew = fminf(fmaxf(want, least), m_ref[qt]);
                                     }
@@ -1122,55 +1131,66 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
 #pragma unroll
                 for (int t = 0; t < DT; ++t)
                     *reinterpret_cast<f32x4 *>(dmp + ((qq * DT + t) * 64 + lane) * 4) = o[qt][t];
-                float l = l_sum[qt];
-                l += __shfl_xor(l, 16, 64);
-                l += __shfl_xor(l, 32, 64);
+                const float l = sum_of_rows(l_sum[qt]);
                 if (g == 0) {
                     mlw[wave * 128 + l16 * 2 * NQT + 2 * qt] = m_ref[qt];
                     mlw[wave * 128 + l16 * 2 * NQT + 2 * qt + 1] = l;
                 }
             }
             lds_barrier();                     // every wave has handed over, and is done with Q
+            // Wave w sums the blocks w * KPW .. of all states, which are of one query tile; everything it reads is requested at once, weights
+            // and output row are found once.  (Block by block, and with the sums over lanes through LDS: a layer of 64 rows of 32768 0.6 us
+            // longer, 8 rows of 8192 20.9 / 21.5 us with selection and merge.)
             constexpr int BLOCKS = QN * DT;
             constexpr int KPW = (BLOCKS + NW - 1) / NW;    // blocks per wave
-            const int slot = my_share + r;
-            float *po = plan.part_o + (int64_t)slot * QTP * D;
-            float *pml = plan.part_ml + (int64_t)slot * QTP * 2;
+            static_assert(DT % KPW == 0, "a wave's blocks are of one query tile");
+            const int k0 = wave * KPW;           // uniform
+            if (BLOCKS % (NW * KPW) && k0 >= BLOCKS) return;
+            const int qt = Q0 + k0 / DT, t0 = k0 % DT;
+            float2 ml[NW];
+            f32x4 part[KPW][NW];
 #pragma unroll
-            for (int kk = 0; kk < KPW; ++kk) {
-                const int k = wave * KPW + kk;   // uniform
-                if (BLOCKS % (NW * KPW) && k >= BLOCKS) break;
-                const int qt = Q0 + k / DT, t = k % DT;
-                float m = -INFINITY;
+            for (int w = 0; w < NW; ++w) ml[w] = *reinterpret_cast<const float2 *>(mlw + w * 128 + l16 * 2 * NQT + 2 * qt);
 #pragma unroll
-                for (int w = 0; w < NW; ++w) m = fmaxf(m, mlw[w * 128 + l16 * 2 * NQT + 2 * qt]);
-                f32x4 acc = (f32x4){0.f, 0.f, 0.f, 0.f};
-                float l = 0.0f;
+            for (int kk = 0; kk < KPW; ++kk)
 #pragma unroll
-                for (int w = 0; w < NW; ++w) {
-                    const float mw = mlw[w * 128 + l16 * 2 * NQT + 2 * qt];
-                    const float f = (mw == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(mw - m);
-                    l += f * mlw[w * 128 + l16 * 2 * NQT + 2 * qt + 1];
-                    acc += f * *reinterpret_cast<const f32x4 *>(reinterpret_cast<const float *>(smem + w * WAVE_LDS) +
-                                                                (k * 64 + lane) * 4);
-                }
-                const int q = qt * 16 + l16;
-                if (q < QT) {
-                    if (final_here) {
-                        const int gh = div_t(plan, q), tt = q - gh * a.T;
-                        const int64_t orow = ((int64_t)b * a.H_q + attn_query_head(a, plan.heads, h, gh)) * a.T + tt;
-                        const f32x4 res = l > 0.0f ? acc / l : (f32x4){0.f, 0.f, 0.f, 0.f};
-                        *reinterpret_cast<f32x4 *>(a.out + orow * D + 16 * t + 4 * g) = res;
+                for (int w = 0; w < NW; ++w)
+                    part[kk][w] = *reinterpret_cast<const f32x4 *>(reinterpret_cast<const float *>(smem + w * WAVE_LDS) + ((k0 + kk) * 64 + lane) * 4);
+            float m = -INFINITY, l = 0.0f;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) m = fmaxf(m, ml[w].x);
+            f32x4 acc[KPW];
+#pragma unroll
+            for (int kk = 0; kk < KPW; ++kk) acc[kk] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                const float f = (ml[w].x == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(ml[w].x - m);
+                l += f * ml[w].y;
+#pragma unroll
+                for (int kk = 0; kk < KPW; ++kk) acc[kk] += f * part[kk][w];
+            }
+            const int q = qt * 16 + l16;
+            if (q < QT) {
+                if (final_here) {
+                    const int gh = div_t(plan, q), tt = q - gh * a.T;
+                    const int64_t orow = ((int64_t)b * a.H_q + attn_query_head(a, plan.heads, h, gh)) * a.T + tt;
+#pragma unroll
+                    for (int kk = 0; kk < KPW; ++kk) {
+                        const int64_t at = orow * D + 16 * (t0 + kk) + 4 * g;
+                        const f32x4 res = l > 0.0f ? acc[kk] / l : (f32x4){0.f, 0.f, 0.f, 0.f};
+                        *reinterpret_cast<f32x4 *>(a.out + at) = res;
                         if (a.out_lowp) {
 #pragma unroll
-                            for (int i = 0; i < 4; ++i) st_lowp(a.out_lowp, orow * D + 16 * t + 4 * g + i, res[i], a.dtype);
+                            for (int i = 0; i < 4; ++i) st_lowp(a.out_lowp, at + i, res[i], a.dtype);
                         }
-                        if (a.lse && g == 0 && t == 0)
-                            a.lse[orow] = l > 0.0f ? (m + log2f(l)) * 0.6931471805599453f : -INFINITY;
-                    } else {
-                        *reinterpret_cast<f32x4 *>(po + q * D + 16 * t + 4 * g) = acc;
-                        if (g == 0 && t == 0) { pml[2 * q] = m; pml[2 * q + 1] = l; }
                     }
+                    if (a.lse && g == 0 && t0 == 0) a.lse[orow] = l > 0.0f ? (m + log2f(l)) * 0.6931471805599453f : -INFINITY;
+                } else {
+                    const int slot = my_share + r;
+                    float *po = plan.part_o + (int64_t)slot * QTP * D, *pml = plan.part_ml + (int64_t)slot * QTP * 2;
+#pragma unroll
+                    for (int kk = 0; kk < KPW; ++kk) *reinterpret_cast<f32x4 *>(po + q * D + 16 * (t0 + kk) + 4 * g) = acc[kk];
+                    if (g == 0 && t0 == 0) { pml[2 * q] = m; pml[2 * q + 1] = l; }
                 }
             }
         });
