@@ -36,7 +36,17 @@ struct Place {                   // outcome of a locate step
     int bits;
 };
 
+// The entries of a boundary bin of at most FINE_SHIFT open bits, as distances from its lowest pattern, and for each of them the number
+// of those not below it (upper byte) and the sum of their distances (128 distances below 2^17 stay below 2^24).
+constexpr int LISTED = 128;
+struct BinList {
+    alignas(16) int entry[LISTED];                             // -1: none
+    uint32_t not_below[LISTED];
+    int n;
+};
+
 struct ResidentShared {
+    BinList list;
     Place place;
     uint32_t top[16];            // largest entry of every wave; all ones: an invalid one
     unsigned wave_sum[16];
@@ -188,13 +198,6 @@ __device__ __forceinline__ void locate_next(const unsigned long long *hist, int 
     place.bits = shift;
 }
 
-__device__ __forceinline__ uint32_t median(uint32_t a, uint32_t b, uint32_t c)
-{
-    uint32_t m;
-    asm("v_med3_u32 %0, %1, %2, %3" : "=v"(m) : "v"(a), "v"(b), "v"(c));
-    return m;
-}
-
 // Largest v of the wave, in every lane.
 __device__ __forceinline__ uint32_t wave_max(uint32_t v)
 {
@@ -206,6 +209,55 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v)
     step((uint32_t)dpp_int<0x142, 0xa>((int)v));    // row_bcast:15 into rows 1 and 3
     step((uint32_t)dpp_int<0x143, 0xc>((int)v));    // row_bcast:31 into rows 2 and 3
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// Decision inside a boundary bin whose entries are listed: every wave compares them with a part of the list, and then takes the
+// decision by itself.  Uniform over the workgroup, one barrier.
+template <int NW> __device__ __forceinline__ void locate_listed(BinList &list, float top_p, Place &place)
+{
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = (int)(place.packed >> CNT_SHIFT);
+    const bool two = n > 64;                                   // (uniform)
+    const int v0 = list.entry[lane], v1 = two ? list.entry[lane + 64] : -1;
+    uint32_t s0 = 0u, s1 = 0u;
+    for (int j = wave * 4; j < n; j += NW * 4) {               // (all lanes read the same four)
+        const int4 w = *reinterpret_cast<const int4 *>(&list.entry[j]);
+        auto compare = [&](int x) {                            // (-1 is below every entry)
+            const uint32_t one = (1u << 24) + (uint32_t)x;
+            s0 += x >= v0 ? one : 0u;
+            if (two) s1 += x >= v1 ? one : 0u;
+        };
+        compare(w.x); compare(w.y); compare(w.z); compare(w.w);
+    }
+    if (lane < n) atomicAdd(&list.not_below[lane], s0);
+    if (lane + 64 < n) atomicAdd(&list.not_below[lane + 64], s1);
+    __syncthreads();
+    s0 = list.not_below[lane];
+    s1 = two ? list.not_below[lane + 64] : 0u;
+    const int e_field = (int)(place.lo >> 23);
+    const double goal = top_p < 1.0f ? place.target : INFINITY;
+    // packed counter of `c` entries whose distances add up to `sum`
+    auto counter = [&](unsigned c, uint32_t sum) {
+        return (unsigned long long)c << CNT_SHIFT | ((unsigned long long)c * (place.lo & 0x7fffffu) + sum);
+    };
+    auto reaches = [&](int v, uint32_t s) { return v >= 0 && place.m_above + fraction_mass(counter(s >> 24, s & 0xffffffu), e_field) >= goal; };
+    const int reached = (int)wave_max(max(reaches(v0, s0) ? v0 + 1 : 0, reaches(v1, s1) ? v1 + 1 : 0));
+    const int tau = reached ? reached - 1 : (int)~wave_max(~min((uint32_t)v0, (uint32_t)v1));
+    const unsigned long long at0 = __ballot(v0 == tau), at1 = __ballot(v1 == tau);
+    const uint32_t s = (uint32_t)(at0 ? __builtin_amdgcn_readlane((int)s0, (int)__ffsll((long long)at0) - 1)
+                                      : __builtin_amdgcn_readlane((int)s1, (int)__ffsll((long long)at1) - 1));
+    const unsigned ties = (unsigned)(__popcll(at0) + __popcll(at1)), above = (s >> 24) - ties;
+    if (above) place.m_above += fraction_mass(counter(above, (s & 0xffffffu) - ties * (uint32_t)tau), e_field);
+    place.c_above += above;
+    place.packed = counter(ties, ties * (uint32_t)tau);
+    place.lo += (uint32_t)tau;
+    place.bits = 0;
+}
+
+__device__ __forceinline__ uint32_t median(uint32_t a, uint32_t b, uint32_t c)
+{
+    uint32_t m;
+    asm("v_med3_u32 %0, %1, %2, %3" : "=v"(m) : "v"(a), "v"(b), "v"(c));
+    return m;
 }
 
 // Eight lanes with eight nibbles each: lane l receives nibble l of every lane, of lane m in nibble m.  (Three exchanges on the vector ALU.)
@@ -236,6 +288,12 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
 {
     constexpr int NW = THREADS / 64;
     constexpr int ITEM = THREADS * 4;                 // positions per item (one uint4 per thread)
+    // A boundary bin of a long row holds tens of entries: three to ten rows in a hundred then met two of them in the boundary bin of the
+    // next pass and took one more (1.9 us), and a call waits for its slowest row.  Up to 128 entries go into a list instead and are
+    // compared with each other.  Rows x entries, bins / list, us: 64 x 13001 10.4 / 9.4, 4 x 16384 10.2 / 9.3, 256 x 16384 11.5 / 10.5,
+    // 256 x 32768 16.9 / 16.3.  Up to 8192 entries the bins are the faster way: few entries, seldom another pass (8 x 8192 7.2 / 7.4,
+    // 8 x 2048 5.2 / 5.5), and where rows come in turns (NV4 = 16) another row fills the wait (1024 x 32768 48.1 / 48.2).
+    constexpr bool LISTS = ITEM * NV4 > 8192 && NV4 <= 8;
     constexpr bool WORDS = NV4 >= 8;                  // compaction by words of 32 positions instead of item by item
     constexpr int TABLE = WORDS ? ITEM / 32 * NV4 : (NV4 * NW + 63) / 64 * 64;
     __shared__ ResidentShared sh;
@@ -291,6 +349,8 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
     }
     // the histograms are cleared while the loads are in flight
     clear_hist<THREADS, RES_HIST>(hist1);
+    if (LISTS && tid < LISTED) { sh.list.entry[tid] = -1; sh.list.not_below[tid] = 0u; }
+    if (LISTS && tid == 0) sh.list.n = 0;
 
     // Largest and smallest entry.  As an unsigned number a sign bit or an exponent of all ones makes an entry too large: then the thread
     // looks closer (-0.0 is zero; negative, infinite and NaN entries make the row invalid).
@@ -379,12 +439,14 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
         while (at.bits > 0 && (at.packed >> CNT_SHIFT) != 1) { // (uniform)
             const int shift = at.bits > DIGIT ? at.bits - DIGIT : 0;
             const uint32_t first = at.lo ? at.lo : 1u, width = (1u << at.bits) - (first - at.lo);
-            clear_hist<THREADS, DIGIT_BINS>(used);             // (read out; the next pass takes it)
+            const bool listed = LISTS && at.bits <= FINE_SHIFT && (at.packed >> CNT_SHIFT) <= LISTED;              // (uniform)
+            if (!listed) clear_hist<THREADS, DIGIT_BINS>(used);                  // (read out; the next pass takes it)
             uint32_t fraction = 0x7fffffu;
             asm volatile("" : "+s"(fraction));                 // (keeps 64 masked entries from being computed ahead of the loop)
             auto add = [&](uint32_t y) {                       // y: distance from `first`
                 const uint32_t z = y + (first - at.lo);
-                atomicAdd(&cur[z >> shift], CNT_ONE | ((at.lo + z) & fraction));
+                if (listed) sh.list.entry[atomicAdd(&sh.list.n, 1)] = (int)z;
+                else atomicAdd(&cur[z >> shift], CNT_ONE | ((at.lo + z) & fraction));
             };
             // A bin of few entries: no thread is likely to hold more than two of them, and those are its smallest distances, three
             // instructions per entry and no branch (compared one by one, 64 entries took 3.1 us of 1024 rows' 24 per pair, now 1.9).
@@ -406,6 +468,10 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
             if (one_by_one)
                 for_entries([&](uint32_t x) { if (x - first < width) add(x - first); });
             __syncthreads();
+            if (listed) {
+                locate_listed<NW>(sh.list, a.top_p, at);
+                break;
+            }
             if (wave == 0) {
                 locate_next(cur, shift, a.top_p, at);
                 if (lane == 0) sh.place = at;

@@ -399,3 +399,26 @@ def test_passes_over_rows_of_every_kind(rows, n):
         least = -126 + cut[-1] if cut.size else -127
         keep = np.flatnonzero((row > 0) & (e > least))
         assert got["counts"][r] == keep.size and np.array_equal(got["indices"][r, :keep.size], keep), r
+
+
+@pytest.mark.parametrize("values", ["distinct", "tied", "equal"])
+@pytest.mark.parametrize("rows,n", [(1, 8193), (1, 16384), (258, 12001), (1, 32767), (258, 20480), (258, 32768), (300, 40001)])
+def test_boundary_bins_of_few_entries(rows, n, values):
+    """Rows whose threshold lies at the first, a middle and the last entry of a boundary bin (1 to 1 + 1/64) of k entries, below, at and
+    beyond the longest list that is compared entry by entry and its halves."""
+    rng = np.random.default_rng(n)
+    made, taus = [], []
+    for k in (1, 2, 3, 4, 5, 31, 32, 33, 63, 64, 65, 66, 127, 128, 129, 200):
+        steps = {"distinct": rng.permutation(1 << 17)[:k], "tied": rng.integers(0, 3, k) * 43690, "equal": np.full(k, 77)}[values]
+        bin_entries = np.sort(1.0 + steps * 2.0 ** -23)[::-1]
+        for j in sorted({0, k // 2, k - 1}):                   # the threshold is the j-th largest
+            large = np.full(k // 2 + 1, 4.0)
+            reach = large.sum() + bin_entries[:j].sum() + 0.5 * bin_entries[j]
+            small = rng.random(n - k - large.size) + 0.5       # they bring the row's sum to twice what is to be reached
+            small *= (2.0 * reach - large.sum() - bin_entries.sum()) / small.sum()
+            assert small.max() < 0.9
+            made.append(rng.permutation(np.concatenate([large, bin_entries, small])).astype(np.float32))
+            taus.append(np.float32(bin_entries[j]))
+    probs = np.stack(made)[np.arange(max(rows, len(made))) % len(made)].reshape(1, -1, n)
+    got, _ = _check(probs, 0.5)
+    assert np.array_equal(got["tau"], np.array(taus)[np.arange(probs.shape[1]) % len(taus)])
