@@ -1044,7 +1044,7 @@ bool select_takes_chunks(int rows, int n_tokens, int n_chunks)
 {
     // A launch and the masses' way through memory less, and with many rows a row's reads overlap other rows' passes; few
     // long rows are read faster by more workgroups than they have.  Measured, us, masses by a kernel of their own / added
-    // up in the selection (rows x positions / chunk): 32 x 2044 / 16 11.1 / 7.4, 64 x 16384 / 8 12.1 / 9.0, 8 x 32768 / 8
+    // up in the selection (rows x positions / chunk): 32 x 2044 / 16 11.1 / 5.7, 64 x 16384 / 8 12.1 / 9.0, 8 x 32768 / 8
     // 13.1 / 11.9, 384 x 32768 / 16 24.3 / 15.1, 2048 x 32768 / 8 91.4 / 75.3; 8 x 40000 / 32 12.2 / 10.2, x 65536 / 32 12.6 /
     // 13.6, x 131072 / 64 14.4 / 20.6; 32 x 65536 / 32 13.3 / 13.8; 128 x 65536 / 32 22.7 / 14.8, x 131072 / 64 34.7 / 25.5;
     // 512 x 65536 / 32 143 / 34.7.

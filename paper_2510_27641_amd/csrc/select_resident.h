@@ -235,10 +235,9 @@ template <int NW> __device__ __forceinline__ void locate_listed(BinList &list, f
     s1 = two ? list.not_below[lane + 64] : 0u;
     const int e_field = (int)(place.lo >> 23);
     const double goal = top_p < 1.0f ? place.target : INFINITY;
-    // packed counter of `c` entries whose distances add up to `sum`
-    auto counter = [&](unsigned c, uint32_t sum) {
-        return (unsigned long long)c << CNT_SHIFT | ((unsigned long long)c * (place.lo & 0x7fffffu) + sum);
-    };
+    // packed counter of `c` entries whose distances add up to `sum` (at most 128 fractions: below 2^31)
+    const uint32_t fraction = place.lo & 0x7fffffu;
+    auto counter = [&](unsigned c, uint32_t sum) { return (unsigned long long)c << CNT_SHIFT | (c * fraction + sum); };
     auto reaches = [&](int v, uint32_t s) { return v >= 0 && place.m_above + fraction_mass(counter(s >> 24, s & 0xffffffu), e_field) >= goal; };
     const int reached = (int)wave_max(max(reaches(v0, s0) ? v0 + 1 : 0, reaches(v1, s1) ? v1 + 1 : 0));
     const int tau = reached ? reached - 1 : (int)~wave_max(~min((uint32_t)v0, (uint32_t)v1));
@@ -258,6 +257,49 @@ __device__ __forceinline__ uint32_t median(uint32_t a, uint32_t b, uint32_t c)
     uint32_t m;
     asm("v_med3_u32 %0, %1, %2, %3" : "=v"(m) : "v"(a), "v"(b), "v"(c));
     return m;
+}
+
+// Rows of at most BRIEF chunks: every wave adds up, for each entry, those of a part of the row that are not below it, and then takes the
+// whole decision by itself (`v0`, `v1`: the row's entries, two to a lane, zeros behind its end).  A sum takes its terms in the same order for
+// every entry, so sums never decrease towards smaller entries.  Uniform over the workgroup, one barrier.
+constexpr int BRIEF = 128;
+template <int NW> __device__ __forceinline__ Place locate_brief(const uint32_t *entries, uint32_t v0, uint32_t v1, int len, double *sums, float top_p)
+{
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool two = len > 64;                                 // (uniform)
+    double m0 = 0.0, m1 = 0.0;
+    for (int j = wave * (BRIEF / NW); j < (wave + 1) * (BRIEF / NW) && j < len; j += 4) {
+        const uint4 w = *reinterpret_cast<const uint4 *>(entries + j);           // (all lanes read the same four)
+        auto add = [&](uint32_t x) {
+            m0 += (double)__uint_as_float(x >= v0 ? x : 0u);
+            if (two) m1 += (double)__uint_as_float(x >= v1 ? x : 0u);
+        };
+        add(w.x); add(w.y); add(w.z); add(w.w);
+    }
+    sums[wave * BRIEF + lane] = m0;
+    sums[wave * BRIEF + 64 + lane] = m1;
+    __syncthreads();
+    m0 = m1 = 0.0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        m0 += sums[w * BRIEF + lane];
+        m1 += sums[w * BRIEF + 64 + lane];
+    }
+    const uint32_t least = ~wave_max(max(v0 ? ~v0 : 0u, v1 ? ~v1 : 0u));
+    auto sum_at = [&](uint32_t v) {                            // of the entries from v up, v one of them
+        const unsigned long long at0 = __ballot(v0 == v), at1 = __ballot(v1 == v);
+        return at0 ? read_lane(m0, (int)__ffsll((long long)at0) - 1) : read_lane(m1, (int)__ffsll((long long)at1) - 1);
+    };
+    Place out;
+    out.target = (double)top_p * sum_at(least);
+    const uint32_t tau = wave_max(max(v0 && m0 >= out.target ? v0 : 0u, v1 && m1 >= out.target ? v1 : 0u));
+    const unsigned ties = (unsigned)(__popcll(__ballot(v0 == tau)) + __popcll(__ballot(v1 == tau)));
+    out.c_above = (unsigned)(__popcll(__ballot(v0 > tau)) + __popcll(__ballot(v1 > tau)));
+    out.m_above = sum_at(tau) - (double)ties * (double)__uint_as_float(tau);
+    out.packed = (unsigned long long)ties << CNT_SHIFT | (ties * (tau & 0x7fffffu));
+    out.lo = tau;
+    out.bits = 0;
+    return out;
 }
 
 // Eight lanes with eight nibbles each: lane l receives nibble l of every lane, of lane m in nibble m.  (Three exchanges on the vector ALU.)
@@ -319,14 +361,20 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
     uint4 data[NV4];
     uint4 tailv = make_uint4(0, 0, 0, 0);
     const int tail_p = (len & 3) ? (len & ~3) : -1;            // start of the partial vector, if any
+    // Chunk lists of up to 2048 positions are mostly this short.  Bins / comparisons, rows x positions / chunk, us: 32 x 2044 / 16 7.8 / 5.7,
+    // 8 x 1024 / 16 5.0 / 4.3, 1024 x 2044 / 16 8.9 / 8.3; the work grows with the square of the chunks, and 256 of them take 6.1 with
+    // bins.  (top_p = 1 has a rule of its own for entries that add nothing.)
+    const bool brief = CHUNKED && len <= BRIEF && a.top_p < 1.0f;              // (uniform)
+    uint32_t *const entries = reinterpret_cast<uint32_t *>(select_dyn);
     if constexpr (CHUNKED) {
         static_assert(ITEM * NV4 * 4 <= (int)select_lds(THREADS), "a row's masses wait in dynamic LDS");
+        static_assert(BRIEF <= ITEM && BRIEF * (4 + NW * 8) <= (int)select_lds(THREADS), "and with them the sums of locate_brief");
         float *mass = reinterpret_cast<float *>(select_dyn);
         for (int c = tid; c < ITEM * NV4; c += THREADS) mass[c] = c < len ? chunk_mass(row, positions, c, a.chunk_shift) : 0.0f;
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < NV4; ++i) data[i] = reinterpret_cast<const uint4 *>(mass)[i * THREADS + tid];
-        __syncthreads();
+        if (!brief) __syncthreads();
     } else {
         if (tail_p >= 0 && tid == (tail_p % ITEM) / 4) {
             tailv.x = __float_as_uint(row[tail_p]);
@@ -348,51 +396,58 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
         }
     }
     // the histograms are cleared while the loads are in flight
-    clear_hist<THREADS, RES_HIST>(hist1);
+    if (!brief) clear_hist<THREADS, RES_HIST>(hist1);
     if (LISTS && tid < LISTED) { sh.list.entry[tid] = -1; sh.list.not_below[tid] = 0u; }
     if (LISTS && tid == 0) sh.list.n = 0;
 
     // Largest and smallest entry.  As an unsigned number a sign bit or an exponent of all ones makes an entry too large: then the thread
     // looks closer (-0.0 is zero; negative, infinite and NaN entries make the row invalid).
-    uint32_t top = 0u, least = 0xffffffffu;
-    auto range = [&](const uint4 &u) {
-        const uint32_t x = u.x > u.y ? u.x : u.y, y = u.z > u.w ? u.z : u.w, v = u.x < u.y ? u.x : u.y, w = u.z < u.w ? u.z : u.w;
-        top = x > top ? x : top;
-        top = y > top ? y : top;
-        least = v < least ? v : least;
-        least = w < least ? w : least;
-    };
-#pragma unroll
-    for (int i = 0; i < NV4; ++i) {
-        if (!CHUNKED && (i + 1) * ITEM > len) {                // (uniform) an item that the row does not fill
-            const int p = (i * THREADS + tid) * 4;
-            if (p + 3 >= len) data[i] = p == tail_p ? tailv : make_uint4(0, 0, 0, 0);
-        }
-        if (i < n_items) range(data[i]);
-    }
-    if (top >= 0x7f800000u) {
-        bool bad = false;
-        auto clean = [&](uint32_t x) -> uint32_t {
-            x = x == 0x80000000u ? 0u : x;
-            bad = bad || x >= 0x7f800000u;
-            return x;
+    uint32_t row_top = 0u, wave_least = 0u, v0 = 0u, v1 = 0u;
+    if (brief) {                                               // (masses are never -0.0)
+        v0 = entries[lane];
+        v1 = entries[64 + lane];
+        row_top = wave_max(max(v0, v1));
+    } else {
+        uint32_t top = 0u, least = 0xffffffffu;
+        auto range = [&](const uint4 &u) {
+            const uint32_t x = u.x > u.y ? u.x : u.y, y = u.z > u.w ? u.z : u.w, v = u.x < u.y ? u.x : u.y, w = u.z < u.w ? u.z : u.w;
+            top = x > top ? x : top;
+            top = y > top ? y : top;
+            least = v < least ? v : least;
+            least = w < least ? w : least;
         };
-        top = 0u;
-        least = 0xffffffffu;
 #pragma unroll
         for (int i = 0; i < NV4; ++i) {
-            data[i] = make_uint4(clean(data[i].x), clean(data[i].y), clean(data[i].z), clean(data[i].w));
+            if (!CHUNKED && (i + 1) * ITEM > len) {                // (uniform) an item that the row does not fill
+                const int p = (i * THREADS + tid) * 4;
+                if (p + 3 >= len) data[i] = p == tail_p ? tailv : make_uint4(0, 0, 0, 0);
+            }
             if (i < n_items) range(data[i]);
         }
-        if (bad) top = 0xffffffffu;
-    }
-    const uint32_t wave_top = wave_max(top), wave_least = ~wave_max(~least);
-    if (lane == 0) sh.top[wave] = wave_top;
-    __syncthreads();                                           // (also: the histograms are clear)
-    uint32_t row_top = 0u;
+        if (top >= 0x7f800000u) {
+            bool bad = false;
+            auto clean = [&](uint32_t x) -> uint32_t {
+                x = x == 0x80000000u ? 0u : x;
+                bad = bad || x >= 0x7f800000u;
+                return x;
+            };
+            top = 0u;
+            least = 0xffffffffu;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) row_top = sh.top[w] > row_top ? sh.top[w] : row_top;
-    row_top = (uint32_t)__builtin_amdgcn_readfirstlane((int)row_top);
+            for (int i = 0; i < NV4; ++i) {
+                data[i] = make_uint4(clean(data[i].x), clean(data[i].y), clean(data[i].z), clean(data[i].w));
+                if (i < n_items) range(data[i]);
+            }
+            if (bad) top = 0xffffffffu;
+        }
+        const uint32_t wave_top = wave_max(top);
+        wave_least = ~wave_max(~least);
+        if (lane == 0) sh.top[wave] = wave_top;
+        __syncthreads();                                           // (also: the histograms are clear)
+#pragma unroll
+        for (int w = 0; w < NW; ++w) row_top = sh.top[w] > row_top ? sh.top[w] : row_top;
+        row_top = (uint32_t)__builtin_amdgcn_readfirstlane((int)row_top);
+    }
     uint32_t *mask_out = a.kept_mask ? a.kept_mask + (int64_t)r * a.blocks_per_row * (SEL_BLOCK / 32) : nullptr;
     const int mask_words = a.blocks_per_row * (SEL_BLOCK / 32);
     if (row_top == 0u || row_top >= 0x7f800000u) {             // an invalid entry, or no mass at all
@@ -413,74 +468,79 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
             if (i < n_items) { fn(data[i].x); fn(data[i].y); fn(data[i].z); fn(data[i].w); }
     };
 
-    // ---- first pass: 64 bins per octave from exponent field e_low up ----------------------------------------------
-    const int e_top = (int)(row_top >> 23), e_low = (e_top > FINE_OCTAVES ? e_top : FINE_OCTAVES) - (FINE_OCTAVES - 1);      // (>= 1)
-    {
-        unsigned long long *base = hist1 - (e_low << (23 - FINE_SHIFT));
-        if (wave_least >= (uint32_t)e_low << 23) {             // (uniform over the wave) no zeros, nothing below the window
-            for_entries([&](uint32_t x) { atomicAdd(base + (x >> FINE_SHIFT), fraction_entry(x)); });
-        } else {
-            for_entries([&](uint32_t x) {
-                if (x) atomicAdd((int)(x >> 23) >= e_low ? base + (x >> FINE_SHIFT) : hist1 + FINE + (x >> 23), fraction_entry(x));
-            });
-        }
-    }
-    __syncthreads();
-    if (wave == 0) {
-        Place p;
-        locate_first(hist1, e_low, a.top_p, p);
-        if (lane == 0) sh.place = p;
-    }
-    __syncthreads();
-    // ---- later passes, ten bits each, inside the boundary bin (zeros left out), until it holds a single entry or value ---
-    Place at = sh.place;
-    {
-        unsigned long long *cur = hist2, *used = hist1;
-        while (at.bits > 0 && (at.packed >> CNT_SHIFT) != 1) { // (uniform)
-            const int shift = at.bits > DIGIT ? at.bits - DIGIT : 0;
-            const uint32_t first = at.lo ? at.lo : 1u, width = (1u << at.bits) - (first - at.lo);
-            const bool listed = LISTS && at.bits <= FINE_SHIFT && (at.packed >> CNT_SHIFT) <= LISTED;              // (uniform)
-            if (!listed) clear_hist<THREADS, DIGIT_BINS>(used);                  // (read out; the next pass takes it)
-            uint32_t fraction = 0x7fffffu;
-            asm volatile("" : "+s"(fraction));                 // (keeps 64 masked entries from being computed ahead of the loop)
-            auto add = [&](uint32_t y) {                       // y: distance from `first`
-                const uint32_t z = y + (first - at.lo);
-                if (listed) sh.list.entry[atomicAdd(&sh.list.n, 1)] = (int)z;
-                else atomicAdd(&cur[z >> shift], CNT_ONE | ((at.lo + z) & fraction));
-            };
-            // A bin of few entries: no thread is likely to hold more than two of them, and those are its smallest distances, three
-            // instructions per entry and no branch (compared one by one, 64 entries took 3.1 us of 1024 rows' 24 per pair, now 1.9).
-            uint32_t y1 = 0xffffffffu, y2 = 0xffffffffu, y3 = 0xffffffffu;       // the three smallest, in order
-            bool one_by_one = (at.packed >> CNT_SHIFT) > THREADS / 2;            // (uniform)
-            if (!one_by_one) {
+    Place at;
+    if (brief) {
+        at = locate_brief<NW>(entries, v0, v1, len, reinterpret_cast<double *>(entries + BRIEF), a.top_p);
+    } else {
+        // ---- first pass: 64 bins per octave from exponent field e_low up ----------------------------------------------
+        const int e_top = (int)(row_top >> 23), e_low = (e_top > FINE_OCTAVES ? e_top : FINE_OCTAVES) - (FINE_OCTAVES - 1);      // (>= 1)
+        {
+            unsigned long long *base = hist1 - (e_low << (23 - FINE_SHIFT));
+            if (wave_least >= (uint32_t)e_low << 23) {             // (uniform over the wave) no zeros, nothing below the window
+                for_entries([&](uint32_t x) { atomicAdd(base + (x >> FINE_SHIFT), fraction_entry(x)); });
+            } else {
                 for_entries([&](uint32_t x) {
-                    const uint32_t y = x - first;
-                    y3 = median(y2, y3, y);
-                    y2 = median(y1, y2, y);
-                    y1 = y < y1 ? y : y1;
+                    if (x) atomicAdd((int)(x >> 23) >= e_low ? base + (x >> FINE_SHIFT) : hist1 + FINE + (x >> 23), fraction_entry(x));
                 });
-                one_by_one = __any(y3 < width);                // (uniform over the wave)
+            }
+        }
+        __syncthreads();
+        if (wave == 0) {
+            Place p;
+            locate_first(hist1, e_low, a.top_p, p);
+            if (lane == 0) sh.place = p;
+        }
+        __syncthreads();
+        // ---- later passes, ten bits each, inside the boundary bin (zeros left out), until it holds a single entry or value ---
+        at = sh.place;
+        {
+            unsigned long long *cur = hist2, *used = hist1;
+            while (at.bits > 0 && (at.packed >> CNT_SHIFT) != 1) { // (uniform)
+                const int shift = at.bits > DIGIT ? at.bits - DIGIT : 0;
+                const uint32_t first = at.lo ? at.lo : 1u, width = (1u << at.bits) - (first - at.lo);
+                const bool listed = LISTS && at.bits <= FINE_SHIFT && (at.packed >> CNT_SHIFT) <= LISTED;              // (uniform)
+                if (!listed) clear_hist<THREADS, DIGIT_BINS>(used);                  // (read out; the next pass takes it)
+                uint32_t fraction = 0x7fffffu;
+                asm volatile("" : "+s"(fraction));                 // (keeps 64 masked entries from being computed ahead of the loop)
+                auto add = [&](uint32_t y) {                       // y: distance from `first`
+                    const uint32_t z = y + (first - at.lo);
+                    if (listed) sh.list.entry[atomicAdd(&sh.list.n, 1)] = (int)z;
+                    else atomicAdd(&cur[z >> shift], CNT_ONE | ((at.lo + z) & fraction));
+                };
+                // A bin of few entries: no thread is likely to hold more than two of them, and those are its smallest distances, three
+                // instructions per entry and no branch (compared one by one, 64 entries took 3.1 us of 1024 rows' 24 per pair, now 1.9).
+                uint32_t y1 = 0xffffffffu, y2 = 0xffffffffu, y3 = 0xffffffffu;       // the three smallest, in order
+                bool one_by_one = (at.packed >> CNT_SHIFT) > THREADS / 2;            // (uniform)
                 if (!one_by_one) {
-                    if (y1 < width) add(y1);
-                    if (y2 < width) add(y2);
+                    for_entries([&](uint32_t x) {
+                        const uint32_t y = x - first;
+                        y3 = median(y2, y3, y);
+                        y2 = median(y1, y2, y);
+                        y1 = y < y1 ? y : y1;
+                    });
+                    one_by_one = __any(y3 < width);                // (uniform over the wave)
+                    if (!one_by_one) {
+                        if (y1 < width) add(y1);
+                        if (y2 < width) add(y2);
+                    }
                 }
+                if (one_by_one)
+                    for_entries([&](uint32_t x) { if (x - first < width) add(x - first); });
+                __syncthreads();
+                if (listed) {
+                    locate_listed<NW>(sh.list, a.top_p, at);
+                    break;
+                }
+                if (wave == 0) {
+                    locate_next(cur, shift, a.top_p, at);
+                    if (lane == 0) sh.place = at;
+                }
+                __syncthreads();
+                at = sh.place;
+                unsigned long long *const swap = cur;
+                cur = used;
+                used = swap;
             }
-            if (one_by_one)
-                for_entries([&](uint32_t x) { if (x - first < width) add(x - first); });
-            __syncthreads();
-            if (listed) {
-                locate_listed<NW>(sh.list, a.top_p, at);
-                break;
-            }
-            if (wave == 0) {
-                locate_next(cur, shift, a.top_p, at);
-                if (lane == 0) sh.place = at;
-            }
-            __syncthreads();
-            at = sh.place;
-            unsigned long long *const swap = cur;
-            cur = used;
-            used = swap;
         }
     }
     // A boundary bin that holds a single entry pins tau*: the bin's fraction sum is that entry's fraction.

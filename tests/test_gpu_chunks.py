@@ -133,3 +133,32 @@ def test_few_long_rows_of_chunks_come_through_memory(rows):
     ref = oracle.topp_select_chunks(probs, 0.9, chunk)
     flagged, mism = compare_select(got, ref)
     assert mism == 0
+
+
+@pytest.mark.parametrize("rows", [9, 603])
+@pytest.mark.parametrize("chunks", [1, 2, 15, 63, 64, 65, 127, 128, 129])
+def test_short_rows_of_chunks(rows, chunks):
+    """Rows of up to 128 chunks compare their masses with each other: of every kind, shorter ones among them, the last chunk partial."""
+    n = chunks * 16 - 3
+    rng = np.random.default_rng(chunks)
+    z = rng.standard_normal((9, n))
+    kinds = np.exp(2.0 * z)
+    kinds[1] = 1.0                                             # ties (but for the last chunk)
+    kinds[2] = np.where(np.arange(n) // 16 % 3 == 1, kinds[2], 0.0)           # chunks without mass
+    kinds[2, 0] += 1.0
+    kinds[3] = kinds[3] * 2.0 ** -140                          # subnormal entries and masses
+    kinds[4] = 2.0 ** -(np.arange(n) // 16).astype(float)      # one octave down per chunk
+    kinds[5, -1] = np.inf
+    kinds[6] = 3e38                                            # finite entries, infinite masses
+    kinds[7] = 0.0
+    kinds[8] = np.exp(10.0 * z[8])
+    lens = np.where(np.arange(rows) % 2 == 0, n, np.maximum(1, n - np.arange(rows) % n)).astype(np.int32)
+    lens[:9] = n
+    probs = np.ascontiguousarray(kinds.astype(np.float32)[np.arange(rows) % 9])
+    for p in (0.3, 0.9, 0.99999, 1.0):
+        got = gpu_select_chunks(probs.reshape(rows, 1, n), p, 16, seq_lens=lens)
+        ref = oracle.topp_select_chunks(probs, p, 16, lens=lens)
+        _, mism = compare_select(got, ref)
+        assert mism == 0 or p == 1.0                           # (there the oracle stops one entry at a time)
+        if n > 16:
+            assert got["flags"][5] & sa.ROW_INVALID and got["flags"][6] & sa.ROW_INVALID and got["flags"][7] & sa.ROW_INVALID
