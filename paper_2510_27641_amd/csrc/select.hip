@@ -471,7 +471,7 @@ __global__ __launch_bounds__(STREAM_THREADS, 4) void topp_select_stream_kernel(S
 
 template <int THREADS, int NV4, bool CHUNKED = false> specattn_status launch_one(const SelectLaunch &a, hipStream_t stream)
 {
-    hipLaunchKernelGGL((topp_select_kernel<THREADS, NV4, CHUNKED>), dim3(a.B * a.H_kv), dim3(THREADS), select_lds(THREADS), stream, a);
+    hipLaunchKernelGGL((topp_select_kernel<THREADS, NV4, CHUNKED>), dim3(a.B * a.H_kv), dim3(THREADS), select_lds(THREADS, NV4), stream, a);
     return check_launch("topp_select_kernel");
 }
 

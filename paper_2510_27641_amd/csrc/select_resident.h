@@ -317,11 +317,14 @@ __device__ __forceinline__ uint32_t transpose_nibbles(uint32_t x, int lane)
 }
 
 // Dynamic LDS: the histograms, and afterwards in their place the buffer in which a row's list is put together in list order for
-// contiguous stores (smaller for the small workgroups, several of which share a CU; longer lists take several rounds).
-constexpr unsigned stage_entries(int threads) { return threads <= 256 ? 4096u : 8192u; }
-constexpr unsigned select_lds(int threads)
+// contiguous stores, 16 bits to a position.  Longer lists take several rounds, and every round walks all of the row's kept bits: so it
+// holds 24576 positions of rows beyond 16384, 16384 below that and, at 256 threads, several of which share a CU, 13312.  Lists with top_p =
+// 0.99, 8192 positions of 32 bits (4096 at 256 threads) / now, us: 24 x 33054 24.2 / 18.4, 64 x 32768 20.7 / 15.9, 1024 x 32768 68.2 / 55.0,
+// 512 x 65536 94.0 / 78.6, 2048 x 16384 61.3 / 48.5, 1024 x 8192 20.4 / 17.4; top_p = 0.97, 1024 x 32768 59.6 / 52.1.
+constexpr unsigned select_lds(int threads, int nv4)
 {
-    return stage_entries(threads) * 4 > RES_HIST * 8 ? stage_entries(threads) * 4 : RES_HIST * 8;
+    const unsigned hist = RES_HIST * 8, stage = threads * nv4 * 4 > 16384 ? 49152 : threads > 256 ? 32768 : 0;
+    return stage > hist ? stage : hist;
 }
 
 // CHUNKED: a.probs are rows of positions; the workgroup adds the chunks up itself, into the LDS that the histograms take over.
@@ -367,8 +370,8 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
     const bool brief = CHUNKED && len <= BRIEF && a.top_p < 1.0f;              // (uniform)
     uint32_t *const entries = reinterpret_cast<uint32_t *>(select_dyn);
     if constexpr (CHUNKED) {
-        static_assert(ITEM * NV4 * 4 <= (int)select_lds(THREADS), "a row's masses wait in dynamic LDS");
-        static_assert(BRIEF <= ITEM && BRIEF * (4 + NW * 8) <= (int)select_lds(THREADS), "and with them the sums of locate_brief");
+        static_assert(ITEM * NV4 * 4 <= (int)select_lds(THREADS, NV4), "a row's masses wait in dynamic LDS");
+        static_assert(BRIEF <= ITEM && BRIEF * (4 + NW * 8) <= (int)select_lds(THREADS, NV4), "and with them the sums of locate_brief");
         float *mass = reinterpret_cast<float *>(select_dyn);
         for (int c = tid; c < ITEM * NV4; c += THREADS) mass[c] = c < len ? chunk_mass(row, positions, c, a.chunk_shift) : 0.0f;
         __syncthreads();
@@ -567,17 +570,29 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
     const int32_t *ptab = (a.emit_physical && a.page_table) ? a.page_table + (int64_t)b * a.max_pages : nullptr;
     // The list is put together in LDS, in list order, and goes out with contiguous stores over the whole workgroup: whole cache
     // lines, whatever the kept counts of the single waves are.  Lists longer than the buffer take several rounds.
-    constexpr unsigned CH = stage_entries(THREADS);
-    int32_t *stage = reinterpret_cast<int32_t *>(select_dyn);
+    constexpr unsigned CH = select_lds(THREADS, NV4) / 2;
+    static_assert(ITEM * NV4 <= 65536 && CH % 4 == 0, "positions of 16 bits, copied out by fours");
+    uint16_t *stage = reinterpret_cast<uint16_t *>(select_dyn);
     const unsigned cap = kept < (unsigned)a.idx_capacity ? kept : (unsigned)a.idx_capacity;
     const bool one_round = kept <= CH;                         // (uniform) every rank of the row fits the buffer, also those beyond a smaller capacity
     auto copy_out = [&](unsigned c0) {
         __syncthreads();
         const unsigned nround = (cap - c0) < CH ? (cap - c0) : CH;
-        for (unsigned k = tid; k < nround; k += THREADS) {
-            int32_t val = stage[k];
-            if (ptab) val = (ptab[val >> a.page_shift] << a.page_shift) | (val & ((1 << a.page_shift) - 1));
-            out[c0 + k] = val;
+        auto place = [&](int32_t val) { return ptab ? (ptab[val >> a.page_shift] << a.page_shift) | (val & ((1 << a.page_shift) - 1)) : val; };
+        if constexpr (WORDS) {
+            typedef int32_t i32x4a __attribute__((ext_vector_type(4), aligned(4)));              // (a list starts anywhere)
+            for (unsigned k = tid * 4; k < nround; k += ITEM) {
+                const ushort4 v = *reinterpret_cast<const ushort4 *>(stage + k);   // (reaches past the list, not past the buffer)
+                if (k + 4 <= nround) {
+                    *reinterpret_cast<i32x4a *>(out + c0 + k) = (i32x4a){place(v.x), place(v.y), place(v.z), place(v.w)};
+                } else {
+                    out[c0 + k] = place(v.x);
+                    if (k + 1 < nround) out[c0 + k + 1] = place(v.y);
+                    if (k + 2 < nround) out[c0 + k + 2] = place(v.z);
+                }
+            }
+        } else {                                               // (short lists: by fours 8 rows of 1024 take 0.1 us longer)
+            for (unsigned k = tid; k < nround; k += THREADS) out[c0 + k] = place(stage[k]);
         }
     };
     if constexpr (WORDS) {
@@ -635,10 +650,10 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
                 unsigned rank = table[at_word[gr]] - c0;       // (wraps around below c0)
                 const int p = at_word[gr] * 32;
                 if (one_round) {
-                    for (; left; left &= left - 1, ++rank) stage[rank] = p + __ffs((int)left) - 1;
+                    for (; left; left &= left - 1, ++rank) stage[rank] = (uint16_t)(p + __ffs((int)left) - 1);
                 } else if (rank < CH || rank + 32u < CH + 32u) {
                     for (; left; left &= left - 1, ++rank)
-                        if (rank < CH) stage[rank] = p + __ffs((int)left) - 1;
+                        if (rank < CH) stage[rank] = (uint16_t)(p + __ffs((int)left) - 1);
                 }
             }
             copy_out(c0);
@@ -694,7 +709,7 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
                 const int p = (i * THREADS + tid) * 4;
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
-                    if (f[k] && (one_round || o < CH)) stage[o] = p + k;
+                    if (f[k] && (one_round || o < CH)) stage[o] = (uint16_t)(p + k);
                     o += f[k] ? 1u : 0u;
                 }
             }
