@@ -579,10 +579,10 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
         __syncthreads();
         const unsigned nround = (cap - c0) < CH ? (cap - c0) : CH;
         auto place = [&](int32_t val) { return ptab ? (ptab[val >> a.page_shift] << a.page_shift) | (val & ((1 << a.page_shift) - 1)) : val; };
+        // Streaming stores: a list is read by later launches on any XCD, and what waits in an L2 as changed lines is written back at the
+        // launch's end (without / with, us: verify step of 16 layers 811.5 / 796.2, 512 ragged rows of up to 65536 609 / 598, 2048 x
+        // 16384 42.2 / 39.7, 64 rows of 13001 with attention 46.1 / 45.8; mask words that way: a union of 1024 members 180.9 / 181.6).
         if constexpr (WORDS) {
-            // Streaming stores: a list is read by later launches on any XCD, and what waits in an L2 as changed lines is written back at
-            // the launch's end (verify step of 16 layers 811.5 / 796.2 us, 512 ragged rows of up to 65536 609 / 598, 2048 x 16384 42.2 /
-            // 39.7 without / with).
             typedef int32_t i32x4a __attribute__((ext_vector_type(4), aligned(4)));              // (a list starts anywhere)
             for (unsigned k = tid * 4; k < nround; k += ITEM) {
                 const ushort4 v = *reinterpret_cast<const ushort4 *>(stage + k);   // (reaches past the list, not past the buffer)
@@ -595,7 +595,7 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
                 }
             }
         } else {                                               // (short lists: by fours 8 rows of 1024 take 0.1 us longer)
-            for (unsigned k = tid; k < nround; k += THREADS) out[c0 + k] = place(stage[k]);
+            for (unsigned k = tid; k < nround; k += THREADS) __builtin_nontemporal_store(place(stage[k]), out + c0 + k);
         }
     };
     if constexpr (WORDS) {
