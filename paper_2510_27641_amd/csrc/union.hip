@@ -283,7 +283,8 @@ __global__ __launch_bounds__(U_THREADS) void union_words_kernel(UnionLaunch a, W
         const int o = before + base_of[k] + __popcll(v & ((1ull << lane) - 1ull));
         if (((v >> lane) & 1ull) && o < a.idx_capacity) {
             const int pos = q0 * 128 + k * 64 + lane;
-            out[o] = ptab ? ((ptab[pos >> a.page_shift] << a.page_shift) | (pos & ((1 << a.page_shift) - 1))) : pos;
+            // (a streaming store, as the selection writes its lists: 1024 members with attention 176.8 us without, 174.8 with)
+            __builtin_nontemporal_store(ptab ? ((ptab[pos >> a.page_shift] << a.page_shift) | (pos & ((1 << a.page_shift) - 1))) : pos, out + o);
         }
     }
 }
