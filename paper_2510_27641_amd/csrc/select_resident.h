@@ -369,9 +369,10 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
     // bins.  (top_p = 1 has a rule of its own for entries that add nothing.)
     const bool brief = CHUNKED && len <= BRIEF && a.top_p < 1.0f;              // (uniform)
     uint32_t *const entries = reinterpret_cast<uint32_t *>(select_dyn);
+    constexpr int BRIEF_SUMS = ITEM * NV4 * 4;                // byte at which the sums start
     if constexpr (CHUNKED) {
-        static_assert(ITEM * NV4 * 4 <= (int)select_lds(THREADS, NV4), "a row's masses wait in dynamic LDS");
-        static_assert(BRIEF <= ITEM && BRIEF * (4 + NW * 8) <= (int)select_lds(THREADS, NV4), "and with them the sums of locate_brief");
+        static_assert(BRIEF <= ITEM && BRIEF_SUMS >= ITEM * NV4 * 4 && BRIEF_SUMS % 8 == 0 && BRIEF_SUMS + NW * BRIEF * 8 <= (int)select_lds(THREADS, NV4),
+                      "a row's masses wait in dynamic LDS, and behind all of them the sums of locate_brief: waves that still read masses meet no sums");
         float *mass = reinterpret_cast<float *>(select_dyn);
         for (int c = tid; c < ITEM * NV4; c += THREADS) mass[c] = c < len ? chunk_mass(row, positions, c, a.chunk_shift) : 0.0f;
         __syncthreads();
@@ -473,7 +474,7 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
 
     Place at;
     if (brief) {
-        at = locate_brief<NW>(entries, v0, v1, len, reinterpret_cast<double *>(entries + BRIEF), a.top_p);
+        at = locate_brief<NW>(entries, v0, v1, len, reinterpret_cast<double *>(entries + BRIEF_SUMS / 4), a.top_p);
     } else {
         // ---- first pass: 64 bins per octave from exponent field e_low up ----------------------------------------------
         const int e_top = (int)(row_top >> 23), e_low = (e_top > FINE_OCTAVES ? e_top : FINE_OCTAVES) - (FINE_OCTAVES - 1);      // (>= 1)

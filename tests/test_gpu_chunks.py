@@ -162,3 +162,17 @@ def test_short_rows_of_chunks(rows, chunks):
         assert mism == 0 or p == 1.0                           # (there the oracle stops one entry at a time)
         if n > 16:
             assert got["flags"][5] & sa.ROW_INVALID and got["flags"][6] & sa.ROW_INVALID and got["flags"][7] & sa.ROW_INVALID
+
+
+@pytest.mark.parametrize("rows,chunks", [(8, 40), (8, 1500), (8, 4096), (520, 40), (520, 1500), (520, 2048), (520, 4000)])
+def test_short_rows_in_calls_of_long_ones(rows, chunks):
+    """Rows of up to 128 chunks beside longer ones, in every shape of workgroup that adds chunks up: what is compared lies in LDS
+    behind all the masses that the workgroup has room for.  Nothing is written behind a row's list."""
+    n = chunks * 4
+    rng = np.random.default_rng(rows + chunks)
+    lens = np.minimum(n, np.array([1, 4, 5, 255, 256, 257, 509, 512, 513, n])[np.arange(rows) % 10]).astype(np.int32)
+    probs = W.draft_probs(rng, rows, n, lens=lens, recency_len=4)
+    got = gpu_select_chunks(probs.reshape(rows, 1, n), 0.97, 4, seq_lens=lens)
+    ref = oracle.topp_select_chunks(probs, 0.97, 4, lens=lens)
+    assert compare_select(got, ref)[1] == 0
+    assert all((got["indices"][r, got["counts"][r]:] == -7).all() for r in range(rows))
