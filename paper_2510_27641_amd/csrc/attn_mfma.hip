@@ -32,6 +32,11 @@ __device__ __forceinline__ float wave_sum(float v)
 // A pass of selection, attention and merge with every divisor and share worked out here from the cost line / with them handed over, us:
 // 32 rows of 2044 positions in chunks with new tokens 24.6 / 21.9, 32 rows of 8192 (d = 64) 22.6 / 21.2, 16 layers of 64 rows of 32768
 // 867 / 839 (the start of the main kernel, below, among it).
+// A partial's (m, l) is the same for all threads, so the compiler takes scalar loads for it: eight of them, which come back in any order
+// and are waited for together, cost 0.12 us more per trip than vector loads that are asked for ahead of the outputs (for the short rest it
+// makes no difference, and 16 layers of 64 rows take 797.6 us with scalar loads there, 798.8 without).  Scalar / vector, us for both launches:
+// one row of 270 tiles among 31 empty ones (268 partials) 31.3 / 27.2, one of 500 among 31 of 3 (131 partials) 21.8 / 19.6, 8 ragged
+// rows of up to 270 13.6 / 13.3; over 440 calls of few rows 4 % on average, none slower.
 template <int D> __global__ __launch_bounds__(D) void merge_partials_kernel(AttnLaunch a, Plan plan, int qtp)
 {
     __shared__ float red[2 * SPECATTN_MAX_T];
@@ -60,14 +65,18 @@ template <int D> __global__ __launch_bounds__(D) void merge_partials_kernel(Attn
         auto trip = [&](int wb, auto most) {        // partials wb .. w1, at most N
             constexpr int N = decltype(most)::value;
             float mw[N], lw[N], ow[N];
+            uint32_t s[N];
 #pragma unroll
             for (int k = 0; k < N; ++k) {           // (behind the last share: that one's again)
-                const uint32_t s = (uint32_t)((min(wb + k, w1) + r) * qtp + q);
-                const float2 ml = reinterpret_cast<const float2 *>(plan.part_ml)[s];
+                s[k] = (uint32_t)((min(wb + k, w1) + r) * qtp + q);
+                if (N == 8) asm("" : "+v"(s[k]));   // (the same in all lanes, but no scalar loads: above)
+                const float2 ml = reinterpret_cast<const float2 *>(plan.part_ml)[s[k]];
                 mw[k] = ml.x;
                 lw[k] = ml.y;
-                ow[k] = plan.part_o[s * D + dv];
             }
+            __builtin_amdgcn_sched_barrier(0);      // the weights first: they are used first
+#pragma unroll
+            for (int k = 0; k < N; ++k) ow[k] = plan.part_o[s[k] * D + dv];
             __builtin_amdgcn_sched_barrier(0);      // all requested before the first is used
 #pragma unroll
             for (int k = 0; k < N; ++k) {           // (a weight of zero must not meet an infinite value)

@@ -336,3 +336,23 @@ def test_rows_and_their_shares(B, H_kv, G, T, n, new_tokens):
         sa.specattn_sparse_decode_attn(att)
         torch.cuda.synchronize()
         assert row_rel_err(out.cpu().numpy(), ref) <= TOL["f16"]
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("B,H_kv", [(1, 2), (2, 4), (2, 8), (8, 8), (13, 5)])
+@pytest.mark.parametrize("others", [0, 3])
+def test_one_long_row_among_short_ones(d, B, H_kv, others):
+    """One row holds nearly all of the line, the others a few positions or none: 64, 128 and 256 shares, and 65 rows."""
+    n, T = 9001, 5
+    rng = np.random.default_rng(B * 10 + H_kv)
+    w = W.llama8b_layer(seed=d, B=B, n=n, H_q=2 * H_kv, H_kv=H_kv, T=T, d=d, dtype="f16")
+    keep = np.full((B, H_kv), others)
+    keep[B // 2, H_kv // 2] = n
+    mask = (rng.permuted(np.broadcast_to(np.arange(n), (B, H_kv, n)), axis=2) < keep[..., None]).astype(np.uint8)
+    q, k, v = kv_tensors(w)
+    idx, cnt = lists(mask)
+    out, lse = gpu_attention(q, k, v, idx, cnt)
+    ref, want_lse = oracle_attention(w, mask)
+    assert row_rel_err(out, ref) <= TOL["f16"]
+    fin = np.isfinite(want_lse)
+    assert np.array_equal(np.isneginf(lse), ~fin) and np.abs(lse[fin] - want_lse[fin]).max() <= 1e-3
