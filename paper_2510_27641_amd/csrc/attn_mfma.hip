@@ -201,8 +201,11 @@ size_t attn_mfma_workspace_min_bytes(int rows, int G, int T, int d)
 // is a few tiles, which the waves of a workgroup take at the same time anyway, and what counts is how many partials the merge has to go
 // through, eight to a trip to memory, and how many shares hold nothing but a row's start.  So 64, doubled where the shares are longer
 // than: 4 units where that leaves a row less than eight partials, 12 (4 where a tile is much work: 64 positions, two query tiles or
-// more) where it leaves it less than sixteen, 10 beyond; and one per workgroup where rows have no more than eight tiles, which is one trip
-// however they are shared out.  Measured with 64 / 128 / 256 shares, us for both launches: 4 rows of 300
+// more) where it leaves it less than sixteen, 10 beyond; and one per workgroup where the rows of the call, empty ones among them, have no more
+// than eight tiles on average: rows of equal counts then take one trip however they are shared out.  (Ragged rows may take more there.  With
+// the longest row tested instead, us: one row of 270 tiles among 15 empty ones 27.2 / 18.3, one of 40 among 15 of 3 11.6 / 10.6, but one of
+// 12 among 31 of 3 9.2 / 9.6 and, with one query row each, 8.5 / 9.4; with the partials of the longest row tested, 16 rows of 12 9.4 / 10.1.)
+// Measured with 64 / 128 / 256 shares, us for both launches: 4 rows of 300
 // units in all 12.3 / 13.3 / 15.5, of 1176 17.0 / 16.4 / 19.2; 8 rows of 600 13.0 / 13.2 / 14.3, of 1224 16.3 / 14.8 / 16.2 (but of 2200 and
 // 64 query rows, from memory, 1.3 more with 128 than with 256); 16 rows of 272 10.5 / 9.9 / 10.1, of 1200 16.0 / 14.1 / 14.6, of 2448 22.2 / 17.5 / 17.4; 32 rows of 544 10.5 / 10.5 / 10.4, of
 // 800 13.5 / 12.0 / 11.5; d = 64, 40 query rows: 8 rows of 152 11.0 / 11.0 / 10.8, 16 rows of 432 13.1 / 11.7 / 12.9, of 704 15.6 / 14.0 / 13.6.
