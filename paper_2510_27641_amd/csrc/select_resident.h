@@ -3,8 +3,8 @@
 //
 // The passes over the registers are bound by instruction issue and by the LDS unit's 64-bit atomics, and short rows by the chain of
 // barriers and locate steps, so the digits are chosen for few and cheap passes: the first one covers the 32 octaves below the row's
-// largest entry with 64 bins each (2048 bins, and a bin per octave for what lies below them), so that the boundary bin holds three
-// entries of a thousand instead of thirty.  The second pass, over ten more bits, then finds few entries and nearly always leaves a bin
+// largest entry with 64 bins each, so that the boundary bin holds three entries of a thousand instead of thirty.  What lies below these
+// octaves is added up in fp64 for the row's sum and gets bins, one per octave, in a pass of its own if the boundary turns out to lie there.  The second pass, over ten more bits, then finds few entries and nearly always leaves a bin
 // with a single one, which is tau*.  With eight bins per octave over all exponents, as the split selection has them, every wave met
 // entries of the boundary bin in nearly every vector of the second pass, and every other row took a third one.
 // Compaction works on words of 32 kept bits, which costs two instructions per entry, instead of on ranks of single entries.
@@ -13,11 +13,12 @@
 // 2048 x 16384 60.2 / 41.1, 128 x 4096 7.3 / 6.3, 8 x 8192 7.9 / 7.2, 8 x 1024 5.6 / 5.0.
 #pragma once
 
-// Bins of the first pass: FINE of them from the lowest exponent of the window up, then one per exponent field (COARSE) for the entries
-// below the window.  A bin's entries share their exponent, so its mass is an exact integer sum.
-constexpr int FINE_OCTAVES = 32, FINE_SHIFT = 17, FINE = FINE_OCTAVES << (23 - FINE_SHIFT), COARSE = 256;
+// Bins of the first pass: FINE of them from the lowest exponent of the window up.  A bin's entries share their exponent, so its mass is an
+// exact integer sum.  Entries below the window, should they be needed: one bin per exponent field.
+constexpr int FINE_OCTAVES = 32, FINE_SHIFT = 17, FINE = FINE_OCTAVES << (23 - FINE_SHIFT), OCTAVES = 256;
 constexpr int DIGIT = 10, DIGIT_BINS = 1 << DIGIT;               // later passes
-constexpr int RES_HIST = FINE + COARSE + DIGIT_BINS;
+constexpr int RES_HIST = FINE + DIGIT_BINS;
+static_assert(OCTAVES <= DIGIT_BINS, "the octaves below the window use the second histogram");
 
 // Counters here hold the count and the sum of the 23 fraction bits; the hidden bits are put back where a mass is read.
 __device__ __forceinline__ unsigned long long fraction_entry(uint32_t u) { return CNT_ONE | (u & 0x7fffffu); }
@@ -49,6 +50,10 @@ struct ResidentShared {
     BinList list;
     Place place;
     uint32_t top[16];            // largest entry of every wave; all ones: an invalid one
+    double low[16];              // sum of every wave's entries below the window
+    double window_mass;          // of the entries in the window, and how many they are
+    unsigned window_count;
+    int below;                   // the boundary may lie below the window
     unsigned wave_sum[16];
 };
 
@@ -85,93 +90,105 @@ __device__ __forceinline__ int pick_bin(unsigned long long counter, int e_field,
     return pick;
 }
 
-// Decision of the first pass, by the first wave alone.  Its lanes own half an octave of the window each, lane 0 the highest, and four
-// of the octaves below.  top_p = 1 takes the lowest non-empty bin, whatever the rounding of the sums above it; octaves below the window
-// count as empty there from the one down from which on the entries all together add less than one unit in the last place of
-// the row's total (a non-empty half octave of the window always adds more: it lies within 2^-32 of the largest of at most 65536 entries).
-__device__ __forceinline__ void locate_first(const unsigned long long *fine, int e_low, float top_p, Place &out)
+// Decision of the first pass, by the first wave alone.  Its lanes own half an octave of the window each, lane 0 the highest.  (sh.below:
+// the window's entries do not reach the target, or top_p is 1, and there are entries below it.)
+template <int NW> __device__ __forceinline__ void locate_first(const unsigned long long *fine, int e_low, float top_p, ResidentShared &sh)
 {
     const int lane = threadIdx.x;
-    const unsigned long long *coarse = fine + FINE;
-    unsigned long long low4[4];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) low4[g] = coarse[(63 - lane) * 4 + g];
+    double low = lane < NW ? sh.low[lane] : 0.0;
     const unsigned long long sum = row_of_bins<FINE / 64>(fine + (63 - lane) * (FINE / 64), lane & 31);
     const double lm = fraction_mass(sum, e_low + ((63 - lane) >> 1));
     const unsigned lc = (unsigned)(sum >> CNT_SHIFT);
-    double incl = lm, incl_low = 0.0, lm_low = 0.0;
-    unsigned inclc = lc, inclc_low = 0, lc_low = 0;
+    double incl = lm;
+    unsigned inclc = lc;
     wave_prefix(incl, inclc);
     double total = read_lane(incl, 63);
-    const double total_fine = total;
-    int cut = -1;                                              // exponent fields below the window up to this one count as empty
-    const bool below = __any((low4[0] | low4[1] | low4[2] | low4[3]) != 0ull);
-    if (below) {                                               // (uniform) rare
-        auto add_up = [&]() {
-            lm_low = 0.0;
-            lc_low = 0;
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int e = (63 - lane) * 4 + g;
-                if (e > cut) { lm_low += fraction_mass(low4[g], e); lc_low += (unsigned)(low4[g] >> CNT_SHIFT); }
-            }
-            incl_low = lm_low;
-            inclc_low = lc_low;
-            wave_prefix(incl_low, inclc_low);
-        };
-        add_up();
-        total += read_lane(incl_low, 63);
-        if (!(top_p < 1.0f) && total > 0.0) {
-            // sums from the bottom up: the lanes in reverse order, then each lane's octaves
-            double tail = __shfl(lm_low, 63 - lane, 64);
-            unsigned none = 0;
-            wave_prefix(tail, none);
-            tail = __shfl(dpp_double<0x138, 0xf>(tail), 63 - lane, 64);
-            const double ulp = __hiloint2double((((__double2hiint(total) >> 20) & 0x7ff) - 52) << 20, 0);
-            int fields = 0;
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                tail += fraction_mass(low4[g], (63 - lane) * 4 + g);
-                fields += __popcll(__ballot(tail < ulp));
-            }
-            cut = fields - 1;
-            add_up();
-        }
+    const bool any_low = __any(low != 0.0);
+    if (any_low) {                                             // (uniform)
+        unsigned none = 0;
+        wave_prefix(low, none);
+        if (lane == 0) { sh.window_mass = total; sh.window_count = (unsigned)__builtin_amdgcn_readlane((int)inclc, 63); }
+        total += read_lane(low, 63);
     }
+    Place out;
     out.target = (double)top_p * total;                        // Algorithm 2: M_target = p * sum a
-    out.bits = -1;
-    out.packed = 0ull;
-    out.c_above = 0;
-    out.m_above = 0.0;
-    out.lo = 0u;
-    if (!(total > 0.0)) return;
     const double goal = top_p < 1.0f ? out.target : INFINITY;
     // mass and count of the lanes before this one (wave_shr:1)
     const double before = dpp_double<0x138, 0xf>(incl);
     const unsigned beforec = (unsigned)dpp_int<0x138, 0xf>((int)inclc);
     // Masses are non-negative, so the running sum never decreases: the first lane whose sum reaches the target holds the boundary.
     const unsigned long long some = __ballot(lc > 0), holds = __ballot(lc > 0 && before + lm >= goal);
-    unsigned long long some_low = 0ull;
-    if (below && !holds) some_low = __ballot(lc_low > 0);
-    if (some_low) {
-        const double before_low = total_fine + dpp_double<0x138, 0xf>(incl_low);
-        const unsigned beforec_low = (unsigned)__builtin_amdgcn_readlane((int)inclc, 63) + (unsigned)dpp_int<0x138, 0xf>((int)inclc_low);
-        const unsigned long long holds_low = __ballot(lc_low > 0 && before_low + lm_low >= goal);
-        const int at = holds_low ? (int)__ffsll((long long)holds_low) - 1 : 63 - __clzll((long long)some_low);
-        out.m_above = read_lane(before_low, at);
-        out.c_above = (unsigned)__builtin_amdgcn_readlane((int)beforec_low, at);
-        const int e = (63 - at) * 4 + 3 - lane;                // lane 0 looks at the lane's highest octave
-        out.lo = (uint32_t)((63 - at) * 4 + 3 - pick_bin(lane < 4 && e > cut ? coarse[e] : 0ull, e, goal, out.m_above, out.c_above, out.packed)) << 23;
-        out.bits = 23;
-        return;
-    }
-    const int at = holds ? (int)__ffsll((long long)holds) - 1 : 63 - __clzll((long long)some);
+    const int at = holds ? (int)__ffsll((long long)holds) - 1 : some ? 63 - __clzll((long long)some) : 0;
     out.m_above = read_lane(before, at);
     out.c_above = (unsigned)__builtin_amdgcn_readlane((int)beforec, at);
     const int high = (63 - at) * (FINE / 64) + FINE / 64 - 1;  // the boundary lane's highest bin
     const int pick = pick_bin(lane < FINE / 64 ? fine[high - lane] : 0ull, e_low + (high >> (23 - FINE_SHIFT)), goal, out.m_above, out.c_above, out.packed);
     out.lo = ((uint32_t)e_low << 23) + ((uint32_t)(high - pick) << FINE_SHIFT);
     out.bits = FINE_SHIFT;
+    if (lane == 0) {
+        sh.place = out;
+        sh.below = any_low && !holds;
+    }
+}
+
+// Decision among the octaves below the window, by the first wave: lane 0 owns the four highest exponent fields.  top_p = 1 takes the
+// lowest non-empty bin, whatever the rounding of the sums above it; octaves count as empty there from the one down from which on the
+// entries all together add less than one unit in the last place of the row's total (a non-empty half octave of the window always adds
+// more: it lies within 2^-32 of the largest of at most 65536 entries).
+__device__ __forceinline__ void locate_below(const unsigned long long *octave, float top_p, ResidentShared &sh)
+{
+    const int lane = threadIdx.x;
+    unsigned long long four[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) four[g] = octave[(63 - lane) * 4 + g];
+    int cut = -1;                                              // exponent fields up to this one count as empty
+    double lm, incl;
+    unsigned lc, inclc;
+    auto add_up = [&]() {
+        lm = 0.0;
+        lc = 0;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const int e = (63 - lane) * 4 + g;
+            if (e > cut) { lm += fraction_mass(four[g], e); lc += (unsigned)(four[g] >> CNT_SHIFT); }
+        }
+        incl = lm;
+        inclc = lc;
+        wave_prefix(incl, inclc);
+    };
+    add_up();
+    if (!(top_p < 1.0f)) {
+        // sums from the bottom up: the lanes in reverse order, then each lane's octaves
+        const double total = sh.window_mass + read_lane(incl, 63);
+        double tail = __shfl(lm, 63 - lane, 64);
+        unsigned none = 0;
+        wave_prefix(tail, none);
+        tail = __shfl(dpp_double<0x138, 0xf>(tail), 63 - lane, 64);
+        const double ulp = __hiloint2double((((__double2hiint(total) >> 20) & 0x7ff) - 52) << 20, 0);
+        int fields = 0;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            tail += fraction_mass(four[g], (63 - lane) * 4 + g);
+            fields += __popcll(__ballot(tail < ulp));
+        }
+        cut = fields - 1;
+        add_up();
+    }
+    const unsigned long long some = __ballot(lc > 0);
+    if (!some) return;                                         // (the window's lowest bin it is)
+    Place out;
+    out.target = sh.place.target;
+    const double goal = top_p < 1.0f ? out.target : INFINITY;
+    const double before = sh.window_mass + dpp_double<0x138, 0xf>(incl);
+    const unsigned beforec = sh.window_count + (unsigned)dpp_int<0x138, 0xf>((int)inclc);
+    const unsigned long long holds = __ballot(lc > 0 && before + lm >= goal);
+    const int at = holds ? (int)__ffsll((long long)holds) - 1 : 63 - __clzll((long long)some);
+    out.m_above = read_lane(before, at);
+    out.c_above = (unsigned)__builtin_amdgcn_readlane((int)beforec, at);
+    const int e = (63 - at) * 4 + 3 - lane;                    // lane 0 looks at the lane's highest octave
+    out.lo = (uint32_t)((63 - at) * 4 + 3 - pick_bin(lane < 4 && e > cut ? octave[e] : 0ull, e, goal, out.m_above, out.c_above, out.packed)) << 23;
+    out.bits = 23;
+    if (lane == 0) sh.place = out;
 }
 
 // Decision of a later pass: DIGIT_BINS bins of 2^shift bit patterns each from `place.lo` up.
@@ -323,8 +340,7 @@ __device__ __forceinline__ uint32_t transpose_nibbles(uint32_t x, int lane)
 // 512 x 65536 94.0 / 78.6, 2048 x 16384 61.3 / 48.5, 1024 x 8192 20.4 / 17.4; top_p = 0.97, 1024 x 32768 59.6 / 52.1.
 constexpr unsigned select_lds(int threads, int nv4)
 {
-    const unsigned hist = RES_HIST * 8, stage = threads * nv4 * 4 > 16384 ? 49152 : threads > 256 ? 32768 : 0;
-    return stage > hist ? stage : hist;
+    return threads * nv4 * 4 > 16384 ? 49152 : threads > 256 ? 32768 : 26624;
 }
 
 // CHUNKED: a.probs are rows of positions; the workgroup adds the chunks up itself, into the LDS that the histograms take over.
@@ -344,17 +360,20 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
     __shared__ ResidentShared sh;
     __shared__ __align__(16) unsigned table[TABLE + 4];   // kept entries per word, or per (item, wave), then their exclusive prefix
     extern __shared__ __align__(16) unsigned long long select_dyn[];
-    unsigned long long *hist1 = select_dyn, *hist2 = select_dyn + FINE + COARSE;
+    static_assert(RES_HIST * 8 <= (int)select_lds(THREADS, NV4), "the histograms share the list's buffer");
+    unsigned long long *hist1 = select_dyn, *hist2 = select_dyn + FINE;
     const int r = blockIdx.x;
     const int b = r / a.H_kv, h = r - b * a.H_kv;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int len = a.seq_lens ? a.seq_lens[b] : a.n_tokens;
     len = len < 0 ? 0 : (len > a.n_tokens ? a.n_tokens : len);
     const int positions = len;
     len = (len + (1 << a.chunk_shift) - 1) >> a.chunk_shift;     // rows of chunk masses: length in chunks
     len = len > a.n_max ? a.n_max : len;
     const float *row = a.probs + (int64_t)b * a.stride_b + (int64_t)h * a.stride_h;
-    const int n_items = (len + ITEM - 1) / ITEM;
+    // Items of which this wave holds entries.  (For all waves alike, nearly every wave of a row of odd length held an empty item and took
+    // it for zeros: 1100 x 16000 31.2 us, now 29.4; 2048 x 12000 37.6 / 36.1; 520 x 8000 12.8 / 12.4.)
+    const int n_items = (len - wave * 256 + ITEM - 1) / ITEM;
 
     // Every thread issues plain 16-byte loads with nothing between them that waits for data, so all of a thread's loads are in
     // flight together.  They need no more than the 4-byte alignment of a float: the rows of an odd length start anywhere (entry
@@ -480,21 +499,34 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
         const int e_top = (int)(row_top >> 23), e_low = (e_top > FINE_OCTAVES ? e_top : FINE_OCTAVES) - (FINE_OCTAVES - 1);      // (>= 1)
         {
             unsigned long long *base = hist1 - (e_low << (23 - FINE_SHIFT));
-            if (wave_least >= (uint32_t)e_low << 23) {             // (uniform over the wave) no zeros, nothing below the window
+            const uint32_t least_in = (uint32_t)e_low << 23;
+            // What is below the window counts in the row's sum, zeros not at all.  (With a bin per octave for it in this pass, which every
+            // other lane of a wide row then hit at the same time, and a test for zeros per entry, us: logits of ten times the usual
+            // spread, 200 x 16000 10.9 / 9.7, 8 x 12000 9.3 / 8.6, 200 x 8000 7.9 / 7.5, and the same when nothing is below.)
+            double low = 0.0;
+            if (wave_least >= least_in) {                          // (uniform over the wave) no zeros, nothing below the window
                 for_entries([&](uint32_t x) { atomicAdd(base + (x >> FINE_SHIFT), fraction_entry(x)); });
             } else {
                 for_entries([&](uint32_t x) {
-                    if (x) atomicAdd((int)(x >> 23) >= e_low ? base + (x >> FINE_SHIFT) : hist1 + FINE + (x >> 23), fraction_entry(x));
+                    low += (double)__uint_as_float(x < least_in ? x : 0u);
+                    if (x >= least_in) atomicAdd(base + (x >> FINE_SHIFT), fraction_entry(x));
                 });
+                unsigned none = 0;
+                wave_prefix(low, none);
             }
+            if (lane == 63) sh.low[wave] = low;
         }
         __syncthreads();
-        if (wave == 0) {
-            Place p;
-            locate_first(hist1, e_low, a.top_p, p);
-            if (lane == 0) sh.place = p;
-        }
+        if (wave == 0) locate_first<NW>(hist1, e_low, a.top_p, sh);
         __syncthreads();
+        if (sh.below) {                                            // (uniform) rare
+            for_entries([&](uint32_t x) { if (x && (int)(x >> 23) < e_low) atomicAdd(hist2 + (x >> 23), fraction_entry(x)); });
+            __syncthreads();
+            if (wave == 0) locate_below(hist2, a.top_p, sh);
+            __syncthreads();
+            clear_hist<THREADS, OCTAVES>(hist2);
+            __syncthreads();
+        }
         // ---- later passes, ten bits each, inside the boundary bin (zeros left out), until it holds a single entry or value ---
         at = sh.place;
         {

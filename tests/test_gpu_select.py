@@ -422,3 +422,21 @@ def test_boundary_bins_of_few_entries(rows, n, values):
     probs = np.stack(made)[np.arange(max(rows, len(made))) % len(made)].reshape(1, -1, n)
     got, _ = _check(probs, 0.5)
     assert np.array_equal(got["tau"], np.array(taus)[np.arange(probs.shape[1]) % len(taus)])
+
+
+@pytest.mark.parametrize("rows,n", [(1, 13001), (1, 16384), (300, 16384), (520, 16381), (1, 32767), (300, 32768), (300, 40001), (70, 65536)])
+def test_thresholds_below_the_window(rows, n):
+    """Rows of one large entry and thousands of ones more than 31 octaves below it: the threshold is the first, the middle or the last of
+    their three values, two of which share an octave; with zeros and without."""
+    rng = np.random.default_rng(n)
+    values = np.array([1.9, 1.2, 0.55]) * 2.0 ** -32
+    for zeros in (False, True):
+        count = n // 4 if zeros else (n - 1) // 3
+        row = np.zeros(n) if zeros else np.full(n, values[2])
+        row[:1 + 3 * count] = np.concatenate([[1.0], np.repeat(values, count)])
+        mass = count * values
+        rows_in = np.tile(rng.permutation(row).astype(np.float32), (1, rows, 1))
+        for j in range(3):                                     # (rows the oracle flags are compared, too: the margin is 2e-7 of the sum at least)
+            p = float(np.float32((1.0 + mass[:j].sum() + 0.5 * mass[j]) / row.sum()))
+            got, _ = _check(rows_in, p)
+            assert (got["tau"] == np.float32(values[j])).all()
