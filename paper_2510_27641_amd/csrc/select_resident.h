@@ -355,6 +355,7 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
     // 256 x 32768 16.9 / 16.3.  Up to 8192 entries the bins are the faster way: few entries, seldom another pass (8 x 8192 7.2 / 7.4,
     // 8 x 2048 5.2 / 5.5), and where rows come in turns (NV4 = 16) another row fills the wait (1024 x 32768 48.1 / 48.2).
     constexpr bool LISTS = ITEM * NV4 > 8192 && NV4 <= 8;
+    constexpr bool FLAT = ITEM * NV4 >= 4096;         // flat rows are added up before they reach a counter
     constexpr bool WORDS = NV4 >= 8;                  // compaction by words of 32 positions instead of item by item
     constexpr int TABLE = WORDS ? ITEM / 32 * NV4 : (NV4 * NW + 63) / 64 * 64;
     __shared__ ResidentShared sh;
@@ -425,7 +426,7 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
 
     // Largest and smallest entry.  As an unsigned number a sign bit or an exponent of all ones makes an entry too large: then the thread
     // looks closer (-0.0 is zero; negative, infinite and NaN entries make the row invalid).
-    uint32_t row_top = 0u, wave_least = 0u, v0 = 0u, v1 = 0u;
+    uint32_t row_top = 0u, wave_top = 0u, wave_least = 0u, v0 = 0u, v1 = 0u;
     if (brief) {                                               // (masses are never -0.0)
         v0 = entries[lane];
         v1 = entries[64 + lane];
@@ -463,7 +464,7 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
             }
             if (bad) top = 0xffffffffu;
         }
-        const uint32_t wave_top = wave_max(top);
+        wave_top = wave_max(top);
         wave_least = ~wave_max(~least);
         if (lane == 0) sh.top[wave] = wave_top;
         __syncthreads();                                           // (also: the histograms are clear)
@@ -486,9 +487,27 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
         return;
     }
     auto for_entries = [&](auto &&fn) {
+        int items = n_items;
+        asm volatile("" : "+s"(items));                        // (compared anew in every pass: the outcomes are not held through the kernel)
 #pragma unroll
         for (int i = 0; i < NV4; ++i)
-            if (i < n_items) { fn(data[i].x); fn(data[i].y); fn(data[i].z); fn(data[i].w); }
+            if (i < items) { fn(data[i].x); fn(data[i].y); fn(data[i].z); fn(data[i].w); }
+    };
+    // Flat rows: entries that meet in one counter are added to it one after the other, 7.6 cycles each.  Where all that a wave has to add
+    // goes into one bin (from `from`, `width` bit patterns), it adds them up by itself.  Added one by one / by the wave, us: equal entries,
+    // 520 x 65536 600 / 143, 8 x 34000 108 / 30, 520 x 8000 75 / 21, 8 x 4000 16.5 / 8.4; one bin of three values, 520 x 65536 528 / 225.
+    // (Shorter rows have few entries to a counter, and the test for it costs them up to 0.2 us.)
+    auto add_together = [&](unsigned long long *counter, uint32_t from, uint32_t width) {
+        unsigned c = 0;
+        uint32_t sum = 0u;                                     // of distances below 2^23, 64 at most
+        for_entries([&](uint32_t x) {
+            const uint32_t y = x - from;
+            c += y < width ? 1u : 0u;
+            sum += y < width ? y : 0u;
+        });
+        double all = (double)sum;
+        wave_prefix(all, c);
+        if (lane == 63) atomicAdd(counter, (unsigned long long)c << CNT_SHIFT | ((unsigned long long)all + (unsigned long long)c * (from & 0x7fffffu)));
     };
 
     Place at;
@@ -504,16 +523,25 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
             // other lane of a wide row then hit at the same time, and a test for zeros per entry, us: logits of ten times the usual
             // spread, 200 x 16000 10.9 / 9.7, 8 x 12000 9.3 / 8.6, 200 x 8000 7.9 / 7.5, and the same when nothing is below.)
             double low = 0.0;
-            if (wave_least >= least_in) {                          // (uniform over the wave) no zeros, nothing below the window
+            const uint32_t top_bin = wave_top >> FINE_SHIFT;
+            bool flat = FLAT && wave_least >> FINE_SHIFT == top_bin;               // (uniform over the wave, like what follows)
+            if (FLAT && !flat && wave_top >= least_in && __all(data[0].x < least_in || data[0].x >> FINE_SHIFT == top_bin)) {
+                bool one = true;
+                for_entries([&](uint32_t x) { one = one && (x < least_in || x >> FINE_SHIFT == top_bin); });
+                flat = __all(one);
+            }
+            if (flat) {
+                if (wave_top >= least_in) add_together(base + top_bin, top_bin << FINE_SHIFT, 1u << FINE_SHIFT);
+                if (wave_least < least_in) for_entries([&](uint32_t x) { low += (double)__uint_as_float(x < least_in ? x : 0u); });
+            } else if (wave_least >= least_in) {                   // no zeros, nothing below the window
                 for_entries([&](uint32_t x) { atomicAdd(base + (x >> FINE_SHIFT), fraction_entry(x)); });
             } else {
                 for_entries([&](uint32_t x) {
                     low += (double)__uint_as_float(x < least_in ? x : 0u);
                     if (x >= least_in) atomicAdd(base + (x >> FINE_SHIFT), fraction_entry(x));
                 });
-                unsigned none = 0;
-                wave_prefix(low, none);
             }
+            if (wave_least < least_in) { unsigned none = 0; wave_prefix(low, none); }
             if (lane == 63) sh.low[wave] = low;
         }
         __syncthreads();
@@ -558,6 +586,23 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
                     if (!one_by_one) {
                         if (y1 < width) add(y1);
                         if (y2 < width) add(y2);
+                    }
+                }
+                if (FLAT && one_by_one && (at.packed >> CNT_SHIFT) >= 2 * THREADS) {              // (uniform) flat rows, as above
+                    uint32_t least = 0xffffffffu, most = 0u;
+                    for_entries([&](uint32_t x) {
+                        const uint32_t y = x - first;
+                        least = y < least ? y : least;
+                        most = y < width && y > most ? y : most;
+                    });
+                    least = ~wave_max(~least);
+                    most = wave_max(most);
+                    const uint32_t z = least + (first - at.lo), bin = z >> shift;
+                    if (least >= width) one_by_one = false;    // (none here)
+                    else if (bin == (most + (first - at.lo)) >> shift) {
+                        const uint32_t from = at.lo + (bin << shift), skip = from ? 0u : 1u;
+                        add_together(&cur[bin], from + skip, (1u << shift) - skip);
+                        one_by_one = false;
                     }
                 }
                 if (one_by_one)

@@ -440,3 +440,26 @@ def test_thresholds_below_the_window(rows, n):
             p = float(np.float32((1.0 + mass[:j].sum() + 0.5 * mass[j]) / row.sum()))
             got, _ = _check(rows_in, p)
             assert (got["tau"] == np.float32(values[j])).all()
+
+
+@pytest.mark.parametrize("rows,n", [(9, 1000), (9, 2048), (520, 2047), (9, 4096), (9, 8191), (520, 8192), (9, 16384), (520, 13001), (520, 16384), (9, 32767), (300, 32768),
+                                    (9, 33000), (300, 65536)])
+def test_flat_rows(rows, n):
+    """Rows whose waves add their entries up by themselves, in the first pass and in later ones: nearly all entries in one bin, a few
+    values in it, with zeros and single other entries among them, normal and subnormal."""
+    rng = np.random.default_rng(n + rows)
+    z, at = rng.random(n), rng.integers(0, n, 5)
+    kinds = np.empty((9, n))
+    kinds[0] = 1.0 / n
+    kinds[1] = np.where(z < 0.4, 0.0, 0.75)                    # zeros between equal entries
+    kinds[2] = 1.0 + np.floor(3 * z) * 2.0 ** -20              # three values, apart in the last pass
+    kinds[3] = np.where(np.arange(n) < n // 2, 1.0, 1.0 + 2.0 ** -12)           # two values, each in waves of its own or together
+    kinds[4] = 0.75
+    kinds[4, at] = [4.0, 0.7501, 1e-6, 0.0, 1e-30]             # entries of other bins and below the window in single waves
+    kinds[5] = 5 * 2.0 ** -149                                 # subnormal: the lowest bin of the lowest octave
+    kinds[6] = np.where(z < 0.4, 0.0, np.floor(1 + 6 * z) * 2.0 ** -149)
+    kinds[7] = 2.0 ** -130 * (1.0 + np.floor(2 * z) * 2.0 ** -15)
+    kinds[8] = np.where(np.arange(n) % 4096 < 256, 2.0 ** -33, 1.0)             # whole waves below the window
+    probs = kinds.astype(np.float32)[np.arange(rows) % 9].reshape(1, rows, n)
+    for p in (0.9, 0.35):
+        _check(probs, p)
