@@ -446,7 +446,7 @@ static size_t workspace_bytes(const specattn_select_args *sel, const specattn_at
         }
         if (sel->chunk_size <= 1) {                   // optional: lets few long rows be split over many workgroups
             if (sel->B <= 0 || sel->H_kv <= 0 || sel->n_max <= 0 || !sel->indices || sel->block_counts) return 0;
-            if (!select_multi_wg_preferred(sel->B * sel->H_kv, sel->n_max)) return 0;
+            if (!select_multi_wg_preferred(sel->B * sel->H_kv, sel->n_max, sel->top_p)) return 0;
             return select_multi_wg_bytes(sel->B * sel->H_kv, sel->n_max);
         }
         if (sel->B <= 0 || sel->H_kv <= 0 || sel->n_max <= 0 || !is_pow2(sel->chunk_size)) return 0;

@@ -49,7 +49,7 @@ constexpr int SELECT_RESIDENT = 65536;    // rows up to this length are read onc
 specattn_status launch_select(const SelectLaunch &a, hipStream_t stream);
 // Few long rows: each row split over many workgroups, lists written.  `scratch` holds select_multi_wg_bytes(rows, n_max), or
 // less, down to 20 KiB per row, at some cost in time.
-bool select_multi_wg_preferred(int rows, int n);
+bool select_multi_wg_preferred(int rows, int n, float top_p);
 size_t select_multi_wg_bytes(int rows, int n);
 specattn_status launch_select_multi_wg(const SelectLaunch &a, void *scratch, size_t scratch_bytes, hipStream_t stream);
 // Chunk-granular selection straight from rows of positions (n_max counts chunks), for the shapes select_takes_chunks accepts

@@ -982,16 +982,22 @@ specattn_status launch_chunk_masses(const float *probs, int64_t stride_b, int64_
     return check_launch("chunk_mass_kernel");
 }
 
-bool select_multi_wg_preferred(int rows, int n)
+bool select_multi_wg_preferred(int rows, int n, float top_p)
 {
     // One workgroup per row leaves most of the chip idle when there are few rows, takes a CU to itself beyond 32768 entries
-    // and streams the row in every pass beyond 65536; the split costs two more launches.  Measured, one workgroup per row /
-    // split, us: 8 rows of 33000 16.8 / 18.6, of 40000 21.2 / 18.5, of 65536 24.7 / 20.0; 32 of 33000 18.8 / 19.2, of 40000 22.1 / 19.2, of
-    // 65536 28.1 / 20.9; 64 of 33000 19.6 / 23.5, of 40000 24.0 / 23.3, of 65536 29.5 / 25.1; 96 of 60000 29.8 / 44.1; 128 of 65536 30.9 /
-    // 34.0; 512 of 65536 69.5 / 92.4; 256 of 131072 104 / 86.
+    // and streams the row in every pass beyond 65536; the split costs two more launches.  Lists of more than 24576 positions take the one
+    // workgroup a second round, so calls that ask for nearly all of the mass are split earlier.  Measured, one workgroup per row / split, us:
+    // top_p = 0.9       8 x 34816 17.3 / 19.3, x 36800 18.7 / 19.5, x 40000 19.4 / 19.1, x 65536 21.2 / 20.2; 32 x 34816 17.7 / 19.6, x 36800 19.0 / 19.5,
+    //                   x 40000 19.5 / 19.2, x 65536 23.9 / 20.2; 64 x 34816 18.0 / 23.9, x 40000 18.2 / 23.7, x 65536 24.3 / 25.6;
+    //                   96 x 60000 23.5 / 44.1; 128 x 65536 25.6 / 34.0; 512 x 65536 59.5 / 92.4; 256 x 131072 104 / 86
+    // top_p = 0.99      8 x 34816 17.8 / 19.4, x 36800 18.4 / 19.4; 32 x 34816 19.1 / 19.9, x 36800 20.4 / 19.8; 64 x 34816 20.0 / 24.8
+    // top_p = 0.999     8 x 34816 22.4 / 18.9, x 36800 23.9 / 19.0; 32 x 34816 24.2 / 19.3, x 36800 25.5 / 19.3; 64 x 34816 24.7 / 24.2
+    // top_p = 1         8 x 34816 23.7 / 17.4; 32 x 34816 24.9 / 18.6; 64 x 34816 26.9 / 23.4
+    // (Rows of equal entries keep everything whatever top_p is: 8 x 34816 30 / 19.)
     const int cus = cu_count();
-    if (n <= SELECT_RESIDENT) return n >= 36864 && rows <= cus / 4;
-    return rows <= 4 * cus;
+    if (n > SELECT_RESIDENT) return rows <= 4 * cus;
+    const bool long_lists = top_p > (rows <= cus / 8 ? 0.99f : 0.999f);
+    return n > (long_lists ? 32768 : 36863) && rows <= cus / 4;
 }
 
 size_t select_multi_wg_bytes(int rows, int n)

@@ -119,6 +119,16 @@ def test_attention_workspace_holds_every_partial_of_the_matrix_core_route(H_q, B
     assert sa.specattn_workspace_size(None, a) >= need
 
 
+@pytest.mark.parametrize("n", [32769, 36863])
+def test_nearly_whole_lists_ask_for_the_split(n):
+    """Few rows just beyond 32768 entries stay with one workgroup per row unless top_p makes their lists long."""
+    size = lambda rows, p: sa.specattn_workspace_size(_sel(B=1, H_kv=rows, n_max=n, probs_stride_h=n, probs_stride_b=rows * n, top_p=p), None)
+    for rows in (1, 8, 32):
+        assert size(rows, 0.9) == size(rows, 0.99) == 0 and size(rows, 0.995) > 0 and size(rows, 1.0) > 0
+    assert size(64, 0.999) == 0 and size(64, 1.0) > 0
+    assert size(65, 1.0) == 0
+
+
 def test_chunk_selection_workspace_size():
     assert sa.specattn_workspace_size(_sel(chunk_size=16), None) == 2 * 4 * 64 * 4
     assert sa.specattn_workspace_size(_sel(chunk_size=16, n_max=1000, probs_stride_h=1024), None) == ((2 * 4 * 63 * 4 + 255) // 256) * 256
