@@ -991,13 +991,11 @@ bool select_multi_wg_preferred(int rows, int n, float top_p)
     //                   x 40000 19.5 / 19.2, x 65536 23.9 / 20.2; 64 x 34816 18.0 / 23.9, x 40000 18.2 / 23.7, x 65536 24.3 / 25.6;
     //                   96 x 60000 23.5 / 44.1; 128 x 65536 25.6 / 34.0; 512 x 65536 59.5 / 92.4; 256 x 131072 104 / 86
     // top_p = 0.99      8 x 34816 17.8 / 19.4, x 36800 18.4 / 19.4; 32 x 34816 19.1 / 19.9, x 36800 20.4 / 19.8; 64 x 34816 20.0 / 24.8
-    // top_p = 0.999     8 x 34816 22.4 / 18.9, x 36800 23.9 / 19.0; 32 x 34816 24.2 / 19.3, x 36800 25.5 / 19.3; 64 x 34816 24.7 / 24.2
-    // top_p = 1         8 x 34816 23.7 / 17.4; 32 x 34816 24.9 / 18.6; 64 x 34816 26.9 / 23.4
-    // (Rows of equal entries keep everything whatever top_p is: 8 x 34816 30 / 19.)
+    // top_p = 0.999     8 x 34816 22.4 / 18.8, x 36800 23.9 / 19.0; 32 x 34816 23.2 / 19.3, x 36800 25.5 / 19.3; 64 x 34816 23.3 / 24.2
+    // top_p = 1         8 x 34816 10.8 / 15.7, with zeros in the rows 21.3 / 15.7; 32 x 34816 11.2 / 18.5, 22.8 / 18.5; 64 x 34816 12.0 / 23.6, 21.9 / 23.4
     const int cus = cu_count();
     if (n > SELECT_RESIDENT) return rows <= 4 * cus;
-    const bool long_lists = top_p > (rows <= cus / 8 ? 0.99f : 0.999f);
-    return n > (long_lists ? 32768 : 36863) && rows <= cus / 4;
+    return n > (top_p > 0.99f && rows <= cus / 8 ? 32768 : 36863) && rows <= cus / 4;
 }
 
 size_t select_multi_wg_bytes(int rows, int n)

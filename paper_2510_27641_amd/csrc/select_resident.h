@@ -653,15 +653,15 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
     uint16_t *stage = reinterpret_cast<uint16_t *>(select_dyn);
     const unsigned cap = kept < (unsigned)a.idx_capacity ? kept : (unsigned)a.idx_capacity;
     const bool one_round = kept <= CH;                         // (uniform) every rank of the row fits the buffer, also those beyond a smaller capacity
+    typedef int32_t i32x4a __attribute__((ext_vector_type(4), aligned(4)));        // (a list starts anywhere)
+    auto place = [&](int32_t val) { return ptab ? (ptab[val >> a.page_shift] << a.page_shift) | (val & ((1 << a.page_shift) - 1)) : val; };
     auto copy_out = [&](unsigned c0) {
         __syncthreads();
         const unsigned nround = (cap - c0) < CH ? (cap - c0) : CH;
-        auto place = [&](int32_t val) { return ptab ? (ptab[val >> a.page_shift] << a.page_shift) | (val & ((1 << a.page_shift) - 1)) : val; };
         // Streaming stores: a list is read by later launches on any XCD, and what waits in an L2 as changed lines is written back at the
         // launch's end (without / with, us: verify step of 16 layers 811.5 / 796.2, 512 ragged rows of up to 65536 609 / 598, 2048 x
         // 16384 42.2 / 39.7, 64 rows of 13001 with attention 46.1 / 45.8; mask words that way: a union of 1024 members 180.9 / 181.6).
         if constexpr (WORDS) {
-            typedef int32_t i32x4a __attribute__((ext_vector_type(4), aligned(4)));              // (a list starts anywhere)
             for (unsigned k = tid * 4; k < nround; k += ITEM) {
                 const ushort4 v = *reinterpret_cast<const ushort4 *>(stage + k);   // (reaches past the list, not past the buffer)
                 if (k + 4 <= nround) {
@@ -676,6 +676,18 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
             for (unsigned k = tid; k < nround; k += THREADS) __builtin_nontemporal_store(place(stage[k]), out + c0 + k);
         }
     };
+    // Every position (flat rows, top_p = 1), where lists may take several rounds.  By rounds / like this, us: equal entries, 8 x 34816 30 / 16.8;
+    // top_p = 1, 64 x 32768 21.1 / 13.9, 1000 x 32768 69 / 45.
+    if (ITEM * NV4 > (int)CH && kept == (unsigned)len && out && !a.block_counts && !mask_out) {              // (uniform)
+        for (unsigned k = tid * 4; k < cap; k += ITEM) {
+            if (k + 4 <= cap) {
+                __builtin_nontemporal_store((i32x4a){place(k), place(k + 1), place(k + 2), place(k + 3)}, reinterpret_cast<i32x4a *>(out + k));
+            } else {
+                for (unsigned j = k; j < cap; ++j) out[j] = place(j);
+            }
+        }
+        return;
+    }
     if constexpr (WORDS) {
         // Long rows: one bit per entry, two instructions each, then the eight lanes that hold 32 consecutive positions of eight items
         // exchange their nibbles, so that every lane holds whole words of the row's kept bits; what follows (counts, prefix,

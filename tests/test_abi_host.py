@@ -125,8 +125,7 @@ def test_nearly_whole_lists_ask_for_the_split(n):
     size = lambda rows, p: sa.specattn_workspace_size(_sel(B=1, H_kv=rows, n_max=n, probs_stride_h=n, probs_stride_b=rows * n, top_p=p), None)
     for rows in (1, 8, 32):
         assert size(rows, 0.9) == size(rows, 0.99) == 0 and size(rows, 0.995) > 0 and size(rows, 1.0) > 0
-    assert size(64, 0.999) == 0 and size(64, 1.0) > 0
-    assert size(65, 1.0) == 0
+    assert size(33, 1.0) == size(64, 0.999) == 0
 
 
 def test_chunk_selection_workspace_size():

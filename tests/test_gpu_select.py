@@ -463,3 +463,26 @@ def test_flat_rows(rows, n):
     probs = kinds.astype(np.float32)[np.arange(rows) % 9].reshape(1, rows, n)
     for p in (0.9, 0.35):
         _check(probs, p)
+
+
+@pytest.mark.parametrize("rows,n", [(3, 5), (3, 1023), (520, 2046), (3, 8191), (520, 13003), (3, 32765), (300, 32768), (3, 33001), (70, 65535)])
+def test_rows_that_keep_everything(rows, n):
+    """Lists of every position: shorter rows beside them, lists cut at any place, rows of lists at any address, pool slots, and next to them
+    rows with a single zero."""
+    rng = np.random.default_rng(n)
+    probs = np.full((rows, n), 0.25, dtype=np.float32)
+    probs[1] = rng.random(n).astype(np.float32) + 0.5          # (top_p = 1 keeps these too)
+    probs[2, n // 2] = 0.0
+    lens = np.full(rows, n, dtype=np.int32)
+    lens[0] = n - 1
+    page = 8
+    table = rng.permutation(-(-n // page) * rows).astype(np.int32).reshape(rows, -1)
+    for cap in (n, n - 3, 3):
+        for phys in (False, True):
+            paged = dict(page_table=table, page_size=page, emit_physical=True) if phys else {}
+            got = gpu_select(probs.reshape(rows, 1, n), 1.0, seq_lens=lens, capacity=cap, split=False, **paged)
+            for r in range(rows):
+                want = np.flatnonzero(probs[r, :lens[r]])
+                assert got["counts"][r] == want.size
+                want = (table[r, want // page] * page + want % page if phys else want)[:cap]
+                assert np.array_equal(got["indices"][r, :want.size], want) and (got["indices"][r, want.size:] == -7).all()
