@@ -210,6 +210,10 @@ __device__ __forceinline__ void clear_hist(unsigned long long *hist)
 
 // The mass of chunk c of a row of `len` positions (Section 4: chunk-granular selection; the score of a chunk is its mass):
 // its entries added up in fp64 in ascending position order, rounded once to fp32; NaN if one of them is invalid.
+// Bound by the reads' latency: a thread has its chunk to itself, and its four requests bring half a cache line.  (A test of every entry by
+// itself, with the requests in whatever order / the largest entry, requests in order, us: 32 x 2044 / 16 5.8 / 5.6, 300 x 30000 / 256 23.5 /
+// 17.3, 300 x 60000 / 512 41.7 / 29.3, 1100 x 32768 / 16 31.0 / 29.5.  Sixteen entries ahead: 300 x 60000 / 512 33.2, and 1100 rows 69 instead of 58 -
+// their lines leave the caches before they are used up.)
 __device__ __forceinline__ float chunk_mass(const float *row, int len, int c, int chunk_shift)
 {
     const int chunk = 1 << chunk_shift;
@@ -218,20 +222,41 @@ __device__ __forceinline__ float chunk_mass(const float *row, int len, int c, in
     p1 = p1 > len ? len : p1;
     double sum = 0.0;
     bool bad = false;
-    auto add = [&](float x) {
-        const uint32_t u = __float_as_uint(x);
-        if (u > 0x80000000u || (u & 0x7fffffffu) >= 0x7f800000u) bad = true;     // negative, infinite or NaN
-        sum += (double)x;
-    };
     if (p1 == p0 + chunk && chunk >= 4) {
-        typedef float f32x4a __attribute__((ext_vector_type(4), aligned(4)));
-#pragma unroll 4
-        for (int p = p0; p < p1; p += 4) {
-            const f32x4a v = *reinterpret_cast<const f32x4a *>(row + p);
-            add(v.x); add(v.y); add(v.z); add(v.w);
+        // As an unsigned number a sign bit or an exponent of all ones makes an entry too large: then the chunk is looked at again (-0.0 is
+        // zero).
+        uint32_t top = 0u;
+        auto add = [&](u32x4a v) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                top = v[e] > top ? v[e] : top;
+                sum += (double)__uint_as_float(v[e]);
+            }
+        };
+        if (chunk >= 16) {
+            for (int p = p0; p < p1; p += 16) {                // four requests, in order, then their entries
+                u32x4a v[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    v[k] = *reinterpret_cast<const u32x4a *>(row + p + 4 * k);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k) add(v[k]);
+            }
+        } else {
+            for (int p = p0; p < p1; p += 4) add(*reinterpret_cast<const u32x4a *>(row + p));
         }
-    } else {
-        for (int p = p0; p < p1; ++p) add(row[p]);
+        bad = top >= 0x7f800000u;
+    }
+    if (bad || p1 != p0 + chunk || chunk < 4) {
+        sum = 0.0;
+        bad = false;
+        for (int p = p0; p < p1; ++p) {
+            const uint32_t u = __float_as_uint(row[p]);
+            bad = bad || (u >= 0x7f800000u && u != 0x80000000u);                   // negative, infinite or NaN
+            sum += (double)row[p];
+        }
     }
     return bad ? __uint_as_float(0x7fc00000u) : (float)sum;
 }
@@ -1048,10 +1073,10 @@ bool select_takes_chunks(int rows, int n_tokens, int n_chunks)
 {
     // A launch and the masses' way through memory less, and with many rows a row's reads overlap other rows' passes; few
     // long rows are read faster by more workgroups than they have.  Measured, us, masses by a kernel of their own / added
-    // up in the selection (rows x positions / chunk): 32 x 2044 / 16 11.1 / 5.7, 64 x 16384 / 8 12.1 / 9.0, 8 x 32768 / 8
-    // 13.1 / 11.9, 384 x 32768 / 16 24.3 / 15.1, 2048 x 32768 / 8 91.4 / 75.3; 8 x 40000 / 32 12.2 / 10.2, x 65536 / 32 12.6 /
-    // 13.6, x 131072 / 64 14.4 / 20.6; 32 x 65536 / 32 13.3 / 13.8; 128 x 65536 / 32 22.7 / 14.8, x 131072 / 64 34.7 / 25.5;
-    // 512 x 65536 / 32 143 / 34.7.
+    // up in the selection (rows x positions / chunk): 32 x 2044 / 16 8.9 / 5.6, 64 x 16384 / 8 9.0 / 8.5, 384 x 32768 / 16 16.9 / 12.8,
+    // 2048 x 32768 / 8 68.8 / 54.1, 512 x 65536 / 32 29.9 / 27.5, 32 x 30000 / 512 47.6 / 36.5; 8 x 65536 / 32 9.6 / 13.3, 32 x 65536 / 32 8.9 / 12.8,
+    // 8 x 131072 / 64 9.5 / 19.7; nearly even between: 8 x 40000 / 32 9.1 / 10.1, 32 x 59000 / 16 10.5 / 11.2, 128 x 65536 / 32 12.8 / 13.8,
+    // x 131072 / 64 20.9 / 21.8.
     return n_chunks <= 4096 && (n_tokens < 60000 || rows > cu_count() / 4);
 }
 

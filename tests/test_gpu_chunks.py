@@ -176,3 +176,20 @@ def test_short_rows_in_calls_of_long_ones(rows, chunks):
     ref = oracle.topp_select_chunks(probs, 0.97, 4, lens=lens)
     assert compare_select(got, ref)[1] == 0
     assert all((got["indices"][r, got["counts"][r]:] == -7).all() for r in range(rows))
+
+
+@pytest.mark.parametrize("chunk", [2, 4, 8, 16, 32, 1024])
+@pytest.mark.parametrize("rows", [6, 70])
+def test_odd_entries_in_whole_chunks(rows, chunk):
+    """Entries that send a chunk's sum the long way: -0.0 counts as zero, negative, infinite and NaN entries make the row invalid, wherever in
+    the chunk they are; with the sums in the selection (few long rows: in a kernel of their own)."""
+    for n in ([5 * chunk + 3] if rows > 6 else [5 * chunk + 3, 60000 + chunk]):
+        rng = np.random.default_rng(chunk + n)
+        probs = (rng.random((rows, n)) + 0.01).astype(np.float32)
+        at = chunk + rng.integers(0, chunk, rows)
+        bad = np.array([-0.0, -1e-30, np.inf, np.nan, -np.inf, np.float32(2.0 ** -149)], dtype=np.float32)[np.arange(rows) % 6]
+        probs[np.arange(rows), at] = bad
+        got = gpu_select_chunks(probs.reshape(rows, 1, n), 0.7, chunk)
+        ref = oracle.topp_select_chunks(probs, 0.7, chunk)
+        assert compare_select(got, ref)[1] == 0
+        assert np.array_equal((got["flags"] & sa.ROW_INVALID) != 0, ~np.isin(np.arange(rows) % 6, (0, 5)))
