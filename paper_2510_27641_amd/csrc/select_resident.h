@@ -541,7 +541,7 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
                     if (x >= least_in) atomicAdd(base + (x >> FINE_SHIFT), fraction_entry(x));
                 });
             }
-            if (wave_least < least_in) { unsigned none = 0; wave_prefix(low, none); }
+            if (__any(low > 0.0)) { unsigned none = 0; wave_prefix(low, none); }
             if (lane == 63) sh.low[wave] = low;
         }
         __syncthreads();
