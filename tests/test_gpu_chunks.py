@@ -135,6 +135,19 @@ def test_few_long_rows_of_chunks_come_through_memory(rows):
     assert mism == 0
 
 
+def chunk_masses(row, chunk):
+    """fp64 sums of the row's chunks, rounded to fp32 (as the definition has them)."""
+    row = np.pad(row.astype(np.float64), (0, -row.size % chunk)).reshape(-1, chunk)
+    return row.cumsum(1)[:, -1].astype(np.float32).astype(np.float64)
+
+
+def least_kept_at_top_p_one(mass):
+    """The least positive entry but, from the smallest octave up, those octaves that together add less than a unit in the last place of the sum."""
+    octave = np.frexp(np.maximum(mass, 2.0 ** -127))[1]
+    low = [x for x in range(-126, 129) if mass[octave <= x].sum() < np.spacing(mass.sum())]
+    return mass[(mass > 0) & (octave > (max(low) if low else -127))].min()
+
+
 @pytest.mark.parametrize("rows", [9, 603])
 @pytest.mark.parametrize("chunks", [1, 2, 15, 63, 64, 65, 127, 128, 129])
 def test_short_rows_of_chunks(rows, chunks):
@@ -159,7 +172,14 @@ def test_short_rows_of_chunks(rows, chunks):
         got = gpu_select_chunks(probs.reshape(rows, 1, n), p, 16, seq_lens=lens)
         ref = oracle.topp_select_chunks(probs, p, 16, lens=lens)
         _, mism = compare_select(got, ref)
-        assert mism == 0 or p == 1.0                           # (there the oracle stops one entry at a time)
+        if p < 1.0:
+            assert mism == 0
+        else:                                                  # (every valid row is flagged, and the oracle stops one entry at a time)
+            for r in list(range(9)) + [rows - 1]:
+                if r % 9 not in (5, 6, 7):
+                    mass = chunk_masses(probs[r, :lens[r]], 16)
+                    keep = np.flatnonzero(mass >= least_kept_at_top_p_one(mass))
+                    assert got["counts"][r] == keep.size and np.array_equal(got["indices"][r, :keep.size], keep), r
         if n > 16:
             assert got["flags"][5] & sa.ROW_INVALID and got["flags"][6] & sa.ROW_INVALID and got["flags"][7] & sa.ROW_INVALID
 
