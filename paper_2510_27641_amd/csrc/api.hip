@@ -8,7 +8,7 @@
 #include <cstdio>
 #include <mutex>
 
-// Scratch memory of specattn_sparse_decode_attn_static: the split partials and the cost prefix of one
+// Scratch memory of specattn_sparse_decode_attn_static: the split partials and the rows' shares of one
 // attention call.  Every GPU the library runs on holds its own copy of this array until the process ends.
 // In host code the name is only a handle for hipGetSymbolAddress; kernels get the address it returns.
 static __device__ __align__(256) unsigned char scratch[SPECATTN_STATIC_SCRATCH_BYTES];

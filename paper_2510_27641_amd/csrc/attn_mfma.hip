@@ -177,7 +177,7 @@ constexpr int WIDE = 64, WIDE_MASK = 48, NARROW = 32;        // query rows a lau
 static size_t workspace_for(int rows, int nqt, int d)
 {
     const size_t slots = (size_t)attn_mfma_workgroups() + rows;
-    size_t bytes = align256(((size_t)rows + 1) * sizeof(int32_t));                        // the rows' shares
+    size_t bytes = align256(((size_t)rows + 1) * sizeof(int32_t));                        // the rows' shares (and a word to spare)
     bytes += slots * nqt * 16 * (d + 2) * sizeof(float);
     return align256(bytes);
 }

@@ -115,8 +115,8 @@ constexpr int LDS_BYTES = 160008;
 // Rows a launch of NQT query tiles can take: what the LDS leaves for the row tables behind the Q tile.
 constexpr int launch_rows(int nqt, int d) { return d == 128 && nqt == 3 ? 1024 : d == 128 && nqt == 4 ? ATTN_MFMA_MAX_ROWS : MAX_ROWS_LIST; }
 // Behind Q: the row tables (cost prefix and kept counts of up to ROWS rows), then a row's block prefix (mask
-// source).  Calls of up to 64 rows keep their row tables in the first kilobyte, and the mask source then uses the
-// rest of the region for the block counts of all rows.
+// source).  Calls of up to 64 rows hold their rows in registers; with three and four query tiles, copies of them lie in the first kilobyte.
+// The mask source then uses the rest of the region for the block counts of all rows.
 template <int NQT, int D> struct Tables {
     static constexpr int Q_BYTES = NQT <= 2 ? 8192 : NQT * 16 * Geo<D>::ROW_BYTES;
     static constexpr int ROWS = launch_rows(NQT, D);

@@ -374,7 +374,8 @@ __global__ __launch_bounds__(MAP_THREADS) void layer_map_kernel(const double *__
 // Up to 64 draft layers: one wave, lane i holds best[i].  A column needs the prefix maximum alone; where it came from is what a column's
 // records (the lanes above everything before them, one ballot) say: the first maximum over the lanes up to i is the last record up to
 // i.  So the columns carry no indices, and the way back is five scalar instructions per column instead of a dependent read from LDS.
-// 22 x 32 layers, back pointers per lane and column / records: 11.9 / 7.2 us.  Records wait in LDS, or, where there are too many, in
+// Back pointers per lane and column / records, us: 22 x 32 layers 11.9 / 7.4, 64 x 80 27.5 / 19.4, 2 x 3 2.6 / 2.5; one call by itself, behind other
+// kernels that have taken the caches (the code is three times as long as before, a call goes through a third of it), 15.3 / 12.0, 30.8 / 24.9, 6.1 / 6.2.  Records wait in LDS, or, where there are too many, in
 // the workspace (8 of the 4 m bytes per column it holds).  Columns that met a NaN, for which an order of maxima has no meaning, are
 // taken again by the general form.
 template <int STEPS> __device__ __forceinline__ double prefix_max(double v)

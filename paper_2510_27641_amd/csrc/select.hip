@@ -105,11 +105,11 @@ __device__ __forceinline__ uint32_t mask_word(uint32_t nibble, int lane)
 // With top_p = 1 the boundary is the lowest non-empty bin, whatever the rounding of the sums above it.  Bins count as empty
 // there from the octave down from which on the entries all together add less than one unit in the last place of the row's
 // total: fp64 sums taken in another order differ by as much.
+// Used by the streaming kernel and the split selection; rows in registers have bins and decisions of their own.
 // The first wave does it alone and the others wait at the one barrier: its lanes own NB / 64 bins each from the top down (lane
 // 0 the highest), add them up as integers (bins of one exponent add exactly), and a prefix over the lanes tells every lane the
-// mass above its bins; the bins of the lane that holds the boundary are then searched one per lane.  All waves together, with
-// the totals of the waves through LDS and two barriers, a step took 2.1 us (2048 bins, 512 threads): a row of 8192 positions
-// 10.7 us then and 8.0 us now, 64 rows of 13001 14.2 and 10.7, 1024 rows of 32768 73.7 and 69.3 us.
+// mass above its bins; the bins of the lane that holds the boundary are then searched one per lane.  (All waves together, with
+// the totals of the waves through LDS and two barriers, took 2.1 us per step of 2048 bins.)
 template <int NB, bool FIRST>
 __device__ __forceinline__ int locate_bin(const unsigned long long *hist, Located &found, int e_field_fixed, float top_p, double &target,
                                           double &m_above, unsigned &c_above, unsigned long long &bin_packed)
@@ -126,7 +126,7 @@ __device__ __forceinline__ int locate_bin(const unsigned long long *hist, Locate
             sum[g] = 0ull;
 #pragma unroll
             for (int j = 0; j < RUN; ++j) sum[g] += mine[g * RUN + j];
-            __builtin_amdgcn_sched_barrier(0);                 // (not all loads at once: the caller's registers hold the row)
+            __builtin_amdgcn_sched_barrier(0);                 // (not all loads at once: 1100 streamed rows of 66000 271.3 / 269.4 us; split ones the same)
         }
         auto exponent = [&](int g) { return FIRST ? (63 - lane) * RUNS + g : e_field_fixed; };
         int cut = -1;                                          // exponent fields up to this one count as empty
@@ -1098,14 +1098,14 @@ specattn_status launch_select(const SelectLaunch &a, hipStream_t stream)
     // passes (workgroups of 256 / 512 / 1024 threads: four to six / two or three / one to a CU).
     // Block counts are per 1024 positions, so every variant has THREADS*4 a multiple of 1024.
     // Measured, us (256 CUs; shape: time):
-    //   2044 x 64 rows      512x1 5.9, 256x2 6.4;        2044 x 1024   256x2 8.2, 512x1 9.1
-    //   4096 x 512          512x2 8.5, 256x4 8.7;        4096 x 1024   256x4 11.1, 512x2 13.7
-    //   8192 x 128          512x4 8.3, 1024x2 8.6;       8192 x 512    512x4 11.5, 256x8 11.8
-    //   8192 x 768          256x8 13.7, 512x4 13.9;      8192 x 1024   256x8 15.8, 512x4 18.1
-    //   13001 x 64          1024x4 10.4, 512x8 10.9;     16384 x 256   1024x4 12.7, 512x8 12.8
-    //   16384 x 512         512x8 17.4, 256x16 19.9;     13001 x 1024  256x16 25.1, 512x8 28.6
-    //   16384 x 2048        256x16 41.1, 512x8 52.4
-    //   32768 x 256         1024x8 19.6, 512x16 21.7;    32768 x 384   512x16 27.3, 1024x8 33.2
+    //   2044 x 64 rows      512x1 6.3, 256x2 6.8;        2044 x 1024   256x2 8.4, 512x1 9.4
+    //   4096 x 512          512x2 7.9, 256x4 8.1;        4096 x 1024   256x4 10.3, 512x2 11.0
+    //   8192 x 128          512x4 8.0, 1024x2 8.4;       8192 x 512    512x4 10.7, 256x8 11.3
+    //   8192 x 768          256x8 12.7, 512x4 12.9;      8192 x 1024   256x8 14.3, 512x4 17.3
+    //   13001 x 64          1024x4 9.4, 512x8 9.7;       16384 x 256   1024x4 10.7, 512x8 11.5
+    //   16384 x 512         512x8 14.8, 256x16 16.6;     13001 x 1024  256x16 21.2, 512x8 24.6
+    //   16384 x 2048        256x16 37.7, 512x8 49.8
+    //   32768 x 256         1024x8 15.8, 512x16 18.2;    32768 x 384   512x16 22.9, 1024x8 29.8
     if (n <= 1024) return launch_one<256, 1>(a, stream);
     if (n <= 2048) return rows <= 2 * cus ? launch_one<512, 1>(a, stream) : launch_one<256, 2>(a, stream);
     if (n <= 4096) return rows <= 2 * cus ? launch_one<512, 2>(a, stream) : launch_one<256, 4>(a, stream);

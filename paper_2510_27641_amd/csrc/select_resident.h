@@ -4,13 +4,14 @@
 // The passes over the registers are bound by instruction issue and by the LDS unit's 64-bit atomics, and short rows by the chain of
 // barriers and locate steps, so the digits are chosen for few and cheap passes: the first one covers the 32 octaves below the row's
 // largest entry with 64 bins each, so that the boundary bin holds three entries of a thousand instead of thirty.  What lies below these
-// octaves is added up in fp64 for the row's sum and gets bins, one per octave, in a pass of its own if the boundary turns out to lie there.  The second pass, over ten more bits, then finds few entries and nearly always leaves a bin
-// with a single one, which is tau*.  With eight bins per octave over all exponents, as the split selection has them, every wave met
-// entries of the boundary bin in nearly every vector of the second pass, and every other row took a third one.
+// octaves is added up in fp64 for the row's sum and gets bins, one per octave, in a pass of its own if the boundary turns out to lie there.
+// The second pass, over ten more bits, then finds few entries and nearly always leaves a bin with a single one, which is tau*.  With eight
+// bins per octave over all exponents, as the split selection has them, every wave met entries of the boundary bin in nearly every vector of
+// the second pass, and every other row took a third one.
 // Compaction works on words of 32 kept bits, which costs two instructions per entry, instead of on ranks of single entries.
-// Rows x entries with that and eight bins per octave / now, us: 1024 x 32768 60.0 / 48.3 (23 vector instructions per entry and lane
-// before the last step, 38 then; the LDS unit is busy 45 % of the time, the vector ALU 50 %), 2048 x 32768 107.8 / 84.0, 512 x 65536 98 / 69.5,
-// 2048 x 16384 60.2 / 41.1, 128 x 4096 7.3 / 6.3, 8 x 8192 7.9 / 7.2, 8 x 1024 5.6 / 5.0.
+// Rows x entries with eight bins per octave and ranks / now, us: 1024 x 32768 60.4 / 44.2 (the LDS unit is busy 45 % of the time, the vector
+// ALU 50 %), 2048 x 32768 108 / 80, 512 x 65536 87 / 61, 2048 x 16384 60.0 / 38.2, 64 x 13001 10.6 / 9.4, 128 x 4096 7.2 / 6.0, 8 x 8192 8.2 / 8.1,
+// 8 x 1024 5.6 / 5.3.  Rows of equal entries save no pass and pay for the row's largest entry: 200 x 200 6.5 / 6.8.
 #pragma once
 
 // Bins of the first pass: FINE of them from the lowest exponent of the window up.  A bin's entries share their exponent, so its mass is an
@@ -384,9 +385,11 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
     uint4 data[NV4];
     uint4 tailv = make_uint4(0, 0, 0, 0);
     const int tail_p = (len & 3) ? (len & ~3) : -1;            // start of the partial vector, if any
-    // Chunk lists of up to 2048 positions are mostly this short.  Bins / comparisons, rows x positions / chunk, us: 32 x 2044 / 16 7.8 / 5.7,
-    // 8 x 1024 / 16 5.0 / 4.3, 1024 x 2044 / 16 8.9 / 8.3; the work grows with the square of the chunks, and 256 of them take 6.1 with
-    // bins.  (top_p = 1 has a rule of its own for entries that add nothing.)
+    // Short lists of chunks.  The work grows with the square of the chunks, and the line lies where two entries per lane end: with four of
+    // them the comparisons break even at 144 chunks for few rows and lose to the bins from 64 on for many.  Bins / comparisons, two to a
+    // lane / four, us: 8 rows of 64 chunks 5.7 / 4.2 / 5.4, of 128 5.7 / 4.4 / 5.5, of 144 5.8 / - / 5.8, of 192 5.9 / - / 6.6; 256 of 128 6.0 / 4.6 /
+    // 5.9, of 192 6.1 / - / 7.1; 1024 of 64 7.6 / 6.1 / 8.2, of 128 7.7 / 7.0 / 10.2, of 192 8.0 / - / 12.5.  (top_p = 1 has a rule of its own
+    // for entries that add nothing.)
     const bool brief = CHUNKED && len <= BRIEF && a.top_p < 1.0f;              // (uniform)
     uint32_t *const entries = reinterpret_cast<uint32_t *>(select_dyn);
     constexpr int BRIEF_SUMS = ITEM * NV4 * 4;                // byte at which the sums start
