@@ -523,11 +523,9 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
             unsigned long long *base = hist1 - (e_low << (23 - FINE_SHIFT));
             const uint32_t least_in = (uint32_t)e_low << 23;
             // What is below the window counts in the row's sum, zeros not at all.  (With a bin per octave for it in this pass, which every
-            // other lane of a wide row then hit at the same time, and a test for zeros per entry / its sum in this pass / in one of its own, us:
-            // logits of ten times the usual spread, 200 x 16000 10.9 / 9.9 / 10.1, 8 x 12000 8.7 / 8.6 / 8.2; three zeros in five entries,
-            // 1024 x 32768 43.2 / 43.0 / 39.7, 64 x 13001 9.2 / 9.1 / 8.9, 200 x 8000 8.5 / 8.3 / 8.2.)
+            // other lane of a wide row then hit at the same time, and a test for zeros per entry, us: logits of ten times the usual
+            // spread, 200 x 16000 10.9 / 9.7, 8 x 12000 9.3 / 8.6, 200 x 8000 7.9 / 7.5, and the same when nothing is below.)
             double low = 0.0;
-            uint32_t low_bits = 0u;                                // of all entries below the window: not zero if there are any
             const uint32_t top_bin = wave_top >> FINE_SHIFT;
             bool flat = FLAT && wave_least >> FINE_SHIFT == top_bin;               // (uniform over the wave, like what follows)
             if (FLAT && !flat && wave_top >= least_in && __all(data[0].x < least_in || data[0].x >> FINE_SHIFT == top_bin)) {
@@ -537,20 +535,16 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
             }
             if (flat) {
                 if (wave_top >= least_in) add_together(base + top_bin, top_bin << FINE_SHIFT, 1u << FINE_SHIFT);
-                if (wave_least < least_in) for_entries([&](uint32_t x) { low_bits |= x < least_in ? x : 0u; });
+                if (wave_least < least_in) for_entries([&](uint32_t x) { low += (double)__uint_as_float(x < least_in ? x : 0u); });
             } else if (wave_least >= least_in) {                   // no zeros, nothing below the window
                 for_entries([&](uint32_t x) { atomicAdd(base + (x >> FINE_SHIFT), fraction_entry(x)); });
             } else {
                 for_entries([&](uint32_t x) {
+                    low += (double)__uint_as_float(x < least_in ? x : 0u);
                     if (x >= least_in) atomicAdd(base + (x >> FINE_SHIFT), fraction_entry(x));
-                    else low_bits |= x;
                 });
             }
-            if (__any(low_bits != 0u)) {
-                for_entries([&](uint32_t x) { low += (double)__uint_as_float(x < least_in ? x : 0u); });
-                unsigned none = 0;
-                wave_prefix(low, none);
-            }
+            if (__any(low > 0.0)) { unsigned none = 0; wave_prefix(low, none); }
             if (lane == 63) sh.low[wave] = low;
         }
         __syncthreads();
