@@ -446,24 +446,41 @@ __device__ __forceinline__ int floor_div(int64_t a, int b)
     return (int)floor((double)a / (double)b);
 }
 
-// The first min(n_wg, total) workgroups share the line: workgroup w takes [w * total / n, (w + 1) * total / n),
+// The first n = min(shares, total) workgroups share the line: workgroup w takes [w * total / n, (w + 1) * total / n),
 // so shares differ by at most one unit and none of them is empty (every workgroup between the first and the
 // last of a row therefore holds tiles of that row, which the merge relies on).
-__device__ __forceinline__ int share_start(int total, int n_wg, int w)
+// Long shares are tilted (TILT_FROM): the XCDs of odd number stream more slowly than the others while all of them read.  With
+// equal shares their workgroups end 4 to 7 % later, in every launch (the rest of the spread has no fixed place; a plain read of 1 GiB in
+// equal parts: even XCDs 132 us, odd ones 150).  So the shares of even XCDs are TILT / 128 larger than the mean, those of odd ones as much
+// smaller: of the four shares of a team (share_index) two are of either kind, so boundaries 2 k stay where they are and the others move by
+// TILT / 128 of a share.  TILT 0 / 4 / 6 / 8 / 12, us: 16 layers of 64 rows of 32768 with their selection 799 / 787 / 786 / 789 / 798
+// (mask source 834 / 817 / 817 / 821 / 833), 512 ragged rows 575 / 569 / 571 / 574 / 580, dense rows of up to 32768 109.6 / 108.4 / 108.2 / 108.1 /
+// 110.0, 64 rows of 13001 45.9 / 45.6 / 45.2 / 45.3 / 45.7.
+constexpr int TILT = 5;
+// Lines whose shares are tilted: of TILT_FROM units a share or more (the mean of TILT 4 and 6 against equal shares, us: 64 rows of 27 units a
+// share 24.6 / 24.7, of 33 28.6 / 28.6, of 38 32.0 / 31.7, of 62 46.8 / 46.1, of 97 67.8 / 67.6; 16 rows of 40 34.7 / 34.8, of 59 47.4 / 46.8).  Not where rows
+// are so many that equal counts make every share whole rows: there a moved boundary costs a partial (256 rows of 2000 positions 48.3 / 51.2).
+constexpr int TILT_FROM = 32;
+template <int TILE> __device__ __forceinline__ Share<TILE> make_share(const Plan &plan, int total, int rows, int w)
 {
-    const int n = n_wg < total ? n_wg : total;
-    if (w >= n) return total;
-    // (fewer units than workgroups: one each; a power of two - the usual 256 workgroups - divides exactly in any arithmetic: a
-    // shift then gives the same floor as the division below at a tenth of the instructions, on the way to a workgroup's first request)
-    if (n == total) return w;
-    if ((n & (n - 1)) == 0) return (int)(((int64_t)w * total) >> (31 - __clz(n)));
-    return floor_div((int64_t)w * total, n);
-}
-template <int TILE> __device__ __forceinline__ Share<TILE> make_share(int total, int n_wg, int w)
-{
+    // (This is on the way to a workgroup's first request: no branches, and the usual numbers of workgroups and shares are powers of two, for
+    // which a shift gives the same floor as the division.)
+    const int n_wg = plan.n_wg;
+    const bool few = (total <= plan.line_128) & (total > (8 + SEG_COST) * rows);
+    const int shares = few ? total <= plan.line_64 ? 64 : 128 : n_wg;
+    int move = ((w >> 1) ^ (w >> 2)) & 1 ? -TILT : TILT;       // of boundary w or w + 1, whichever is odd
+    move = (total >= TILT_FROM * n_wg) & ((rows * 2 <= n_wg) | ((total & (n_wg - 1)) != 0)) ? move : 0;
+    const int64_t from = (int64_t)(w * 128 + ((w & 1) ? move : 0)) * total, to = (int64_t)(w * 128 + 128 + ((w & 1) ? 0 : move)) * total;
     Share<TILE> s;
-    s.c0 = share_start(total, n_wg, w);
-    s.c1 = share_start(total, n_wg, w + 1);
+    s.c0 = (int)(from >> (38 - __clz(shares)));
+    s.c1 = (int)(to >> (38 - __clz(shares)));
+    if (__builtin_expect((shares & (shares - 1)) != 0, 0)) {   // (equal shares: share_index deals these to XCDs as they come)
+        s.c0 = floor_div((int64_t)w * total, shares);
+        s.c1 = floor_div((int64_t)(w + 1) * total, shares);
+    }
+    const bool units = total < shares;                         // fewer units than shares: one each
+    s.c0 = min(units ? w : s.c0, total);
+    s.c1 = min(units ? w + 1 : s.c1, total);
     return s;
 }
 // Which share of the line a workgroup takes.  The hardware deals workgroup i to XCD i mod 8; the owners of
@@ -644,7 +661,7 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
     // This workgroup's share of the cost line, and the rows of which it holds tiles
     const int my_share = __builtin_amdgcn_readfirstlane(share_index(blockIdx.x, plan.n_wg));
     total = __builtin_amdgcn_readfirstlane(total);
-    const Share<TILE> sh = make_share<TILE>(total, total > plan.line_128 || total <= (8 + SEG_COST) * rows ? plan.n_wg : total <= plan.line_64 ? 64 : 128, my_share);
+    const Share<TILE> sh = make_share<TILE>(plan, total, rows, my_share);
     const int c0 = sh.c0, c1 = sh.c1;
     if (c0 >= c1) return;                                // more workgroups than units of work
     int my_lb = 0, my_le = 0;                            // few rows: local tile range of row `lane`
