@@ -143,10 +143,17 @@ def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else C.c_void_p(t.data_ptr())
 
 
-def _stream(stream) -> C.c_void_p:
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream)
+# The current stream's handle without a Stream object around it: torch.cuda.current_stream() takes 2.7 us, this 0.27, and a selection with
+# attention over 8 rows of 1024 positions 13.0 us of host time with one of them per call, more than its kernels.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream(stream) -> Optional[int]:
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 # ------------------------------------------------------------------------------------------
