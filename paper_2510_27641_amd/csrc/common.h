@@ -44,6 +44,7 @@ struct SelectLaunch {
     int n_tokens;            // positions behind a row: seq_lens counts these (n_max << chunk_shift at most)
     int chunk_shift;         // log2 of the chunk size when the row holds chunk masses, else 0
     uint32_t *kept_mask;     // may be null; [rows][blocks_per_row * SEL_BLOCK / 32]: bit i of word w = position 32 w + i kept
+    int by_length;           // > 0: workgroups take the sequences from the longest down, compared by their lengths >> (by_length - 1)
 };
 constexpr int SELECT_RESIDENT = 65536;    // rows up to this length are read once (one workgroup holds them in registers)
 specattn_status launch_select(const SelectLaunch &a, hipStream_t stream);

@@ -344,6 +344,29 @@ constexpr unsigned select_lds(int threads, int nv4)
     return threads * nv4 * 4 > 16384 ? 49152 : threads > 256 ? 32768 : 26624;
 }
 
+// The sequence that comes k-th (k < n <= 64) when n of them are taken from the longest down, sequences of one level in their order: from the
+// top bit of the levels down, those with the bit set come first.  `len`: sequence i's in lane i.  (A level is a length of eight bits.)
+__device__ __forceinline__ int kth_longest(int len, int shift, int n, int k)
+{
+    const uint32_t level = (uint32_t)len >> shift;
+    unsigned long long left = n < 64 ? (1ull << n) - 1ull : ~0ull;
+    auto halve = [&](unsigned long long first) {
+        const unsigned long long with = left & first;
+        const int c = __popcll(with);
+        left = k < c ? with : left & ~first;
+        k -= k < c ? 0 : c;
+    };
+#pragma unroll
+    for (int bit = 7; bit >= 0; --bit) halve(__ballot((level >> bit) & 1u));
+    halve(0x00000000ffffffffull);
+    halve(0x0000ffff0000ffffull);
+    halve(0x00ff00ff00ff00ffull);
+    halve(0x0f0f0f0f0f0f0f0full);
+    halve(0x3333333333333333ull);
+    halve(0x5555555555555555ull);
+    return (int)__ffsll((long long)left) - 1;
+}
+
 // CHUNKED: a.probs are rows of positions; the workgroup adds the chunks up itself, into the LDS that the histograms take over.
 template <int THREADS, int NV4, bool CHUNKED = false>
 __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
@@ -364,11 +387,18 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
     extern __shared__ __align__(16) unsigned long long select_dyn[];
     static_assert(RES_HIST * 8 <= (int)select_lds(THREADS, NV4), "the histograms share the list's buffer");
     unsigned long long *hist1 = select_dyn, *hist2 = select_dyn + FINE;
-    const int r = blockIdx.x;
-    const int b = r / a.H_kv, h = r - b * a.H_kv;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    int len = a.seq_lens ? a.seq_lens[b] : a.n_tokens;
-    len = len < 0 ? 0 : (len > a.n_tokens ? a.n_tokens : len);
+    int b = blockIdx.x / a.H_kv, len;
+    const int h = blockIdx.x - b * a.H_kv;
+    auto clamped = [&](int n) { return n < 0 ? 0 : (n > a.n_tokens ? a.n_tokens : n); };
+    if (a.by_length) {                                         // (uniform)
+        const int lens = lane < a.B ? clamped(a.seq_lens[lane]) : 0;
+        b = __builtin_amdgcn_readfirstlane(kth_longest(lens, a.by_length - 1, a.B, b));
+        len = __builtin_amdgcn_readlane(lens, b);
+    } else {
+        len = clamped(a.seq_lens ? a.seq_lens[b] : a.n_tokens);
+    }
+    const int r = b * a.H_kv + h;
     const int positions = len;
     len = (len + (1 << a.chunk_shift) - 1) >> a.chunk_shift;     // rows of chunk masses: length in chunks
     len = len > a.n_max ? a.n_max : len;

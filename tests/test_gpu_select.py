@@ -488,3 +488,17 @@ def test_rows_that_keep_everything(rows, n):
                 assert got["counts"][r] == want.size
                 want = (table[r, want // page] * page + want % page if phys else want)[:cap]
                 assert np.array_equal(got["indices"][r, :want.size], want) and (got["indices"][r, want.size:] == -7).all()
+
+
+@pytest.mark.parametrize("B,H,n", [(64, 17, 300), (63, 17, 1000), (2, 600, 1500), (37, 8, 33000), (64, 9, 18000), (65, 9, 18000)])
+def test_more_rows_of_different_lengths_than_fit_the_chip(B, H, n):
+    """Workgroups take up to 64 sequences from the longest down (every thread count; equal lengths, lengths of one level and empty rows
+    among them); beyond 64 in the order of the batch."""
+    rng = np.random.default_rng(B * n)
+    lens = rng.integers(0, n + 1, size=B).astype(np.int32)
+    lens[: B // 3] = lens[0]                                 # one length
+    lens[B // 2 : B // 2 + B // 4] = n - rng.integers(0, 3, size=B // 4)
+    lens[-1], lens[B // 3] = 0, n
+    probs = W.draft_probs(rng, 8, n, recency_len=min(64, n))[rng.integers(0, 8, size=B * H)].reshape(B, H, n)
+    probs *= np.exp2(rng.integers(-3, 4, size=(B, H, 1))).astype(np.float32)     # (no two rows alike)
+    _check(probs, 0.9, allow_flagged_mismatch=True, seq_lens=lens)
