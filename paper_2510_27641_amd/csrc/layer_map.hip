@@ -8,7 +8,7 @@
 // 2. Alignment: the non-decreasing map f (verifier layer -> draft layer) that maximises sum_j S[f(j)][j],
 //    by the recurrence of Algorithm 3 (its "above" transition contains the other two):
 //    best[i][j] = S[i][j] + max_{k <= i} best[k][j-1], first maximum at ties.  One workgroup, thread i holds
-//    draft layer i; every column is one prefix-maximum scan over the threads.
+//    draft layer i; up to 64 of them go through the table by diagonals, more take a prefix maximum over the threads per column.
 #include "common.h"
 
 #include <cmath>
@@ -276,14 +276,6 @@ template <int CTRL, int ROW_MASK> __device__ __forceinline__ void scan_step(Best
     if (ix != 0x7fffffff && !(b.val > left)) { b.val = left; b.idx = ix; }
 }
 
-// v of the lane that the step moves from; -infinity where there is none.
-template <int CTRL, int ROW_MASK> __device__ __forceinline__ double shifted(double v)
-{
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROW_MASK, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp((int)0xfff00000, __double2hiint(v), CTRL, ROW_MASK, 0xf, false);
-    return __hiloint2double(hi, lo);
-}
-
 // One thread per draft layer, up to 1024.  A column is a prefix maximum inside every wave on the vector ALU and, with more than 64
 // draft layers, one over the wave totals through LDS (double-buffered: one barrier per column).  The columns of S are
 // fetched eight at a time and ahead; back pointers stay in LDS as long as they fit.  Bound by the serial chain of n
@@ -292,10 +284,7 @@ struct AlignShared {
     double wval[2][MAP_THREADS / 64];
     int widx[2][MAP_THREADS / 64];
     int start;
-    union {
-        uint16_t back[MAP_LDS_BACK];
-        unsigned long long records[MAP_LDS_BACK / 4];
-    };
+    uint16_t back[MAP_LDS_BACK];
 };
 __device__ __forceinline__ void align_threads(const double *__restrict__ S, int m, int n, int32_t *__restrict__ back, int32_t *__restrict__ f,
                               double *__restrict__ total, AlignShared &sh)
@@ -371,83 +360,141 @@ __global__ __launch_bounds__(MAP_THREADS) void layer_map_kernel(const double *__
     align_threads(S, m, n, back, f, total, sh);
 }
 
-// Up to 64 draft layers: one wave, lane i holds best[i].  A column needs the prefix maximum alone; where it came from is what a column's
-// records (the lanes above everything before them, one ballot) say: the first maximum over the lanes up to i is the last record up to
-// i.  So the columns carry no indices, and the way back is five scalar instructions per column instead of a dependent read from LDS.
-// Back pointers per lane and column / records, us: 22 x 32 layers 11.9 / 7.4, 64 x 80 27.5 / 19.4, 2 x 3 2.6 / 2.5; one call by itself, behind other
-// kernels that have taken the caches (the code is three times as long as before, a call goes through a third of it), 15.3 / 12.0, 30.8 / 24.9, 6.1 / 6.2.  Records wait in LDS, or, where there are too many, in
-// the workspace (8 of the 4 m bytes per column it holds).  Columns that met a NaN, for which an order of maxima has no meaning, are
-// taken again by the general form.
-template <int STEPS> __device__ __forceinline__ double prefix_max(double v)
+// Up to 64 draft layers: lane i of one wave holds draft layer i and works on verifier layer t - i in step t, one behind its neighbour: the maximum
+// over the layers before it, which that neighbour found a step ago, and its own of the verifier layer before are all it needs, so a step is one
+// lane move, one sum and one maximum.  No indices are carried: a column's records, the lanes above everything before them, say where its prefix
+// maxima lie (the first maximum over the lanes up to i is the last record up to i), and the way back is three scalar instructions per column.
+// Bound by that serial chain of n + m - 1 steps and n columns back behind one trip to memory; the other waves only fetch.  A prefix maximum over
+// the lanes per column, six dependent lane moves and maxima each / a step per diagonal, us: 32 x 48 layers 10.6 / 6.9, 32 x 80 16.7 / 8.8, 64 x 80 19.6 / 12.5, 64 x 1000 213 /
+// 85, similarity and alignment of 22 x 32 layers 28.0 / 25.2; 16 x 24 and smaller, bound by the host, 6.0 both.
+// S waits in LDS by steps (lane i's entry of step t is that of column t - i), so that a step's entries lie side by side.  Records: a word
+// per block of 64 columns and layer; in LDS, or, where there are too many, in the workspace (an eighth of m bytes per column, of the 4 m it holds).
+// A NaN, for which an order of maxima has no meaning, and entries above 1e300, whose sums may end in one (infinity and -infinity; 65535 columns of
+// less do not overflow), leave the call to the general form.
+constexpr int WAVE_MOST = 64;                                  // draft layers
+constexpr int WAVE_THREADS = 256, WAVE_BLOCK = 64, WAVE_RING = 2 * WAVE_BLOCK;       // steps between two fetches; steps held
+constexpr int WAVE_PITCH = WAVE_MOST + 1;                      // doubles of a step (odd: a layer's columns, a step apart, fall on different banks)
+constexpr int WAVE_RECORDS = MAP_LDS_BACK / 4;                 // words of records that are kept in LDS
+__host__ __device__ inline int wave_records(int m, int n) { return (n + 63) / 64 * m; }
+size_t wave_lds_bytes(int m, int n)
 {
-    // (no NaN matters here, so a bare instruction; two wait states for the lane move that reads its result)
-    auto step = [&](double left) { asm("v_max_f64 %0, %1, %2\n s_nop 1" : "=v"(v) : "v"(v), "v"(left)); };
-    if (STEPS > 0) step(shifted<0x111, 0xf>(v));    // row_shr:1
-    if (STEPS > 1) step(shifted<0x112, 0xf>(v));    // row_shr:2
-    if (STEPS > 2) step(shifted<0x114, 0xf>(v));    // row_shr:4
-    if (STEPS > 3) step(shifted<0x118, 0xf>(v));    // row_shr:8
-    if (STEPS > 4) step(shifted<0x142, 0xa>(v));    // row_bcast:15 into rows 1 and 3
-    if (STEPS > 5) step(shifted<0x143, 0xc>(v));    // row_bcast:31 into rows 2 and 3
-    return v;
+    const int words = wave_records(m, n);
+    const size_t bytes = ((size_t)WAVE_PITCH * WAVE_RING + (words <= WAVE_RECORDS ? words : 0)) * sizeof(double);
+    return bytes > sizeof(AlignShared) ? bytes : sizeof(AlignShared);
 }
-// Forward columns; returns whether a NaN came up, the last column's maximum in `top`.
-template <int STEPS> __device__ __forceinline__ bool align_columns(const double *__restrict__ S, int m, int n, unsigned long long *records, double &top)
+// Eight steps of a wave.  left: the lane before's; best = entry + own; a record (another bit of rec) where best > left; own = the larger.  Written
+// out because this is the chain that a call waits for: a wave by itself issues an instruction in 4 to 8 cycles.  (The lane moves need two wait
+// states behind what they read, the carry as many behind the comparison.)
+__device__ __forceinline__ void diagonal_steps(double &own, double &left, uint32_t &rec, const double (&entry)[8])
 {
-    const int lane = threadIdx.x;
-    constexpr int AHEAD = 16;
-    const double *row = S + (int64_t)(lane < m ? lane : m - 1) * n;
-    double cur[AHEAD], nxt[AHEAD];
+#define SPECATTN_STEP(E) \
+    "v_mov_b32_dpp v102, v100 wave_shr:1 row_mask:0xf bank_mask:0xf\n" \
+    "v_mov_b32_dpp v103, v101 wave_shr:1 row_mask:0xf bank_mask:0xf\n" \
+    "v_add_f64 v[104:105], " E ", v[100:101]\n" \
+    "v_cmp_gt_f64 vcc, v[104:105], v[102:103]\n" \
+    "v_max_f64 v[100:101], v[104:105], v[102:103]\n" \
+    "s_nop 0\n" \
+    "v_addc_co_u32 %2, vcc, %2, %2, vcc\n"
+    asm("s_nop 1\n" SPECATTN_STEP("%3") SPECATTN_STEP("%4") SPECATTN_STEP("%5") SPECATTN_STEP("%6")
+        SPECATTN_STEP("%7") SPECATTN_STEP("%8") SPECATTN_STEP("%9") SPECATTN_STEP("%10")
+        : "+{v[100:101]}"(own), "+{v[102:103]}"(left), "+v"(rec)
+        : "v"(entry[0]), "v"(entry[1]), "v"(entry[2]), "v"(entry[3]), "v"(entry[4]), "v"(entry[5]), "v"(entry[6]), "v"(entry[7])
+        : "vcc", "v104", "v105");
+#undef SPECATTN_STEP
+}
+__global__ __launch_bounds__(WAVE_THREADS) void layer_map_wave_kernel(const double *__restrict__ S, int m, int n, int32_t *__restrict__ back,
+                                                                      int32_t *__restrict__ f, double *__restrict__ total)
+{
+    extern __shared__ __align__(16) double map_lds[];
+    double *ring = map_lds;                                    // [WAVE_RING][WAVE_PITCH]: step t at t % WAVE_RING
+    unsigned long long *records = wave_records(m, n) <= WAVE_RECORDS ? reinterpret_cast<unsigned long long *>(ring + WAVE_RING * WAVE_PITCH) : reinterpret_cast<unsigned long long *>(back);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int steps = n + m - 1;
+    constexpr int WAVES = WAVE_THREADS / 64, MOST_ROWS = WAVE_MOST / WAVES;
+    // Columns a lane has not reached yet and columns past the last one count as -0.0, which leaves a lane what it has.
+    auto cell = [&](int t, int i) -> double & { return ring[(t & (WAVE_RING - 1)) * WAVE_PITCH + i]; };
+    for (int i = wave; i < m; i += WAVES)
+        if (lane < i) cell(lane, i) = -0.0;
+    double own = -0.0;                                         // maximum over the lanes up to this one, of the column the lane was at
+    double left = -INFINITY;                                   // ... over the lanes before it, a step ahead; lane 0 keeps -infinity
+    bool odd = false;
+    // The records of a block of columns: column j0 + c of lane i was step j0 + c + i.  (Columns past the last one: none moves the way back.)
+    auto keep_records = [&](int j0, unsigned long long steps0, unsigned long long steps1) {
+        unsigned long long r = steps0 >> lane | (lane ? steps1 << (64 - lane) : ~0ull);        // (lane 0: always)
+        if (lane == 0) r = ~0ull;
+        if (n - j0 < 64) r |= ~0ull << (n - j0);
+        if (lane < m) records[j0 / 64 * m + lane] = r;
+    };
+    unsigned long long before = 0ull;                          // records of the block of steps before
+    for (int t0 = 0; t0 < steps; t0 += WAVE_BLOCK) {
+        const int half = t0 & WAVE_BLOCK;
+        double col[MOST_ROWS];
 #pragma unroll
-    for (int c = 0; c < AHEAD; ++c) cur[c] = row[c < n ? c : n - 1];
-    double before = -0.0;                                      // maximum over the lanes up to this one, column before
-    unsigned long long mine = 0;                               // records of column (lane) of the current 64
-    bool nan = false;
-    for (int j0 = 0; j0 < n; j0 += AHEAD) {
+        for (int k = 0; k < MOST_ROWS; ++k) {
+            const int i = wave + k * WAVES;
+            if (i < m) col[k] = t0 + lane < n ? S[(int64_t)i * n + t0 + lane] : -0.0;
+        }
 #pragma unroll
-        for (int c = 0; c < AHEAD; ++c) nxt[c] = row[j0 + AHEAD + c < n ? j0 + AHEAD + c : n - 1];
-#pragma unroll
-        for (int c = 0; c < AHEAD; ++c) {
-            if (j0 + c < n) {                                  // (uniform)
-                const double best = lane < m ? cur[c] + before : -INFINITY;      // (lanes past m never win a maximum)
-                nan |= best != best;
-                before = prefix_max<STEPS>(best);
-                const unsigned long long rec = __ballot(best > shifted<0x138, 0xf>(before)) | 1ull;     // wave_shr:1; lane 0 always
-                if (lane == (j0 & 63) + c) mine = rec;
+        for (int k = 0; k < MOST_ROWS; ++k) {
+            const int i = wave + k * WAVES;
+            if (i < m) {
+                cell(t0 + lane + i, i) = col[k];
+                odd |= !(col[k] <= 1e300);
             }
         }
-        const int end = j0 + AHEAD < n ? j0 + AHEAD : n, at = (j0 & ~63) + lane;
-        if (((end & 63) == 0 || end == n) && at < end) records[at] = mine;
+        __syncthreads();
+        if (wave == 0) {
+            constexpr int AHEAD = 8;
+            const double *entry = ring + half * WAVE_PITCH + lane;                 // (lanes past m: nothing reads what they find)
+            auto fetch = [&](double (&v)[AHEAD], int u0) {
 #pragma unroll
-        for (int c = 0; c < AHEAD; ++c) cur[c] = nxt[c];
+                for (int u = 0; u < AHEAD; ++u) v[u] = entry[(u0 + u) * WAVE_PITCH];
+            };
+            double cur[AHEAD], nxt[AHEAD];
+            uint32_t rec[2] = {0u, 0u};                        // a bit per step, the first one highest
+            fetch(cur, 0);
+#pragma unroll
+            for (int u0 = 0; u0 < WAVE_BLOCK; u0 += AHEAD) {
+                if (t0 + u0 < steps) {                         // (uniform)
+                    if (u0 + AHEAD < WAVE_BLOCK) fetch(nxt, u0 + AHEAD);
+                    diagonal_steps(own, left, rec[u0 >> 5], cur);
+#pragma unroll
+                    for (int u = 0; u < AHEAD; ++u) cur[u] = nxt[u];
+                } else {
+                    rec[u0 >> 5] <<= AHEAD;
+                }
+            }
+            const unsigned long long now = (unsigned long long)__brev(rec[1]) << 32 | __brev(rec[0]);
+            if (t0) keep_records(t0 - WAVE_BLOCK, before, now);        // (complete: their last step lies at most 62 behind t0)
+            if (t0 + WAVE_BLOCK >= steps && t0 < n) keep_records(t0, now, 0ull);
+            before = now;
+        }
+        __syncthreads();
     }
-    top = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(before), m - 1), __builtin_amdgcn_readlane(__double2loint(before), m - 1));
-    return __any(nan);
-}
-__global__ __launch_bounds__(64) void layer_map_wave_kernel(const double *__restrict__ S, int m, int n, int32_t *__restrict__ back,
-                                                            int32_t *__restrict__ f, double *__restrict__ total)
-{
-    __shared__ AlignShared sh;
-    const int lane = threadIdx.x;
-    unsigned long long *records = n <= (int)(sizeof(sh.records) / 8) ? sh.records : reinterpret_cast<unsigned long long *>(back);
-    double top;
-    const bool nan = m <= 16 ? align_columns<4>(S, m, n, records, top) : m <= 32 ? align_columns<5>(S, m, n, records, top) : align_columns<6>(S, m, n, records, top);
-    if (nan) {                                                 // (uniform)
-        align_threads(S, m, n, back, f, total, sh);
+    if (__syncthreads_or(odd)) {                               // (also orders the records)
+        align_threads(S, m, n, back, f, total, *reinterpret_cast<AlignShared *>(map_lds));
         return;
     }
-    __syncthreads();                                           // (one wave: orders its records)
-    if (lane == 0) *total = top;
-    int at = m - 1;
+    if (wave) return;
+    if (lane == m - 1) *total = own;
+    int up = 64 - m;                                           // 63 - (the layer chosen)
     for (int j0 = (n - 1) & ~63; j0 >= 0; j0 -= 64) {
-        const unsigned long long rec = records[j0 + lane < n ? j0 + lane : n - 1];
+        const unsigned long long rec = lane < m ? records[j0 / 64 * m + lane] : 0ull;
         int chosen = 0;
-        for (int k = n - 1 - j0 < 63 ? n - 1 - j0 : 63; k >= 0; --k) {
-            const unsigned long long r = (unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(rec >> 32), k) << 32 |
-                                         (unsigned)__builtin_amdgcn_readlane((int)(uint32_t)rec, k);
-            at = 63 - __clzll((long long)(r & (~0ull >> (63 - at))));
-            if (lane == k) chosen = at;
+#pragma unroll
+        for (int k0 = 56; k0 >= 0; k0 -= 8) {
+            if (j0 + k0 < n) {                                 // (uniform)
+#pragma unroll
+                for (int k = k0 + 7; k >= k0; --k) {
+                    // (up = leading zeros of the records up to the layer: the next one; written out, so that scalar instructions alone write it)
+                    const unsigned long long r = __ballot((uint32_t)(rec >> (k & 32)) & (1u << (k & 31)));
+                    unsigned long long upto;
+                    asm("s_lshr_b64 %1, -1, %0\n s_and_b64 %1, %1, %2\n s_flbit_i32_b64 %0, %1" : "+s"(up), "=&s"(upto) : "s"(r) : "scc");
+                    asm("v_writelane_b32 %0, %1, %2" : "+v"(chosen) : "s"(up), "n"(k));
+                }
+            }
         }
-        if (j0 + lane < n) f[j0 + lane] = chosen;
+        if (j0 + lane < n) f[j0 + lane] = 63 - chosen;
     }
 }
 
@@ -488,7 +535,7 @@ bool bad_dims(int m, int n, int rows, int L)
 
 }  // namespace
 
-// The similarity kernel's LDS size, set once per device.
+// The LDS sizes of the similarity and of the alignment in one wave, set once per device.
 specattn_status layer_map_configure()
 {
     constexpr int MAX_DEVICES = 64;
@@ -505,6 +552,12 @@ specattn_status layer_map_configure()
     if (hipFuncSetAttribute(reinterpret_cast<const void *>(&layer_kl_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kl_lds_bytes(KL_WAVES)) != hipSuccess) {
         (void)hipGetLastError();
         set_error("cannot reserve %d bytes of LDS", kl_lds_bytes(KL_WAVES));
+        return SPECATTN_EHIP;
+    }
+    if (hipFuncSetAttribute(reinterpret_cast<const void *>(&layer_map_wave_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)wave_lds_bytes(WAVE_MOST, WAVE_RECORDS / WAVE_MOST * 64)) != hipSuccess) {
+        (void)hipGetLastError();
+        set_error("cannot reserve %zu bytes of LDS", wave_lds_bytes(WAVE_MOST, WAVE_RECORDS / WAVE_MOST * 64));
         return SPECATTN_EHIP;
     }
     done[dev] = true;
@@ -571,9 +624,15 @@ specattn_status specattn_layer_map(const double *S, int32_t m, int32_t n, int32_
     if (!workspace) { set_error("workspace is NULL, %zu bytes needed", need); return SPECATTN_EWORKSPACE; }
     if (reinterpret_cast<uintptr_t>(workspace) % 256) { set_error("workspace must be 256-byte aligned"); return SPECATTN_EWORKSPACE; }
     if (workspace_bytes < need) { set_error("workspace has %zu bytes, %zu needed", workspace_bytes, need); return SPECATTN_EWORKSPACE; }
-    const bool one_wave = m <= 64 && (m > 1 || n <= MAP_LDS_BACK / 4);          // (the workspace of a single layer holds no records)
-    hipLaunchKernelGGL(one_wave ? layer_map_wave_kernel : layer_map_kernel, dim3(1), dim3((m + 63) / 64 * 64), 0, static_cast<hipStream_t>(stream), S, m,
-                       n, static_cast<int32_t *>(workspace), f, total);
+    hipStream_t hs = static_cast<hipStream_t>(stream);
+    int32_t *back = static_cast<int32_t *>(workspace);
+    if (m <= WAVE_MOST) {
+        const specattn_status st = layer_map_configure();
+        if (st != SPECATTN_OK) return st;
+        hipLaunchKernelGGL(layer_map_wave_kernel, dim3(1), dim3(WAVE_THREADS), wave_lds_bytes(m, n), hs, S, m, n, back, f, total);
+    } else {
+        hipLaunchKernelGGL(layer_map_kernel, dim3(1), dim3((m + 63) / 64 * 64), 0, hs, S, m, n, back, f, total);
+    }
     return check_launch("layer_map_kernel");
 }
 

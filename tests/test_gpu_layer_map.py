@@ -130,6 +130,23 @@ def test_alignment_in_one_wave(m, n):
     assert np.array_equal([v], [v_ref], equal_nan=True) and np.array_equal(f, f_ref)
 
 
+@pytest.mark.parametrize("m,n", [(1, 64), (2, 63), (64, 1), (64, 64), (64, 65), (63, 66), (2, 128), (64, 129), (5, 192), (40, 9900)])
+def test_alignment_by_diagonals(m, n):
+    """Steps and columns around the blocks of 64, records in LDS and in memory; entries whose sums could end in a NaN, for which the general
+    form (more than 64 layers, the others -infinity) is the measure."""
+    rng = np.random.default_rng(m * 13 + n)
+    S = np.round(rng.normal(size=(m, n)) * 2)
+    f_ref, v_ref = oracle.layer_map(S)
+    f, v = gpu_map(S)
+    assert v == v_ref and np.array_equal(f, f_ref)
+    for large in (2e300, np.inf):
+        S[rng.integers(m, size=3), rng.integers(n, size=3)] = large
+        S[rng.integers(m, size=n), np.arange(n)] = -np.inf
+        f, v = gpu_map(S)
+        f_ref, v_ref = gpu_map(np.vstack([S, np.full((65 - m, n), -np.inf)]))
+        assert np.array_equal([v], [v_ref], equal_nan=True) and np.array_equal(f, f_ref)
+
+
 def test_layers_compared_with_themselves():
     ad, _ = W.layer_attention_maps(seed=9, m=5, n=5, rows=4, L=128)
     S = gpu_similarity(ad, ad)
