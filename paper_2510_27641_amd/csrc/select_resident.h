@@ -59,10 +59,27 @@ struct ResidentShared {
 };
 
 // Sum of BPL counters of a lane's row of bins.  Rows start 128 or 256 bytes apart: every lane takes them in an order of its own, so
-// that the lanes of a read fall on different banks.
-template <int BPL> __device__ __forceinline__ unsigned long long row_of_bins(const unsigned long long *row, int swizzle)
+// that the lanes of a read fall on different banks.  Bound by the reads' latency: PAIRED ones bring two counters each and are all on their way
+// together, half as many as before in rounds of eight (us: 8 rows of 1024 5.2 / 4.8, of 8192 7.2 / 7.1, 256 of 16384 11.0 / 10.8).  Beside a row of 64 entries
+// per thread there are no registers for that (1024 rows of 32768 46.4 / 51.8): there single ones, eight at a time.
+template <int BPL, bool PAIRED> __device__ __forceinline__ unsigned long long row_of_bins(const unsigned long long *row, int lane)
 {
     unsigned long long sum = 0ull;
+    if constexpr (PAIRED) {
+        typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));
+        constexpr int PAIRS = BPL / 2;
+        const int swizzle = BPL == 32 ? lane & 15 : (lane >> 1) & 7;
+        const u64x2 *pairs = reinterpret_cast<const u64x2 *>(row);
+        u64x2 v[PAIRS];
+#pragma unroll
+        for (int j = 0; j < PAIRS; ++j) v[j] = pairs[j ^ swizzle];
+        __builtin_amdgcn_sched_barrier(0);
+        unsigned long long other = 0ull;                   // (two chains)
+#pragma unroll
+        for (int j = 0; j < PAIRS; ++j) { sum += v[j][0]; other += v[j][1]; }
+        return sum + other;
+    }
+    const int swizzle = BPL == 32 ? lane & 31 : (lane >> 1) & (BPL - 1);
 #pragma unroll
     for (int j0 = 0; j0 < BPL; j0 += 8) {
         unsigned long long v[8];
@@ -70,7 +87,7 @@ template <int BPL> __device__ __forceinline__ unsigned long long row_of_bins(con
         for (int j = 0; j < 8; ++j) v[j] = row[(j0 + j) ^ swizzle];
 #pragma unroll
         for (int j = 0; j < 8; ++j) sum += v[j];
-        __builtin_amdgcn_sched_barrier(0);                 // (not all loads at once: the caller's registers hold the row)
+        __builtin_amdgcn_sched_barrier(0);                 // (not all loads at once)
     }
     return sum;
 }
@@ -93,11 +110,11 @@ __device__ __forceinline__ int pick_bin(unsigned long long counter, int e_field,
 
 // Decision of the first pass, by the first wave alone.  Its lanes own half an octave of the window each, lane 0 the highest.  (sh.below:
 // the window's entries do not reach the target, or top_p is 1, and there are entries below it.)
-template <int NW> __device__ __forceinline__ void locate_first(const unsigned long long *fine, int e_low, float top_p, ResidentShared &sh)
+template <int NW, bool PAIRED> __device__ __forceinline__ void locate_first(const unsigned long long *fine, int e_low, float top_p, ResidentShared &sh)
 {
     const int lane = threadIdx.x;
     double low = lane < NW ? sh.low[lane] : 0.0;
-    const unsigned long long sum = row_of_bins<FINE / 64>(fine + (63 - lane) * (FINE / 64), lane & 31);
+    const unsigned long long sum = row_of_bins<FINE / 64, PAIRED>(fine + (63 - lane) * (FINE / 64), lane);
     const double lm = fraction_mass(sum, e_low + ((63 - lane) >> 1));
     const unsigned lc = (unsigned)(sum >> CNT_SHIFT);
     double incl = lm;
@@ -193,12 +210,12 @@ __device__ __forceinline__ void locate_below(const unsigned long long *octave, f
 }
 
 // Decision of a later pass: DIGIT_BINS bins of 2^shift bit patterns each from `place.lo` up.
-__device__ __forceinline__ void locate_next(const unsigned long long *hist, int shift, float top_p, Place &place)
+template <bool PAIRED> __device__ __forceinline__ void locate_next(const unsigned long long *hist, int shift, float top_p, Place &place)
 {
     constexpr int BPL = DIGIT_BINS / 64;
     const int lane = threadIdx.x, e_field = (int)(place.lo >> 23);
     const double goal = top_p < 1.0f ? place.target : INFINITY;
-    const unsigned long long sum = row_of_bins<BPL>(hist + (63 - lane) * BPL, (lane >> 1) & (BPL - 1));
+    const unsigned long long sum = row_of_bins<BPL, PAIRED>(hist + (63 - lane) * BPL, lane);
     const double lm = fraction_mass(sum, e_field);
     const unsigned lc = (unsigned)(sum >> CNT_SHIFT);
     double incl = lm;
@@ -379,6 +396,7 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
     // 256 x 32768 16.9 / 16.3.  Up to 8192 entries the bins are the faster way: few entries, seldom another pass (8 x 8192 7.2 / 7.4,
     // 8 x 2048 5.2 / 5.5), and where rows come in turns (NV4 = 16) another row fills the wait (1024 x 32768 48.1 / 48.2).
     constexpr bool LISTS = ITEM * NV4 > 8192 && NV4 <= 8;
+    constexpr bool PAIRED = NV4 <= 8;                 // (row_of_bins)
     constexpr bool FLAT = ITEM * NV4 >= 4096;         // flat rows are added up before they reach a counter
     constexpr bool WORDS = NV4 >= 8;                  // compaction by words of 32 positions instead of item by item
     constexpr int TABLE = WORDS ? ITEM / 32 * NV4 : (NV4 * NW + 63) / 64 * 64;
@@ -578,7 +596,7 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
             if (lane == 63) sh.low[wave] = low;
         }
         __syncthreads();
-        if (wave == 0) locate_first<NW>(hist1, e_low, a.top_p, sh);
+        if (wave == 0) locate_first<NW, PAIRED>(hist1, e_low, a.top_p, sh);
         __syncthreads();
         if (sh.below) {                                            // (uniform) rare
             for_entries([&](uint32_t x) { if (x && (int)(x >> 23) < e_low) atomicAdd(hist2 + (x >> 23), fraction_entry(x)); });
@@ -646,7 +664,7 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
                     break;
                 }
                 if (wave == 0) {
-                    locate_next(cur, shift, a.top_p, at);
+                    locate_next<PAIRED>(cur, shift, a.top_p, at);
                     if (lane == 0) sh.place = at;
                 }
                 __syncthreads();
