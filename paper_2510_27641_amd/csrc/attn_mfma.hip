@@ -22,13 +22,32 @@ __device__ __forceinline__ float wave_sum(float v)
     return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), 63));
 }
 
+// What the merge needs of a launch, apart from the rest: it is a launch behind another one and starts with a trip to memory for its arguments,
+// so they are few, and all fetched at once.
+struct MergeArgs {
+    const uint32_t *row_parts;            // as in Plan
+    const float *part_ml, *part_o;
+    float *out, *lse;
+    void *out_lowp;
+    uint32_t per_h, per_t;
+    int H_q, H_kv, T, heads, g_first, qtp;
+    // the new tokens behind the cache
+    float sm_scale;
+    const uint16_t *q, *k_new, *v_new;
+    int64_t q_stride_b, q_stride_h, q_stride_t;
+};
+
 // After the main kernel, one workgroup per (query row, row): rows shared by several workgroups get
 // their partials (r, w) combined; rows without any kept position get out = 0, lse = -inf.  When the
-// caller gave the new tokens behind the cache, every row goes through here (the main kernel then
+// caller gave the new tokens behind the cache (TAIL), every row goes through here (the main kernel then
 // leaves partials only) and query t also attends to new tokens 0..t.
-// Bound by latency: the row's shares, then a trip to memory and a chain of sums per eight partials.  The head dimension is a
-// constant, the grid and the plan leave no division, and every load of a trip is requested before the first partial is used; a short
-// rest asks for two or five, since eight are a chain too long there.  What the new tokens need is requested ahead of the shares.
+// Bound by latency: the arguments, the row's shares, then a trip to memory and two chains of sums per eight partials.  Head dimension and
+// element type are constants, the grid and the plan leave no division, and every load of a trip is requested before the first partial is used; a short
+// rest asks for two or five, since eight are a chain too long there.  What the new tokens need is requested ahead of the shares, in one go.
+// (With the element type tested at every one of those loads, each waited for the one before; with all arguments of the launch, fetched in three
+// turns; and with the partials joined one after the other - as it was / now, us,
+// with selection and attention: 32 rows of 2044 positions in chunks with new tokens 20.0 / 17.7, 8 rows of 8192 19.6 / 19.0, 16 of 8192 (d = 64) 19.2 / 18.7; 64
+// dense rows of up to 32768 with new tokens 111.7 / 108.6.)
 // A pass of selection, attention and merge with every divisor and share worked out here from the cost line / with them handed over, us:
 // 32 rows of 2044 positions in chunks with new tokens 24.6 / 21.9, 32 rows of 8192 (d = 64) 22.6 / 21.2, 16 layers of 64 rows of 32768
 // 867 / 839 (the start of the main kernel, below, among it).
@@ -37,54 +56,63 @@ __device__ __forceinline__ float wave_sum(float v)
 // makes no difference, and 16 layers of 64 rows take 797.6 us with scalar loads there, 798.8 without).  Scalar / vector, us for both launches:
 // one row of 270 tiles among 31 empty ones (268 partials) 31.3 / 27.2, one of 500 among 31 of 3 (131 partials) 21.8 / 19.6, 8 ragged
 // rows of up to 270 13.6 / 13.3; over 440 calls of few rows 4 % on average, none slower.
-template <int D> __global__ __launch_bounds__(D) void merge_partials_kernel(AttnLaunch a, Plan plan, int qtp)
+template <int D, bool F16, bool TAIL> __global__ __launch_bounds__(D) void merge_partials_kernel(MergeArgs a)
 {
     __shared__ float red[2 * SPECATTN_MAX_T];
+    // (one batch, as in the main kernel)
+#define SPECATTN_PRELOAD(x) asm volatile("" ::"s"(x))
+    SPECATTN_PRELOAD(a.row_parts); SPECATTN_PRELOAD(a.part_ml); SPECATTN_PRELOAD(a.part_o); SPECATTN_PRELOAD(a.out); SPECATTN_PRELOAD(a.lse); SPECATTN_PRELOAD(a.out_lowp);
+    SPECATTN_PRELOAD(a.per_h); SPECATTN_PRELOAD(a.per_t); SPECATTN_PRELOAD(a.H_q); SPECATTN_PRELOAD(a.H_kv); SPECATTN_PRELOAD(a.T); SPECATTN_PRELOAD(a.heads);
+    SPECATTN_PRELOAD(a.g_first); SPECATTN_PRELOAD(a.qtp);
+    if (TAIL) {
+        SPECATTN_PRELOAD(a.sm_scale); SPECATTN_PRELOAD(a.q); SPECATTN_PRELOAD(a.k_new); SPECATTN_PRELOAD(a.v_new);
+        SPECATTN_PRELOAD(a.q_stride_b); SPECATTN_PRELOAD(a.q_stride_h); SPECATTN_PRELOAD(a.q_stride_t);
+    }
+#undef SPECATTN_PRELOAD
     const int q = blockIdx.x, r = blockIdx.y;
-    const int b = div_h(plan, r), h = r - b * a.H_kv;
-    const int gh = div_t(plan, q), t = q - gh * a.T;
-    const int head = attn_query_head(a, plan.heads, h, gh);
+    const uint32_t parts = a.row_parts[r];
+    const int b = (int)__umulhi((uint32_t)r << 1, a.per_h), h = r - b * a.H_kv;              // (div_h, div_t)
+    const int gh = (int)(((uint32_t)q * a.per_t) >> 16), t = q - gh * a.T;
+    const int head = h * a.heads + a.g_first + gh;
     const int64_t orow = ((int64_t)b * a.H_q + head) * a.T + t;
     const int dv = threadIdx.x;
-    const bool tail = a.k_new != nullptr;
-    const uint32_t parts = plan.row_parts[r];
-    float qe = 0.0f, ke[SPECATTN_MAX_T], ve[SPECATTN_MAX_T];
-    if (tail) {
-        const int64_t noff = (int64_t)r * a.T * D + dv;
-        qe = ld_elem(a.q, (int64_t)b * a.q_stride_b + (int64_t)head * a.q_stride_h + (int64_t)t * a.q_stride_t + dv, a.dtype);
+    auto value = [](uint16_t x) { return F16 ? (float)__builtin_bit_cast(_Float16, x) : __uint_as_float((uint32_t)x << 16); };
+    uint16_t qe = 0, ke[SPECATTN_MAX_T], ve[SPECATTN_MAX_T];
+    if constexpr (TAIL) {
+        const uint16_t *kn = a.k_new + (int64_t)r * a.T * D + dv, *vn = a.v_new + (int64_t)r * a.T * D + dv;
+        qe = a.q[(int64_t)b * a.q_stride_b + (int64_t)head * a.q_stride_h + (int64_t)t * a.q_stride_t + dv];
 #pragma unroll
-        for (int p = 0; p < SPECATTN_MAX_T; ++p) {
-            ke[p] = p <= t ? ld_elem(a.k_new, noff + (int64_t)p * D, a.dtype) : 0.0f;
-            ve[p] = p <= t ? ld_elem(a.v_new, noff + (int64_t)p * D, a.dtype) : 0.0f;
+        for (int p = 0; p < SPECATTN_MAX_T; ++p) {              // (tokens past t: t's again, not used)
+            ke[p] = kn[(p < t ? p : t) * D];
+            ve[p] = vn[(p < t ? p : t) * D];
         }
     }
     Merge acc;
     if (parts != ROW_EMPTY) {
         const int w0 = parts & 0xffffu, w1 = parts >> 16;
-        if (w0 == w1 && !tail) return;              // finished by its only workgroup
+        if (w0 == w1 && !TAIL) return;              // finished by its only workgroup
         auto trip = [&](int wb, auto most) {        // partials wb .. w1, at most N
             constexpr int N = decltype(most)::value;
             float mw[N], lw[N], ow[N];
             uint32_t s[N];
 #pragma unroll
             for (int k = 0; k < N; ++k) {           // (behind the last share: that one's again)
-                s[k] = (uint32_t)((min(wb + k, w1) + r) * qtp + q);
+                s[k] = (uint32_t)((min(wb + k, w1) + r) * a.qtp + q);
                 if (N == 8) asm("" : "+v"(s[k]));   // (the same in all lanes, but no scalar loads: above)
-                const float2 ml = reinterpret_cast<const float2 *>(plan.part_ml)[s[k]];
+                const float2 ml = reinterpret_cast<const float2 *>(a.part_ml)[s[k]];
                 mw[k] = ml.x;
                 lw[k] = ml.y;
             }
             __builtin_amdgcn_sched_barrier(0);      // the weights first: they are used first
 #pragma unroll
-            for (int k = 0; k < N; ++k) ow[k] = plan.part_o[s[k] * D + dv];
+            for (int k = 0; k < N; ++k) ow[k] = a.part_o[s[k] * D + dv];
             __builtin_amdgcn_sched_barrier(0);      // all requested before the first is used
 #pragma unroll
             for (int k = 0; k < N; ++k) {           // (a weight of zero must not meet an infinite value)
                 mw[k] = wb + k <= w1 ? mw[k] : -INFINITY;
                 ow[k] = wb + k <= w1 ? ow[k] : 0.0f;
             }
-#pragma unroll
-            for (int k = 0; k < N; ++k) acc.add(mw[k], lw[k], ow[k]);
+            acc.add_all(mw, lw, ow);
         };
         int wb = w0;
         for (; wb + 7 <= w1; wb += 8) trip(wb, std::integral_constant<int, 8>{});
@@ -93,26 +121,37 @@ template <int D> __global__ __launch_bounds__(D) void merge_partials_kernel(Attn
         else if (left > 2) trip(wb, std::integral_constant<int, 5>{});
         else if (left > 0) trip(wb, std::integral_constant<int, 2>{});
     }
-    if (tail) {
+    if constexpr (TAIL) {
         // scores of the query row against new tokens 0..t, over all threads of the workgroup
         const int lane = dv & 63, wave = dv >> 6;
 #pragma unroll
         for (int p = 0; p < SPECATTN_MAX_T; ++p) {
             if (p > t) break;                       // (uniform)
-            const float x = wave_sum(qe * ke[p]);
+            const float x = wave_sum(value(qe) * value(ke[p]));
             if (lane == 0) red[wave * SPECATTN_MAX_T + p] = x;
         }
         __syncthreads();
         const float scale2 = a.sm_scale * 1.4426950408889634f;       // m is in log2 units
+        float mw[SPECATTN_MAX_T], lw[SPECATTN_MAX_T], ow[SPECATTN_MAX_T];
 #pragma unroll
-        for (int p = 0; p < SPECATTN_MAX_T; ++p)
-            if (p <= t) acc.add((red[p] + (D > 64 ? red[SPECATTN_MAX_T + p] : 0.0f)) * scale2, 1.0f, ve[p]);
+        for (int p = 0; p < SPECATTN_MAX_T; ++p) {
+            mw[p] = p <= t ? (red[p] + (D > 64 ? red[SPECATTN_MAX_T + p] : 0.0f)) * scale2 : -INFINITY;
+            lw[p] = p <= t ? 1.0f : 0.0f;
+            ow[p] = p <= t ? value(ve[p]) : 0.0f;
+        }
+        acc.add_all(mw, lw, ow);
     }
     const float res = acc.l > 0.0f ? acc.o / acc.l : 0.0f;
     a.out[orow * D + dv] = res;
-    if (a.out_lowp) st_lowp(a.out_lowp, orow * D + dv, res, a.dtype);
+    if (a.out_lowp) st_lowp(a.out_lowp, orow * D + dv, res, F16 ? SPECATTN_F16 : SPECATTN_BF16);
     // m is in log2 units of the scaled scores
     if (a.lse && dv == 0) a.lse[orow] = acc.l > 0.0f ? (acc.m + log2f(acc.l)) * 0.6931471805599453f : -INFINITY;
+}
+
+template <int D> auto merge_variant(bool f16, bool tail)
+{
+    return f16 ? tail ? merge_partials_kernel<D, true, true> : merge_partials_kernel<D, true, false>
+               : tail ? merge_partials_kernel<D, false, true> : merge_partials_kernel<D, false, false>;
 }
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -255,8 +294,11 @@ static specattn_status launch_chunk(const AttnLaunch &a, hipStream_t stream)
     }
     st = check_launch("attn_mfma_kernel");
     if (st != SPECATTN_OK) return st;
-    const auto merge = a.d == 64 ? merge_partials_kernel<64> : merge_partials_kernel<128>;
-    hipLaunchKernelGGL(merge, dim3(QT, rows), dim3(a.d), 0, stream, a, plan, qtp);
+    const MergeArgs m = {plan.row_parts, plan.part_ml, plan.part_o, a.out, a.lse, a.out_lowp, plan.per_h, plan.per_t, a.H_q, a.H_kv, a.T, plan.heads, a.g_first, qtp,
+                         a.sm_scale, static_cast<const uint16_t *>(a.q), static_cast<const uint16_t *>(a.k_new), static_cast<const uint16_t *>(a.v_new),
+                         a.q_stride_b, a.q_stride_h, a.q_stride_t};
+    const auto merge = a.d == 64 ? merge_variant<64>(f16, a.k_new != nullptr) : merge_variant<128>(f16, a.k_new != nullptr);
+    hipLaunchKernelGGL(merge, dim3(QT, rows), dim3(a.d), 0, stream, m);
     return check_launch("merge_partials_kernel");
 }
 

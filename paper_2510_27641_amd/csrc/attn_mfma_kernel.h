@@ -518,6 +518,31 @@ struct Merge {
         o = o * fa + ow * fb;
         m = mn;
     }
+    // N at once: their largest first, then weights that wait for nothing else, and sums in two chains.
+    template <int N> __device__ __forceinline__ void add_all(const float (&mw)[N], const float (&lw)[N], const float (&ow)[N])
+    {
+        float top[N];
+#pragma unroll
+        for (int k = 0; k < N; ++k) top[k] = mw[k];
+#pragma unroll
+        for (int step = 1; step < N; step *= 2)
+#pragma unroll
+            for (int k = 0; k + step < N; k += 2 * step) top[k] = fmaxf(top[k], top[k + step]);
+        const float mn = fmaxf(m, top[0]), ref = mn == -INFINITY ? 0.0f : mn;
+        float f[N];
+#pragma unroll
+        for (int k = 0; k < N; ++k) f[k] = __builtin_amdgcn_exp2f(mw[k] - ref);
+        const float fa = __builtin_amdgcn_exp2f(m - ref);
+        float l2[2] = {l * fa, 0.0f}, o2[2] = {o * fa, 0.0f};
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            l2[k & 1] = fmaf(f[k], lw[k], l2[k & 1]);
+            o2[k & 1] = fmaf(f[k], ow[k], o2[k & 1]);
+        }
+        l = l2[0] + l2[1];
+        o = o2[0] + o2[1];
+        m = mn;
+    }
 };
 // Sum and largest over the four lanes l, l + 16, l + 32, l + 48, in each of them (exchanged on the vector ALU, not through LDS).
 template <typename F> __device__ __forceinline__ float over_rows(float x, F &&join)
