@@ -2,6 +2,7 @@
 // attn_mfma_kernel.h, its variants in three translation units (this one: index lists, d = 128).
 #include "attn_mfma_kernel.h"
 
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -236,23 +237,22 @@ size_t attn_mfma_workspace_min_bytes(int rows, int G, int T, int d)
     return workspace_for(rows < MAX_ROWS ? rows : MAX_ROWS, query_tiles(G, T, NARROW), d);
 }
 
-// Shares that the cost line is cut into: as many as there are workgroups, but fewer where the rows are few and short.  There a share
-// is a few tiles, which the waves of a workgroup take at the same time anyway, and what counts is how many partials the merge has to go
-// through, eight to a trip to memory, and how many shares hold nothing but a row's start.  So 64, doubled where the shares are longer
-// than: 4 units where that leaves a row less than eight partials, 12 (4 where a tile is much work: 64 positions, two query tiles or
-// more) where it leaves it less than sixteen, 10 beyond; and one per workgroup where the rows of the call, empty ones among them, have no more
-// than eight tiles on average: rows of equal counts then take one trip however they are shared out.  (Ragged rows may take more there.  With
-// the longest row tested instead, us: one row of 270 tiles among 15 empty ones 27.2 / 18.3, one of 40 among 15 of 3 11.6 / 10.6, but one of
-// 12 among 31 of 3 9.2 / 9.6 and, with one query row each, 8.5 / 9.4; with the partials of the longest row tested, 16 rows of 12 9.4 / 10.1.)
-// Measured with 64 / 128 / 256 shares, us for both launches: 4 rows of 300
-// units in all 12.3 / 13.3 / 15.5, of 1176 17.0 / 16.4 / 19.2; 8 rows of 600 13.0 / 13.2 / 14.3, of 1224 16.3 / 14.8 / 16.2 (but of 2200 and
-// 64 query rows, from memory, 1.3 more with 128 than with 256); 16 rows of 272 10.5 / 9.9 / 10.1, of 1200 16.0 / 14.1 / 14.6, of 2448 22.2 / 17.5 / 17.4; 32 rows of 544 10.5 / 10.5 / 10.4, of
-// 800 13.5 / 12.0 / 11.5; d = 64, 40 query rows: 8 rows of 152 11.0 / 11.0 / 10.8, 16 rows of 432 13.1 / 11.7 / 12.9, of 704 15.6 / 14.0 / 13.6.
-static void share_lines(Plan &plan, int rows, int nqt, int d)
+// Calls of up to 64 rows with few tiles in all: every share is `unit` tiles (3, 4, 6, 8, 12, ... 32) of one row, so that no workgroup starts twice or
+// holds a row's start alone, and a call's time is that of one share.  How many shares: fewer tiles in each are fewer to wait for, and
+// spread a call's bytes over more CUs; but from about 48 parts of a row on the merge, eight parts to a trip to memory, costs more than that saves, and
+// with nearly all CUs taken the last shares come late.  So the least unit that leaves 218 of 256 workgroups a share (fewer where rounding
+// rows up could take the others) and a row 48 parts; three tiles where that is one tile per wave and few partials.  Longer ones, whose shares are many rounds of tiles, are cut from the line with its equal shares.
+// The line, cut into 64, 128 or 256 shares / units of 4 / 6 / 8 / 12 / 16 / 24 tiles, us for both launches, rows x tiles:
+//   8 x 25 10.3 / 9.6 / 10.6 / 11.4;  8 x 48 11.4 / 10.5 / 11.2 / 11.5;  8 x 154 14.7 / - / 14.0 / 14.1 / 13.8 / 14.5;  8 x 457 20.2 / - / - / - / - / 19.8 / 19.5
+//   16 x 60 13.4 / 13.3 / 13.0 / 13.1 / 13.2;  16 x 115 15.3 / - / - / 15.3 / 14.6 / 14.8;  32 x 56 14.8 / - / - / 14.5 / 14.1 / 14.8;  32 x 108 18.3 / - / - / - / - / 17.9 / 18.5
+//   64 x 9 11.6 / 10.7 / 11.2 / 11.8;  64 x 19 13.5 / - / 12.8 / 13.3 / 13.3;  64 x 37 15.9 / - / - / - / 15.1 / 15.6 / 17.5;  64 x 61 19.4 / - / - / - / - / - / 19.6
+//   (units of 3 / 4) 8 x 9 9.0 / 9.2, 1 x 14 8.3 / 8.5, 4 x 16 (d = 64) 10.3 / 10.7, but 8 x 25 9.7 / 9.6, 64 x 9 11.0 / 10.7
+//   1 x 99 11.0 / 9.3 / 9.5 / 9.5 / 9.9;  1 x 573 14.3 / 17.5 / 15.2 / 14.4 / 13.9 / 14.2 / 15.6;  4 x 128 (d = 64) 14.9 / 12.9 / 13.5 / 13.8 / 15.0
+static void share_units(Plan &plan, int rows)
 {
-    auto longest = [&](int n) { return n >= plan.n_wg ? 0 : n * (n < 8 * rows || (n < 16 * rows && d == 64 && nqt >= 2) ? 4 : n < 16 * rows ? 12 : 10); };
-    plan.line_64 = longest(64);
-    plan.line_128 = longest(128);
+    const int goal = std::min({plan.n_wg * 218 / 256, plan.n_wg - rows, 48 * rows});
+    plan.unit_line = rows > FEW_ROWS || goal <= 1 ? -1 : (rows > 32 ? 16 : rows > 4 ? 24 : 32) * goal;
+    plan.per_share = goal <= 1 ? 0 : (uint32_t)((((uint64_t)1 << 32) + goal - 1) / goal);
 }
 
 static specattn_status launch_chunk(const AttnLaunch &a, hipStream_t stream)
@@ -263,7 +263,7 @@ static specattn_status launch_chunk(const AttnLaunch &a, hipStream_t stream)
     const int nqt = (QT + 15) / 16, qtp = nqt * 16;
     Plan plan;
     plan.n_wg = attn_mfma_workgroups();
-    share_lines(plan, rows, nqt, a.d);
+    share_units(plan, rows);
     plan.heads = a.H_q / a.H_kv;
     plan.group = G;
     plan.per_h = (uint32_t)((((uint64_t)1 << 31) + a.H_kv - 1) / a.H_kv);

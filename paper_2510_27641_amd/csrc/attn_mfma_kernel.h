@@ -354,7 +354,8 @@ struct Plan {
     float *part_o;            // [slots][16 * NQT][d]
     uint32_t *row_parts;      // [rows] in the workspace: the shares that hold a row's first (low half) and last tile, or ROW_EMPTY
     int n_wg;
-    int line_64, line_128;    // lines of up to so many units are cut into 64 or 128 shares (share_lines)
+    int unit_line;            // calls of up to so many tiles are cut into shares of single rows (share_units), or -1
+    uint32_t per_share;       // 2^32 / (their number to aim for), rounded up
     int heads, group;         // query heads per kv head: in all, and in this launch
     uint32_t per_h, per_t;    // 2^31 / H_kv and 2^16 / T, rounded up
 };
@@ -446,7 +447,7 @@ __device__ __forceinline__ int floor_div(int64_t a, int b)
     return (int)floor((double)a / (double)b);
 }
 
-// The first n = min(shares, total) workgroups share the line: workgroup w takes [w * total / n, (w + 1) * total / n),
+// The first n = min(n_wg, total) workgroups share the line: workgroup w takes [w * total / n, (w + 1) * total / n),
 // so shares differ by at most one unit and none of them is empty (every workgroup between the first and the
 // last of a row therefore holds tiles of that row, which the merge relies on).
 // Long shares are tilted (TILT_FROM): the XCDs of odd number stream more slowly than the others while all of them read.  With
@@ -461,24 +462,21 @@ constexpr int TILT = 5;
 // share 24.6 / 24.7, of 33 28.6 / 28.6, of 38 32.0 / 31.7, of 62 46.8 / 46.1, of 97 67.8 / 67.6; 16 rows of 40 34.7 / 34.8, of 59 47.4 / 46.8).  Not where rows
 // are so many that equal counts make every share whole rows: there a moved boundary costs a partial (256 rows of 2000 positions 48.3 / 51.2).
 constexpr int TILT_FROM = 32;
-template <int TILE> __device__ __forceinline__ Share<TILE> make_share(const Plan &plan, int total, int rows, int w)
+template <int TILE> __device__ __forceinline__ Share<TILE> make_share(int total, int n_wg, int rows, int w)
 {
-    // (This is on the way to a workgroup's first request: no branches, and the usual numbers of workgroups and shares are powers of two, for
-    // which a shift gives the same floor as the division.)
-    const int n_wg = plan.n_wg;
-    const bool few = (total <= plan.line_128) & (total > (8 + SEG_COST) * rows);
-    const int shares = few ? total <= plan.line_64 ? 64 : 128 : n_wg;
+    // (This is on the way to a workgroup's first request: no branches, and the usual numbers of workgroups are powers of two, for which a
+    // shift gives the same floor as the division.)
     int move = ((w >> 1) ^ (w >> 2)) & 1 ? -TILT : TILT;       // of boundary w or w + 1, whichever is odd
     move = (total >= TILT_FROM * n_wg) & ((rows * 2 <= n_wg) | ((total & (n_wg - 1)) != 0)) ? move : 0;
     const int64_t from = (int64_t)(w * 128 + ((w & 1) ? move : 0)) * total, to = (int64_t)(w * 128 + 128 + ((w & 1) ? 0 : move)) * total;
     Share<TILE> s;
-    s.c0 = (int)(from >> (38 - __clz(shares)));
-    s.c1 = (int)(to >> (38 - __clz(shares)));
-    if (__builtin_expect((shares & (shares - 1)) != 0, 0)) {   // (equal shares: share_index deals these to XCDs as they come)
-        s.c0 = floor_div((int64_t)w * total, shares);
-        s.c1 = floor_div((int64_t)(w + 1) * total, shares);
+    s.c0 = (int)(from >> (38 - __clz(n_wg)));
+    s.c1 = (int)(to >> (38 - __clz(n_wg)));
+    if (__builtin_expect((n_wg & (n_wg - 1)) != 0, 0)) {       // (equal shares: share_index deals these to XCDs as they come)
+        s.c0 = floor_div((int64_t)w * total, n_wg);
+        s.c1 = floor_div((int64_t)(w + 1) * total, n_wg);
     }
-    const bool units = total < shares;                         // fewer units than shares: one each
+    const bool units = total < n_wg;                           // fewer units than shares: one each
     s.c0 = min(units ? w : s.c0, total);
     s.c1 = min(units ? w + 1 : s.c1, total);
     return s;
@@ -623,7 +621,7 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
     SPECATTN_PRELOAD(a.g_first); SPECATTN_PRELOAD(a.k_new);
     SPECATTN_PRELOAD(a.out); SPECATTN_PRELOAD(a.out_lowp); SPECATTN_PRELOAD(a.lse);
     SPECATTN_PRELOAD(plan.part_ml); SPECATTN_PRELOAD(plan.part_o); SPECATTN_PRELOAD(plan.row_parts);
-    SPECATTN_PRELOAD(plan.n_wg); SPECATTN_PRELOAD(plan.line_64); SPECATTN_PRELOAD(plan.line_128); SPECATTN_PRELOAD(plan.heads); SPECATTN_PRELOAD(plan.group); SPECATTN_PRELOAD(plan.per_h); SPECATTN_PRELOAD(plan.per_t);
+    SPECATTN_PRELOAD(plan.n_wg); SPECATTN_PRELOAD(plan.unit_line); SPECATTN_PRELOAD(plan.per_share); SPECATTN_PRELOAD(plan.heads); SPECATTN_PRELOAD(plan.group); SPECATTN_PRELOAD(plan.per_h); SPECATTN_PRELOAD(plan.per_t);
     if (LAYOUT != CONTIGUOUS) { SPECATTN_PRELOAD(a.page_table); SPECATTN_PRELOAD(a.page_shift); SPECATTN_PRELOAD(a.max_pages); SPECATTN_PRELOAD(a.kv_stride_page); }
     if (SRC == LIST) { SPECATTN_PRELOAD(a.indices); SPECATTN_PRELOAD(a.idx_stride); }
     if (SRC == MASK) { SPECATTN_PRELOAD(a.kept_mask); SPECATTN_PRELOAD(a.block_counts); SPECATTN_PRELOAD(a.blocks_per_row); SPECATTN_PRELOAD(a.n_max); }
@@ -645,11 +643,23 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
     // every row's local tile range without a table, a barrier or a search; more rows go through tables in LDS.
     const bool few_rows = rows <= FEW_ROWS;              // uniform
     int row_lo = 0, row_cnt = 0, total;                  // few rows: cost prefix and kept count of row `lane`
+    int unit = 0;                                        // tiles of a share that is a part of one row, or 0: a share of the line
     if (__builtin_expect(few_rows, 1)) {
         row_cnt = lane < rows ? attn_row_count(a, lane, div_h(plan, lane)) : 0;
         const int cost = row_cost<TILE>(row_cnt), inc = wave_inclusive_sum(cost);
         row_lo = inc - cost;
         total = __builtin_amdgcn_readlane(inc, 63);      // (lanes past the last row add nothing)
+        // Few tiles in all: shares of `unit` tiles of one row each (share_units)
+        const int tiles = total - SEG_COST * (int)__popcll(__ballot(row_cnt > 0));
+        if (tiles <= plan.unit_line) {                   // (uniform)
+            const int least = (int)__umulhi((uint32_t)(tiles > 0 ? tiles - 1 : 0), plan.per_share) + 1;
+            unit = (least <= 3) & (tiles > 4 * rows) & (tiles <= 128) ? 3 : least <= 4 ? 4 : least <= 6 ? 6 : (least + 3) & ~3;
+            // (exact: fewer than 2^16 tiles, and half a tile is more than the reciprocal is off)
+            const int parts = (int)(((float)((row_cnt + TILE - 1) / TILE + unit - 1) + 0.5f) * __builtin_amdgcn_rcpf((float)unit));
+            const int parts_inc = wave_inclusive_sum(parts);
+            row_lo = (parts_inc - parts) * unit;
+            total = __builtin_amdgcn_readlane(parts_inc, 63) * unit;
+        }
         if (TIGHT) { pre[lane] = row_lo; cnt_lds[lane] = row_cnt; }     // (every wave the same values, and a wave reads behind its own)
         if (blockIdx.x == 0 && tid < rows && row_cnt == 0) plan.row_parts[tid] = ROW_EMPTY;
     } else {
@@ -686,14 +696,18 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
     // This workgroup's share of the cost line, and the rows of which it holds tiles
     const int my_share = __builtin_amdgcn_readfirstlane(share_index(blockIdx.x, plan.n_wg));
     total = __builtin_amdgcn_readfirstlane(total);
-    const Share<TILE> sh = make_share<TILE>(plan, total, rows, my_share);
+    Share<TILE> sh;
+    sh.c0 = min(my_share * unit, total);
+    sh.c1 = min(sh.c0 + unit, total);
+    if (unit == 0) sh = make_share<TILE>(total, plan.n_wg, rows, my_share);
+    const int seg_cost = unit ? 0 : SEG_COST;
     const int c0 = sh.c0, c1 = sh.c1;
     if (c0 >= c1) return;                                // more workgroups than units of work
     int my_lb = 0, my_le = 0;                            // few rows: local tile range of row `lane`
     unsigned long long seg_mask = 0;                     // few rows: the rows with tiles in this share
     auto local_tiles = [&]() {
         const int tiles = (row_cnt + TILE - 1) / TILE;
-        const int lo = c0 - row_lo - SEG_COST, hi = c1 - row_lo - SEG_COST;
+        const int lo = c0 - row_lo - seg_cost, hi = c1 - row_lo - seg_cost;
         my_lb = lo < 0 ? 0 : (lo > tiles ? tiles : lo);
         my_le = hi < 0 ? 0 : (hi > tiles ? tiles : hi);
     };

@@ -356,3 +356,33 @@ def test_one_long_row_among_short_ones(d, B, H_kv, others):
     assert row_rel_err(out, ref) <= TOL["f16"]
     fin = np.isfinite(want_lse)
     assert np.array_equal(np.isneginf(lse), ~fin) and np.abs(lse[fin] - want_lse[fin]).max() <= 1e-3
+
+
+@pytest.mark.parametrize("B,H_kv,tiles", [(1, 2, 8), (1, 2, 9), (1, 2, 128), (1, 2, 129), (1, 1, 192), (1, 1, 193), (1, 1, 1152), (1, 1, 1153),
+                                          (1, 8, 872), (1, 8, 873), (2, 4, 1308), (2, 4, 1309), (1, 8, 1745), (1, 8, 5232), (1, 8, 5233),
+                                          (8, 8, 768), (8, 8, 769), (4, 16, 1152), (8, 8, 3072), (8, 8, 3073), (3, 11, 3488), (5, 13, 300)])
+def test_shares_of_whole_tiles(B, H_kv, tiles):
+    """Totals of tiles at which the shares of up to 64 rows become longer (3, 4, 6, 8, ... tiles) and go over to the line's, in rows
+    of uneven lengths with an empty one among them; 65 rows."""
+    n_tiles = rng_tiles(tiles, B * H_kv)
+    n = 32 * int(n_tiles.max())
+    w = W.llama8b_layer(seed=tiles, B=B, n=n, H_q=2 * H_kv, H_kv=H_kv, T=2, d=128, dtype="f16")
+    rng = np.random.default_rng(tiles)
+    keep = np.maximum(n_tiles * 32 - rng.integers(0, 32, size=B * H_kv) * (n_tiles > 0), 0).reshape(B, H_kv)
+    mask = (np.arange(n) < keep[..., None]).astype(np.uint8)
+    q, k, v = kv_tensors(w)
+    idx, cnt = lists(mask)
+    out, lse = gpu_attention(q, k, v, idx, cnt)
+    ref, want_lse = oracle_attention(w, mask)
+    assert row_rel_err(out, ref) <= TOL["f16"]
+    fin = np.isfinite(want_lse)
+    assert np.array_equal(np.isneginf(lse), ~fin) and np.abs(lse[fin] - want_lse[fin]).max() <= 1e-3
+
+
+def rng_tiles(total, rows):
+    """`rows` tile counts that add up to `total`: the last one 0 where there are more than two, the others uneven."""
+    rng = np.random.default_rng(total * 100 + rows)
+    full = rows - 1 if rows > 2 else rows
+    part = np.floor(total * rng.dirichlet(np.full(full, 8.0))).astype(int)
+    part[0] += total - part.sum()
+    return np.concatenate([part, np.zeros(rows - full, dtype=int)])
