@@ -60,8 +60,6 @@ struct MergeArgs {
 template <int D, bool F16, bool TAIL> __global__ __launch_bounds__(D) void merge_partials_kernel(MergeArgs a)
 {
     __shared__ float red[2 * SPECATTN_MAX_T];
-    // (one batch, as in the main kernel)
-#define SPECATTN_PRELOAD(x) asm volatile("" ::"s"(x))
     SPECATTN_PRELOAD(a.row_parts); SPECATTN_PRELOAD(a.part_ml); SPECATTN_PRELOAD(a.part_o); SPECATTN_PRELOAD(a.out); SPECATTN_PRELOAD(a.lse); SPECATTN_PRELOAD(a.out_lowp);
     SPECATTN_PRELOAD(a.per_h); SPECATTN_PRELOAD(a.per_t); SPECATTN_PRELOAD(a.H_q); SPECATTN_PRELOAD(a.H_kv); SPECATTN_PRELOAD(a.T); SPECATTN_PRELOAD(a.heads);
     SPECATTN_PRELOAD(a.g_first); SPECATTN_PRELOAD(a.qtp);
@@ -69,7 +67,6 @@ template <int D, bool F16, bool TAIL> __global__ __launch_bounds__(D) void merge
         SPECATTN_PRELOAD(a.sm_scale); SPECATTN_PRELOAD(a.q); SPECATTN_PRELOAD(a.k_new); SPECATTN_PRELOAD(a.v_new);
         SPECATTN_PRELOAD(a.q_stride_b); SPECATTN_PRELOAD(a.q_stride_h); SPECATTN_PRELOAD(a.q_stride_t);
     }
-#undef SPECATTN_PRELOAD
     const int q = blockIdx.x, r = blockIdx.y;
     const uint32_t parts = a.row_parts[r];
     const int b = (int)__umulhi((uint32_t)r << 1, a.per_h), h = r - b * a.H_kv;              // (div_h, div_t)

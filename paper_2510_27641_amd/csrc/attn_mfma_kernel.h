@@ -608,10 +608,7 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
     uint32_t lane_chunk = (uint32_t)(((lane & (LPR - 1)) ^ GEO::swz(lrow)) << 4);
     auto chunk_flip = [](int i) -> uint32_t { return D == 128 ? ((i & 1) << 7) | ((i & 2) << 3) : (i & 1) << 4; };
 
-    // Every kernel argument the main path uses is fetched here, in one batch: left to the compiler, the
-    // argument loads are issued where each is first needed, and every such group is one more round trip to
-    // memory on the way to the first gather.
-#define SPECATTN_PRELOAD(x) asm volatile("" ::"s"(x))
+    // Every kernel argument the main path uses, in one batch.
     SPECATTN_PRELOAD(a.q); SPECATTN_PRELOAD(a.k); SPECATTN_PRELOAD(a.v);
     SPECATTN_PRELOAD(a.B); SPECATTN_PRELOAD(a.H_q); SPECATTN_PRELOAD(a.H_kv); SPECATTN_PRELOAD(a.T);
     SPECATTN_PRELOAD(a.sm_scale);
@@ -625,7 +622,6 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
     if (LAYOUT != CONTIGUOUS) { SPECATTN_PRELOAD(a.page_table); SPECATTN_PRELOAD(a.page_shift); SPECATTN_PRELOAD(a.max_pages); SPECATTN_PRELOAD(a.kv_stride_page); }
     if (SRC == LIST) { SPECATTN_PRELOAD(a.indices); SPECATTN_PRELOAD(a.idx_stride); }
     if (SRC == MASK) { SPECATTN_PRELOAD(a.kept_mask); SPECATTN_PRELOAD(a.block_counts); SPECATTN_PRELOAD(a.blocks_per_row); SPECATTN_PRELOAD(a.n_max); }
-#undef SPECATTN_PRELOAD
     // Mask source, small calls: the per-block kept counts of all rows are requested together with the counts (the row
     // this workgroup starts in is not known yet), so that its first segment need not go to memory for them again.
     constexpr int BC_PT = TAB::BC_ALL / THREADS;

@@ -18,6 +18,25 @@ int cu_count();
 // records a failed launch in the error text; returns SPECATTN_EHIP or SPECATTN_OK
 specattn_status check_launch(const char *what);
 
+// Kernel arguments that lie in this statement's way are fetched in one batch, ahead of it: left to the compiler, the argument loads are issued
+// where each is first needed, and every such group is one more round trip to memory (0.3 to 0.5 us where the launch comes from the host and
+// its arguments are in no cache yet).
+#define SPECATTN_PRELOAD(x) asm volatile("" ::"s"(x))
+
+// n / d for n < 2^31 by a multiplication: the divisor is known on the host.  mul = 2^32 * (2^shift - d) / d + 1 rounded down, with
+// shift = log2 of d rounded up (T. Granlund, P. L. Montgomery, "Division by invariant integers using multiplication", 1994).
+struct FastDivisor {
+    uint32_t mul = 1;
+    int shift = 0;
+    FastDivisor() = default;
+    explicit FastDivisor(int d)
+    {
+        while (((int64_t)1 << shift) < d) ++shift;
+        mul = (uint32_t)((((uint64_t)1 << 32) * (((uint64_t)1 << shift) - d)) / d + 1);
+    }
+    __host__ __device__ int divide(int n) const { return (int)(((uint32_t)(((uint64_t)mul * (uint32_t)n) >> 32) + (uint32_t)n) >> shift); }
+};
+
 // ---- selection -----------------------------------------------------------------------------
 // Per-block kept counts for the fused path: block_counts[r][blk] = number kept among positions
 // [blk*SEL_BLOCK, (blk+1)*SEL_BLOCK) of row r.
@@ -44,6 +63,7 @@ struct SelectLaunch {
     int n_tokens;            // positions behind a row: seq_lens counts these (n_max << chunk_shift at most)
     int chunk_shift;         // log2 of the chunk size when the row holds chunk masses, else 0
     uint32_t *kept_mask;     // may be null; [rows][blocks_per_row * SEL_BLOCK / 32]: bit i of word w = position 32 w + i kept
+    FastDivisor per_h;       // by H_kv (set by the launch)
     int by_length;           // > 0: workgroups take the sequences from the longest down, compared by their lengths >> (by_length - 1)
 };
 constexpr int SELECT_RESIDENT = 65536;    // rows up to this length are read once (one workgroup holds them in registers)

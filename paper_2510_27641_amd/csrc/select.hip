@@ -497,6 +497,7 @@ __global__ __launch_bounds__(STREAM_THREADS, 4) void topp_select_stream_kernel(S
 template <int THREADS, int NV4, bool CHUNKED = false> specattn_status launch_one(const SelectLaunch &asked, hipStream_t stream)
 {
     SelectLaunch a = asked;
+    a.per_h = FastDivisor(a.H_kv);
     // Rows of different lengths that come in turns: the longest first, so that no long one starts when the others are done.  Not where all
     // workgroups are on the chip at once (16 waves to a CU), and up to 64 sequences, which the lanes of a wave compare.  In the order of the batch / from the
     // longest down, us: 64 sequences x 8 heads of up to 65536 49.7 / 44.0, 48 x 8 44.9 / 36.4, 40 x 8 of up to 40000 30.7 / 27.9.

@@ -405,8 +405,13 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
     extern __shared__ __align__(16) unsigned long long select_dyn[];
     static_assert(RES_HIST * 8 <= (int)select_lds(THREADS, NV4), "the histograms share the list's buffer");
     unsigned long long *hist1 = select_dyn, *hist2 = select_dyn + FINE;
+    SPECATTN_PRELOAD(a.probs); SPECATTN_PRELOAD(a.stride_b); SPECATTN_PRELOAD(a.stride_h); SPECATTN_PRELOAD(a.B); SPECATTN_PRELOAD(a.H_kv); SPECATTN_PRELOAD(a.n_max);
+    SPECATTN_PRELOAD(a.seq_lens); SPECATTN_PRELOAD(a.top_p); SPECATTN_PRELOAD(a.indices); SPECATTN_PRELOAD(a.idx_stride); SPECATTN_PRELOAD(a.idx_capacity);
+    SPECATTN_PRELOAD(a.counts); SPECATTN_PRELOAD(a.thresholds); SPECATTN_PRELOAD(a.row_flags); SPECATTN_PRELOAD(a.page_table); SPECATTN_PRELOAD(a.emit_physical);
+    SPECATTN_PRELOAD(a.block_counts); SPECATTN_PRELOAD(a.blocks_per_row); SPECATTN_PRELOAD(a.n_tokens); SPECATTN_PRELOAD(a.chunk_shift); SPECATTN_PRELOAD(a.kept_mask);
+    SPECATTN_PRELOAD(a.per_h.mul); SPECATTN_PRELOAD(a.per_h.shift); SPECATTN_PRELOAD(a.by_length);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    int b = blockIdx.x / a.H_kv, len;
+    int b = a.per_h.divide(blockIdx.x), len;
     const int h = blockIdx.x - b * a.H_kv;
     auto clamped = [&](int n) { return n < 0 ? 0 : (n > a.n_tokens ? a.n_tokens : n); };
     if (a.by_length) {                                         // (uniform)
