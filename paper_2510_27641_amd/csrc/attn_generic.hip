@@ -99,9 +99,23 @@ template <int D> struct Lds {
     static constexpr size_t bytes(int nqt) { return sizeof(float) * (size_t)(q_floats(nqt) + O_FLOATS + ML_FLOATS + TAIL_FLOATS); }
 };
 
+struct F32Plan {
+    int n_splits, group;          // splits of a row; query heads per kv head
+    FastDivisor per_split, per_h;
+    uint32_t per_t;               // 2^16 / T, rounded up: q / T for q < 2^12, T < 2^4
+    float *part_o, *part_ml;
+};
+
 template <typename T, int D, int NQT>
-__global__ __launch_bounds__(GEN_THREADS, 1) void attn_f32_kernel(AttnLaunch a, int n_splits, float *part_o, float *part_ml)
+__global__ __launch_bounds__(GEN_THREADS, 1) void attn_f32_kernel(AttnLaunch a, F32Plan plan)
 {
+    SPECATTN_PRELOAD(a.q); SPECATTN_PRELOAD(a.k); SPECATTN_PRELOAD(a.v); SPECATTN_PRELOAD(a.H_q); SPECATTN_PRELOAD(a.H_kv); SPECATTN_PRELOAD(a.T); SPECATTN_PRELOAD(a.n_max);
+    SPECATTN_PRELOAD(a.sm_scale); SPECATTN_PRELOAD(a.q_stride_b); SPECATTN_PRELOAD(a.q_stride_h); SPECATTN_PRELOAD(a.q_stride_t); SPECATTN_PRELOAD(a.kv_stride_b);
+    SPECATTN_PRELOAD(a.kv_stride_h); SPECATTN_PRELOAD(a.kv_stride_n); SPECATTN_PRELOAD(a.page_table); SPECATTN_PRELOAD(a.page_shift); SPECATTN_PRELOAD(a.indices);
+    SPECATTN_PRELOAD(a.idx_stride); SPECATTN_PRELOAD(a.counts); SPECATTN_PRELOAD(a.idx_capacity); SPECATTN_PRELOAD(a.indices_are_physical); SPECATTN_PRELOAD(a.dense);
+    SPECATTN_PRELOAD(a.chunk_shift); SPECATTN_PRELOAD(a.k_new); SPECATTN_PRELOAD(a.out); SPECATTN_PRELOAD(a.out_lowp); SPECATTN_PRELOAD(a.lse); SPECATTN_PRELOAD(a.seq_lens);
+    SPECATTN_PRELOAD(plan.n_splits); SPECATTN_PRELOAD(plan.per_split.mul); SPECATTN_PRELOAD(plan.per_split.shift); SPECATTN_PRELOAD(plan.per_h.mul);
+    SPECATTN_PRELOAD(plan.per_h.shift); SPECATTN_PRELOAD(plan.group); SPECATTN_PRELOAD(plan.per_t); SPECATTN_PRELOAD(plan.part_o); SPECATTN_PRELOAD(plan.part_ml);
     extern __shared__ __attribute__((aligned(16))) float smem[];
     typedef Lds<D> L;
     constexpr int KJ = D / 16;            // 16-byte loads per key and lane
@@ -111,13 +125,29 @@ __global__ __launch_bounds__(GEN_THREADS, 1) void attn_f32_kernel(AttnLaunch a, 
     float *ml = Os + L::O_FLOATS;         // [wave][query row][2]
     float *tail = ml + L::ML_FLOATS;      // [query row][new token]
 
-    const int r = blockIdx.x / n_splits, s = blockIdx.x - r * n_splits;
-    const int b = r / a.H_kv, h = r - b * a.H_kv;
-    const int G = a.H_q / a.H_kv, QT = G * a.T;
+    const int n_splits = plan.n_splits;
+    const int r = plan.per_split.divide(blockIdx.x), s = blockIdx.x - r * n_splits;
+    const int b = plan.per_h.divide(r), h = r - b * a.H_kv;
+    const int G = plan.group, QT = G * a.T;
+    auto head_of = [&](int q) { return (int)(((uint32_t)q * plan.per_t) >> 16); };      // q / T
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, g = lane >> 4;
     const float scale2 = a.sm_scale * 1.4426950408889634f;            // scores in log2 units
+    // Q first: it waits for nothing but the arguments, and loads come back in order.  (Behind the first keys and values, with arguments in several
+    // turns and divisions / now, us with the selection: 8 rows of 1024 11.8 / 11.7, of 1024 with d = 128 14.8 / 14.2, 32 of 8192 with 32 query rows
+    // 26.4 / 25.1, 16 of 8192 with d = 128 and 24 query rows 34.2 / 32.1.  The barrier behind the loads instead: 32 of 2000 15.5 / 16.0.)
+    constexpr int Q_PER = (NQT * 16 * (D / 4) + GEN_THREADS - 1) / GEN_THREADS;
+    f32x4 qv[Q_PER];
+#pragma unroll
+    for (int k = 0; k < Q_PER; ++k) {
+        const int e = k * GEN_THREADS + tid, qi = e / (D / 4), ch = e - qi * (D / 4);
+        qv[k] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        if (qi < QT) {
+            const int gh = head_of(qi), tt = qi - gh * a.T;
+            qv[k] = Elem<T>::ld4(a.q, (int64_t)b * a.q_stride_b + (int64_t)(h * G + gh) * a.q_stride_h + (int64_t)tt * a.q_stride_t + 4 * ch);
+        }
+    }
     const int count = attn_row_count(a, r, b);
     const int tiles = (count + GEN_TILE - 1) / GEN_TILE;
     const int per = (tiles + n_splits - 1) / n_splits;
@@ -145,22 +175,19 @@ __global__ __launch_bounds__(GEN_THREADS, 1) void attn_f32_kernel(AttnLaunch a, 
     };
     int t = s * per + wave;
     int64_t off_next = 0;
-    if (t < t_end) {                      // the first tile's rows are on their way before anything else is set up
-        const int64_t off = tile_off(t);
+    int64_t off = 0;
+    if (t < t_end) off = tile_off(t);
+#pragma unroll
+    for (int k = 0; k < Q_PER; ++k) {
+        const int e = k * GEN_THREADS + tid, qi = e / (D / 4), ch = e - qi * (D / 4);
+        if (e < NQT * 16 * (D / 4)) *reinterpret_cast<f32x4 *>(Qs + qi * L::ROW + 4 * ch) = qv[k];
+    }
+    __syncthreads();                      // (ahead of the loads of keys and values: all waves' start together)
+    if (t < t_end) {
         load_k(off);
         load_v(off);
         if (t + GEN_WAVES < t_end) off_next = tile_off(t + GEN_WAVES);
     }
-    for (int e = tid; e < NQT * 16 * (D / 4); e += GEN_THREADS) {
-        const int qi = e / (D / 4), ch = e - qi * (D / 4);
-        f32x4 x = (f32x4){0.f, 0.f, 0.f, 0.f};
-        if (qi < QT) {
-            const int gh = qi / a.T, tt = qi - gh * a.T;
-            x = Elem<T>::ld4(a.q, (int64_t)b * a.q_stride_b + (int64_t)(h * G + gh) * a.q_stride_h + (int64_t)tt * a.q_stride_t + 4 * ch);
-        }
-        *reinterpret_cast<f32x4 *>(Qs + qi * L::ROW + 4 * ch) = x;
-    }
-    __syncthreads();
 
     f32x4 o[NQT][DH][4];                  // [query tile][64 u +][i]: dv = 64 u + 16 g + 4 x + i in component x
     float m_ref[NQT], l_sum[NQT];
@@ -278,7 +305,7 @@ __global__ __launch_bounds__(GEN_THREADS, 1) void attn_f32_kernel(AttnLaunch a, 
         __syncthreads();
         const int ql = tid / (D / 4), dv = 4 * (tid & (D / 4 - 1)), q = qt * 16 + ql;
         if (ql < 16 && q < QT) {
-            const int gh = q / a.T, tt = q - gh * a.T;
+            const int gh = head_of(q), tt = q - gh * a.T;
             float m = -INFINITY;
 #pragma unroll
             for (int w = 0; w < GEN_WAVES; ++w) m = fmaxf(m, ml[(w * MAX_QT + q) * 2]);
@@ -310,8 +337,8 @@ __global__ __launch_bounds__(GEN_THREADS, 1) void attn_f32_kernel(AttnLaunch a, 
                 if (a.lse && dv == 0) a.lse[orow] = lt > 0.0f ? (m + log2f(lt)) * 0.6931471805599453f : -INFINITY;
             } else {
                 const int64_t slot = ((int64_t)r * n_splits + s) * QT + q;
-                *reinterpret_cast<f32x4 *>(part_o + slot * D + dv) = acc;
-                if (dv == 0) { part_ml[2 * slot] = m; part_ml[2 * slot + 1] = lt; }
+                *reinterpret_cast<f32x4 *>(plan.part_o + slot * D + dv) = acc;
+                if (dv == 0) { plan.part_ml[2 * slot] = m; plan.part_ml[2 * slot + 1] = lt; }
             }
         }
     }
@@ -479,7 +506,8 @@ specattn_status launch_attn(const AttnLaunch &a, hipStream_t stream)
     if (st != SPECATTN_OK) return st;
     float *part_o = static_cast<float *>(a.workspace);
     float *part_ml = part_o + (size_t)rows * ns * QT * a.d;
-    void *kargs[] = {const_cast<AttnLaunch *>(&a), &ns, &part_o, &part_ml};
+    F32Plan plan{ns, G, FastDivisor(ns), FastDivisor(a.H_kv), (65536u + a.T - 1) / a.T, part_o, part_ml};
+    void *kargs[] = {const_cast<AttnLaunch *>(&a), &plan};
     if (hipLaunchKernel(fn, dim3(rows * ns), dim3(GEN_THREADS), kargs, lds_bytes(a.d, nqt), stream) != hipSuccess) {
         set_error("attn_f32_kernel: launch failed");
         (void)hipGetLastError();
