@@ -189,9 +189,9 @@ specattn_status attn_mfma_configure()
     if (done[dev]) return SPECATTN_OK;
     for (int k = 0; k < 3 * 4 * 3 * 2; ++k) {
         const void *fn = attn_mfma_variant(k % 3 == 2 ? 64 : 128, k % 3 == 1 ? MASK : LIST, k / 3 % 4 + 1, k / 12 % 3, k / 36 != 0);
-        if (fn && hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES) != hipSuccess) {
+        if (fn && hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes(MASK)) != hipSuccess) {
             (void)hipGetLastError();
-            set_error("cannot reserve %d bytes of LDS", LDS_BYTES);
+            set_error("cannot reserve %d bytes of LDS", lds_bytes(MASK));
             return SPECATTN_EHIP;
         }
     }
@@ -284,7 +284,7 @@ static specattn_status launch_chunk(const AttnLaunch &a, hipStream_t stream)
     specattn_status st = attn_mfma_configure();
     if (st != SPECATTN_OK) return st;
     void *kargs[] = {const_cast<AttnLaunch *>(&a), &plan};
-    if (hipLaunchKernel(fn, dim3(plan.n_wg), dim3(THREADS), kargs, LDS_BYTES, stream) != hipSuccess) {
+    if (hipLaunchKernel(fn, dim3(plan.n_wg), dim3(THREADS), kargs, lds_bytes(src), stream) != hipSuccess) {
         set_error("attn_mfma_kernel: launch failed");
         (void)hipGetLastError();
         return SPECATTN_EHIP;

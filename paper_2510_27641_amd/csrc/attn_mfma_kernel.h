@@ -97,7 +97,6 @@ template <int D> struct Geo {
     }
 };
 constexpr int MAX_ROWS = ATTN_MFMA_MAX_ROWS;          // rows whose cost prefix fits the LDS table
-constexpr int MAX_BLOCKS = SPECATTN_MAX_N / SEL_BLOCK;   // selection blocks per row, at most
 constexpr int SLOT_BYTES = 256;       // one wave-wide LDS-DMA of 4 bytes per lane
 constexpr int KV_AUX = 2;             // cache policy of the K/V gathers: non-temporal (each row is used once)
 constexpr int SEG_COST = 12;          // cost of picking a row up, in tiles
@@ -107,37 +106,36 @@ constexpr int OFF_WSUM = NW * WAVE_LDS;                         // int[NW]
 constexpr int OFF_MISC = OFF_WSUM + NW * 4;                     // int[4]: spare
 constexpr int OFF_SLOT = (OFF_MISC + 16 + 255) & ~255;          // [NW][2][SLOT_BYTES] list / mask words in flight;
                                                                 // a wave's (m, l) table of the wave merge uses them afterwards
-constexpr int OFF_SCAT = OFF_SLOT + NW * 2 * SLOT_BYTES;        // uint[NW][2][32] positions of a tile (mask source)
-constexpr int OFF_Q = OFF_SCAT + NW * 256;                      // Q tile [NQT * 16 rows], chunks swizzled like K
+constexpr int OFF_SCAT = OFF_SLOT + NW * 2 * SLOT_BYTES;        // list: row offsets between two gathers; mask: uint[NW][POS_CAP] positions of a wave's next tiles
+constexpr int POS_CAP = 240;                                    // (what the LDS leaves)
 constexpr int MAX_ROWS_LIST = ATTN_MFMA_MAX_ROWS_LIST;
 constexpr int FEW_ROWS = 64;                                    // rows a single wave scans by itself
-constexpr int LDS_BYTES = 160008;
+// Where the kept positions of a row come from: an index list in memory (also chunk lists and dense calls, which
+// have no list at all), or the kept-position mask and per-block counts of the selection (fused call).
+enum Source { LIST = 0, MASK = 1 };
+constexpr int off_q(int src) { return OFF_SCAT + NW * (src == MASK ? POS_CAP * 4 : 256); }   // Q tile [NQT * 16 rows], chunks swizzled like K
+constexpr int lds_bytes(int src) { return 157956 + off_q(src) - off_q(LIST); }
 // Rows a launch of NQT query tiles can take: what the LDS leaves for the row tables behind the Q tile.
 constexpr int launch_rows(int nqt, int d) { return d == 128 && nqt == 3 ? 1024 : d == 128 && nqt == 4 ? ATTN_MFMA_MAX_ROWS : MAX_ROWS_LIST; }
-// Behind Q: the row tables (cost prefix and kept counts of up to ROWS rows), then a row's block prefix (mask
-// source).  Calls of up to 64 rows hold their rows in registers; with three and four query tiles, copies of them lie in the first kilobyte.
+// Behind Q: the row tables (cost prefix and kept counts of up to ROWS rows).  Calls of up to 64 rows hold their rows in registers; with three and four query tiles, copies of them lie in the first kilobyte.
 // The mask source then uses the rest of the region for the block counts of all rows.
-template <int NQT, int D> struct Tables {
+template <int NQT, int D, int SRC> struct Tables {
     static constexpr int Q_BYTES = NQT <= 2 ? 8192 : NQT * 16 * Geo<D>::ROW_BYTES;
     static constexpr int ROWS = launch_rows(NQT, D);
-    static constexpr int OFF_TAB = OFF_Q + Q_BYTES;
+    static constexpr int OFF_TAB = off_q(SRC) + Q_BYTES;
     static constexpr int TAB_BYTES = (2 * ROWS + 1) * 4;        // int[rows + 1] cost prefix, int[rows] kept counts, clamped
     static constexpr int OFF_BC = OFF_TAB + 1024;               // int[BC_ALL] block counts of all rows (mask source, <= FEW_ROWS rows)
     static constexpr int BC_ALL = (TAB_BYTES - 1024) / 4 / THREADS * THREADS < 2048 ? (TAB_BYTES - 1024) / 4 / THREADS * THREADS : 2048;
-    static constexpr int OFF_BLK = OFF_TAB + TAB_BYTES;         // int[MAX_BLOCKS + 1] kept before block (mask source)
     static_assert((2 * FEW_ROWS + 1) * 4 <= 1024 && BC_ALL > 0, "the block counts must fit behind the tables of a small call");
-    static_assert(OFF_BLK + (MAX_BLOCKS + 1) * 4 <= LDS_BYTES, "the tables must fit");
+    static_assert(OFF_TAB + TAB_BYTES <= lds_bytes(SRC), "the tables must fit");
 };
 static_assert(4 * 16 * 2 * 4 <= 2 * SLOT_BYTES, "a wave's (m, l) table must fit its slots");
-static_assert(LDS_BYTES * WG_PER_CU <= 160 * 1024, "the workgroups of a CU must fit its LDS");
+static_assert(lds_bytes(MASK) * WG_PER_CU <= 160 * 1024 && lds_bytes(LIST) <= lds_bytes(MASK), "the workgroups of a CU must fit its LDS");
 
 // Where the gathered rows live.  A list entry is a logical position (contiguous layout) or a pool
 // slot page * page_size + offset (paged layouts; logical positions are mapped through the page
 // table when the tile's row offsets are formed).
 enum Layout { CONTIGUOUS = 0, PAGE_TABLE = 1, PHYSICAL = 2 };
-// Where a row's kept positions come from: an index list in memory (also chunk lists and dense calls, which
-// have no list at all), or the kept-position mask and per-block counts of the selection (fused call).
-enum Source { LIST = 0, MASK = 1 };
 
 // Row offsets are held in 32 bits, in units of 2^unit_shift bytes.  Rows of 64 elements in pools: whole rows of 128 bytes
 // (512 GiB, more than a GPU has); the host sends strides that are no multiple of a row to the fp32 kernel.
@@ -292,31 +290,6 @@ __device__ __forceinline__ uint32_t global_read_word(const uint32_t *p)
     uint32_t r;
     asm volatile("global_load_dword %0, %1, off\n s_waitcnt vmcnt(0)" : "=&v"(r) : "v"(p) : "memory");
     return r;
-}
-// The values of `a` and `b` in lane `src_lane` (cross-lane reads through the LDS crossbar, one round trip for both; no
-// memory is touched).
-__device__ __forceinline__ void lane_read2(uint32_t a, uint32_t b, int src_lane, uint32_t &ra, uint32_t &rb)
-{
-    asm volatile("ds_bpermute_b32 %0, %2, %3\n ds_bpermute_b32 %1, %2, %4\n s_waitcnt lgkmcnt(0)"
-                 : "=&v"(ra), "=&v"(rb) : "v"(src_lane << 2), "v"(a), "v"(b) : "memory");
-}
-// Forward permute: every lane pushes `v` to lane `dst_lane`; a lane nobody pushes to receives 0, and of several
-// pushes to one lane the highest pushing lane's value arrives.
-__device__ __forceinline__ uint32_t lane_push(uint32_t v, int dst_lane)
-{
-    uint32_t r;
-    asm volatile("ds_permute_b32 %0, %1, %2\n s_waitcnt lgkmcnt(0)" : "=&v"(r) : "v"(dst_lane << 2), "v"(v) : "memory");
-    return r;
-}
-// Inclusive prefix maximum over lanes 0..31 (the two lower rows of 16 lanes) on the vector ALU.
-__device__ __forceinline__ int prefix_max32(int v)
-{
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false));    // row_shr:1
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false));    // row_shr:2
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false));    // row_shr:4
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false));    // row_shr:8
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false));    // row_bcast:15 into rows 1 and 3
-    return v;
 }
 // Index of the k-th set bit of x (k = 0 is the lowest; k must be below the number of set bits).
 __device__ __forceinline__ int kth_set_bit(uint32_t x, int k)
@@ -561,7 +534,7 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     static_assert(D == 128 || SRC == LIST, "the mask source is built for 32-position tiles");
     typedef Geo<D> GEO;
-    typedef Tables<NQT, D> TAB;
+    typedef Tables<NQT, D, SRC> TAB;
     constexpr int TILE = GEO::TILE, ROW_BYTES = GEO::ROW_BYTES, LPR = GEO::LPR, RPI = GEO::RPI, PT = GEO::PT, KS = GEO::KS, PB = GEO::PB, DT = GEO::DT;
     constexpr int UNIT = unit_shift<D, LAYOUT>();
     constexpr int QTP = NQT * 16;
@@ -577,8 +550,7 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
     int *pre = reinterpret_cast<int *>(smem + TAB::OFF_TAB);
     int *cnt_lds = pre + ((a.B * a.H_kv <= FEW_ROWS ? FEW_ROWS : TAB::ROWS) + 1);
     int *wsum = reinterpret_cast<int *>(smem + OFF_WSUM);
-    int *blk_pre = reinterpret_cast<int *>(smem + TAB::OFF_BLK);
-    char *q_lds = smem + OFF_Q;
+    char *q_lds = smem + off_q(SRC);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int l16 = lane & 15, g = lane >> 4;
@@ -588,8 +560,7 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
     const uint32_t ks_addr = (uint32_t)(uintptr_t)LDS_PTR(char, wave_lds);
     const uint32_t vs_addr = ks_addr + TILE_BYTES;
     const uint32_t slot_addr = (uint32_t)(uintptr_t)LDS_PTR(char, slot_lds);
-    const uint32_t scat_addr = (uint32_t)(uintptr_t)LDS_PTR(char, smem + OFF_SCAT + wave * 256);
-    const uint32_t blk_addr = (uint32_t)(uintptr_t)LDS_PTR(int, blk_pre);
+    const uint32_t scat_addr = (uint32_t)(uintptr_t)LDS_PTR(char, smem + OFF_SCAT + wave * (SRC == MASK ? POS_CAP * 4 : 256));
     const uint32_t q_addr = (uint32_t)(uintptr_t)LDS_PTR(char, q_lds);
     // K fragment of k-step c: row l16 (+16 per position tile), 16-byte chunk 4c + g - address k_off ^ (64 c)
     uint32_t k_off = ks_addr + (uint32_t)(l16 * ROW_BYTES + ((g ^ GEO::swz(l16)) << 4));
@@ -649,7 +620,7 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
         const int tiles = total - SEG_COST * (int)__popcll(__ballot(row_cnt > 0));
         if (tiles <= plan.unit_line) {                   // (uniform)
             const int least = (int)__umulhi((uint32_t)(tiles > 0 ? tiles - 1 : 0), plan.per_share) + 1;
-            unit = (least <= 3) & (tiles > 4 * rows) & (tiles <= 128) ? 3 : least <= 4 ? 4 : least <= 6 ? 6 : (least + 3) & ~3;
+            unit = ((least <= 3) & (tiles > 4 * rows) & (tiles <= 128)) ? 3 : least <= 4 ? 4 : least <= 6 ? 6 : (least + 3) & ~3;
             // (exact: fewer than 2^16 tiles, and half a tile is more than the reciprocal is off)
             const int parts = (int)(((float)((row_cnt + TILE - 1) / TILE + unit - 1) + 0.5f) * __builtin_amdgcn_rcpf((float)unit));
             const int parts_inc = wave_inclusive_sum(parts);
@@ -669,6 +640,9 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
 #pragma unroll
         for (int k = 0; k < BC_PT; ++k) bc_lds[tid + k * THREADS] = bc_pf[k];   // (read behind the first segment's barrier)
     }
+    // Everything loaded so far has arrived, which the compiler does not see where the block counts are requested and used under a condition each: it
+    // would wait for the first gathers before it gives those registers to others.
+    if (SRC == MASK) __builtin_amdgcn_s_waitcnt(0x0f70);             // vmcnt(0)
     const int QT = plan.group * a.T;
     const float scale2 = a.sm_scale * 1.4426950408889634f;            // scores in log2 units
 
@@ -761,11 +735,11 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
             local_tiles();
         }
         seg_range(r, lt_begin, lt_end);
+        if (SRC == MASK) { lt_begin = __builtin_amdgcn_readfirstlane(lt_begin); lt_end = __builtin_amdgcn_readfirstlane(lt_end); }
         const int r_next = __builtin_amdgcn_readfirstlane(next_seg(r + 1));
         const int b = div_h(plan, r), h = r - b * a.H_kv;
-        const int count = row_count(r);
+        const int count = SRC == MASK ? __builtin_amdgcn_readfirstlane(row_count(r)) : row_count(r);
         const int tiles = (count + TILE - 1) / TILE;
-        const int tile_end = lt_end;             // the tiles [lt_begin, lt_end) of the row are this workgroup's
         const KvMap map = make_map<LAYOUT>(a, b, h);
         const char *kbh = static_cast<const char *>(a.k) + map.base * 2;
         const char *vbh = static_cast<const char *>(a.v) + map.base * 2;
@@ -774,97 +748,97 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
         const int n_idx = (SRC == MASK || !a.dense) ? 1 : 0;            // LDS-DMA instructions per tile for list / mask words
 
         // ---- the wave's tiles --------------------------------------------------------------------------
-        // tile k of the share goes to wave k mod NW
-        int t_cur = lt_begin + wave, t_nxt = t_cur + NW, t_nn = t_nxt + NW;
-        // Mask source: where a tile's 32 kept positions start.  Returns the block b that holds rank 32 t and
-        // leaves in `skip` the kept positions of b that come before that rank.  (LDS reads by hand, see above.)
-        auto mask_locate = [&](int t, int &skip) -> int {
-            const int rank = t * TILE;
-            const int nb = a.blocks_per_row;
-            const int stride = (nb + 63) >> 6;                          // blocks per lane of the coarse step
-            int lo = lane * stride < nb ? (int)lds_read_word(blk_addr + (uint32_t)(lane * stride) * 4) : 0x7fffffff;
-            int cnum = __popcll(__ballot(lo <= rank));                  // blk_pre[0] = 0 <= rank: at least 1
-            int bb = (cnum > 0 ? cnum - 1 : 0) * stride;
-            if (stride > 1) {
-                lo = (lane < stride && bb + lane < nb) ? (int)lds_read_word(blk_addr + (uint32_t)(bb + lane) * 4) : 0x7fffffff;
-                cnum = __popcll(__ballot(lo <= rank));
-                bb += cnum > 0 ? cnum - 1 : 0;
-            }
-            bb = __builtin_amdgcn_readfirstlane(bb);
-            skip = rank - (int)__builtin_amdgcn_readfirstlane(lds_read_word(blk_addr + (uint32_t)bb * 4));
-            return bb;
-        };
-        // Requests the words tile t needs into slot s (one LDS-DMA instruction): its 32 list words, or 64 words of
-        // the kept mask from the block that holds its first rank.  Tiles past the end request the last tile's.
-        int m_blk0 = 0, m_blk1 = 0, m_skip0 = 0, m_skip1 = 0;           // mask source: what slots 0 and 1 hold
-        auto request = [&](int t, int s) {
-            if (t >= tiles) t = tiles - 1;
-            if (SRC == MASK) {
-                int skip;
-                const int bb = mask_locate(t, skip);
-                if (s) { m_blk1 = bb; m_skip1 = skip; } else { m_blk0 = bb; m_skip0 = skip; }
-                const int nw = a.blocks_per_row * (SEL_BLOCK / 32);
-                int w = bb * (SEL_BLOCK / 32) + lane;
-                w = w < nw ? w : nw - 1;
-                __builtin_amdgcn_global_load_lds(GLOBAL_PTR(mask_row + w), LDS_PTR(void, slot_lds + s * SLOT_BYTES), 4, 0, 0);
-            } else if (!a.dense) {
-                request_words(idx_row, count, t, s);
-            }
-        };
-        // Mask source: turns the 64 mask words in slot s into the 32 positions of tile t (table s of the wave).  The
-        // words start at block m_blk; the tile's ranks start m_skip kept positions into them.  Lane w counts its
-        // word's bits and a wave-wide prefix gives the rank of its first bit; every word that holds ranks of the
-        // tile marks the first of them, a prefix maximum over the marks tells lane j (< 32) which word holds rank
-        // j, and the lane picks its bit out of that word: no loop over bits.  Done one iteration before the
-        // tile's gathers are issued.  (A row so sparse that 2048 positions hold fewer than 32 kept ones takes
-        // further rounds over the next 64 words.)
-        auto decode = [&](int t, int s) {
-            if (t >= tiles) t = tiles - 1;
-            const int need = (count - t * TILE) < TILE ? (count - t * TILE) : TILE;
-            int have = 0;                                               // ranks of the tile found so far
-            int word0 = (s ? m_blk1 : m_blk0) * (SEL_BLOCK / 32);
-            int skip = s ? m_skip1 : m_skip0;
-            const int nw = a.blocks_per_row * (SEL_BLOCK / 32);
-            const uint32_t table = scat_addr + (uint32_t)s * 128;
-            uint32_t bits = lds_read_word(slot_addr + (uint32_t)(s * SLOT_BYTES + lane * 4));
-            for (;;) {
-                if (word0 + lane >= nw) bits = 0u;
-                const int pc = __popc(bits);
-                const int inc = wave_inclusive_sum(pc);
-                const int ex = inc - pc;
-                const int got = __builtin_amdgcn_readlane(inc, 63) - skip;     // ranks of the tile among these words
-                if (got > 0) {
-                    const int lo = ex - skip + have, hi = lo + pc;      // table slots this word's bits would take
-                    // every word that holds ranks of the tile pushes its number to the lane of its first such rank
-                    // (the others push to lane 63, which stands for no rank)
-                    const bool holds = pc > 0 && hi > have && lo < need;
-                    const int mark = (int)lane_push(holds ? (uint32_t)lane + 1u : 0u, holds ? (lo > have ? lo : have) : 63);
-                    const int owner = prefix_max32((lane >= have && lane < 32) ? mark : 0) - 1;   // the word that holds rank `lane`
-                    const int src = owner >= 0 ? owner : 0;
-                    uint32_t wbits, wex;
-                    lane_read2(bits, (uint32_t)ex, src, wbits, wex);
-                    const int top = (have + got) < need ? (have + got) : need;
-                    if (lane >= have && lane < top && owner >= 0) {
-                        const int k = lane - have + skip - (int)wex;    // which of the word's bits
-                        lds_write_word(table + (uint32_t)lane * 4, (uint32_t)((word0 + src) * 32 + kth_set_bit(wbits, k)));
-                    }
+        // list: tile k of the share goes to wave k mod NW; mask: every wave takes a run of tiles, whose positions it finds by itself
+        constexpr int STEP = SRC == MASK ? 1 : NW;
+        const int run = lt_end - lt_begin;
+        const int t_first = lt_begin + (SRC == MASK ? run * wave / NW : wave);
+        const int tile_end = SRC == MASK ? lt_begin + run * (wave + 1) / NW : lt_end;
+        int t_cur = t_first, t_nxt = t_cur + STEP, t_nn = t_nxt + STEP;
+        // Mask source.  A wave turns mask words into positions as it needs them, a few tiles' worth at a time: 64 words travel to LDS by
+        // LDS-DMA an iteration ahead, lane w takes word w, a prefix sum over the bit counts gives its first rank, and its bits go one
+        // after the other to their places in the wave's buffer.  As many words are taken as fit there.
+        // Before, every tile was located and decoded by itself, with one rank to a lane, and a row's block prefix was a table behind two barriers: a
+        // verify step of 16 layers x 64 rows of 32768 835.4 / 830.0 us, 12 x 8 rows of 30000 231.0 / 226.0, 8 x 24 rows of 12345 175.3 / 171.0, 4 x 192
+        // rows of 16384 301.5 / 300.0.  Runs of tiles cost some of what they save, since a wave's rows then lie far from the other waves' (the list
+        // source with such runs: 781 / 794 us); the tiles in turns, with the positions of a whole share found by the workgroup at once: 2 barriers
+        // more ahead of the first gathers, 0.6 % slower than this.
+        int p_at = 0, p_have = 0;                                       // the buffer holds the next p_have positions from entry p_at on
+        int p_word = 0, p_skip = 0;                                     // the first word not taken yet; kept positions in it and behind to be passed over
+        const int nw = SRC == MASK ? a.blocks_per_row * (SEL_BLOCK / 32) : 0;
+        // Where the wave's first tile starts: the block that holds its first rank, and the block's kept positions ahead of it.
+        auto mask_locate = [&](int t) {
+            const int rank = t * TILE, nb = a.blocks_per_row;
+            const int32_t *bc = a.block_counts + (int64_t)r * nb;
+            int before = 0;
+            for (int base = 0;; base += 64) {
+                const int at = min(base + lane, nb - 1);
+                int c = bc_all ? bc_lds[r * nb + at] : bc[at];
+                c = base + lane < nb ? c : 0;
+                const int inc = before + wave_inclusive_sum(c), all = __builtin_amdgcn_readlane(inc, 63);
+                if (all > rank || base + 64 >= nb) {
+                    const int ahead = min((int)__popcll(__ballot(inc <= rank)), min(63, nb - 1 - base));    // blocks that end ahead of it
+                    p_skip = max(rank - __builtin_amdgcn_readlane(inc - c, ahead), 0);
+                    p_word = (base + ahead) * (SEL_BLOCK / 32);
+                    return;
                 }
-                have += got > 0 ? got : 0;
-                skip = got < 0 ? -got : 0;
-                word0 += 64;
-                if (have >= need || word0 >= nw) break;
-                bits = global_read_word(mask_row + (word0 + lane < nw ? word0 + lane : nw - 1));   // sparse row: the tile reaches further
-            }
-            // (no wait: the table is read by this wave's own later LDS reads, which the LDS unit serves in order)
-            if (need < TILE) {
-                lds_wait();                                          // ranks past the end repeat the last kept position
-                const uint32_t last_pos = lds_read_word(table + (uint32_t)((need > 0 ? need : 1) - 1) * 4);
-                if (lane >= need && lane < TILE) lds_write_word(table + (uint32_t)lane * 4, last_pos);
-                lds_wait();
+                before = all;
             }
         };
-        // Row offsets (in units) of the 8 rows this lane helps to fetch for tile t, whose list words (or decoded
-        // positions) are in slot / table s.
+        // Requests what the wave's next gathers need (one LDS-DMA instruction): tile t's list words into slot s (tiles past the end: the
+        // last tile's), or the next 64 mask words.
+        auto request = [&](int t, int s) {
+            if (SRC == MASK) {
+                const int w = p_word + lane;
+                __builtin_amdgcn_global_load_lds(GLOBAL_PTR(mask_row + (w < nw ? w : nw - 1)), LDS_PTR(void, slot_lds), 4, 0, 0);
+            } else if (!a.dense) {
+                request_words(idx_row, count, t < tiles ? t : tiles - 1, s);
+            }
+        };
+        // Makes sure that the buffer holds the positions of tile t, which start at p_at.  `fresh`: the slot has the words from p_word on (requested
+        // there, and arrived but for the newest 16 requests).  Rows so sparse that those do not hold the tile take further words from memory.
+        auto positions = [&](int t, bool fresh) {
+            const int need = (count - t * TILE) < TILE ? (count - t * TILE) : TILE;
+            if (p_have < need) {
+                if (p_at > 0) {                                         // what is left goes to the front
+                    if (lane < p_have) lds_write_word(scat_addr + (uint32_t)lane * 4, lds_read_word(scat_addr + (uint32_t)(p_at + lane) * 4));
+                    p_at = 0;
+                }
+                uint32_t bits;
+                if (fresh) {
+                    vm_wait(16);
+                    bits = lds_read_word(slot_addr + (uint32_t)(lane * 4));
+                }
+                while (p_have < need && p_word < nw) {
+                    if (!fresh) bits = global_read_word(mask_row + (p_word + lane < nw ? p_word + lane : nw - 1));
+                    fresh = false;
+                    if (p_word + lane >= nw) bits = 0u;
+                    const int pc = __popc(bits), inc = wave_inclusive_sum(pc), skip = inc - pc - p_skip;
+                    // whole words, as many as fit (the first one does, and 31 entries are left for the padding below)
+                    const int taken = (int)__popcll(__ballot(inc - p_skip <= POS_CAP - (TILE - 1) - p_have));
+                    const int got = __builtin_amdgcn_readlane(inc, taken - 1) - p_skip;
+                    if (lane >= taken) bits = 0u;
+                    if (p_skip > 0 && skip < 0) bits = -skip < pc ? bits & (~0u << kth_set_bit(bits, -skip < pc ? -skip : 0)) : 0u;
+                    uint32_t at = scat_addr + (uint32_t)(p_have + (skip > 0 ? skip : 0)) * 4;
+                    const int first = (p_word + lane) * 32;
+                    while (bits) {
+                        lds_write_word(at, (uint32_t)(first + __ffs((int)bits) - 1));
+                        at += 4;
+                        bits &= bits - 1;
+                    }
+                    p_have += got > 0 ? got : 0;
+                    p_skip = got < 0 ? -got : 0;
+                    p_word += taken;
+                }
+            }
+            // (no wait: the buffer is read by this wave's own later LDS reads, which the LDS unit serves in order)
+            if (need < TILE) {                                          // ranks past the end repeat the last kept position
+                lds_wait();
+                const uint32_t last_pos = lds_read_word(scat_addr + (uint32_t)(p_at + (need > 0 ? need : 1) - 1) * 4);
+                if (lane >= need && lane < TILE) lds_write_word(scat_addr + (uint32_t)(p_at + lane) * 4, last_pos);
+            }
+        };
+        // Row offsets (in units) of the 8 rows this lane helps to fetch for tile t, whose list words are in slot s (or whose positions
+        // are the buffer's next, which are used up with this).
         auto entries = [&](int t, int s, uint32_t (&ent)[8]) {
             int pos[8];
             auto rank = [&](int i) -> int {                             // ranks past the end repeat the last kept position
@@ -873,8 +847,10 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
             };
             if (SRC == MASK) {
                 uint32_t e[8];
-                lds_read_entries<RPI>(e, scat_addr + (uint32_t)(s * 128 + lrow * 4));
-                // (a mask that does not hold `count` bits would leave table entries unwritten: stay inside the row)
+                lds_read_entries<RPI>(e, scat_addr + (uint32_t)((p_at + lrow) * 4));
+                p_at += TILE;
+                p_have = p_have > TILE ? p_have - TILE : 0;
+                // (a mask that does not hold `count` bits would leave entries unwritten: stay inside the row)
 #pragma unroll
                 for (int i = 0; i < 8; ++i) pos[i] = e[i] < (uint32_t)a.n_max ? (int)e[i] : a.n_max - 1;
             } else if (a.dense) {
@@ -897,9 +873,8 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
                 for (int i = 0; i < 8; ++i) ent[i] += (lane_chunk ^ chunk_flip(i)) >> 4;
             }
         };
-        // Where a tile's row offsets wait for the V gathers when they are not held in registers: the position tables, which
-        // only the mask source uses, or (mask source) the slot whose words have been decoded.
-        auto stash_addr = [&](int s) { return (SRC == LIST ? scat_addr : slot_addr + (uint32_t)(s * SLOT_BYTES)) + (uint32_t)(lrow * 4); };
+        // Where a tile's row offsets wait for the V gathers when they are not held in registers (the mask source has one slot to spare).
+        auto stash_addr = [&]() { return (SRC == LIST ? scat_addr : slot_addr + (uint32_t)SLOT_BYTES) + (uint32_t)(lrow * 4); };
         // gather a tile's rows of one tensor into this wave's buffer: 8 instructions of 1 KiB
         auto issue = [&](const char *base, char *buf, const uint32_t (&ent)[8]) {
 #pragma unroll
@@ -913,26 +888,13 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
         //      segment needs, since the first gathers wait for them (counts -> list words -> K/V rows are three
         //      dependent trips to memory); then Q goes into LDS ---------------------------------------------------
         if (!first_seg) lds_barrier();           // the previous segment's readers of the wave buffers, slots and Q are done
-        if (SRC == MASK) {
-            // the row's block prefix first: a tile's mask words are found through it
-            if (first_seg && bc_all) lds_barrier();                     // the block counts of all rows are in LDS
-            {
-                if (wave == 0) {                                        // (a scan per wave into a register was slower)
-                    const int32_t *bc = a.block_counts + (int64_t)r * a.blocks_per_row;
-                    int running = 0;
-                    for (int base = 0; base < a.blocks_per_row; base += 64) {
-                        const int c = (base + lane < a.blocks_per_row) ? (bc_all ? bc_lds[r * a.blocks_per_row + base + lane] : bc[base + lane]) : 0;
-                        const int inc = wave_inclusive_sum(c);
-                        if (base + lane < a.blocks_per_row) blk_pre[base + lane + 1] = running + inc;
-                        running += __builtin_amdgcn_readlane(inc, 63);
-                    }
-                    if (lane == 0) blk_pre[0] = 0;
-                }
-                lds_barrier();
-            }
-        }
+        if (SRC == MASK && first_seg && bc_all) lds_barrier();          // the block counts of all rows are in LDS
         if (SRC == MASK || !first_seg) {
-            if (t_cur < tile_end) { request(t_cur, 0); request(t_nxt, 1); }
+            if (t_cur < tile_end) {
+                if (SRC == MASK) mask_locate(t_cur);
+                request(t_cur, 0);
+                if (SRC == LIST) request(t_nxt, 1);
+            }
             load_q(r);
         }
 
@@ -953,11 +915,11 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
         uint32_t ent[8];
         if (t_cur < tile_end) {
             vm_wait(n_q);                                               // the words of the first two tiles are there
-            if (SRC == MASK) decode(t_cur, 0);
+            if (SRC == MASK) positions(t_cur, true);
             entries(t_cur, 0, ent);
             issue(kbh, wave_lds, ent);
             issue(vbh, wave_lds + TILE_BYTES, ent);
-            if (SRC == MASK) decode(t_nxt, 1);                          // (behind the first gathers, not ahead of them)
+            if (SRC == MASK && t_nxt < tile_end) positions(t_nxt, false);
             request(t_nn, 0);
             vm_wait(16 + n_idx);                                        // this wave's part of Q is there
         } else {
@@ -980,7 +942,7 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
                     if (has_next) {                                    // the K buffer is free again
                         entries(t_nxt, s_nxt, ent);
                         issue(kbh, wave_lds, ent);
-                        if (TIGHT) lds_write_entries<RPI>(ent, stash_addr(s_nxt));
+                        if (TIGHT) lds_write_entries<RPI>(ent, stash_addr());
                     }
                     static_for<NQT / QG>([&](auto grp) {
                         constexpr int Q0 = decltype(grp)::value * QG;
@@ -1081,7 +1043,7 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
                     VFrags vh;
                     lds_read_v_batch<D, B>(vh, v_off);
                     if (B == 1 && has_next) {                          // the V buffer is free again
-                        if (TIGHT) lds_read_entries<RPI>(ent, stash_addr(s_nxt));
+                        if (TIGHT) lds_read_entries<RPI>(ent, stash_addr());
                         issue(vbh, wave_lds + TILE_BYTES, ent);
                     }
 #pragma unroll
@@ -1095,13 +1057,10 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
                     }
                 });
                 // ---- the tile after the next two: request its words -------------------------------------------
-                const int t_new = t_nn + NW;
+                const int t_new = t_nn + STEP;
                 if (has_next) {
-                    request(t_new, s_nxt);                             // the slot t_nxt's words were read from
-                    if (SRC == MASK && t_nn < tile_end) {              // the positions of the tile that is next but one
-                        vm_wait(17);                                   // its words (requested an iteration ago) are there
-                        decode(t_nn, s_nxt ^ 1);
-                    }
+                    if (SRC == MASK && t_nn < tile_end) positions(t_nn, true);
+                    request(t_new, s_nxt);                             // (list: the slot t_nxt's words were read from)
                 }
                 t_cur = t_nxt; t_nxt = t_nn; t_nn = t_new;
                 s_nxt ^= 1;

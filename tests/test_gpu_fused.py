@@ -134,6 +134,52 @@ def test_sparse_rows_whose_tiles_span_many_mask_words():
     assert np.abs(lse - l).max() <= 2e-3
 
 
+@pytest.mark.parametrize("B,H_q,H_kv,T,n", [(1, 8, 2, 5, 40000), (3, 24, 2, 4, 9001), (18, 8, 4, 3, 2500)])
+def test_positions_of_any_density_come_out_of_the_mask(B, H_q, H_kv, T, n):
+    """Rows of every density - all positions, all but a few, words full and words empty in turns, one in 4 to one in 3000 - against the
+    same attention over lists: two query tiles, three, and more rows than a wave scans by itself."""
+    rng = np.random.default_rng(n)
+    R, nblk = B * H_kv, -(-n // sa.SEL_BLOCK)
+    kept = np.zeros((R, nblk * sa.SEL_BLOCK), dtype=np.uint8)
+    pos = np.arange(n)
+    for r in range(R):
+        kind = r % 8
+        row = [rng.random(n) < 2.0, rng.random(n) < 0.998, (pos >> 5) % 3 == 0, rng.random(n) < 0.25, rng.random(n) < 0.02,
+               rng.random(n) < 1 / 300, (pos % 1024 >= 900) | (pos > n - 7), rng.random(n) < 0.6][kind]
+        kept[r, :n] = row
+        kept[r, n - 1 - r % 2] = 1
+    counts = kept.sum(axis=1).astype(np.int32)
+    idx = np.zeros((R, n), dtype=np.int32)
+    for r in range(R):
+        idx[r, :counts[r]] = np.flatnonzero(kept[r])
+    bc = dev(kept.reshape(R, nblk, -1).sum(axis=2).astype(np.int32))
+    km, d_idx = dev(np.packbits(kept, axis=1, bitorder="little").view(np.int32)), dev(idx)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    draw = lambda *shape: torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    q, k, v = draw(B, H_q, T, 128), draw(B, H_kv, n, 128), draw(B, H_kv, n, 128)
+    outs = []
+    for fused in (False, True):
+        out = torch.full((B, H_q, T, 128), float("nan"), device="cuda")
+        d_counts = dev(counts)
+        if fused:
+            probs = torch.full((B, H_kv, n), 1.0 / n, device="cuda")
+            tau = torch.zeros(R, device="cuda")
+            sel = sa.select_args(probs, 0.9, indices=None, counts=d_counts, thresholds=tau, block_counts=bc, kept_mask=km, reuse_selection=True)
+            att = sa.attn_args(q, k, v, out=out)
+        else:
+            sel, att = None, sa.attn_args(q, k, v, out=out, indices=d_idx, counts=d_counts)
+        ws = sa.alloc_workspace(sa.specattn_workspace_size(sel, att))
+        att.workspace, att.workspace_bytes = ws.data_ptr(), ws.numel()
+        if fused:
+            sa.specattn_fused(sel, att)
+        else:
+            sa.specattn_sparse_decode_attn(att)
+        torch.cuda.synchronize()
+        outs.append(out.cpu().numpy())
+    # (the same weights and products, summed in another order: fp32 sums of 16-bit weight parts, 2.4e-6 against 64 bits)
+    assert row_rel_err(outs[1], outs[0]) <= 2e-5
+
+
 @pytest.mark.parametrize("B", [80, 200])
 def test_many_rows_through_the_mask_source(B):
     # 640 rows (two rounds of the workgroup-wide cost prefix) and 1600 rows (1536 + 64: two launches)
