@@ -110,7 +110,8 @@ __device__ __forceinline__ uint32_t mask_word(uint32_t nibble, int lane)
 // 0 the highest), add them up as integers (bins of one exponent add exactly), and a prefix over the lanes tells every lane the
 // mass above its bins; the bins of the lane that holds the boundary are then searched one per lane.  (All waves together, with
 // the totals of the waves through LDS and two barriers, took 2.1 us per step of 2048 bins.)
-template <int NB, bool FIRST>
+// Beside few registers (the streaming kernel) the bins are read an exponent's at a time, else (TOGETHER) all at once.
+template <int NB, bool FIRST, bool TOGETHER = false>
 __device__ __forceinline__ int locate_bin(const unsigned long long *hist, Located &found, int e_field_fixed, float top_p, double &target,
                                           double &m_above, unsigned &c_above, unsigned long long &bin_packed)
 {
@@ -124,9 +125,18 @@ __device__ __forceinline__ int locate_bin(const unsigned long long *hist, Locate
 #pragma unroll
         for (int g = 0; g < RUNS; ++g) {
             sum[g] = 0ull;
+            if constexpr (TOGETHER) continue;
 #pragma unroll
             for (int j = 0; j < RUN; ++j) sum[g] += mine[g * RUN + j];
-            __builtin_amdgcn_sched_barrier(0);                 // (not all loads at once: 1100 streamed rows of 66000 271.3 / 269.4 us; split ones the same)
+            __builtin_amdgcn_sched_barrier(0);                 // (not all loads at once: 1100 streamed rows of 66000 271.3 / 269.4 us)
+        }
+        if constexpr (TOGETHER) {
+            unsigned long long v[BPL];
+#pragma unroll
+            for (int j = 0; j < BPL; ++j) v[j] = mine[j];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < BPL; ++j) sum[j / RUN] += v[j];
         }
         auto exponent = [&](int g) { return FIRST ? (63 - lane) * RUNS + g : e_field_fixed; };
         int cut = -1;                                          // exponent fields up to this one count as empty
@@ -525,6 +535,9 @@ template <int THREADS, int NV4, bool CHUNKED = false> specattn_status launch_one
 // the row, by atomics in memory after a launch that clears it (integers: any order gives the same sums), and as many of the
 // boundary bin's entries are collected as there is room for: 32 heavy-tailed rows of 131072 in an eighth of the workspace 24.4 us
 // (24.1 with all of it, 71 without any), 8 of 65536 20.8 (19.2, 26.7).
+// The three kernels' arguments in dependent turns with two divisions, the bins of a locate step eight at a time, a wave's second slice behind its
+// first one / arguments in one batch, all bins at once, both slices together, us: 32 rows of 131072 24.5 / 23.8, 8 of them 19.4 / 18.2, 16 of 250001
+// 27.8 / 26.6, 32 of 70000 23.8 / 23.0, 8 of 65536 20.9 / 19.9.
 constexpr int MW_THREADS = 512;
 constexpr int MW_WAVES = MW_THREADS / 64;
 constexpr int MW_ITEM = MW_THREADS * 4;           // positions a workgroup loads with one instruction
@@ -553,6 +566,15 @@ struct MwLaunch {
     int slices, slice_len;           // workgroups per row; positions per workgroup (a multiple of MW_ITEM)
     int collect;                     // entries of a slice that can be collected: slice_len >> MW_COLLECT_SHIFT; LEAN: at most
 };
+
+// What the three kernels use, in one batch (left to the compiler, the row and slice alone take three dependent turns).
+__device__ __forceinline__ void mw_preload(const MwLaunch &w)
+{
+    SPECATTN_PRELOAD(w.a.probs); SPECATTN_PRELOAD(w.a.stride_b); SPECATTN_PRELOAD(w.a.stride_h); SPECATTN_PRELOAD(w.a.H_kv); SPECATTN_PRELOAD(w.a.n_max);
+    SPECATTN_PRELOAD(w.a.seq_lens); SPECATTN_PRELOAD(w.a.top_p); SPECATTN_PRELOAD(w.a.n_tokens); SPECATTN_PRELOAD(w.a.per_h.mul); SPECATTN_PRELOAD(w.a.per_h.shift);
+    SPECATTN_PRELOAD(w.hist); SPECATTN_PRELOAD(w.head); SPECATTN_PRELOAD(w.entries); SPECATTN_PRELOAD(w.counts); SPECATTN_PRELOAD(w.state);
+    SPECATTN_PRELOAD(w.slices); SPECATTN_PRELOAD(w.slice_len); SPECATTN_PRELOAD(w.collect);
+}
 
 __device__ __forceinline__ int mw_row_len(const SelectLaunch &a, int b)
 {
@@ -675,8 +697,9 @@ template <bool LEAN> __device__ __forceinline__ void mw_hist(const MwLaunch &w)
     __shared__ unsigned long long hist[NB1];
     __shared__ int range[2][MW_WAVES];
     const SelectLaunch &a = w.a;
-    const int r = blockIdx.x / w.slices, sl = blockIdx.x - r * w.slices;
-    const int b = r / a.H_kv, h = r - b * a.H_kv;
+    mw_preload(w);
+    const int r = blockIdx.y, sl = blockIdx.x;
+    const int b = a.per_h.divide(r), h = r - b * a.H_kv;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     MwSlice slice(w, b, h, sl, mw_row_len(a, b));
 #pragma unroll
@@ -739,8 +762,9 @@ template <bool LEAN> __device__ __forceinline__ void mw_collect(const MwLaunch &
     __shared__ int ends[2][MW_WAVES];
     __shared__ int found;
     const SelectLaunch &a = w.a;
-    const int r = blockIdx.x / w.slices, sl = blockIdx.x - r * w.slices;
-    const int b = r / a.H_kv, h = r - b * a.H_kv;
+    mw_preload(w);
+    const int r = blockIdx.y, sl = blockIdx.x;
+    const int b = a.per_h.divide(r), h = r - b * a.H_kv;
     const int tid = threadIdx.x, lane = tid & 63;
     const int len = mw_row_len(a, b);
     const size_t row_at = (size_t)r * w.slices, at = row_at + sl;
@@ -753,7 +777,7 @@ template <bool LEAN> __device__ __forceinline__ void mw_collect(const MwLaunch &
     double target = 0.0, m_above = 0.0;
     unsigned c_above = 0;
     unsigned long long bin_packed = 0;
-    const int bin = locate_bin<NB1, true>(hist, located, 0, a.top_p, target, m_above, c_above, bin_packed);
+    const int bin = locate_bin<NB1, true, true>(hist, located, 0, a.top_p, target, m_above, c_above, bin_packed);
     const bool invalid = bad || bin < 0 || len == 0;                     // uniform
     if (sl == 0 && tid == 0) w.state[r] = MwState{bin_packed, target, m_above, c_above, bin, invalid ? 1 : 0};
     if (invalid) return;
@@ -802,13 +826,16 @@ __global__ __launch_bounds__(MW_THREADS) void mw_emit_kernel(MwLaunch w)
     __shared__ int sums[MW_WAVES];
     __shared__ unsigned tot[2][MW_FLIGHT * MW_WAVES];
     const SelectLaunch &a = w.a;
-    const int r = blockIdx.x / w.slices, sl = blockIdx.x - r * w.slices;
-    const int b = r / a.H_kv, h = r - b * a.H_kv;
+    mw_preload(w);
+    const int r = blockIdx.y, sl = blockIdx.x;
+    const int b = a.per_h.divide(r), h = r - b * a.H_kv;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int len = mw_row_len(a, b);
     const size_t row_at = (size_t)r * w.slices;
     const MwState st = w.state[r];
     int4 count = w.counts[row_at + (lane < w.slices ? lane : 0)];        // lane j: slice j's (never written for an invalid row)
+    clear_hist<MW_THREADS, HIST2>(hist2);                                // (while they are on their way)
+    clear_hist<MW_THREADS, HIST2>(hist3);
     if (lane >= w.slices) count.x = count.y = 0;                         // (slice 0's smallest and largest again)
     if (st.invalid) {
         if (sl == 0 && tid == 0) {
@@ -828,17 +855,29 @@ __global__ __launch_bounds__(MW_THREADS) void mw_emit_kernel(MwLaunch w)
     const bool in_lds = all <= MW_LDS_ENTRIES && !__any(count.y > w.collect);
     // fn(entry, its number in slice order) for the row's entries in the boundary bin, of slices 0 .. last
     auto each_from_memory = [&](int last, auto &&fn) {
-        for (int j = wave; j <= last; j += MW_WAVES) {                   // a wave per slice, eight loads in flight
-            const int n = __builtin_amdgcn_readlane(count.y, j), first = __builtin_amdgcn_readlane(place, j) - n;
-            if (n > w.collect) continue;
-            const uint32_t *src = w.entries + (row_at + j) * w.collect;
-            for (int k0 = 0; k0 < n; k0 += 512) {
-                uint32_t x[8];
+        // Two slices per wave at a time, eight loads of either in flight.
+        for (int j = wave; j <= last; j += 2 * MW_WAVES) {
+            const uint32_t *src[2];
+            int n[2], first[2];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) x[i] = src[k0 + i * 64 + lane < n ? k0 + i * 64 + lane : n - 1];
+            for (int s = 0; s < 2; ++s) {
+                const int js = j + s * MW_WAVES;
+                src[s] = w.entries + (row_at + min(js, w.slices - 1)) * w.collect;
+                n[s] = __builtin_amdgcn_readlane(count.y, js & 63);
+                first[s] = __builtin_amdgcn_readlane(place, js & 63) - n[s];
+                if (js > last || n[s] > w.collect) n[s] = 0;
+            }
+            for (int k0 = 0; k0 < max(n[0], n[1]); k0 += 512) {
+                uint32_t x[2][8];
 #pragma unroll
-                for (int i = 0; i < 8; ++i)
-                    if (k0 + i * 64 + lane < n) fn(x[i], first + k0 + i * 64 + lane);
+                for (int s = 0; s < 2; ++s)
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) x[s][i] = src[s][min(k0 + i * 64 + lane, max(n[s], 1) - 1)];
+#pragma unroll
+                for (int s = 0; s < 2; ++s)
+#pragma unroll
+                    for (int i = 0; i < 8; ++i)
+                        if (k0 + i * 64 + lane < n[s]) fn(x[s][i], first[s] + k0 + i * 64 + lane);
             }
         }
         if (in_lds) return;
@@ -882,19 +921,17 @@ __global__ __launch_bounds__(MW_THREADS) void mw_emit_kernel(MwLaunch w)
     if (tied) {
         base += earlier;
     } else {
-        clear_hist<MW_THREADS, HIST2>(hist2);
-        clear_hist<MW_THREADS, HIST2>(hist3);
-        __syncthreads();                                                 // (also: the entries are in LDS)
+        __syncthreads();                                                 // the histograms are clear, the entries in LDS
         each_entry([&](uint32_t x, int) { add(hist2, x, (x >> 10) & 1023u); });
         __syncthreads();
-        const int b2 = locate_bin<NB2, false>(hist2, located, e_field, a.top_p, target, m_above, c_above, bin_packed);
+        const int b2 = locate_bin<NB2, false, true>(hist2, located, e_field, a.top_p, target, m_above, c_above, bin_packed);
         const uint32_t prefix = (want << 10) | (uint32_t)b2;
         if ((bin_packed >> CNT_SHIFT) == 1) {
             tau_bits = ((uint32_t)e_field << 23) | ((uint32_t)bin_packed & 0x7fffffu);
         } else {
             each_entry([&](uint32_t x, int) { if ((x >> 10) == prefix) add(hist3, x, x & 1023u); });
             __syncthreads();
-            const int b3 = locate_bin<NB2, false>(hist3, located, e_field, a.top_p, target, m_above, c_above, bin_packed);
+            const int b3 = locate_bin<NB2, false, true>(hist3, located, e_field, a.top_p, target, m_above, c_above, bin_packed);
             tau_bits = (prefix << 10) | (uint32_t)b3;
         }
         int mine = 0;
@@ -1050,6 +1087,7 @@ specattn_status launch_select_multi_wg(const SelectLaunch &a, void *scratch, siz
     const size_t hists = lean ? (size_t)rows : S;
     MwLaunch w;
     w.a = a;
+    w.a.per_h = FastDivisor(a.H_kv);
     w.slices = plan.slices;
     w.slice_len = plan.slice_len;
     w.collect = plan.slice_len >> MW_COLLECT_SHIFT;
@@ -1065,7 +1103,7 @@ specattn_status launch_select_multi_wg(const SelectLaunch &a, void *scratch, siz
     w.head = reinterpret_cast<MwHead *>(p); p += mw_align(hists * sizeof(MwHead));
     w.counts = reinterpret_cast<int4 *>(p); p += mw_align(S * sizeof(int4));
     w.state = reinterpret_cast<MwState *>(p);
-    const dim3 grid((unsigned)S);
+    const dim3 grid((unsigned)plan.slices, (unsigned)rows);
     if (lean) {
         hipLaunchKernelGGL(mw_clear_kernel, dim3(rows), dim3(MW_THREADS), 0, stream, w);
         hipLaunchKernelGGL(mw_hist_lean_kernel, grid, dim3(MW_THREADS), 0, stream, w);
