@@ -18,6 +18,8 @@ FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # packed fp32 VALU forms are kept out of the generated code (some have given wrong results on gfx950)
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # as many leading scalar arguments of a kernel as fit come in registers with the launch, not from memory
+    "-mllvm", "-amdgpu-kernarg-preload-count=14",
     "-Wall", "-Wno-unused-function",
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
 ]

@@ -23,15 +23,14 @@ __device__ __forceinline__ float wave_sum(float v)
     return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), 63));
 }
 
-// What the merge needs of a launch, apart from the rest: it is a launch behind another one and starts with a trip to memory for its arguments,
-// so they are few, and all fetched at once.
+// What the merge needs of a launch only in the end; with the new tokens, also what those need.  What its first requests need are the leading arguments, scalars
+// of 14 words in all: those come in registers with the launch (the build asks for it), without a trip to memory.  All arguments from memory in
+// one batch / so, us, with what goes before: 64 rows of 13001 positions (40 query rows each) 45.15 / 44.55, 8 of 8192 19.3 / 19.1, 32 of 2044 in chunks with new tokens
+// 17.8 / 17.7, 16 layers of 64 rows of 32768 776.5 / 772.8.  (The main kernel's arguments the same way, with the counts requested ahead of the rest:
+// 8 rows of 8192 19.5 / 19.8, 16 layers 778 / 784.)
 struct MergeArgs {
-    const uint32_t *row_parts;            // as in Plan
-    const float *part_ml, *part_o;
     float *out, *lse;
     void *out_lowp;
-    uint32_t per_h, per_t;
-    int H_q, H_kv, T, heads, g_first, qtp;
     // the new tokens behind the cache
     float sm_scale;
     const uint16_t *q, *k_new, *v_new;
@@ -57,27 +56,27 @@ struct MergeArgs {
 // makes no difference, and 16 layers of 64 rows take 797.6 us with scalar loads there, 798.8 without).  Scalar / vector, us for both launches:
 // one row of 270 tiles among 31 empty ones (268 partials) 31.3 / 27.2, one of 500 among 31 of 3 (131 partials) 21.8 / 19.6, 8 ragged
 // rows of up to 270 13.6 / 13.3; over 440 calls of few rows 4 % on average, none slower.
-template <int D, bool F16, bool TAIL> __global__ __launch_bounds__(D) void merge_partials_kernel(MergeArgs a)
+template <int D, bool F16, bool TAIL>
+__global__ __launch_bounds__(D) void merge_partials_kernel(const uint32_t *row_parts, const float *part_ml, const float *part_o, uint32_t per_h, uint32_t per_t, int H_q,
+                                                           int H_kv, int T, int heads, int g_first, int qtp, MergeArgs a)
 {
     __shared__ float red[2 * SPECATTN_MAX_T];
-    SPECATTN_PRELOAD(a.row_parts); SPECATTN_PRELOAD(a.part_ml); SPECATTN_PRELOAD(a.part_o); SPECATTN_PRELOAD(a.out); SPECATTN_PRELOAD(a.lse); SPECATTN_PRELOAD(a.out_lowp);
-    SPECATTN_PRELOAD(a.per_h); SPECATTN_PRELOAD(a.per_t); SPECATTN_PRELOAD(a.H_q); SPECATTN_PRELOAD(a.H_kv); SPECATTN_PRELOAD(a.T); SPECATTN_PRELOAD(a.heads);
-    SPECATTN_PRELOAD(a.g_first); SPECATTN_PRELOAD(a.qtp);
+    const int q = blockIdx.x, r = blockIdx.y;
+    const uint32_t parts = row_parts[r];
+    SPECATTN_PRELOAD(a.out); SPECATTN_PRELOAD(a.lse); SPECATTN_PRELOAD(a.out_lowp);
     if (TAIL) {
         SPECATTN_PRELOAD(a.sm_scale); SPECATTN_PRELOAD(a.q); SPECATTN_PRELOAD(a.k_new); SPECATTN_PRELOAD(a.v_new);
         SPECATTN_PRELOAD(a.q_stride_b); SPECATTN_PRELOAD(a.q_stride_h); SPECATTN_PRELOAD(a.q_stride_t);
     }
-    const int q = blockIdx.x, r = blockIdx.y;
-    const uint32_t parts = a.row_parts[r];
-    const int b = (int)__umulhi((uint32_t)r << 1, a.per_h), h = r - b * a.H_kv;              // (div_h, div_t)
-    const int gh = (int)(((uint32_t)q * a.per_t) >> 16), t = q - gh * a.T;
-    const int head = h * a.heads + a.g_first + gh;
-    const int64_t orow = ((int64_t)b * a.H_q + head) * a.T + t;
+    const int b = (int)__umulhi((uint32_t)r << 1, per_h), h = r - b * H_kv;              // (div_h, div_t)
+    const int gh = (int)(((uint32_t)q * per_t) >> 16), t = q - gh * T;
+    const int head = h * heads + g_first + gh;
+    const int64_t orow = ((int64_t)b * H_q + head) * T + t;
     const int dv = threadIdx.x;
     auto value = [](uint16_t x) { return F16 ? (float)__builtin_bit_cast(_Float16, x) : __uint_as_float((uint32_t)x << 16); };
     uint16_t qe = 0, ke[SPECATTN_MAX_T], ve[SPECATTN_MAX_T];
     if constexpr (TAIL) {
-        const uint16_t *kn = a.k_new + (int64_t)r * a.T * D + dv, *vn = a.v_new + (int64_t)r * a.T * D + dv;
+        const uint16_t *kn = a.k_new + (int64_t)r * T * D + dv, *vn = a.v_new + (int64_t)r * T * D + dv;
         qe = a.q[(int64_t)b * a.q_stride_b + (int64_t)head * a.q_stride_h + (int64_t)t * a.q_stride_t + dv];
 #pragma unroll
         for (int p = 0; p < SPECATTN_MAX_T; ++p) {              // (tokens past t: t's again, not used)
@@ -95,15 +94,15 @@ template <int D, bool F16, bool TAIL> __global__ __launch_bounds__(D) void merge
             uint32_t s[N];
 #pragma unroll
             for (int k = 0; k < N; ++k) {           // (behind the last share: that one's again)
-                s[k] = (uint32_t)((min(wb + k, w1) + r) * a.qtp + q);
+                s[k] = (uint32_t)((min(wb + k, w1) + r) * qtp + q);
                 if (N == 8) asm("" : "+v"(s[k]));   // (the same in all lanes, but no scalar loads: above)
-                const float2 ml = reinterpret_cast<const float2 *>(a.part_ml)[s[k]];
+                const float2 ml = reinterpret_cast<const float2 *>(part_ml)[s[k]];
                 mw[k] = ml.x;
                 lw[k] = ml.y;
             }
             __builtin_amdgcn_sched_barrier(0);      // the weights first: they are used first
 #pragma unroll
-            for (int k = 0; k < N; ++k) ow[k] = a.part_o[s[k] * D + dv];
+            for (int k = 0; k < N; ++k) ow[k] = part_o[s[k] * D + dv];
             __builtin_amdgcn_sched_barrier(0);      // all requested before the first is used
 #pragma unroll
             for (int k = 0; k < N; ++k) {           // (a weight of zero must not meet an infinite value)
@@ -291,11 +290,11 @@ static specattn_status launch_chunk(const AttnLaunch &a, hipStream_t stream)
     }
     st = check_launch("attn_mfma_kernel");
     if (st != SPECATTN_OK) return st;
-    const MergeArgs m = {plan.row_parts, plan.part_ml, plan.part_o, a.out, a.lse, a.out_lowp, plan.per_h, plan.per_t, a.H_q, a.H_kv, a.T, plan.heads, a.g_first, qtp,
-                         a.sm_scale, static_cast<const uint16_t *>(a.q), static_cast<const uint16_t *>(a.k_new), static_cast<const uint16_t *>(a.v_new),
+    const MergeArgs m = {a.out, a.lse, a.out_lowp, a.sm_scale, static_cast<const uint16_t *>(a.q), static_cast<const uint16_t *>(a.k_new), static_cast<const uint16_t *>(a.v_new),
                          a.q_stride_b, a.q_stride_h, a.q_stride_t};
     const auto merge = a.d == 64 ? merge_variant<64>(f16, a.k_new != nullptr) : merge_variant<128>(f16, a.k_new != nullptr);
-    hipLaunchKernelGGL(merge, dim3(QT, rows), dim3(a.d), 0, stream, m);
+    hipLaunchKernelGGL(merge, dim3(QT, rows), dim3(a.d), 0, stream, plan.row_parts, plan.part_ml, plan.part_o, plan.per_h, plan.per_t, a.H_q, a.H_kv, a.T, plan.heads,
+                       a.g_first, qtp, m);
     return check_launch("merge_partials_kernel");
 }
 
