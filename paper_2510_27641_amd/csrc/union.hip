@@ -13,6 +13,8 @@
 
 #include "common.h"
 
+#include <type_traits>
+
 namespace specattn {
 namespace {
 
@@ -221,13 +223,19 @@ struct WordsLaunch {
 // all segments before (on average half the row's words: 16 segments read 8 / 32 = a quarter of what the rows weigh, from
 // L2), which costs less than a launch of its own or a pass over the rows: 64 rows of 32768 positions, 16 members each,
 // 8.5 us behind a selection of 58 us (without the bits: selection 48 us, mask pass over the rows 44 us, compaction 6.5 us).
+// Bound by its chain of trips: the arguments come in one batch, up to 16 members' words are requested together, the segments that read most start
+// first, and all segments of a row go to one XCD (where the rows are a multiple of eight), whose L2 then fetches the row's words once.
+// (Before / so, us, with the selection: 64 rows of 16 members of 32768 46.0 / 41.4, of 10 of 30000 38.2 / 35.6, of 2 of 32768 17.5 / 16.9, 16 rows
+// of 6 of 8192 11.8 / 10.7.)
 __global__ __launch_bounds__(U_THREADS) void union_words_kernel(UnionLaunch a, WordsLaunch w)
 {
     __shared__ uint4 words4[W_MOST / 128];
     __shared__ int wave_sum[2][U_WAVES];
     __shared__ int base_of[W_MOST / 64];                      // kept in the segment before each 64-bit word
-    const int r = blockIdx.x / w.segments, seg = blockIdx.x - r * w.segments;
-    const int b = r / a.H_kv;
+    SPECATTN_PRELOAD(w.masks); SPECATTN_PRELOAD(w.words); SPECATTN_PRELOAD(w.segments); SPECATTN_PRELOAD(w.seg_words); SPECATTN_PRELOAD(a.M); SPECATTN_PRELOAD(a.H_kv);
+    SPECATTN_PRELOAD(a.counts); SPECATTN_PRELOAD(a.row_flags); SPECATTN_PRELOAD(a.indices); SPECATTN_PRELOAD(a.idx_stride); SPECATTN_PRELOAD(a.idx_capacity);
+    SPECATTN_PRELOAD(a.emit_physical); SPECATTN_PRELOAD(a.page_table); SPECATTN_PRELOAD(a.page_shift); SPECATTN_PRELOAD(a.max_pages);
+    const int r = blockIdx.x, seg = w.segments - 1 - (int)blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int row4 = w.words >> 2, seg4 = w.seg_words >> 2;
     const int q0 = seg * seg4;
@@ -237,11 +245,17 @@ __global__ __launch_bounds__(U_THREADS) void union_words_kernel(UnionLaunch a, W
     int before = 0;
     for (int q = tid; q < q1; q += U_THREADS) {
         uint4 v = make_uint4(0u, 0u, 0u, 0u);
-#pragma unroll 8
-        for (int m = 0; m < a.M; ++m) {
-            const uint4 u = masks[(int64_t)m * row4 + q];
-            v.x |= u.x; v.y |= u.y; v.z |= u.z; v.w |= u.w;
-        }
+        auto members = [&](int m0, auto most) {                // (behind the last member: that one again)
+            constexpr int N = decltype(most)::value;
+            uint4 u[N];
+#pragma unroll
+            for (int k = 0; k < N; ++k) u[k] = masks[(int64_t)min(m0 + k, a.M - 1) * row4 + q];
+#pragma unroll
+            for (int k = 0; k < N; ++k) { v.x |= u[k].x; v.y |= u[k].y; v.z |= u[k].z; v.w |= u[k].w; }
+        };
+        int m = 0;
+        for (; m + 8 < a.M; m += 16) members(m, std::integral_constant<int, 16>{});
+        if (m < a.M) members(m, std::integral_constant<int, 8>{});
         if (q >= q0) words4[q - q0] = v;
         else before += __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
     }
@@ -277,7 +291,7 @@ __global__ __launch_bounds__(U_THREADS) void union_words_kernel(UnionLaunch a, W
     }
     __syncthreads();
     int32_t *out = a.indices + (int64_t)r * a.idx_stride;
-    const int32_t *ptab = (a.emit_physical && a.page_table) ? a.page_table + (int64_t)b * a.max_pages : nullptr;
+    const int32_t *ptab = (a.emit_physical && a.page_table) ? a.page_table + (int64_t)(r / a.H_kv) * a.max_pages : nullptr;
     for (int k = wave; k < n64; k += U_WAVES) {               // lane i: position i of the word
         const unsigned long long v = words[k];
         const int o = before + base_of[k] + __popcll(v & ((1ull << lane) - 1ull));
@@ -334,7 +348,7 @@ specattn_status launch_threshold_union(const float *probs, int64_t stride_b, int
         seg = seg < W_LEAST ? W_LEAST : seg;
         w.seg_words = (seg + 127) / 128 * 4;
         w.segments = (w.words + w.seg_words - 1) / w.seg_words;
-        hipLaunchKernelGGL(union_words_kernel, dim3((unsigned)(w.segments * rows)), dim3(U_THREADS), 0, stream, a, w);
+        hipLaunchKernelGGL(union_words_kernel, dim3((unsigned)rows, (unsigned)w.segments), dim3(U_THREADS), 0, stream, a, w);
         return check_launch("union_words_kernel");
     }
     const dim3 grid((unsigned)(blocks * rows));
