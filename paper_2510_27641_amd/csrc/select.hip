@@ -698,7 +698,7 @@ template <bool LEAN> __device__ __forceinline__ void mw_hist(const MwLaunch &w)
     __shared__ int range[2][MW_WAVES];
     const SelectLaunch &a = w.a;
     mw_preload(w);
-    const int r = blockIdx.y, sl = blockIdx.x;
+    const int r = blockIdx.x, sl = blockIdx.y;
     const int b = a.per_h.divide(r), h = r - b * a.H_kv;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     MwSlice slice(w, b, h, sl, mw_row_len(a, b));
@@ -763,7 +763,7 @@ template <bool LEAN> __device__ __forceinline__ void mw_collect(const MwLaunch &
     __shared__ int found;
     const SelectLaunch &a = w.a;
     mw_preload(w);
-    const int r = blockIdx.y, sl = blockIdx.x;
+    const int r = blockIdx.x, sl = blockIdx.y;
     const int b = a.per_h.divide(r), h = r - b * a.H_kv;
     const int tid = threadIdx.x, lane = tid & 63;
     const int len = mw_row_len(a, b);
@@ -827,7 +827,7 @@ __global__ __launch_bounds__(MW_THREADS) void mw_emit_kernel(MwLaunch w)
     __shared__ unsigned tot[2][MW_FLIGHT * MW_WAVES];
     const SelectLaunch &a = w.a;
     mw_preload(w);
-    const int r = blockIdx.y, sl = blockIdx.x;
+    const int r = blockIdx.x, sl = blockIdx.y;
     const int b = a.per_h.divide(r), h = r - b * a.H_kv;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int len = mw_row_len(a, b);
@@ -1103,7 +1103,9 @@ specattn_status launch_select_multi_wg(const SelectLaunch &a, void *scratch, siz
     w.head = reinterpret_cast<MwHead *>(p); p += mw_align(hists * sizeof(MwHead));
     w.counts = reinterpret_cast<int4 *>(p); p += mw_align(S * sizeof(int4));
     w.state = reinterpret_cast<MwState *>(p);
-    const dim3 grid((unsigned)plan.slices, (unsigned)rows);
+    // The slices of a row on one XCD (rows a multiple of eight): what they hand each other stays in its L2.  Next to each other, so dealt to all
+    // XCDs / so, us: 32 rows of 131072 23.8 / 22.4, 8 of them 17.8 / 17.0, 32 of 70000 22.8 / 21.9, 8 of 65536 19.7 / 18.7, 24 of 131072 23.1 / 22.1.
+    const dim3 grid((unsigned)rows, (unsigned)plan.slices);
     if (lean) {
         hipLaunchKernelGGL(mw_clear_kernel, dim3(rows), dim3(MW_THREADS), 0, stream, w);
         hipLaunchKernelGGL(mw_hist_lean_kernel, grid, dim3(MW_THREADS), 0, stream, w);
