@@ -95,7 +95,7 @@ __global__ __launch_bounds__(D) void merge_partials_kernel(const uint32_t *row_p
 #pragma unroll
             for (int k = 0; k < N; ++k) {           // (behind the last share: that one's again)
                 s[k] = (uint32_t)((min(wb + k, w1) + r) * qtp + q);
-                if (N == 8) asm("" : "+v"(s[k]));   // (the same in all lanes, but no scalar loads: above)
+                if (N >= 8) asm("" : "+v"(s[k]));   // (the same in all lanes, but no scalar loads: above)
                 const float2 ml = reinterpret_cast<const float2 *>(part_ml)[s[k]];
                 mw[k] = ml.x;
                 lw[k] = ml.y;
@@ -112,9 +112,10 @@ __global__ __launch_bounds__(D) void merge_partials_kernel(const uint32_t *row_p
             acc.add_all(mw, lw, ow);
         };
         int wb = w0;
-        for (; wb + 7 <= w1; wb += 8) trip(wb, std::integral_constant<int, 8>{});
+        for (; wb + 15 <= w1; wb += 16) trip(wb, std::integral_constant<int, 16>{});
         const int left = w1 - wb + 1;
-        if (left > 5) trip(wb, std::integral_constant<int, 8>{});
+        if (left > 8) trip(wb, std::integral_constant<int, 16>{});
+        else if (left > 5) trip(wb, std::integral_constant<int, 8>{});
         else if (left > 2) trip(wb, std::integral_constant<int, 5>{});
         else if (left > 0) trip(wb, std::integral_constant<int, 2>{});
     }
