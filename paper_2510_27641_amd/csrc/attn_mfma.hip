@@ -1,5 +1,5 @@
 // Host side of the matrix-core attention route and the merge of its partials; the kernel itself is in
-// attn_mfma_kernel.h, its variants in three translation units (this one: index lists, d = 128).
+// attn_mfma_kernel.h, its variants in four translation units of their own.
 #include "attn_mfma_kernel.h"
 
 #include <algorithm>
@@ -156,9 +156,6 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 }  // namespace
 
-// variants<D, SRC>() of the translation units that hold them
-const void *attn_mfma_list_128(int nqt, int layout, bool f16) { return variant<128, LIST>(nqt, layout, f16); }
-
 bool attn_mfma_supported(const AttnLaunch &a)
 {
     // any number of query heads per kv head: groups of more than 64 query rows run as several launches
@@ -167,10 +164,10 @@ bool attn_mfma_supported(const AttnLaunch &a)
 
 int attn_mfma_workgroups() { return cu_count() * WG_PER_CU; }
 
-static const void *attn_mfma_variant(int d, int src, int nqt, int layout, bool f16)
+static const void *attn_mfma_variant(int d, int src, int form, int nqt, int layout, bool f16)
 {
-    if (d == 64) return src == LIST ? attn_mfma_list_64(nqt, layout, f16) : nullptr;
-    return src == LIST ? attn_mfma_list_128(nqt, layout, f16) : attn_mfma_mask_128(nqt, layout, f16);
+    if (src == MASK) return d == 128 && form != FEW_ANY ? attn_mfma_mask(form, nqt, layout, f16) : nullptr;
+    return form == FEW_POSITIONS ? attn_mfma_few_positions(d, nqt, layout, f16) : form == FEW_ANY ? attn_mfma_few_any(d, nqt, layout, f16) : attn_mfma_many(d, nqt, layout, f16);
 }
 
 // The kernels use more LDS than the default limit: raise it for every variant, once per device.
@@ -187,8 +184,8 @@ specattn_status attn_mfma_configure()
     }
     std::lock_guard<std::mutex> lock(mu);
     if (done[dev]) return SPECATTN_OK;
-    for (int k = 0; k < 3 * 4 * 3 * 2; ++k) {
-        const void *fn = attn_mfma_variant(k % 3 == 2 ? 64 : 128, k % 3 == 1 ? MASK : LIST, k / 3 % 4 + 1, k / 12 % 3, k / 36 != 0);
+    for (int k = 0; k < 3 * 4 * 3 * 2 * 3; ++k) {
+        const void *fn = attn_mfma_variant(k % 3 == 2 ? 64 : 128, k % 3 == 1 ? MASK : LIST, k / 72, k / 3 % 4 + 1, k / 12 % 3, k / 36 % 2 != 0);
         if (fn && hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes(MASK)) != hipSuccess) {
             (void)hipGetLastError();
             set_error("cannot reserve %d bytes of LDS", lds_bytes(MASK));
@@ -279,7 +276,11 @@ static specattn_status launch_chunk(const AttnLaunch &a, hipStream_t stream)
     const int layout = a.indices_are_physical ? PHYSICAL : (a.page_table ? PAGE_TABLE : CONTIGUOUS);
     const int src = a.kept_mask ? MASK : LIST;
     const bool f16 = a.dtype == SPECATTN_F16;
-    const void *fn = attn_mfma_variant(a.d, src, nqt, layout, f16);
+    // (The form for single positions spills six registers more at four query tiles of 128: 64 rows of 13001 positions with 64 query rows 43.0 one form for
+    // all, 44.0 that one, 42.5 the form for lists of any kind.)
+    const bool any = src == LIST && (a.dense || a.chunk_shift || (nqt == 4 && a.d == 128));
+    const int form = rows > FEW_ROWS ? MANY : any ? FEW_ANY : FEW_POSITIONS;
+    const void *fn = attn_mfma_variant(a.d, src, form, nqt, layout, f16);
     if (!fn) { set_error("the fused path takes logical positions, not pool slots"); return SPECATTN_EUNSUPPORTED; }
     specattn_status st = attn_mfma_configure();
     if (st != SPECATTN_OK) return st;

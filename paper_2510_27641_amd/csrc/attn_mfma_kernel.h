@@ -113,6 +113,12 @@ constexpr int FEW_ROWS = 64;                                    // rows a single
 // Where the kept positions of a row come from: an index list in memory (also chunk lists and dense calls, which
 // have no list at all), or the kept-position mask and per-block counts of the selection (fused call).
 enum Source { LIST = 0, MASK = 1 };
+// What a kernel is built for: up to FEW_ROWS rows with lists of single positions (or the mask), as many rows with chunk lists or no
+// lists, any number of rows.  A launch starts with cold instruction caches, and what it does not need is jumped over and held in
+// registers all the same.  One form for all calls / these three, us, with the selection: 8 rows of 8192 18.6 / 18.2, 16 of 8192 (d = 64) 18.3 /
+// 17.7, 64 of 13001 44.3 / 43.6, 32 of 2044 in chunks with new tokens 17.8 / 17.4, 16 layers of 64 rows of 32768 777 / 770, over the mask 835 / 830; 512
+// ragged rows 548.3 / 547.9.
+enum Form { FEW_POSITIONS = 0, FEW_ANY = 1, MANY = 2 };
 constexpr int off_q(int src) { return OFF_SCAT + NW * (src == MASK ? POS_CAP * 4 : 256); }   // Q tile [NQT * 16 rows], chunks swizzled like K
 constexpr int lds_bytes(int src) { return 157956 + off_q(src) - off_q(LIST); }
 // Rows a launch of NQT query tiles can take: what the LDS leaves for the row tables behind the Q tile.
@@ -341,6 +347,12 @@ __device__ __forceinline__ int div_t(const Plan &p, int q) { return (int)(((uint
 // (fresh Q, partial write), so that workgroups holding many short rows get fewer tiles.
 template <int TILE> __device__ __forceinline__ int row_cost(int count) { return count > 0 ? (count + TILE - 1) / TILE + SEG_COST : 0; }
 
+// The positions row r of sequence b attends to; PLAIN: as many as its list or mask has.
+template <bool PLAIN> __device__ __forceinline__ int row_positions(const AttnLaunch &a, int r, int b)
+{
+    return PLAIN ? min(max(a.counts[r], 0), a.idx_capacity) : attn_row_count(a, r, b);
+}
+
 // Exclusive prefix of the row costs into pre[0..rows], every workgroup for itself (more than FEW_ROWS rows).
 template <int TILE, int TABLE_ROWS> __device__ __forceinline__ void cost_prefix(const AttnLaunch &a, const Plan &plan, int rows, int *pre, int *cnt, int *wsum)
 {
@@ -526,7 +538,7 @@ template <typename F> __device__ __forceinline__ float over_rows(float x, F &&jo
 __device__ __forceinline__ float sum_of_rows(float x) { return over_rows(x, [](float a, float b) { return a + b; }); }
 __device__ __forceinline__ float max_of_rows(float x) { return over_rows(x, [](float a, float b) { return fmaxf(a, b); }); }
 
-template <int D, int NQT, int LAYOUT, int SRC, bool F16>
+template <int D, int NQT, int LAYOUT, int SRC, bool F16, int FORM>
 __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunch a, Plan plan)
 {
     typedef typename Half<F16>::x8 h16x8;
@@ -546,9 +558,13 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
     constexpr bool TIGHT = NQT >= 3;                                    // registers are short: what the tile loop can fetch again is not held
     constexpr bool FOLD = !TIGHT && UNIT == 4;                          // a lane's chunk of a row is part of the row offset it holds
     constexpr int QG = NQT <= 2 ? NQT : 1;                              // query tiles whose scores are held at a time
+    constexpr bool few_rows = FORM != MANY;                             // the launch has at most FEW_ROWS rows
+    constexpr bool PLAIN = FORM == FEW_POSITIONS || SRC == MASK;        // ranks are single positions of a list or mask
+    const bool dense = !PLAIN && a.dense;
+    const int chunk_shift = PLAIN ? 0 : a.chunk_shift;
     const int rows = a.B * a.H_kv;
     int *pre = reinterpret_cast<int *>(smem + TAB::OFF_TAB);
-    int *cnt_lds = pre + ((a.B * a.H_kv <= FEW_ROWS ? FEW_ROWS : TAB::ROWS) + 1);
+    int *cnt_lds = pre + ((few_rows ? FEW_ROWS : TAB::ROWS) + 1);
     int *wsum = reinterpret_cast<int *>(smem + OFF_WSUM);
     char *q_lds = smem + off_q(SRC);
     const int tid = threadIdx.x, lane = tid & 63;
@@ -585,7 +601,8 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
     SPECATTN_PRELOAD(a.sm_scale);
     SPECATTN_PRELOAD(a.q_stride_b); SPECATTN_PRELOAD(a.q_stride_h); SPECATTN_PRELOAD(a.q_stride_t);
     SPECATTN_PRELOAD(a.kv_stride_b); SPECATTN_PRELOAD(a.kv_stride_h); SPECATTN_PRELOAD(a.kv_stride_n);
-    SPECATTN_PRELOAD(a.counts); SPECATTN_PRELOAD(a.idx_capacity); SPECATTN_PRELOAD(a.dense); SPECATTN_PRELOAD(a.chunk_shift);
+    SPECATTN_PRELOAD(a.counts); SPECATTN_PRELOAD(a.idx_capacity);
+    if (!PLAIN) { SPECATTN_PRELOAD(a.dense); SPECATTN_PRELOAD(a.chunk_shift); }
     SPECATTN_PRELOAD(a.g_first); SPECATTN_PRELOAD(a.k_new);
     SPECATTN_PRELOAD(a.out); SPECATTN_PRELOAD(a.out_lowp); SPECATTN_PRELOAD(a.lse);
     SPECATTN_PRELOAD(plan.part_ml); SPECATTN_PRELOAD(plan.part_o); SPECATTN_PRELOAD(plan.row_parts);
@@ -597,7 +614,7 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
     // this workgroup starts in is not known yet), so that its first segment need not go to memory for them again.
     constexpr int BC_PT = TAB::BC_ALL / THREADS;
     int *bc_lds = reinterpret_cast<int *>(smem + TAB::OFF_BC);
-    const bool bc_all = SRC == MASK && rows <= FEW_ROWS && rows * a.blocks_per_row <= TAB::BC_ALL;
+    const bool bc_all = SRC == MASK && few_rows && rows * a.blocks_per_row <= TAB::BC_ALL;
     int bc_pf[BC_PT];
     if (bc_all) {
 #pragma unroll
@@ -608,11 +625,10 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
     }
     // Every workgroup finds the cost line by itself.  Up to 64 rows, lane i of every wave holds row i: counts, prefix, share and
     // every row's local tile range without a table, a barrier or a search; more rows go through tables in LDS.
-    const bool few_rows = rows <= FEW_ROWS;              // uniform
     int row_lo = 0, row_cnt = 0, total;                  // few rows: cost prefix and kept count of row `lane`
     int unit = 0;                                        // tiles of a share that is a part of one row, or 0: a share of the line
-    if (__builtin_expect(few_rows, 1)) {
-        row_cnt = lane < rows ? attn_row_count(a, lane, div_h(plan, lane)) : 0;
+    if constexpr (few_rows) {
+        row_cnt = lane < rows ? row_positions<PLAIN>(a, lane, div_h(plan, lane)) : 0;
         const int cost = row_cost<TILE>(row_cnt), inc = wave_inclusive_sum(cost);
         row_lo = inc - cost;
         total = __builtin_amdgcn_readlane(inc, 63);      // (lanes past the last row add nothing)
@@ -712,10 +728,10 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
     auto request_words = [&](const int32_t *idx_row, int count, int t, int s) {
         int jj = t * TILE + (lane & (TILE - 1));
         jj = jj < count ? jj : count - 1;
-        __builtin_amdgcn_global_load_lds(GLOBAL_PTR(idx_row + (jj >> a.chunk_shift)), LDS_PTR(void, slot_lds + s * SLOT_BYTES), 4, 0, 0);
+        __builtin_amdgcn_global_load_lds(GLOBAL_PTR(idx_row + (jj >> chunk_shift)), LDS_PTR(void, slot_lds + s * SLOT_BYTES), 4, 0, 0);
     };
     if (r < rows) {
-        if (SRC == LIST && !a.dense) {
+        if (SRC == LIST && !dense) {
             int lt_begin, lt_end;
             seg_range(r, lt_begin, lt_end);
             if (lt_begin + wave < lt_end) {
@@ -743,9 +759,9 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
         const KvMap map = make_map<LAYOUT>(a, b, h);
         const char *kbh = static_cast<const char *>(a.k) + map.base * 2;
         const char *vbh = static_cast<const char *>(a.v) + map.base * 2;
-        const int32_t *idx_row = (SRC == LIST && !a.dense) ? a.indices + (int64_t)r * a.idx_stride : nullptr;
+        const int32_t *idx_row = (SRC == LIST && !dense) ? a.indices + (int64_t)r * a.idx_stride : nullptr;
         const uint32_t *mask_row = SRC == MASK ? a.kept_mask + (int64_t)r * a.blocks_per_row * (SEL_BLOCK / 32) : nullptr;
-        const int n_idx = (SRC == MASK || !a.dense) ? 1 : 0;            // LDS-DMA instructions per tile for list / mask words
+        const int n_idx = (SRC == MASK || !dense) ? 1 : 0;            // LDS-DMA instructions per tile for list / mask words
 
         // ---- the wave's tiles --------------------------------------------------------------------------
         // list: tile k of the share goes to wave k mod NW; mask: every wave takes a run of tiles, whose positions it finds by itself
@@ -790,7 +806,7 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
             if (SRC == MASK) {
                 const int w = p_word + lane;
                 __builtin_amdgcn_global_load_lds(GLOBAL_PTR(mask_row + (w < nw ? w : nw - 1)), LDS_PTR(void, slot_lds), 4, 0, 0);
-            } else if (!a.dense) {
+            } else if (!dense) {
                 request_words(idx_row, count, t < tiles ? t : tiles - 1, s);
             }
         };
@@ -853,13 +869,13 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
                 // (a mask that does not hold `count` bits would leave entries unwritten: stay inside the row)
 #pragma unroll
                 for (int i = 0; i < 8; ++i) pos[i] = e[i] < (uint32_t)a.n_max ? (int)e[i] : a.n_max - 1;
-            } else if (a.dense) {
+            } else if (dense) {
 #pragma unroll
                 for (int i = 0; i < 8; ++i) pos[i] = rank(i);
             } else {
                 uint32_t e[8];
                 lds_read_entries<RPI>(e, slot_addr + (uint32_t)(s * SLOT_BYTES + lrow * 4));
-                const int cs = a.chunk_shift, low = (1 << cs) - 1;
+                const int cs = chunk_shift, low = (1 << cs) - 1;
 #pragma unroll
                 for (int i = 0; i < 8; ++i) pos[i] = (int)e[i];
                 if (cs) {
@@ -1211,10 +1227,10 @@ __global__ __launch_bounds__(THREADS, WG_PER_CU) void attn_mfma_kernel(AttnLaunc
 
 }
 
-// Kernel variants of one head dimension and source, by query tiles, layout and element type (null: not built).
-template <int D, int SRC> const void *variant(int nqt, int layout, bool f16)
+// Kernel variants of one head dimension, source and form, by query tiles, layout and element type (null: not built).
+template <int D, int SRC, int FORM> const void *variant(int nqt, int layout, bool f16)
 {
-#define SPECATTN_FN(NQT, LAY) (f16 ? reinterpret_cast<const void *>(&attn_mfma_kernel<D, NQT, LAY, SRC, true>) : reinterpret_cast<const void *>(&attn_mfma_kernel<D, NQT, LAY, SRC, false>))
+#define SPECATTN_FN(NQT, LAY) (f16 ? reinterpret_cast<const void *>(&attn_mfma_kernel<D, NQT, LAY, SRC, true, FORM>) : reinterpret_cast<const void *>(&attn_mfma_kernel<D, NQT, LAY, SRC, false, FORM>))
 #define SPECATTN_LAYOUTS(NQT) \
     do { \
         if (layout == CONTIGUOUS) return SPECATTN_FN(NQT, CONTIGUOUS); \
@@ -1226,7 +1242,7 @@ template <int D, int SRC> const void *variant(int nqt, int layout, bool f16)
     case 1: SPECATTN_LAYOUTS(1);
     case 2: SPECATTN_LAYOUTS(2);
     case 3: SPECATTN_LAYOUTS(3);
-    case 4: if constexpr (SRC == LIST) SPECATTN_LAYOUTS(4); else return nullptr;   // (its tile loop would spill)
+    case 4: if constexpr (SRC == LIST && !(D == 128 && FORM == FEW_POSITIONS)) SPECATTN_LAYOUTS(4); else return nullptr;   // (the mask's tile loop would spill)
     }
     return nullptr;
 #undef SPECATTN_LAYOUTS

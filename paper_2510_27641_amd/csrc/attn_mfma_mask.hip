@@ -3,6 +3,9 @@
 
 namespace specattn {
 
-const void *attn_mfma_mask_128(int nqt, int layout, bool f16) { return variant<128, MASK>(nqt, layout, f16); }
+const void *attn_mfma_mask(int form, int nqt, int layout, bool f16)
+{
+    return form == MANY ? variant<128, MASK, MANY>(nqt, layout, f16) : variant<128, MASK, FEW_POSITIONS>(nqt, layout, f16);
+}
 
 }  // namespace specattn

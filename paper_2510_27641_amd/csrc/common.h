@@ -224,9 +224,10 @@ size_t attn_mfma_workspace_bytes(int rows, int G, int T, int d);       // what l
 size_t attn_mfma_workspace_narrow_bytes(int rows, int G, int T, int d);   // the same with two query tiles per launch
 size_t attn_mfma_workspace_min_bytes(int rows, int G, int T, int d);   // the least a call runs with
 // kernel variants by query tiles (1 .. 4), layout and element type; null where none is built
-const void *attn_mfma_list_128(int nqt, int layout, bool f16);
-const void *attn_mfma_mask_128(int nqt, int layout, bool f16);
-const void *attn_mfma_list_64(int nqt, int layout, bool f16);
+const void *attn_mfma_few_positions(int d, int nqt, int layout, bool f16);
+const void *attn_mfma_few_any(int d, int nqt, int layout, bool f16);
+const void *attn_mfma_many(int d, int nqt, int layout, bool f16);
+const void *attn_mfma_mask(int form, int nqt, int layout, bool f16);
 specattn_status launch_attn_mfma(const AttnLaunch &a, hipStream_t stream);
 
 }  // namespace specattn
