@@ -41,9 +41,9 @@ struct MergeArgs {
 // their partials (r, w) combined; rows without any kept position get out = 0, lse = -inf.  When the
 // caller gave the new tokens behind the cache (TAIL), every row goes through here (the main kernel then
 // leaves partials only) and query t also attends to new tokens 0..t.
-// Bound by latency: the arguments, the row's shares, then a trip to memory and two chains of sums per eight partials.  Head dimension and
+// Bound by latency: the arguments, the row's shares, then a trip to memory and two chains of sums per sixteen partials.  Head dimension and
 // element type are constants, the grid and the plan leave no division, and every load of a trip is requested before the first partial is used; a short
-// rest asks for two or five, since eight are a chain too long there.  What the new tokens need is requested ahead of the shares, in one go.
+// rest asks for two, five or eight, since sixteen are a chain too long there (rows of 9 to 16 parts in two trips of eight / one: 8 rows of 8192 19.2 / 19.0 us).  What the new tokens need is requested ahead of the shares, in one go.
 // (With the element type tested at every one of those loads, each waited for the one before; with all arguments of the launch, fetched in three
 // turns; and with the partials joined one after the other - as it was / now, us,
 // with selection and attention: 32 rows of 2044 positions in chunks with new tokens 20.0 / 17.7, 8 rows of 8192 19.6 / 19.0, 16 of 8192 (d = 64) 19.2 / 18.7; 64
