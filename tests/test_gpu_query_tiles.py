@@ -386,3 +386,40 @@ def rng_tiles(total, rows):
     part = np.floor(total * rng.dirichlet(np.full(full, 8.0))).astype(int)
     part[0] += total - part.sum()
     return np.concatenate([part, np.zeros(rows - full, dtype=int)])
+
+
+@pytest.mark.parametrize("rows", [63, 64, 65])
+@pytest.mark.parametrize("kind", ["positions", "chunks", "dense"])
+@pytest.mark.parametrize("d,G,T", [(128, 4, 5), (128, 8, 8), (64, 8, 5)])
+def test_forms_of_the_kernel_at_the_line_between_them(d, G, T, kind, rows):
+    """Up to 64 rows and more run in kernels of their own, lists of single positions apart from chunk lists and dense calls, and four query tiles
+    of 128 apart from fewer: every sequence on its own against the oracle, some of them without a kept position."""
+    n, chunk = 333, 8
+    w = W.llama8b_layer(seed=rows + G, B=rows, n=n, H_q=G, H_kv=1, T=T, d=d)
+    rng = np.random.default_rng(rows)
+    keep = rng.random((rows, -(-n // chunk))) < 0.3
+    keep[::7] = False
+    keep[1::7, -1] = True                                      # (the partial chunk at the end)
+    mask = np.ones((rows, 1, n), dtype=np.uint8)
+    kw = {}
+    if kind == "chunks":
+        mask = np.repeat(keep, chunk, axis=1)[:, :n].astype(np.uint8).reshape(rows, 1, n)
+        idx, cnt = lists(keep.reshape(rows, 1, -1))
+        kw = dict(indices=idx, counts=cnt, chunk_size=chunk)
+    elif kind == "positions":
+        mask = (rng.random((rows, 1, n)) < 0.3).astype(np.uint8)
+        mask[::7] = 0
+        idx, cnt = lists(mask)
+        kw = dict(indices=idx, counts=cnt)
+    q, k, v = kv_tensors(w)
+    out = torch.full(q.shape, float("nan"), device="cuda")
+    a = sa.attn_args(q, k, v, out=out, **kw)
+    ws = sa.alloc_workspace(sa.specattn_workspace_size(None, a))
+    a.workspace, a.workspace_bytes = ws.data_ptr(), ws.numel()
+    sa.specattn_sparse_decode_attn(a)
+    torch.cuda.synchronize()
+    out = out.cpu().numpy()
+    ref, _ = oracle_attention(w, mask)
+    if kind != "dense":
+        assert (out[::7] == 0).all()
+    assert row_rel_err(out, ref) <= tol(w)
