@@ -427,7 +427,7 @@ template <int TILE> struct Share {
 // floor(a / b) for 0 <= a < 2^52, 0 < b < 2^31 in one fp64 division instead of the long 64-bit integer division
 // sequence: both operands are exact in fp64, the correctly rounded quotient can only reach the next integer from
 // below when a / b is within 2^-53 of it, and a true quotient that is no integer lies at least 1 / b below it.
-__device__ __forceinline__ int floor_div(int64_t a, int b)
+__host__ __device__ __forceinline__ int floor_div(int64_t a, int b)
 {
     return (int)floor((double)a / (double)b);
 }
@@ -447,16 +447,19 @@ constexpr int TILT = 5;
 // share 24.6 / 24.7, of 33 28.6 / 28.6, of 38 32.0 / 31.7, of 62 46.8 / 46.1, of 97 67.8 / 67.6; 16 rows of 40 34.7 / 34.8, of 59 47.4 / 46.8).  Not where rows
 // are so many that equal counts make every share whole rows: there a moved boundary costs a partial (256 rows of 2000 positions 48.3 / 51.2).
 constexpr int TILT_FROM = 32;
-template <int TILE> __device__ __forceinline__ Share<TILE> make_share(int total, int n_wg, int rows, int w)
+// ... and only with the workgroups of a whole GPU, 32 on each of eight XCDs: on a partition of it a share's parity says nothing about an XCD that is
+// known to be slower (with one XCD all shares are on the same one), and the shares stay equal.
+constexpr int TILT_WORKGROUPS = 256;
+template <int TILE> __host__ __device__ __forceinline__ Share<TILE> make_share(int total, int n_wg, int rows, int w)
 {
     // (This is on the way to a workgroup's first request: no branches, and the usual numbers of workgroups are powers of two, for which a
     // shift gives the same floor as the division.)
     int move = ((w >> 1) ^ (w >> 2)) & 1 ? -TILT : TILT;       // of boundary w or w + 1, whichever is odd
-    move = (total >= TILT_FROM * n_wg) & ((rows * 2 <= n_wg) | ((total & (n_wg - 1)) != 0)) ? move : 0;
+    move = (n_wg == TILT_WORKGROUPS) & (total >= TILT_FROM * n_wg) & ((rows * 2 <= n_wg) | ((total & (n_wg - 1)) != 0)) ? move : 0;
     const int64_t from = (int64_t)(w * 128 + ((w & 1) ? move : 0)) * total, to = (int64_t)(w * 128 + 128 + ((w & 1) ? 0 : move)) * total;
     Share<TILE> s;
-    s.c0 = (int)(from >> (38 - __clz(n_wg)));
-    s.c1 = (int)(to >> (38 - __clz(n_wg)));
+    s.c0 = (int)(from >> (38 - __builtin_clz(n_wg)));
+    s.c1 = (int)(to >> (38 - __builtin_clz(n_wg)));
     if (__builtin_expect((n_wg & (n_wg - 1)) != 0, 0)) {       // (equal shares: share_index deals these to XCDs as they come)
         s.c0 = floor_div((int64_t)w * total, n_wg);
         s.c1 = floor_div((int64_t)(w + 1) * total, n_wg);
@@ -470,7 +473,7 @@ template <int TILE> __device__ __forceinline__ Share<TILE> make_share(int total,
 // four consecutive shares (the usual team of a row) are four workgroups on four different XCDs, and the sets
 // {x, x+1, x+3, x+6} rotate from team to team, so that every XCD serves half of the teams and a difference in
 // speed between XCDs is spread over all rows.  (A bijection of 0 .. n_wg - 1 when n_wg is a multiple of 32.)
-__device__ __forceinline__ int share_index(int wg, int n_wg)
+__host__ __device__ __forceinline__ int share_index(int wg, int n_wg)
 {
     if (n_wg & 31) return wg;
     const int x = wg & 7, c = wg >> 3, m = c & 3;
