@@ -109,6 +109,10 @@ struct F32Plan {
 // PLAIN: contiguous keys and values, lists of single positions, no new tokens.  A launch starts with cold instruction caches, and what it does not
 // need is jumped over and held in registers all the same.  One form for all calls / two, us: selection and attention of 8 rows of 1024 11.4 / 10.8;
 // attention of 8 rows of 8192 11.4 / 10.9, 32 of 6000 with 32 query rows (d = 128) 27.8 / 26.1, 16 of 4000 with 6 (d = 128) 10.5 / 9.7.
+// Not with four query tiles of 128: either form spills there, this one 112 bytes per lane, the other 84.  PLAIN / the other, attention alone: 64 query
+// rows, 8 rows of 512 kept positions 22.9 / 22.5, 16 of 1024 28.3 / 27.2, 64 of 320 47.3 / 45.6, 8 of 4000 56.7 / 54.3; but three tiles 17.0 / 17.5, and
+// four of 64 (16 of 1024) 31.4 / 31.9.
+constexpr bool plain_form(int d, int nqt) { return !(d == 128 && nqt == 4); }
 template <typename T, int D, int NQT, bool PLAIN>
 __global__ __launch_bounds__(GEN_THREADS, 1) void attn_f32_kernel(AttnLaunch a, F32Plan plan)
 {
@@ -397,7 +401,7 @@ template <typename T, int D, bool PLAIN> const void *variant(int nqt)
     case 1: return reinterpret_cast<const void *>(&attn_f32_kernel<T, D, 1, PLAIN>);
     case 2: return reinterpret_cast<const void *>(&attn_f32_kernel<T, D, 2, PLAIN>);
     case 3: return reinterpret_cast<const void *>(&attn_f32_kernel<T, D, 3, PLAIN>);
-    case 4: return reinterpret_cast<const void *>(&attn_f32_kernel<T, D, 4, PLAIN>);
+    case 4: return reinterpret_cast<const void *>(&attn_f32_kernel<T, D, 4, PLAIN && plain_form(D, 4)>);
     }
     return nullptr;
 }
@@ -508,7 +512,7 @@ specattn_status launch_attn(const AttnLaunch &a, hipStream_t stream)
     if (attn_mfma_supported(a) && (a.d == 128 || attn_mfma_takes_64(a))) return launch_attn_mfma(a, stream);
     const int QT = G * a.T, nqt = (QT + 15) / 16;
     int ns = splits(rows, a.idx_capacity << a.chunk_shift, nqt, a.d);
-    const bool plain = !a.dense && !a.chunk_shift && !a.page_table && !a.indices_are_physical && !a.k_new;
+    const bool plain = plain_form(a.d, nqt) && !a.dense && !a.chunk_shift && !a.page_table && !a.indices_are_physical && !a.k_new;
     const void *fn = plain ? variant<true>(a.dtype, a.d, nqt) : variant<false>(a.dtype, a.d, nqt);
     if (!fn) { set_error("no attention kernel for dtype %d, d %d", a.dtype, a.d); return SPECATTN_EUNSUPPORTED; }
     specattn_status st = attn_generic_configure();

@@ -72,6 +72,22 @@ def test_query_rows_around_the_tiles_with_new_tokens(d, n, G, T):
     assert torch.equal(out, low)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n", [300, 2500])
+@pytest.mark.parametrize("G,T", [(1, 1), (2, 8), (17, 1), (4, 8), (11, 3), (8, 6), (7, 7), (8, 8)])
+def test_query_rows_around_the_tiles(d, n, G, T):
+    """Contiguous lists of single positions alone, which have a form of their own up to three query tiles of 128."""
+    w = W.llama8b_layer(seed=G * T, B=2, n=n, H_q=3 * G, H_kv=3, T=T, d=d, dtype="f32")
+    mask = oracle.topp_select(w.probs.reshape(-1, w.n), w.top_p).mask().reshape(w.B, w.H_kv, w.n)
+    mask[1, 1] = 0
+    q, k, v = kv_tensors(w)
+    out, lse = gpu_attention(q, k, v, *lists(mask, n))
+    ref, want_lse = oracle_attention(w, mask)
+    assert row_rel_err(out, ref) <= TOL["f32"] and (out[1, G:2 * G] == 0).all()
+    live = np.isfinite(want_lse)
+    assert np.abs(lse[live] - want_lse[live]).max() <= 1e-5 and np.isneginf(lse[~live]).all()
+
+
 def test_infinite_value_in_a_partial_tile():
     """A kept position with an infinite value in the row's last, partial tile: it alone decides, nothing turns into NaN."""
     w = W.tiny_f32(seed=1, n=600, H=2, d=64)
@@ -83,10 +99,11 @@ def test_infinite_value_in_a_partial_tile():
     assert np.isposinf(out[0, 0]).all() and np.isfinite(out[0, 1]).all()
 
 
+@pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
-def test_many_kv_heads_in_16_bits(dtype):
+def test_many_kv_heads_in_16_bits(dtype, d):
     """More than 512 kv heads are beyond the 16-bit kernel's tables."""
-    w = W.llama8b_layer(seed=2, B=1, n=40, H_q=1026, H_kv=513, T=3, d=64, dtype=dtype)
+    w = W.llama8b_layer(seed=2, B=1, n=40, H_q=1026, H_kv=513, T=3, d=d, dtype=dtype)
     mask = oracle.topp_select(w.probs.reshape(-1, w.n), w.top_p).mask().reshape(w.B, w.H_kv, w.n)
     q, k, v = kv_tensors(w)
     out, _ = gpu_attention(q, k, v, *lists(mask, w.n))
