@@ -492,19 +492,10 @@ template <int N, int I = 0, typename F> __device__ __forceinline__ void static_f
     }
 }
 
-// One step of merging partial (m, l, o) triples that share the log2-unit convention.
+// A row's partials (m, l, o) as they are joined, m in log2 units.
 struct Merge {
     float m = -INFINITY, l = 0.0f, o = 0.0f;
-    __device__ __forceinline__ void add(float mw, float lw, float ow)
-    {
-        const float mn = fmaxf(m, mw);
-        const float fa = (m == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(m - mn);
-        const float fb = (mw == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(mw - mn);
-        l = l * fa + lw * fb;
-        o = o * fa + ow * fb;
-        m = mn;
-    }
-    // N at once: their largest first, then weights that wait for nothing else, and sums in two chains.
+    // N of them: their largest first, then weights that wait for nothing else, and sums in two chains.
     template <int N> __device__ __forceinline__ void add_all(const float (&mw)[N], const float (&lw)[N], const float (&ow)[N])
     {
         float top[N];
