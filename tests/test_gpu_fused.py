@@ -134,29 +134,53 @@ def test_sparse_rows_whose_tiles_span_many_mask_words():
     assert np.abs(lse - l).max() <= 2e-3
 
 
-@pytest.mark.parametrize("B,H_q,H_kv,T,n", [(1, 8, 2, 5, 40000), (3, 24, 2, 4, 9001), (18, 8, 4, 3, 2500)])
-def test_positions_of_any_density_come_out_of_the_mask(B, H_q, H_kv, T, n):
-    """Rows of every density - all positions, all but a few, words full and words empty in turns, one in 4 to one in 3000 - against the
-    same attention over lists: two query tiles, three, and more rows than a wave scans by itself."""
-    rng = np.random.default_rng(n)
-    R, nblk = B * H_kv, -(-n // sa.SEL_BLOCK)
-    kept = np.zeros((R, nblk * sa.SEL_BLOCK), dtype=np.uint8)
+def _rows_of_every_density(rng, R, n, first):
+    """Kept rows [R, n], row r of kind (first + r) % 8: all positions, all but a few, words full and words empty in turns, one in 4, one in 50,
+    one in 300, the ends of the blocks, six in ten; one of the last two positions is always kept."""
+    kept = np.zeros((R, n), dtype=bool)
     pos = np.arange(n)
     for r in range(R):
-        kind = r % 8
-        row = [rng.random(n) < 2.0, rng.random(n) < 0.998, (pos >> 5) % 3 == 0, rng.random(n) < 0.25, rng.random(n) < 0.02,
-               rng.random(n) < 1 / 300, (pos % 1024 >= 900) | (pos > n - 7), rng.random(n) < 0.6][kind]
-        kept[r, :n] = row
-        kept[r, n - 1 - r % 2] = 1
+        kind = (first + r) % 8
+        if kind == 2:
+            kept[r] = (pos >> 5) % 3 == 0
+        elif kind == 6:
+            kept[r] = (pos % 1024 >= 900) | (pos > n - 7)
+        else:
+            kept[r] = rng.random(n) < (2.0, 0.998, 0.0, 0.25, 0.02, 1 / 300, 0.0, 0.6)[kind]
+        kept[r, n - 1 - r % 2] = True
+    return kept
+
+
+def _sparse_rows(rng, R, n, densities):
+    """Kept rows [R, n], a part densities[r % len] of row r's positions at random; row 1 keeps none in its middle half."""
+    kept = np.stack([rng.random(n) < densities[r % len(densities)] for r in range(R)])
+    kept[1, n // 4:3 * n // 4] = False
+    return kept
+
+
+def _check_mask_against_lists(kept, B, H_q, H_kv, T, shared_pool=False):
+    """The fused call over a given selection state against the attention over the same positions as lists.  shared_pool: all sequences
+    read the same pages, each in an order of its own."""
+    R, n = kept.shape
+    nblk = -(-n // sa.SEL_BLOCK)
     counts = kept.sum(axis=1).astype(np.int32)
     idx = np.zeros((R, n), dtype=np.int32)
     for r in range(R):
         idx[r, :counts[r]] = np.flatnonzero(kept[r])
-    bc = dev(kept.reshape(R, nblk, -1).sum(axis=2).astype(np.int32))
-    km, d_idx = dev(np.packbits(kept, axis=1, bitorder="little").view(np.int32)), dev(idx)
+    padded = np.zeros((R, nblk * sa.SEL_BLOCK), dtype=np.uint8)
+    padded[:, :n] = kept
+    bc = dev(padded.reshape(R, nblk, -1).sum(axis=2).astype(np.int32))
+    km, d_idx = dev(np.packbits(padded, axis=1, bitorder="little").view(np.int32)), dev(idx)
     gen = torch.Generator(device="cuda").manual_seed(n)
     draw = lambda *shape: torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
-    q, k, v = draw(B, H_q, T, 128), draw(B, H_kv, n, 128), draw(B, H_kv, n, 128)
+    q, kw = draw(B, H_q, T, 128), {}
+    if shared_pool:
+        pages = -(-n // W.PAGE_SIZE)
+        order = np.stack([np.random.default_rng(b).permutation(pages) for b in range(B)]).astype(np.int32)
+        kw = dict(page_table=dev(order), page_size=W.PAGE_SIZE, n_max=n)
+        k, v = draw(pages, H_kv, W.PAGE_SIZE, 128), draw(pages, H_kv, W.PAGE_SIZE, 128)
+    else:
+        k, v = draw(B, H_kv, n, 128), draw(B, H_kv, n, 128)
     outs = []
     for fused in (False, True):
         out = torch.full((B, H_q, T, 128), float("nan"), device="cuda")
@@ -165,9 +189,9 @@ def test_positions_of_any_density_come_out_of_the_mask(B, H_q, H_kv, T, n):
             probs = torch.full((B, H_kv, n), 1.0 / n, device="cuda")
             tau = torch.zeros(R, device="cuda")
             sel = sa.select_args(probs, 0.9, indices=None, counts=d_counts, thresholds=tau, block_counts=bc, kept_mask=km, reuse_selection=True)
-            att = sa.attn_args(q, k, v, out=out)
+            att = sa.attn_args(q, k, v, out=out, **kw)
         else:
-            sel, att = None, sa.attn_args(q, k, v, out=out, indices=d_idx, counts=d_counts)
+            sel, att = None, sa.attn_args(q, k, v, out=out, indices=d_idx, counts=d_counts, **kw)
         ws = sa.alloc_workspace(sa.specattn_workspace_size(sel, att))
         att.workspace, att.workspace_bytes = ws.data_ptr(), ws.numel()
         if fused:
@@ -178,6 +202,33 @@ def test_positions_of_any_density_come_out_of_the_mask(B, H_q, H_kv, T, n):
         outs.append(out.cpu().numpy())
     # (the same weights and products, summed in another order: fp32 sums of 16-bit weight parts, 2.4e-6 against 64 bits)
     assert row_rel_err(outs[1], outs[0]) <= 2e-5
+
+
+@pytest.mark.parametrize("B,H_q,H_kv,T,n,first", [(1, 8, 2, 5, 40000, 0), (1, 8, 2, 5, 40000, 2), (1, 8, 2, 5, 40000, 4), (1, 8, 2, 5, 40000, 6),
+                                                  (3, 24, 2, 4, 9001, 0), (18, 8, 4, 3, 2500, 0)])
+def test_positions_of_any_density_come_out_of_the_mask(B, H_q, H_kv, T, n, first):
+    """Rows of every density against the same attention over lists, a few tiles to a wave: two query tiles, three, and more rows than a wave scans by itself."""
+    rng = np.random.default_rng(n)
+    _check_mask_against_lists(_rows_of_every_density(rng, B * H_kv, n, first), B, H_q, H_kv, T)
+
+
+@pytest.mark.parametrize("B,H_q,H_kv,T,n,first,shared_pool", [(2, 8, 8, 5, 131072, 0, False), (2, 32, 8, 5, 131072, 3, False), (2, 64, 8, 6, 100001, 5, True),
+                                                              (9, 32, 8, 1, 30000, 1, False), (9, 32, 8, 5, 30000, 6, True), (11, 40, 10, 8, 20011, 4, True), (11, 60, 10, 8, 20011, 7, False)])
+def test_waves_that_take_many_tiles_from_the_mask(B, H_q, H_kv, T, n, first, shared_pool):
+    """8 and more tiles of a row to a wave, so that its buffer of positions is filled again and again inside the tile loop and what is left in it moves to the front;
+    rows of up to 128 blocks (two rounds of the search for a wave's first one); up to 64 rows and more, one to three query tiles."""
+    rng = np.random.default_rng(n + first)
+    _check_mask_against_lists(_rows_of_every_density(rng, B * H_kv, n, first), B, H_q, H_kv, T, shared_pool)
+
+
+@pytest.mark.parametrize("B,H_kv,G,T,densities", [(8, 8, 4, 5, (1 / 40, 1 / 50, 1 / 70, 1 / 100)), (8, 8, 1, 3, (1 / 50, 1 / 66, 1 / 80, 1 / 60)), (8, 8, 8, 5, (1 / 70,)),
+                                                  (24, 4, 4, 5, (1 / 100,)), (24, 4, 2, 5, (1 / 60, 1 / 300, 1 / 90)), (24, 4, 8, 5, (1 / 80,)), (96, 4, 4, 4, (1 / 300,))])
+def test_waves_that_take_sparse_tiles_from_the_mask(B, H_kv, G, T, densities):
+    """Three and more tiles to a wave whose positions span more than the 64 words fetched ahead, so that a tile's positions are completed from memory
+    inside the tile loop; rows of 256 blocks, a pool shared by all sequences."""
+    n = 262144
+    rng = np.random.default_rng(B + G)
+    _check_mask_against_lists(_sparse_rows(rng, B * H_kv, n, densities), B, G * H_kv, H_kv, T, shared_pool=True)
 
 
 @pytest.mark.parametrize("B", [80, 200])
