@@ -56,6 +56,22 @@ def test_ragged_lengths_partial_chunks_and_invalid_rows():
     assert got["flags"][1] & sa.ROW_INVALID and got["flags"][2] & sa.ROW_INVALID
 
 
+@pytest.mark.parametrize("B,H,n,chunk", [(64, 17, 3000, 16), (64, 17, 20003, 16), (60, 18, 9001, 4)])
+def test_more_ragged_rows_than_fit_the_chip(B, H, n, chunk):
+    """Chunk sums of rows that the workgroups take from the longest sequence down (every thread count; lengths that are no whole chunks, one
+    length, an empty row)."""
+    rng = np.random.default_rng(B * n)
+    lens = rng.integers(0, n + 1, size=B).astype(np.int32)
+    lens[: B // 3] = lens[0]
+    lens[-1], lens[B // 3] = 0, n
+    probs = W.draft_probs(rng, 8, n)[rng.integers(0, 8, size=B * H)].reshape(B, H, n)
+    probs *= np.exp2(rng.integers(-3, 4, size=(B, H, 1))).astype(np.float32)     # (no two rows alike)
+    got = gpu_select_chunks(probs, 0.9, chunk, seq_lens=lens)
+    ref = oracle.topp_select_chunks(probs.reshape(B * H, n), 0.9, chunk, lens=np.repeat(lens, H))
+    flagged, _ = compare_select(got, ref)
+    assert flagged < B * H // 2
+
+
 @pytest.mark.parametrize("paged", [False, True])
 def test_attention_over_chunk_lists(paged):
     if paged:

@@ -490,10 +490,8 @@ def test_rows_that_keep_everything(rows, n):
                 assert np.array_equal(got["indices"][r, :want.size], want) and (got["indices"][r, want.size:] == -7).all()
 
 
-@pytest.mark.parametrize("B,H,n", [(64, 17, 300), (63, 17, 1000), (2, 600, 1500), (37, 8, 33000), (64, 9, 18000), (65, 9, 18000)])
-def test_more_rows_of_different_lengths_than_fit_the_chip(B, H, n):
-    """Workgroups take up to 64 sequences from the longest down (every thread count; equal lengths, lengths of one level and empty rows
-    among them); beyond 64 in the order of the batch."""
+def _ragged_batch(B, H, n):
+    """Rows of B sequences and their lengths: equal ones, some of one level and an empty one among them."""
     rng = np.random.default_rng(B * n)
     lens = rng.integers(0, n + 1, size=B).astype(np.int32)
     lens[: B // 3] = lens[0]                                 # one length
@@ -501,4 +499,37 @@ def test_more_rows_of_different_lengths_than_fit_the_chip(B, H, n):
     lens[-1], lens[B // 3] = 0, n
     probs = W.draft_probs(rng, 8, n, recency_len=min(64, n))[rng.integers(0, 8, size=B * H)].reshape(B, H, n)
     probs *= np.exp2(rng.integers(-3, 4, size=(B, H, 1))).astype(np.float32)     # (no two rows alike)
+    return probs, lens
+
+
+@pytest.mark.parametrize("B,H,n", [(64, 17, 300), (63, 17, 1000), (2, 600, 1500), (37, 8, 33000), (64, 9, 18000), (65, 9, 18000)])
+def test_more_rows_of_different_lengths_than_fit_the_chip(B, H, n):
+    """Workgroups take up to 64 sequences from the longest down (every thread count; equal lengths, lengths of one level and empty rows
+    among them); beyond 64 in the order of the batch."""
+    probs, lens = _ragged_batch(B, H, n)
     _check(probs, 0.9, allow_flagged_mismatch=True, seq_lens=lens)
+
+
+@pytest.mark.parametrize("B,H,n", [(64, 17, 1000), (37, 8, 33000), (64, 9, 18000), (64, 9, 3000)])
+def test_pool_slots_and_state_of_rows_taken_by_length(B, H, n):
+    """The same order where the lists hold pool slots, and where the kept mask and the block counts take their place."""
+    probs, lens = _ragged_batch(B, H, n)
+    R, page, nblk = B * H, 16, -(-n // sa.SEL_BLOCK)
+    ref = oracle.topp_select(probs.reshape(R, n), 0.9, np.repeat(lens, H))
+    table = np.random.default_rng(n).permutation(B * -(-n // page)).astype(np.int32).reshape(B, -1)
+    got = gpu_select(probs, 0.9, seq_lens=lens, page_table=table, page_size=page, emit_physical=True, split=False)
+    compare_select(got, ref, to_physical=lambda r, pos: table[r // H, pos // page] * page + pos % page)
+
+    counts, tau = torch.full((R,), -7, dtype=torch.int32, device="cuda"), torch.full((R,), -7.0, device="cuda")
+    bc, km = (torch.full((R, m), -1, dtype=torch.int32, device="cuda") for m in (nblk, nblk * sa.SEL_BLOCK // 32))
+    sa.specattn_topp_select(sa.select_args(dev(probs), 0.9, indices=None, counts=counts, thresholds=tau, seq_lens=dev(lens), block_counts=bc, kept_mask=km))
+    torch.cuda.synchronize()
+    want = np.zeros((R, nblk * sa.SEL_BLOCK), dtype=np.uint8)
+    want[:, :n] = ref.mask().reshape(R, n)
+    sure = (ref.flags & oracle.ROW_NEAR_BOUNDARY) == 0
+    assert sure.sum() > R // 2
+    assert np.array_equal(counts.cpu().numpy()[sure], ref.counts[sure])
+    valid = sure & ((ref.flags & oracle.ROW_INVALID) == 0)
+    assert np.array_equal(tau.cpu().numpy()[valid], ref.tau[valid])
+    assert np.array_equal(np.unpackbits(km.cpu().numpy().view(np.uint8), axis=1, bitorder="little")[sure], want[sure])
+    assert np.array_equal(bc.cpu().numpy()[sure], want.reshape(R, nblk, -1).sum(axis=2)[sure])
