@@ -23,11 +23,11 @@ __device__ __forceinline__ float wave_sum(float v)
     return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), 63));
 }
 
-// What the merge needs of a launch only in the end; with the new tokens, also what those need.  What its first requests need are the leading arguments, scalars
-// of 14 words in all: those come in registers with the launch (the build asks for it), without a trip to memory.  All arguments from memory in
-// one batch / so, us, with what goes before: 64 rows of 13001 positions (40 query rows each) 45.15 / 44.55, 8 of 8192 19.3 / 19.1, 32 of 2044 in chunks with new tokens
-// 17.8 / 17.7, 16 layers of 64 rows of 32768 776.5 / 772.8.  (The main kernel's arguments the same way, with the counts requested ahead of the rest:
-// 8 rows of 8192 19.5 / 19.8, 16 layers 778 / 784.)
+// What the merge needs of a launch only in the end; with the new tokens, also what those need.  What its first requests need are the
+// leading arguments, scalars of 14 words in all: those come in registers with the launch (the build asks for it), without a trip to memory.
+// All arguments from memory in one batch / so, us, with what goes before: 8 rows of 8192 19.3 / 19.1, 64 of 13001 (40 query rows each)
+// 45.2 / 44.6, 16 layers of 64 rows of 32768 776.5 / 772.8.  (The main kernel's arguments the same way, with the counts requested ahead of
+// the rest: 8 rows of 8192 19.5 / 19.8, 16 layers 778 / 784.)
 struct MergeArgs {
     float *out, *lse;
     void *out_lowp;
@@ -41,21 +41,14 @@ struct MergeArgs {
 // their partials (r, w) combined; rows without any kept position get out = 0, lse = -inf.  When the
 // caller gave the new tokens behind the cache (TAIL), every row goes through here (the main kernel then
 // leaves partials only) and query t also attends to new tokens 0..t.
-// Bound by latency: the arguments, the row's shares, then a trip to memory and two chains of sums per sixteen partials.  Head dimension and
-// element type are constants, the grid and the plan leave no division, and every load of a trip is requested before the first partial is used; a short
-// rest asks for two, five or eight, since sixteen are a chain too long there (rows of 9 to 16 parts in two trips of eight / one: 8 rows of 8192 19.2 / 19.0 us).  What the new tokens need is requested ahead of the shares, in one go.
-// (With the element type tested at every one of those loads, each waited for the one before; with all arguments of the launch, fetched in three
-// turns; and with the partials joined one after the other - as it was / now, us,
-// with selection and attention: 32 rows of 2044 positions in chunks with new tokens 20.0 / 17.7, 8 rows of 8192 19.6 / 19.0, 16 of 8192 (d = 64) 19.2 / 18.7; 64
-// dense rows of up to 32768 with new tokens 111.7 / 108.6.)
-// A pass of selection, attention and merge with every divisor and share worked out here from the cost line / with them handed over, us:
-// 32 rows of 2044 positions in chunks with new tokens 24.6 / 21.9, 32 rows of 8192 (d = 64) 22.6 / 21.2, 16 layers of 64 rows of 32768
-// 867 / 839 (the start of the main kernel, below, among it).
+// Bound by latency: the row's shares, then a trip to memory and two chains of sums per sixteen partials.  Head dimension and element type
+// are constants, the host hands divisors over as reciprocals, and every load of a trip is requested before the first partial is used; a
+// short rest asks for two, five or eight, since sixteen are a chain too long there (rows of 9 to 16 parts in two trips of eight / one: 8
+// rows of 8192 19.2 / 19.0 us).  What the new tokens need is requested ahead of the shares, in one go (with the element type tested at each
+// of those loads, one waited for the other, and partials joined one by one: 32 rows of 2044 in chunks with new tokens 20.0 / 17.7).
 // A partial's (m, l) is the same for all threads, so the compiler takes scalar loads for it: eight of them, which come back in any order
-// and are waited for together, cost 0.12 us more per trip than vector loads that are asked for ahead of the outputs (for the short rest it
-// makes no difference, and 16 layers of 64 rows take 797.6 us with scalar loads there, 798.8 without).  Scalar / vector, us for both launches:
-// one row of 270 tiles among 31 empty ones (268 partials) 31.3 / 27.2, one of 500 among 31 of 3 (131 partials) 21.8 / 19.6, 8 ragged
-// rows of up to 270 13.6 / 13.3; over 440 calls of few rows 4 % on average, none slower.
+// and are waited for together, cost 0.12 us more per trip than vector loads that are asked for ahead of the outputs (one row of 270 tiles
+// among 31 empty ones, 268 partials, 31.3 / 27.2 us; over 440 calls of few rows 4 % on average, none slower).
 template <int D, bool F16, bool TAIL>
 __global__ __launch_bounds__(D) void merge_partials_kernel(const uint32_t *row_parts, const float *part_ml, const float *part_o, uint32_t per_h, uint32_t per_t, int H_q,
                                                            int H_kv, int T, int heads, int g_first, int qtp, MergeArgs a)
@@ -95,7 +88,7 @@ __global__ __launch_bounds__(D) void merge_partials_kernel(const uint32_t *row_p
 #pragma unroll
             for (int k = 0; k < N; ++k) {           // (behind the last share: that one's again)
                 s[k] = (uint32_t)((min(wb + k, w1) + r) * qtp + q);
-                if (N >= 8) asm("" : "+v"(s[k]));   // (the same in all lanes, but no scalar loads: above)
+                if (N >= 8) asm("" : "+v"(s[k]));   // (the same in all lanes, but no scalar loads: above; the short rest does not care)
                 const float2 ml = reinterpret_cast<const float2 *>(part_ml)[s[k]];
                 mw[k] = ml.x;
                 lw[k] = ml.y;
@@ -231,17 +224,22 @@ size_t attn_mfma_workspace_min_bytes(int rows, int G, int T, int d)
     return workspace_for(rows < MAX_ROWS ? rows : MAX_ROWS, query_tiles(G, T, NARROW), d);
 }
 
-// Calls of up to 64 rows with few tiles in all: every share is `unit` tiles (3, 4, 6, 8, 12, ... 32) of one row, so that no workgroup starts twice or
-// holds a row's start alone, and a call's time is that of one share.  How many shares: fewer tiles in each are fewer to wait for, and
-// spread a call's bytes over more CUs; but from about 48 parts of a row on the merge, eight parts to a trip to memory, costs more than that saves, and
-// with nearly all CUs taken the last shares come late.  So the least unit that leaves 218 of 256 workgroups a share (fewer where rounding
-// rows up could take the others) and a row 48 parts; three tiles where that is one tile per wave and few partials.  Longer ones, whose shares are many rounds of tiles, are cut from the line with its equal shares.
-// The line, cut into 64, 128 or 256 shares / units of 4 / 6 / 8 / 12 / 16 / 24 tiles, us for both launches, rows x tiles:
-//   8 x 25 10.3 / 9.6 / 10.6 / 11.4;  8 x 48 11.4 / 10.5 / 11.2 / 11.5;  8 x 154 14.7 / - / 14.0 / 14.1 / 13.8 / 14.5;  8 x 457 20.2 / - / - / - / - / 19.8 / 19.5
-//   16 x 60 13.4 / 13.3 / 13.0 / 13.1 / 13.2;  16 x 115 15.3 / - / - / 15.3 / 14.6 / 14.8;  32 x 56 14.8 / - / - / 14.5 / 14.1 / 14.8;  32 x 108 18.3 / - / - / - / - / 17.9 / 18.5
-//   64 x 9 11.6 / 10.7 / 11.2 / 11.8;  64 x 19 13.5 / - / 12.8 / 13.3 / 13.3;  64 x 37 15.9 / - / - / - / 15.1 / 15.6 / 17.5;  64 x 61 19.4 / - / - / - / - / - / 19.6
-//   (units of 3 / 4) 8 x 9 9.0 / 9.2, 1 x 14 8.3 / 8.5, 4 x 16 (d = 64) 10.3 / 10.7, but 8 x 25 9.7 / 9.6, 64 x 9 11.0 / 10.7
-//   1 x 99 11.0 / 9.3 / 9.5 / 9.5 / 9.9;  1 x 573 14.3 / 17.5 / 15.2 / 14.4 / 13.9 / 14.2 / 15.6;  4 x 128 (d = 64) 14.9 / 12.9 / 13.5 / 13.8 / 15.0
+// Calls of up to 64 rows with few tiles in all: every share is `unit` tiles (3, 4, 6, 8, 12, ... 32) of one row, so that no workgroup
+// starts twice or holds a row's start alone, and a call's time is that of one share.  How many shares: fewer tiles in each are fewer to
+// wait for, and spread a call's bytes over more CUs; but every sixteen parts of a row are one more trip of the merge, which from about 48
+// on costs more than that saves, and with nearly all CUs taken the last shares come late.  So the least unit that leaves 218 of 256
+// workgroups a share (fewer where rounding rows up could take the others) and a row 48 parts; three tiles where that is one tile per wave
+// and few partials.  Longer ones, whose shares are many rounds of tiles, are cut from the line.
+// Measured, rows x tiles (d = 128, 20 query rows): the line / units, the rule's in brackets, us for both launches:
+//   1 x 50 10.4 / [3] 8.9, 4 8.8, 8 9.6;  1 x 200 18.0 / 4 11.0, [6] 11.2, 12 11.9;  1 x 573 21.6 / 8 14.4, [12] 13.5, 16 14.4
+//   4 x 24 9.3 / [3] 8.45, 4 8.5;  4 x 150 12.6 / 3 12.2, [4] 11.5, 8 12.0;  4 x 500 16.2 / 8 16.1, [12] 15.0, 16 15.0;  4 x 1500 24.9 / 28 24.7, [32] 24.0
+//   8 x 25 9.9 / 3 9.3, [4] 9.0, 6 9.9;  8 x 87 11.2 / 3 11.3, [4] 10.9, 6 11.0, 8 11.6;  8 x 154 12.5 / [6] 12.4, 8 12.7;  8 x 300 15.2 / [12] 14.8, 16 15.0;
+//   8 x 457 19.0 / 16 18.5, [20] 17.7, 24 18.4;  8 x 640 22.2 / 20 21.4, [24] 21.2, 28 21.0
+//   32 x 28 11.1 / 4 10.7, [6] 11.1, 8 11.7;  32 x 56 13.4 / 8 13.2, [12] 13.0;  32 x 160 21.2 / 20 20.9, [24] 20.5
+//   64 x 9 10.5 / 3 10.0, [4] 10.2;  64 x 19 12.4 / 6 12.0, [8] 12.3, 12 12.3;  64 x 37 14.3 / 12 14.1, [16] 14.7;  64 x 48 15.8 / 12 15.6, [16] 15.7
+//   d = 64: 4 x 128 11.8 / 3 11.0, [4] 10.4, 6 11.4;  64 x 25 13.2 / 8 12.8, [12] 13.2;  64 x 45 15.6 / 12 15.0, [16] 15.8
+// Rows alone or in twos with more than 900 tiles would do with more than 48 parts: 1 x 1200 22.8 / 12 16.8, 16 16.4, [28] 18.3;
+// 1 x 1530 23.5 / 16 17.4, 24 18.1, [32] 19.6; 2 x 1530 20.7 / 20 19.1, [32] 20.7.  (64 parts for all of them: 2 x 450 13.6 / 14.2.)
 static void share_units(Plan &plan, int rows)
 {
     const int goal = std::min({plan.n_wg * 218 / 256, plan.n_wg - rows, 48 * rows});

@@ -3,12 +3,14 @@
 // matrix-core variant.
 //
 // Work split ("stream-K" over kept positions): the kept positions of all rows, in tiles of 8 KiB of keys
-// (32 positions of 128, 64 positions of 64), form one line; the line is cut into equal shares, one per workgroup (one workgroup of eight waves
-// per CU), so the split is balanced by the *kept* count whatever the per-row counts are.  A fixed
+// (32 positions of 128, 64 positions of 64), form one line; the line is cut into one share per workgroup (one workgroup of eight waves
+// per CU), so the split is balanced by the *kept* count whatever the per-row counts are: equal shares, long ones a few per cent
+// larger on even XCDs (make_share), or, in calls of up to 64 rows with few tiles, a few tiles of one row each (share_units).  A fixed
 // permutation of the workgroup numbers puts the owners of consecutive shares on different XCDs.  A share
 // that crosses row boundaries yields one partial (m, l, o) per (row, workgroup); partial (r, w) lives in
 // slot w + r.  merge_partials_kernel combines a row's partials, in workgroup order.  Inside a share tile k goes
-// to wave k mod 8, so every sum is taken in a fixed order and the outputs are bit-identical from run to run.
+// to wave k mod 8, over the mask wave w takes the w-th eighth of the tiles, so every sum is taken in a fixed order and the outputs are
+// bit-identical from run to run.
 // Measured and dropped: waves claiming the tiles of a share from an LDS counter as their data arrives (no
 // faster on any workload, 1.3 us slower on the 32K layer, and it gives the fixed summation order up); tiles of
 // a row claimed by all of its workgroups from a counter in memory (a device-scope atomic takes about as long
@@ -432,23 +434,27 @@ __host__ __device__ __forceinline__ int floor_div(int64_t a, int b)
     return (int)floor((double)a / (double)b);
 }
 
-// The first n = min(n_wg, total) workgroups share the line: workgroup w takes [w * total / n, (w + 1) * total / n),
-// so shares differ by at most one unit and none of them is empty (every workgroup between the first and the
-// last of a row therefore holds tiles of that row, which the merge relies on).
-// Long shares are tilted (TILT_FROM): the XCDs of odd number stream more slowly than the others while all of them read.  With
-// equal shares their workgroups end 4 to 7 % later, in every launch (the rest of the spread has no fixed place; a plain read of 1 GiB in
-// equal parts: even XCDs 132 us, odd ones 150).  So the shares of even XCDs are TILT / 128 larger than the mean, those of odd ones as much
-// smaller: of the four shares of a team (share_index) two are of either kind, so boundaries 2 k stay where they are and the others move by
-// TILT / 128 of a share.  TILT 0 / 4 / 6 / 8 / 12, us: 16 layers of 64 rows of 32768 with their selection 799 / 787 / 786 / 789 / 798
-// (mask source 834 / 817 / 817 / 821 / 833), 512 ragged rows 575 / 569 / 571 / 574 / 580, dense rows of up to 32768 109.6 / 108.4 / 108.2 / 108.1 /
-// 110.0, 64 rows of 13001 45.9 / 45.6 / 45.2 / 45.3 / 45.7.
+// The first n = min(n_wg, total) workgroups share the line.  Equal shares: workgroup w takes [w * total / n, (w + 1) * total / n), which
+// differ by one unit at most.  None is empty, tilted ones neither (every workgroup between the first and the last of a row therefore holds
+// tiles of that row, which the merge relies on).
+// Long shares are tilted (TILT_FROM): while all XCDs read, those of odd number mostly stream more slowly, and with equal shares their
+// workgroups end 4 to 7 % later (the rest of the spread has no fixed place; a plain read of 1 GiB in equal parts: even XCDs 132 us, odd
+// ones 150).  So the shares of even XCDs are TILT / 128 larger than the mean, those of odd ones as much smaller: of the four shares of a
+// team (share_index) two are of either kind, so boundaries 2 k stay where they are and the others move by TILT / 128 of a share.
+// TILT 0 / 4 / 6 / 8 / 12, us: 16 layers of 64 rows of 32768 with their selection 799 / 787 / 786 / 789 / 798 (mask source 834 / 817 / 817 /
+// 821 / 833), dense rows of up to 32768 109.6 / 108.4 / 108.2 / 108.1 / 110.0.  TILT 0 / 5 / -5: 16 layers 786 / 772 / 788, 512 ragged rows
+// 512 / 508 / 520.  It does not help every call: over 40 of one layer (32 to 320 rows, 38 to 122 units a share) it gives 0.6 % on average,
+// from 2.7 faster to 1.6 slower, the slower ones 128 rows with shares of 50 units and 256 rows with 65 to 80; rows of random
+// positions have taken up to 2.5 % longer.
 constexpr int TILT = 5;
-// Lines whose shares are tilted: of TILT_FROM units a share or more (the mean of TILT 4 and 6 against equal shares, us: 64 rows of 27 units a
-// share 24.6 / 24.7, of 33 28.6 / 28.6, of 38 32.0 / 31.7, of 62 46.8 / 46.1, of 97 67.8 / 67.6; 16 rows of 40 34.7 / 34.8, of 59 47.4 / 46.8).  Not where rows
-// are so many that equal counts make every share whole rows: there a moved boundary costs a partial (256 rows of 2000 positions 48.3 / 51.2).
+// Lines whose shares are tilted: of TILT_FROM units a share or more (the mean of TILT 4 and 6 against equal shares, us: 64 rows of 27
+// units a share 24.6 / 24.7, of 33 28.6 / 28.6, of 38 32.0 / 31.7, of 62 46.8 / 46.1, of 97 67.8 / 67.6).  Not where rows are so many that
+// equal counts make every share whole rows: there a moved boundary costs a partial (256 rows of 30 tiles 30.4 / 33.6, of 60 48.8 / 52.7,
+// 512 of 60 91.4 / 95.3).  Whole shares make the line a multiple of their number, and that is what is tested: it keeps the shares of
+// other lines of that length equal too, one in 256 of those of uneven rows, which costs them what the tilt gives.
 constexpr int TILT_FROM = 32;
-// ... and only with the workgroups of a whole GPU, 32 on each of eight XCDs: on a partition of it a share's parity says nothing about an XCD that is
-// known to be slower (with one XCD all shares are on the same one), and the shares stay equal.
+// ... and only with the workgroups of a whole GPU, 32 on each of eight XCDs: on a partition of it a share's parity says nothing about an
+// XCD that is known to be slower (with one XCD all shares are on the same one), and the shares stay equal.
 constexpr int TILT_WORKGROUPS = 256;
 template <int TILE> __host__ __device__ __forceinline__ Share<TILE> make_share(int total, int n_wg, int rows, int w)
 {
