@@ -193,6 +193,11 @@ __global__ __launch_bounds__(GEN_THREADS, 1) void attn_f32_kernel(AttnLaunch a, 
         const int e = k * GEN_THREADS + tid, qi = e / (D / 4), ch = e - qi * (D / 4);
         if (e < NQT * 16 * (D / 4)) *reinterpret_cast<f32x4 *>(Qs + qi * L::ROW + 4 * ch) = qv[k];
     }
+    // Q and the list words have arrived, also for threads without a part of Q.  The compiler only sees that those have not waited, takes the
+    // registers that the first keys share with Q for still on their way, and waits for the values as well ahead of every tile's scores.
+    // (Without / with, us: 8 query rows and more of d = 64 in the form for all calls, 64 dense rows of 2000 29.3 / 27.0, 128 rows of 2000 in chunks
+    // 14.7 / 13.4, with new tokens 16.6 / 15.0.)
+    __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
     __syncthreads();                      // (ahead of the loads of keys and values: all waves' start together)
     if (t < t_end) {
         load_k(off);
