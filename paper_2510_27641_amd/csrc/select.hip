@@ -509,9 +509,16 @@ template <int THREADS, int NV4, bool CHUNKED = false> specattn_status launch_one
     SelectLaunch a = asked;
     a.per_h = FastDivisor(a.H_kv);
     // Rows of different lengths that come in turns: the longest first, so that no long one starts when the others are done.  Not where all
-    // workgroups are on the chip at once (16 waves to a CU), and up to 64 sequences, which the lanes of a wave compare.  In the order of the batch / from the
-    // longest down, us: 64 sequences x 8 heads of up to 65536 49.7 / 44.0, 48 x 8 44.9 / 36.4, 40 x 8 of up to 40000 30.7 / 27.9.
-    if (a.seq_lens && a.B > 1 && a.B <= 64 && a.B * a.H_kv > 1024 / THREADS * cu_count()) {
+    // workgroups are on the chip at once (16 waves to a CU) nor for more than three turns, over which lengths even out and long rows
+    // side by side only wait for the same things, nor for short rows, to which a workgroup's search for its sequence is 0.5 to 1 us more
+    // (chunk sums take a quarter of the time of as many entries); and up to 64 sequences, which the lanes of a wave compare.  In the order
+    // of the batch / from the longest down, us, sequences x heads of a sixteenth to the whole length: 64 x 8 of 65536 44.9 / 38.8, 48 x 8
+    // 42.0 / 32.5, 64 x 12 60.7 / 57.0; 40 x 8 of 40000 29.5 / 26.8; 64 x 13 of 32768 35.1 / 32.2, 64 x 24 49.7 / 48.0; 64 x 20 of 14000
+    // 24.7 / 23.6; but 64 x 17 of 65536 (4.25 turns) 82.5 / 88.5, 64 x 32 of 40000 (8) 116.6 / 121.3, of 32768 (4) 62.6 / 62.7, 64 x 17 of 8000
+    // 15.2 / 16.0, of 1000 7.4 / 8.5.  In chunks of 16: 64 x 32 of 65536 58.8 / 56.5, but 64 x 24 of 33000 28.8 / 31.3.  Rows of nearly
+    // one length lose 1 to 5 %.
+    const int rows = a.B * a.H_kv, turn = 1024 / THREADS * cu_count();
+    if (a.seq_lens && a.B > 1 && a.B <= 64 && rows > turn && rows <= 3 * turn && (CHUNKED ? a.n_tokens / 4 : a.n_max) > 12288) {
         a.by_length = 1;
         while (a.n_tokens >> (a.by_length - 1) > 255) ++a.by_length;
     }

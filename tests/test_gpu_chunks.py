@@ -56,10 +56,10 @@ def test_ragged_lengths_partial_chunks_and_invalid_rows():
     assert got["flags"][1] & sa.ROW_INVALID and got["flags"][2] & sa.ROW_INVALID
 
 
-@pytest.mark.parametrize("B,H,n,chunk", [(64, 17, 3000, 16), (64, 17, 20003, 16), (60, 18, 9001, 4)])
+@pytest.mark.parametrize("B,H,n,chunk", [(64, 17, 3000, 16), (64, 17, 20003, 16), (60, 18, 9001, 4), (64, 17, 49153, 16), (64, 17, 60001, 64)])
 def test_more_ragged_rows_than_fit_the_chip(B, H, n, chunk):
-    """Chunk sums of rows that the workgroups take from the longest sequence down (every thread count; lengths that are no whole chunks, one
-    length, an empty row)."""
+    """Chunk sums of rows that the workgroups take in turns, in the order of the batch and, long ones, from the longest sequence down
+    (lengths that are no whole chunks, one length, an empty row)."""
     rng = np.random.default_rng(B * n)
     lens = rng.integers(0, n + 1, size=B).astype(np.int32)
     lens[: B // 3] = lens[0]

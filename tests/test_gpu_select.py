@@ -502,15 +502,16 @@ def _ragged_batch(B, H, n):
     return probs, lens
 
 
-@pytest.mark.parametrize("B,H,n", [(64, 17, 300), (63, 17, 1000), (2, 600, 1500), (37, 8, 33000), (64, 9, 18000), (65, 9, 18000)])
+@pytest.mark.parametrize("B,H,n", [(64, 17, 300), (63, 17, 1000), (2, 600, 1500), (37, 8, 33000), (64, 9, 18000), (65, 9, 18000),
+                                   (64, 17, 12288), (64, 17, 12289), (64, 12, 33000), (64, 13, 33000)])
 def test_more_rows_of_different_lengths_than_fit_the_chip(B, H, n):
-    """Workgroups take up to 64 sequences from the longest down (every thread count; equal lengths, lengths of one level and empty rows
-    among them); beyond 64 in the order of the batch."""
+    """Workgroups take up to 64 sequences of long rows from the longest down where they come in up to three turns (every thread count; equal
+    lengths, lengths of one level and empty rows among them), others in the order of the batch: both sides of each line."""
     probs, lens = _ragged_batch(B, H, n)
     _check(probs, 0.9, allow_flagged_mismatch=True, seq_lens=lens)
 
 
-@pytest.mark.parametrize("B,H,n", [(64, 17, 1000), (37, 8, 33000), (64, 9, 18000), (64, 9, 3000)])
+@pytest.mark.parametrize("B,H,n", [(64, 17, 1000), (37, 8, 33000), (64, 9, 18000), (64, 17, 13000)])
 def test_pool_slots_and_state_of_rows_taken_by_length(B, H, n):
     """The same order where the lists hold pool slots, and where the kept mask and the block counts take their place."""
     probs, lens = _ragged_batch(B, H, n)
