@@ -396,7 +396,8 @@ __global__ __launch_bounds__(THREADS, 4) void topp_select_kernel(SelectLaunch a)
     // 256 x 32768 16.9 / 16.3.  Up to 8192 entries the bins are the faster way: few entries, seldom another pass (8 x 8192 7.2 / 7.4,
     // 8 x 2048 5.2 / 5.5), and where rows come in turns (NV4 = 16) another row fills the wait (1024 x 32768 48.1 / 48.2).
     constexpr bool LISTS = ITEM * NV4 > 8192 && NV4 <= 8;
-    constexpr bool PAIRED = NV4 <= 8;                 // (row_of_bins)
+    // (row_of_bins; not where its registers would cost a fifth workgroup per CU: 1088 rows of 8000 12.9 / 15.1 us)
+    constexpr bool PAIRED = NV4 <= 8 && !(THREADS == 256 && NV4 == 8);
     constexpr bool FLAT = ITEM * NV4 >= 4096;         // flat rows are added up before they reach a counter
     constexpr bool WORDS = NV4 >= 8;                  // compaction by words of 32 positions instead of item by item
     constexpr int TABLE = WORDS ? ITEM / 32 * NV4 : (NV4 * NW + 63) / 64 * 64;
