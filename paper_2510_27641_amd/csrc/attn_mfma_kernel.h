@@ -447,8 +447,9 @@ __host__ __device__ __forceinline__ int floor_div(int64_t a, int b)
 // from 2.7 faster to 1.6 slower, the slower ones 128 rows with shares of 50 units and 256 rows with 65 to 80; rows of random
 // positions have taken up to 2.5 % longer.
 constexpr int TILT = 5;
-// Lines whose shares are tilted: of TILT_FROM units a share or more (the mean of TILT 4 and 6 against equal shares, us: 64 rows of 27
-// units a share 24.6 / 24.7, of 33 28.6 / 28.6, of 38 32.0 / 31.7, of 62 46.8 / 46.1, of 97 67.8 / 67.6).  Not where rows are so many that
+// Lines whose shares are tilted: of TILT_FROM tiles a share or more, as little as moved boundaries cost (equal / tilted, us: 64 rows of 120
+// tiles, 30 a share, 30.5 / 31.0, of 15 times 256 tiles in 768 rows of five 31.5 / 32.8, 128 of 60 32.9 / 33.1; 64 rows of 20011 positions, 35
+// a share, 31.0 / 30.5; the mean of TILT 4 and 6, 64 rows of 59 tiles a share 46.8 / 46.1, of 94 67.8 / 67.6).  Not where rows are so many that
 // equal counts make every share whole rows: there a moved boundary costs a partial (256 rows of 30 tiles 30.4 / 33.6, of 60 48.8 / 52.7,
 // 512 of 60 91.4 / 95.3).  Whole shares make the line a multiple of their number, and that is what is tested: it keeps the shares of
 // other lines of that length equal too, one in 256 of those of uneven rows, which costs them what the tilt gives.
@@ -461,7 +462,7 @@ template <int TILE> __host__ __device__ __forceinline__ Share<TILE> make_share(i
     // (This is on the way to a workgroup's first request: no branches, and the usual numbers of workgroups are powers of two, for which a
     // shift gives the same floor as the division.)
     int move = ((w >> 1) ^ (w >> 2)) & 1 ? -TILT : TILT;       // of boundary w or w + 1, whichever is odd
-    move = (n_wg == TILT_WORKGROUPS) & (total >= TILT_FROM * n_wg) & ((rows * 2 <= n_wg) | ((total & (n_wg - 1)) != 0)) ? move : 0;
+    move = (n_wg == TILT_WORKGROUPS) & (total - SEG_COST * rows >= TILT_FROM * n_wg) & ((rows * 2 <= n_wg) | ((total & (n_wg - 1)) != 0)) ? move : 0;
     const int64_t from = (int64_t)(w * 128 + ((w & 1) ? move : 0)) * total, to = (int64_t)(w * 128 + 128 + ((w & 1) ? 0 : move)) * total;
     Share<TILE> s;
     s.c0 = (int)(from >> (38 - __builtin_clz(n_wg)));

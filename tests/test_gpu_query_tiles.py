@@ -362,11 +362,11 @@ def test_one_long_row_among_short_ones(d, B, H_kv, others):
                                           (1, 8, 872), (1, 8, 873), (2, 4, 1308), (2, 4, 1309), (1, 8, 1745), (1, 8, 5232), (1, 8, 5233),
                                           (8, 8, 768), (8, 8, 769), (4, 16, 1152), (8, 8, 3072), (8, 8, 3073), (3, 11, 3488), (5, 13, 300),
                                           (1, 1, 1536), (1, 1, 1537), (1, 2, 3072), (1, 2, 3073), (3, 11, 3489),
-                                          (3, 11, 7807), (3, 11, 7808), (3, 11, 7809), (5, 13, 7423), (5, 13, 7424), (5, 13, 7425), (2, 4, 12000)])
+                                          (3, 11, 8203), (3, 11, 8204), (3, 11, 8205), (5, 13, 8203), (5, 13, 8204), (5, 13, 8205), (2, 4, 12000)])
 def test_shares_of_whole_tiles(B, H_kv, tiles):
     """Totals of tiles at which the shares of up to 64 rows become longer (3, 4, 6, 8, ... 32 tiles) and go over to the line's, in rows
-    of uneven lengths with an empty one among them; 65 rows; lines around 32 units to each of 256 shares (the tiles and 12 for a row
-    that has any), from which on every second boundary is moved."""
+    of uneven lengths with an empty one among them; 65 rows; lines around 32 tiles to each of 256 shares (12 less for an empty row),
+    from which on every second boundary is moved."""
     n_tiles = rng_tiles(tiles, B * H_kv)
     n = 32 * int(n_tiles.max())
     w = W.llama8b_layer(seed=tiles, B=B, n=n, H_q=2 * H_kv, H_kv=H_kv, T=2, d=128, dtype="f16")

@@ -45,10 +45,11 @@ def shares(tmp_path_factory):
 @pytest.mark.parametrize("n_wg", [32, 38, 64, 128, 256, 304])
 def test_the_line_is_shared_out_whole(shares, n_wg):
     """Shares follow each other without gaps, none is empty ahead of the line's end, every one has an owner.  They are equal but
-    for one unit, or - long ones, on a whole GPU of eight XCDs - but for the tilt, which leaves every second boundary in its place."""
+    for one unit, or - of 32 tiles and more, on a whole GPU of eight XCDs - but for the tilt, which leaves every second boundary in its place."""
     rng = np.random.default_rng(n_wg)
-    totals = [0, 1, n_wg - 1, n_wg, n_wg + 1, 32 * n_wg - 1, 32 * n_wg, 32 * n_wg + 1, 33 * n_wg + 7, 1000 * n_wg, 1000 * n_wg + 5, 2 ** 22 - 3]
-    questions = [(int(t), n_wg, rows) for t in totals + list(rng.integers(1, 400 * n_wg, size=20)) for rows in (1, 64, 128, 256, 1536)]
+    totals = [0, 1, n_wg - 1, n_wg, n_wg + 1, 1000 * n_wg, 1000 * n_wg + 5, 2 ** 22 - 3]
+    questions = [(int(t), n_wg, rows) for rows in (1, 64, 128, 256, 1536)
+                 for t in totals + [32 * n_wg + 12 * rows + k for k in (-1, 0, 1)] + list(rng.integers(1, 400 * n_wg, size=20))]
     for (total, _, rows), s in zip(questions, shares(questions)):
         begin, end, owner = s.T
         assert begin[0] == 0 and end[-1] == total and np.array_equal(begin[1:], end[:-1])
@@ -57,7 +58,7 @@ def test_the_line_is_shared_out_whole(shares, n_wg):
         assert np.array_equal(np.sort(owner), np.arange(n_wg))
         exact = np.arange(n_wg + 1) * total // n_wg if total >= n_wg else np.minimum(np.arange(n_wg + 1), total)
         bounds = np.append(begin, total)
-        tilted = n_wg == 256 and total >= 32 * n_wg and (2 * rows <= n_wg or total % n_wg != 0)
+        tilted = n_wg == 256 and total - 12 * rows >= 32 * n_wg and (2 * rows <= n_wg or total % n_wg != 0)
         assert np.array_equal(bounds[::2], exact[::2])
         assert np.array_equal(bounds, exact) != tilted
         assert np.abs(bounds - exact).max() <= (total / n_wg * 5 / 128 + 1 if tilted else 0)
