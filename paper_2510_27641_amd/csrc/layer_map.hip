@@ -279,7 +279,7 @@ template <int CTRL, int ROW_MASK> __device__ __forceinline__ void scan_step(Best
 // One thread per draft layer, up to 1024.  A column is a prefix maximum inside every wave on the vector ALU and, with more than 64
 // draft layers, one over the wave totals through LDS (double-buffered: one barrier per column).  The columns of S are
 // fetched eight at a time and ahead; back pointers stay in LDS as long as they fit.  Bound by the serial chain of n
-// columns and n back pointers.
+// columns and n back pointers.  `waves`: those of the workgroup that are here (one has nothing to wait for).
 struct AlignShared {
     double wval[2][MAP_THREADS / 64];
     int widx[2][MAP_THREADS / 64];
@@ -287,9 +287,9 @@ struct AlignShared {
     uint16_t back[MAP_LDS_BACK];
 };
 __device__ __forceinline__ void align_threads(const double *__restrict__ S, int m, int n, int32_t *__restrict__ back, int32_t *__restrict__ f,
-                              double *__restrict__ total, AlignShared &sh)
+                              double *__restrict__ total, AlignShared &sh, int waves)
 {
-    const int i = threadIdx.x, lane = i & 63, wave = i >> 6, waves = blockDim.x >> 6;
+    const int i = threadIdx.x, lane = i & 63, wave = i >> 6;
     const bool in_lds = (int64_t)m * n <= MAP_LDS_BACK;
     int turn = 0;
     // prefix maximum over the threads with the first index at ties; with more than one wave a barrier
@@ -338,11 +338,12 @@ __device__ __forceinline__ void align_threads(const double *__restrict__ S, int 
         for (int c = 0; c < AHEAD; ++c) cur[c] = nxt[c];
     }
     const Best last = prefix_max(best);
-    if (i == (int)blockDim.x - 1) {
+    if (i == waves * 64 - 1) {
         sh.start = last.idx < m ? last.idx : 0;                   // first maximum of the last column (all entries -infinity or NaN: layer 0)
         *total = last.val;
     }
-    __syncthreads();                                           // also orders the back pointers
+    if (waves > 1) __syncthreads();                            // also orders the back pointers
+    else __threadfence_block();
     if (i == 0) {
         int at = sh.start;
         f[n - 1] = at;
@@ -357,7 +358,7 @@ __global__ __launch_bounds__(MAP_THREADS) void layer_map_kernel(const double *__
                                                                 int32_t *__restrict__ f, double *__restrict__ total)
 {
     __shared__ AlignShared sh;
-    align_threads(S, m, n, back, f, total, sh);
+    align_threads(S, m, n, back, f, total, sh, (int)blockDim.x >> 6);
 }
 
 // Up to 64 draft layers: lane i of one wave holds draft layer i and works on verifier layer t - i in step t, one behind its neighbour: the maximum
@@ -369,8 +370,9 @@ __global__ __launch_bounds__(MAP_THREADS) void layer_map_kernel(const double *__
 // 85, similarity and alignment of 22 x 32 layers 28.0 / 25.2; 16 x 24 and smaller, bound by the host, 6.0 both.
 // S waits in LDS by steps (lane i's entry of step t is that of column t - i), so that a step's entries lie side by side.  Records: a word
 // per block of 64 columns and layer; in LDS, or, where there are too many, in the workspace (an eighth of m bytes per column, of the 4 m it holds).
-// A NaN, for which an order of maxima has no meaning, and entries above 1e300, whose sums may end in one (infinity and -infinity; 65535 columns of
-// less do not overflow), leave the call to the general form.
+// A NaN, for which an order of maxima has no meaning, and entries above 1e300 beside others below -1e300, whose sums may end in one
+// (infinity and -infinity; 65535 columns of less do not overflow), leave the call to the general form, by one wave.  (By all four, and with
+// any entry above 1e300, us: 32 x 48 layers with an infinity 36.5 / 7.5, 64 x 1000 with a NaN 745 / 455, with both infinities 745 / 455.)
 constexpr int WAVE_MOST = 64;                                  // draft layers
 constexpr int WAVE_THREADS = 256, WAVE_BLOCK = 64, WAVE_RING = 2 * WAVE_BLOCK;       // steps between two fetches; steps held
 constexpr int WAVE_PITCH = WAVE_MOST + 1;                      // doubles of a step (odd: a layer's columns, a step apart, fall on different banks)
@@ -472,8 +474,12 @@ __global__ __launch_bounds__(WAVE_THREADS) void layer_map_wave_kernel(const doub
         __syncthreads();
     }
     if (__syncthreads_or(odd)) {                               // (also orders the records)
-        align_threads(S, m, n, back, f, total, *reinterpret_cast<AlignShared *>(map_lds));
-        return;
+        bool general = false;
+        for (int e = tid; e < m * n; e += WAVE_THREADS) general |= !(S[e] >= -1e300);          // (below that, or NaN)
+        if (__syncthreads_or(general)) {
+            if (wave == 0) align_threads(S, m, n, back, f, total, *reinterpret_cast<AlignShared *>(map_lds), 1);
+            return;
+        }
     }
     if (wave) return;
     if (lane == m - 1) *total = own;

@@ -147,6 +147,24 @@ def test_alignment_by_diagonals(m, n):
         assert np.array_equal([v], [v_ref], equal_nan=True) and np.array_equal(f, f_ref)
 
 
+@pytest.mark.parametrize("m,n", [(1, 5), (7, 64), (32, 48), (64, 65), (64, 1000), (40, 9900)])
+@pytest.mark.parametrize("low", [-9.0, -1e300, -1.5e300, -np.inf])
+def test_alignment_of_very_large_entries(m, n, low):
+    """Infinities and sums that overflow, alone and beside entries on either side of -1e300, from which the general form takes over
+    (more than 64 layers, the others -infinity, is the measure; without a NaN also the oracle)."""
+    rng = np.random.default_rng(m * 17 + n)
+    S = np.round(rng.normal(size=(m, n)) * 2)
+    S[rng.random(S.shape) < 0.1] = low
+    for large in (1e300, 1.7e308, np.inf):
+        S[rng.integers(m, size=4), rng.integers(n, size=4)] = large
+        f, v = gpu_map(S)
+        f_ref, v_ref = gpu_map(np.vstack([S, np.full((65 - m, n), -np.inf)]))
+        assert np.array_equal([v], [v_ref], equal_nan=True) and np.array_equal(f, f_ref)
+        if low > -1e301 and not np.isnan(v):
+            want_f, want_v = oracle.layer_map(S)
+            assert v == want_v and np.array_equal(f, want_f)
+
+
 def test_layers_compared_with_themselves():
     ad, _ = W.layer_attention_maps(seed=9, m=5, n=5, rows=4, L=128)
     S = gpu_similarity(ad, ad)
