@@ -161,7 +161,8 @@ def test_alignment_of_very_large_entries(m, n, low):
         f_ref, v_ref = gpu_map(np.vstack([S, np.full((65 - m, n), -np.inf)]))
         assert np.array_equal([v], [v_ref], equal_nan=True) and np.array_equal(f, f_ref)
         if low > -1e301 and not np.isnan(v):
-            want_f, want_v = oracle.layer_map(S)
+            with np.errstate(over="ignore"):
+                want_f, want_v = oracle.layer_map(S)
             assert v == want_v and np.array_equal(f, want_f)
 
 
